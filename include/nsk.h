@@ -107,7 +107,7 @@ int nsk_last_hip_error(void);
  *   NSK_POOL_GENERAL, NSK_REDUCE4, NSK_WH_NO_SPLIT   (set = that special kernel or variant is not chosen);
  *   NSK_HALO_WIDE_ALWAYS, NSK_STATS_ALWAYS          (set = chosen also where it does not pay);
  *   NSK_BIG_MIN_TILES, NSK_PW_MIN_ROWS, NSK_WIDE_MIN_ROWS = n   (size threshold of a special kernel);
- *   NSK_IGEMM_TILE = 1..3                           (tile shape of the generic kernel). */
+ *   NSK_IGEMM_TILE = 1..6                           (tile shape of the generic kernel, which then takes every plain layer). */
 void nsk_test_hooks_reload(void);
 
 /* Output extent of a convolution.  Host only.  NSK_ERR_BAD_DESC if the descriptor is invalid

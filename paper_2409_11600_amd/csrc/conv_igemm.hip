@@ -1,15 +1,15 @@
-// Implicit-GEMM convolution on the MFMA units of gfx950: the kernel behind conv forward and
-// backward-data (both are "gather a shifted activation tile, multiply by a packed filter").
+// Implicit-GEMM convolution on the MFMA units of gfx950: the dispatch of conv forward and backward-data to their kernels,
+// and the kernel for channel counts that no 16-byte load fits (both passes are "gather a shifted activation tile,
+// multiply by a packed filter").
 //
 // GEMM view (the forward pass of a convolution layer of the ResNet recipe the paper trains,
 // section "Experiments and Discussion"): rows m = output pixels, columns n = output channels,
-// reduction k = (filter tap, input channel).  In NHWC each tap is a contiguous run of channels,
-// so a k-tile is fetched with 16-byte loads and no im2col buffer ever exists in memory.
+// reduction k = (filter tap, input channel).  In NHWC each tap is a contiguous run of channels, and no im2col buffer
+// ever exists in memory.
 //
-// Work decomposition: 256 threads = 4 wavefronts per block, block tile BM x BN, k-tile of 64
-// bytes per row.  Tiles are staged through LDS (rows padded to 80 bytes so the 16-byte fragment
-// reads of 8 consecutive lanes cover all 32 banks once) with register prefetch of the next
-// k-tile and two LDS buffers, so one barrier per k-tile suffices.  Each wavefront owns a
+// The element-wise kernel: 256 threads = 4 wavefronts per block, block tile BM x BN, k-tile of 64 bytes per row, staged
+// through LDS (rows padded to 80 bytes so the 16-byte fragment reads of 8 consecutive lanes cover all 32 banks once) with
+// register prefetch of the next k-tile and two LDS buffers, so one barrier per k-tile suffices.  Each wavefront owns a
 // WM x WN sub-tile made of 32x32 MFMA accumulators.
 #include <stdlib.h>
 
@@ -41,7 +41,7 @@ template <typename Vec> __device__ inline Vec zero_vec()
 __device__ inline float to_float(float v) { return v; }
 __device__ inline float to_float(bf16_t v) { return (float)v; }
 
-template <typename T, int BM, int BN, int WM, int WN, int BKB, bool VECLOAD>
+template <typename T, int BM, int BN, int WM, int WN, int BKB>
 __global__ __launch_bounds__(256) void igemm_kernel(const IgemmArgs a)
 {
     typedef Traits<T> TR;
@@ -80,16 +80,11 @@ __global__ __launch_bounds__(256) void igemm_kernel(const IgemmArgs a)
     const T *__restrict__ src = (const T *)a.src;
     const T *__restrict__ wpk = (const T *)a.wpk;
 
-    // Each thread gathers the same rows in every k-tile: decode them once.  For the vector path the
-    // per-row state is a 32-bit byte offset of the row's base pixel and a bit mask of the taps that
-    // fall inside the image; a k-tile then costs one shift, one add and one select per load.  Loads go
-    // through buffer descriptors: an offset of ~0 is out of range and returns zeros without a branch.
+    // Each thread gathers the same rows in every k-tile: decode them once.
     const int kv = tid % VPR;  // which 16-byte vector of the k-tile row
     const int r0 = tid / VPR;  // row within a pass of RPP rows
     int a_img[A_PASSES], a_bh[A_PASSES], a_bw[A_PASSES];
     bool a_ok[A_PASSES];
-    unsigned a_base[A_PASSES];
-    unsigned long long a_mask[A_PASSES];
 #pragma unroll
     for (int u = 0; u < A_PASSES; ++u) {
         const int row = r0 + RPP * u;
@@ -104,92 +99,39 @@ __global__ __launch_bounds__(256) void igemm_kernel(const IgemmArgs a)
         a_img[u] = img * a.Hs;
         a_bh[u] = i * a.mult_h + a.add_h;
         a_bw[u] = j * a.mult_w + a.add_w;
-        a_base[u] = (unsigned)(((((long)a_img[u] + a_bh[u]) * a.Ws + a_bw[u]) * ld + src_c0) * (long)sizeof(T));
         if (kv == 0)
             out_off[row] = a_ok[u] ? (((long)img * a.Ho + (i * a.osh + a.oa)) * a.Wo + (j * a.osw + a.ob)) * a.Co + wrow0
                                    : -1L;
     }
     __syncthreads();
-    if (VECLOAD) {
-#pragma unroll
-        for (int u = 0; u < A_PASSES; ++u) {
-            unsigned long long mask = 0;
-            if (a_ok[u])
-                for (int t = 0; t < a.ntaps; ++t) {
-                    const int h = a_bh[u] + s_offh[t], w = a_bw[u] + s_offw[t];
-                    if ((unsigned)h < (unsigned)a.Hs && (unsigned)w < (unsigned)a.Ws) mask |= 1ull << t;
-                }
-            a_mask[u] = mask;
-        }
-    }
-    const __amdgpu_buffer_rsrc_t src_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.src, 0, a.src_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t wpk_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.wpk, 0, a.wpk_bytes, 0x00020000);
-
     Vec ra[A_PASSES], rb[B_PASSES];
-    int cur_tap = 0, cur_c = kv * VEC;  // position of this thread's vector inside (tap, channel)
-    if (VECLOAD) {
-        while (cur_c >= a.Cs && cur_tap < a.ntaps) {
-            cur_c -= a.Cs;
-            ++cur_tap;
-        }
-    }
-    unsigned b_row_off[B_PASSES];
-#pragma unroll
-    for (int u = 0; u < B_PASSES; ++u) {
-        const int row = r0 + RPP * u;
-        const int n = n0 + row;
-        b_row_off[u] = (row < BN && n < a.Ngemm) ? (unsigned)((wrow0 + n) * a.Ktot * (long)sizeof(T)) : ~0u;
-    }
 
     auto load_tile = [&](int kt) {
         const int kk = kt * BK + kv * VEC;
-        if (VECLOAD) {
-            const bool kok = kk < a.Ktot;
-            const int tap = kok ? cur_tap : 0;
-            const unsigned delta = (unsigned)((((int)s_offh[tap] * a.Ws + (int)s_offw[tap]) * ld + cur_c) * (int)sizeof(T));
+        // Element-wise gather for channel counts that are not a multiple of the vector width
+        // (the 3-channel image stem).
 #pragma unroll
-            for (int u = 0; u < A_PASSES; ++u) {
-                const bool ok = kok && ((a_mask[u] >> tap) & 1ull);
-                const unsigned off = ok ? a_base[u] + delta : ~0u;
-                ra[u] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(src_rsrc, off, 0, 0));
-            }
+        for (int u = 0; u < A_PASSES; ++u) ra[u] = zero_vec<Vec>();
 #pragma unroll
-            for (int u = 0; u < B_PASSES; ++u) {
-                const unsigned off = (kok && b_row_off[u] != ~0u) ? b_row_off[u] + (unsigned)(kk * (int)sizeof(T)) : ~0u;
-                rb[u] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(wpk_rsrc, off, 0, 0));
-            }
-            // advance to the next k-tile
-            cur_c += BK;
-            while (cur_c >= a.Cs && cur_tap < a.ntaps) {
-                cur_c -= a.Cs;
-                ++cur_tap;
-            }
-        } else {
-            // Element-wise gather for channel counts that are not a multiple of the vector width
-            // (the 3-channel image stem).
+        for (int u = 0; u < B_PASSES; ++u) rb[u] = zero_vec<Vec>();
 #pragma unroll
-            for (int u = 0; u < A_PASSES; ++u) ra[u] = zero_vec<Vec>();
+        for (int e = 0; e < VEC; ++e) {
+            const int k = kk + e;
+            if (k < a.Ktot) {
+                const int tap = k / a.Cs;
+                const int c = k - tap * a.Cs;
+                const int oh = s_offh[tap], ow = s_offw[tap];
 #pragma unroll
-            for (int u = 0; u < B_PASSES; ++u) rb[u] = zero_vec<Vec>();
+                for (int u = 0; u < A_PASSES; ++u) {
+                    const int h = a_bh[u] + oh, w = a_bw[u] + ow;
+                    const bool ok = a_ok[u] && (unsigned)h < (unsigned)a.Hs && (unsigned)w < (unsigned)a.Ws;
+                    if (ok) ra[u][e] = src[((long)(a_img[u] + h) * a.Ws + w) * ld + src_c0 + c];
+                }
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const int k = kk + e;
-                if (k < a.Ktot) {
-                    const int tap = k / a.Cs;
-                    const int c = k - tap * a.Cs;
-                    const int oh = s_offh[tap], ow = s_offw[tap];
-#pragma unroll
-                    for (int u = 0; u < A_PASSES; ++u) {
-                        const int h = a_bh[u] + oh, w = a_bw[u] + ow;
-                        const bool ok = a_ok[u] && (unsigned)h < (unsigned)a.Hs && (unsigned)w < (unsigned)a.Ws;
-                        if (ok) ra[u][e] = src[((long)(a_img[u] + h) * a.Ws + w) * ld + src_c0 + c];
-                    }
-#pragma unroll
-                    for (int u = 0; u < B_PASSES; ++u) {
-                        const int row = r0 + RPP * u;
-                        const int n = n0 + row;
-                        if (row < BN && n < a.Ngemm) rb[u][e] = wpk[(wrow0 + n) * a.Ktot + k];
-                    }
+                for (int u = 0; u < B_PASSES; ++u) {
+                    const int row = r0 + RPP * u;
+                    const int n = n0 + row;
+                    if (row < BN && n < a.Ngemm) rb[u][e] = wpk[(wrow0 + n) * a.Ktot + k];
                 }
             }
         }
@@ -367,23 +309,22 @@ __global__ __launch_bounds__(256) void igemm_kernel(const IgemmArgs a)
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int BKB>
-int launch_tile(const IgemmArgs &a, bool vec, hipStream_t stream)
+int launch_tile(const IgemmArgs &a, hipStream_t stream)
 {
     dim3 grid(ceil_div(a.M, BM), ceil_div(a.Ngemm, BN), a.groups);
-    if (vec)
-        hipLaunchKernelGGL((igemm_kernel<T, BM, BN, WM, WN, BKB, true>), grid, dim3(256), 0, stream, a);
-    else
-        hipLaunchKernelGGL((igemm_kernel<T, BM, BN, WM, WN, 64, false>), grid, dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((igemm_kernel<T, BM, BN, WM, WN, BKB>), grid, dim3(256), 0, stream, a);
     return check_launch();
 }
 
-// NSK_IGEMM_TILE=<n> forces a tile variant (A/B experiments); unset or 0 = automatic choice.
-int forced_tile()
+// Channel runs and filter rows on 16-byte boundaries: the pipelined kernel takes the launch.  (For a grouped launch
+// Cs % VEC == 0 also puts every group's channel run and filter rows on such boundaries.)
+bool vector_runs(int dtype, const IgemmArgs &a)
 {
-    return hooks().igemm_tile;
+    const int vec = dtype == NSK_BF16 ? 8 : 4, ld = a.groups > 1 ? a.src_ld : a.Cs;
+    return a.Cs % vec == 0 && ld % vec == 0 && a.Ktot % vec == 0 && ((uintptr_t)a.src % 16 == 0) && ((uintptr_t)a.wpk % 16 == 0);
 }
 
-// Automatic tile choice: 0 = 256x32 (64-row wavefront tiles), 1 = 128x64 (32-row), 2 = 128x128 (64-row).
+// Tile of the element-wise kernel: 0 = 256x32 (64-row wavefront tiles), 1 = 128x64 (32-row), 2 = 128x128 (64-row).
 int auto_tile(const IgemmArgs &a, int es)
 {
     if (a.Ngemm <= 32) return 0;
@@ -394,26 +335,12 @@ int auto_tile(const IgemmArgs &a, int es)
 
 template <typename T> int launch_typed(const IgemmArgs &a, hipStream_t stream)
 {
-    constexpr int VEC = Traits<T>::VEC;
-    // (for a grouped launch Cs % VEC == 0 also puts every group's channel run and filter rows on 16-byte boundaries)
-    const bool vec = a.Cs % VEC == 0 && a.src_ld % VEC == 0 && a.Ktot % VEC == 0 && ((uintptr_t)a.src % 16 == 0) &&
-                     ((uintptr_t)a.wpk % 16 == 0);
-    switch (forced_tile()) {
-    case 1: return launch_tile<T, 256, 64, 64, 64, 64>(a, vec, stream);
-    case 2: return launch_tile<T, 256, 64, 64, 64, 128>(a, vec, stream);
-    case 3: return launch_tile<T, 128, 64, 32, 64, 64>(a, vec, stream);
-    case 4: return launch_tile<T, 128, 64, 32, 64, 128>(a, vec, stream);
-    case 5: return launch_tile<T, 128, 128, 64, 64, 64>(a, vec, stream);
-    case 6: return launch_tile<T, 128, 128, 64, 64, 128>(a, vec, stream);
-    default: break;
-    }
     // Measured on MI355X: with 64 or fewer columns the 128-row tile wins (more blocks in flight hide
-    // the per-block prologue and epilogue); wide problems with a long reduction take 128x128 tiles
-    // with 128-byte k-tiles (half as many barriers).
+    // the per-block prologue and epilogue); wide problems with a long reduction take 128x128 tiles.
     switch (auto_tile(a, (int)sizeof(T))) {
-    case 0: return launch_tile<T, 256, 32, 64, 32, 64>(a, vec, stream);
-    case 1: return launch_tile<T, 128, 64, 32, 64, 64>(a, vec, stream);
-    default: return launch_tile<T, 128, 128, 64, 64, 128>(a, vec, stream);
+    case 0: return launch_tile<T, 256, 32, 64, 32, 64>(a, stream);
+    case 1: return launch_tile<T, 128, 64, 32, 64, 64>(a, stream);
+    default: return launch_tile<T, 128, 128, 64, 64, 64>(a, stream);
     }
 }
 
@@ -423,15 +350,18 @@ int igemm_stats_rows(int dtype, const IgemmArgs &a)
 {
     // the same order of tests as launch_igemm
     if (a.M <= 0 || a.Ngemm <= 0 || a.accumulate) return 0;
-    if (forced_tile() != 0 || a.groups > 1) return 0;
-    if (tiny_src_applicable(dtype, a) || tiny_out_applicable(dtype, a)) return 0;   // no statistics epilogue there
-    if (halo64_applicable(dtype, a)) return halo64_stats_rows(a);
-    if (halo64_f32_applicable(dtype, a)) return halo64_f32_stats_rows(a);
-    if (fs64_fwd_s2_applicable(dtype, a)) return fs64_fwd_s2_stats_rows(a);
-    if (conv_pw_applicable(dtype, a)) return conv_pw_stats_rows(a);
-    if (halo_wide_applicable(dtype, a)) return halo_wide_stats_rows(a);
-    if (halo_wide_fwd_s2_applicable(dtype, a)) return halo_wide_fwd_s2_stats_rows(a);
-    if (igemm_big_applicable(dtype, a)) return igemm_big_stats_rows(a);
+    if (a.groups > 1) return 0;
+    const bool special = hooks().igemm_tile == 0;
+    if (special) {
+        if (tiny_src_applicable(dtype, a) || tiny_out_applicable(dtype, a)) return 0;   // no statistics epilogue there
+        if (halo64_applicable(dtype, a)) return halo64_stats_rows(a);
+        if (halo64_f32_applicable(dtype, a)) return halo64_f32_stats_rows(a);
+        if (fs64_fwd_s2_applicable(dtype, a)) return fs64_fwd_s2_stats_rows(a);
+        if (conv_pw_applicable(dtype, a)) return conv_pw_stats_rows(a);
+        if (halo_wide_applicable(dtype, a)) return halo_wide_stats_rows(a);
+        if (halo_wide_fwd_s2_applicable(dtype, a)) return halo_wide_fwd_s2_stats_rows(a);
+        if (igemm_big_applicable(dtype, a)) return igemm_big_stats_rows(a);
+    }
     // generic kernel: needs the vector epilogue; one row per wavefront row of every row block.  Measured: with a
     // short reduction the per-block cross-lane sums and the many rows of partial sums cost more than the separate
     // statistics pass they replace (config 5 stage A: +45 us on a 140 us layer), so only long reductions use it.
@@ -439,6 +369,7 @@ int igemm_stats_rows(int dtype, const IgemmArgs &a)
     if (!(a.Ngemm % vec == 0 && a.Co % vec == 0 && (uintptr_t)a.out % 16 == 0)) return 0;
     if (a.Ktot < 1024 && !hooks().stats_always) return 0;   // the variable is a test hook
     if (a.Ngemm % 4 != 0) return 0;   // 16-byte stores of the partial sums
+    if (vector_runs(dtype, a)) return igemm_pipe_stats_rows(dtype, a);
     static const int bm[3] = {256, 128, 128}, wm[3] = {64, 32, 64};
     const int t = auto_tile(a, dtype == NSK_BF16 ? 2 : 4);
     return ceil_div(a.M, bm[t]) * (bm[t] / wm[t]);
@@ -447,7 +378,7 @@ int igemm_stats_rows(int dtype, const IgemmArgs &a)
 bool igemm_act_fused(int dtype, const IgemmArgs &a)
 {
     // the same order of tests as launch_igemm, up to the kernels that have the fused load
-    if (a.M <= 0 || a.Ngemm <= 0 || a.accumulate || a.groups > 1 || a.zero_cell || forced_tile() != 0) return false;
+    if (a.M <= 0 || a.Ngemm <= 0 || a.accumulate || a.groups > 1 || a.zero_cell || hooks().igemm_tile != 0) return false;
     if (tiny_src_applicable(dtype, a) || tiny_out_applicable(dtype, a) || halo64_applicable(dtype, a)) return false;
     return halo64_f32_applicable(dtype, a);
 }
@@ -459,7 +390,7 @@ int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream)
     const bool grouped = a.groups > 1;   // only the generic kernel knows about groups
     if (grouped && (a.groups > 65535 || a.src_ld != a.groups * a.Cs || a.zero_cell || a.stats)) return NSK_ERR_BAD_DESC;
     if (a.zero_cell) return launch_conv_pw(a, stream);   // the caller has checked that this kernel applies
-    const bool special = forced_tile() == 0 && !grouped;
+    const bool special = hooks().igemm_tile == 0 && !grouped;   // (the variable is a test hook)
     if (special && tiny_src_applicable(dtype, a)) return launch_tiny_src(dtype, a, stream);
     if (special && tiny_out_applicable(dtype, a)) return launch_tiny_out(dtype, a, stream);
     if (special && halo64_applicable(dtype, a)) return launch_halo64(a, stream);
@@ -469,7 +400,7 @@ int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream)
     if (special && halo_wide_applicable(dtype, a)) return launch_halo_wide(a, stream);
     if (special && halo_wide_fwd_s2_applicable(dtype, a)) return launch_halo_wide_fwd_s2(a, stream);
     if (special && igemm_big_applicable(dtype, a)) return launch_igemm_big(a, stream);
-    if (grouped && forced_tile() == 0 && !hooks().no_depthwise && depthwise_applicable(dtype, a))
+    if (grouped && hooks().igemm_tile == 0 && !hooks().no_depthwise && depthwise_applicable(dtype, a))
         return launch_depthwise(dtype, a, stream);
     IgemmArgs b = a;
     if (!grouped) {
@@ -478,6 +409,7 @@ int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream)
     }
     const int vec = dtype == NSK_BF16 ? 8 : 4;
     b.vec_out = (b.Ngemm % vec == 0 && b.Co % vec == 0 && (uintptr_t)b.out % 16 == 0) ? 1 : 0;
+    if (vector_runs(dtype, b)) return launch_igemm_pipe(dtype, b, stream);
     return dtype == NSK_BF16 ? launch_typed<bf16_t>(b, stream) : launch_typed<float>(b, stream);
 }
 

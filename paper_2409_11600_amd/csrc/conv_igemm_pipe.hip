@@ -1,0 +1,477 @@
+// Implicit-GEMM convolution for every layer without a kernel of its own whose channel runs are 16-byte granular
+// (forward, backward-data, grouped launches; fp32 and bf16): the pipelined tile kernel.
+//
+// GEMM view: rows m = output pixels, columns n = output channels, reduction k = (filter tap, input channel).
+//
+// What bounds it: a k-tile is 128 bytes of the reduction index for BM + BN rows.  With one k-tile in flight per block
+// (register prefetch, one barrier) a 128 x 128 bf16 tile took 2000 clocks per k-tile, of which the matrix units need
+// 512: the rest was the latency of the loads, because layers with few output pixels (7x7 images) give a CU one block
+// only.  Here the operands go from memory straight into LDS (16 bytes per lane, no registers), ST k-tiles deep, and a
+// k-tile costs one counted wait and one barrier.
+//
+// Layout in LDS: rows of 128 bytes, the eight 16-byte pieces of row r stored at piece ^ ((r >> 1) & 7), so that the
+// sixteen rows a fragment read serves at once cover all 64 banks.  A direct load writes 64 consecutive 16-byte slots
+// (eight rows), so the exchange is made in the source address: a lane always fetches the same piece of its rows.
+//
+// Small problems: the block's four wavefronts are WM x WN x WK; with WK > 1 the wavefronts of a group multiply
+// different parts of each k-tile and their sums are added through LDS in a fixed order, so that a 32 x 32 tile still
+// keeps four wavefronts busy.
+//
+// Measured against the one-tile-ahead kernel (us, forward): bf16 3x3 512->512 at 7x7, N=64 77.7 -> 27.2; fp32 3x3 72->100
+// at 29x37, N=20 80.8 -> 43.9; fp32 3x3 16->16 at 32x32, N=8 16.8 -> 5.7.  Without the exchange of pieces the first takes
+// 64 us (bank conflicts).
+#include <limits.h>
+
+#include "nsk_internal.h"
+
+namespace nsk {
+namespace {
+
+template <typename T> struct PipeTraits;
+template <> struct PipeTraits<float> {
+    static constexpr int VEC = 4;
+    typedef f32x4 Vec;
+};
+template <> struct PipeTraits<bf16_t> {
+    static constexpr int VEC = 8;
+    typedef bf16x8 Vec;
+};
+
+__device__ inline float to_f(float v) { return v; }
+__device__ inline float to_f(bf16_t v) { return (float)v; }
+
+typedef __attribute__((address_space(3))) void lds_void;
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int PK_BYTES = 128;   // bytes of reduction index per k-tile row
+
+// s_waitcnt vmcnt(n) alone
+template <int N> __device__ inline void wait_vm()
+{
+    static_assert(N >= 0 && N < 64, "six-bit counter");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int WK, int ST>
+__global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const IgemmArgs a, int tiles_m, int tiles_n)
+{
+    typedef typename PipeTraits<T>::Vec Vec;
+    constexpr int VEC = PipeTraits<T>::VEC, ES = (int)sizeof(T), BK = PK_BYTES / ES;
+    constexpr int NW = WM * WN * WK;                    // wavefronts per block
+    static_assert((NW == 4 || NW == 8) && BM <= 64 * NW, "four or eight wavefronts per block");
+    constexpr int FM = BM / WM / 32, FN = BN / WN / 32;
+    constexpr int RA = BM / 8 / NW, RB = BN / 8 / NW;           // direct loads per wavefront and k-tile (eight rows each)
+    constexpr int LOADS = RA + RB;
+    constexpr int TA = BM * PK_BYTES, TB = BN * PK_BYTES;
+    constexpr int SROW = 32 * ES + 16;                  // epilogue: staged bytes per pixel (padded)
+    constexpr int EPI = NW * 32 * SROW + (WK > 1 ? 3 * FM * FN * 4096 : 0);
+    constexpr int TA0 = TA > EPI ? TA : EPI;
+    static_assert(ST == 3 || ST == 4, "stages");
+
+    // one variable per stage and operand: the compiler keeps the reads of one apart from the direct loads into the others
+    __shared__ __attribute__((aligned(1024))) unsigned char sa0[TA0], sa1[TA], sa2[TA], sa3[ST == 4 ? TA : 16];
+    __shared__ __attribute__((aligned(1024))) unsigned char sb0[TB], sb1[TB], sb2[TB], sb3[ST == 4 ? TB : 16];
+    __shared__ unsigned s_base[BM], s_out[BM];   // byte offsets of a row's base pixel in src and of its pixel in out (~0: none)
+    __shared__ int s_bh[BM], s_bw[BM];
+    __shared__ int s_oh[kMaxTaps], s_ow[kMaxTaps];
+    __shared__ unsigned s_delta[kMaxTaps];
+#define NSK_STAGE(S, P) ((S) == 0 ? P##0 : (S) == 1 ? P##1 : (S) == 2 ? P##2 : P##3)
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave % WK, wn = (wave / WK) % WN, wm = wave / (WK * WN);
+
+    // Tiles of one row block on one XCD, next to each other (blocks go to the eight XCDs in turn): its L2 then holds
+    // the activation rows they share.
+    int bm, bn;
+    {
+        const int total = tiles_m * tiles_n, x = blockIdx.x & 7, i = blockIdx.x >> 3;
+        const int q = total >> 3, r = total & 7;
+        const int t = x * q + min(x, r) + i;
+        bm = t / tiles_n;
+        bn = t - bm * tiles_n;
+    }
+    const int m0 = bm * BM, n0 = bn * BN;
+    const int grp = blockIdx.z, ld = a.src_ld;
+    const int src_c0 = grp * a.Cs;
+    const long wrow0 = (long)grp * a.Ngemm;
+
+    if (tid < kMaxTaps) {
+        const int oh = a.off_h[tid], ow = a.off_w[tid];
+        s_oh[tid] = oh;
+        s_ow[tid] = ow;
+        s_delta[tid] = (unsigned)((oh * a.Ws + ow) * ld * ES);
+    }
+    if (tid < BM) {
+        const int m = m0 + tid, per_img = a.Mi * a.Mj;
+        const int img = m / per_img, rem = m - img * per_img, i = rem / a.Mj, j = rem - i * a.Mj;
+        const int bh = i * a.mult_h + a.add_h, bw = j * a.mult_w + a.add_w;
+        s_bh[tid] = m < a.M ? bh : INT_MIN / 2;      // (no tap brings such a row into the image)
+        s_bw[tid] = bw;
+        s_base[tid] = (unsigned)(((((long)img * a.Hs + bh) * a.Ws + bw) * ld + src_c0) * (long)ES);
+        s_out[tid] = m < a.M ? (unsigned)(((((long)img * a.Ho + (i * a.osh + a.oa)) * a.Wo + (j * a.osw + a.ob)) * a.Co + wrow0) * ES)
+                             : ~0u;
+    }
+    __syncthreads();
+
+    // This lane's rows of the activation tile: byte offset of the row's base pixel and one validity bit per tap.
+    const int lr = lane >> 3;
+        const int piece = (lane & 7) ^ ((wave & 1) * 4 + (lr >> 1));
+    unsigned a_base[RA];
+    unsigned long long a_mask[RA];
+    {
+        int bh[RA], bw[RA];
+#pragma unroll
+        for (int u = 0; u < RA; ++u) {
+            const int row = 8 * (wave + NW * u) + lr;
+            a_base[u] = s_base[row];
+            bh[u] = s_bh[row];
+            bw[u] = s_bw[row];
+            a_mask[u] = 0;
+        }
+#pragma unroll 1
+        for (int t = 0; t < a.ntaps; ++t) {
+            const int oh = s_oh[t], ow = s_ow[t];
+#pragma unroll
+            for (int u = 0; u < RA; ++u) {
+                const bool in = (unsigned)(bh[u] + oh) < (unsigned)a.Hs & (unsigned)(bw[u] + ow) < (unsigned)a.Ws;
+                a_mask[u] |= (unsigned long long)in << t;
+            }
+        }
+    }
+    unsigned b_row[RB], b_bad[RB];
+#pragma unroll
+    for (int u = 0; u < RB; ++u) {
+        const int n = n0 + 8 * (wave + NW * u) + lr;
+        b_row[u] = (unsigned)((wrow0 + n) * a.Ktot * (long)ES) + (unsigned)(piece * 16);
+        b_bad[u] = n < a.Ngemm ? 0u : ~0u;
+    }
+    const __amdgpu_buffer_rsrc_t src_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.src, 0, a.src_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wpk_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.wpk, 0, a.wpk_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t out_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        a.out, 0, (unsigned)((long)a.Nimg * a.Ho * a.Wo * a.Co * ES), 0x00020000);
+
+    // position of this lane's piece inside (tap, channel), of the next k-tile to be requested; a k-tile further is
+    // q_tap taps and r_c channels
+    const int q_tap = BK / a.Cs, r_c = BK - q_tap * a.Cs;
+    int cur_tap = piece * VEC / a.Cs, cur_c = piece * VEC - cur_tap * a.Cs;
+    // Offsets are made out of range (reads: zeros, writes: dropped) with bit operations: a branch around a direct load
+    // would split it in two.
+    auto request = [&](auto S) {
+        constexpr int I = S.value;
+        const unsigned k_bad = (unsigned)((a.ntaps - 1 - cur_tap) >> 31);
+        const int tap = cur_tap & (kMaxTaps - 1);
+        const unsigned delta = s_delta[tap] + (unsigned)(cur_c * ES);
+#pragma unroll
+        for (int u = 0; u < RA; ++u) {
+            const unsigned bad = ((unsigned)(a_mask[u] >> tap) & 1u) - 1u;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(src_rsrc, (lds_void *)&NSK_STAGE(I, sa)[(wave + NW * u) * 1024], 16,
+                                                     (int)((a_base[u] + delta) | bad | k_bad), 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < RB; ++u) {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wpk_rsrc, (lds_void *)&NSK_STAGE(I, sb)[(wave + NW * u) * 1024], 16,
+                                                     (int)(b_row[u] | b_bad[u] | k_bad), 0, 0, 0);
+            b_row[u] += PK_BYTES;
+        }
+        cur_c += r_c;
+        cur_tap += q_tap;
+        const bool wrap = cur_c >= a.Cs;
+        cur_c -= wrap ? a.Cs : 0;
+        cur_tap += wrap ? 1 : 0;
+    };
+
+    // The filter rows are the MFMA "A" operand and the pixels the "B" operand, so a lane ends up with 4 consecutive
+    // channels of one pixel per accumulator quad: acc[mi][ni][4g+j] is channel 32*ni + 8*g + 4*(lane/32) + j of pixel
+    // 32*mi + lane%32 of the wavefront's sub-tile.
+    const int frow = lane & 31, fk = lane >> 5,  fsw = (frow >> 1) & 7;
+    T *__restrict__ out = (T *)a.out;
+    const int wcol0 = n0 + wn * (FN * 32), wrow = wm * (FM * 32);
+    f32x16 acc[FM][FN];
+#pragma unroll
+    for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
+    if (a.accumulate && a.vec_out && wk == 0) {
+        // start from the old values: the sum is then rounded to the storage type exactly once
+#pragma unroll
+        for (int mi = 0; mi < FM; ++mi) {
+            const unsigned off = s_out[wrow + mi * 32 + frow], off_bad = off == ~0u ? ~0u : 0u;
+#pragma unroll
+            for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int col = wcol0 + ni * 32 + g * 8 + fk * 4;
+                    const int at = (int)((off + (unsigned)(col * ES)) | off_bad | (col < a.Ngemm ? 0u : ~0u));
+                    if constexpr (ES == 2) {
+                        const bf16x4 v = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(out_rsrc, at, 0, 0));
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) acc[mi][ni][g * 4 + j] = (float)v[j];
+                    } else {
+                        const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(out_rsrc, at, 0, 0));
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) acc[mi][ni][g * 4 + j] = v[j];
+                    }
+                }
+        }
+    }
+
+    const int nk = (a.Ktot + BK - 1) / BK;
+    static_for<0, ST - 1>([&](auto S) { request(S); });   // (k-tiles past the end are requested out of range: zeros)
+    auto multiply = [&](auto S) {
+        constexpr int I = S.value;
+        const int oa = (wrow + frow) * PK_BYTES, ob = (wn * (FN * 32) + frow) * PK_BYTES;
+#pragma unroll
+        for (int i = 0; i < 4 / WK; ++i) {
+            const int ks = wk * (4 / WK) + i, at = (((ks * 2 + fk) ^ fsw) * 16);
+            Vec af[FM], bfv[FN];
+#pragma unroll
+            for (int mi = 0; mi < FM; ++mi) af[mi] = *(const Vec *)&NSK_STAGE(I, sa)[oa + at + mi * 32 * PK_BYTES];
+#pragma unroll
+            for (int ni = 0; ni < FN; ++ni) bfv[ni] = *(const Vec *)&NSK_STAGE(I, sb)[ob + at + ni * 32 * PK_BYTES];
+            if constexpr (ES == 2) {
+#pragma unroll
+                for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < FN; ++ni)
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfv[ni], af[mi], acc[mi][ni], 0, 0, 0);
+            } else {
+                // lane (row, half) holds k = 4*half + t of this group of 8, the same map for both operands
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+                        for (int ni = 0; ni < FN; ++ni)
+                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(bfv[ni][t], af[mi][t], acc[mi][ni], 0, 0, 0);
+            }
+        }
+    };
+    // The loop body is ST steps without a branch, the remainder follows: where a step could leave the loop, the compiler
+    // would take the stage requested last for one that the first step reads, and wait for it.
+#define NSK_STEP(S)                                                                                              \
+    wait_vm<(ST - 2) * LOADS>();  /* this wavefront's part of the k-tile has arrived */                          \
+    __builtin_amdgcn_s_barrier(); /* everybody's has, and nobody reads the stage requested next any more */      \
+    asm volatile("" ::: "memory");                                                                               \
+    request(std::integral_constant<int, ((S) + ST - 1) % ST>{});                                                 \
+    multiply(std::integral_constant<int, (S)>{});
+    for (int n = nk / ST; n > 0; --n) {
+        NSK_STEP(0)
+        NSK_STEP(1)
+        NSK_STEP(2)
+        if constexpr (ST == 4) {
+            NSK_STEP(3)
+        }
+    }
+#undef NSK_STEP
+    // (the last ST - 1 k-tiles have been requested; what the loop requested past the end were zeros)
+#define NSK_REST(S)                             \
+    wait_vm<(ST - 2 - (S)) * LOADS>();          \
+    __builtin_amdgcn_s_barrier();               \
+    asm volatile("" ::: "memory");              \
+    multiply(std::integral_constant<int, (S)>{});
+    const int rest = nk % ST;
+    if (rest > 0) {
+        NSK_REST(0)
+    }
+    if (rest > 1) {
+        NSK_REST(1)
+    }
+    if constexpr (ST == 4) {
+        if (rest > 2) {
+            NSK_REST(2)
+        }
+    }
+#undef NSK_REST
+    wait_vm<0>();          // (requests past the end still write zeros into LDS)
+    __syncthreads();
+
+    if constexpr (WK > 1) {
+        // add the wavefronts of a group in a fixed order
+        float *red = (float *)(sa0 + NW * 32 * SROW);
+        const int slot = (wm * WN + wn) * (WK - 1);
+        if (wk > 0) {
+#pragma unroll
+            for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+                    for (int v = 0; v < 16; v += 4)
+                        *(f32x4 *)(red + ((((slot + wk - 1) * FM + mi) * FN + ni) * 4 + v / 4) * 256 + lane * 4) =
+                            f32x4{acc[mi][ni][v], acc[mi][ni][v + 1], acc[mi][ni][v + 2], acc[mi][ni][v + 3]};
+        }
+        __syncthreads();
+        if (wk > 0) return;
+#pragma unroll
+        for (int w = 1; w < WK; ++w)
+#pragma unroll
+            for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+                    for (int v = 0; v < 16; v += 4) {
+                        const f32x4 p = *(const f32x4 *)(red + ((((slot + w - 1) * FM + mi) * FN + ni) * 4 + v / 4) * 256 + lane * 4);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) acc[mi][ni][v + j] += p[j];
+                    }
+    }
+
+    if (a.vec_out) {
+        // Round to the storage type, transpose one 32 x 32 accumulator tile at a time through this wavefront's strip of
+        // the (now idle) first stage, and store 16 contiguous bytes per lane.
+        typedef T T4 __attribute__((ext_vector_type(4)));
+        constexpr int CPP = 32 * ES / 16;               // 16-byte chunks per pixel
+        unsigned char *my_st = sa0 + wave * (32 * SROW);
+        // Statistics epilogue (forward with a batch-norm behind it): a lane always reads back the same 16-byte piece
+        // (VEC channels) of each staged row, so it adds those channels up over all the rows it stores; one cross-lane
+        // reduction per block and one row of partial sums per wavefront row.
+        float ssum[FN][VEC], ssq[FN][VEC];
+#pragma unroll
+        for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) ssum[ni][e] = ssq[ni][e] = 0.f;
+#pragma unroll
+        for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < FN; ++ni) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    T4 pk;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) pk[j] = (T)acc[mi][ni][g * 4 + j];
+                    *(T4 *)(my_st + frow * SROW + (g * 8 + fk * 4) * ES) = pk;
+                }
+#pragma unroll
+                for (int jj = 0; jj < 32 * CPP / 64; ++jj) {
+                    const int idx = lane + 64 * jj, pos = idx / CPP, ck = idx % CPP;
+                    const Vec v = *(const Vec *)(my_st + pos * SROW + ck * 16);
+                    const unsigned off = s_out[wrow + mi * 32 + pos];
+                    const int col = wcol0 + ni * 32 + ck * VEC;
+                    const unsigned bad = (off == ~0u ? ~0u : 0u) | (col < a.Ngemm ? 0u : ~0u);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out_rsrc, (int)((off + (unsigned)(col * ES)) | bad), 0, 0);
+                    if (a.stats) {
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) {
+                            const float f = bad ? 0.f : to_f(v[e]);
+                            ssum[ni][e] += f;
+                            ssq[ni][e] += f * f;
+                        }
+                    }
+                }
+            }
+        if (a.stats) {
+            const int row = bm * WM + wm, ck = lane % CPP;
+#pragma unroll
+            for (int ni = 0; ni < FN; ++ni) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e)
+#pragma unroll
+                    for (int o = CPP; o < 64; o <<= 1) {
+                        ssum[ni][e] += __shfl_xor(ssum[ni][e], o, 64);
+                        ssq[ni][e] += __shfl_xor(ssq[ni][e], o, 64);
+                    }
+                const int col = wcol0 + ni * 32 + ck * VEC;
+                if (lane < CPP && col < a.Ngemm) {
+                    // 16-byte stores: a handful of lanes writing single floats would cost one memory instruction each
+                    float *r0 = a.stats + (size_t)row * a.Ngemm + col;
+                    float *r1 = r0 + (size_t)a.stats_rows * a.Ngemm;
+#pragma unroll
+                    for (int e = 0; e < VEC; e += 4) {
+                        *(f32x4 *)(r0 + e) = f32x4{ssum[ni][e], ssum[ni][e + 1], ssum[ni][e + 2], ssum[ni][e + 3]};
+                        *(f32x4 *)(r1 + e) = f32x4{ssq[ni][e], ssq[ni][e + 1], ssq[ni][e + 2], ssq[ni][e + 3]};
+                    }
+                }
+            }
+        }
+    } else {
+        // element-wise stores (output rows that are not 16-byte granular)
+#pragma unroll
+        for (int mi = 0; mi < FM; ++mi) {
+            const unsigned off_b = s_out[wrow + mi * 32 + frow];
+            if (off_b == ~0u) continue;
+            const long off = off_b / ES;
+#pragma unroll
+            for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int col = wcol0 + ni * 32 + 8 * (v >> 2) + 4 * fk + (v & 3);
+                    if (col < a.Ngemm) {
+                        float r = acc[mi][ni][v];
+                        if (a.accumulate) r += to_f(out[off + col]);
+                        out[off + col] = (T)r;
+                    }
+                }
+        }
+    }
+}
+
+// Tile shapes with what a k-tile and the rest of a block cost in shader clocks, measured (31 problems, both types).  bf16
+// is bound by the fill of LDS: eight wavefronts per block bring 38-42 B/clk into a CU, four only 31, so all bf16 shapes
+// but the narrowest have eight.  fp32 is bound by the matrix units (256 clocks per 32 x 32 and k-tile), so there small
+// tiles, which spread evenly over the CUs, win throughout.
+struct PipeTile {
+    int bm, bn, wm;          // wm: wavefront rows = rows of statistics per tile
+    double step, rest;
+};
+constexpr PipeTile kTilesBf16[] = {{256, 128, 4, 1300, 16000}, {128, 128, 2, 830, 9000}, {256, 64, 4, 1000, 8500},
+                                   {128, 64, 4, 700, 5000},    {64, 64, 2, 400, 3000},   {128, 32, 4, 550, 3000}};
+constexpr PipeTile kTilesF32[] = {{64, 64, 2, 1150, 3000}, {128, 32, 4, 1150, 3000}, {64, 32, 2, 580, 2000}, {32, 32, 1, 290, 1500}};
+
+template <int N> int cheapest(const PipeTile (&tiles)[N], int es, const IgemmArgs &a)
+{
+    const int forced = hooks().igemm_tile;   // NSK_IGEMM_TILE = 1.. (test hook)
+    if (forced >= 1) return (forced - 1) % N;
+    const int groups = a.groups > 1 ? a.groups : 1;
+    const double nk = (double)(((long)a.Ktot * es + PK_BYTES - 1) / PK_BYTES);
+    int best = 0;
+    double best_cost = 0;
+    for (int i = 0; i < N; ++i) {
+        const long blocks = (long)ceil_div(a.M, tiles[i].bm) * ceil_div(a.Ngemm, tiles[i].bn) * groups;
+        const double cost = (double)((blocks + 255) / 256) * (nk * tiles[i].step + tiles[i].rest);   // 256 CUs
+        if (i == 0 || cost < best_cost) {
+            best = i;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int WK, int ST> int launch(const IgemmArgs &a, hipStream_t stream)
+{
+    const int tm = ceil_div(a.M, BM), tn = ceil_div(a.Ngemm, BN);
+    hipLaunchKernelGGL((igemm_pipe_kernel<T, BM, BN, WM, WN, WK, ST>), dim3((unsigned)tm * tn, 1, a.groups),
+                       dim3(64 * WM * WN * WK), 0, stream, a, tm, tn);
+    return check_launch();
+}
+
+}  // namespace
+
+// groups, src_ld and vec_out are set; the caller has checked that channel runs are 16-byte granular
+int launch_igemm_pipe(int dtype, const IgemmArgs &a, hipStream_t stream)
+{
+    if (dtype == NSK_BF16) {
+        switch (cheapest(kTilesBf16, 2, a)) {
+        case 0: return launch<bf16_t, 256, 128, 4, 2, 1, 3>(a, stream);
+        case 1: return launch<bf16_t, 128, 128, 2, 4, 1, 4>(a, stream);
+        case 2: return launch<bf16_t, 256, 64, 4, 2, 1, 3>(a, stream);
+        case 3: return launch<bf16_t, 128, 64, 4, 2, 1, 4>(a, stream);
+        case 4: return launch<bf16_t, 64, 64, 2, 2, 2, 3>(a, stream);
+        default: return launch<bf16_t, 128, 32, 4, 1, 1, 3>(a, stream);
+        }
+    }
+    switch (cheapest(kTilesF32, 4, a)) {
+    case 0: return launch<float, 64, 64, 2, 2, 1, 4>(a, stream);
+    case 1: return launch<float, 128, 32, 4, 1, 1, 3>(a, stream);
+    case 2: return launch<float, 64, 32, 2, 1, 2, 4>(a, stream);
+    default: return launch<float, 32, 32, 1, 1, 4, 4>(a, stream);
+    }
+}
+
+int igemm_pipe_stats_rows(int dtype, const IgemmArgs &a)
+{
+    const PipeTile &t = dtype == NSK_BF16 ? kTilesBf16[cheapest(kTilesBf16, 2, a)] : kTilesF32[cheapest(kTilesF32, 4, a)];
+    return ceil_div(a.M, t.bm) * t.wm;
+}
+
+}  // namespace nsk

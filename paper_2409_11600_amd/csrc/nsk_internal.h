@@ -123,6 +123,9 @@ bool igemm_act_fused(int dtype, const IgemmArgs &a);
 // Rows of partial sums the kernel launch_igemm would pick writes from its epilogue; 0 if that kernel has no
 // statistics epilogue (the caller then runs a separate reduction pass).  Host only, depends on the shape alone.
 int igemm_stats_rows(int dtype, const IgemmArgs &a);
+// every layer whose channel runs are 16-byte granular and that has no kernel of its own (groups, src_ld, vec_out set)
+int launch_igemm_pipe(int dtype, const IgemmArgs &a, hipStream_t stream);
+int igemm_pipe_stats_rows(int dtype, const IgemmArgs &a);
 // bf16 large-tile kernel for wide layers (channel counts that are multiples of 64, enough tiles to fill the chip)
 bool igemm_big_applicable(int dtype, const IgemmArgs &a);
 int launch_igemm_big(const IgemmArgs &a, hipStream_t stream);

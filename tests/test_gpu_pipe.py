@@ -1,0 +1,84 @@
+"""The pipelined implicit-GEMM kernel, every tile shape of it, where a tile can go wrong: fewer k-tiles than stages and
+every remainder of them, several taps inside one k-tile, ragged rows and columns, strided classes, old values added,
+statistics, groups.  The tile is forced through its test hook (which also keeps the other kernels out)."""
+import numpy as np
+import pytest
+import torch
+
+import nsk_inputs as gen
+import oracle
+from paper_2409_11600_amd import binding as B
+from parity import TOL, guarded, max_rel_err, on_grid, to_gpu, to_host, torch_dtype
+
+pytestmark = pytest.mark.gpu
+
+# N, C, H, W, K, R, S, stride, pad, dilation; a k-tile is 64 (bf16) or 32 (f32) reduction indices
+SHAPES = [
+    (1, 8, 5, 5, 8, 1, 1, 1, 0, 1),            # one short k-tile, one tile
+    (2, 40, 9, 11, 40, 1, 1, 1, 0, 1),         # one or two k-tiles, ragged on all sides
+    (3, 24, 17, 13, 72, 3, 3, 1, 1, 1),        # 216 indices: taps change inside k-tiles, remainder of the stages
+    (2, 64, 14, 10, 136, 3, 3, 2, 1, 1),       # stride 2: four classes in backward-data, 9 k-tiles
+    (2, 16, 12, 20, 200, 2, 3, (1, 2), (0, 1), (2, 1)),   # four taps a k-tile, anisotropic
+    (1, 8, 15, 15, 8, 7, 7, 1, 3, 1),          # 49 taps of 8 channels
+    (5, 320, 7, 7, 264, 1, 1, 1, 0, 1),        # 5 k-tiles (bf16), 10 (f32), three column tiles of 128
+]
+
+
+@pytest.mark.parametrize("tile", range(1, 7))
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("i", range(len(SHAPES)))
+def test_every_tile(i, dtype, tile, nsk_env):
+    if dtype == "f32" and tile > 4:
+        pytest.skip("four tile shapes in f32")
+    nsk_env("NSK_IGEMM_TILE", str(tile))
+    nsk_env("NSK_STATS_ALWAYS", "1")
+    N, C, H, W, K, R, S, st, pd, dl = SHAPES[i]
+    print(f"pipelined kernel, shape {SHAPES[i]} {dtype} tile {tile}", flush=True)
+    tol, ws, lay = TOL[dtype], B.Workspace(), B.NSK_NHWC
+    x = on_grid(gen.normal(900 + i, 0, (N, C, H, W)), dtype)
+    w = on_grid(gen.he_normal(900 + i, 1, (K, C, R, S)), dtype)
+    P, Q = oracle.conv2d_out_dims(x.shape, w.shape, st, pd, dl)
+    dy = on_grid(gen.normal(900 + i, 2, (N, K, P, Q)), dtype)
+    old = on_grid(gen.normal(900 + i, 3, x.shape), dtype)
+    gx, gw, gdy = (to_gpu(a, dtype, lay) for a in (x, w, dy))
+
+    y, check = guarded(gdy.shape, torch_dtype(dtype))
+    _, stats = B.conv2d_fwd_stats(gx, gw, st, pd, dl, lay, out=y, ws=ws)
+    torch.cuda.synchronize()
+    check()
+    got = to_host(y, lay)
+    assert max_rel_err(got, oracle.conv2d_fwd(x, w, st, pd, dl)) <= tol
+    # float sums of at most N*P*Q stored values of either sign: absolute bars of sqrt(n) roundings of the largest partial sum
+    sums = stats.double().sum(1).cpu().numpy()
+    n = N * P * Q
+    assert np.allclose(sums[0], got.sum((0, 2, 3)), rtol=0, atol=1e-6 * n * np.abs(got).max())
+    assert np.allclose(sums[1], (got ** 2).sum((0, 2, 3)), rtol=1e-5, atol=1e-6)
+
+    want = oracle.conv2d_dgrad(dy, w, x.shape, st, pd, dl)
+    for accumulate in (False, True):
+        dx, check = guarded(gx.shape, torch_dtype(dtype))
+        if accumulate:
+            dx.copy_(to_gpu(old, dtype, lay))
+        B.conv2d_dgrad(gdy, gw, x.shape, st, pd, dl, lay, out=dx, accumulate=accumulate, ws=ws)
+        torch.cuda.synchronize()
+        check()
+        assert max_rel_err(to_host(dx, lay), want + old if accumulate else want) <= tol
+
+
+@pytest.mark.parametrize("tile", range(1, 7))
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_every_tile_grouped(dtype, tile, nsk_env):
+    if dtype == "f32" and tile > 4:
+        pytest.skip("four tile shapes in f32")
+    nsk_env("NSK_IGEMM_TILE", str(tile))
+    N, cg, kg, G, H, W = 2, 16, 24, 3, 9, 13
+    x = on_grid(gen.normal(950, 0, (N, G * cg, H, W)), dtype)
+    w = on_grid(gen.he_normal(950, 1, (G * kg, cg, 3, 3)), dtype)
+    dy = on_grid(gen.normal(950, 2, (N, G * kg, H, W)), dtype)
+    gx, gw, gdy = (to_gpu(a, dtype, B.NSK_NHWC) for a in (x, w, dy))
+    y = B.conv2d_grouped_fwd(gx, gw, G, 1, 1)
+    dx = B.conv2d_grouped_dgrad(gdy, gw, x.shape, G, 1, 1)
+    for g in range(G):
+        c, k = slice(g * cg, (g + 1) * cg), slice(g * kg, (g + 1) * kg)
+        assert max_rel_err(to_host(y, B.NSK_NHWC)[:, k], oracle.conv2d_fwd(x[:, c], w[k], 1, 1, 1)) <= TOL[dtype]
+        assert max_rel_err(to_host(dx, B.NSK_NHWC)[:, c], oracle.conv2d_dgrad(dy[:, k], w[k], x[:, c].shape, 1, 1, 1)) <= TOL[dtype]
