@@ -45,11 +45,13 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int PK_BYTES = 128;   // bytes of reduction index per k-tile row
 
-// s_waitcnt vmcnt(n) alone
+// Until at most N of the wavefront's direct loads are on their way and all its LDS reads have arrived (a barrier behind it
+// then also says that nobody reads the stage before any more).
 template <int N> __device__ inline void wait_vm()
 {
     static_assert(N >= 0 && N < 64, "six-bit counter");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int WK, int ST>

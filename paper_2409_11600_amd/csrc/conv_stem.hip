@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256) void stem_unpack_dw_kernel(const float *__rest
 struct StemPlan {
     size_t x2 = 0, w2 = 0, dx2 = 0, act = 0, part = 0, dw2 = 0, total = 0;
     int splits = 1, rows_per_split = 0;
-    bool wide = false;   // backward-weight through the large-tile kernel
+    bool pipe = false;   // backward-weight on the pipelined kernel
 };
 
 // backward-weight on the space-to-depth image: 16 channels, stride 1, U x U taps
@@ -195,8 +195,8 @@ StemPlan stem_plan(const ConvGeo &g, const StemGeo &s, int pass)
         if (nchw) p.act = take(g.y_elems * g.es);   // NHWC copy of dy
         WgradArgs wa{};
         stem_wgrad_geometry(g, s, &wa);
-        p.wide = wgrad_wide_applicable(s.dtype, wa);
-        p.rows_per_split = p.wide ? wgrad_wide_rows_per_split(wa, &p.splits)
+        p.pipe = wgrad_pipe_applicable(s.dtype, wa.C, s.K, 1);
+        p.rows_per_split = p.pipe ? wgrad_pipe_rows_per_split(s.dtype, wa.L, s.K, s.U * s.U * SC, 1, &p.splits)
                                   : wgrad_rows_per_split(s.dtype, wa.L, s.K, s.U * s.U * SC, &p.splits);
         p.part = take((size_t)p.splits * w2 * sizeof(float));
         p.dw2 = take(w2 * sizeof(float));
@@ -386,10 +386,14 @@ int stem_wgrad(const ConvGeo &g, const void *x, const void *dy, float *dw, int a
     a.x = ws + p.x2; a.dy = dys; a.part = (float *)(ws + p.part);
     a.rows_per_split = p.rows_per_split;
     a.splits = p.splits;
-    if (p.wide)
-        STEM_TRY(launch_wgrad_wide(a, st));
-    else
+    if (p.pipe) {
+        a.groups = 1;
+        a.ldx = a.C;
+        a.ldy = a.K;
+        STEM_TRY(launch_wgrad_pipe(s.dtype, a, st));
+    } else {
         STEM_TRY(launch_wgrad(s.dtype, a, st));
+    }
     float *dw2 = (float *)(ws + p.dw2);
     STEM_TRY(launch_wgrad_reduce(a.part, dw2, p.splits, s.K, a.ntaps, SC, (long)a.ntaps * SC, (long)SC, 1L, 0, st));
     long sk, sc, sr, ss;

@@ -7,7 +7,8 @@
 // across blocks (blockIdx.z) into float partials that a second kernel adds in a fixed order:
 // results are bitwise reproducible, no floating-point atomics.
 //
-// Block tile: 64 rows x (64*FN) columns, four wavefronts as 2 x 2, each owning a 32 x (32*FN) strip
+// The kernel here serves channel counts that no 16-byte load fits (every other layer without a kernel of its own runs on the
+// pipelined one), element by element.  Block tile: 64 rows x (64*FN) columns, four wavefronts as 2 x 2, each owning a 32 x (32*FN) strip
 // of 32x32 MFMA accumulators.  FN = 3 makes a column tile exactly one filter row of a 3x3 filter with
 // 64 channels, so x is re-read three times (not nine) across column tiles and every barrier is
 // followed by three times as many MFMAs.
@@ -36,7 +37,7 @@ template <> struct WTraits<bf16_t> {
     typedef bf16x8 Vec;
 };
 
-template <typename T, int FN, bool VECLOAD>
+template <typename T, int FN>
 __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a)
 {
     typedef WTraits<T> TR;
@@ -89,21 +90,6 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a)
     const int l_end = min(a.L, l_begin + a.rows_per_split);
     const int nk = (l_end - l_begin + BK - 1) / BK;
 
-    // column (tap, channel) of this thread's x vectors: fixed for the whole loop
-    int b_c[B_LOADS], b_oh[B_LOADS], b_ow[B_LOADS];
-    bool b_ok[B_LOADS];
-#pragma unroll
-    for (int u = 0; u < B_LOADS; ++u) {
-        const int n = n0 + vb[u] * VEC;
-        b_ok[u] = VECLOAD && n < NT;
-        b_c[u] = b_oh[u] = b_ow[u] = 0;
-        if (b_ok[u]) {
-            const int tap = n / a.C;
-            b_c[u] = n - tap * a.C;
-            b_oh[u] = s_offh[tap];
-            b_ow[u] = s_offw[tap];
-        }
-    }
     const int kA = k0 + va * VEC;
 
     Vec ra, rb[B_LOADS];
@@ -124,13 +110,9 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a)
         {
             const int l = base + la;
             if (l < l_end) {
-                if (VECLOAD) {
-                    if (kA < a.K) ra = *(const Vec *)(dy + (long)l * ldy + kA);
-                } else {
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e)
-                        if (kA + e < a.K) ra[e] = dy[(long)l * ldy + kA + e];
-                }
+                for (int e = 0; e < VEC; ++e)
+                    if (kA + e < a.K) ra[e] = dy[(long)l * ldy + kA + e];
             }
         }
 #pragma unroll
@@ -140,23 +122,15 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a)
             if (l >= l_end) continue;
             int img, p, q;
             decode(l, img, p, q);
-            if (VECLOAD) {
-                if (b_ok[u]) {
-                    const int h = p * a.sh - a.ph + b_oh[u], w = q * a.sw - a.pw + b_ow[u];
-                    if ((unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W)
-                        rb[u] = *(const Vec *)(x + (((long)img * a.H + h) * a.W + w) * ldx + b_c[u]);
-                }
-            } else {
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) {
-                    const int n = n0 + vb[u] * VEC + e;
-                    if (n < NT) {
-                        const int tap = n / a.C;
-                        const int c = n - tap * a.C;
-                        const int h = p * a.sh - a.ph + s_offh[tap], w = q * a.sw - a.pw + s_offw[tap];
-                        if ((unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W)
-                            rb[u][e] = x[(((long)img * a.H + h) * a.W + w) * ldx + c];
-                    }
+            for (int e = 0; e < VEC; ++e) {
+                const int n = n0 + vb[u] * VEC + e;
+                if (n < NT) {
+                    const int tap = n / a.C;
+                    const int c = n - tap * a.C;
+                    const int h = p * a.sh - a.ph + s_offh[tap], w = q * a.sw - a.pw + s_offw[tap];
+                    if ((unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W)
+                        rb[u][e] = x[(((long)img * a.H + h) * a.W + w) * ldx + c];
                 }
             }
         }
@@ -324,22 +298,15 @@ int wgrad_rows_per_split(int dtype, int L, int K, int ntapsC, int *splits)
     return rows;
 }
 
-template <typename T> int launch_wgrad_typed(const WgradArgs &a, bool vec, hipStream_t stream)
+template <typename T> int launch_wgrad_typed(const WgradArgs &a, hipStream_t stream)
 {
     const int NT = a.ntaps * a.C;
     const int fn = column_frags(NT);
     dim3 grid(ceil_div(NT, 64 * fn), ceil_div(a.K, WBM), a.splits * a.groups);
-    if (fn == 3) {
-        if (vec)
-            hipLaunchKernelGGL((wgrad_kernel<T, 3, true>), grid, dim3(256), 0, stream, a);
-        else
-            hipLaunchKernelGGL((wgrad_kernel<T, 3, false>), grid, dim3(256), 0, stream, a);
-    } else {
-        if (vec)
-            hipLaunchKernelGGL((wgrad_kernel<T, 1, true>), grid, dim3(256), 0, stream, a);
-        else
-            hipLaunchKernelGGL((wgrad_kernel<T, 1, false>), grid, dim3(256), 0, stream, a);
-    }
+    if (fn == 3)
+        hipLaunchKernelGGL((wgrad_kernel<T, 3>), grid, dim3(256), 0, stream, a);
+    else
+        hipLaunchKernelGGL((wgrad_kernel<T, 1>), grid, dim3(256), 0, stream, a);
     return check_launch();
 }
 
@@ -355,11 +322,8 @@ int launch_wgrad(int dtype, const WgradArgs &a0, hipStream_t stream)
     }
     if (tiny_wgrad_applicable(dtype, a)) return launch_tiny_wgrad(dtype, a, stream);
     if (!hooks().no_depthwise && depthwise_wgrad_applicable(dtype, a)) return launch_depthwise_wgrad(dtype, a, stream);
-    const int VEC = dtype == NSK_BF16 ? 8 : 4;
-    // (with C and K multiples of VEC every group's channel runs start on 16-byte boundaries too)
-    const bool vec = a.C % VEC == 0 && a.K % VEC == 0 && (uintptr_t)a.x % 16 == 0 && (uintptr_t)a.dy % 16 == 0;
-    if (dtype == NSK_BF16) return launch_wgrad_typed<bf16_t>(a, vec, stream);
-    return launch_wgrad_typed<float>(a, vec, stream);
+    if (dtype == NSK_BF16) return launch_wgrad_typed<bf16_t>(a, stream);
+    return launch_wgrad_typed<float>(a, stream);
 }
 
 int launch_wgrad_reduce(const float *part, float *dw, int splits, int K, int ntaps, int C, long sk,

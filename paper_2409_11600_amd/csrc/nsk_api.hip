@@ -68,9 +68,15 @@ void wgrad_geometry(const ConvGeo &g, WgradArgs *a)
         }
 }
 
-bool use_wgrad_halo(const ConvGeo &g, const WgradArgs &a)
+// The 3x3 64->64 kernels write 147 KB of partial sums per block, which only a long reduction pays for.  Measured against
+// the pipelined kernel (us): bf16 100 k rows 23.3 / 21.4, 200 k 30.0 / 32.7, 400 k 44 / 56; fp32 on 32-wide images 16 k
+// rows 29.6 / 21.9, 49 k 44.9 / 43.8, 66 k 53.0 / 55.0, 131 k 87 / 101.  act: the call applies a batch-norm on load,
+// which only these kernels do (elsewhere it costs a pass of its own).
+bool use_wgrad_halo(const ConvGeo &g, const WgradArgs &a, bool act)
 {
-    return wgrad_halo64_applicable(g.dtype, a) && !hooks().no_halo;
+    if (!wgrad_halo64_applicable(g.dtype, a) || hooks().no_halo) return false;
+    if (act && wgrad_halo64_act_fused(g.dtype, a)) return true;
+    return a.L >= (hooks().wh_min_rows >= 0 ? hooks().wh_min_rows : g.dtype == NSK_BF16 ? 150000 : 55000);
 }
 
 // Workspace segments (byte offsets, each 256-aligned).
@@ -83,7 +89,7 @@ struct ConvPlan {
     size_t total = 0;
     int splits = 1, rows_per_split = 0;
     bool halo = false;   // wgrad: the 3x3 64->64 kernel writes one partial per block
-    bool wide = false;   // wgrad: the large-tile kernel for wide bf16 layers
+    bool pipe = false;   // wgrad: the pipelined kernel
     bool stem = false;   // the space-to-depth path plans its own workspace
     size_t act_tmp = 0;  // fused-activation calls on a kernel without the fused load: the applied activation
     bool act_fused = false;
@@ -115,7 +121,7 @@ ConvPlan plan_conv(const ConvGeo &g, int pass, int groups = 1, bool act = false)
         } else if (pass == NSK_PASS_WGRAD && !p.stem) {
             WgradArgs wa{};
             wgrad_geometry(g, &wa);
-            p.act_fused = use_wgrad_halo(g, wa) && wgrad_halo64_act_fused(g.dtype, wa);
+            p.act_fused = use_wgrad_halo(g, wa, true) && wgrad_halo64_act_fused(g.dtype, wa);
         }
         if (!p.act_fused) p.act_tmp = take(g.x_elems * g.es);
     }
@@ -142,15 +148,22 @@ ConvPlan plan_conv(const ConvGeo &g, int pass, int groups = 1, bool act = false)
         }
         WgradArgs wa{};
         wgrad_geometry(g, &wa);
-        p.halo = groups == 1 && use_wgrad_halo(g, wa);
-        p.wide = groups == 1 && !p.halo && wgrad_wide_applicable(g.dtype, wa);
+        p.halo = groups == 1 && use_wgrad_halo(g, wa, act);
         if (p.halo)
             p.splits = wgrad_halo64_partials(g.dtype, wa, nullptr);
-        else if (p.wide)
-            p.rows_per_split = wgrad_wide_rows_per_split(wa, &p.splits);
-        else
-            p.rows_per_split = wgrad_rows_per_split(g.dtype, g.N * g.P * g.Q, g.K, g.R * g.S * (g.C / groups), &p.splits);
-        if (groups > 1 && g.C == g.K && (g.C == groups || g.C == 2 * groups || g.C == 4 * groups || g.C == 8 * groups)) {
+        else {
+            WgradArgs one = wa;   // one group's problem (aligned pointers and a split count stand for every launch)
+            one.C = g.C / groups; one.K = g.K / groups;
+            one.groups = groups; one.ldx = g.C; one.ldy = g.K;
+            one.splits = 1;
+            const bool direct = tiny_wgrad_applicable(g.dtype, one) || (!hooks().no_depthwise && depthwise_wgrad_applicable(g.dtype, one));
+            p.pipe = !direct && wgrad_pipe_applicable(g.dtype, one.C, one.K, groups);
+            if (p.pipe)
+                p.rows_per_split = wgrad_pipe_rows_per_split(g.dtype, one.L, one.K, one.ntaps * one.C, groups, &p.splits);
+            else
+                p.rows_per_split = wgrad_rows_per_split(g.dtype, one.L, g.K, one.ntaps * one.C, &p.splits);
+        }
+        if (!p.pipe && groups > 1 && g.C == g.K && (g.C == groups || g.C == 2 * groups || g.C == 4 * groups || g.C == 8 * groups)) {
             // depthwise and its neighbours: the direct kernel runs blocks of 16 channel vectors x one split and wants
             // about four per CU
             const int vec = g.dtype == NSK_BF16 ? 8 : 4, L = g.N * g.P * g.Q;
@@ -161,7 +174,7 @@ ConvPlan plan_conv(const ConvGeo &g, int pass, int groups = 1, bool act = false)
             p.splits = ceil_div(L, p.rows_per_split);
         }
         // a grouped launch puts groups * splits on gridDim.z
-        while ((long)groups * p.splits > 65535) {
+        while (!p.pipe && (long)groups * p.splits > 65535) {
             p.rows_per_split *= 2;
             p.splits = ceil_div(g.N * g.P * g.Q, p.rows_per_split);
         }
@@ -373,7 +386,6 @@ void read_hooks()
     h.no_stem = on("NSK_NO_STEM");
     h.no_stem_halo = on("NSK_NO_STEM_HALO");
     h.no_tiny = on("NSK_NO_TINY");
-    h.no_wide = on("NSK_NO_WIDE");
     h.no_depthwise = on("NSK_NO_DEPTHWISE");
     h.depthwise_no_rows = on("NSK_DEPTHWISE_NO_ROWS");
     h.depthwise_no_cols = on("NSK_DEPTHWISE_NO_COLS");
@@ -383,7 +395,7 @@ void read_hooks()
     h.wh_no_split = on("NSK_WH_NO_SPLIT");
     h.big_min_tiles = num("NSK_BIG_MIN_TILES");
     h.pw_min_rows = num("NSK_PW_MIN_ROWS");
-    h.wide_min_rows = num("NSK_WIDE_MIN_ROWS");
+    h.wh_min_rows = num("NSK_WH_MIN_ROWS");
     const long long tile = num("NSK_IGEMM_TILE");
     h.igemm_tile = tile > 0 ? (int)tile : 0;
     g_hooks = h;
@@ -633,10 +645,19 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
         a.C = cg;
         a.K = kg;
     }
+    if (p.pipe && groups <= 1) {
+        a.groups = 1;
+        a.ldx = g.C;
+        a.ldy = g.K;
+    }
+    if (p.pipe && p.splits == 1 && !nchw && !accumulate) {   // one partial sum in the order of dw: it is the result
+        a.part = dw;
+        return launch_wgrad_pipe(g.dtype, a, st);
+    }
     if (p.halo)
         NSK_TRY(launch_wgrad_halo64(g.dtype, a, st));
-    else if (p.wide)
-        NSK_TRY(launch_wgrad_wide(a, st));
+    else if (p.pipe)
+        NSK_TRY(launch_wgrad_pipe(g.dtype, a, st));
     else
         NSK_TRY(launch_wgrad(g.dtype, a, st));
     const long RS = (long)g.R * g.S;

@@ -48,9 +48,9 @@ __device__ inline void lds_barrier()
 // the launch path.  Each one only narrows or widens the choice among kernels that all compute the same result.
 struct TestHooks {
     bool no_big, no_big_multi, no_pw, no_halo, no_fs, no_halo_wide, halo_wide_always, halo_single, no_stem, no_stem_halo,
-        no_tiny, no_wide, no_depthwise, depthwise_no_rows, depthwise_no_cols, pool_general, stats_always, reduce4,
+        no_tiny, no_depthwise, depthwise_no_rows, depthwise_no_cols, pool_general, stats_always, reduce4,
         wh_no_split;
-    long long big_min_tiles, pw_min_rows, wide_min_rows;   // -1: not set
+    long long big_min_tiles, pw_min_rows, wh_min_rows;   // -1: not set
     int igemm_tile;                                         // 0: not set
 };
 const TestHooks &hooks();
@@ -203,15 +203,15 @@ struct WgradArgs {
 };
 int wgrad_rows_per_split(int dtype, int L, int K, int ntapsC, int *splits);
 int launch_wgrad(int dtype, const WgradArgs &a, hipStream_t stream);
+// the pipelined kernel: channel runs of C and K (of one group) that are 16-byte granular, and no kernel of their own
+bool wgrad_pipe_applicable(int dtype, int C, int K, int groups);
+int wgrad_pipe_rows_per_split(int dtype, int L, int K, int ntapsC, int groups, int *splits);
+int launch_wgrad_pipe(int dtype, const WgradArgs &a, hipStream_t stream);   // groups, ldx, ldy set
 // 3x3 stride-1 64->64 special case: one [K][taps][C] partial per block, `partials` of them
 bool wgrad_halo64_applicable(int dtype, const WgradArgs &a);
 int wgrad_halo64_partials(int dtype, const WgradArgs &a, int *chunks_per_block);
 int launch_wgrad_halo64(int dtype, const WgradArgs &a, hipStream_t stream);
 bool wgrad_halo64_act_fused(int dtype, const WgradArgs &a);
-// wide bf16 layers (C, K multiples of 64, long reduction): large tiles, about one block per CU
-bool wgrad_wide_applicable(int dtype, const WgradArgs &a);
-int wgrad_wide_rows_per_split(const WgradArgs &a, int *splits);
-int launch_wgrad_wide(const WgradArgs &a, hipStream_t stream);
 // at most four input channels: partial sums in the layout of the generic kernel
 bool tiny_wgrad_applicable(int dtype, const WgradArgs &a);
 int launch_tiny_wgrad(int dtype, const WgradArgs &a, hipStream_t stream);
