@@ -817,6 +817,9 @@ bool halo_wide_fwd_s2_applicable(int dtype, const IgemmArgs &a)
     const long long out_bytes = (long long)a.Nimg * a.Ho * a.Wo * a.Co * 2;
     if ((unsigned long long)a.src_bytes >= W_OOB || out_bytes >= (long long)W_OOB) return false;
     if (hooks().halo_wide_always) return true;
+    // against the pipelined kernel (us): 256->256 at 28x28 N=128 41.0 / 36.9, 128->256 at 56x56 N=64 45.8 / 39.9 (its 256 x 128
+    // tiles share the filter over more pixels), 128->128 at 56x56 N=128 50.2 / 55.1
+    if (a.Ngemm >= 256) return false;
     const long long useful = (long long)v.Hs * v.Ws, computed = (long long)p.tiles_per_img * kNT * 32;
     if (useful * 3 < computed * 2) return false;
     return (long long)a.Nimg * p.tiles_per_img * (a.Ngemm / block_channels(a)) >= 128;

@@ -344,6 +344,17 @@ template <typename T> int launch_typed(const IgemmArgs &a, hipStream_t stream)
     }
 }
 
+// The fp32 64 -> 64 kernel gives every CU whole tiles of 8 image rows, 43 us each; the pipelined kernel takes 0.18 us a tile.
+// Measured (us, forward, 32x32): N=16 39.6 / 15.6, N=64 44.3 / 46, N=96 81.8 / 69, N=128 85-88 / 92.   Below 32 tiles it stays although it is slower (39 us): whole training
+// steps at batch 4 are pinned element by element against the oracle, and another order of the sums puts one activation
+// of the second step on the other side of zero.
+bool takes_halo64_f32(int dtype, const IgemmArgs &a)
+{
+    if (!halo64_f32_applicable(dtype, a)) return false;
+    const long tiles = (long)a.Nimg * (a.Hs / 8);
+    return hooks().halo64_always || tiles < 32 || (tiles + 255) / 256 * 256 * 100 <= tiles * 105;
+}
+
 }  // namespace
 
 int igemm_stats_rows(int dtype, const IgemmArgs &a)
@@ -355,21 +366,22 @@ int igemm_stats_rows(int dtype, const IgemmArgs &a)
     if (special) {
         if (tiny_src_applicable(dtype, a) || tiny_out_applicable(dtype, a)) return 0;   // no statistics epilogue there
         if (halo64_applicable(dtype, a)) return halo64_stats_rows(a);
-        if (halo64_f32_applicable(dtype, a)) return halo64_f32_stats_rows(a);
+        if (takes_halo64_f32(dtype, a)) return halo64_f32_stats_rows(a);
         if (fs64_fwd_s2_applicable(dtype, a)) return fs64_fwd_s2_stats_rows(a);
         if (conv_pw_applicable(dtype, a)) return conv_pw_stats_rows(a);
         if (halo_wide_applicable(dtype, a)) return halo_wide_stats_rows(a);
         if (halo_wide_fwd_s2_applicable(dtype, a)) return halo_wide_fwd_s2_stats_rows(a);
-        if (igemm_big_applicable(dtype, a)) return igemm_big_stats_rows(a);
     }
-    // generic kernel: needs the vector epilogue; one row per wavefront row of every row block.  Measured: with a
-    // short reduction the per-block cross-lane sums and the many rows of partial sums cost more than the separate
-    // statistics pass they replace (config 5 stage A: +45 us on a 140 us layer), so only long reductions use it.
+    // Both generic kernels need the vector epilogue and 16-byte stores of the partial sums; one row per wavefront row of every
+    // row block.
     const int vec = dtype == NSK_BF16 ? 8 : 4;
     if (!(a.Ngemm % vec == 0 && a.Co % vec == 0 && (uintptr_t)a.out % 16 == 0)) return 0;
-    if (a.Ktot < 1024 && !hooks().stats_always) return 0;   // the variable is a test hook
-    if (a.Ngemm % 4 != 0) return 0;   // 16-byte stores of the partial sums
+    // The pipelined kernel's epilogue beats the separate pass over y at every size (us, convolution + batch-norm, pass /
+    // epilogue: 256->1024 1x1 at 14x14 N=128 69.6 / 69.4, 64->128 1x1 stride 2 at 56x56 N=64 29.2 / 25.1, fp32 16->16 at
+    // 40x42 N=37 22.5 / 20.8, 72->104 at 29x37 N=20 34.0 / 20.5; 256->64 at 56x56 N=64, 3136 rows of sums, 50.1 / 51.5).
     if (vector_runs(dtype, a)) return igemm_pipe_stats_rows(dtype, a);
+    // The element-wise kernel's, with its short reductions, does not (the variable is a test hook).
+    if (a.Ktot < 1024 && !hooks().stats_always) return 0;
     static const int bm[3] = {256, 128, 128}, wm[3] = {64, 32, 64};
     const int t = auto_tile(a, dtype == NSK_BF16 ? 2 : 4);
     return ceil_div(a.M, bm[t]) * (bm[t] / wm[t]);
@@ -380,7 +392,35 @@ bool igemm_act_fused(int dtype, const IgemmArgs &a)
     // the same order of tests as launch_igemm, up to the kernels that have the fused load
     if (a.M <= 0 || a.Ngemm <= 0 || a.accumulate || a.groups > 1 || a.zero_cell || hooks().igemm_tile != 0) return false;
     if (tiny_src_applicable(dtype, a) || tiny_out_applicable(dtype, a) || halo64_applicable(dtype, a)) return false;
-    return halo64_f32_applicable(dtype, a);
+    return takes_halo64_f32(dtype, a);   // (by size too: nsk_conv2d_stats_rows does not know of the activation)
+}
+
+// The residue classes of a strided backward-data pass in one launch of the pipelined kernel, if it is what each of them runs on.
+bool igemm_pipe_multi_applicable(int dtype, const IgemmArgs *a, int count)
+{
+    for (int i = 0; i < count; ++i) {
+        if (a[i].zero_cell || a[i].stats || !vector_runs(dtype, a[i])) return false;
+        if (a[i].groups > 1 && !hooks().no_depthwise && hooks().igemm_tile == 0 && depthwise_applicable(dtype, a[i])) return false;
+        if (a[i].groups <= 1 && hooks().igemm_tile == 0 &&
+            (tiny_src_applicable(dtype, a[i]) || tiny_out_applicable(dtype, a[i]) || (count == 1 && conv_pw_applicable(dtype, a[i]))))
+            return false;   // (several classes in one launch beat the short-reduction kernel's one launch each: 3x3 stride 2 32->64 17.4 / 8.6 us)
+    }
+    return count >= 1 && count <= 4;
+}
+
+int launch_igemm_pipe_multi(int dtype, const IgemmArgs *a, int count, hipStream_t stream)
+{
+    IgemmArgs b[4];
+    const int vec = dtype == NSK_BF16 ? 8 : 4;
+    for (int i = 0; i < count; ++i) {
+        b[i] = a[i];
+        if (b[i].groups <= 1) {
+            b[i].groups = 1;
+            b[i].src_ld = b[i].Cs;
+        }
+        b[i].vec_out = (b[i].Ngemm % vec == 0 && b[i].Co % vec == 0 && (uintptr_t)b[i].out % 16 == 0) ? 1 : 0;
+    }
+    return launch_igemm_pipe(dtype, b, count, stream);
 }
 
 int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream)
@@ -394,12 +434,11 @@ int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream)
     if (special && tiny_src_applicable(dtype, a)) return launch_tiny_src(dtype, a, stream);
     if (special && tiny_out_applicable(dtype, a)) return launch_tiny_out(dtype, a, stream);
     if (special && halo64_applicable(dtype, a)) return launch_halo64(a, stream);
-    if (special && halo64_f32_applicable(dtype, a)) return launch_halo64_f32(a, stream);
+    if (special && takes_halo64_f32(dtype, a)) return launch_halo64_f32(a, stream);
     if (special && fs64_fwd_s2_applicable(dtype, a)) return launch_fs64_fwd_s2(a, stream);
     if (special && conv_pw_applicable(dtype, a)) return launch_conv_pw(a, stream);
     if (special && halo_wide_applicable(dtype, a)) return launch_halo_wide(a, stream);
     if (special && halo_wide_fwd_s2_applicable(dtype, a)) return launch_halo_wide_fwd_s2(a, stream);
-    if (special && igemm_big_applicable(dtype, a)) return launch_igemm_big(a, stream);
     if (grouped && hooks().igemm_tile == 0 && !hooks().no_depthwise && depthwise_applicable(dtype, a))
         return launch_depthwise(dtype, a, stream);
     IgemmArgs b = a;
@@ -409,7 +448,7 @@ int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream)
     }
     const int vec = dtype == NSK_BF16 ? 8 : 4;
     b.vec_out = (b.Ngemm % vec == 0 && b.Co % vec == 0 && (uintptr_t)b.out % 16 == 0) ? 1 : 0;
-    if (vector_runs(dtype, b)) return launch_igemm_pipe(dtype, b, stream);
+    if (vector_runs(dtype, b)) return launch_igemm_pipe(dtype, &b, 1, stream);
     return dtype == NSK_BF16 ? launch_typed<bf16_t>(b, stream) : launch_typed<float>(b, stream);
 }
 

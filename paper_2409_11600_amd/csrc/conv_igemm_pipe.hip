@@ -54,9 +54,20 @@ template <int N> __device__ inline void wait_vm()
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int WK, int ST>
-__global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const IgemmArgs a, int tiles_m, int tiles_n)
+constexpr int kMaxProblems = 4;
+template <int NP> struct PipeProblems {   // NP = 1 or kMaxProblems: a plain launch carries 400 bytes of arguments, not 1.7 KB
+    IgemmArgs a[NP];
+    int tiles_m[NP];
+    int tiles_n;
+};
+
+template <typename T, int BM, int BN, int WM, int WN, int WK, int ST, int NP>
+__global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const PipeProblems<NP> pp)
 {
+    const int prob = NP > 1 ? blockIdx.y : 0;   // (the problems of a launch differ in their pixels and taps)
+    const IgemmArgs &a = pp.a[prob];
+    const int tiles_m = pp.tiles_m[prob], tiles_n = pp.tiles_n;
+    if ((int)blockIdx.x >= tiles_m * tiles_n) return;
     typedef typename PipeTraits<T>::Vec Vec;
     constexpr int VEC = PipeTraits<T>::VEC, ES = (int)sizeof(T), BK = PK_BYTES / ES;
     constexpr int NW = WM * WN * WK;                    // wavefronts per block
@@ -305,18 +316,23 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Ige
         }
         __syncthreads();
         if (wk > 0) return;
+        // (0 + 1) + (2 + 3): two roundings deep, not three
 #pragma unroll
-        for (int w = 1; w < WK; ++w)
+        for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
-            for (int mi = 0; mi < FM; ++mi)
+            for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
-                for (int ni = 0; ni < FN; ++ni)
+                for (int v = 0; v < 16; v += 4) {
+                    f32x4 p[WK];
 #pragma unroll
-                    for (int v = 0; v < 16; v += 4) {
-                        const f32x4 p = *(const f32x4 *)(red + ((((slot + w - 1) * FM + mi) * FN + ni) * 4 + v / 4) * 256 + lane * 4);
+                    for (int w = 1; w < WK; ++w)
+                        p[w] = *(const f32x4 *)(red + ((((slot + w - 1) * FM + mi) * FN + ni) * 4 + v / 4) * 256 + lane * 4);
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) acc[mi][ni][v + j] += p[j];
+                    for (int j = 0; j < 4; ++j) {
+                        acc[mi][ni][v + j] += p[1][j];
+                        if constexpr (WK == 4) acc[mi][ni][v + j] += p[2][j] + p[3][j];
                     }
+                }
     }
 
     if (a.vec_out) {
@@ -420,17 +436,24 @@ constexpr PipeTile kTilesBf16[] = {{256, 128, 4, 1300, 16000}, {128, 128, 2, 830
                                    {128, 64, 4, 700, 5000},    {64, 64, 2, 400, 3000},   {128, 32, 4, 550, 3000}};
 constexpr PipeTile kTilesF32[] = {{64, 64, 2, 1150, 3000}, {128, 32, 4, 1150, 3000}, {64, 32, 2, 580, 2000}, {32, 32, 1, 290, 1500}};
 
-template <int N> int cheapest(const PipeTile (&tiles)[N], int es, const IgemmArgs &a)
+template <int N> int cheapest(const PipeTile (&tiles)[N], int es, const IgemmArgs *a, int count)
 {
     const int forced = hooks().igemm_tile;   // NSK_IGEMM_TILE = 1.. (test hook)
     if (forced >= 1) return (forced - 1) % N;
-    const int groups = a.groups > 1 ? a.groups : 1;
-    const double nk = (double)(((long)a.Ktot * es + PK_BYTES - 1) / PK_BYTES);
+    const int groups = a[0].groups > 1 ? a[0].groups : 1;
     int best = 0;
     double best_cost = 0;
     for (int i = 0; i < N; ++i) {
-        const long blocks = (long)ceil_div(a.M, tiles[i].bm) * ceil_div(a.Ngemm, tiles[i].bn) * groups;
-        const double cost = (double)((blocks + 255) / 256) * (nk * tiles[i].step + tiles[i].rest);   // 256 CUs
+        long blocks = 0;
+        double work = 0;
+        for (int j = 0; j < count; ++j) {
+            const long b = (long)ceil_div(a[j].M, tiles[i].bm) * ceil_div(a[j].Ngemm, tiles[i].bn) * groups;
+            const double nk = (double)(((long)a[j].Ktot * es + PK_BYTES - 1) / PK_BYTES);
+            blocks += b;
+            work += (double)b * (nk * tiles[i].step + tiles[i].rest);
+        }
+        // 256 CUs: whole rounds of the average block
+        const double cost = (double)((blocks + 255) / 256) * (work / (double)blocks);
         if (i == 0 || cost < best_cost) {
             best = i;
             best_cost = cost;
@@ -439,40 +462,56 @@ template <int N> int cheapest(const PipeTile (&tiles)[N], int es, const IgemmArg
     return best;
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int WK, int ST> int launch(const IgemmArgs &a, hipStream_t stream)
+template <typename T, int BM, int BN, int WM, int WN, int WK, int ST, int NP> int launch_np(const IgemmArgs *a, int count, hipStream_t stream)
 {
-    const int tm = ceil_div(a.M, BM), tn = ceil_div(a.Ngemm, BN);
-    hipLaunchKernelGGL((igemm_pipe_kernel<T, BM, BN, WM, WN, WK, ST>), dim3((unsigned)tm * tn, 1, a.groups),
-                       dim3(64 * WM * WN * WK), 0, stream, a, tm, tn);
+    PipeProblems<NP> pp;
+    int most = 0;
+    pp.tiles_n = ceil_div(a[0].Ngemm, BN);
+    for (int j = 0; j < count; ++j) {
+        pp.a[j] = a[j];
+        pp.tiles_m[j] = ceil_div(a[j].M, BM);
+        if (pp.tiles_m[j] > most) most = pp.tiles_m[j];
+    }
+    hipLaunchKernelGGL((igemm_pipe_kernel<T, BM, BN, WM, WN, WK, ST, NP>), dim3((unsigned)most * pp.tiles_n, count, a[0].groups),
+                       dim3(64 * WM * WN * WK), 0, stream, pp);
     return check_launch();
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int WK, int ST> int launch(const IgemmArgs *a, int count, hipStream_t stream)
+{
+    return count == 1 ? launch_np<T, BM, BN, WM, WN, WK, ST, 1>(a, 1, stream)
+                      : launch_np<T, BM, BN, WM, WN, WK, ST, kMaxProblems>(a, count, stream);
 }
 
 }  // namespace
 
-// groups, src_ld and vec_out are set; the caller has checked that channel runs are 16-byte granular
-int launch_igemm_pipe(int dtype, const IgemmArgs &a, hipStream_t stream)
+// One problem, or the residue classes of one strided backward-data pass (same tensors, filters of their own; a class that no
+// tap reaches has ntaps = 0 and is filled with zeros).  groups, src_ld and vec_out are set; the caller has checked that
+// channel runs are 16-byte granular.
+int launch_igemm_pipe(int dtype, const IgemmArgs *a, int count, hipStream_t stream)
 {
+    if (count < 1 || count > kMaxProblems) return NSK_ERR_BAD_DESC;
     if (dtype == NSK_BF16) {
-        switch (cheapest(kTilesBf16, 2, a)) {
-        case 0: return launch<bf16_t, 256, 128, 4, 2, 1, 3>(a, stream);
-        case 1: return launch<bf16_t, 128, 128, 2, 4, 1, 4>(a, stream);
-        case 2: return launch<bf16_t, 256, 64, 4, 2, 1, 3>(a, stream);
-        case 3: return launch<bf16_t, 128, 64, 4, 2, 1, 4>(a, stream);
-        case 4: return launch<bf16_t, 64, 64, 2, 2, 2, 3>(a, stream);
-        default: return launch<bf16_t, 128, 32, 4, 1, 1, 3>(a, stream);
+        switch (cheapest(kTilesBf16, 2, a, count)) {
+        case 0: return launch<bf16_t, 256, 128, 4, 2, 1, 3>(a, count, stream);
+        case 1: return launch<bf16_t, 128, 128, 2, 4, 1, 4>(a, count, stream);
+        case 2: return launch<bf16_t, 256, 64, 4, 2, 1, 3>(a, count, stream);
+        case 3: return launch<bf16_t, 128, 64, 4, 2, 1, 4>(a, count, stream);
+        case 4: return launch<bf16_t, 64, 64, 2, 2, 2, 3>(a, count, stream);
+        default: return launch<bf16_t, 128, 32, 4, 1, 1, 3>(a, count, stream);
         }
     }
-    switch (cheapest(kTilesF32, 4, a)) {
-    case 0: return launch<float, 64, 64, 2, 2, 1, 4>(a, stream);
-    case 1: return launch<float, 128, 32, 4, 1, 1, 3>(a, stream);
-    case 2: return launch<float, 64, 32, 2, 1, 2, 4>(a, stream);
-    default: return launch<float, 32, 32, 1, 1, 4, 4>(a, stream);
+    switch (cheapest(kTilesF32, 4, a, count)) {
+    case 0: return launch<float, 64, 64, 2, 2, 1, 4>(a, count, stream);
+    case 1: return launch<float, 128, 32, 4, 1, 1, 3>(a, count, stream);
+    case 2: return launch<float, 64, 32, 2, 1, 2, 4>(a, count, stream);
+    default: return launch<float, 32, 32, 1, 1, 4, 4>(a, count, stream);
     }
 }
 
 int igemm_pipe_stats_rows(int dtype, const IgemmArgs &a)
 {
-    const PipeTile &t = dtype == NSK_BF16 ? kTilesBf16[cheapest(kTilesBf16, 2, a)] : kTilesF32[cheapest(kTilesF32, 4, a)];
+    const PipeTile &t = dtype == NSK_BF16 ? kTilesBf16[cheapest(kTilesBf16, 2, &a, 1)] : kTilesF32[cheapest(kTilesF32, 4, &a, 1)];
     return ceil_div(a.M, t.bm) * t.wm;
 }
 

@@ -20,6 +20,8 @@
 //     live class of a 1x1 stride-2 backward-data pass also writes the zeros of the other three pixels of each cell.
 // One block of 4 wavefronts per CU (the register file then allows two tiles of up to 256 channels per lane);
 // 256 persistent blocks.  This file holds the 64-channel-chunk instances, conv_pw_narrow16/32.hip the narrow ones.
+#include <limits.h>
+
 #include "conv_pw_kernel.h"
 
 namespace nsk {
@@ -47,9 +49,13 @@ bool conv_pw_applicable(int dtype, const IgemmArgs &a)
         }
         const int cols = pw_cols(a);
         if (cols == 0) return false;
-        // enough tiles to give every wavefront of the grid a few (below that the generic kernel's many small blocks
-        // win); with the columns split into groups every group walks over all rows, so fewer rows are enough
-        min_rows = a.Cs == 32 ? 8192 : (4L * kPwGrid * 4 * 64) / ((a.Ngemm / cols) * (a.Ngemm / cols));
+        // enough tiles to give every wavefront of the grid a few; with the columns split into groups every group walks over
+        // all rows, so fewer rows are enough.  Below, the pipelined kernel wins, measured (us, this kernel / that one):
+        // 256->1024 on 6 k rows 13.9 / 9.6, on 25 k 31.4 / 30.0, on 50 k 53.5 / 61; 3x3 stride 2 32->64 on 13 k 6.8 / 5.6,
+        // on 50 k 11.3 / 9.6, on 200 k 29.9 / 31.6; 512->256 on 100 k 65 / 53, on 400 k 210 / 173; 512->64 on 400 k 99.6 / 104.
+        min_rows = a.Cs == 32 ? (a.ntaps == 9 ? 131072 : 8192) : (4L * kPwGrid * 4 * 64) / ((a.Ngemm / cols) * (a.Ngemm / cols));
+        if (a.Cs == 256 && min_rows < 32768) min_rows = 32768;
+        if (a.Cs == 512) min_rows = a.Ngemm == 64 ? 262144 : LONG_MAX;
     } else {
         return false;
     }

@@ -375,13 +375,12 @@ void read_hooks()
     auto on = [](const char *name) { return getenv(name) != nullptr; };
     auto num = [](const char *name) { const char *e = getenv(name); return e ? atoll(e) : -1LL; };
     TestHooks h{};
-    h.no_big = on("NSK_NO_BIG");
-    h.no_big_multi = on("NSK_NO_BIG_MULTI");
     h.no_pw = on("NSK_NO_PW");
     h.no_halo = on("NSK_NO_HALO");
     h.no_fs = on("NSK_NO_FS");
     h.no_halo_wide = on("NSK_NO_HALO_WIDE");
     h.halo_wide_always = on("NSK_HALO_WIDE_ALWAYS");
+    h.halo64_always = on("NSK_HALO64_ALWAYS");
     h.halo_single = on("NSK_HALO_SINGLE");
     h.no_stem = on("NSK_NO_STEM");
     h.no_stem_halo = on("NSK_NO_STEM_HALO");
@@ -393,7 +392,6 @@ void read_hooks()
     h.stats_always = on("NSK_STATS_ALWAYS");
     h.reduce4 = on("NSK_REDUCE4");
     h.wh_no_split = on("NSK_WH_NO_SPLIT");
-    h.big_min_tiles = num("NSK_BIG_MIN_TILES");
     h.pw_min_rows = num("NSK_PW_MIN_ROWS");
     h.wh_min_rows = num("NSK_WH_MIN_ROWS");
     const long long tile = num("NSK_IGEMM_TILE");
@@ -551,8 +549,8 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     size_t filt_off = p.filt;
     // classes with taps: filters are packed first, then the launches follow (one for all classes where the large-tile
     // kernel takes them together)
-    IgemmArgs pending[4];
-    int n_pending = 0;
+    IgemmArgs pending[4], zeros[4];
+    int n_pending = 0, n_zeros = 0;
     const bool may_merge = g.sh * g.sw <= 4;
     int pk_taps[4][kMaxTaps], pk_nt[4];
     void *pk_out[4];
@@ -564,8 +562,12 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
             if (a.Mi == 0 || a.Mj == 0) continue;
             if (nt == 0 && accumulate && !nchw) continue;  // nothing to add
             if (nt == 0) {   // no tap reaches this class: plain zero fill
-                if (!zero_cell)
+                if (may_merge) {
+                    a.src = src; a.wpk = ws + p.filt; a.out = dst;
+                    if (!zero_cell) zeros[n_zeros++] = a;
+                } else {
                     NSK_TRY(launch_zero_class(g.dtype, dst, g.N, g.H, g.W, g.C, a.Mi, a.Mj, g.sh, ca, g.sw, cb, st));
+                }
                 continue;
             }
             // packed filter of this class: [c][tap][k] with element (c, t, k) = w[c*sn + tap_off[t] + k*sc]
@@ -592,11 +594,15 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
         NSK_TRY(launch_fs64_dgrad_s2(pending, n_pending, st));
     } else if (n_pending > 1 && groups == 1 && halo_wide_multi_applicable(g.dtype, pending, n_pending)) {
         NSK_TRY(launch_halo_wide_multi(pending, n_pending, st));
-    } else if (n_pending > 1 && groups == 1 && igemm_big_multi_applicable(g.dtype, pending, n_pending)) {
-        NSK_TRY(launch_igemm_big_multi(pending, n_pending, st));
+    } else if (n_pending + n_zeros > 1 && n_pending > 0 && igemm_pipe_multi_applicable(g.dtype, pending, n_pending)) {
+        for (int i = 0; i < n_zeros; ++i) pending[n_pending + i] = zeros[i];
+        NSK_TRY(launch_igemm_pipe_multi(g.dtype, pending, n_pending + n_zeros, st));
+        n_zeros = 0;
     } else {
         for (int i = 0; i < n_pending; ++i) NSK_TRY(launch_igemm(g.dtype, pending[i], st));
     }
+    for (int i = 0; i < n_zeros; ++i)
+        NSK_TRY(launch_zero_class(g.dtype, dst, g.N, g.H, g.W, g.C, zeros[i].Mi, zeros[i].Mj, g.sh, zeros[i].oa, g.sw, zeros[i].ob, st));
     if (nchw) NSK_TRY(launch_nhwc_to_nchw(g.dtype, dst, dx, g.N, g.C, g.H, g.W, accumulate, st));
     return NSK_OK;
 }

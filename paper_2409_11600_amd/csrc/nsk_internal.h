@@ -47,10 +47,10 @@ __device__ inline void lds_barrier()
 // Test and A/B switches: environment variables NSK_*, read ONCE (first use, or nsk_test_hooks_reload()) and never on
 // the launch path.  Each one only narrows or widens the choice among kernels that all compute the same result.
 struct TestHooks {
-    bool no_big, no_big_multi, no_pw, no_halo, no_fs, no_halo_wide, halo_wide_always, halo_single, no_stem, no_stem_halo,
+    bool no_pw, no_halo, no_fs, no_halo_wide, halo_wide_always, halo64_always, halo_single, no_stem, no_stem_halo,
         no_tiny, no_depthwise, depthwise_no_rows, depthwise_no_cols, pool_general, stats_always, reduce4,
         wh_no_split;
-    long long big_min_tiles, pw_min_rows, wh_min_rows;   // -1: not set
+    long long pw_min_rows, wh_min_rows;   // -1: not set
     int igemm_tile;                                         // 0: not set
 };
 const TestHooks &hooks();
@@ -124,15 +124,12 @@ bool igemm_act_fused(int dtype, const IgemmArgs &a);
 // statistics epilogue (the caller then runs a separate reduction pass).  Host only, depends on the shape alone.
 int igemm_stats_rows(int dtype, const IgemmArgs &a);
 // every layer whose channel runs are 16-byte granular and that has no kernel of its own (groups, src_ld, vec_out set)
-int launch_igemm_pipe(int dtype, const IgemmArgs &a, hipStream_t stream);
+int launch_igemm_pipe(int dtype, const IgemmArgs *a, int count, hipStream_t stream);
 int igemm_pipe_stats_rows(int dtype, const IgemmArgs &a);
-// bf16 large-tile kernel for wide layers (channel counts that are multiples of 64, enough tiles to fill the chip)
-bool igemm_big_applicable(int dtype, const IgemmArgs &a);
-int launch_igemm_big(const IgemmArgs &a, hipStream_t stream);
-int igemm_big_stats_rows(const IgemmArgs &a);
-// the residue classes of one strided backward-data pass (2..4 argument sets on the same tensors) in one launch
-bool igemm_big_multi_applicable(int dtype, const IgemmArgs *a, int count);
-int launch_igemm_big_multi(const IgemmArgs *a, int count, hipStream_t stream);
+// the residue classes of one strided backward-data pass (up to four argument sets on the same tensors) in one launch of it; a
+// class that no tap reaches (ntaps = 0) is filled with zeros
+bool igemm_pipe_multi_applicable(int dtype, const IgemmArgs *a, int count);
+int launch_igemm_pipe_multi(int dtype, const IgemmArgs *a, int count, hipStream_t stream);
 // bf16 layers with one, two or four taps and at most 256 reduction indices (memory-bound: filter resident in LDS,
 // pixels loaded straight into MFMA operand registers)
 bool conv_pw_applicable(int dtype, const IgemmArgs &a);

@@ -82,3 +82,51 @@ def test_every_tile_grouped(dtype, tile, nsk_env):
         c, k = slice(g * cg, (g + 1) * cg), slice(g * kg, (g + 1) * kg)
         assert max_rel_err(to_host(y, B.NSK_NHWC)[:, k], oracle.conv2d_fwd(x[:, c], w[k], 1, 1, 1)) <= TOL[dtype]
         assert max_rel_err(to_host(dx, B.NSK_NHWC)[:, c], oracle.conv2d_dgrad(dy[:, k], w[k], x[:, c].shape, 1, 1, 1)) <= TOL[dtype]
+
+
+# N, C, H, W, K, R, S, stride, pad: strided backward-data passes whose classes share a launch
+CLASSES = [
+    (2, 16, 9, 12, 24, 3, 3, 2, 1),            # four classes of 1, 2, 2, 4 taps, odd height
+    (3, 40, 10, 8, 32, 1, 1, 2, 0),            # one class with a tap, three that are only zeros
+    (2, 16, 7, 7, 16, 2, 2, 2, 0),             # cells past the last window belong to no tap
+    (1, 8, 11, 9, 24, 5, 3, (2, 1), (2, 1)),   # two classes
+]
+
+
+@pytest.mark.parametrize("tile", [0, 1, 4, 6])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("i", range(len(CLASSES)))
+def test_strided_backward_data_in_one_launch(i, dtype, tile, nsk_env):
+    nsk_env("NSK_IGEMM_TILE", str(tile))
+    N, C, H, W, K, R, S, st, pd = CLASSES[i]
+    w = on_grid(gen.he_normal(970 + i, 1, (K, C, R, S)), dtype)
+    P, Q = oracle.conv2d_out_dims((N, C, H, W), w.shape, st, pd, 1)
+    dy = on_grid(gen.normal(970 + i, 2, (N, K, P, Q)), dtype)
+    old = on_grid(gen.normal(970 + i, 3, (N, C, H, W)), dtype)
+    want = oracle.conv2d_dgrad(dy, w, (N, C, H, W), st, pd, 1)
+    for lay in (B.NSK_NHWC, B.NSK_NCHW):
+        gw, gdy, ws = to_gpu(w, dtype, lay), to_gpu(dy, dtype, lay), B.Workspace()
+        gold = to_gpu(old, dtype, lay)
+        for accumulate in (False, True):
+            dx, check = guarded(gold.shape, torch_dtype(dtype))
+            if accumulate:
+                dx.copy_(gold)
+            B.conv2d_dgrad(gdy, gw, (N, C, H, W), st, pd, 1, lay, out=dx, accumulate=accumulate, ws=ws)
+            torch.cuda.synchronize()
+            check()
+            got = to_host(dx, lay)
+            assert max_rel_err(got, want + old if accumulate else want) <= TOL[dtype]
+            if not accumulate:
+                assert np.all(got[want == 0.0] == 0.0)
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_f32_64_to_64_kernel_below_its_size(accumulate, nsk_env):
+    nsk_env("NSK_HALO64_ALWAYS", "1")
+    x, dy = (on_grid(gen.normal(975, t, (3, 64, 16, 32)), "f32") for t in (0, 2))
+    w = on_grid(gen.he_normal(975, 1, (64, 64, 3, 3)), "f32")
+    gx, gw, gdy = (to_gpu(a, "f32", B.NSK_NHWC) for a in (x, w, dy))
+    assert max_rel_err(to_host(B.conv2d_fwd(gx, gw, 1, 1), B.NSK_NHWC), oracle.conv2d_fwd(x, w, 1, 1, 1)) <= TOL["f32"]
+    want = oracle.conv2d_dgrad(dy, w, x.shape, 1, 1, 1) + (x if accumulate else 0)
+    dx = B.conv2d_dgrad(gdy, gw, x.shape, 1, 1, out=gx.clone(), accumulate=accumulate)
+    assert max_rel_err(to_host(dx, B.NSK_NHWC), want) <= TOL["f32"]
