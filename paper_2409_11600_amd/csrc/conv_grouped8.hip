@@ -1,0 +1,352 @@
+// Grouped 3x3 stride-1 layers with eight channels per group on both sides, bf16 (32 groups of 8 and their like): forward,
+// backward-data and backward-weight on the matrix units.
+//
+// What bounds them: memory (the contraction is 72 indices long).  The direct kernels of conv_depthwise.hip do 2 x 72
+// two-element dot products per eight outputs and read every input vector nine times through the L1: 84 us per data pass
+// and 153 us backward-weight for 256 channels at 28x28, N=128, whose operands stream in 20 us.  Here a strip of image
+// rows with its halo is copied into LDS once (straight from memory, 16 bytes per lane) and a 16x16x32 MFMA takes one
+// filter row of one group: its 32 reduction indices are four pixels x eight channels, exactly the 16-byte pieces a
+// lane reads, so nothing is shuffled.  Half of the matrix unit idles (eight output channels, three of four pixels),
+// which at 5 us of MFMA time does not matter.  No zero weight ever meets a real pixel (the fourth pixel is read from a
+// row of zeros, and so is everything past the end of a strip), so infinities stay where they belong.
+//
+// Measured (us, 256 channels at 28x28, N=128; direct kernels -> these): forward and backward-data 84.6 -> 30-35 (103 MB:
+// 3.0-3.4 TB/s), backward-weight 153.5 + 8.2 -> 45.0 + 4.8.
+//
+// Work: a block is 64 channels (eight groups, two per wavefront) of a strip of full image rows.
+#include "nsk_internal.h"
+
+namespace nsk {
+namespace {
+
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+
+constexpr int G8_ENTRIES = 480;        // pixels of a strip with halo: 60 KB of LDS, two blocks per CU
+constexpr int G8_WG_ENTRIES = 600;     // backward-weight: with the strip of dy 75 KB, two blocks per CU
+
+struct Div {       // n / d for 0 <= n < 2^31 as (n * mul) >> sh
+    unsigned mul;
+    int sh;
+};
+Div make_div(int d)
+{
+    int s = 0;
+    while ((1LL << s) < d) ++s;
+    Div r;
+    r.mul = (unsigned)(((1ULL << (31 + s)) + (unsigned)d - 1) / (unsigned)d);
+    r.sh = 31 + s;
+    return r;
+}
+__device__ inline int divide(int n, const Div &d) { return (int)(((unsigned long long)(unsigned)n * d.mul) >> d.sh); }
+
+struct G8Args {
+    const void *src, *wpk;
+    void *out;
+    int H, W, C, rows, strips, chunks;     // rows of a strip, strips of an image, 64-channel chunks
+    unsigned src_bytes, wpk_bytes, out_bytes;
+    unsigned long long taps;               // tap of window position 3*r + s, four bits each
+    int accumulate;
+    Div by_pw, by_w;                       // W + 2, W
+};
+
+// The strip with its halo, rows of eight 16-byte pieces per pixel: piece p of entry e lies at p ^ swap(e).
+template <typename F> __device__ inline void stage(__amdgpu_buffer_rsrc_t rsrc, unsigned char *lds, int entries, int wave, int lane, F offset_of)
+{
+    for (int i = wave; i * 8 < entries; i += 4) {
+        const int e = i * 8 + (lane >> 3);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(lds + i * 1024), 16, (int)offset_of(e, lane & 7), 0, 0, 0);
+    }
+}
+
+// every wavefront's direct loads and LDS writes have arrived
+__device__ inline void direct_loads_done()
+{
+    __builtin_amdgcn_s_waitcnt(7 << 4);
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(256) void grouped8_kernel(const G8Args a)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int chunk = blockIdx.x % a.chunks, rest = blockIdx.x / a.chunks;
+    const int strip = rest % a.strips, img = rest / a.strips;
+    const int h0 = strip * a.rows, rows = min(a.rows, a.H - h0), PW = a.W + 2;
+    const int entries = (rows + 2) * PW, zero = (entries + 7) & ~7;
+    const __amdgpu_buffer_rsrc_t src_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.src, 0, a.src_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wpk_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.wpk, 0, a.wpk_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t out_rsrc = __builtin_amdgcn_make_buffer_rsrc(a.out, 0, a.out_bytes, 0x00020000);
+    // sixteen neighbouring pixels are read at once: their pieces are exchanged so that they cover all banks
+    stage(src_rsrc, smem, entries, wave, lane, [&](int e, int slot) {
+        const int er = divide(e, a.by_pw), h = h0 - 1 + er, w = e - er * PW - 1;
+        const int ch = chunk * 64 + ((slot ^ (e >> 1)) & 7) * 8;
+        const unsigned bad = (unsigned)((h | (a.H - 1 - h) | w | (a.W - 1 - w) | (a.C - 1 - ch) | (entries - 1 - e)) >> 31);
+        return ((unsigned)(((img * a.H + h) * a.W + w) * a.C + ch) * 2u) | bad;
+    });
+    if (threadIdx.x < 8) *(f32x4 *)(smem + zero * 128 + threadIdx.x * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // filter rows: lane (output channel m = lane % 16, window column c = lane / 16) holds the eight input channels
+    const int m = lane & 15, c = lane >> 4;
+    bf16x8 wf[2][3];
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int k = chunk * 64 + (wave * 2 + g) * 8 + m;
+            const unsigned tap = (unsigned)(a.taps >> (4 * (3 * r + (c < 3 ? c : 0)))) & 15u;
+            const unsigned at = (m < 8 && c < 3 && k < a.C) ? (unsigned)(k * 72 + tap * 8) * 2u : ~0u;
+            wf[g][r] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wpk_rsrc, (int)at, 0, 0));
+        }
+    direct_loads_done();
+
+    const int pixels = rows * a.W;
+    const int ch = chunk * 64 + wave * 16 + (c & 1) * 4;                     // of the first group's results
+    const unsigned pix0 = (unsigned)((img * a.H + h0) * a.W);
+    for (int l0 = 0; l0 < pixels; l0 += 16) {
+        const int l = l0 + m, row = divide(l, a.by_w), e0 = row * PW + (l - row * a.W) + c;
+        const bool real = c < 3 && l < pixels;
+        const unsigned base = (pix0 + (unsigned)l) * (unsigned)a.C + (unsigned)ch;
+        unsigned at[2];
+        f32x4 acc[2];
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            at[g] = c < 2 && l < pixels && ch + 8 * g < a.C ? (base + 8u * g) * 2u : ~0u;
+            acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        if (a.accumulate) {     // start from the old values: one rounding
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                const bf16x4 old = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(out_rsrc, (int)at[g], 0, 0));
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[g][j] = (float)old[j];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int e = real ? e0 + r * PW : zero;
+            const unsigned char *p = smem + e * 128 + (((wave * 2) ^ (e >> 1)) & 7) * 16;
+            const bf16x8 b0 = *(const bf16x8 *)p;
+            const bf16x8 b1 = *(const bf16x8 *)(smem + ((unsigned)(p - smem) ^ 16u));
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[0][r], b0, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[1][r], b1, acc[1], 0, 0, 0);
+        }
+        // lane (pixel, quarter): rows 4*quarter .. of the result; quarters 2 and 3 hold nothing
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            bf16x4 o;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[j] = (bf16_t)acc[g][j];
+            typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), out_rsrc, (int)at[g], 0, 0);
+        }
+    }
+}
+
+// ---- backward-weight: dw[k][tap][c] of a group = sum over pixels of dy[pixel][k] * x[pixel + tap][c].  A wavefront takes two
+// groups: rows of the MFMA = their sixteen dy channels, columns = their sixteen x channels of one tap (the two off-diagonal
+// blocks are not stored), reduction = 32 consecutive pixels of the strip, through the transposing LDS read.
+struct G8WArgs {
+    const void *x, *dy;
+    float *part;
+    int H, W, C, rows, strips, chunks, tiles, splits;
+    unsigned x_bytes, dy_bytes;
+    unsigned long long taps;
+    Div by_pw, by_w, by_strips;
+};
+
+// within 32 lanes a transposing read serves the pixels 0..3 and 8..11 of a run, 32 bytes each: spread over all banks
+__device__ inline int g8_swap(int e) { return (e & 2) | ((e >> 1) & 4); }
+
+__global__ __launch_bounds__(256) void grouped8_wgrad_kernel(const G8WArgs a)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int chunk = blockIdx.x % a.chunks, split = blockIdx.x / a.chunks, PW = a.W + 2;
+    const int dy_at = (((a.rows + 2) * PW + 7) & ~7) * 128, zero = dy_at + ((a.rows * a.W + 7) & ~7) * 128;   // bytes
+    const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, a.x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t dy_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.dy, 0, a.dy_bytes, 0x00020000);
+    if (threadIdx.x < 8) *(f32x4 *)(smem + zero + threadIdx.x * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const int q = lane >> 4, i16 = lane & 15;
+    const int piece = wave * 2 + ((i16 & 3) >> 1), inner = (i16 & 1) * 8;
+    f32x4 sum[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) sum[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int tile = split; tile < a.tiles; tile += a.splits) {
+        const int img = divide(tile, a.by_strips), h0 = (tile - img * a.strips) * a.rows, rows = min(a.rows, a.H - h0);
+        const int entries = (rows + 2) * PW, pixels = rows * a.W;
+        __syncthreads();   // everybody has read the strip before
+        for (int i = wave; i * 8 < entries; i += 4) {
+            const int e = i * 8 + (lane >> 3), er = divide(e, a.by_pw), h = h0 - 1 + er, w = e - er * PW - 1;
+            const int ch = chunk * 64 + ((lane & 7) ^ g8_swap(e)) * 8;
+            const unsigned bad = (unsigned)((h | (a.H - 1 - h) | w | (a.W - 1 - w) | (a.C - 1 - ch) | (entries - 1 - e)) >> 31);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_void *)(smem + i * 1024), 16,
+                                                     (int)(((unsigned)(((img * a.H + h) * a.W + w) * a.C + ch) * 2u) | bad), 0, 0, 0);
+        }
+        for (int i = wave; i * 8 < pixels; i += 4) {
+            const int e = i * 8 + (lane >> 3);
+            const int ch = chunk * 64 + ((lane & 7) ^ g8_swap(e)) * 8;
+            const unsigned bad = (unsigned)(((a.C - 1 - ch) | (pixels - 1 - e)) >> 31);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(dy_rsrc, (lds_void *)(smem + dy_at + i * 1024), 16,
+                                                     (int)(((unsigned)(((img * a.H + h0) * a.W + e) * a.C + ch) * 2u) | bad), 0, 0, 0);
+        }
+        direct_loads_done();
+        f32x4 acc[9];
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int l0 = 0; l0 < pixels; l0 += 32) {
+            bf16x4 d[2];
+            int e[2];
+            bool real[2];
+#pragma unroll
+            for (int hi = 0; hi < 2; ++hi) {
+                const int l = l0 + 8 * q + 4 * hi + (i16 >> 2), row = divide(l, a.by_w);
+                real[hi] = l < pixels;
+                e[hi] = row * PW + (l - row * a.W);
+                const int at = real[hi] ? dy_at + l * 128 + (piece ^ g8_swap(l)) * 16 : zero;
+                d[hi] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(smem + at + inner));
+            }
+            const bf16x8 af = __builtin_shufflevector(d[0], d[1], 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                bf16x4 b[2];
+#pragma unroll
+                for (int hi = 0; hi < 2; ++hi) {
+                    const int en = e[hi] + (t / 3) * PW + t % 3;
+                    const int at = real[hi] ? en * 128 + (piece ^ g8_swap(en)) * 16 : zero;
+                    b[hi] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(smem + at + inner));
+                }
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, __builtin_shufflevector(b[0], b[1], 0, 1, 2, 3, 4, 5, 6, 7), acc[t], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 9; ++t) sum[t] += acc[t];      // (a strip's sum at a time: the chains stay short)
+    }
+    // result rows 4*q + j = dy channel, column i16 = x channel of the wavefront's sixteen: same group on the diagonal blocks
+    if ((q >> 1) == (i16 >> 3)) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            const int tap = (int)(a.taps >> (4 * t)) & 15;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int k = chunk * 64 + wave * 16 + 4 * q + j;
+                if (k < a.C) a.part[((size_t)split * a.C + k) * 72 + tap * 8 + (i16 & 7)] = sum[t][j];
+            }
+        }
+    }
+}
+
+// Rows of a strip so that `per_row` * rows + `fixed` entries stay within `most`; balanced over the image.
+int strip_rows(int H, int per_row, int fixed, int most)
+{
+    int rows = (most - fixed) / per_row;
+    if (rows < 1) return 0;
+    if (rows > H) rows = H;
+    return ceil_div(H, ceil_div(H, rows));
+}
+
+// window position 3*r + s -> tap, four bits each; false if the taps are not the nine of a 3x3 window around the pixel
+template <typename A> bool window_taps(const A &a, int add_h, int add_w, unsigned long long *taps)
+{
+    if (a.ntaps != 9) return false;
+    unsigned seen = 0;
+    unsigned long long v = 0;
+    for (int t = 0; t < 9; ++t) {
+        const int eh = add_h + a.off_h[t], ew = add_w + a.off_w[t];
+        if (eh < -1 || eh > 1 || ew < -1 || ew > 1) return false;
+        const int at = 3 * (eh + 1) + ew + 1;
+        seen |= 1u << at;
+        v |= (unsigned long long)t << (4 * at);
+    }
+    *taps = v;
+    return seen == 511u;
+}
+
+bool al16(const void *p) { return ((uintptr_t)p & 15) == 0; }
+
+}  // namespace
+
+bool grouped8_applicable(int dtype, const IgemmArgs &a)
+{
+    unsigned long long taps;
+    if (dtype != NSK_BF16 || hooks().no_depthwise || hooks().no_grouped8 || a.groups <= 1 || a.Cs != 8 || a.Ngemm != 8) return false;
+    const int C = 8 * a.groups;
+    if (a.src_ld != C || a.Co != C || a.Ktot != 72 || a.stats) return false;
+    if (a.mult_h != 1 || a.mult_w != 1 || a.osh != 1 || a.osw != 1 || a.oa != 0 || a.ob != 0) return false;
+    if (a.Hs != a.Ho || a.Ws != a.Wo || a.Mi != a.Ho || a.Mj != a.Wo) return false;
+    return window_taps(a, a.add_h, a.add_w, &taps) && strip_rows(a.Hs, a.Ws + 2, 2 * (a.Ws + 2), G8_ENTRIES) > 0 && al16(a.src) &&
+           al16(a.wpk) && al16(a.out);
+}
+
+int launch_grouped8(const IgemmArgs &a, hipStream_t stream)
+{
+    G8Args g{};
+    g.src = a.src; g.wpk = a.wpk; g.out = a.out;
+    g.H = a.Hs; g.W = a.Ws; g.C = 8 * a.groups;
+    g.rows = strip_rows(a.Hs, a.Ws + 2, 2 * (a.Ws + 2), G8_ENTRIES);
+    g.strips = ceil_div(a.Hs, g.rows);
+    g.chunks = ceil_div(g.C, 64);
+    g.src_bytes = a.src_bytes;
+    g.wpk_bytes = (unsigned)(g.C * 72 * 2);
+    g.out_bytes = (unsigned)((long)a.Nimg * a.Ho * a.Wo * a.Co * 2);
+    window_taps(a, a.add_h, a.add_w, &g.taps);
+    g.accumulate = a.accumulate;
+    g.by_pw = make_div(g.W + 2);
+    g.by_w = make_div(g.W);
+    const size_t smem = (size_t)((((g.rows + 2) * (g.W + 2) + 7) & ~7) + 1) * 128;
+    hipLaunchKernelGGL(grouped8_kernel, dim3((unsigned)(a.Nimg * g.strips * g.chunks)), dim3(256), smem, stream, g);
+    return check_launch();
+}
+
+// groups, ldx, ldy, C = K = 8 of one group
+bool grouped8_wgrad_applicable(int dtype, const WgradArgs &a)
+{
+    unsigned long long taps;
+    if (dtype != NSK_BF16 || hooks().no_depthwise || hooks().no_grouped8 || a.groups <= 1 || a.C != 8 || a.K != 8) return false;
+    if (a.ldx != 8 * a.groups || a.ldy != 8 * a.groups || a.sh != 1 || a.sw != 1 || a.P != a.H || a.Q != a.W) return false;
+    return window_taps(a, -a.ph, -a.pw, &taps) && strip_rows(a.H, 2 * a.W + 2, 2 * (a.W + 2) + 16, G8_WG_ENTRIES) > 0 && al16(a.x) && al16(a.dy);
+}
+
+int grouped8_wgrad_splits(const WgradArgs &a)
+{
+    const int rows = strip_rows(a.H, 2 * a.W + 2, 2 * (a.W + 2) + 16, G8_WG_ENTRIES);
+    const int tiles = a.Nimg * ceil_div(a.H, rows);
+    // two blocks per CU
+    int splits = 512 / ceil_div(8 * a.groups, 64);
+    if (splits < 1) splits = 1;
+    return splits < tiles ? splits : tiles;
+}
+
+int launch_grouped8_wgrad(const WgradArgs &a, hipStream_t stream)
+{
+    G8WArgs g{};
+    g.x = a.x; g.dy = a.dy; g.part = a.part;
+    g.H = a.H; g.W = a.W; g.C = 8 * a.groups;
+    g.rows = strip_rows(a.H, 2 * a.W + 2, 2 * (a.W + 2) + 16, G8_WG_ENTRIES);
+    g.strips = ceil_div(a.H, g.rows);
+    g.chunks = ceil_div(g.C, 64);
+    g.tiles = a.Nimg * g.strips;
+    g.splits = a.splits;
+    g.x_bytes = g.dy_bytes = (unsigned)((long)a.Nimg * a.H * a.W * g.C * 2);
+    window_taps(a, -a.ph, -a.pw, &g.taps);
+    g.by_pw = make_div(g.W + 2);
+    g.by_w = make_div(g.W);
+    g.by_strips = make_div(g.strips);
+    const size_t smem = (size_t)((((g.rows + 2) * (g.W + 2) + 7) & ~7) + ((g.rows * g.W + 7) & ~7) + 1) * 128;
+    static bool attr_set = false;
+    if (!attr_set) {
+        const hipError_t e = hipFuncSetAttribute((const void *)grouped8_wgrad_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+        if (e != hipSuccess) {
+            set_last_hip_error(e);
+            return NSK_ERR_HIP;
+        }
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(grouped8_wgrad_kernel, dim3((unsigned)(g.chunks * g.splits)), dim3(256), smem, stream, g);
+    return check_launch();
+}
+
+}  // namespace nsk

@@ -439,6 +439,7 @@ int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream)
     if (special && conv_pw_applicable(dtype, a)) return launch_conv_pw(a, stream);
     if (special && halo_wide_applicable(dtype, a)) return launch_halo_wide(a, stream);
     if (special && halo_wide_fwd_s2_applicable(dtype, a)) return launch_halo_wide_fwd_s2(a, stream);
+    if (grouped && hooks().igemm_tile == 0 && grouped8_applicable(dtype, a)) return launch_grouped8(a, stream);
     if (grouped && hooks().igemm_tile == 0 && !hooks().no_depthwise && depthwise_applicable(dtype, a))
         return launch_depthwise(dtype, a, stream);
     IgemmArgs b = a;

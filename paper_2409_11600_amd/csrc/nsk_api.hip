@@ -90,6 +90,7 @@ struct ConvPlan {
     int splits = 1, rows_per_split = 0;
     bool halo = false;   // wgrad: the 3x3 64->64 kernel writes one partial per block
     bool pipe = false;   // wgrad: the pipelined kernel
+    bool grouped8 = false;   // wgrad: the kernel for groups of eight channels
     bool stem = false;   // the space-to-depth path plans its own workspace
     size_t act_tmp = 0;  // fused-activation calls on a kernel without the fused load: the applied activation
     bool act_fused = false;
@@ -156,14 +157,17 @@ ConvPlan plan_conv(const ConvGeo &g, int pass, int groups = 1, bool act = false)
             one.C = g.C / groups; one.K = g.K / groups;
             one.groups = groups; one.ldx = g.C; one.ldy = g.K;
             one.splits = 1;
-            const bool direct = tiny_wgrad_applicable(g.dtype, one) || (!hooks().no_depthwise && depthwise_wgrad_applicable(g.dtype, one));
+            p.grouped8 = grouped8_wgrad_applicable(g.dtype, one);
+            const bool direct = p.grouped8 || tiny_wgrad_applicable(g.dtype, one) || (!hooks().no_depthwise && depthwise_wgrad_applicable(g.dtype, one));
             p.pipe = !direct && wgrad_pipe_applicable(g.dtype, one.C, one.K, groups);
-            if (p.pipe)
+            if (p.grouped8)
+                p.splits = grouped8_wgrad_splits(one);
+            else if (p.pipe)
                 p.rows_per_split = wgrad_pipe_rows_per_split(g.dtype, one.L, one.K, one.ntaps * one.C, groups, &p.splits);
             else
                 p.rows_per_split = wgrad_rows_per_split(g.dtype, one.L, g.K, one.ntaps * one.C, &p.splits);
         }
-        if (!p.pipe && groups > 1 && g.C == g.K && (g.C == groups || g.C == 2 * groups || g.C == 4 * groups || g.C == 8 * groups)) {
+        if (!p.pipe && !p.grouped8 && groups > 1 && g.C == g.K && (g.C == groups || g.C == 2 * groups || g.C == 4 * groups || g.C == 8 * groups)) {
             // depthwise and its neighbours: the direct kernel runs blocks of 16 channel vectors x one split and wants
             // about four per CU
             const int vec = g.dtype == NSK_BF16 ? 8 : 4, L = g.N * g.P * g.Q;
@@ -174,7 +178,7 @@ ConvPlan plan_conv(const ConvGeo &g, int pass, int groups = 1, bool act = false)
             p.splits = ceil_div(L, p.rows_per_split);
         }
         // a grouped launch puts groups * splits on gridDim.z
-        while (!p.pipe && (long)groups * p.splits > 65535) {
+        while (!p.pipe && !p.grouped8 && (long)groups * p.splits > 65535) {
             p.rows_per_split *= 2;
             p.splits = ceil_div(g.N * g.P * g.Q, p.rows_per_split);
         }
@@ -386,6 +390,7 @@ void read_hooks()
     h.no_stem_halo = on("NSK_NO_STEM_HALO");
     h.no_tiny = on("NSK_NO_TINY");
     h.no_depthwise = on("NSK_NO_DEPTHWISE");
+    h.no_grouped8 = on("NSK_NO_GROUPED8");
     h.depthwise_no_rows = on("NSK_DEPTHWISE_NO_ROWS");
     h.depthwise_no_cols = on("NSK_DEPTHWISE_NO_COLS");
     h.pool_general = on("NSK_POOL_GENERAL");
@@ -664,6 +669,8 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
         NSK_TRY(launch_wgrad_halo64(g.dtype, a, st));
     else if (p.pipe)
         NSK_TRY(launch_wgrad_pipe(g.dtype, a, st));
+    else if (p.grouped8)
+        NSK_TRY(launch_grouped8_wgrad(a, st));
     else
         NSK_TRY(launch_wgrad(g.dtype, a, st));
     const long RS = (long)g.R * g.S;

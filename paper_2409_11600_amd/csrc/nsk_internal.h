@@ -48,7 +48,7 @@ __device__ inline void lds_barrier()
 // the launch path.  Each one only narrows or widens the choice among kernels that all compute the same result.
 struct TestHooks {
     bool no_pw, no_halo, no_fs, no_halo_wide, halo_wide_always, halo64_always, halo_single, no_stem, no_stem_halo,
-        no_tiny, no_depthwise, depthwise_no_rows, depthwise_no_cols, pool_general, stats_always, reduce4,
+        no_tiny, no_depthwise, no_grouped8, depthwise_no_rows, depthwise_no_cols, pool_general, stats_always, reduce4,
         wh_no_split;
     long long pw_min_rows, wh_min_rows;   // -1: not set
     int igemm_tile;                                         // 0: not set
@@ -174,6 +174,10 @@ int launch_tiny_out(int dtype, const IgemmArgs &a, hipStream_t stream);
 bool depthwise_applicable(int dtype, const IgemmArgs &a);
 int launch_depthwise(int dtype, const IgemmArgs &a, hipStream_t stream);
 
+// grouped bf16 3x3 stride-1 layers with eight channels per group on both sides: matrix units, strips of rows in LDS
+bool grouped8_applicable(int dtype, const IgemmArgs &a);
+int launch_grouped8(const IgemmArgs &a, hipStream_t stream);
+
 // ------------------------------------------------------------------ wgrad
 // part[split][k][t][c] = sum over the split's share of rows l = (img, p, q) of
 //   dy[img][p][q][k] * x[img][p*sh - ph + off_h[t]][q*sw - pw + off_w[t]][c]
@@ -215,6 +219,10 @@ int launch_tiny_wgrad(int dtype, const WgradArgs &a, hipStream_t stream);
 // depthwise layers: partial sums in the layout of the generic kernel's grouped launch
 bool depthwise_wgrad_applicable(int dtype, const WgradArgs &a);
 int launch_depthwise_wgrad(int dtype, const WgradArgs &a, hipStream_t stream);
+// grouped bf16 3x3 stride-1 layers with eight channels per group: partial sums in the same layout, splits of its own
+bool grouped8_wgrad_applicable(int dtype, const WgradArgs &a);
+int grouped8_wgrad_splits(const WgradArgs &a);
+int launch_grouped8_wgrad(const WgradArgs &a, hipStream_t stream);
 // dw[k*sk + t*st + c*sc] (=|+=) sum_s part[s][k][t][c], fixed order.
 int launch_wgrad_reduce(const float *part, float *dw, int splits, int K, int ntaps, int C,
                         long sk, long st, long sc, int accumulate, hipStream_t stream);
