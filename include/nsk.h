@@ -411,6 +411,17 @@ int nsk_gru_step_bwd(int dtype, int N, int H, const void *saved, const void *h_p
                      const void *dh_direct_next, const void *dgh_next, const void *w_hh_t, void *dgi, void *dgh,
                      void *dh_direct, void *stream);
 
+/* All T steps of the recurrence, forward and backward, in one call each (same gate convention, layouts and sizes as the
+ * step calls, whose nsk_gru_step_supported also speaks for these; N*H elements must be a multiple of 16 bytes so that every
+ * step's rows are aligned).  Up to 256 hidden units a call is a single launch in which a block runs one sample through all
+ * steps; above, it issues the T step launches.
+ * forward: gi [T,N,3H]; h [T+1,N,H] holds the initial state in h[0] and receives h[1..T]; saved [T,N,4H].
+ * backward: dh_top [N,H] is the gradient of h[T]; dgi, dgh [T,N,3H] are written; dh_scratch [2,N,H] of `dtype` is scratch. */
+int nsk_gru_seq_fwd(int dtype, int T, int N, int H, const void *gi, const void *w_hh, const float *b_ih, const float *b_hh,
+                    void *h, void *saved, void *stream);
+int nsk_gru_seq_bwd(int dtype, int T, int N, int H, const void *saved, const void *h, const void *dh_top, const void *w_hh_t,
+                    void *dgi, void *dgh, void *dh_scratch, void *stream);
+
 /* ---------------------------------------------------------------------------------------------------------------
  * Device memory pool and cache (section "Caching and Pooling"): what hands out the raw pointers every entry point
  * above takes, for callers that have no allocator of their own.  Host code; no entry point above uses it.

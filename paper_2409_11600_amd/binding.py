@@ -189,6 +189,10 @@ def lib() -> ctypes.CDLL:
         L.nsk_gru_step_fwd.argtypes = [ci, ci, ci, vp, vp, vp, vp, vp, vp, vp, vp]
         L.nsk_gru_step_bwd.restype = ci
         L.nsk_gru_step_bwd.argtypes = [ci, ci, ci, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+        L.nsk_gru_seq_fwd.restype = ci
+        L.nsk_gru_seq_fwd.argtypes = [ci, ci, ci, ci, vp, vp, vp, vp, vp, vp, vp]
+        L.nsk_gru_seq_bwd.restype = ci
+        L.nsk_gru_seq_bwd.argtypes = [ci, ci, ci, ci, vp, vp, vp, vp, vp, vp, vp, vp]
         vpp, szp = ctypes.POINTER(vp), ctypes.POINTER(sz)
         L.nsk_pool_create.restype = ci
         L.nsk_pool_create.argtypes = [ci, vpp]
@@ -220,7 +224,7 @@ EXPORTS = ("nsk_version", "nsk_test_hooks_reload", "nsk_status_string", "nsk_las
            "nsk_linear_dgrad", "nsk_linear_wgrad", "nsk_transpose2d", "nsk_softmax_xent_fwd", "nsk_softmax_xent_bwd",
            "nsk_sgd_momentum_step", "nsk_adamw_step", "nsk_sgd_momentum_step_multi", "nsk_adamw_step_multi", "nsk_sumsq_accumulate", "nsk_clip_scale",
            "nsk_embedding_fwd", "nsk_embedding_bwd", "nsk_gru_gates_fwd", "nsk_gru_gates_bwd",
-           "nsk_gru_step_supported", "nsk_gru_step_fwd", "nsk_gru_step_bwd",
+           "nsk_gru_step_supported", "nsk_gru_step_fwd", "nsk_gru_step_bwd", "nsk_gru_seq_fwd", "nsk_gru_seq_bwd",
            "nsk_pool_create", "nsk_pool_get", "nsk_pool_put", "nsk_pool_cached", "nsk_pool_stats", "nsk_pool_destroy")
 NSK_POOL_DEVICE, NSK_POOL_HOST = 0, 1
 NSK_SUMSQ_PARTIALS = 256
@@ -865,6 +869,20 @@ def gru_step_bwd(saved, h_prev, w_hh_t, dh_a=None, dh_direct_next=None, dgh_next
                                   _ptr(dh_direct_next), _ptr(dgh_next), _ptr(w_hh_t), _ptr(dgi), _ptr(dgh), _ptr(dh_direct),
                                   _stream()), "nsk_gru_step_bwd")
     return dgi, dgh, dh_direct
+
+
+def gru_seq_fwd(gi, w_hh, b_ih, b_hh, h, saved):
+    """All steps: gi [T,N,3H]; h [T+1,N,H] with the initial state in h[0]; fills h[1:] and saved [T,N,4H]."""
+    T, N, H = h.shape[0] - 1, h.shape[1], h.shape[2]
+    _check(lib().nsk_gru_seq_fwd(_dtype_code(h), int(T), int(N), int(H), _ptr(gi), _ptr(w_hh), _ptr(b_ih), _ptr(b_hh), _ptr(h),
+                                 _ptr(saved), _stream()), "nsk_gru_seq_fwd")
+
+
+def gru_seq_bwd(saved, h, dh_top, w_hh_t, dgi, dgh, dh_scratch):
+    """All steps in reverse: dh_top [N,H] is the gradient of h[T]; fills dgi and dgh [T,N,3H]; dh_scratch [2,N,H]."""
+    T, N, H = h.shape[0] - 1, h.shape[1], h.shape[2]
+    _check(lib().nsk_gru_seq_bwd(_dtype_code(h), int(T), int(N), int(H), _ptr(saved), _ptr(h), _ptr(dh_top), _ptr(w_hh_t),
+                                 _ptr(dgi), _ptr(dgh), _ptr(dh_scratch), _stream()), "nsk_gru_seq_bwd")
 
 
 # ------------------------------------------------------------------------------------ memory pool

@@ -2,9 +2,9 @@
 backward through time, gradient clip and AdamW (the recipe of the paper's section "Experiments and Discussion").
 
 Sequencing and buffer management only: every arithmetic step is a libnsk entry point.  The input products of all time
-steps are one matrix product (x @ W_ih over T*N rows); each step then costs one product (h @ W_hh) and one fused gate
-kernel, and in the backward pass one gate kernel and one product (dgh @ W_hh, by the backward-data form of the `@`
-operator); the four weight and bias gradients and the gradient of the embedded input are again single products over
+steps are one matrix product (x @ W_ih over T*N rows); the recurrence is one call per direction (nsk_gru_seq_*) where
+the sizes allow it, else each step costs one product (h @ W_hh) and one gate kernel, and in the backward pass one gate
+kernel and one product (dgh @ W_hh, by the backward-data form of the `@` operator); the four weight and bias gradients and the gradient of the embedded input are again single products over
 all T*N rows.  All buffers are created in the constructor; a step allocates nothing and can be captured into a HIP
 graph.
 """
@@ -54,7 +54,8 @@ class GpuGruClassifier:
         self.loss = torch.zeros(1, dtype=torch.float32, device=dev)
         self.dh_top = z(N, H)
         self.dgi, self.dgh = z(T * N, 3 * H), z(T * N, 3 * H)
-        self.dh_direct, self.dh_rec = [z(N, H), z(N, H)], [z(N, H), z(N, H)]
+        self.dh_scratch = z(2, N, H)
+        self.dh_direct, self.dh_rec = [self.dh_scratch[0], self.dh_scratch[1]], [z(N, H), z(N, H)]
         self.dx = z(T * N, E)
         self.ws = B.Workspace(dev)
         order = ["table", "w_ih", "w_hh", "w_out", "b_ih", "b_hh", "b_out"]
@@ -76,10 +77,9 @@ class GpuGruClassifier:
         B.embedding_fwd(self.tokens, w["table"], out=self.x)
         B.linear_fwd(self.x, w["w_ih"], None, out=self.gi, ws=self.ws)
         gi = self.gi.view(T, N, 3 * H)
-        for t in range(T):
-            if self.fused_steps:
-                B.gru_step_fwd(gi[t], w["w_hh"], w["b_ih"], w["b_hh"], self.h[t], h_new=self.h[t + 1], saved=self.saved[t])
-                continue
+        if self.fused_steps:
+            B.gru_seq_fwd(gi, w["w_hh"], w["b_ih"], w["b_hh"], self.h, self.saved)
+        for t in range(0 if self.fused_steps else T):
             B.linear_dgrad(self.h[t], self.w_hh_t, out=self.gh, ws=self.ws)      # h @ W_hh (see w_hh_t)
             B.gru_gates_fwd(gi[t], self.gh, w["b_ih"], w["b_hh"], self.h[t], h_new=self.h[t + 1], saved=self.saved[t])
         B.linear_fwd(self.h[T], w["w_out"], w["b_out"], out=self.logits, ws=self.ws)
@@ -91,14 +91,10 @@ class GpuGruClassifier:
         B.linear_wgrad(self.h[T], self.dlogits, dw=g["w_out"], db=g["b_out"], ws=self.ws)
         B.linear_dgrad(self.dlogits, w["w_out"], out=self.dh_top, ws=self.ws)
         dgi, dgh = self.dgi.view(T, N, 3 * H), self.dgh.view(T, N, 3 * H)
-        for t in reversed(range(T)):
+        if self.fused_steps:
+            B.gru_seq_bwd(self.saved, self.h, self.dh_top, self.w_hh_t, dgi, dgh, self.dh_scratch)
+        for t in reversed(range(0 if self.fused_steps else T)):
             p = t & 1
-            if self.fused_steps:
-                last = t == T - 1
-                B.gru_step_bwd(self.saved[t], self.h[t], self.w_hh_t, dh_a=self.dh_top if last else None,
-                               dh_direct_next=None if last else self.dh_direct[p ^ 1], dgh_next=None if last else dgh[t + 1],
-                               dgi=dgi[t], dgh=dgh[t], dh_direct=self.dh_direct[p])
-                continue
             if t == T - 1:
                 B.gru_gates_bwd(self.saved[t], self.h[t], self.dh_top, dgi=dgi[t], dgh=dgh[t], dh_direct=self.dh_direct[p])
             else:                                            # the two parts of the gradient the step after this one left
