@@ -316,6 +316,14 @@ int launch_tile(const IgemmArgs &a, hipStream_t stream)
     return check_launch();
 }
 
+// What the output rows are made of: whole 16-byte vectors (1), whole 8-byte ones (2, bf16), neither (0).
+int output_vectors(int dtype, const IgemmArgs &a)
+{
+    const int vec = dtype == NSK_BF16 ? 8 : 4;
+    if ((uintptr_t)a.out % 16 != 0 || a.Ngemm % 4 != 0 || a.Co % 4 != 0) return 0;
+    return a.Ngemm % vec == 0 && a.Co % vec == 0 ? 1 : 2;
+}
+
 // Channel runs and filter rows on 16-byte boundaries: the pipelined kernel takes the launch.  (For a grouped launch
 // Cs % VEC == 0 also puts every group's channel run and filter rows on such boundaries.)
 bool vector_runs(int dtype, const IgemmArgs &a)
@@ -374,13 +382,14 @@ int igemm_stats_rows(int dtype, const IgemmArgs &a)
     }
     // Both generic kernels need the vector epilogue and 16-byte stores of the partial sums; one row per wavefront row of every
     // row block.
-    const int vec = dtype == NSK_BF16 ? 8 : 4;
-    if (!(a.Ngemm % vec == 0 && a.Co % vec == 0 && (uintptr_t)a.out % 16 == 0)) return 0;
+    const int vectors = output_vectors(dtype, a);
+    if (vectors == 0) return 0;
     // The pipelined kernel's epilogue beats the separate pass over y at every size (us, convolution + batch-norm, pass /
     // epilogue: 256->1024 1x1 at 14x14 N=128 69.6 / 69.4, 64->128 1x1 stride 2 at 56x56 N=64 29.2 / 25.1, fp32 16->16 at
     // 40x42 N=37 22.5 / 20.8, 72->104 at 29x37 N=20 34.0 / 20.5; 256->64 at 56x56 N=64, 3136 rows of sums, 50.1 / 51.5).
     if (vector_runs(dtype, a)) return igemm_pipe_stats_rows(dtype, a);
     // The element-wise kernel's, with its short reductions, does not (the variable is a test hook).
+    if (vectors != 1) return 0;
     if (a.Ktot < 1024 && !hooks().stats_always) return 0;
     static const int bm[3] = {256, 128, 128}, wm[3] = {64, 32, 64};
     const int t = auto_tile(a, dtype == NSK_BF16 ? 2 : 4);
@@ -411,14 +420,13 @@ bool igemm_pipe_multi_applicable(int dtype, const IgemmArgs *a, int count)
 int launch_igemm_pipe_multi(int dtype, const IgemmArgs *a, int count, hipStream_t stream)
 {
     IgemmArgs b[4];
-    const int vec = dtype == NSK_BF16 ? 8 : 4;
     for (int i = 0; i < count; ++i) {
         b[i] = a[i];
         if (b[i].groups <= 1) {
             b[i].groups = 1;
             b[i].src_ld = b[i].Cs;
         }
-        b[i].vec_out = (b[i].Ngemm % vec == 0 && b[i].Co % vec == 0 && (uintptr_t)b[i].out % 16 == 0) ? 1 : 0;
+        b[i].vec_out = output_vectors(dtype, b[i]);
     }
     return launch_igemm_pipe(dtype, b, count, stream);
 }
@@ -447,9 +455,9 @@ int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream)
         b.groups = 1;
         b.src_ld = b.Cs;
     }
-    const int vec = dtype == NSK_BF16 ? 8 : 4;
-    b.vec_out = (b.Ngemm % vec == 0 && b.Co % vec == 0 && (uintptr_t)b.out % 16 == 0) ? 1 : 0;
+    b.vec_out = output_vectors(dtype, b);
     if (vector_runs(dtype, b)) return launch_igemm_pipe(dtype, &b, 1, stream);
+    b.vec_out = b.vec_out == 1 ? 1 : 0;
     return dtype == NSK_BF16 ? launch_typed<bf16_t>(b, stream) : launch_typed<float>(b, stream);
 }
 

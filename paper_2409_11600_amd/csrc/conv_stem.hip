@@ -341,7 +341,7 @@ int stem_dgrad(const ConvGeo &g, const void *dy, const void *w, void *dx, int ac
     const StemPlan p = stem_plan(g, s, NSK_PASS_DGRAD);
     const void *src = dy;
     if (g.layout == NSK_NCHW) {
-        STEM_TRY(launch_nchw_to_nhwc(g.dtype, dy, ws + p.act, g.N, g.K, g.P, g.Q, st));
+        STEM_TRY(launch_nchw_to_nhwc(g.dtype, dy, ws + p.act, g.N, g.K, g.P, g.Q, g.K, st));
         src = ws + p.act;
     }
     STEM_TRY(pack_filter<1>(g, s, w, ws + p.w2, st));
@@ -378,7 +378,7 @@ int stem_wgrad(const ConvGeo &g, const void *x, const void *dy, float *dw, int a
     STEM_TRY(space_to_depth(g, s, x, ws + p.x2, st));
     const void *dys = dy;
     if (g.layout == NSK_NCHW) {
-        STEM_TRY(launch_nchw_to_nhwc(g.dtype, dy, ws + p.act, g.N, g.K, g.P, g.Q, st));
+        STEM_TRY(launch_nchw_to_nhwc(g.dtype, dy, ws + p.act, g.N, g.K, g.P, g.Q, g.K, st));
         dys = ws + p.act;
     }
     WgradArgs a{};
@@ -395,7 +395,7 @@ int stem_wgrad(const ConvGeo &g, const void *x, const void *dy, float *dw, int a
         STEM_TRY(launch_wgrad(s.dtype, a, st));
     }
     float *dw2 = (float *)(ws + p.dw2);
-    STEM_TRY(launch_wgrad_reduce(a.part, dw2, p.splits, s.K, a.ntaps, SC, (long)a.ntaps * SC, (long)SC, 1L, 0, st));
+    STEM_TRY(launch_wgrad_reduce(a.part, dw2, p.splits, s.K, s.K, a.ntaps, SC, SC, (long)a.ntaps * SC, (long)SC, 1L, 0, st));
     long sk, sc, sr, ss;
     filter_strides(g, &sk, &sc, &sr, &ss);
     const int total = s.K * s.C * s.R * s.R;

@@ -204,25 +204,26 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a)
 // dw[...] (=|+=) sum over splits of part[split][i], splits taken in four interleaved groups that
 // are combined in a fixed order (reproducible).  One block covers 64 consecutive outputs.
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restrict__ part, float *__restrict__ dw,
-                                                            int splits, int K, int ntaps, int C, long sk, long st,
+                                                            int splits, long step, int K, int ntaps, int C, int Cp, long sk, long st,
                                                             long sc, int accumulate)
 {
     __shared__ float red[4][64];
-    const long total = (long)K * ntaps * C;
+    const long total = (long)K * ntaps * Cp;
     const int g = threadIdx.x >> 6;
     const long i = (long)blockIdx.x * 64 + (threadIdx.x & 63);
     float s = 0.f;
     if (i < total)
 #pragma unroll 8
-        for (int sp = g; sp < splits; sp += 4) s += part[(long)sp * total + i];
+        for (int sp = g; sp < splits; sp += 4) s += part[(long)sp * step + i];
     red[g][threadIdx.x & 63] = s;
     __syncthreads();
     if (g != 0 || i >= total) return;
     s = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
-    const int c = (int)(i % C);
-    const long r = i / C;
+    const int c = (int)(i % Cp);
+    const long r = i / Cp;
     const int t = (int)(r % ntaps);
     const long k = r / ntaps;
+    if (c >= C) return;
     float *o = dw + k * sk + t * st + c * sc;
     *o = accumulate ? *o + s : s;
 }
@@ -255,27 +256,28 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float *__re
 // network: a few thousand outputs, hundreds of splits): 16 interleaved groups of splits instead of four, so that a lane's
 // chain of dependent loads is a quarter as long.  One block covers 16 consecutive outputs; fixed order as above.
 __global__ __launch_bounds__(256) void wgrad_reduce16_kernel(const float *__restrict__ part, float *__restrict__ dw,
-                                                              int splits, int K, int ntaps, int C, long sk, long st,
+                                                              int splits, long step, int K, int ntaps, int C, int Cp, long sk, long st,
                                                               long sc, int accumulate)
 {
     __shared__ float red[16][16];
-    const long total = (long)K * ntaps * C;
+    const long total = (long)K * ntaps * Cp;
     const int g = threadIdx.x >> 4, j = threadIdx.x & 15;
     const long i = (long)blockIdx.x * 16 + j;
     float s = 0.f;
     if (i < total)
 #pragma unroll 4
-        for (int sp = g; sp < splits; sp += 16) s += part[(long)sp * total + i];
+        for (int sp = g; sp < splits; sp += 16) s += part[(long)sp * step + i];
     red[g][j] = s;
     __syncthreads();
     if (g != 0 || i >= total) return;
     float r = 0.f;
 #pragma unroll
     for (int q = 0; q < 16; q += 4) r += (red[q][j] + red[q + 1][j]) + (red[q + 2][j] + red[q + 3][j]);
-    const int c = (int)(i % C);
-    const long rr = i / C;
+    const int c = (int)(i % Cp);
+    const long rr = i / Cp;
     const int t = (int)(rr % ntaps);
     const long k = rr / ntaps;
+    if (c >= C) return;
     float *o = dw + k * sk + t * st + c * sc;
     *o = accumulate ? *o + r : r;
 }
@@ -326,12 +328,12 @@ int launch_wgrad(int dtype, const WgradArgs &a0, hipStream_t stream)
     return launch_wgrad_typed<float>(a, stream);
 }
 
-int launch_wgrad_reduce(const float *part, float *dw, int splits, int K, int ntaps, int C, long sk,
+int launch_wgrad_reduce(const float *part, float *dw, int splits, int K, int Kp, int ntaps, int C, int Cp, long sk,
                         long st, long sc, int accumulate, hipStream_t stream)
 {
-    const long total = (long)K * ntaps * C;
+    const long total = (long)K * ntaps * Cp, step = (long)Kp * ntaps * Cp;
     // dw in the order of the partial sums: vector loads (bitwise the same sums); enough blocks to cover the chip
-    const bool flat = sc == 1 && st == (long)C && sk == (long)ntaps * C && !hooks().reduce4 &&
+    const bool flat = C == Cp && K == Kp && sc == 1 && st == (long)C && sk == (long)ntaps * C && !hooks().reduce4 &&
                       (((uintptr_t)part | (uintptr_t)dw) & 15) == 0;
     if (flat && total % 4 == 0 && total >= 4 * 64 * 512) {
         hipLaunchKernelGGL(wgrad_reduce_vec_kernel<4>, dim3((unsigned)((total / 4 + 63) / 64)), dim3(256), 0, stream, part, dw, splits, total, accumulate);
@@ -343,10 +345,10 @@ int launch_wgrad_reduce(const float *part, float *dw, int splits, int K, int nta
     }
     if (total <= 16384 && splits >= 64 && !hooks().reduce4)   // (the variable is an A/B hook)
         hipLaunchKernelGGL(wgrad_reduce16_kernel, dim3((unsigned)((total + 15) / 16)), dim3(256), 0, stream, part, dw,
-                           splits, K, ntaps, C, sk, st, sc, accumulate);
+                           splits, step, K, ntaps, C, Cp, sk, st, sc, accumulate);
     else
         hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)((total + 63) / 64)), dim3(256), 0, stream, part, dw,
-                           splits, K, ntaps, C, sk, st, sc, accumulate);
+                           splits, step, K, ntaps, C, Cp, sk, st, sc, accumulate);
     return check_launch();
 }
 

@@ -79,10 +79,39 @@ bool use_wgrad_halo(const ConvGeo &g, const WgradArgs &a, bool act)
     return a.L >= (hooks().wh_min_rows >= 0 ? hooks().wh_min_rows : g.dtype == NSK_BF16 ? 150000 : 55000);
 }
 
+bool whole_vectors(const ConvGeo &g, int channels) { return channels % (g.dtype == NSK_BF16 ? 8 : 4) == 0; }
+
+// The layer as the kernels see it: where the channels that the pass reads are not whole 16-byte vectors (of x in the forward
+// pass, of dy backward, of both for the weights), the operands are copied into the workspace with zero channels up to the
+// next whole one, and the kernels for whole vectors run: the copy is a pass at memory speed and a launch, where the
+// element-wise kernels take 3 to 40 times their time.  Measured (us, element-wise / copy and whole vectors; forward, weights,
+// backward): bf16 3x3 100->100 at 28x28 N=32 174, 125, 186 / 20, 29, 21; 300->300 stride 2 at 14x14 N=16 506, 45, 555 /
+// 24, 22, 20; 1x1 20->100 at 28x28 N=64 28, 28, 36 / 14, 20, 15; 3x3 20->20 at 7x7 N=1 27, 11, 30 / 9, 9, 9; fp32 3x3 30->30 at
+// 28x28 N=64 49, 49, 51 / 25, 38, 25.  Up to four channels have kernels of their own; 5 and 6 in fp32 gain nothing
+// (3x3 5->48 at 56x56 N=64 36, 46, 76 / 51, 44, 75).
+ConvGeo padded_geometry(const ConvGeo &g, int pass, int groups)
+{
+    const int vec = g.dtype == NSK_BF16 ? 8 : 4;
+    const int least = g.dtype == NSK_BF16 ? 4 : 6;
+    const bool pad_c = pass != NSK_PASS_DGRAD && !whole_vectors(g, g.C), pad_k = pass != NSK_PASS_FWD && !whole_vectors(g, g.K);
+    if (groups > 1 || !(pad_c || pad_k) || stem_applicable(g) || hooks().no_pad) return g;
+    if ((pad_c && g.C <= least) || (pad_k && g.K <= least)) return g;
+    ConvGeo p = g;
+    if (pad_c) p.C = ceil_div(g.C, vec) * vec;
+    if (pad_k) p.K = ceil_div(g.K, vec) * vec;
+    const size_t pix_in = (size_t)g.N * g.H * g.W, pix_out = (size_t)g.N * g.P * g.Q;
+    p.x_elems = pix_in * p.C;
+    p.y_elems = pix_out * p.K;
+    p.w_elems = (size_t)p.K * g.R * g.S * p.C;
+    // (the limits of conv_geometry)
+    if (p.x_elems * 4 >= 0xFFFFFFFFull || p.y_elems * 4 >= 0xFFFFFFFFull || p.w_elems >= (size_t)INT_MAX) return g;
+    return p;
+}
+
 // Workspace segments (byte offsets, each 256-aligned).
 struct ConvPlan {
-    size_t act_in = 0;   // NHWC copy of the NCHW input activation (x or dy)
-    size_t act_in2 = 0;  // wgrad only: NHWC copy of dy
+    size_t act_in = 0;   // NHWC copy of the NCHW input activation (x or dy), or its copy with whole channel vectors
+    size_t act_in2 = 0;  // wgrad only: the same of dy
     size_t filt = 0;     // packed filter
     size_t act_out = 0;  // NHWC result before conversion to NCHW
     size_t part = 0;     // wgrad partial sums
@@ -102,9 +131,11 @@ void fwd_geometry(const ConvGeo &g, IgemmArgs *a);
 
 // act: the call applies a batch-norm + ReLU to x on load (NHWC, one group); where the kernel that takes the layer has no
 // fused load the activation is applied into the workspace first.
-ConvPlan plan_conv(const ConvGeo &g, int pass, int groups = 1, bool act = false)
+ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = false)
 {
     ConvPlan p;
+    const ConvGeo g = padded_geometry(desc, pass, groups);
+    const bool pad_c = g.C != desc.C, pad_k = g.K != desc.K;
     const size_t w_elems = g.w_elems / (size_t)groups;
     p.stem = groups == 1 && stem_applicable(g);
     size_t off = 0;
@@ -124,7 +155,7 @@ ConvPlan plan_conv(const ConvGeo &g, int pass, int groups = 1, bool act = false)
             wgrad_geometry(g, &wa);
             p.act_fused = use_wgrad_halo(g, wa, true) && wgrad_halo64_act_fused(g.dtype, wa);
         }
-        if (!p.act_fused) p.act_tmp = take(g.x_elems * g.es);
+        if (!p.act_fused) p.act_tmp = take(desc.x_elems * g.es);
     }
     if (p.stem) {
         p.total = off + stem_workspace_bytes(g, pass);
@@ -132,21 +163,19 @@ ConvPlan plan_conv(const ConvGeo &g, int pass, int groups = 1, bool act = false)
     }
     const bool nchw = g.layout == NSK_NCHW;
     if (pass == NSK_PASS_FWD) {
-        if (nchw) {
+        if (nchw || pad_c) {
             p.act_in = take(g.x_elems * g.es);
             p.filt = take(w_elems * g.es);
-            p.act_out = take(g.y_elems * g.es);
         }
+        if (nchw) p.act_out = take(g.y_elems * g.es);
     } else if (pass == NSK_PASS_DGRAD) {
-        if (nchw) p.act_in = take(g.y_elems * g.es);
+        if (nchw || pad_k) p.act_in = take(g.y_elems * g.es);
         // one packed filter per stride parity class; together they hold every tap once
         p.filt = take(w_elems * g.es + 256 * (size_t)g.sh * g.sw);
         if (nchw) p.act_out = take(g.x_elems * g.es);
     } else {
-        if (nchw) {
-            p.act_in = take(g.x_elems * g.es);
-            p.act_in2 = take(g.y_elems * g.es);
-        }
+        if (nchw || pad_c) p.act_in = take(g.x_elems * g.es);
+        if (nchw || pad_k) p.act_in2 = take(g.y_elems * g.es);
         WgradArgs wa{};
         wgrad_geometry(g, &wa);
         p.halo = groups == 1 && use_wgrad_halo(g, wa, act);
@@ -267,7 +296,7 @@ int conv_stats_rows(const ConvGeo &g, bool *fused = nullptr)
         rows = stem_stats_rows(g);
     } else {
         IgemmArgs a{};
-        fwd_geometry(g, &a);
+        fwd_geometry(padded_geometry(g, NSK_PASS_FWD, 1), &a);
         rows = igemm_stats_rows(g.dtype, a);
     }
     if (fused) *fused = rows > 0;
@@ -332,18 +361,23 @@ int conv_fwd_impl(const nsk_conv_desc_t *desc, int groups, const void *x, const 
 
     const void *src = x, *filt = w;
     void *dst = y;
-    if (g.layout == NSK_NCHW) {
-        NSK_TRY(launch_nchw_to_nhwc(g.dtype, x, ws + p.act_in, g.N, g.C, g.H, g.W, st));
+    const ConvGeo gp = padded_geometry(g, NSK_PASS_FWD, groups);
+    const bool nchw = g.layout == NSK_NCHW;
+    if (nchw || gp.C != g.C) {
+        if (nchw)
+            NSK_TRY(launch_nchw_to_nhwc(g.dtype, x, ws + p.act_in, g.N, g.C, g.H, g.W, gp.C, st));
+        else
+            NSK_TRY(launch_pad_channels(g.dtype, x, ws + p.act_in, (long)g.N * g.H * g.W, g.C, gp.C, st));
         int tap_off[kMaxTaps];
-        for (int t = 0; t < g.R * g.S; ++t) tap_off[t] = t;
-        NSK_TRY(launch_pack_filter(g.dtype, w, ws + p.filt, g.K, g.R * g.S, cg, (long)cg * g.R * g.S,
-                                   (long)g.R * g.S, tap_off, st));
+        for (int t = 0; t < g.R * g.S; ++t) tap_off[t] = nchw ? t : t * cg;
+        NSK_TRY(launch_pack_filter(g.dtype, w, ws + p.filt, g.K, g.R * g.S, gp.C / groups, cg, (long)cg * g.R * g.S,
+                                   nchw ? (long)g.R * g.S : 1L, tap_off, st));
         src = ws + p.act_in;
         filt = ws + p.filt;
-        dst = ws + p.act_out;
+        if (nchw) dst = ws + p.act_out;
     }
     IgemmArgs a{};
-    fwd_geometry(g, &a);
+    fwd_geometry(gp, &a);
     a.src = src; a.wpk = filt; a.out = dst;
     if (groups > 1) {   // `groups` problems of cg -> kg channels on channel runs of the same tensors
         a.groups = groups;
@@ -360,7 +394,7 @@ int conv_fwd_impl(const nsk_conv_desc_t *desc, int groups, const void *x, const 
     a.act = act;
     NSK_TRY(launch_igemm(g.dtype, a, st));
     if (stats && !fused) NSK_TRY(launch_bn_stats(output_as_bn(g), dst, stats, st));
-    if (g.layout == NSK_NCHW) NSK_TRY(launch_nhwc_to_nchw(g.dtype, dst, y, g.N, g.K, g.P, g.Q, 0, st));
+    if (nchw) NSK_TRY(launch_nhwc_to_nchw(g.dtype, dst, y, g.N, g.K, g.P, g.Q, 0, st));
     return NSK_OK;
 }
 
@@ -391,6 +425,7 @@ void read_hooks()
     h.no_tiny = on("NSK_NO_TINY");
     h.no_depthwise = on("NSK_NO_DEPTHWISE");
     h.no_grouped8 = on("NSK_NO_GROUPED8");
+    h.no_pad = on("NSK_NO_PAD");
     h.depthwise_no_rows = on("NSK_DEPTHWISE_NO_ROWS");
     h.depthwise_no_cols = on("NSK_DEPTHWISE_NO_COLS");
     h.pool_general = on("NSK_POOL_GENERAL");
@@ -484,7 +519,8 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     if (accumulate != 0 && accumulate != 1) return NSK_ERR_BAD_DESC;
     if (misaligned(dy) || misaligned(w) || misaligned(dx)) return NSK_ERR_ALIGNMENT;
     const ConvPlan p = plan_conv(g, NSK_PASS_DGRAD, groups);
-    const int cg = g.C / groups, kg = g.K / groups;   // channels of one group (all of them for a plain convolution)
+    const ConvGeo gp = padded_geometry(g, NSK_PASS_DGRAD, groups);
+    const int cg = g.C / groups, kg = gp.K / groups;   // channels of one group (all of them for a plain convolution)
     NSK_TRY(check_ws(workspace, workspace_bytes, p.total));
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
@@ -495,10 +531,13 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     void *dst = dx;
     int acc_kernel = accumulate;
     if (nchw) {
-        NSK_TRY(launch_nchw_to_nhwc(g.dtype, dy, ws + p.act_in, g.N, g.K, g.P, g.Q, st));
+        NSK_TRY(launch_nchw_to_nhwc(g.dtype, dy, ws + p.act_in, g.N, g.K, g.P, g.Q, gp.K, st));
         src = ws + p.act_in;
         dst = ws + p.act_out;
         acc_kernel = 0;  // the conversion back to NCHW does the add
+    } else if (gp.K != g.K) {
+        NSK_TRY(launch_pad_channels(g.dtype, dy, ws + p.act_in, (long)g.N * g.P * g.Q, g.K, gp.K, st));
+        src = ws + p.act_in;
     }
     // dx[h] with h = a + sh*i receives dy[p] * w[r] exactly for the taps r with
     // (a + ph - r*dh) divisible by sh, at p = i + (a + ph - r*dh)/sh: one dense sub-problem per
@@ -527,11 +566,11 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
         a->Ngemm = cg;
         if (groups > 1) {
             a->groups = groups;
-            a->src_ld = g.K;
+            a->src_ld = g.K;   // (grouped layers are not padded)
         }
         a->Ho = g.H; a->Wo = g.W; a->Co = g.C; a->osh = g.sh; a->oa = ca; a->osw = g.sw; a->ob = cb;
         a->accumulate = acc_kernel;
-        a->src_bytes = (unsigned)(g.y_elems * g.es);
+        a->src_bytes = (unsigned)(gp.y_elems * g.es);
         a->wpk_bytes = (unsigned)((size_t)g.C * nt * kg * g.es);
         return nt;
     };
@@ -550,7 +589,8 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     }
     // element (k, tap, c) of the filter: k * w_sc + tap_off + c * w_sn; one group's filters are w_gstep elements long
     const long w_sn = nchw ? (long)g.R * g.S : 1L, w_sc = (long)g.R * g.S * cg;
-    const long w_gstep = (long)kg * w_sc;
+    const int kr = g.K / groups;
+    const long w_gstep = (long)kr * w_sc;
     size_t filt_off = p.filt;
     // classes with taps: filters are packed first, then the launches follow (one for all classes where the large-tile
     // kernel takes them together)
@@ -587,14 +627,14 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
                 int taps1[1][kMaxTaps];
                 for (int t = 0; t < kMaxTaps; ++t) taps1[0][t] = t < nt ? tap_off[t] : 0;
                 void *out1[1] = {ws + filt_off};
-                NSK_TRY(launch_pack_filters_grouped(g.dtype, 1, w, out1, cg, &nt, kg, w_sn, w_sc, taps1, groups, w_gstep, st));
+                NSK_TRY(launch_pack_filters_grouped(g.dtype, 1, w, out1, cg, &nt, kg, kr, w_sn, w_sc, taps1, groups, w_gstep, st));
                 NSK_TRY(launch_igemm(g.dtype, a, st));
             }
             filt_off += align_up((size_t)g.C * nt * kg * g.es);
         }
     // one packing launch for all classes, then their multiplies
     if (n_pending > 0)
-        NSK_TRY(launch_pack_filters_grouped(g.dtype, n_pending, w, pk_out, cg, pk_nt, kg, w_sn, w_sc, pk_taps, groups, w_gstep, st));
+        NSK_TRY(launch_pack_filters_grouped(g.dtype, n_pending, w, pk_out, cg, pk_nt, kg, kr, w_sn, w_sc, pk_taps, groups, w_gstep, st));
     if (n_pending == 4 && groups == 1 && fs64_dgrad_s2_applicable(g.dtype, pending, n_pending)) {
         NSK_TRY(launch_fs64_dgrad_s2(pending, n_pending, st));
     } else if (n_pending > 1 && groups == 1 && halo_wide_multi_applicable(g.dtype, pending, n_pending)) {
@@ -637,16 +677,21 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     const bool nchw = g.layout == NSK_NCHW;
     if (p.stem) return stem_wgrad(g, x, dy, dw, accumulate, ws, st);
     const void *xs = x, *dys = dy;
+    const ConvGeo gp = padded_geometry(g, NSK_PASS_WGRAD, groups);
+    const bool pad_c = gp.C != g.C, pad_k = gp.K != g.K;
     if (nchw) {
-        NSK_TRY(launch_nchw_to_nhwc(g.dtype, x, ws + p.act_in, g.N, g.C, g.H, g.W, st));
-        NSK_TRY(launch_nchw_to_nhwc(g.dtype, dy, ws + p.act_in2, g.N, g.K, g.P, g.Q, st));
-        xs = ws + p.act_in;
-        dys = ws + p.act_in2;
+        NSK_TRY(launch_nchw_to_nhwc(g.dtype, x, ws + p.act_in, g.N, g.C, g.H, g.W, gp.C, st));
+        NSK_TRY(launch_nchw_to_nhwc(g.dtype, dy, ws + p.act_in2, g.N, g.K, g.P, g.Q, gp.K, st));
+    } else {
+        if (pad_c) NSK_TRY(launch_pad_channels(g.dtype, x, ws + p.act_in, (long)g.N * g.H * g.W, g.C, gp.C, st));
+        if (pad_k) NSK_TRY(launch_pad_channels(g.dtype, dy, ws + p.act_in2, (long)g.N * g.P * g.Q, g.K, gp.K, st));
     }
+    if (nchw || pad_c) xs = ws + p.act_in;
+    if (nchw || pad_k) dys = ws + p.act_in2;
     WgradArgs a{};
     a.x = xs; a.dy = dys; a.part = (float *)(ws + p.part);
     a.act = act;
-    wgrad_geometry(g, &a);
+    wgrad_geometry(gp, &a);
     a.rows_per_split = p.rows_per_split;
     a.splits = p.splits;
     if (groups > 1) {   // `groups` problems of cg x kg channels; their partial sums stack to [splits][K][taps * cg]
@@ -658,10 +703,10 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     }
     if (p.pipe && groups <= 1) {
         a.groups = 1;
-        a.ldx = g.C;
-        a.ldy = g.K;
+        a.ldx = gp.C;
+        a.ldy = gp.K;
     }
-    if (p.pipe && p.splits == 1 && !nchw && !accumulate) {   // one partial sum in the order of dw: it is the result
+    if (p.pipe && p.splits == 1 && !nchw && !accumulate && !pad_c && !pad_k) {   // one partial sum in the order of dw: it is the result
         a.part = dw;
         return launch_wgrad_pipe(g.dtype, a, st);
     }
@@ -675,9 +720,9 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
         NSK_TRY(launch_wgrad(g.dtype, a, st));
     const long RS = (long)g.R * g.S;
     if (nchw)
-        NSK_TRY(launch_wgrad_reduce(a.part, dw, p.splits, g.K, a.ntaps, cg, (long)cg * RS, 1L, RS, accumulate, st));
+        NSK_TRY(launch_wgrad_reduce(a.part, dw, p.splits, g.K, gp.K, a.ntaps, cg, gp.C / groups, (long)cg * RS, 1L, RS, accumulate, st));
     else
-        NSK_TRY(launch_wgrad_reduce(a.part, dw, p.splits, g.K, a.ntaps, cg, RS * cg, (long)cg, 1L, accumulate, st));
+        NSK_TRY(launch_wgrad_reduce(a.part, dw, p.splits, g.K, gp.K, a.ntaps, cg, gp.C / groups, RS * cg, (long)cg, 1L, accumulate, st));
     return NSK_OK;
 }
 

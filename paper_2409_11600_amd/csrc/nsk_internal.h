@@ -48,7 +48,7 @@ __device__ inline void lds_barrier()
 // the launch path.  Each one only narrows or widens the choice among kernels that all compute the same result.
 struct TestHooks {
     bool no_pw, no_halo, no_fs, no_halo_wide, halo_wide_always, halo64_always, halo_single, no_stem, no_stem_halo,
-        no_tiny, no_depthwise, no_grouped8, depthwise_no_rows, depthwise_no_cols, pool_general, stats_always, reduce4,
+        no_tiny, no_depthwise, no_grouped8, no_pad, depthwise_no_rows, depthwise_no_cols, pool_general, stats_always, reduce4,
         wh_no_split;
     long long pw_min_rows, wh_min_rows;   // -1: not set
     int igemm_tile;                                         // 0: not set
@@ -94,7 +94,7 @@ struct IgemmArgs {
     int Ho, Wo, Co;
     int osh, oa, osw, ob;
     int accumulate;
-    int vec_out;  // set by launch_igemm: output rows are 16-byte granular, vector epilogue
+    int vec_out;  // set by launch_igemm: output rows are 16-byte granular (1) or, pipelined bf16 kernel, 8-byte granular (2): vector epilogue
     unsigned src_bytes, wpk_bytes;  // sizes of src and wpk (both below 4 GiB: buffer addressing)
     // Optional per-channel partial sums of the STORED output for a following batch-norm: stats[0][r][n] = sum and
     // stats[1][r][n] = sum of squares over the r-th disjoint share of the rows, r < stats_rows.  Only set when
@@ -223,8 +223,8 @@ int launch_depthwise_wgrad(int dtype, const WgradArgs &a, hipStream_t stream);
 bool grouped8_wgrad_applicable(int dtype, const WgradArgs &a);
 int grouped8_wgrad_splits(const WgradArgs &a);
 int launch_grouped8_wgrad(const WgradArgs &a, hipStream_t stream);
-// dw[k*sk + t*st + c*sc] (=|+=) sum_s part[s][k][t][c], fixed order.
-int launch_wgrad_reduce(const float *part, float *dw, int splits, int K, int ntaps, int C,
+// dw[k*sk + t*st + c*sc] (=|+=) sum_s part[s][k][t][c], k < K, c < C, fixed order; part is [splits][Kp][ntaps][Cp].
+int launch_wgrad_reduce(const float *part, float *dw, int splits, int K, int Kp, int ntaps, int C, int Cp,
                         long sk, long st, long sc, int accumulate, hipStream_t stream);
 
 // ------------------------------------------------------------------ image stem
@@ -248,20 +248,20 @@ int launch_stem_halo(int backward, const void *src, const void *wpk, void *out, 
 int stem_halo_stats_rows(int Nimg, int H, int W);
 
 // ------------------------------------------------------------------ layout helpers
-// dst NHWC <- src NCHW (plain copy).
-int launch_nchw_to_nhwc(int dtype, const void *src, void *dst, int N, int C, int H, int W,
+// dst NHWC with Cp >= C channels per pixel (those from C on are zeros) <- src NCHW.
+int launch_nchw_to_nhwc(int dtype, const void *src, void *dst, int N, int C, int H, int W, int Cp,
                         hipStream_t stream);
+// dst [rows][Cp] <- src [rows][C], zeros from C on; Cp elements are a multiple of 16 bytes.
+int launch_pad_channels(int dtype, const void *src, void *dst, long rows, int C, int Cp, hipStream_t stream);
 // dst NCHW (=|+=) src NHWC.
 int launch_nhwc_to_nchw(int dtype, const void *src, void *dst, int N, int C, int H, int W,
                         int accumulate, hipStream_t stream);
-// out[n][t][c] = w[n*sn + tap_off[t] + c*sc] for n < Nn, t < ntaps, c < Cs.
-int launch_pack_filter(int dtype, const void *w, void *out, int Nn, int ntaps, int Cs, long sn,
+// out[n][t][c] = w[n*sn + tap_off[t] + c*sc] for n < Nn, t < ntaps, c < Cr, and 0 for Cr <= c < Cs.
+int launch_pack_filter(int dtype, const void *w, void *out, int Nn, int ntaps, int Cs, int Cr, long sn,
                        long sc, const int *tap_off_host, hipStream_t stream);
-// The same for up to four tap subsets of one filter in one launch: out[k][n][t][c] with ntaps[k] taps tap_off_host[k][.].
-int launch_pack_filters(int dtype, int count, const void *w, void *const *out, int Nn, const int *ntaps, int Cs, long sn,
-                        long sc, const int (*tap_off_host)[kMaxTaps], hipStream_t stream);
-// The same for `groups` filters that lie w_gstep elements apart in w: out[k][g][n][t][c] = w[g*w_gstep + n*sn + ...].
-int launch_pack_filters_grouped(int dtype, int count, const void *w, void *const *out, int Nn, const int *ntaps, int Cs,
+// The same for up to four tap subsets of one filter in one launch, out[k][..][n][t][c] with ntaps[k] taps tap_off_host[k][.],
+// and for `groups` filters that lie w_gstep elements apart in w: out[k][g][n][t][c] = w[g*w_gstep + n*sn + ...].
+int launch_pack_filters_grouped(int dtype, int count, const void *w, void *const *out, int Nn, const int *ntaps, int Cs, int Cr,
                                 long sn, long sc, const int (*tap_off_host)[kMaxTaps], int groups, long w_gstep,
                                 hipStream_t stream);
 
