@@ -13,23 +13,17 @@
 // E[(x-s)^2] - E[x-s]^2 does not cancel badly, and the per-block partials are combined in fp64 in
 // a fixed order (reproducible, no atomics).
 //
-// Two code paths: a vectorised NHWC path (16-byte accesses, a thread keeps the same channels for
-// all its rows) and a generic strided path that serves NCHW and channel counts the fast path
-// cannot tile.
+// Two code paths: a vectorised NHWC path (16-byte accesses, 8-byte ones in bf16 where C % 8 is 4; a
+// thread keeps the same channels for all its rows) and a generic strided path that serves NCHW and
+// channel counts that are not a multiple of four.
+#include <type_traits>
+
 #include "nsk_internal.h"
 
 namespace nsk {
 namespace {
 
-template <typename T> struct BT;
-template <> struct BT<float> {
-    static constexpr int VEC = 4;
-    typedef f32x4 Vec;
-};
-template <> struct BT<bf16_t> {
-    static constexpr int VEC = 8;
-    typedef bf16x8 Vec;
-};
+template <typename T, int V> using VecOf = T __attribute__((ext_vector_type(V)));
 
 __device__ inline float wave_sum(float v)
 {
@@ -46,6 +40,8 @@ __device__ inline double wave_sum_f64(double v)
     return v;
 }
 
+// Channel counts whose vectors divide a block: the calls that hand a ReLU mask or an activation's coefficients from pass to
+// pass take these.
 bool nhwc_fast(const nsk_bn_desc_t &d)
 {
     if (d.layout != NSK_NHWC) return false;
@@ -55,12 +51,43 @@ bool nhwc_fast(const nsk_bn_desc_t &d)
     return cv <= 256 && 256 % cv == 0;
 }
 
-// ----------------------------------------------------------------------------- NHWC fast path
+// Elements per access of the NHWC path, 0: the generic path, which a small tensor's three launches are no worse off with (us,
+// forward / backward, generic / NHWC: bf16 24 channels, 8 images of 14x14 7.9, 8.0 / 9.9, 10.3; fp32 48 channels, 4 of 28x28,
+// 150 k elements, 8.4, 9.5 / 8.5, 9.4).
+int nhwc_vec(const nsk_bn_desc_t &d)
+{
+    if (d.layout != NSK_NHWC || d.C % 4) return 0;
+    if (!nhwc_fast(d) && (long)d.N * d.H * d.W * d.C < (128L << 10)) return 0;
+    return d.dtype == NSK_BF16 && d.C % 8 == 0 ? 8 : 4;
+}
+
+// ----------------------------------------------------------------------------- NHWC path
+// A block of 256 threads covers RP whole rows of the (up to 256) channel vectors of its chunk blockIdx.y: thread t has vector
+// t % CV of row t / CV, and keeps it.  Where CV does not divide 256 the last 256 % CV threads idle, which costs less than the
+// generic path's strided element accesses.  Measured with ReLU, 64 images of 28x28, forward, backward (us, generic / here):
+// bf16 96 channels 39, 96 / 16, 25, 100 channels 38, 91 / 15, 28; fp32 100 channels 43, 105 / 18, 35; bf16 1000 channels, 7x7
+// 36, 83 / 22, 29; 96 channels at 56x56 behind a convolution that left 3136 rows of sums 55, 358 / 25, 60.
+struct Tile {
+    int cv0, CV, RP, cv, rr;
+    bool live;
+};
+template <int V> __device__ inline Tile tile_of(int C)
+{
+    Tile t;
+    t.cv0 = blockIdx.y * 256;
+    t.CV = min(C / V - t.cv0, 256);
+    t.RP = 256 / t.CV;
+    t.rr = threadIdx.x / t.CV;
+    t.cv = threadIdx.x - t.rr * t.CV;
+    t.live = t.rr < t.RP;
+    t.cv += t.cv0;
+    return t;
+}
 
 // Accumulates, per channel, sum(f0) and sum(f1) over the rows of this block, where (f0,f1) is
 //   MODE 0 (forward stats):  (x - shift, (x - shift)^2)
 //   MODE 1 (backward)     :  (dz, dz * xhat)
-template <typename T, int MODE>
+template <typename T, int VEC, int MODE>
 __global__ __launch_bounds__(256) void bn_reduce_nhwc(const T *__restrict__ x, const T *__restrict__ out,
                                                       const T *__restrict__ dout, const float *__restrict__ mean,
                                                       const float *__restrict__ invstd, int relu, long M, int C,
@@ -69,10 +96,9 @@ __global__ __launch_bounds__(256) void bn_reduce_nhwc(const T *__restrict__ x, c
                                                       const unsigned char *__restrict__ mask_in, int noshift = 0,
                                                       const float *__restrict__ act = nullptr)
 {
-    typedef typename BT<T>::Vec Vec;
-    constexpr int VEC = BT<T>::VEC;
-    const int CV = C / VEC, RP = 256 / CV;
-    const int cv = threadIdx.x % CV, rr = threadIdx.x / CV;
+    typedef VecOf<T, VEC> Vec;
+    const Tile t = tile_of<VEC>(C);
+    const int cv = t.live ? t.cv : t.cv0, RP = t.RP;
     float s0[VEC], s1[VEC], sh[VEC], sc[VEC], as[VEC], ab[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
@@ -91,9 +117,9 @@ __global__ __launch_bounds__(256) void bn_reduce_nhwc(const T *__restrict__ x, c
         }
     }
     const long r_begin = (long)blockIdx.x * rows_per_block;
-    const long r_end = min(M, r_begin + rows_per_block);
+    const long r_end = t.live ? min(M, r_begin + rows_per_block) : 0;
 #pragma unroll 4
-    for (long r = r_begin + rr; r < r_end; r += RP) {
+    for (long r = r_begin + t.rr; r < r_end; r += RP) {
         const long off = r * C + cv * VEC;
         const Vec xv = *(const Vec *)(x + off);
         if (MODE == 0) {
@@ -117,7 +143,7 @@ __global__ __launch_bounds__(256) void bn_reduce_nhwc(const T *__restrict__ x, c
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) bits |= ((float)ov[e] > 0.f ? 1u : 0u) << e;
                 // one byte per vector: the apply pass reads this instead of `out` (an eighth or a sixteenth of its bytes)
-                mask[off / VEC] = (unsigned char)bits;
+                if (mask) mask[off / VEC] = (unsigned char)bits;
             }
 #pragma unroll
             for (int e = 0; e < VEC; ++e) {
@@ -135,36 +161,38 @@ __global__ __launch_bounds__(256) void bn_reduce_nhwc(const T *__restrict__ x, c
         red1[threadIdx.x * VEC + e] = s1[e];
     }
     __syncthreads();
-    // thread t < C sums column t over the RP row groups (row group rr holds channels at rr*C..)
-    for (int c = threadIdx.x; c < C; c += 256) {
+    // the columns of the chunk are summed over the RP row groups (row group rr holds its channels at rr*CC..)
+    const int CC = t.CV * VEC, c0 = t.cv0 * VEC;
+    for (int c = threadIdx.x; c < CC; c += 256) {
         float a0 = 0.f, a1 = 0.f;
+#pragma unroll 8
         for (int g = 0; g < RP; ++g) {
-            a0 += red0[g * C + c];
-            a1 += red1[g * C + c];
+            a0 += red0[g * CC + c];
+            a1 += red1[g * CC + c];
         }
-        p0[(long)blockIdx.x * C + c] = a0;
-        p1[(long)blockIdx.x * C + c] = a1;
+        p0[(long)blockIdx.x * C + c0 + c] = a0;
+        p1[(long)blockIdx.x * C + c0 + c] = a1;
     }
 }
 
-template <typename T, bool HAS_RES, bool RELU>
+template <typename T, int VEC, bool HAS_RES, bool RELU>
 __global__ __launch_bounds__(256) void bn_apply_nhwc(const T *__restrict__ x, const T *__restrict__ res,
                                                      T *__restrict__ out, const float *__restrict__ scale,
                                                      const float *__restrict__ bias, long nvec, int C,
                                                      unsigned char *__restrict__ mask)
 {
-    typedef typename BT<T>::Vec Vec;
-    constexpr int VEC = BT<T>::VEC;
-    // C/VEC divides 256 and the grid stride is a multiple of 256 vectors, so a thread always sees
-    // the same VEC channels: their coefficients live in registers.
-    const int c0 = (threadIdx.x % (C / VEC)) * VEC;
+    typedef VecOf<T, VEC> Vec;
+    // a thread always sees the same VEC channels: their coefficients live in registers
+    const Tile t = tile_of<VEC>(C);
+    if (!t.live) return;
+    const int c0 = t.cv * VEC, CV = C / VEC;
     float sc[VEC], bi[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
         sc[e] = scale[c0 + e];
         bi[e] = bias[c0 + e];
     }
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < nvec; i += (long)gridDim.x * 256) {
+    for (long i = ((long)blockIdx.x * t.RP + t.rr) * CV + t.cv; i < nvec; i += (long)gridDim.x * t.RP * CV) {
         const Vec xv = __builtin_nontemporal_load((const Vec *)(x + i * VEC));
         Vec rv;
         if (HAS_RES) rv = __builtin_nontemporal_load((const Vec *)(res + i * VEC));
@@ -184,7 +212,8 @@ __global__ __launch_bounds__(256) void bn_apply_nhwc(const T *__restrict__ x, co
 }
 
 // dx = a*(dz - b - xhat*cc) with a = gamma*invstd, b = dbeta/M, cc = dgamma/M ; dres = dz
-template <typename T, bool HAS_RES, bool RELU>
+// RELU: 0 none, 1 with the mask of the reduction or forward pass, 2 from the sign of out
+template <typename T, int VEC, bool HAS_RES, int RELU>
 __global__ __launch_bounds__(256) void bn_bwd_apply_nhwc(const T *__restrict__ x, const T *__restrict__ out,
                                                          const T *__restrict__ dout, T *__restrict__ dx,
                                                          T *__restrict__ dres, const float *__restrict__ mean,
@@ -192,9 +221,10 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_nhwc(const T *__restrict__ x
                                                          const float *__restrict__ coef, long nvec, int C,
                                                          const unsigned char *__restrict__ mask)
 {
-    typedef typename BT<T>::Vec Vec;
-    constexpr int VEC = BT<T>::VEC;
-    const int c0 = (threadIdx.x % (C / VEC)) * VEC;   // fixed per thread, see bn_apply_nhwc
+    typedef VecOf<T, VEC> Vec;
+    const Tile t = tile_of<VEC>(C);
+    if (!t.live) return;
+    const int c0 = t.cv * VEC, CV = C / VEC;   // fixed per thread, see bn_apply_nhwc
     float mu[VEC], is[VEC], ka[VEC], kb[VEC], kc[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
@@ -204,12 +234,18 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_nhwc(const T *__restrict__ x
         kb[e] = coef[C + c0 + e];
         kc[e] = coef[2 * C + c0 + e];
     }
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < nvec; i += (long)gridDim.x * 256) {
+    for (long i = ((long)blockIdx.x * t.RP + t.rr) * CV + t.cv; i < nvec; i += (long)gridDim.x * t.RP * CV) {
         const Vec xv = __builtin_nontemporal_load((const Vec *)(x + i * VEC));
         const Vec gv = __builtin_nontemporal_load((const Vec *)(dout + i * VEC));
         // ReLU mask of these VEC elements, written by the reduction pass (bit e set: out > 0)
         unsigned bits = ~0u;
-        if (RELU) bits = __builtin_nontemporal_load(mask + i);
+        if (RELU == 1) bits = __builtin_nontemporal_load(mask + i);
+        if (RELU == 2) {
+            const Vec ov = __builtin_nontemporal_load((const Vec *)(out + i * VEC));
+            bits = 0;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) bits |= ((float)ov[e] > 0.f ? 1u : 0u) << e;
+        }
         Vec dxv, drv;
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
@@ -404,8 +440,9 @@ __global__ __launch_bounds__(256) void bn_bwd_finalize(const float *__restrict__
 struct Geom {
     long M, HW, total;
     int G;
-    bool fast;
-    long rows_per_block;  // fast path
+    int vec;              // NHWC path: elements per access (0: generic path)
+    int chunks, RP;       // NHWC path: chunks of 256 vectors in a row, rows a block covers at a time
+    long rows_per_block;
     int npg;              // generic path: images per partial block
     long sn, sc, ss;
 };
@@ -416,19 +453,24 @@ Geom geometry(const nsk_bn_desc_t &d, bool backward)
     g.HW = (long)d.H * d.W;
     g.M = (long)d.N * g.HW;
     g.total = g.M * d.C;
-    g.fast = nhwc_fast(d);
-    if (g.fast) {
-        const int VEC = d.dtype == NSK_BF16 ? 8 : 4;
-        const int RP = 256 / (d.C / VEC);
+    g.vec = nhwc_vec(d);
+    if (g.vec) {
+        const int cv = d.C / g.vec, RP = cv < 256 ? 256 / cv : 1;
+        g.chunks = ceil_div(cv, 256);
+        g.RP = RP;
         // at least four passes of its 256 threads per block (measured on the 2-8 MB tensors of the CIFAR-sized network:
         // eight passes leave one block per CU there and the whole step 1.5% slower; two are no better than four)
         long G = (g.M + (long)RP * 4 - 1) / ((long)RP * 4);
+        // few rows: one pass, while that makes no more than 64 blocks (bf16 64 channels, 4 images of 28x28, backward 12.7 -> 10.7)
+        if (G < 64) G = (g.M + RP - 1) / RP < 64 ? (g.M + RP - 1) / RP : 64;
         // Measured: the forward statistics pass over a large tensor (one input stream) is fastest with eight blocks
         // per CU, the backward pass (three input streams) and small tensors with two.
         // More blocks also mean more partial sums for the finalize kernel to read (G x C floats, twice): the larger
         // count is only used while that stays within 2 MB per array.
         long cap = (!backward && g.total >= (16L << 20)) ? 2048 : 512;
         if (cap * d.C > (512L << 10)) cap = 512;
+        // (other channel counts, up to 65535, stay within 2 MB per array throughout: 8 blocks of 32 chunks at the most)
+        if (!nhwc_fast(d) && cap * d.C > (512L << 10)) cap = (512L << 10) / d.C;
         if (G > cap) G = cap;
         if (G < 1) G = 1;
         g.rows_per_block = (g.M + G - 1) / G;
@@ -441,6 +483,7 @@ Geom geometry(const nsk_bn_desc_t &d, bool backward)
         g.npg = ceil_div(d.N, G);
         g.G = ceil_div(d.N, g.npg);
         g.rows_per_block = 0;
+        g.chunks = g.RP = 1;
     }
     if (d.layout == NSK_NCHW) {
         g.sn = (long)d.C * g.HW;
@@ -454,13 +497,24 @@ Geom geometry(const nsk_bn_desc_t &d, bool backward)
     return g;
 }
 
-int stream_blocks(long work_items)
+int stream_blocks(long work_items, int per_block = 256)
 {
-    long b = (work_items + 255) / 256;
+    long b = (work_items + per_block - 1) / per_block;
     const long cap = 256 * 16;  // 16 blocks per CU keep every CU streaming
     if (b > cap) b = cap;
     if (b < 1) b = 1;
     return (int)b;
+}
+
+dim3 apply_grid(const Geom &g) { return dim3(stream_blocks(g.M, g.RP), g.chunks); }
+
+// f(std::integral_constant<int, VEC>): the access width of the NHWC path as a constant
+template <typename T, typename F> void with_vec(const Geom &g, F f)
+{
+    if constexpr (sizeof(T) == 2) {
+        if (g.vec == 8) return f(std::integral_constant<int, 8>{});
+    }
+    f(std::integral_constant<int, 4>{});
 }
 
 template <typename T>
@@ -470,7 +524,6 @@ int bn_fwd_typed(const nsk_bn_desc_t &d, const T *x, const T *res, const float *
 {
     const Geom g = geometry(d, false);
     float *p0 = ws, *p1 = ws + (long)g.G * d.C, *scale = p1 + (long)g.G * d.C, *bias = scale + d.C;
-    constexpr int VEC = BT<T>::VEC;
     if (stats) {
         // partial sums of x and x^2 left by the producer of x ([2][stats_rows][C], not shifted): no reduction pass.
         // A producer with small tiles leaves tens of thousands of rows: those are first folded into at most G rows
@@ -487,10 +540,12 @@ int bn_fwd_typed(const nsk_bn_desc_t &d, const T *x, const T *res, const float *
         hipLaunchKernelGGL((bn_fwd_finalize<T>), dim3(d.C), dim3(256), 0, stream, q0, q1, rows, d.C,
                            (double)g.M, (const T *)nullptr, 0L, gamma, beta, d.eps, d.momentum, save_mean, save_invstd,
                            running_mean, running_var, scale, bias);
-    } else if (g.fast) {
-        hipLaunchKernelGGL((bn_reduce_nhwc<T, 0>), dim3(g.G), dim3(256), 0, stream, x, (const T *)nullptr,
-                           (const T *)nullptr, (const float *)nullptr, (const float *)nullptr, 0, g.M, d.C,
-                           g.rows_per_block, p0, p1, (unsigned char *)nullptr, (const unsigned char *)nullptr);
+    } else if (g.vec) {
+        with_vec<T>(g, [&](auto V) {
+            hipLaunchKernelGGL((bn_reduce_nhwc<T, V.value, 0>), dim3(g.G, g.chunks), dim3(256), 0, stream, x, (const T *)nullptr,
+                               (const T *)nullptr, (const float *)nullptr, (const float *)nullptr, 0, g.M, d.C,
+                               g.rows_per_block, p0, p1, (unsigned char *)nullptr, (const unsigned char *)nullptr, 0, (const float *)nullptr);
+        });
     } else {
         hipLaunchKernelGGL((bn_reduce_generic<T, 0>), dim3(d.C, g.G), dim3(256), 0, stream, x, (const T *)nullptr,
                            (const T *)nullptr, (const float *)nullptr, (const float *)nullptr, 0, d.N, g.HW, g.sn,
@@ -500,16 +555,18 @@ int bn_fwd_typed(const nsk_bn_desc_t &d, const T *x, const T *res, const float *
         hipLaunchKernelGGL((bn_fwd_finalize<T>), dim3(d.C), dim3(256), 0, stream, p0, p1, g.G, d.C,
                            (double)g.M, x, g.sc, gamma, beta, d.eps, d.momentum, save_mean, save_invstd, running_mean,
                            running_var, scale, bias);
-    if (g.fast) {
-        const long nvec = g.total / VEC;
-        const dim3 grid(stream_blocks(nvec));
+    if (g.vec) {
+        const long nvec = g.total / g.vec;
+        const dim3 grid = apply_grid(g);
 #define NSK_APPLY(R, L) \
-    hipLaunchKernelGGL((bn_apply_nhwc<T, R, L>), grid, dim3(256), 0, stream, x, res, out, scale, bias, nvec, d.C, relu_mask)
-        if (res) {
-            if (d.relu) NSK_APPLY(true, true); else NSK_APPLY(true, false);
-        } else {
-            if (d.relu) NSK_APPLY(false, true); else NSK_APPLY(false, false);
-        }
+    hipLaunchKernelGGL((bn_apply_nhwc<T, V.value, R, L>), grid, dim3(256), 0, stream, x, res, out, scale, bias, nvec, d.C, relu_mask)
+        with_vec<T>(g, [&](auto V) {
+            if (res) {
+                if (d.relu) NSK_APPLY(true, true); else NSK_APPLY(true, false);
+            } else {
+                if (d.relu) NSK_APPLY(false, true); else NSK_APPLY(false, false);
+            }
+        });
 #undef NSK_APPLY
     } else {
         const dim3 grid(stream_blocks(g.total));
@@ -529,31 +586,35 @@ int bn_bwd_typed(const nsk_bn_desc_t &d, const T *x, const T *out, const T *dout
                  const unsigned char *mask_in, hipStream_t stream, const float *act = nullptr)
 {
     const Geom g = geometry(d, true);
-    if (act && !(g.fast && d.relu)) return NSK_ERR_UNSUPPORTED;
+    const bool masked = nhwc_fast(d);   // the ReLU mask goes from pass to pass; else both read out
+    if (act && !(masked && d.relu)) return NSK_ERR_UNSUPPORTED;
     float *p0 = ws, *p1 = ws + (long)g.G * d.C, *coef = p1 + (long)g.G * d.C;
     // the ReLU mask bytes follow the float part of the workspace (see bn_mask_bytes)
     unsigned char *mask = (unsigned char *)ws + align_up((2 * (size_t)bn_partial_blocks(d) * d.C + 4 * (size_t)d.C) * sizeof(float));
-    constexpr int VEC = BT<T>::VEC;
-    if (g.fast) {
-        hipLaunchKernelGGL((bn_reduce_nhwc<T, 1>), dim3(g.G), dim3(256), 0, stream, x, out, dout, mean, invstd,
-                           d.relu, g.M, d.C, g.rows_per_block, p0, p1, mask, mask_in, 0, act);
+    if (g.vec) {
+        with_vec<T>(g, [&](auto V) {
+            hipLaunchKernelGGL((bn_reduce_nhwc<T, V.value, 1>), dim3(g.G, g.chunks), dim3(256), 0, stream, x, out, dout, mean, invstd,
+                               d.relu, g.M, d.C, g.rows_per_block, p0, p1, masked ? mask : (unsigned char *)nullptr, mask_in, 0, act);
+        });
     } else {
         hipLaunchKernelGGL((bn_reduce_generic<T, 1>), dim3(d.C, g.G), dim3(256), 0, stream, x, out, dout, mean,
                            invstd, d.relu, d.N, g.HW, g.sn, g.sc, g.ss, g.npg, d.C, p0, p1);
     }
     hipLaunchKernelGGL(bn_bwd_finalize, dim3(d.C), dim3(256), 0, stream, p0, p1, g.G, d.C,
                        (double)g.M, gamma, invstd, dgamma, dbeta, coef);
-    if (g.fast) {
-        const long nvec = g.total / VEC;
-        const dim3 grid(stream_blocks(nvec));
+    if (g.vec) {
+        const long nvec = g.total / g.vec;
+        const dim3 grid = apply_grid(g);
 #define NSK_BAPPLY(R, L)                                                                                       \
-    hipLaunchKernelGGL((bn_bwd_apply_nhwc<T, R, L>), grid, dim3(256), 0, stream, x, out, dout, dx, dres, mean, \
+    hipLaunchKernelGGL((bn_bwd_apply_nhwc<T, V.value, R, L>), grid, dim3(256), 0, stream, x, out, dout, dx, dres, mean, \
                        invstd, coef, nvec, d.C, mask_in ? mask_in : mask)
-        if (dres) {
-            if (d.relu) NSK_BAPPLY(true, true); else NSK_BAPPLY(true, false);
-        } else {
-            if (d.relu) NSK_BAPPLY(false, true); else NSK_BAPPLY(false, false);
-        }
+        with_vec<T>(g, [&](auto V) {
+            if (dres) {
+                if (!d.relu) NSK_BAPPLY(true, 0); else if (masked) NSK_BAPPLY(true, 1); else NSK_BAPPLY(true, 2);
+            } else {
+                if (!d.relu) NSK_BAPPLY(false, 0); else if (masked) NSK_BAPPLY(false, 1); else NSK_BAPPLY(false, 2);
+            }
+        });
 #undef NSK_BAPPLY
     } else {
         const dim3 grid(stream_blocks(g.total));
@@ -605,10 +666,13 @@ int launch_bn_stats(const nsk_bn_desc_t &d, const void *x, float *stats, hipStre
     const Geom g = geometry(d, false);
     float *p0 = stats, *p1 = stats + (long)g.G * d.C;
 #define NSK_STATS(T)                                                                                                   \
-    if (g.fast)                                                                                                        \
-        hipLaunchKernelGGL((bn_reduce_nhwc<T, 0>), dim3(g.G), dim3(256), 0, stream, (const T *)x, (const T *)nullptr,  \
-                           (const T *)nullptr, (const float *)nullptr, (const float *)nullptr, 0, g.M, d.C,            \
-                           g.rows_per_block, p0, p1, (unsigned char *)nullptr, (const unsigned char *)nullptr, 1);     \
+    if (g.vec)                                                                                                         \
+        with_vec<T>(g, [&](auto V) {                                                                                   \
+            hipLaunchKernelGGL((bn_reduce_nhwc<T, V.value, 0>), dim3(g.G, g.chunks), dim3(256), 0, stream, (const T *)x, \
+                               (const T *)nullptr, (const T *)nullptr, (const float *)nullptr, (const float *)nullptr, \
+                               0, g.M, d.C, g.rows_per_block, p0, p1, (unsigned char *)nullptr,                        \
+                               (const unsigned char *)nullptr, 1, (const float *)nullptr);                             \
+        });                                                                                                            \
     else                                                                                                               \
         hipLaunchKernelGGL((bn_reduce_generic<T, 0>), dim3(d.C, g.G), dim3(256), 0, stream, (const T *)x,              \
                            (const T *)nullptr, (const T *)nullptr, (const float *)nullptr, (const float *)nullptr, 0,  \
@@ -635,7 +699,7 @@ int launch_bn_bwd(const nsk_bn_desc_t &d, const void *x, const void *out, const 
 }
 
 // True if the fused-activation calls take this tensor: NHWC with a channel count the vector kernels handle.
-bool bn_act_supported(const nsk_bn_desc_t &d) { return geometry(d, false).fast && geometry(d, true).fast; }
+bool bn_act_supported(const nsk_bn_desc_t &d) { return nhwc_fast(d); }
 
 // Batch statistics and the coefficients of out = scale*x + shift (scale = gamma*invstd, shift = beta - mean*scale) from
 // partial sums of x and x^2 ([2][stats_rows][C], not shifted), without the apply pass: coeffs = [2][C] floats.
@@ -670,16 +734,14 @@ int launch_bn_coeffs(const nsk_bn_desc_t &d, const float *gamma, const float *be
 int launch_bn_act(const nsk_bn_desc_t &d, const void *x, const float *coeffs, void *out, hipStream_t stream)
 {
     const Geom g = geometry(d, false);
-    if (!g.fast) return NSK_ERR_UNSUPPORTED;
-    if (d.dtype == NSK_BF16) {
-        const long nvec = g.total / BT<bf16_t>::VEC;
-        hipLaunchKernelGGL((bn_apply_nhwc<bf16_t, false, true>), dim3(stream_blocks(nvec)), dim3(256), 0, stream, (const bf16_t *)x,
+    if (!nhwc_fast(d)) return NSK_ERR_UNSUPPORTED;
+    const long nvec = g.total / g.vec;
+    if (d.dtype == NSK_BF16)
+        hipLaunchKernelGGL((bn_apply_nhwc<bf16_t, 8, false, true>), apply_grid(g), dim3(256), 0, stream, (const bf16_t *)x,
                            (const bf16_t *)nullptr, (bf16_t *)out, coeffs, coeffs + d.C, nvec, d.C, (unsigned char *)nullptr);
-    } else {
-        const long nvec = g.total / BT<float>::VEC;
-        hipLaunchKernelGGL((bn_apply_nhwc<float, false, true>), dim3(stream_blocks(nvec)), dim3(256), 0, stream, (const float *)x,
+    else
+        hipLaunchKernelGGL((bn_apply_nhwc<float, 4, false, true>), apply_grid(g), dim3(256), 0, stream, (const float *)x,
                            (const float *)nullptr, (float *)out, coeffs, coeffs + d.C, nvec, d.C, (unsigned char *)nullptr);
-    }
     return check_launch();
 }
 

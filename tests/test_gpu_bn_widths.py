@@ -1,0 +1,74 @@
+"""Batch-norm on channel counts whose vectors do not divide a block of the NHWC kernels: one vector, idle threads at the end of a
+block, more than one chunk of 256 vectors, 8-byte vectors in bf16, tensors below the size from which the
+vectors are used; thousands of rows of statistics handed in; against the oracle and against the general path (the same values as NCHW)."""
+import numpy as np
+import pytest
+import torch
+
+import nsk_inputs as gen
+import oracle
+from paper_2409_11600_amd import binding as B
+from parity import TOL, guarded, max_rel_err, on_grid, to_gpu, to_host, torch_dtype
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("relu,res", [(True, True), (True, False), (False, True)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("C", [4, 12, 24, 36, 96, 100, 344, 520, 1028, 1032, 2056, 4100])
+def test_any_width(C, dtype, relu, res):
+    N, H, W = (2, 7, -(-131072 // (14 * C)) + (0 if relu else 3)) if res or C > 400 else (3, 11, 13)   # from 128 k elements on; below
+    print(f"batch-norm C={C} {dtype} relu={relu} residual={res}", flush=True)
+    tol, s = TOL[dtype], 7000 + C
+    # means of about one: a mean comes from chains of float sums of differences of size 1..4, at most 32 long here, so it is good to
+    # 32 * 2^-24 * 4 = 8e-6 in absolute terms (a mean of 0.01 has no relative bar of 1e-5)
+    x, r, dout = (on_grid(gen.normal(s, k, (N, C, H, W)) + (k == 0), dtype) for k in range(3))
+    gamma, beta = 1 + 0.2 * gen.normal(s, 3, (C,)).astype(np.float32), 0.2 * gen.normal(s, 4, (C,)).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).to("cuda:0")
+    want, wmean, winv = oracle.bn_relu_add_fwd(x, gamma, beta, r if res else None, 1e-5, relu)[:3]
+    wmean, winv = wmean.astype(np.float32), winv.astype(np.float32)
+    kept = on_grid(want, dtype)
+    wdx, wdres, wdg, wdb = oracle.bn_relu_add_bwd(x, kept, dout, gamma, wmean, winv, relu, want_dresidual=res)
+    for lay in (B.NSK_NHWC, B.NSK_NCHW):
+        gx, gr, gd, gk, ws = *(to_gpu(a, dtype, lay) for a in (x, r, dout, kept)), B.Workspace()
+        out, ok = guarded(gx.shape, torch_dtype(dtype))
+        _, mean, inv = B.bn_relu_add_fwd(gx, dev(gamma), dev(beta), gr if res else None, 1e-5, relu, lay, out=out, ws=ws)
+        torch.cuda.synchronize()
+        ok()
+        assert max_rel_err(to_host(out, lay), want) <= tol
+        assert max_rel_err(mean.cpu().numpy(), wmean) <= 1e-5 and max_rel_err(inv.cpu().numpy(), winv) <= 1e-5
+        dx, ok = guarded(gx.shape, torch_dtype(dtype))
+        _, dres, dg, db = B.bn_relu_add_bwd(gx, gk, gd, dev(gamma), dev(wmean), dev(winv), relu, lay, dx=dx, want_dresidual=res, ws=ws)
+        torch.cuda.synchronize()
+        ok()
+        assert max_rel_err(to_host(dx, lay), wdx) <= tol
+        assert max_rel_err(dg.cpu().numpy(), wdg) <= 1e-4 and max_rel_err(db.cpu().numpy(), wdb) <= 1e-4
+        if res:
+            assert np.array_equal(to_host(dres, lay), wdres)      # a masked copy: exact
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("C,rows", [(96, 3000), (100, 2000), (1032, 1500), (64, 5000)])
+def test_statistics_handed_in(C, rows, dtype):
+    N, H, W, lay, s = 2, 25, 31, B.NSK_NHWC, 7900 + C
+    x = on_grid(gen.normal(s, 0, (N, C, H, W)), dtype)
+    gx = to_gpu(x, dtype, lay)
+    # the rows add up to the tensor's sums: as many random rows as fit, the rest in the last
+    part = (0.01 * gen.normal(s, 1, (2, rows, C))).astype(np.float32)
+    total = np.stack([x.sum((0, 2, 3)), (x.astype(np.float64) ** 2).sum((0, 2, 3))])
+    part[:, -1] = total - part[:, :-1].astype(np.float64).sum(1)
+    gamma, beta = torch.ones(C, device="cuda:0"), torch.zeros(C, device="cuda:0")
+    out, mean, inv = B.bn_relu_add_fwd(gx, gamma, beta, None, 1e-5, False, lay, stats=torch.from_numpy(part).to("cuda:0"))
+    want, wmean, winv = oracle.bn_relu_add_fwd(x, np.ones(C), np.zeros(C), None, 1e-5, False)[:3]
+    # the last row is rounded to float and up to `rows` of size 0.01 are added in float by the fold
+    assert np.abs(mean.cpu().numpy() - wmean).max() <= 1e-5 and max_rel_err(inv.cpu().numpy(), winv) <= 1e-4
+    assert max_rel_err(to_host(out, lay), want) <= max(TOL[dtype], 1e-4)
+
+
+def test_what_was_refused_stays_refused():
+    x = torch.zeros((2, 3, 5, 96), device="cuda:0")
+    assert B.bn_mask_bytes(x) == 0
+    z = torch.zeros(96, device="cuda:0")
+    with pytest.raises(B.NskError) as e:
+        B.bn_relu_bwd_act(x, torch.zeros((2, 96), device="cuda:0"), x, z, z, z)
+    assert e.value.status == B.NSK_ERR_UNSUPPORTED
