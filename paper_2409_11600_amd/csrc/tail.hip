@@ -120,25 +120,35 @@ __global__ __launch_bounds__(256) void add_bias_kernel(T *__restrict__ y, const 
     for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long)gridDim.x * 256)
         y[i] = (T)(ld(y, i) + bias[i % K]);
 }
-// db[k] (+)= sum_n dy[n][k]: a block owns 64 columns (lane = column, so a wavefront reads contiguous bytes of a row),
-// its 16 wavefronts take every 16th row each and their partial sums are added in a fixed order.
-template <typename T>
+// db[k] (+)= sum_n dy[n][k]: a block owns CB columns (neighbouring lanes, so a wavefront reads contiguous bytes of 64/CB
+// rows), its 1024/CB row lanes take every (1024/CB)-th row each and their partial sums are added in a fixed order.
+// Bound by how many loads are on their way: with 64 columns a block, 768 columns are 12 blocks.  From 1024 rows on a block
+// has 16 columns (fp32 10000 x 768: 32.1 us with 64 columns, 24.3 with 16).
+template <typename T, int CB>
 __global__ __launch_bounds__(1024) void bias_grad_kernel(const T *__restrict__ dy, float *__restrict__ db, int N, int K,
                                                          int accumulate)
 {
-    __shared__ float part[16][64];
-    const int lane = threadIdx.x & 63, rl = threadIdx.x >> 6, k = blockIdx.x * 64 + lane;
+    constexpr int RL = 1024 / CB;
+    __shared__ float part[RL][CB], few[16][CB];
+    const int col = threadIdx.x % CB, rl = threadIdx.x / CB, k = blockIdx.x * CB + col;
     float s = 0.f;
     if (k < K) {
 #pragma unroll 8
-        for (int n = rl; n < N; n += 16) s += ld(dy, (long)n * K + k);
+        for (int n = rl; n < N; n += RL) s += ld(dy, (long)n * K + k);
     }
-    part[rl][lane] = s;
+    part[rl][col] = s;
+    __syncthreads();
+    if (rl < 16) {
+        float t = 0.f;
+#pragma unroll
+        for (int r = 0; r < RL / 16; ++r) t += part[rl * (RL / 16) + r][col];
+        few[rl][col] = t;
+    }
     __syncthreads();
     if (rl == 0 && k < K) {
         float t = 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) t += part[r][lane];
+        for (int r = 0; r < 16; ++r) t += few[r][col];
         db[k] = accumulate ? db[k] + t : t;
     }
 }
@@ -298,25 +308,42 @@ __global__ __launch_bounds__(256) void optimizer_kernel(const ParamTable tab, fl
     }
 }
 
-__global__ __launch_bounds__(256) void sumsq_partial_kernel(size_t n, const float *__restrict__ g, float *__restrict__ partials)
+// Bound by memory once enough loads are on their way: at most 256 partial sums, so a block is 1024 threads that take 16 bytes
+// at a time (g is on a 16-byte boundary), four of them at once (us with the final sum, 256 threads and
+// single floats / here: 8.4 M elements 27.3 / 7.1, 197 k 12.5 / 5.7, 768 4.4 / 4.4).
+__global__ __launch_bounds__(1024) void sumsq_partial_kernel(size_t n, const float *__restrict__ g, float *__restrict__ partials)
 {
-    __shared__ double part[4];
+    __shared__ double part[16];
     double s = 0.0;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-        const float v = g[i];
+    const size_t nv = n / 4, step = (size_t)gridDim.x * 1024, first = (size_t)blockIdx.x * 1024 + threadIdx.x;
+#pragma unroll 4
+    for (size_t i = first; i < nv; i += step) {
+        const f32x4 v = *(const f32x4 *)(g + 4 * i);
+        s += ((double)(v[0] * v[0]) + (double)(v[1] * v[1])) + ((double)(v[2] * v[2]) + (double)(v[3] * v[3]));
+    }
+    if (first < n - 4 * nv) {
+        const float v = g[4 * nv + first];
         s += (double)(v * v);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0) partials[blockIdx.x] = (float)((part[0] + part[1]) + (part[2] + part[3]));
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) t += part[w];
+        partials[blockIdx.x] = (float)t;
+    }
 }
-__global__ void sumsq_final_kernel(const float *__restrict__ partials, int nb, float *__restrict__ sumsq)
+// one wavefront: lane l adds the partial sums l, l + 64, ..., the lanes are added in a fixed order
+__global__ __launch_bounds__(64) void sumsq_final_kernel(const float *__restrict__ partials, int nb, float *__restrict__ sumsq)
 {
     double s = 0.0;
-    for (int i = 0; i < nb; ++i) s += (double)partials[i];
-    sumsq[0] = (float)((double)sumsq[0] + s);
+    for (int i = threadIdx.x; i < nb; i += 64) s += (double)partials[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (threadIdx.x == 0) sumsq[0] = (float)((double)sumsq[0] + s);
 }
 __global__ void clip_scale_kernel(const float *__restrict__ sumsq, float max_norm, float *__restrict__ scale)
 {
@@ -483,13 +510,15 @@ int nsk_linear_wgrad(const nsk_linear_desc_t *desc, const void *x, const void *d
     const nsk_conv_desc_t c = linear_as_conv(desc);
     TAIL_TRY(nsk_conv2d_wgrad(&c, x, dy, dw, accumulate, workspace, workspace_bytes, stream));
     if (db) {
-        const dim3 grid((unsigned)((desc->K + 63) / 64));
-        if (desc->dtype == NSK_BF16)
-            hipLaunchKernelGGL(bias_grad_kernel<bf16_t>, grid, dim3(1024), 0, (hipStream_t)stream, (const bf16_t *)dy, db, desc->N,
-                               desc->K, accumulate);
-        else
-            hipLaunchKernelGGL(bias_grad_kernel<float>, grid, dim3(1024), 0, (hipStream_t)stream, (const float *)dy, db, desc->N,
-                               desc->K, accumulate);
+#define NSK_BIAS(T, CB)                                                                                                  \
+    hipLaunchKernelGGL((bias_grad_kernel<T, CB>), dim3((unsigned)((desc->K + CB - 1) / CB)), dim3(1024), 0, (hipStream_t)stream, \
+                       (const T *)dy, db, desc->N, desc->K, accumulate)
+        if (desc->dtype == NSK_BF16) {
+            if (desc->N < 1024) NSK_BIAS(bf16_t, 64); else NSK_BIAS(bf16_t, 16);
+        } else {
+            if (desc->N < 1024) NSK_BIAS(float, 64); else NSK_BIAS(float, 16);
+        }
+#undef NSK_BIAS
         return check_launch();
     }
     return NSK_OK;
@@ -625,8 +654,8 @@ int nsk_sumsq_accumulate(size_t n, const float *g, float *partials, float *sumsq
     if (unaligned(g) || unaligned(partials) || ((uintptr_t)sumsq & 3)) return NSK_ERR_ALIGNMENT;
     size_t nb = (n + 1023) / 1024;
     if (nb > NSK_SUMSQ_PARTIALS) nb = NSK_SUMSQ_PARTIALS;
-    hipLaunchKernelGGL(sumsq_partial_kernel, dim3((unsigned)nb), dim3(256), 0, (hipStream_t)stream, n, g, partials);
-    hipLaunchKernelGGL(sumsq_final_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, partials, (int)nb, sumsq);
+    hipLaunchKernelGGL(sumsq_partial_kernel, dim3((unsigned)nb), dim3(1024), 0, (hipStream_t)stream, n, g, partials);
+    hipLaunchKernelGGL(sumsq_final_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, partials, (int)nb, sumsq);
     return check_launch();
 }
 
