@@ -4,7 +4,7 @@
 // "Experiments and Discussion"); with 2304 or more reduction indices they are the layers where the matrix units, not
 // memory, should be the limit.
 //
-// The large-tile kernel re-stages every activation row nine times (once per tap) and every filter row once per row
+// A tile kernel re-stages every activation row nine times (once per tap) and every filter row once per row
 // block, all through LDS: 144 KB of LDS traffic and 48 KB of L2 traffic per 1024 MFMA clocks, which holds it below
 // 40% MFMA utilisation.  This kernel removes both:
 //   * the input tile (whole image rows with their halo, ALL input channels) is staged into LDS once; the nine taps

@@ -592,7 +592,7 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     const int kr = g.K / groups;
     const long w_gstep = (long)kr * w_sc;
     size_t filt_off = p.filt;
-    // classes with taps: filters are packed first, then the launches follow (one for all classes where the large-tile
+    // classes with taps: filters are packed first, then the launches follow (one for all classes where the pipelined
     // kernel takes them together)
     IgemmArgs pending[4], zeros[4];
     int n_pending = 0, n_zeros = 0;
