@@ -48,9 +48,10 @@ def test_any_width(C, dtype, relu, res):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("C,rows", [(96, 3000), (100, 2000), (1032, 1500), (64, 5000)])
-def test_statistics_handed_in(C, rows, dtype):
-    N, H, W, lay, s = 2, 25, 31, B.NSK_NHWC, 7900 + C
+@pytest.mark.parametrize("C,rows,lay", [(96, 3000, B.NSK_NHWC), (100, 2000, B.NSK_NHWC), (1032, 1500, B.NSK_NHWC), (64, 5000, B.NSK_NHWC),
+                                        (20, 4000, B.NSK_NCHW), (96, 1100, B.NSK_NCHW)])
+def test_statistics_handed_in(C, rows, lay, dtype):
+    N, H, W, s = 2, 25, 31, 7900 + C
     x = on_grid(gen.normal(s, 0, (N, C, H, W)), dtype)
     gx = to_gpu(x, dtype, lay)
     # the rows add up to the tensor's sums: as many random rows as fit, the rest in the last
@@ -72,3 +73,19 @@ def test_what_was_refused_stays_refused():
     with pytest.raises(B.NskError) as e:
         B.bn_relu_bwd_act(x, torch.zeros((2, 96), device="cuda:0"), x, z, z, z)
     assert e.value.status == B.NSK_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("lay", [B.NSK_NHWC, B.NSK_NCHW], ids=["nhwc", "nchw"])
+def test_many_rows_are_added_without_long_float_chains(lay):
+    """One image's sums in 4000 rows that are far larger than their total."""
+    C, rows, H, W = 20, 4000, 64, 104
+    g = np.random.default_rng(5)
+    part = np.stack([g.standard_normal((rows, C)), np.abs(g.standard_normal((rows, C))) + 50]).astype(np.float32)
+    part[0] += np.where(np.arange(rows) < rows // 2, 100, -100).astype(np.float32)[:, None]
+    shape = (1, H, W, C) if lay == B.NSK_NHWC else (1, C, H, W)
+    x, one, zero = torch.zeros(shape, device="cuda:0"), torch.ones(C, device="cuda:0"), torch.zeros(C, device="cuda:0")
+    _, mean, _ = B.bn_relu_add_fwd(x, one, zero, None, 1e-5, False, lay, stats=torch.from_numpy(part).to("cuda:0"))
+    want = part[0].astype(np.float64).sum(0) / (H * W)
+    # no run of float additions is longer than 64 rows of 104 before fp64: at most 64 roundings of 6656 in 63 runs, in a random walk
+    bar = 8 * np.sqrt(64 * 63) * 2.0 ** -24 * 6656 / 2 / (H * W)
+    assert np.abs(mean.cpu().numpy() - want).max() <= bar + 2.0 ** -24 * np.abs(want).max()
