@@ -81,7 +81,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
     constexpr int LOADS = RA + RB;
     constexpr int TA = BM * PK_BYTES, TB = BN * PK_BYTES;
     constexpr int SROW = 32 * ES + 16;                  // epilogue: staged bytes per pixel (padded)
-    constexpr int EPI = NW * 32 * SROW + (WK > 1 ? 3 * FM * FN * 4096 : 0);
+    constexpr int EPI = NW * 32 * SROW + WM * WN * (WK - 1) * FM * FN * 4096;   // and the sums of the wavefronts wk > 0
     constexpr int TA0 = TA > EPI ? TA : EPI;
     static_assert(ST == 3 || ST == 4, "stages");
 
@@ -307,6 +307,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
     if constexpr (WK > 1) {
         // add the wavefronts of a group in a fixed order
         float *red = (float *)(sa0 + NW * 32 * SROW);
+        static_assert(NW * 32 * SROW + WM * WN * (WK - 1) * FM * FN * 4 * 256 * (int)sizeof(float) <= (int)sizeof(sa0),
+                      "strips and partial sums lie inside the first stage");
         const int slot = (wm * WN + wn) * (WK - 1);
         if (wk > 0) {
 #pragma unroll
