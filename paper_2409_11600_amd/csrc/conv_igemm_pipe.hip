@@ -438,25 +438,51 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
     }
 }
 
-// Tile shapes with what a k-tile and the rest of a block cost in shader clocks, measured (31 problems, both types).  bf16
-// is bound by the fill of LDS: eight wavefronts per block bring 38-42 B/clk into a CU, four only 31, so all bf16 shapes
-// but the narrowest have eight.  fp32 is bound by the matrix units (256 clocks per 32 x 32 and k-tile), so there small
-// tiles, which spread evenly over the CUs, win throughout.
+// Tile shapes with what a launch of them costs (us): `fixed` + the larger of whole rounds of blocks on the 256 CUs, a block
+// costing `step` a k-tile and `rest` once, and `per_mb` a megabyte moved (what one or two blocks a CU keep on their way).
+// `stats` and 1.5 ns a row of them are what the statistics add, in the epilogue and in the batch-norm that reads them.
+// Fitted to 900 bf16 passes of 1x1 and 3x3 filters, stride 1 and 2, 16 to 2048 channels, 0.5 k to 400 k pixels, each timed with
+// every shape: the choice is on average 0.7% off the best shape and 5% in the worst twentieth (with the clocks of a block
+// alone and no bound on the bytes 2% and 14%: 1x1 layers whose last round was nearly empty took up to 1.5 times the time
+// of the best one, 64 -> 128 on 38 k pixels 9.0 us instead of 6.1).
+// bf16 is bound by the fill of LDS: eight wavefronts per block bring 38-42 B/clk into a CU, four only 31, so all bf16 shapes
+// but the narrowest have eight.  128 x 64 has three stages, not four, where there are blocks enough to put two on a CU, which
+// fill while the other stores (median over those layers 0.76 of its time; 128 -> 64 on 75 k pixels 10.0 -> 7.5 us,
+// 256 -> 128 on 200 k 50 -> 35).
+// fp32 is bound by the matrix units (256 clocks per 32 x 32 and k-tile), so there small tiles, which spread evenly over
+// the CUs, win throughout.
 struct PipeTile {
-    int bm, bn, wm;          // wm: wavefront rows = rows of statistics per tile
-    double step, rest;
+    int bm, bn, wm, wk;      // wm: wavefront rows = rows of statistics per tile; wk: parts a k-tile's sums are made in
+    double step, rest, fixed, per_mb, stats;
 };
-constexpr PipeTile kTilesBf16[] = {{256, 128, 4, 1300, 16000}, {128, 128, 2, 830, 9000}, {256, 64, 4, 1000, 8500},
-                                   {128, 64, 4, 700, 5000},    {64, 64, 2, 400, 3000},   {128, 32, 4, 550, 3000}};
-constexpr PipeTile kTilesF32[] = {{64, 64, 2, 1150, 3000}, {128, 32, 4, 1150, 3000}, {64, 32, 2, 580, 2000}, {32, 32, 1, 290, 1500}};
+constexpr PipeTile kTilesBf16[] = {{256, 128, 4, 1, 0.827, 4.71, 0.99, 0.017, 1.4}, {128, 128, 2, 1, 0.494, 3.15, 1.3, 0.219, 0},
+                                   {256, 64, 4, 1, 0.587, 3.34, 0.92, 0.217, 0},    {128, 64, 4, 1, 0.302, 1.47, 2.96, 0.074, 0},
+                                   {64, 64, 2, 2, 0.224, 2.12, 1.25, 0.251, 0},     {128, 32, 4, 1, 0.30, 0.9, 2.34, 0.162, 0}};
+constexpr PipeTile kTilesF32[] = {{64, 64, 2, 1, 0.575, 1.5, 0, 0, 0}, {128, 32, 4, 1, 0.575, 1.5, 0, 0, 0}, {64, 32, 2, 2, 0.29, 1.0, 0, 0, 0},
+                                  {32, 32, 1, 4, 0.145, 0.75, 0, 0, 0}};
 
-template <int N> int cheapest(const PipeTile (&tiles)[N], int es, const IgemmArgs *a, int count)
+long block_count(const PipeTile &t, const IgemmArgs *a, int count)
+{
+    long blocks = 0;
+    for (int j = 0; j < count; ++j) blocks += (long)ceil_div(a[j].M, t.bm) * ceil_div(a[j].Ngemm, t.bn);
+    return blocks * (a[0].groups > 1 ? a[0].groups : 1);
+}
+
+// stats: the launch leaves statistics.  Its shape then makes every sum in the same order as the one without would, so that the
+// output does not depend on whether they are asked for.
+template <int N> int cheapest(const PipeTile (&tiles)[N], int es, const IgemmArgs *a, int count, bool stats)
 {
     const int forced = hooks().igemm_tile;   // NSK_IGEMM_TILE = 1.. (test hook)
     if (forced >= 1) return (forced - 1) % N;
     const int groups = a[0].groups > 1 ? a[0].groups : 1;
+    double read = 0, mb = 0;                 // what the problems read of the source, at most all of it, and write
+    for (int j = 0; j < count; ++j) {
+        read += (double)a[j].M * a[j].Ktot * groups * es;
+        mb += (double)a[j].M * a[j].Ngemm * groups * es * 1e-6;
+    }
+    mb += (read < a[0].src_bytes ? read : a[0].src_bytes) * 1e-6;
+    double cost[N];
     int best = 0;
-    double best_cost = 0;
     for (int i = 0; i < N; ++i) {
         long blocks = 0;
         double work = 0;
@@ -467,12 +493,14 @@ template <int N> int cheapest(const PipeTile (&tiles)[N], int es, const IgemmArg
             work += (double)b * (nk * tiles[i].step + tiles[i].rest);
         }
         // 256 CUs: whole rounds of the average block
-        const double cost = (double)((blocks + 255) / 256) * (work / (double)blocks);
-        if (i == 0 || cost < best_cost) {
-            best = i;
-            best_cost = cost;
-        }
+        const double rounds = (double)((blocks + 255) / 256) * (work / (double)blocks), bytes = mb * tiles[i].per_mb;
+        cost[i] = tiles[i].fixed + (rounds > bytes ? rounds : bytes);
+        if (cost[i] < cost[best]) best = i;
     }
+    if (es != 2 || !stats || tiles[best].wk > 1) return best;   // (fp32: no shape gained)
+    for (int i = 0; i < N; ++i) cost[i] += tiles[i].stats + 1.5e-3 * ceil_div(a[0].M, tiles[i].bm) * tiles[i].wm;
+    for (int i = 0; i < N; ++i)
+        if (tiles[i].wk == 1 && cost[i] < cost[best]) best = i;
     return best;
 }
 
@@ -506,16 +534,18 @@ int launch_igemm_pipe(int dtype, const IgemmArgs *a, int count, hipStream_t stre
 {
     if (count < 1 || count > kMaxProblems) return NSK_ERR_BAD_DESC;
     if (dtype == NSK_BF16) {
-        switch (cheapest(kTilesBf16, 2, a, count)) {
+        switch (cheapest(kTilesBf16, 2, a, count, a->stats != nullptr)) {
         case 0: return launch<bf16_t, 256, 128, 4, 2, 1, 3>(a, count, stream);
         case 1: return launch<bf16_t, 128, 128, 2, 4, 1, 4>(a, count, stream);
         case 2: return launch<bf16_t, 256, 64, 4, 2, 1, 3>(a, count, stream);
-        case 3: return launch<bf16_t, 128, 64, 4, 2, 1, 4>(a, count, stream);
+        case 3:   // (four stages where a CU gets one block: 512 -> 512 3x3 at 14x14, N=16 28.9 -> 27.3 us)
+            return block_count(kTilesBf16[3], a, count) > 256 ? launch<bf16_t, 128, 64, 4, 2, 1, 3>(a, count, stream)
+                                                             : launch<bf16_t, 128, 64, 4, 2, 1, 4>(a, count, stream);
         case 4: return launch<bf16_t, 64, 64, 2, 2, 2, 3>(a, count, stream);
         default: return launch<bf16_t, 128, 32, 4, 1, 1, 3>(a, count, stream);
         }
     }
-    switch (cheapest(kTilesF32, 4, a, count)) {
+    switch (cheapest(kTilesF32, 4, a, count, a->stats != nullptr)) {
     case 0: return launch<float, 64, 64, 2, 2, 1, 4>(a, count, stream);
     case 1: return launch<float, 128, 32, 4, 1, 1, 3>(a, count, stream);
     case 2: return launch<float, 64, 32, 2, 1, 2, 4>(a, count, stream);
@@ -525,7 +555,7 @@ int launch_igemm_pipe(int dtype, const IgemmArgs *a, int count, hipStream_t stre
 
 int igemm_pipe_stats_rows(int dtype, const IgemmArgs &a)
 {
-    const PipeTile &t = dtype == NSK_BF16 ? kTilesBf16[cheapest(kTilesBf16, 2, &a, 1)] : kTilesF32[cheapest(kTilesF32, 4, &a, 1)];
+    const PipeTile &t = dtype == NSK_BF16 ? kTilesBf16[cheapest(kTilesBf16, 2, &a, 1, true)] : kTilesF32[cheapest(kTilesF32, 4, &a, 1, true)];
     return ceil_div(a.M, t.bm) * t.wm;
 }
 

@@ -53,8 +53,15 @@ bool conv_pw_applicable(int dtype, const IgemmArgs &a)
         // all rows, so fewer rows are enough.  Below, the pipelined kernel wins, measured (us, this kernel / that one):
         // 256->1024 on 6 k rows 13.9 / 9.6, on 25 k 31.4 / 30.0, on 50 k 53.5 / 61; 3x3 stride 2 32->64 on 13 k 6.8 / 5.6,
         // on 50 k 11.3 / 9.6, on 200 k 29.9 / 31.6; 512->256 on 100 k 65 / 53, on 400 k 210 / 173; 512->64 on 400 k 99.6 / 104.
+        // One tap of 64 channels has the least to keep and needs fewer: 64->64 on 63 k 5.0 / 5.1, on 75 k 7.1 / 7.1, on 100 k 7.6 /
+        // 8.4; 64->256 on 88 k 17.5 / 16.4, on 100 k 17.5 / 21.1; 64->512 (two groups) on 38 k 17.2 / 16.1, on 50 k 17.2 / 20.5;
+        // likewise a whole 128->256: on 88 k 22.9 / 20.1, on 100 k 23.2 / 24.5 (128->128 on 100 k 16.1 / 15.0, on 200 k 24.3 / 25.5).
         min_rows = a.Cs == 32 ? (a.ntaps == 9 ? 131072 : 8192) : (4L * kPwGrid * 4 * 64) / ((a.Ngemm / cols) * (a.Ngemm / cols));
         if (a.Cs == 256 && min_rows < 32768) min_rows = 32768;
+        if (a.ntaps == 1 && (a.Cs == 64 || (a.Cs == 128 && cols == 256))) {
+            const long fewer = a.Ngemm == 64 ? 65536 : 98304 / (a.Ngemm / cols);
+            if (min_rows > fewer) min_rows = fewer;
+        }
         if (a.Cs == 512) min_rows = a.Ngemm == 64 ? 262144 : LONG_MAX;
     } else {
         return false;

@@ -84,6 +84,38 @@ def test_every_tile_grouped(dtype, tile, nsk_env):
         assert max_rel_err(to_host(dx, B.NSK_NHWC)[:, c], oracle.conv2d_dgrad(dy[:, k], w[k], x[:, c].shape, 1, 1, 1)) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("C,R", [(8, 1), (24, 3), (72, 1)])     # one, four and two k-tiles
+def test_128_by_64_tile_with_two_blocks_on_a_cu(C, R, nsk_env):
+    """More than 256 blocks of it (132 x 2 here): three stages instead of four."""
+    nsk_env("NSK_IGEMM_TILE", "4")
+    N, H, W, K, lay, ws = 1, 129, 130, 72, B.NSK_NHWC, B.Workspace()
+    print(f"pipelined kernel, 128 x 64 tile, 264 blocks, C={C} R={R}", flush=True)
+    x = on_grid(gen.normal(955, 0, (N, C, H, W)), "bf16")
+    w = on_grid(gen.he_normal(955, 1, (K, C, R, R)), "bf16")
+    gx, gw = to_gpu(x, "bf16", lay), to_gpu(w, "bf16", lay)
+    y, check = guarded((N, H, W, K), torch.bfloat16)
+    B.conv2d_fwd(gx, gw, 1, R // 2, 1, lay, out=y, ws=ws)
+    torch.cuda.synchronize()
+    check()
+    assert max_rel_err(to_host(y, lay), oracle.conv2d_fwd(x, w, 1, R // 2, 1)) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("N,C,H,K,R,stride", [(24, 128, 28, 512, 1, 1), (48, 256, 28, 256, 1, 1), (80, 512, 28, 64, 1, 1), (6, 192, 14, 192, 3, 1),
+                                              (55, 448, 37, 16, 1, 1)])
+def test_statistics_do_not_change_the_output(N, C, H, K, R, stride):
+    """Taking them may change the tile, never the order of a sum."""
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn((N, H, H, C), generator=g, device="cuda").bfloat16()
+    w = (0.05 * torch.randn((K, R, R, C), generator=g, device="cuda")).bfloat16()
+    ws = B.Workspace()
+    y = B.conv2d_fwd(x, w, stride, R // 2, ws=ws)
+    ys, stats = B.conv2d_fwd_stats(x, w, stride, R // 2, ws=ws)
+    assert torch.equal(y, ys)
+    want = y.double().sum((0, 1, 2))
+    scale = (y.double() ** 2).sum((0, 1, 2)).mul(y.numel() / K).sqrt()
+    assert float(((stats[0].double().sum(0) - want).abs() / scale).max()) <= 1e-6      # as the other statistics tests
+
+
 # N, C, H, W, K, R, S, stride, pad: strided backward-data passes whose classes share a launch
 CLASSES = [
     (2, 16, 9, 12, 24, 3, 3, 2, 1),            # four classes of 1, 2, 2, 4 taps, odd height
