@@ -16,8 +16,12 @@
 // per clock) or two rows x 128 bytes (fp32) that one fragment read serves at once would fall into the same banks, so a
 // row's 64-byte (fp32: 128-byte) pieces are exchanged with its number; the exchange is made in the source address.
 //
-// Sums: a chain of at most kChain k-tiles is added up in the accumulators and then added to a second set, so that the
-// error does not grow with the length of a split.
+// Sums: the products of ST k-tiles go alternately into two sets of accumulators, which are then added to a third, so that the
+// error does not grow with the length of a split: fp32 chains are at most 64 pixels long (128 in splits of more than kLong
+// k-tiles, where the adds would take 3%), bf16 ones 8 products of 16 pixels.  Error against 64 bits (2-norm, random data;
+// one accumulator and chains of 16-18 k-tiles / this / the kernels before): fp32 16->16 at 32x32 N=8 2.15e-7, 1.61e-7,
+// 1.61e-7; 744->744 1x1 stride 2 at 24x24 N=3 3.73e-7, 1.48e-7, 1.63e-7; 128->128 at 28x28 N=64 4.06e-7, 2.30e-7,
+// 4.99e-7; bf16 416->416 1x1 at 25x25 N=3 1.14e-7, 0.77e-7, 0.81e-7.  Time within 3% of one accumulator (512->512 3x3 at 7x7 N=64 29.7 -> 30.5 us).
 #include "nsk_internal.h"
 
 namespace nsk {
@@ -26,7 +30,7 @@ namespace {
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-constexpr int kChain = 16;
+constexpr int kLong = 16;   // see Sums
 
 // Until at most N of the wavefront's direct loads are on their way and all its LDS reads have arrived (a barrier behind it
 // then also says that nobody reads the stage before any more).
@@ -150,13 +154,13 @@ __global__ __launch_bounds__(64 * WM * WN) void wgrad_pipe_kernel(const PipeArgs
         lx += KT;
     };
 
-    f32x16 acc[FM][FN], sum[FM][FN];
+    f32x16 acc[2][FM][FN], sum[FM][FN];
 #pragma unroll
     for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
         for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = sum[mi][ni][v] = 0.f;
+            for (int v = 0; v < 16; ++v) sum[mi][ni][v] = 0.f;
 
     // Fragment addresses.  bf16, transposing read: within 16 lanes, lanes 4j..4j+3 address pixel row j (four 8-byte pieces =
     // 16 channels) and lane i receives channel i of rows 0..3; lane (channel = lane%32, half = lane/32) of an MFMA operand
@@ -197,7 +201,7 @@ __global__ __launch_bounds__(64 * WM * WN) void wgrad_pipe_kernel(const PipeArgs
                 for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
                     for (int ni = 0; ni < FN; ++ni)
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[mi], bx[ni], acc[mi][ni], 0, 0, 0);
+                        acc[ks & 1][mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[mi], bx[ni], acc[ks & 1][mi][ni], 0, 0, 0);
             }
         } else {
 #pragma unroll
@@ -211,9 +215,19 @@ __global__ __launch_bounds__(64 * WM * WN) void wgrad_pipe_kernel(const PipeArgs
                 for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
                     for (int ni = 0; ni < FN; ++ni)
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi], bx[ni], acc[mi][ni], 0, 0, 0);
+                        acc[t & 1][mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi], bx[ni], acc[t & 1][mi][ni], 0, 0, 0);
             }
         }
+    };
+    auto start_chains = [&]() {
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[c][mi][ni][v] = 0.f;
     };
     auto bank_sums = [&]() {
 #pragma unroll
@@ -221,10 +235,7 @@ __global__ __launch_bounds__(64 * WM * WN) void wgrad_pipe_kernel(const PipeArgs
 #pragma unroll
             for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    sum[mi][ni][v] += acc[mi][ni][v];
-                    acc[mi][ni][v] = 0.f;
-                }
+                for (int v = 0; v < 16; ++v) sum[mi][ni][v] += acc[0][mi][ni][v] + acc[1][mi][ni][v];
     };
 
     static_for<0, ST - 1>([&](auto S) { request(S); });   // (k-tiles past the end are requested out of range: zeros)
@@ -236,18 +247,31 @@ __global__ __launch_bounds__(64 * WM * WN) void wgrad_pipe_kernel(const PipeArgs
     asm volatile("" ::: "memory");                                                                               \
     request(std::integral_constant<int, ((S) + ST - 1) % ST>{});                                                 \
     multiply(std::integral_constant<int, (S)>{});
-    int chain = 0;
-    for (int n = nk / ST; n > 0; --n) {
+    int n = nk / ST;
+    if constexpr (ES == 4) {
+        static_assert(ST == 4, "eight steps are two rounds of the stages");
+        for (; nk > kLong && n > 1; n -= 2) {
+            start_chains();
+            NSK_STEP(0)
+            NSK_STEP(1)
+            NSK_STEP(2)
+            NSK_STEP(3)
+            NSK_STEP(0)
+            NSK_STEP(1)
+            NSK_STEP(2)
+            NSK_STEP(3)
+            bank_sums();
+        }
+    }
+    for (; n > 0; --n) {
+        start_chains();
         NSK_STEP(0)
         NSK_STEP(1)
         NSK_STEP(2)
         if constexpr (ST == 4) {
             NSK_STEP(3)
         }
-        if ((chain += ST) >= kChain) {
-            bank_sums();
-            chain = 0;
-        }
+        bank_sums();
     }
 #undef NSK_STEP
     // (the last ST - 1 k-tiles have been requested; what the loop requested past the end were zeros)
@@ -257,6 +281,7 @@ __global__ __launch_bounds__(64 * WM * WN) void wgrad_pipe_kernel(const PipeArgs
     asm volatile("" ::: "memory");              \
     multiply(std::integral_constant<int, (S)>{});
     const int rest = nk % ST;
+    start_chains();
     if (rest > 0) {
         NSK_REST(0)
     }
