@@ -154,15 +154,44 @@ __global__ __launch_bounds__(256) void bn_reduce_nhwc(const T *__restrict__ x, c
             }
         }
     }
-    __shared__ float red0[256 * VEC], red1[256 * VEC];
+    __shared__ __attribute__((aligned(16))) float red0[256 * VEC], red1[256 * VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
         red0[threadIdx.x * VEC + e] = s0[e];
         red1[threadIdx.x * VEC + e] = s1[e];
     }
     __syncthreads();
-    // the columns of the chunk are summed over the RP row groups (row group rr holds its channels at rr*CC..)
+    // The columns of the chunk are summed over the RP row groups (row group rr holds its channels at rr*CC..).  Few channels make RP
+    // large (85 for 24 channels in bf16): up to 16 threads a column then take every 16th group each, and all is added in
+    // fp64.  With one thread and one float chain a column that chain was the largest error of the pass (24 channels, 62
+    // images of 12x16: invstd 1.5e-7, dgamma 2.0e-7 against 64 bits) and took longer (16 channels, 256 images of 32x32,
+    // forward and backward 14.2, 20.5 -> 13.2, 19.8 us).
     const int CC = t.CV * VEC, c0 = t.cv0 * VEC;
+    if (RP > 32) {          // (CC is at most 56)
+        const int parts = min(256 / CC, 16), q = threadIdx.x / CC, c = threadIdx.x - q * CC;
+        double a0 = 0., a1 = 0.;
+        if (q < parts)
+            for (int g = q; g < RP; g += parts) {
+                a0 += red0[g * CC + c];
+                a1 += red1[g * CC + c];
+            }
+        __syncthreads();
+        double *const few0 = (double *)red0, *const few1 = (double *)red1;
+        if (q < parts) {
+            few0[q * CC + c] = a0;
+            few1[q * CC + c] = a1;
+        }
+        __syncthreads();
+        if (q == 0) {
+            for (int g = 1; g < parts; ++g) {
+                a0 += few0[g * CC + c];
+                a1 += few1[g * CC + c];
+            }
+            p0[(long)blockIdx.x * C + c0 + c] = (float)a0;
+            p1[(long)blockIdx.x * C + c0 + c] = (float)a1;
+        }
+        return;
+    }
     for (int c = threadIdx.x; c < CC; c += 256) {
         float a0 = 0.f, a1 = 0.f;
 #pragma unroll 8

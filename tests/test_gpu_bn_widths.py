@@ -89,3 +89,20 @@ def test_many_rows_are_added_without_long_float_chains(lay):
     # no run of float additions is longer than 64 rows of 104 before fp64: at most 64 roundings of 6656 in 63 runs, in a random walk
     bar = 8 * np.sqrt(64 * 63) * 2.0 ** -24 * 6656 / 2 / (H * W)
     assert np.abs(mean.cpu().numpy() - want).max() <= bar + 2.0 ** -24 * np.abs(want).max()
+
+
+# A thread adds up at most eight rows here, three roundings a row, and what follows is in fp64: 2.5e-8 * sqrt(24 / 2), 2.5e-8 being
+# the rms of one rounding.
+@pytest.mark.parametrize("dtype,N,C,H,W", [("bf16", 95, 24, 20, 17), ("bf16", 27, 24, 40, 66), ("f32", 64, 12, 28, 28), ("f32", 64, 16, 40, 42)])
+def test_sums_of_few_channels_keep_their_precision(dtype, N, C, H, W):
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x, dy = (torch.randn((N, H, W, C), generator=g, device="cuda").to(torch_dtype(dtype)) for _ in range(2))
+    one, zero = torch.ones(C, device="cuda"), torch.zeros(C, device="cuda")
+    out, mean, inv = B.bn_relu_add_fwd(x, one, zero, None, 1e-5, True)
+    _, _, dg, db = B.bn_relu_add_bwd(x, out, dy, one, mean, inv, True)
+    off = lambda a, w: float((a.double() - w).norm() / w.norm())
+    dz = torch.where(out > 0, dy.double(), torch.zeros((), dtype=torch.float64, device="cuda"))
+    assert off(db, dz.sum((0, 1, 2))) <= 9e-8
+    assert off(dg, (dz * ((x.double() - mean.double()) * inv.double())).sum((0, 1, 2))) <= 9e-8
+    var = ((x.double() - x.double().mean((0, 1, 2))) ** 2).mean((0, 1, 2))
+    assert off(inv, torch.rsqrt(var + 1e-5)) <= 9e-8
