@@ -51,14 +51,17 @@ bool nhwc_fast(const nsk_bn_desc_t &d)
     return cv <= 256 && 256 % cv == 0;
 }
 
-// Elements per access of the NHWC path, 0: the generic path, which a small tensor's three launches are no worse off with (us,
-// forward / backward, generic / NHWC: bf16 24 channels, 8 images of 14x14 7.9, 8.0 / 9.9, 10.3; fp32 48 channels, 4 of 28x28,
-// 150 k elements, 8.4, 9.5 / 8.5, 9.4).
+// Elements per access of the NHWC path, 0: the generic path, which is the faster one for small tensors of few channels (a block's
+// last sums are longer here, the generic path divides per element).  Forward + backward with ReLU, 16 images, us, generic /
+// here, thousands of elements: bf16 24 channels 198 16 / 19, 433 18 / 22, 693 24 / 23; 96 181 17 / 18, 433 21 / 22, 661 26 /
+// 21; with 8-byte vectors 36 297 18 / 18, 441 19 / 19, 689 24 / 20; 100 189 17 / 19, 264 19 / 18, 400 21 / 18; fp32 12 300 17 /
+// 20, 432 22 / 21; 24 198 17 / 19, 294 18 / 18, 433 23 / 20; 100 189 17 / 19, 264 19 / 18, 400 24 / 18.
 int nhwc_vec(const nsk_bn_desc_t &d)
 {
     if (d.layout != NSK_NHWC || d.C % 4) return 0;
-    if (!nhwc_fast(d) && (long)d.N * d.H * d.W * d.C < (128L << 10)) return 0;
-    return d.dtype == NSK_BF16 && d.C % 8 == 0 ? 8 : 4;
+    const int vec = d.dtype == NSK_BF16 && d.C % 8 == 0 ? 8 : 4;
+    const long least = d.dtype == NSK_F32 ? (d.C < 16 ? 384L << 10 : 256L << 10) : vec == 4 && d.C >= 48 ? 256L << 10 : 512L << 10;
+    return nhwc_fast(d) || (long)d.N * d.H * d.W * d.C >= least ? vec : 0;
 }
 
 // ----------------------------------------------------------------------------- NHWC path

@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("C", [4, 12, 24, 36, 96, 100, 344, 520, 1028, 1032, 2056, 4100])
 def test_any_width(C, dtype, relu, res):
-    N, H, W = (2, 7, -(-131072 // (14 * C)) + (0 if relu else 3)) if res or C > 400 else (3, 11, 13)   # from 128 k elements on; below
+    N, H, W = (2, 7, -(-524288 // (14 * C)) + (0 if relu else 3)) if res or C > 400 else (3, 11, 13)   # from 512 k elements on; below
     print(f"batch-norm C={C} {dtype} relu={relu} residual={res}", flush=True)
     tol, s = TOL[dtype], 7000 + C
     # means of about one: a mean comes from chains of float sums of differences of size 1..4, at most 32 long here, so it is good to
@@ -51,7 +51,7 @@ def test_any_width(C, dtype, relu, res):
 @pytest.mark.parametrize("C,rows,lay", [(96, 3000, B.NSK_NHWC), (100, 2000, B.NSK_NHWC), (1032, 1500, B.NSK_NHWC), (64, 5000, B.NSK_NHWC),
                                         (20, 4000, B.NSK_NCHW), (96, 1100, B.NSK_NCHW)])
 def test_statistics_handed_in(C, rows, lay, dtype):
-    N, H, W, s = 2, 25, 31, 7900 + C
+    N, H, W, s = 2, 50, 54 if lay == B.NSK_NHWC else 31, 7900 + C      # (NHWC: enough elements for the vectors)
     x = on_grid(gen.normal(s, 0, (N, C, H, W)), dtype)
     gx = to_gpu(x, dtype, lay)
     # the rows add up to the tensor's sums: as many random rows as fit, the rest in the last
