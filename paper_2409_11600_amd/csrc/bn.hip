@@ -378,16 +378,18 @@ __global__ __launch_bounds__(256) void bn_stats_fold(const float *__restrict__ i
     for (int c = threadIdx.x; c < 2 * C; c += 256) {
         const int arr = c / C, cc = c - arr * C;
         const float *p = in + (size_t)arr * R * C + cc;
-        float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+        // fp64: in float a share of 1500 rows would cost E[x^2] - E[x]^2 its last digits; eight loads on their way
+        double s[4] = {};
         int r = r0;
-        for (; r + 3 < r1; r += 4) {
-            s0 += p[(size_t)r * C];
-            s1 += p[(size_t)(r + 1) * C];
-            s2 += p[(size_t)(r + 2) * C];
-            s3 += p[(size_t)(r + 3) * C];
+        for (; r + 7 < r1; r += 8) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = p[(size_t)(r + e) * C];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] += (double)v[e] + (double)v[e + 4];
         }
-        for (; r < r1; ++r) s0 += p[(size_t)r * C];
-        out[(size_t)arr * R2 * C + (size_t)j * C + cc] = (s0 + s1) + (s2 + s3);
+        for (; r < r1; ++r) s[0] += (double)p[(size_t)r * C];
+        out[(size_t)arr * R2 * C + (size_t)j * C + cc] = (float)((s[0] + s[1]) + (s[2] + s[3]));
     }
 }
 
@@ -501,7 +503,7 @@ Geom geometry(const nsk_bn_desc_t &d, bool backward)
         // count is only used while that stays within 2 MB per array.
         long cap = (!backward && g.total >= (16L << 20)) ? 2048 : 512;
         if (cap * d.C > (512L << 10)) cap = 512;
-        // (other channel counts, up to 65535, stay within 2 MB per array throughout: 8 blocks of 32 chunks at the most)
+        // (other channel counts, up to 65535, stay within 2 MB per array throughout)
         if (!nhwc_fast(d) && cap * d.C > (512L << 10)) cap = (512L << 10) / d.C;
         if (G > cap) G = cap;
         if (G < 1) G = 1;
@@ -538,10 +540,19 @@ int stream_blocks(long work_items, int per_block = 256)
     return (int)b;
 }
 
-// Thousands of rows of statistics are folded into G before the finalize kernel reads them, unless that leaves few blocks with
-// long float chains (the general path of a batch of few images): then it reads them all, in fp64.  fp32 1x1 20 -> 20 at 112x108,
-// N=3, NCHW, 1134 rows, all passes 127.5 us with three blocks, 97.0 without.
-bool fold_pays(int stats_rows, const Geom &g) { return stats_rows > 1024 && stats_rows > g.G && g.G >= 64; }
+// Thousands of rows of statistics are folded into at most G (what the workspace holds) before the finalize kernel, a block per
+// channel, reads them column by column.  That kernel alone takes 0.5-0.9 ns a row while the sums fit an L2 of 4 MB, and
+// 1.2-2 ns beyond, since every block then fetches whole cache lines for its four bytes a row; a fold block takes 21 ns a
+// row of its share.  So with few blocks (the general path: 1024 / C, at most one an image) folding only pays beyond 4 MB, or
+// from 48 blocks on where the rows are very many (us for both, NCHW, folded / not: 32 channels G=32 20 k rows 19 / 36, 50 k 38 /
+// 82; 40 channels G=24 15 k 20 / 32; 20 channels G=32 30 k 26 / 42; 8 channels G=48 20 k 15 / 21, 50 k 28 / 46; with four loads
+// on their way and 34 ns a row: 40 channels G=24 10 k 20 / 13, 20 channels G=3 10 k 110 / 10, 512 channels G=2 1540 / 77; from
+// G=64 on folding never loses above 1024 rows).
+bool fold_pays(int stats_rows, int C, const Geom &g)
+{
+    if (stats_rows <= 1024 || stats_rows <= g.G) return false;
+    return g.G >= 64 || (g.G >= 24 && (long)stats_rows * C * 8 > (4L << 20)) || (g.G >= 48 && stats_rows > 16384);
+}
 
 dim3 apply_grid(const Geom &g) { return dim3(stream_blocks(g.M, g.RP), g.chunks); }
 
@@ -567,7 +578,7 @@ int bn_fwd_typed(const nsk_bn_desc_t &d, const T *x, const T *res, const float *
         // (the finalize kernel has one wavefront per channel).
         const float *q0 = stats, *q1 = stats + (long)stats_rows * d.C;
         int rows = stats_rows;
-        if (fold_pays(stats_rows, g)) {
+        if (fold_pays(stats_rows, d.C, g)) {
             const int run = ceil_div(stats_rows, g.G), r2 = ceil_div(stats_rows, run);
             hipLaunchKernelGGL(bn_stats_fold, dim3(r2), dim3(256), 0, stream, stats, stats_rows, d.C, run, p0, r2);
             q0 = p0;
@@ -748,7 +759,7 @@ int launch_bn_coeffs(const nsk_bn_desc_t &d, const float *gamma, const float *be
     float *p0 = (float *)ws;
     const float *q0 = stats, *q1 = stats + (long)stats_rows * d.C;
     int rows = stats_rows;
-    if (fold_pays(stats_rows, g)) {
+    if (fold_pays(stats_rows, d.C, g)) {
         const int run = ceil_div(stats_rows, g.G), r2 = ceil_div(stats_rows, run);
         hipLaunchKernelGGL(bn_stats_fold, dim3(r2), dim3(256), 0, stream, stats, stats_rows, d.C, run, p0, r2);
         q0 = p0;

@@ -106,3 +106,18 @@ def test_sums_of_few_channels_keep_their_precision(dtype, N, C, H, W):
     assert off(dg, (dz * ((x.double() - mean.double()) * inv.double())).sum((0, 1, 2))) <= 9e-8
     var = ((x.double() - x.double().mean((0, 1, 2))) ** 2).mean((0, 1, 2))
     assert off(inv, torch.rsqrt(var + 1e-5)) <= 9e-8
+
+
+# N, C: G = min(1024 / C, N) blocks; either side of the lines for folding (rows x C x 8 bytes of 4 MB, 16384 rows at 48 blocks)
+@pytest.mark.parametrize("N,C,rows", [(24, 40, 13000), (24, 40, 13200), (32, 32, 16300), (32, 32, 16500), (48, 8, 16300), (48, 8, 16500),
+                                      (64, 8, 1100), (23, 32, 17000), (3, 20, 30000)])
+def test_rows_of_statistics_either_side_of_the_fold(N, C, rows):
+    g, side = np.random.default_rng(N + C + rows), int(np.sqrt(rows / N)) + 1
+    part = np.stack([g.standard_normal((rows, C)) + 1, np.abs(g.standard_normal((rows, C))) + 3]).astype(np.float32)
+    x, one, zero = torch.zeros((N, C, side, side), device="cuda:0"), torch.ones(C, device="cuda:0"), torch.zeros(C, device="cuda:0")
+    _, mean, inv = B.bn_relu_add_fwd(x, one, zero, None, 1e-5, False, B.NSK_NCHW, stats=torch.from_numpy(part).to("cuda:0"))
+    n = N * side * side
+    s = part.astype(np.float64).sum(1) / n
+    # the rows are added in fp64; a folded row, mean and invstd are each rounded to float once
+    assert max_rel_err(mean.cpu().numpy(), s[0]) <= 2.0 ** -23
+    assert max_rel_err(inv.cpu().numpy(), 1 / np.sqrt(s[1] - s[0] ** 2 + 1e-5)) <= 2.0 ** -23 * (s[1] + 2 * s[0] ** 2).max() / (s[1] - s[0] ** 2).min()
