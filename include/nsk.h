@@ -115,7 +115,10 @@ void nsk_test_hooks_reload(void);
 int nsk_conv2d_out_dims(const nsk_conv_desc_t *desc, int *P, int *Q);
 
 /* Bytes of workspace the given pass (NSK_PASS_*) needs for this descriptor; 0 for an invalid
- * descriptor or pass.  Host only, deterministic, never exceeds what the call will use. */
+ * descriptor or pass.  Host only, deterministic, never exceeds what the call will use.
+ * Where channels are not whole 16-byte vectors (C forward, K backward, both for the weights) it counts copies of the
+ * operands with zero channels up to the next whole one, which the calls run 3 to 40 times faster on.  A call with less still
+ * runs if there is room for what the operands as they lie need (an NSK_NHWC forward pass: nothing, NULL will do). */
 size_t nsk_conv2d_workspace_bytes(const nsk_conv_desc_t *desc, int pass);
 
 /* Forward convolution.  x: [N,C,H,W] in desc->layout, w: [K,C,R,S] (KCRS or KRSC),

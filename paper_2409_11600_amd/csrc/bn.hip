@@ -705,13 +705,18 @@ int launch_bn_fwd(const nsk_bn_desc_t &d, const void *x, const void *residual, c
                                save_invstd, running_mean, running_var, (float *)ws, relu_mask, stats, stats_rows, stream);
 }
 
-// Partial sums of x and x^2 per channel, [2][bn_stats_rows(d)][C] floats, not shifted: what the convolution kernels
+// Partial sums of x and x^2 per channel, [2][rows][C] floats (bn_stats_rows(d) of them are best), not shifted: what the convolution kernels
 // with a fused statistics epilogue write, produced here by a reduction pass for the shapes they do not cover.
 int bn_stats_rows(const nsk_bn_desc_t &d) { return geometry(d, false).G; }
 
-int launch_bn_stats(const nsk_bn_desc_t &d, const void *x, float *stats, hipStream_t stream)
+int launch_bn_stats(const nsk_bn_desc_t &d, const void *x, float *stats, int rows, hipStream_t stream)
 {
-    const Geom g = geometry(d, false);
+    Geom g = geometry(d, false);
+    if (rows != g.G) {      // blocks past the end of the tensor leave zeros
+        g.G = rows;
+        g.rows_per_block = (g.M + rows - 1) / rows;
+        g.npg = ceil_div(d.N, rows);
+    }
     float *p0 = stats, *p1 = stats + (long)g.G * d.C;
 #define NSK_STATS(T)                                                                                                   \
     if (g.vec)                                                                                                         \

@@ -110,6 +110,7 @@ ConvGeo padded_geometry(const ConvGeo &g, int pass, int groups)
 
 // Workspace segments (byte offsets, each 256-aligned).
 struct ConvPlan {
+    ConvGeo geo;         // the layer as the kernels see it
     size_t act_in = 0;   // NHWC copy of the NCHW input activation (x or dy), or its copy with whole channel vectors
     size_t act_in2 = 0;  // wgrad only: the same of dy
     size_t filt = 0;     // packed filter
@@ -131,10 +132,11 @@ void fwd_geometry(const ConvGeo &g, IgemmArgs *a);
 
 // act: the call applies a batch-norm + ReLU to x on load (NHWC, one group); where the kernel that takes the layer has no
 // fused load the activation is applied into the workspace first.
-ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = false)
+ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = false, bool pad = true)
 {
     ConvPlan p;
-    const ConvGeo g = padded_geometry(desc, pass, groups);
+    const ConvGeo g = pad ? padded_geometry(desc, pass, groups) : desc;
+    p.geo = g;
     const bool pad_c = g.C != desc.C, pad_k = g.K != desc.K;
     const size_t w_elems = g.w_elems / (size_t)groups;
     p.stem = groups == 1 && stem_applicable(g);
@@ -215,6 +217,16 @@ ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = fal
     }
     p.total = off;
     return p;
+}
+
+// The plan of a call: where the workspace is too small for the copies with whole channel vectors (an NHWC forward pass on the
+// operands as they lie needs none at all), the element-wise kernels take the layer.
+ConvPlan plan_within(const ConvGeo &desc, int pass, int groups, bool act, const void *ws, size_t have)
+{
+    const ConvPlan p = plan_conv(desc, pass, groups, act);
+    if ((ws ? have : 0) >= p.total || (p.geo.C == desc.C && p.geo.K == desc.K)) return p;
+    const ConvPlan q = plan_conv(desc, pass, groups, act, false);
+    return q.total <= (ws ? have : 0) ? q : p;
 }
 
 bool misaligned(const void *p) { return ((uintptr_t)p & 15) != 0; }
@@ -339,7 +351,7 @@ int conv_fwd_impl(const nsk_conv_desc_t *desc, int groups, const void *x, const 
     if (!x || !w || !y) return NSK_ERR_NULL;
     if (misaligned(x) || misaligned(w) || misaligned(y)) return NSK_ERR_ALIGNMENT;
     NSK_TRY(check_act(g, groups, act));
-    const ConvPlan p = plan_conv(g, NSK_PASS_FWD, groups, act != nullptr);
+    const ConvPlan p = plan_within(g, NSK_PASS_FWD, groups, act != nullptr, workspace, workspace_bytes);
     const int cg = g.C / groups, kg = g.K / groups;
     NSK_TRY(check_ws(workspace, workspace_bytes, p.total));
     hipStream_t st = (hipStream_t)stream;
@@ -352,16 +364,17 @@ int conv_fwd_impl(const nsk_conv_desc_t *desc, int groups, const void *x, const 
     }
     bool fused = false;
     const int rows = stats ? conv_stats_rows(g, &fused) : 0;
+    if (p.geo.C == g.C && padded_geometry(g, NSK_PASS_FWD, groups).C != g.C) fused = false;   // (rows: what the query answered)
     if (p.stem) {
         void *y_nhwc = nullptr;
         NSK_TRY(stem_fwd(g, x, w, y, ws, fused ? stats : nullptr, rows, &y_nhwc, st));
-        if (stats && !fused) NSK_TRY(launch_bn_stats(output_as_bn(g), y_nhwc, stats, st));
+        if (stats && !fused) NSK_TRY(launch_bn_stats(output_as_bn(g), y_nhwc, stats, rows, st));
         return NSK_OK;
     }
 
     const void *src = x, *filt = w;
     void *dst = y;
-    const ConvGeo gp = padded_geometry(g, NSK_PASS_FWD, groups);
+    const ConvGeo &gp = p.geo;
     const bool nchw = g.layout == NSK_NCHW;
     if (nchw || gp.C != g.C) {
         if (nchw)
@@ -393,7 +406,7 @@ int conv_fwd_impl(const nsk_conv_desc_t *desc, int groups, const void *x, const 
     }
     a.act = act;
     NSK_TRY(launch_igemm(g.dtype, a, st));
-    if (stats && !fused) NSK_TRY(launch_bn_stats(output_as_bn(g), dst, stats, st));
+    if (stats && !fused) NSK_TRY(launch_bn_stats(output_as_bn(g), dst, stats, rows, st));
     if (nchw) NSK_TRY(launch_nhwc_to_nchw(g.dtype, dst, y, g.N, g.K, g.P, g.Q, 0, st));
     return NSK_OK;
 }
@@ -518,8 +531,8 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     if (!dy || !w || !dx) return NSK_ERR_NULL;
     if (accumulate != 0 && accumulate != 1) return NSK_ERR_BAD_DESC;
     if (misaligned(dy) || misaligned(w) || misaligned(dx)) return NSK_ERR_ALIGNMENT;
-    const ConvPlan p = plan_conv(g, NSK_PASS_DGRAD, groups);
-    const ConvGeo gp = padded_geometry(g, NSK_PASS_DGRAD, groups);
+    const ConvPlan p = plan_within(g, NSK_PASS_DGRAD, groups, false, workspace, workspace_bytes);
+    const ConvGeo &gp = p.geo;
     const int cg = g.C / groups, kg = gp.K / groups;   // channels of one group (all of them for a plain convolution)
     NSK_TRY(check_ws(workspace, workspace_bytes, p.total));
     hipStream_t st = (hipStream_t)stream;
@@ -663,7 +676,7 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     if (accumulate != 0 && accumulate != 1) return NSK_ERR_BAD_DESC;
     if (misaligned(x) || misaligned(dy) || misaligned(dw)) return NSK_ERR_ALIGNMENT;
     NSK_TRY(check_act(g, groups, act));
-    const ConvPlan p = plan_conv(g, NSK_PASS_WGRAD, groups, act != nullptr);
+    const ConvPlan p = plan_within(g, NSK_PASS_WGRAD, groups, act != nullptr, workspace, workspace_bytes);
     const int cg = g.C / groups, kg = g.K / groups;
     NSK_TRY(check_ws(workspace, workspace_bytes, p.total));
     hipStream_t st = (hipStream_t)stream;
@@ -677,7 +690,7 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     const bool nchw = g.layout == NSK_NCHW;
     if (p.stem) return stem_wgrad(g, x, dy, dw, accumulate, ws, st);
     const void *xs = x, *dys = dy;
-    const ConvGeo gp = padded_geometry(g, NSK_PASS_WGRAD, groups);
+    const ConvGeo &gp = p.geo;
     const bool pad_c = gp.C != g.C, pad_k = gp.K != g.K;
     if (nchw) {
         NSK_TRY(launch_nchw_to_nhwc(g.dtype, x, ws + p.act_in, g.N, g.C, g.H, g.W, gp.C, st));

@@ -277,7 +277,7 @@ int launch_bn_fwd(const nsk_bn_desc_t &d, const void *x, const void *residual, c
                   float *running_mean, float *running_var, void *ws, unsigned char *relu_mask, const float *stats,
                   int stats_rows, hipStream_t stream);
 int bn_stats_rows(const nsk_bn_desc_t &d);
-int launch_bn_stats(const nsk_bn_desc_t &d, const void *x, float *stats, hipStream_t stream);
+int launch_bn_stats(const nsk_bn_desc_t &d, const void *x, float *stats, int rows, hipStream_t stream);   // any number of rows
 int launch_bn_bwd(const nsk_bn_desc_t &d, const void *x, const void *out, const void *dout,
                   const float *gamma, const float *save_mean, const float *save_invstd, void *dx,
                   void *dres, float *dgamma, float *dbeta, void *ws, const unsigned char *relu_mask,

@@ -36,7 +36,10 @@ def nsk_env(monkeypatch):
     from paper_2409_11600_amd import binding
 
     def set_switch(name, value):
-        monkeypatch.setenv(name, value)
+        if value is None:
+            monkeypatch.delenv(name)
+        else:
+            monkeypatch.setenv(name, value)
         binding.lib().nsk_test_hooks_reload()
 
     yield set_switch

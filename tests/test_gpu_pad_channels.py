@@ -1,6 +1,8 @@
 """Layers whose channel counts are not whole 16-byte vectors: the operands are copied with zero channels up to the next whole
 vector and the kernels for whole vectors run.  All passes, both layouts, old values added, statistics, against the oracle and
 against the element-wise kernels (the copies switched off); values that are not finite stay where they reach."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -102,3 +104,53 @@ def test_values_that_are_not_finite(dtype, nsk_env):
     for a, b in zip(got, passes()):
         assert torch.equal(torch.isnan(a), torch.isnan(b))
         assert torch.equal(torch.isinf(a), torch.isinf(b)) and not torch.isfinite(a).all() and torch.isfinite(a).any()
+
+
+@pytest.mark.parametrize("layout", [B.NSK_NHWC, B.NSK_NCHW], ids=["nhwc", "nchw"])
+@pytest.mark.parametrize("dtype,C,K", [("bf16", 20, 36), ("bf16", 13, 24), ("f32", 30, 10), ("f32", 9, 7)])
+def test_a_workspace_without_room_for_the_copies(dtype, C, K, layout, nsk_env):
+    """The layer then runs on the operands as they lie, with what that needs: nothing at all for a forward pass in NHWC."""
+    N, H, W, t = 2, 9, 11, torch_dtype(dtype)
+    x, dy = (on_grid(gen.normal(996, k, (N, c, H, W)), dtype) for k, c in ((0, C), (2, K)))
+    w = on_grid(gen.he_normal(996, 1, (K, C, 3, 3)), dtype)
+    gx, gw, gdy = (to_gpu(a, dtype, layout) for a in (x, w, dy))
+    d = B.conv_desc((N, C, H, W), (K, 3, 3), 1, 1, 1, B._dtype_code(gx), layout)
+    ref, L = ctypes.byref(d), B.lib()
+    full = [L.nsk_conv2d_workspace_bytes(ref, p) for p in range(3)]
+    rows = int(L.nsk_conv2d_stats_rows(ref))
+    nsk_env("NSK_NO_PAD", "1")
+    least = [L.nsk_conv2d_workspace_bytes(ref, p) for p in range(3)]
+    nsk_env("NSK_NO_PAD", None)
+    assert [L.nsk_conv2d_workspace_bytes(ref, p) for p in range(3)] == full
+    assert least[0] < full[0] and (layout == B.NSK_NCHW or least[0] == 0)
+    ws = torch.empty(max(least + [1]), dtype=torch.uint8, device="cuda:0")
+    at = lambda p: (ws.data_ptr() if least[p] else None, least[p])
+    stream = torch.cuda.current_stream().cuda_stream
+    y, check = guarded(gdy.shape, t)
+    stats, check_stats = guarded((2, rows, K), torch.float32)
+    assert L.nsk_conv2d_fwd(ref, gx.data_ptr(), gw.data_ptr(), y.data_ptr(), *at(0), stream) == B.NSK_OK
+    first = y.clone()
+    y.zero_()
+    stats.fill_(float("nan"))
+    assert L.nsk_conv2d_fwd_stats(ref, gx.data_ptr(), gw.data_ptr(), y.data_ptr(), stats.data_ptr(), *at(0), stream) == B.NSK_OK
+    dx, dw = torch.empty_like(gx), torch.empty(gw.shape, device="cuda:0")
+    assert L.nsk_conv2d_dgrad(ref, gdy.data_ptr(), gw.data_ptr(), dx.data_ptr(), 0, *at(1), stream) == B.NSK_OK
+    assert L.nsk_conv2d_wgrad(ref, gx.data_ptr(), gdy.data_ptr(), dw.data_ptr(), 0, *at(2), stream) == B.NSK_OK
+    torch.cuda.synchronize()
+    check()
+    check_stats()
+    assert torch.equal(y, first)
+    got = to_host(y, layout)
+    assert max_rel_err(got, oracle.conv2d_fwd(x, w, 1, 1, 1)) <= TOL[dtype]
+    # float sums of at most 198 values in every row: 198 roundings of the largest partial sum
+    sums = stats.double().sum(1).cpu().numpy()
+    assert np.abs(sums[0] - got.sum((0, 2, 3))).max() <= 198 * 2.0 ** -24 * np.abs(got).sum((0, 2, 3)).max()
+    assert np.abs(sums[1] - (got ** 2).sum((0, 2, 3))).max() <= 198 * 2.0 ** -24 * (got ** 2).sum((0, 2, 3)).max()
+    assert max_rel_err(to_host(dx, layout), oracle.conv2d_dgrad(dy, w, x.shape, 1, 1, 1)) <= TOL[dtype]
+    assert max_rel_err(to_host(dw, layout), oracle.conv2d_wgrad(x, dy, w.shape, 1, 1, 1)) <= TOL["f32"]
+    for p in (0, 1, 2):                 # less than that is refused as ever
+        if least[p]:
+            args = [(gx, gw, y), (gdy, gw, dx), (gx, gdy, dw)][p]
+            call = [L.nsk_conv2d_fwd, L.nsk_conv2d_dgrad, L.nsk_conv2d_wgrad][p]
+            mid = () if p == 0 else (0,)
+            assert call(ref, *(a.data_ptr() for a in args), *mid, ws.data_ptr(), least[p] - 1, stream) == B.NSK_ERR_WORKSPACE
