@@ -336,15 +336,9 @@ int launch_grouped8_wgrad(const WgradArgs &a, hipStream_t stream)
     g.by_w = make_div(g.W);
     g.by_strips = make_div(g.strips);
     const size_t smem = (size_t)((((g.rows + 2) * (g.W + 2) + 7) & ~7) + ((g.rows * g.W + 7) & ~7) + 1) * 128;
-    static bool attr_set = false;
-    if (!attr_set) {
-        const hipError_t e = hipFuncSetAttribute((const void *)grouped8_wgrad_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
-        if (e != hipSuccess) {
-            set_last_hip_error(e);
-            return NSK_ERR_HIP;
-        }
-        attr_set = true;
-    }
+    static std::atomic<unsigned long long> done{0};
+    const int rc = allow_lds((const void *)grouped8_wgrad_kernel, 80 * 1024, done);
+    if (rc != NSK_OK) return rc;
     hipLaunchKernelGGL(grouped8_wgrad_kernel, dim3((unsigned)(g.chunks * g.splits)), dim3(256), smem, stream, g);
     return check_launch();
 }

@@ -235,14 +235,10 @@ __global__ __launch_bounds__(GQ_THREADS) void gru_seq_kernel(const GruSeqArgs a)
 template <typename T, bool BWD, int IU, int M, int RS, int LS> int launch(const GruSeqArgs &a, hipStream_t stream)
 {
     const size_t smem = 2 * (BWD ? 3 : 1) * 32 * M * sizeof(T) + (size_t)LS * M * GQ_THREADS * 4 * sizeof(T);
-    static bool attr_set = false;
-    if (!attr_set && smem > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute((const void *)gru_seq_kernel<T, BWD, IU, M, RS, LS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) {
-            set_last_hip_error(e);
-            return NSK_ERR_HIP;
-        }
-        attr_set = true;
+    static std::atomic<unsigned long long> done{0};
+    if (smem > 64 * 1024) {
+        const int rc = allow_lds((const void *)gru_seq_kernel<T, BWD, IU, M, RS, LS>, smem, done);
+        if (rc != NSK_OK) return rc;
     }
     hipLaunchKernelGGL((gru_seq_kernel<T, BWD, IU, M, RS, LS>), dim3(a.N), dim3(GQ_THREADS), smem, stream, a);
     return check_launch();

@@ -5,6 +5,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <type_traits>
 
 #include "nsk.h"
@@ -64,6 +65,22 @@ inline int check_launch()
         set_last_hip_error(e);
         return NSK_ERR_HIP;
     }
+    return NSK_OK;
+}
+
+// Allows a kernel `bytes` of dynamic LDS on the current device: once per device, whose own copy of the function it belongs to.
+inline int allow_lds(const void *kernel, size_t bytes, std::atomic<unsigned long long> &done)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    const unsigned long long bit = dev < 64 ? 1ull << dev : 0;
+    if (e == hipSuccess && (done.load(std::memory_order_relaxed) & bit)) return NSK_OK;
+    if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) {
+        set_last_hip_error(e);
+        return NSK_ERR_HIP;
+    }
+    done.fetch_or(bit, std::memory_order_relaxed);
     return NSK_OK;
 }
 
