@@ -353,14 +353,12 @@ template <typename T> int launch_typed(const IgemmArgs &a, hipStream_t stream)
 }
 
 // The fp32 64 -> 64 kernel gives every CU whole tiles of 8 image rows, 43 us each; the pipelined kernel takes 0.18 us a tile.
-// Measured (us, forward, 32x32): N=16 39.6 / 15.6, N=64 44.3 / 46, N=96 81.8 / 69, N=128 85-88 / 92.   Below 32 tiles it stays although it is slower (39 us): whole training
-// steps at batch 4 are pinned element by element against the oracle, and another order of the sums puts one activation
-// of the second step on the other side of zero.
+// Measured (us, forward, 32x32): N=2 38.9 / 7.7, N=16 39.6 / 15.6, N=64 44.3 / 46, N=96 81.8 / 69, N=128 85-88 / 92.
 bool takes_halo64_f32(int dtype, const IgemmArgs &a)
 {
     if (!halo64_f32_applicable(dtype, a)) return false;
     const long tiles = (long)a.Nimg * (a.Hs / 8);
-    return hooks().halo64_always || tiles < 32 || (tiles + 255) / 256 * 256 * 100 <= tiles * 105;
+    return hooks().halo64_always || (tiles + 255) / 256 * 256 * 100 <= tiles * 105;
 }
 
 }  // namespace

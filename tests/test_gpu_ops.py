@@ -578,6 +578,7 @@ def test_conv_statistics_feed_the_batch_norm(i, big, layout, nsk_env):
     with the oracle."""
     dtype, (N, C, H, W, K, R, S, st, pd, dl) = STATS_SHAPES[i]
     nsk_env("NSK_STATS_ALWAYS", "1")     # the generic kernel's statistics epilogue also for short reductions
+    nsk_env("NSK_HALO64_ALWAYS", "1")
     if big:
         if dtype != "bf16" or C % 64 or K % 64:
             pytest.skip("the large-tile kernel takes bf16 layers with channel counts that are multiples of 64")
@@ -663,7 +664,8 @@ ACT_SHAPES = [
 
 
 @pytest.mark.parametrize("i", range(len(ACT_SHAPES)))
-def test_fused_activation_calls(i):
+def test_fused_activation_calls(i, nsk_env):
+    nsk_env("NSK_HALO64_ALWAYS", "1")    # the fused operand load also below the size from which its kernel is chosen
     dtype, shape, K, R, stride, pad = ACT_SHAPES[i]
     N, C, H, W = shape
     print(f"fused activation case {ACT_SHAPES[i]}", flush=True)
