@@ -105,7 +105,7 @@ int nsk_last_hip_error(void);
  *   NSK_NO_PW, NSK_NO_HALO, NSK_NO_FS, NSK_NO_HALO_WIDE, NSK_HALO_SINGLE, NSK_NO_STEM,
  *   NSK_NO_STEM_HALO, NSK_NO_TINY, NSK_NO_DEPTHWISE, NSK_NO_GROUPED8, NSK_NO_PAD, NSK_DEPTHWISE_NO_ROWS, NSK_DEPTHWISE_NO_COLS,
  *   NSK_POOL_GENERAL, NSK_REDUCE4, NSK_WH_NO_SPLIT   (set = that special kernel or variant is not chosen);
- *   NSK_HALO_WIDE_ALWAYS, NSK_HALO64_ALWAYS, NSK_STATS_ALWAYS (set = chosen also where it does not pay);
+ *   NSK_HALO_WIDE_ALWAYS, NSK_HALO64_ALWAYS (set = chosen also where it does not pay);
  *   NSK_PW_MIN_ROWS, NSK_WH_MIN_ROWS = n   (size threshold of a special kernel);
  *   NSK_IGEMM_TILE = 1..6                           (tile shape of the generic kernel, which then takes every plain layer). */
 void nsk_test_hooks_reload(void);

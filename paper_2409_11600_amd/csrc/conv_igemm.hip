@@ -225,14 +225,6 @@ __global__ __launch_bounds__(256) void igemm_kernel(const IgemmArgs a)
         constexpr int CPP = 32 * (int)sizeof(T) / 16;       // 16-byte chunks per pixel
         static_assert(4 * 32 * SROW <= (int)sizeof(smem_ab), "epilogue staging fits in the operand buffers");
         unsigned char *my_st = (unsigned char *)smem_ab + wave * (32 * SROW);
-        // Statistics epilogue (forward with a batch-norm behind it): a lane always reads back the same 16-byte piece
-        // (VEC channels) of each staged row, so it adds those channels up over all the rows it stores; one cross-lane
-        // reduction per block and one row of partial sums per wavefront.
-        float ssum[FN][VEC], ssq[FN][VEC];
-#pragma unroll
-        for (int ni = 0; ni < FN; ++ni)
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) ssum[ni][e] = ssq[ni][e] = 0.f;
 #pragma unroll
         for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
@@ -250,43 +242,9 @@ __global__ __launch_bounds__(256) void igemm_kernel(const IgemmArgs a)
                     const Vec v = *(const Vec *)(my_st + pos * SROW + ck * 16);
                     const long off = out_off[wm * WM + mi * 32 + pos];
                     const int col = wcol0 + ni * 32 + ck * VEC;
-                    if (off >= 0 && col < a.Ngemm) {
-                        *(Vec *)(out + off + col) = v;
-                        if (a.stats) {
-#pragma unroll
-                            for (int e = 0; e < VEC; ++e) {
-                                const float f = to_float(v[e]);
-                                ssum[ni][e] += f;
-                                ssq[ni][e] += f * f;
-                            }
-                        }
-                    }
+                    if (off >= 0 && col < a.Ngemm) *(Vec *)(out + off + col) = v;
                 }
             }
-        if (a.stats) {
-            const int row = blockIdx.x * (BM / WM) + wm, ck = lane % CPP;
-#pragma unroll
-            for (int ni = 0; ni < FN; ++ni) {
-#pragma unroll
-                for (int e = 0; e < VEC; ++e)
-#pragma unroll
-                    for (int o = CPP; o < 64; o <<= 1) {
-                        ssum[ni][e] += __shfl_xor(ssum[ni][e], o, 64);
-                        ssq[ni][e] += __shfl_xor(ssq[ni][e], o, 64);
-                    }
-                const int col = wcol0 + ni * 32 + ck * VEC;
-                if (lane < CPP && col < a.Ngemm) {
-                    // 16-byte stores: a handful of lanes writing single floats would cost one memory instruction each
-                    float *r0 = a.stats + (size_t)row * a.Ngemm + col;
-                    float *r1 = r0 + (size_t)a.stats_rows * a.Ngemm;
-#pragma unroll
-                    for (int e = 0; e < VEC; e += 4) {
-                        *(f32x4 *)(r0 + e) = f32x4{ssum[ni][e], ssum[ni][e + 1], ssum[ni][e + 2], ssum[ni][e + 3]};
-                        *(f32x4 *)(r1 + e) = f32x4{ssq[ni][e], ssq[ni][e + 1], ssq[ni][e + 2], ssq[ni][e + 3]};
-                    }
-                }
-            }
-        }
     } else {
         // element-wise stores (output rows that are not 16-byte granular)
 #pragma unroll
@@ -378,20 +336,11 @@ int igemm_stats_rows(int dtype, const IgemmArgs &a)
         if (halo_wide_applicable(dtype, a)) return halo_wide_stats_rows(a);
         if (halo_wide_fwd_s2_applicable(dtype, a)) return halo_wide_fwd_s2_stats_rows(a);
     }
-    // Both generic kernels need the vector epilogue and 16-byte stores of the partial sums; one row per wavefront row of every
-    // row block.
-    const int vectors = output_vectors(dtype, a);
-    if (vectors == 0) return 0;
-    // The pipelined kernel's epilogue beats the separate pass over y at every size (us, convolution + batch-norm, pass /
-    // epilogue: 256->1024 1x1 at 14x14 N=128 69.6 / 69.4, 64->128 1x1 stride 2 at 56x56 N=64 29.2 / 25.1, fp32 16->16 at
-    // 40x42 N=37 22.5 / 20.8, 72->104 at 29x37 N=20 34.0 / 20.5; 256->64 at 56x56 N=64, 3136 rows of sums, 50.1 / 51.5).
-    if (vector_runs(dtype, a)) return igemm_pipe_stats_rows(dtype, a);
-    // The element-wise kernel's, with its short reductions, does not (the variable is a test hook).
-    if (vectors != 1) return 0;
-    if (a.Ktot < 1024 && !hooks().stats_always) return 0;
-    static const int bm[3] = {256, 128, 128}, wm[3] = {64, 32, 64};
-    const int t = auto_tile(a, dtype == NSK_BF16 ? 2 : 4);
-    return ceil_div(a.M, bm[t]) * (bm[t] / wm[t]);
+    // The pipelined kernel needs 16-byte stores of the partial sums; one row per wavefront row of every row block.  Its epilogue beats
+    // the separate pass over y at every size (us, convolution + batch-norm, pass / epilogue: 256->1024 1x1 at 14x14 N=128
+    // 69.6 / 69.4, 64->128 1x1 stride 2 at 56x56 N=64 29.2 / 25.1, fp32 16->16 at 40x42 N=37 22.5 / 20.8, 72->104 at 29x37
+    // N=20 34.0 / 20.5; 256->64 at 56x56 N=64, 3136 rows of sums, 50.1 / 51.5).
+    return output_vectors(dtype, a) != 0 && vector_runs(dtype, a) ? igemm_pipe_stats_rows(dtype, a) : 0;
 }
 
 bool igemm_act_fused(int dtype, const IgemmArgs &a)
@@ -455,6 +404,7 @@ int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream)
     }
     b.vec_out = output_vectors(dtype, b);
     if (vector_runs(dtype, b)) return launch_igemm_pipe(dtype, &b, 1, stream);
+    if (b.stats) return NSK_ERR_BAD_DESC;   // (igemm_stats_rows named none)
     b.vec_out = b.vec_out == 1 ? 1 : 0;
     return dtype == NSK_BF16 ? launch_typed<bf16_t>(b, stream) : launch_typed<float>(b, stream);
 }

@@ -52,7 +52,8 @@ bool conv_pw_applicable(int dtype, const IgemmArgs &a)
         // enough tiles to give every wavefront of the grid a few; with the columns split into groups every group walks over
         // all rows, so fewer rows are enough.  Below, the pipelined kernel wins, measured (us, this kernel / that one):
         // 256->1024 on 6 k rows 13.9 / 9.6, on 25 k 31.4 / 30.0, on 50 k 53.5 / 61; 3x3 stride 2 32->64 on 13 k 6.8 / 5.6,
-        // on 50 k 11.3 / 9.6, on 200 k 29.9 / 31.6; 512->256 on 100 k 65 / 53, on 400 k 210 / 173; 512->64 on 400 k 99.6 / 104.
+        // on 50 k 11.3 / 9.6, on 200 k 29.9 / 31.6; 512 channels: to 128 on 50 k 26 / 14, on 200 k 61 / 51, to 256 on 100 k 59 / 49,
+        // on 200 k 111 / 103, to 512 on 200 k 202 / 172; to 64 on 300 k with its statistics 73 / 77, on 100 k 29 / 27.
         // One tap of 64 channels has the least to keep and needs fewer: 64->64 on 63 k 5.0 / 5.1, on 75 k 7.1 / 7.1, on 100 k 7.6 /
         // 8.4; 64->256 on 88 k 17.5 / 16.4, on 100 k 17.5 / 21.1; 64->512 (two groups) on 38 k 17.2 / 16.1, on 50 k 17.2 / 20.5;
         // likewise a whole 128->256: on 88 k 22.9 / 20.1, on 100 k 23.2 / 24.5 (128->128 on 100 k 16.1 / 15.0, on 200 k 24.3 / 25.5).

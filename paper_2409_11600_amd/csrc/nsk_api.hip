@@ -442,7 +442,6 @@ void read_hooks()
     h.depthwise_no_rows = on("NSK_DEPTHWISE_NO_ROWS");
     h.depthwise_no_cols = on("NSK_DEPTHWISE_NO_COLS");
     h.pool_general = on("NSK_POOL_GENERAL");
-    h.stats_always = on("NSK_STATS_ALWAYS");
     h.reduce4 = on("NSK_REDUCE4");
     h.wh_no_split = on("NSK_WH_NO_SPLIT");
     h.pw_min_rows = num("NSK_PW_MIN_ROWS");

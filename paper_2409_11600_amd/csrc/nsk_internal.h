@@ -49,7 +49,7 @@ __device__ inline void lds_barrier()
 // the launch path.  Each one only narrows or widens the choice among kernels that all compute the same result.
 struct TestHooks {
     bool no_pw, no_halo, no_fs, no_halo_wide, halo_wide_always, halo64_always, halo_single, no_stem, no_stem_halo,
-        no_tiny, no_depthwise, no_grouped8, no_pad, depthwise_no_rows, depthwise_no_cols, pool_general, stats_always, reduce4,
+        no_tiny, no_depthwise, no_grouped8, no_pad, depthwise_no_rows, depthwise_no_cols, pool_general, reduce4,
         wh_no_split;
     long long pw_min_rows, wh_min_rows;   // -1: not set
     int igemm_tile;                                         // 0: not set

@@ -20,7 +20,7 @@ HOOKS = [
     {},
     {"NSK_PW_MIN_ROWS": "1"},
     {"NSK_BIG_MIN_TILES": "1", "NSK_WIDE_MIN_ROWS": "1"},
-    {"NSK_PW_MIN_ROWS": "1", "NSK_BIG_MIN_TILES": "1", "NSK_WIDE_MIN_ROWS": "1", "NSK_STATS_ALWAYS": "1"},
+    {"NSK_PW_MIN_ROWS": "1", "NSK_BIG_MIN_TILES": "1", "NSK_WIDE_MIN_ROWS": "1"},
     {"NSK_HALO_WIDE_ALWAYS": "1"},       # with channel counts the wide halo kernel takes (64, 128, 256 in; multiples of 64 out)
 ]
 WIDE_HALO_GROUP = 4

@@ -577,7 +577,6 @@ def test_conv_statistics_feed_the_batch_norm(i, big, layout, nsk_env):
     sums of the stored y, and the batch-norm results must agree with the plain call (which reads y once more) and
     with the oracle."""
     dtype, (N, C, H, W, K, R, S, st, pd, dl) = STATS_SHAPES[i]
-    nsk_env("NSK_STATS_ALWAYS", "1")     # the generic kernel's statistics epilogue also for short reductions
     nsk_env("NSK_HALO64_ALWAYS", "1")
     if big:
         if dtype != "bf16" or C % 64 or K % 64:

@@ -31,7 +31,6 @@ def test_every_tile(i, dtype, tile, nsk_env):
     if dtype == "f32" and tile > 4:
         pytest.skip("four tile shapes in f32")
     nsk_env("NSK_IGEMM_TILE", str(tile))
-    nsk_env("NSK_STATS_ALWAYS", "1")
     N, C, H, W, K, R, S, st, pd, dl = SHAPES[i]
     print(f"pipelined kernel, shape {SHAPES[i]} {dtype} tile {tile}", flush=True)
     tol, ws, lay = TOL[dtype], B.Workspace(), B.NSK_NHWC
