@@ -1,4 +1,5 @@
 import os
+import re
 import sys
 
 import pytest
@@ -29,13 +30,23 @@ def pytest_collection_modifyitems(config, items):
             item.add_marker(skip)
 
 
+def nsk_switches():
+    """The names that the library's header lists as its test switches."""
+    text = open(os.path.join(ROOT, "include", "nsk.h")).read()
+    listed = text[text.index("/* Test and A/B switches."):text.index("void nsk_test_hooks_reload")]
+    return set(re.findall(r"NSK_[A-Z0-9_]+", listed))
+
+
 @pytest.fixture
 def nsk_env(monkeypatch):
-    """Sets one of libnsk's NSK_* test switches for the duration of a test.  The library reads its switches once,
-    so every change (and the restoration afterwards) is followed by nsk_test_hooks_reload()."""
+    """Sets one of libnsk's NSK_* test switches for the duration of a test (None: not set).  The library reads its switches
+    once, so every change (and the restoration afterwards) is followed by nsk_test_hooks_reload().  A name that the
+    library does not read would force nothing: it is refused."""
     from paper_2409_11600_amd import binding
+    known = nsk_switches()
 
     def set_switch(name, value):
+        assert name in known, f"{name} is no switch of the library"
         if value is None:
             monkeypatch.delenv(name)
         else:

@@ -205,3 +205,18 @@ def test_binding_raises_loudly_when_library_is_missing(monkeypatch, tmp_path):
     monkeypatch.setattr(B, "LIB_PATH", str(tmp_path / "libnsk.so"))
     with pytest.raises(RuntimeError, match="no fallback"):
         B.lib()
+
+
+def test_the_header_lists_the_switches_that_the_library_reads():
+    from conftest import nsk_switches
+    source = open(os.path.join(ROOT, "paper_2409_11600_amd", "csrc", "nsk_api.hip")).read()
+    assert nsk_switches() == set(re.findall(r'(?:on|num)\("(NSK_[A-Z0-9_]+)"\)', source))
+
+
+def test_the_tests_set_only_switches_that_the_library_reads():
+    from conftest import nsk_switches
+    here = os.path.dirname(os.path.abspath(__file__))
+    for name in sorted(os.listdir(here)):
+        if name.startswith("test_gpu") and name.endswith(".py"):
+            text = open(os.path.join(here, name)).read()
+            assert set(re.findall(r'(?:nsk_env\(|[{ ])"(NSK_[A-Z0-9_]+)"', text)) <= nsk_switches(), name

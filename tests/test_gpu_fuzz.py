@@ -1,9 +1,9 @@
 """Seeded sweep over random small convolution problems (both types and layouts, strides 1-3 per axis, padding 0-3,
 dilation 1-2, square and non-square filters, channel counts that select every kernel family), each run forward,
 backward-data (overwrite and accumulate) and backward-weight (overwrite and accumulate) against the oracle.  The
-size thresholds of the special kernels are lowered through their test hooks in four of the five groups, so that the
-small problems the fp64 oracle can afford reach the large-tile, short-reduction, merged-class and wide-halo code
-paths in shapes no hand-written case lists."""
+size thresholds of the special kernels are lowered through their test hooks in three of the five groups and the pipelined
+kernels' tile is forced in one, so that the small problems the fp64 oracle can afford reach every tile, the
+short-reduction, merged-class, 64-channel and wide-halo code paths in shapes no hand-written case lists."""
 import numpy as np
 import pytest
 import torch
@@ -19,15 +19,15 @@ CHANNELS = [3, 8, 16, 24, 32, 40, 64, 64, 128, 256]
 HOOKS = [
     {},
     {"NSK_PW_MIN_ROWS": "1"},
-    {"NSK_BIG_MIN_TILES": "1", "NSK_WIDE_MIN_ROWS": "1"},
-    {"NSK_PW_MIN_ROWS": "1", "NSK_BIG_MIN_TILES": "1", "NSK_WIDE_MIN_ROWS": "1"},
+    {"NSK_IGEMM_TILE": "each in turn"},  # the pipelined kernels' tile shapes; keeps the special kernels out
+    {"NSK_PW_MIN_ROWS": "1", "NSK_WH_MIN_ROWS": "1", "NSK_HALO64_ALWAYS": "1"},
     {"NSK_HALO_WIDE_ALWAYS": "1"},       # with channel counts the wide halo kernel takes (64, 128, 256 in; multiples of 64 out)
 ]
 WIDE_HALO_GROUP = 4
 CASES_PER_GROUP = 120
 
 
-def _draw(rng, wide_halo=False):
+def _draw(rng, wide_halo=False, hooked64=False):
     while True:
         C, K = (int(rng.choice(CHANNELS)) for _ in range(2))
         R, S = (int(rng.choice([1, 1, 2, 3, 3, 3, 5])) for _ in range(2))
@@ -43,6 +43,10 @@ def _draw(rng, wide_halo=False):
         dh, dw = (int(rng.choice([1, 1, 1, 2])) for _ in range(2))
         N = int(rng.integers(1, 5))
         H, W = int(rng.integers(4, 19)), int(rng.integers(4, 19))
+        if hooked64 and rng.random() < 0.25:      # what the kernels of the 64 -> 64 layers take, on any extents
+            C, K, R, S, sh, sw, ph, pw, dh, dw = 64, 64, 3, 3, 1, 1, 1, 1, 1, 1
+            if rng.random() < 0.4:                # ... and the fp32 one, which wants whole rows of 32 and multiples of eight of them
+                H, W = int(rng.choice([8, 16])), 32
         if C * K >= 128 * 128:
             N, H, W = min(N, 2), min(H, 10), min(W, 10)
         P = (H + 2 * ph - dh * (R - 1) - 1) // sh + 1
@@ -53,14 +57,18 @@ def _draw(rng, wide_halo=False):
 
 @pytest.mark.parametrize("group", range(len(HOOKS)))
 def test_random_convolutions_match_the_oracle(group, nsk_env):
+    tile_in_turn = "NSK_IGEMM_TILE" in HOOKS[group]
     for k, v in HOOKS[group].items():
-        nsk_env(k, v)
+        if not tile_in_turn:
+            nsk_env(k, v)
     rng = np.random.default_rng(4200 + group)
     ws = B.Workspace()
     for case in range(CASES_PER_GROUP):
-        N, C, H, W, K, R, S, st, pd, dl = shape = _draw(rng, group == WIDE_HALO_GROUP)
+        N, C, H, W, K, R, S, st, pd, dl = shape = _draw(rng, group == WIDE_HALO_GROUP, "NSK_HALO64_ALWAYS" in HOOKS[group])
         dtype = "bf16" if rng.random() < 0.65 else "f32"
         layout = B.NSK_NHWC if rng.random() < 0.8 else B.NSK_NCHW
+        if tile_in_turn:
+            nsk_env("NSK_IGEMM_TILE", str(1 + case % 6))
         print(f"fuzz group {group} case {case}: {shape} {dtype} layout={layout} hooks={sorted(HOOKS[group])}", flush=True)
         seed = 5000 + 100 * group + case
         x = on_grid(gen.normal(seed, 0, (N, C, H, W)), dtype)

@@ -81,8 +81,8 @@ def test_conv_fwd_dgrad_wgrad(i, dtype, layout):
     assert max_rel_err(to_host(dw_view, layout), oracle.conv2d_wgrad(x, dy, w.shape, st, pd, dl)) <= tol
 
 
-# Shapes with channel counts that are multiples of 64: routed through the large-tile bf16 kernel by lowering
-# its tile-count threshold (at their full sizes these layers take it on their own).
+# Shapes that take the largest tiles of the pipelined kernels (256 x 128, backward-weight 128 x 128) at their full sizes: here by
+# the switch, which also keeps the special kernels out.
 WIDE_SHAPES = [
     (2, 128, 9, 9, 256, 1, 1, 1, 0, 1),        # 1x1, two column blocks, ragged row block
     (3, 256, 10, 9, 64, 1, 1, 1, 0, 1),        # 1x1, 64-column variant, four k-tiles
@@ -90,7 +90,7 @@ WIDE_SHAPES = [
     (2, 128, 11, 13, 128, 3, 3, 1, 1, 1),      # 3x3 stride 1, 18 k-tiles, padding on every side
     (4, 64, 16, 16, 192, 1, 1, 2, 0, 1),       # 1x1 stride 2, 192 columns (half-empty second column block)
     (1, 64, 33, 17, 64, 3, 3, 1, 2, 2),        # dilation 2
-    (2, 3, 20, 24, 64, 7, 7, 2, 3, 1),         # image stem: space-to-depth, then the large-tile backward-weight kernel on 16 channels
+    (2, 3, 20, 24, 64, 7, 7, 2, 3, 1),         # image stem: space-to-depth, then backward-weight on 16 channels
     (2, 32, 12, 10, 64, 3, 3, 2, 1, 1),        # 32 input channels (four taps per 128-column tile)
     (4, 16, 12, 12, 16, 3, 3, 1, 1, 1),        # 16 -> 16: a quarter of the 64-row backward-weight tile is live
     (4, 16, 12, 12, 32, 3, 3, 2, 1, 1),        # 16 -> 32 stride 2
@@ -105,9 +105,8 @@ WIDE_SHAPES = [
 
 @pytest.mark.parametrize("layout", LAYOUTS)
 @pytest.mark.parametrize("i", range(len(WIDE_SHAPES)))
-def test_conv_wide_layers_large_tile_kernel(i, layout, nsk_env):
-    nsk_env("NSK_BIG_MIN_TILES", "1")
-    nsk_env("NSK_WIDE_MIN_ROWS", "1")
+def test_conv_wide_layers_on_the_largest_tiles(i, layout, nsk_env):
+    nsk_env("NSK_IGEMM_TILE", "1")
     N, C, H, W, K, R, S, st, pd, dl = WIDE_SHAPES[i]
     print(f"wide conv case {i} {WIDE_SHAPES[i]} layout={layout}", flush=True)
     dtype = "bf16"
@@ -135,7 +134,7 @@ def test_conv_wide_layers_large_tile_kernel(i, layout, nsk_env):
     assert np.all(got_dx[want_dx == 0.0] == 0.0)
     want_acc = oracle.conv2d_dgrad(dy, w, x.shape, st, pd, dl, into=base.astype(np.float64))
     assert max_rel_err(to_host(gacc, layout), want_acc) <= tol
-    # backward-weight through the large-tile kernel, overwrite and accumulate
+    # backward-weight, overwrite and accumulate
     dw_view, dw_check = guarded(gw.shape, torch.float32)
     B.conv2d_wgrad(gx, gdy, w.shape, st, pd, dl, layout, out=dw_view, ws=ws)
     base_w = gen.normal(700 + i, 4, w.shape).astype(np.float32)
@@ -413,6 +412,7 @@ def test_halo_backward_weight_many_chunks_per_block(dtype, nsk_env):
     """3x3 64->64 backward-weight on enough positions that every block of the halo kernel walks several chunks (the
     double-buffered hand-over between its moving and its multiplying wavefronts), against the oracle; the variant
     without split roles must give the same bits."""
+    nsk_env("NSK_WH_MIN_ROWS", "1")
     N, C, H, W, K = 8, 64, 46, 46, 64
     print(f"halo backward-weight, many chunks: {(N, C, H, W, K)} {dtype}", flush=True)
     x = on_grid(gen.normal(880, 0, (N, C, H, W)), dtype)
@@ -559,9 +559,9 @@ def test_conv_is_bitwise_reproducible(dtype):
 STATS_SHAPES = [
     ("bf16", (3, 64, 20, 24, 64, 3, 3, 1, 1, 1)),      # bf16 3x3 64->64 (two-group halo kernel), several tiles per block
     ("f32", (2, 64, 16, 32, 64, 3, 3, 1, 1, 1)),       # fp32 row-aligned halo kernel
-    ("bf16", (2, 128, 9, 9, 256, 1, 1, 1, 0, 1)),      # generic kernel, 128x128 tiles
-    ("bf16", (2, 32, 16, 16, 64, 3, 3, 2, 1, 1)),      # generic kernel, 128x64 tiles, stride 2
-    ("f32", (2, 16, 15, 15, 32, 1, 1, 2, 0, 1)),       # generic kernel, fp32, 256x32 tiles, ragged
+    ("bf16", (2, 128, 9, 9, 256, 1, 1, 1, 0, 1)),      # 1x1, pipelined kernel
+    ("bf16", (2, 32, 16, 16, 64, 3, 3, 2, 1, 1)),      # stride 2, pipelined kernel
+    ("f32", (2, 16, 15, 15, 32, 1, 1, 2, 0, 1)),       # fp32, ragged
     ("bf16", (2, 3, 20, 24, 64, 7, 7, 2, 3, 1)),       # image stem (space-to-depth + halo kernel)
     ("bf16", (1, 5, 9, 9, 7, 3, 3, 3, 1, 1)),          # scalar epilogue: separate reduction pass
     ("f32", (2, 3, 30, 30, 16, 3, 3, 1, 1, 1)),        # 3-channel stem on the generic path
@@ -569,20 +569,18 @@ STATS_SHAPES = [
 
 
 @pytest.mark.parametrize("layout", LAYOUTS)
-@pytest.mark.parametrize("big", [False, True])
+@pytest.mark.parametrize("largest_tile", [False, True])
 @pytest.mark.parametrize("i", range(len(STATS_SHAPES)))
-def test_conv_statistics_feed_the_batch_norm(i, big, layout, nsk_env):
+def test_conv_statistics_feed_the_batch_norm(i, largest_tile, layout, nsk_env):
     """nsk_conv2d_fwd_stats leaves per-channel partial sums of its stored output; nsk_bn_relu_add_fwd_stats takes its
     batch statistics from them.  y must equal the plain forward bit for bit, the partial sums must add up to the
     sums of the stored y, and the batch-norm results must agree with the plain call (which reads y once more) and
     with the oracle."""
     dtype, (N, C, H, W, K, R, S, st, pd, dl) = STATS_SHAPES[i]
     nsk_env("NSK_HALO64_ALWAYS", "1")
-    if big:
-        if dtype != "bf16" or C % 64 or K % 64:
-            pytest.skip("the large-tile kernel takes bf16 layers with channel counts that are multiples of 64")
-        nsk_env("NSK_BIG_MIN_TILES", "1")
-    print(f"stats case {STATS_SHAPES[i]} big={big} layout={layout}", flush=True)
+    if largest_tile:
+        nsk_env("NSK_IGEMM_TILE", "1")
+    print(f"stats case {STATS_SHAPES[i]} largest_tile={largest_tile} layout={layout}", flush=True)
     x = on_grid(gen.normal(900 + i, 0, (N, C, H, W)), dtype)
     w = on_grid(gen.he_normal(900 + i, 1, (K, C, R, S)), dtype)
     g = (1.0 + 0.3 * gen.normal(900 + i, 3, (K,))).astype(np.float32)
