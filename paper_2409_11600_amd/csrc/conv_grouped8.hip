@@ -25,21 +25,6 @@ typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 constexpr int G8_ENTRIES = 480;        // pixels of a strip with halo: 60 KB of LDS, two blocks per CU
 constexpr int G8_WG_ENTRIES = 600;     // backward-weight: with the strip of dy 75 KB, two blocks per CU
 
-struct Div {       // n / d for 0 <= n < 2^31 as (n * mul) >> sh
-    unsigned mul;
-    int sh;
-};
-Div make_div(int d)
-{
-    int s = 0;
-    while ((1LL << s) < d) ++s;
-    Div r;
-    r.mul = (unsigned)(((1ULL << (31 + s)) + (unsigned)d - 1) / (unsigned)d);
-    r.sh = 31 + s;
-    return r;
-}
-__device__ inline int divide(int n, const Div &d) { return (int)(((unsigned long long)(unsigned)n * d.mul) >> d.sh); }
-
 struct G8Args {
     const void *src, *wpk;
     void *out;

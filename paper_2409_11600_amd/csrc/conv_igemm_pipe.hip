@@ -49,15 +49,6 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int PK_BYTES = 128;   // bytes of reduction index per k-tile row
 
-// Until at most N of the wavefront's direct loads are on their way and all its LDS reads have arrived (a barrier behind it
-// then also says that nobody reads the stage before any more).
-template <int N> __device__ inline void wait_vm()
-{
-    static_assert(N >= 0 && N < 64, "six-bit counter");
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
-}
-
 constexpr int kMaxProblems = 4;
 template <int NP> struct PipeProblems {   // NP = 1 or kMaxProblems: a plain launch carries 400 bytes of arguments, not 1.7 KB
     IgemmArgs a[NP];
@@ -132,7 +123,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
 
     // This lane's rows of the activation tile: byte offset of the row's base pixel and one validity bit per tap.
     const int lr = lane >> 3;
-        const int piece = (lane & 7) ^ ((wave & 1) * 4 + (lr >> 1));
+    const int piece = (lane & 7) ^ ((wave & 1) * 4 + (lr >> 1));
     unsigned a_base[RA];
     unsigned long long a_mask[RA];
     {
@@ -200,7 +191,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
     // The filter rows are the MFMA "A" operand and the pixels the "B" operand, so a lane ends up with 4 consecutive
     // channels of one pixel per accumulator quad: acc[mi][ni][4g+j] is channel 32*ni + 8*g + 4*(lane/32) + j of pixel
     // 32*mi + lane%32 of the wavefront's sub-tile.
-    const int frow = lane & 31, fk = lane >> 5,  fsw = (frow >> 1) & 7;
+    const int frow = lane & 31, fk = lane >> 5, fsw = (frow >> 1) & 7;
     T *__restrict__ out = (T *)a.out;
     const int wcol0 = n0 + wn * (FN * 32), wrow = wm * (FM * 32);
     f32x16 acc[FM][FN];

@@ -32,31 +32,6 @@ typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
 constexpr int kLong = 16;   // see Sums
 
-// Until at most N of the wavefront's direct loads are on their way and all its LDS reads have arrived (a barrier behind it
-// then also says that nobody reads the stage before any more).
-template <int N> __device__ inline void wait_vm()
-{
-    static_assert(N >= 0 && N < 64, "six-bit counter");
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
-}
-
-// n / d for 0 <= n < 2^31 as (n * mul) >> sh with mul = ceil(2^(31+s) / d), s = ceil(log2 d), sh = 31 + s
-struct Div {
-    unsigned mul;
-    int sh;
-};
-Div make_div(int d)
-{
-    int s = 0;
-    while ((1LL << s) < d) ++s;
-    Div r;
-    r.mul = (unsigned)(((1ULL << (31 + s)) + (unsigned)d - 1) / (unsigned)d);
-    r.sh = 31 + s;
-    return r;
-}
-__device__ inline int divide(int n, const Div &d) { return (int)(((unsigned long long)(unsigned)n * d.mul) >> d.sh); }
-
 struct PipeArgs {
     WgradArgs g;
     Div by_pq, by_q;

@@ -45,6 +45,31 @@ __device__ inline void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Until at most N of the wavefront's direct loads (memory to LDS) are on their way and all its LDS reads have arrived: a barrier
+// behind it then also says that nobody reads the stage before any more.
+template <int N> __device__ inline void wait_vm()
+{
+    static_assert(N >= 0 && N < 64, "six-bit counter");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
+}
+
+// n / d for 0 <= n < 2^31 as (n * mul) >> sh with mul = ceil(2^(31+s) / d), s = ceil(log2 d), sh = 31 + s
+struct Div {
+    unsigned mul;
+    int sh;
+};
+inline Div make_div(int d)
+{
+    int s = 0;
+    while ((1LL << s) < d) ++s;
+    Div r;
+    r.mul = (unsigned)(((1ULL << (31 + s)) + (unsigned)d - 1) / (unsigned)d);
+    r.sh = 31 + s;
+    return r;
+}
+__device__ inline int divide(int n, const Div &d) { return (int)(((unsigned long long)(unsigned)n * d.mul) >> d.sh); }
+
 // Test and A/B switches: environment variables NSK_*, read ONCE (first use, or nsk_test_hooks_reload()) and never on
 // the launch path.  Each one only narrows or widens the choice among kernels that all compute the same result.
 struct TestHooks {
