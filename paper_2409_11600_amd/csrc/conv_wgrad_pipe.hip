@@ -16,12 +16,14 @@
 // per clock) or two rows x 128 bytes (fp32) that one fragment read serves at once would fall into the same banks, so a
 // row's 64-byte (fp32: 128-byte) pieces are exchanged with its number; the exchange is made in the source address.
 //
-// Sums: the products of ST k-tiles go alternately into two sets of accumulators, which are then added to a third, so that the
-// error does not grow with the length of a split: fp32 chains are at most 64 pixels long (128 in splits of more than kLong
-// k-tiles, where the adds would take 3%), bf16 ones 8 products of 16 pixels.  Error against 64 bits (2-norm, random data;
-// one accumulator and chains of 16-18 k-tiles / this / the kernels before): fp32 16->16 at 32x32 N=8 2.15e-7, 1.61e-7,
-// 1.61e-7; 744->744 1x1 stride 2 at 24x24 N=3 3.73e-7, 1.48e-7, 1.63e-7; 128->128 at 28x28 N=64 4.06e-7, 2.30e-7,
-// 4.99e-7; bf16 416->416 1x1 at 25x25 N=3 1.14e-7, 0.77e-7, 0.81e-7.  Time within 3% of one accumulator (512->512 3x3 at 7x7 N=64 29.7 -> 30.5 us).
+// Sums: the products of ST k-tiles are added up in one or two sets of accumulators (alternately) and those then added to another,
+// so that the error does not grow with the length of a split.  Short splits, up to kLong k-tiles, have two sets: chains of
+// 64 pixels in fp32, 8 products of 16 pixels in bf16.  Long ones, whose error was larger before, have twice as long chains:
+// eight k-tiles in two sets (fp32), one set (bf16), where the adds would take 3%.  Error against 64 bits (2-norm,
+// random data; one set, 16-18 k-tiles / this / the kernels before): fp32 16->16 at 32x32 N=8 2.15e-7, 1.61e-7, 1.61e-7;
+// 744->744 1x1 stride 2 at 24x24 N=3 3.73e-7, 1.48e-7, 1.63e-7; 128->128 at 28x28 N=64 4.06e-7, 2.30e-7, 4.99e-7; bf16
+// 416->416 1x1 at 25x25 N=3 1.14e-7, 0.77e-7, 0.81e-7; 512->512 at 7x7 N=64 1.75e-7, 1.07e-7, 1.52e-7.  Time
+// up to 3% more in fp32, 1-3% less in bf16.
 #include "nsk_internal.h"
 
 namespace nsk {
@@ -47,7 +49,7 @@ template <int ES, int RB> __device__ constexpr int piece_swap(int r)
     else return ((r >> 1) & 1) << 2;
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int KT, int ST>
+template <typename T, int BM, int BN, int WM, int WN, int KT, int ST, int CH>
 __global__ __launch_bounds__(64 * WM * WN) void wgrad_pipe_kernel(const PipeArgs w)
 {
     const WgradArgs &a = w.g;
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(64 * WM * WN) void wgrad_pipe_kernel(const PipeArgs
         lx += KT;
     };
 
-    f32x16 acc[2][FM][FN], sum[FM][FN];
+    f32x16 acc[CH][FM][FN], sum[FM][FN];   // CH chains of products, see Sums
 #pragma unroll
     for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
@@ -176,7 +178,7 @@ __global__ __launch_bounds__(64 * WM * WN) void wgrad_pipe_kernel(const PipeArgs
                 for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
                     for (int ni = 0; ni < FN; ++ni)
-                        acc[ks & 1][mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[mi], bx[ni], acc[ks & 1][mi][ni], 0, 0, 0);
+                        acc[ks % CH][mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[mi], bx[ni], acc[ks % CH][mi][ni], 0, 0, 0);
             }
         } else {
 #pragma unroll
@@ -190,13 +192,13 @@ __global__ __launch_bounds__(64 * WM * WN) void wgrad_pipe_kernel(const PipeArgs
                 for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
                     for (int ni = 0; ni < FN; ++ni)
-                        acc[t & 1][mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi], bx[ni], acc[t & 1][mi][ni], 0, 0, 0);
+                        acc[t % CH][mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[mi], bx[ni], acc[t % CH][mi][ni], 0, 0, 0);
             }
         }
     };
     auto start_chains = [&]() {
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
+        for (int c = 0; c < CH; ++c)
 #pragma unroll
             for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
@@ -210,7 +212,7 @@ __global__ __launch_bounds__(64 * WM * WN) void wgrad_pipe_kernel(const PipeArgs
 #pragma unroll
             for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) sum[mi][ni][v] += acc[0][mi][ni][v] + acc[1][mi][ni][v];
+                for (int v = 0; v < 16; ++v) sum[mi][ni][v] += CH == 2 ? acc[0][mi][ni][v] + acc[CH - 1][mi][ni][v] : acc[0][mi][ni][v];
     };
 
     static_for<0, ST - 1>([&](auto S) { request(S); });   // (k-tiles past the end are requested out of range: zeros)
@@ -339,7 +341,7 @@ int choose(int dtype, int L, int K, int NT, int groups, int *splits, int *rows)
     return best;
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int KT, int ST> int launch(const WgradArgs &a, hipStream_t stream)
+template <typename T, int BM, int BN, int WM, int WN, int KT, int ST, int CH> int launch(const WgradArgs &a, hipStream_t stream)
 {
     PipeArgs w{};
     w.g = a;
@@ -349,7 +351,7 @@ template <typename T, int BM, int BN, int WM, int WN, int KT, int ST> int launch
     w.tiles_k = ceil_div(a.K, BM);
     w.x_bytes = (unsigned)((long long)a.Nimg * a.H * a.W * a.ldx * (int)sizeof(T));
     w.dy_bytes = (unsigned)((long long)a.L * a.ldy * (int)sizeof(T));
-    hipLaunchKernelGGL((wgrad_pipe_kernel<T, BM, BN, WM, WN, KT, ST>), dim3((unsigned)(w.tiles_n * w.tiles_k * a.splits), 1, a.groups),
+    hipLaunchKernelGGL((wgrad_pipe_kernel<T, BM, BN, WM, WN, KT, ST, CH>), dim3((unsigned)(w.tiles_n * w.tiles_k * a.splits), 1, a.groups),
                        dim3(64 * WM * WN), 0, stream, w);
     return check_launch();
 }
@@ -377,11 +379,12 @@ int launch_wgrad_pipe(int dtype, const WgradArgs &a, hipStream_t stream)
     int splits, rows;
     const int i = choose(dtype, a.L, a.K, a.ntaps * a.C, a.groups, &splits, &rows);
     if (splits != a.splits || rows != a.rows_per_split) return NSK_ERR_BAD_DESC;
-    if (dtype != NSK_BF16) return launch<float, 64, 64, 2, 2, 32, 4>(a, stream);
+    if (dtype != NSK_BF16) return launch<float, 64, 64, 2, 2, 32, 4, 2>(a, stream);
+    const bool is_long = rows > kLong * 64;
     switch (i) {
-    case 0: return launch<bf16_t, 128, 128, 2, 4, 64, 4>(a, stream);
-    case 1: return launch<bf16_t, 64, 128, 2, 4, 64, 4>(a, stream);
-    default: return launch<bf16_t, 64, 64, 2, 2, 64, 3>(a, stream);
+    case 0: return is_long ? launch<bf16_t, 128, 128, 2, 4, 64, 4, 1>(a, stream) : launch<bf16_t, 128, 128, 2, 4, 64, 4, 2>(a, stream);
+    case 1: return is_long ? launch<bf16_t, 64, 128, 2, 4, 64, 4, 1>(a, stream) : launch<bf16_t, 64, 128, 2, 4, 64, 4, 2>(a, stream);
+    default: return is_long ? launch<bf16_t, 64, 64, 2, 2, 64, 3, 1>(a, stream) : launch<bf16_t, 64, 64, 2, 2, 64, 3, 2>(a, stream);
     }
 }
 

@@ -69,10 +69,10 @@ def test_every_tile_grouped(dtype, tile, nsk_env):
 
 # A float sum of n terms of either sign, added one after the other, is off by about 2.5e-8 * sqrt(n / 2) of its size (2.5e-8: the
 # rms of one rounding).  fp32: chains of at most 128 pixels 2.0e-7, with the few sums of chains and splits behind them 2.2e-7;
-# bf16: 8 products of 16 pixels, four roundings in each, 1.0e-7.
+# bf16: 8 products of 16 pixels, four roundings in each, 1.0e-7, 16 products in splits of more than 16 k-tiles (the last), 1.4e-7.
 @pytest.mark.parametrize("dtype,bar,N,C,H,K,R,stride", [("f32", 1.9e-7, 8, 16, 32, 16, 3, 1),       # 64 splits of 128 pixels: chains of 64, 1.4e-7
                                                         ("f32", 2.3e-7, 3, 744, 24, 744, 1, 2), ("f32", 2.3e-7, 7, 48, 17, 808, 3, 1),
-                                                        ("bf16", 1.05e-7, 3, 416, 25, 416, 1, 1), ("bf16", 1.05e-7, 4, 48, 65, 240, 3, 1)])
+                                                        ("bf16", 1.05e-7, 3, 416, 25, 416, 1, 1), ("bf16", 1.5e-7, 4, 48, 65, 240, 3, 1)])
 def test_error_does_not_grow_with_the_split(dtype, bar, N, C, H, K, R, stride):
     g = torch.Generator(device="cuda").manual_seed(11)
     P, pad = (H - 1) // stride + 1, R // 2
