@@ -1,23 +1,37 @@
 // All time steps of the GRU in one launch per direction, for few samples and hidden sizes up to 256.
 //
 // What bounds the step-by-step form: 2T dependent launches of 5.5-7 us each (a launch, an L2 round trip for the operands, a
-// store) and as many calls from the host.  But a sample's state depends on that sample alone: here a block owns one sample
-// and runs all T steps by itself, so nothing is exchanged between blocks and nothing is launched in between.  What has to
-// be at hand in every step is the whole recurrent weight (3*H*H values: 786 KB in fp32 at H = 256, more than the 512 KB of
-// registers and 160 KB of LDS of a CU): a thread keeps most of its part in registers for all T steps, some of it lies in
-// LDS, and in fp32 above H = 192 the rest is read from L2 again in every step, while the resident part is multiplied.
+// store) and as many calls from the host.  But a sample's state depends on that sample alone: here G blocks own one sample
+// and run all T steps by themselves.  What has to be at hand in every step is the whole recurrent weight (3*H*H values: 786 KB
+// in fp32 at H = 256, more than the 512 KB of registers and 160 KB of LDS of a CU).
 //
-// Work inside a block of 512 threads: eight neighbouring lanes q share a hidden unit's dot products (lane q takes the
-// columns 4*(q + 8*m) ..), 64 groups of lanes hold the units slot, slot + 64, ...; the lane sums run over the eight lanes
-// in a fixed order, then lane q goes on with the gates of unit slot + 64*q.  The state (forward) or the gate gradients
-// (backward) go through LDS, double-buffered: one barrier per step.
+// G = 1: a block has the sample to itself and nothing is exchanged.  A thread keeps most of its part of the weight in registers
+// for all T steps, some of it lies in LDS, and in fp32 above H = 192 the rest is read from L2 again in every step, while the
+// resident part is multiplied.
+//
+// G = 2, 4 or 8 (few samples): each block owns H/G of the hidden units, so its part of the weight stays on the CU and a step's
+// products take 1/G of the time; what it pays is an exchange per step.  The exchange goes through the output itself (h forward,
+// dgh backward): a fill launch puts a NaN that no step stores in front of it, a block's gate lanes store their units with
+// agent-scope atomics, and a wavefront of its own per vector polls the others' values until none of them is that NaN, so value
+// and flag arrive together (a store and the load that sees it take 0.5 us on one XCD, 0.6 us across; the members of a group
+// are blocks b, b + 8, ..: one XCD when blocks go round the eight).  The pollers are wavefronts of their own because a
+// wavefront's loads return in order: behind the elementwise operands, which come from HBM, every poll would wait for those.
+// Waiting ends: members of a group are dispatched one after the other and hold no more CUs than the XCD has (split_of), other
+// groups of the launch wait for nobody here, and a poller that has seen 2^24 polls fail in all goes on with NaN.
+//
+// Work inside a block of 512 (32 units: 256) multiplying threads: eight neighbouring lanes q share a hidden unit's dot products
+// (lane q takes the columns 4*(q + 8*m) ..), 64 (32) groups of lanes hold the units slot, slot + 64, ...; the lane sums run over
+// the eight lanes in a fixed order, then lane q goes on with the gates of unit slot + 64*q.  The state (forward) or the gate
+// gradients (backward) go through LDS, double-buffered: one barrier per step.
 //
 // Measured, us for T = 200 steps (step launches -> this kernel, forward / backward): fp32, 50 samples, H = 256: 973 / 1255 ->
-// 705 / 619 (and 2.4 ms of host calls gone); H = 192: 859 / 1142 -> 363 / 293; H = 64: 627 / 688 -> 147 / 134; bf16, H = 256:
-// 1065 / 1218 -> 395 / 322; fp32, 200 samples, H = 256: 2843 / 3435 -> 805 / 705.  A training step of the fp32 model with 50
-// samples, H = 256, T = 200: 5.4 -> 1.8 ms.  At H = 256 in fp32 a step is bound by the 5/12 of the weight that a block
-// reads from L2 (328 KB per step); below, by the LDS reads, the lane sums and the chain of the gates.
+// 287 / 333 (one block per sample, as before the split: 705 / 619); H = 192: 859 / 1142 -> 274 / 274; H = 64: 627 / 688 -> 106 / 105;
+// bf16, H = 256: 1065 / 1218 -> 228 / 276; fp32, 200 samples, H = 256: 2843 / 3435 -> 609 / 650.  A split step of 1.5 us is 0.65 us
+// of exchange, 0.35 us of products and the chain of sums and gates; without a split it is that chain (0.5 us), the products
+// and, at H = 256, the part of the weight that comes from L2.
 #include <math.h>
+
+#include <algorithm>
 
 #include "nsk_internal.h"
 
@@ -26,7 +40,38 @@ namespace {
 
 bool unaligned16(const void *p) { return ((uintptr_t)p & 15) != 0; }
 
-__device__ inline float sigmoidf(float a) { return 1.f / (1.f + expf(-a)); }
+// Gate functions, written for a chain of few dependent instructions (a step is one chain; the library's take 1.5 times as many):
+// exp as the hardware's 2^t with the rounding of t = x*log2(e) put back as a factor, a reciprocal of 1 + e with one Newton step, tanh as
+// 1 - 2/(e^2x + 1) and, below 0.75 where that cancels, as an odd polynomial (least squares on Chebyshev nodes, relative error 7e-9).  Arguments
+// of exp are held at +-88, where it stays finite; NaN goes through.  Mean errors of r, z, tanh and h against 64 bits over five sizes:
+// 3.1, 3.1, 4.3, 7.4e-8 (with the library's functions 4.2, 4.2, 4.3, 8.1e-8).
+__device__ inline float exp_to88(float x)
+{
+    x = x > 88.f ? 88.f : x < -88.f ? -88.f : x;
+    const float t = x * 1.44269502f;
+    const float lo = fmaf(x, 1.44269502f, -t) + x * 1.92596303e-8f;
+    const float e = __builtin_amdgcn_exp2f(t);
+    return fmaf(e, lo * 0.693147182f, e);
+}
+// 1 / (1 + e), the rounding of 1 + e put back in the Newton step
+__device__ inline float reciprocal1p(float e)
+{
+    const float d = 1.f + e, r = __builtin_amdgcn_rcpf(d);
+    return fmaf(fmaf(d - 1.f - e, r, fmaf(-d, r, 1.f)), r, r);
+}
+__device__ inline float gate_sigmoid(float a) { return reciprocal1p(exp_to88(-a)); }
+__device__ inline float gate_tanh(float a)
+{
+    const float x = fabsf(a), z = x * x;
+    const float big = fmaf(-2.f, reciprocal1p(exp_to88(2.f * x)), 1.f);
+    float p = fmaf(0.00191453542f, z, -0.007940921f);
+    p = fmaf(p, z, 0.0216188431f);
+    p = fmaf(p, z, -0.0539365672f);
+    p = fmaf(p, z, 0.13333185f);
+    p = fmaf(p, z, -0.333333313f);
+    const float y = x < 0.75f ? fmaf(x * z, p, x) : big;
+    return copysignf(y, a);
+}
 
 typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -52,38 +97,117 @@ template <> struct SeqT<bf16_t> {
     static __device__ inline V fetch(__amdgpu_buffer_rsrc_t r, unsigned at) { return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, (int)at, 0, 0)); }
 };
 
-constexpr int GQ_THREADS = 512;
+constexpr unsigned kUnset = 0xffffffffu;      // a NaN in fp32 and, twice, in bf16; NaNs that a step stores are 0x7fc0(0000)
+constexpr int kPolls = 1 << 24;               // failed polls of a wavefront before it gives up: several seconds
+// Polls cross the chip (650 ns there and back, whoever stores) and slow the stores that they wait for: a poll that comes too early
+// costs a second one, four on their way at a time cost 487 / 690 us where one alone costs 371 / 466.  So a poller sleeps before
+// its first poll of a step, in quarters of 64 clocks: 16 more after a first poll that failed, one less after every step
+// (302 / 344 us; 6 and 1 whole units 300 / 374, eighths 40 and 1 307 / 337 but unsteady).
+constexpr int kSleepUp = 16, kSleepMost = 256;
+
+// sum over the eight lanes of a group, in every lane: neighbours 1 and 2 away, then the mirrored lane of the other four
+__device__ inline float sum8(float v)
+{
+    auto other = [](float x, auto ctl) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctl)::value, 0xf, 0xf, true));
+    };
+    v += other(v, std::integral_constant<int, 0xb1>{});     // quad_perm 1,0,3,2
+    v += other(v, std::integral_constant<int, 0x4e>{});     // quad_perm 2,3,0,1
+    v += other(v, std::integral_constant<int, 0x141>{});    // row_half_mirror
+    return v;
+}
+
+// values that blocks exchange: stored and loaded at agent scope
+__device__ inline void publish(float *p, float v)
+{
+    const unsigned b = v != v ? 0x7fc00000u : __builtin_bit_cast(unsigned, v);
+    __hip_atomic_store((unsigned *)p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void publish(bf16_t *p, bf16_t v)
+{
+    const unsigned short b = (float)v != (float)v ? (unsigned short)0x7fc0 : __builtin_bit_cast(unsigned short, v);
+    __hip_atomic_store((unsigned short *)p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+typedef unsigned long long u64;
+__device__ inline u64 seen(const void *p) { return __hip_atomic_load((const u64 *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T> __device__ inline bool unset(u64 v)
+{
+    if (sizeof(T) == 4) return (unsigned)v == kUnset || (unsigned)(v >> 32) == kUnset;
+    bool any = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) any |= ((v >> (16 * e)) & 0xffff) == 0xffff;
+    return any;
+}
 
 struct GruSeqArgs {
     const void *gi, *w, *saved_in, *dh_top;      // w: W_hh [3H][H] forward, its transpose [H][3H] backward
     const float *b_ih, *b_hh;
     void *h, *saved, *dgi, *dgh;
     int T, N, H;
+    int G, HU;       // blocks per sample and units per block (1 and H where a block has the sample to itself)
 };
 
-// IU = units per thread, M = 4-column pieces per lane and gate; of the 3*IU (unit, gate) parts RS stay in registers, LS in LDS
-template <typename T, bool BWD, int IU, int M, int RS, int LS>
-__global__ __launch_bounds__(GQ_THREADS) void gru_seq_kernel(const GruSeqArgs a)
+// IU = units per thread, M = 4-column pieces per lane and gate; of the 3*IU (unit, gate) parts RS stay in registers, LS in LDS;
+// SLOTS = groups of eight lanes; SPLIT: a.G blocks per sample
+template <typename T, bool BWD, int IU, int M, int RS, int LS, int SLOTS, bool SPLIT>
+__global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void gru_seq_kernel(const GruSeqArgs a)
 {
     typedef SeqT<T> ST;
     typedef typename ST::V V;
-    constexpr int S = 3 * IU, SS = S - RS - LS, HP = 32 * M, NV = BWD ? 3 : 1;
+    constexpr int S = 3 * IU, SS = S - RS - LS, HP = 32 * M, NV = BWD ? 3 : 1, MT = 8 * SLOTS;
     static_assert(SS >= 0, "parts");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     T *const vec = (T *)smem;                                   // [2][NV][HP]: what the step multiplies
-    V *const lw = (V *)(smem + 2 * NV * HP * sizeof(T));        // [LS][M][512]
-    const int tid = threadIdx.x, q = tid & 7, slot = tid >> 3, n = blockIdx.x, H = a.H, N = a.N;
+    V *const lw = (V *)(smem + 2 * NV * HP * sizeof(T));        // [LS][M][MT]
+    const int tid = threadIdx.x, q = tid & 7, slot = tid >> 3, H = a.H, N = a.N;
+    // SPLIT: groups of G blocks that lie eight apart
+    const int n = SPLIT ? blockIdx.x / (8 * a.G) * 8 + blockIdx.x % 8 : blockIdx.x;
+    const int u0 = SPLIT ? blockIdx.x % (8 * a.G) / 8 * a.HU : 0, u1 = SPLIT ? min(u0 + a.HU, H) : H;
+    if (SPLIT && n >= N) return;
+    const long NH = (long)N * H;
 
-    // part p = (unit slot + 64*(p/3), gate p%3): byte offset of its row of this thread's columns; columns past H read zeros
+    if (SPLIT && tid >= MT) {
+        // a polling wavefront: vector g of the step, four columns per lane
+        const int g = (tid - MT) >> 6, c = 4 * (tid & 63);
+        const bool live = c < H;
+        int left = kPolls, wait = 0;
+        for (int step = 0; step < a.T; ++step) {
+            if (step > 0 && live) {
+                const int t = BWD ? a.T - step : step;          // the row that the step before this one has left
+                const T *src = BWD ? (const T *)a.dgh + (long)t * 3 * NH + (long)n * 3 * H + g * H + c : (const T *)a.h + (long)t * NH + (long)n * H + c;
+                constexpr int W = sizeof(T) / 2;
+                u64 v[W];
+                for (int i = 0; i < wait / 4; ++i) __builtin_amdgcn_s_sleep(1);
+                bool un, first = true;
+                do {
+                    un = false;
+#pragma unroll
+                    for (int e = 0; e < W; ++e) v[e] = seen((const char *)src + 8 * e);
+#pragma unroll
+                    for (int e = 0; e < W; ++e) un |= unset<T>(v[e]);
+                    un = __any(un) && --left > 0;
+                    if (un && first) wait = min(wait + kSleepUp, kSleepMost);
+                    first = false;
+                } while (un);
+                if (wait > 0) wait -= 1;
+#pragma unroll
+                for (int e = 0; e < W; ++e) *(u64 *)((char *)(vec + (step & 1) * NV * HP + g * HP + c) + 8 * e) = v[e];
+            }
+            lds_barrier();
+        }
+        return;
+    }
+
+    // part p = (unit slot + SLOTS*(p/3), gate p%3): byte offset of its row of this thread's columns; columns past H read zeros
     const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.w, 0, (unsigned)(3 * H * H * (int)sizeof(T)), 0x00020000);
     auto row = [&](int p) -> unsigned {
-        const int u = min(slot + 64 * (p / 3), H - 1), g = p % 3;
+        const int u = min(u0 + slot + SLOTS * (p / 3), H - 1), g = p % 3;
         return (unsigned)((BWD ? u * 3 * H + g * H : (g * H + u) * H) + 4 * q) * (unsigned)sizeof(T);
     };
     auto column = [&](int m) { return 4 * (q + 8 * m); };
     auto load = [&](unsigned r, int m) -> V {
         const unsigned at = r + (unsigned)(32 * m * (int)sizeof(T));
-        if (32 * m + 32 <= 64 * (IU - 1)) return ST::fetch(w_rsrc, at);     // (H > 64*(IU - 1))
+        if (32 * m + 32 <= 32 * (M - 2)) return ST::fetch(w_rsrc, at);     // (H > 32*(M - 2))
         return ST::fetch(w_rsrc, column(m) < H ? at : ~0u);
     };
     V wr[RS][M];
@@ -94,7 +218,7 @@ __global__ __launch_bounds__(GQ_THREADS) void gru_seq_kernel(const GruSeqArgs a)
 #pragma unroll
     for (int p = 0; p < LS; ++p)
 #pragma unroll
-        for (int m = 0; m < M; ++m) lw[(p * M + m) * GQ_THREADS + tid] = load(row(RS + p), m);
+        for (int m = 0; m < M; ++m) lw[(p * M + m) * MT + tid] = load(row(RS + p), m);
     // The parts that fit nowhere: one piece of each at a time.  The next piece is requested as soon as the one before has been
     // used, so it is on its way while the resident parts are multiplied; the first piece of a step comes during the gates
     // of the step before.
@@ -105,14 +229,16 @@ __global__ __launch_bounds__(GQ_THREADS) void gru_seq_kernel(const GruSeqArgs a)
         rs[p] = row(RS + LS + p);
         sw[p] = load(rs[p], 0);
     }
-    for (int i = tid; i < 2 * NV * HP; i += GQ_THREADS) vec[i] = (T)0.f;
-    __syncthreads();
+    // (SPLIT: the second half is the pollers', who fill its first H columns at the second step; all read those past H)
+    for (int i = tid; i < 2 * NV * HP; i += MT)
+        if (!SPLIT || i < NV * HP || i % HP >= H) vec[i] = !BWD && SPLIT && i < H ? ((const T *)a.h)[(long)n * H + i] : (T)0.f;
+    if constexpr (!SPLIT) __syncthreads();
 
     // this lane's unit in the elementwise part
-    const int u = slot + 64 * q;
-    const bool mine = q < IU && u < H;
+    const int u = u0 + slot + SLOTS * q;
+    const bool mine = q < IU && u < u1;
     const int ue = mine ? u : 0;
-    const long NH = (long)N * H, at = (long)n * H + ue;
+    const long at = (long)n * H + ue;
     float br = 0.f, bz = 0.f, bin = 0.f, bhn = 0.f, state = 0.f;   // state: h (forward), the direct part of dh (backward)
     if constexpr (!BWD) {
         br = a.b_ih[ue] + a.b_hh[ue];
@@ -120,29 +246,42 @@ __global__ __launch_bounds__(GQ_THREADS) void gru_seq_kernel(const GruSeqArgs a)
         bin = a.b_ih[2 * H + ue];
         bhn = a.b_hh[2 * H + ue];
         state = (float)((const T *)a.h)[at];
-        if (mine) vec[u] = (T)state;
-        __syncthreads();
+        if constexpr (!SPLIT) {
+            if (mine) vec[u] = (T)state;
+            __syncthreads();
+        }
     } else {
         state = (float)((const T *)a.dh_top)[at];
     }
 
-    for (int step = 0; step < a.T; ++step) {
-        const int t = BWD ? a.T - 1 - step : step, buf = step & 1;
-        // the elementwise operands are requested before the products
-        float e0, e1, e2, e3 = 0.f, e4 = 0.f;
-        if constexpr (!BWD) {
-            const T *gi = (const T *)a.gi + (long)t * 3 * NH + (long)n * 3 * H + ue;
-            e0 = (float)gi[0];
-            e1 = (float)gi[H];
-            e2 = (float)gi[2 * H];
-        } else {
-            const T *sv = (const T *)a.saved_in + (long)t * 4 * NH + (long)n * 4 * H + ue;
-            e0 = (float)sv[0];
-            e1 = (float)sv[H];
-            e2 = (float)sv[2 * H];
-            e3 = (float)sv[3 * H];
-            e4 = (float)((const T *)a.h)[(long)t * NH + at];
-        }
+    // The elementwise operands of a step, requested two steps ahead (they come from HBM, which takes longer than a step): 618 / 621 ->
+    // 566 / 594 us at H = 256 without a split, 119 / 113 -> 95 / 88 at H = 40; only one ahead at 192 units in fp32, which
+    // has no registers left for more (274 / 274, 288 / 288 with two).
+    constexpr int NE = BWD ? 5 : 3, D = sizeof(T) == 4 && M == 6 ? 1 : 2;
+    T e[D][NE];
+    auto operands = [&](T *to, int step) {
+        const int t = BWD ? a.T - 1 - step : step;
+        const T *p = BWD ? (const T *)a.saved_in + (long)t * 4 * NH + (long)n * 4 * H + ue : (const T *)a.gi + (long)t * 3 * NH + (long)n * 3 * H + ue;
+#pragma unroll
+        for (int i = 0; i < (BWD ? 4 : 3); ++i) to[i] = p[i * H];
+        if constexpr (BWD) to[NE - 1] = ((const T *)a.h)[(long)t * NH + at];
+    };
+#pragma unroll
+    for (int k = 0; k < D; ++k) operands(e[k], min(k, a.T - 1));
+
+    for (int first = 0; first < a.T; first += D)
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        const int step = first + k, t = BWD ? a.T - 1 - step : step, buf = step & 1;
+        if (k > 0 && step >= a.T) break;
+        T ec[NE];
+        auto take = [&] {
+#pragma unroll
+            for (int i = 0; i < NE; ++i) ec[i] = e[k][i];
+        };
+        if constexpr (D == 1 || SPLIT) take();     // (waits here for what was requested; without a split the products come first)
+        if constexpr (D == 1) operands(e[k], min(step + 1, a.T - 1));
+        if constexpr (SPLIT) lds_barrier();
         float acc[S];
 #pragma unroll
         for (int p = 0; p < S; ++p) acc[p] = 0.f;
@@ -161,8 +300,8 @@ __global__ __launch_bounds__(GQ_THREADS) void gru_seq_kernel(const GruSeqArgs a)
 #pragma unroll
                 for (int p = 0; p < RS; ++p) acc[p] = ST::mac(acc[p], wr[p][m], v[BWD ? p % 3 : 0]);
 #pragma unroll
-                for (int p = 0; p < LS; ++p) acc[RS + p] = ST::mac(acc[RS + p], lw[(p * M + m) * GQ_THREADS + tid], v[BWD ? (RS + p) % 3 : 0]);
-                __builtin_amdgcn_sched_barrier(0);     // (or every piece of the step is fetched ahead, into scratch)
+                for (int p = 0; p < LS; ++p) acc[RS + p] = ST::mac(acc[RS + p], lw[(p * M + m) * MT + tid], v[BWD ? (RS + p) % 3 : 0]);
+                if constexpr (SS > 0) __builtin_amdgcn_sched_barrier(0);     // (or every piece of the step is fetched ahead, into scratch)
             }
         }
         if constexpr (BWD) {
@@ -174,10 +313,8 @@ __global__ __launch_bounds__(GQ_THREADS) void gru_seq_kernel(const GruSeqArgs a)
         }
         constexpr int R = BWD ? IU : S;
 #pragma unroll
-        for (int p = 0; p < R; ++p) {
-#pragma unroll
-            for (int o = 1; o < 8; o <<= 1) acc[p] += __shfl_xor(acc[p], o, 64);
-        }
+        for (int p = 0; p < R; ++p) acc[p] = sum8(acc[p]);
+        if constexpr (!(D == 1 || SPLIT)) take();
         T *vn = vec + (buf ^ 1) * NV * HP;
         if constexpr (!BWD) {
             float gr = acc[0], gz = acc[1], gn = acc[2];
@@ -188,14 +325,19 @@ __global__ __launch_bounds__(GQ_THREADS) void gru_seq_kernel(const GruSeqArgs a)
                 gn = q == i ? acc[3 * i + 2] : gn;
             }
             if (mine) {
-                const float r = sigmoidf(e0 + gr + br);
-                const float z = sigmoidf(e1 + gz + bz);
+                const float r = gate_sigmoid((float)ec[0] + gr + br);
+                const float z = gate_sigmoid((float)ec[1] + gz + bz);
                 const float qq = gn + bhn;
-                const float c = tanhf(e2 + bin + r * qq);
+                const float c = gate_tanh((float)ec[2] + bin + r * qq);
                 const T hn = (T)((1.f - z) * c + z * state);
                 state = (float)hn;
-                vn[u] = hn;
-                ((T *)a.h)[(long)(t + 1) * NH + at] = hn;
+                T *const hp = (T *)a.h + (long)(t + 1) * NH + at;
+                if constexpr (SPLIT) {
+                    publish(hp, hn);
+                } else {
+                    vn[u] = hn;
+                    *hp = hn;
+                }
                 T *sv = (T *)a.saved + (long)t * 4 * NH + (long)n * 4 * H + u;
                 sv[0] = (T)r;
                 sv[H] = (T)z;
@@ -209,65 +351,146 @@ __global__ __launch_bounds__(GQ_THREADS) void gru_seq_kernel(const GruSeqArgs a)
             for (int i = 1; i < IU; ++i) dh = q == i ? acc[i] : dh;
             if (mine) {
                 dh += state;
-                const float r = e0, z = e1, c = e2, qq = e3;
+                const float r = (float)ec[0], z = (float)ec[1], c = (float)ec[2], qq = (float)ec[3];
                 const float da_n = dh * (1.f - z) * (1.f - c * c);
-                const float da_z = dh * (e4 - c) * z * (1.f - z);
+                const float da_z = dh * ((float)ec[4] - c) * z * (1.f - z);
                 const float da_r = da_n * qq * r * (1.f - r);
                 state = (float)(T)(dh * z);
                 const T tr = (T)da_r, tz = (T)da_z, tn = (T)(da_n * r);
-                vn[u] = tr;
-                vn[HP + u] = tz;
-                vn[2 * HP + u] = tn;
                 const long g0 = (long)t * 3 * NH + (long)n * 3 * H + u;
                 T *dgi = (T *)a.dgi + g0, *dgh = (T *)a.dgh + g0;
+                if constexpr (SPLIT) {
+                    publish(dgh, tr);
+                    publish(dgh + H, tz);
+                    publish(dgh + 2 * H, tn);
+                } else {
+                    vn[u] = tr;
+                    vn[HP + u] = tz;
+                    vn[2 * HP + u] = tn;
+                    dgh[0] = tr;
+                    dgh[H] = tz;
+                    dgh[2 * H] = tn;
+                }
                 dgi[0] = tr;
                 dgi[H] = tz;
                 dgi[2 * H] = (T)da_n;
-                dgh[0] = tr;
-                dgh[H] = tz;
-                dgh[2 * H] = tn;
             }
         }
-        lds_barrier();
+        if constexpr (D > 1) operands(e[k], min(step + D, a.T - 1));
+        if constexpr (!SPLIT) lds_barrier();
     }
 }
 
-template <typename T, bool BWD, int IU, int M, int RS, int LS> int launch(const GruSeqArgs &a, hipStream_t stream)
+__global__ void unset_kernel(u64 *p, size_t n)
 {
-    const size_t smem = 2 * (BWD ? 3 : 1) * 32 * M * sizeof(T) + (size_t)LS * M * GQ_THREADS * 4 * sizeof(T);
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = ~0ull;
+}
+
+template <typename T, bool BWD, int IU, int M, int RS, int LS, int SLOTS, bool SPLIT> int launch(const GruSeqArgs &a, hipStream_t stream)
+{
+    constexpr int MT = 8 * SLOTS;
+    const size_t smem = 2 * (BWD ? 3 : 1) * 32 * M * sizeof(T) + (size_t)LS * M * MT * 4 * sizeof(T);
     static std::atomic<unsigned long long> done{0};
     if (smem > 64 * 1024) {
-        const int rc = allow_lds((const void *)gru_seq_kernel<T, BWD, IU, M, RS, LS>, smem, done);
+        const int rc = allow_lds((const void *)gru_seq_kernel<T, BWD, IU, M, RS, LS, SLOTS, SPLIT>, smem, done);
         if (rc != NSK_OK) return rc;
     }
-    hipLaunchKernelGGL((gru_seq_kernel<T, BWD, IU, M, RS, LS>), dim3(a.N), dim3(GQ_THREADS), smem, stream, a);
+    if (SPLIT) {
+        // rows that are exchanged: h[1..T), or all of dgh (H * sizeof(T) is a multiple of 8)
+        const size_t row = (size_t)a.N * a.H * sizeof(T);
+        u64 *p = (u64 *)(BWD ? (char *)a.dgh : (char *)a.h + row);
+        const size_t words = (BWD ? 3 * (size_t)a.T : (size_t)a.T) * row / 8;
+        hipLaunchKernelGGL(unset_kernel, dim3((unsigned)std::min<size_t>((words + 1023) / 1024, 2048)), dim3(256), 0, stream, p, words);
+        const int rc = check_launch();
+        if (rc != NSK_OK) return rc;
+    }
+    const int blocks = SPLIT ? ceil_div(a.N, 8) * 8 * a.G : a.N, threads = MT + (SPLIT ? 64 * (BWD ? 3 : 1) : 0);
+    hipLaunchKernelGGL((gru_seq_kernel<T, BWD, IU, M, RS, LS, SLOTS, SPLIT>), dim3(blocks), dim3(threads), smem, stream, a);
     return check_launch();
 }
 
-// The split of the parts is what the register file takes without spilling (512 threads: 256 registers each), the rest in LDS.
-// fp32 at H > 192, forward / backward in us: 5 parts in registers 705 / 619, 4 parts 775 / 691, 3 parts 893 / 784; 6 spill:
-// 807 / 862.
-template <bool BWD> int dispatch(int dtype, const GruSeqArgs &a, hipStream_t stream)
+// Whether a stream may use all `cus` compute units (a mask may take some away)
+bool whole_chip(hipStream_t stream, int cus)
+{
+    uint32_t mask[32] = {0};
+    if (hipExtStreamGetCUMask(stream, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    int n = 0;
+    for (uint32_t m : mask) n += __builtin_popcount(m);
+    return n >= cus;
+}
+
+// Blocks per sample.  The groups of an XCD must fit on its CUs side by side: 4 up to 64 samples, 2 up to 128.  Splitting pays where
+// one CU cannot hold the weight, above 192 units: us for T = 200, forward / backward, without -> with: fp32, 50 samples of 256
+// units 566 / 594 -> 287 / 333 (G = 4; G = 8, 32 samples: 313 / 293 but unsteady), 100 samples 566 / 594 -> 448 / 447 (G = 2);
+// bf16, 50 samples 316 / 285 -> 228 / 276, but G = 2 293 / 334; 192 units: fp32 274 / 274 -> 252 / 292, bf16 215 / 205 -> 217 / 263.
+int split_of(int dtype, int N, int H, hipStream_t stream)
+{
+    if (H % 8 != 0 || H <= 192) return 1;    // (polled in whole 8-byte words)
+    static std::atomic<int> cus[64];         // of each device, once known
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 1;
+    int c = cus[dev].load(std::memory_order_relaxed);
+    if (c == 0) {
+        if (hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 1;
+        cus[dev].store(c, std::memory_order_relaxed);
+    }
+    const int forced = hooks().gru_split;
+    int g = 4;
+    while (g > 1 && (ceil_div(N, 8) * g > c / 8 || (forced > 0 && g > forced))) g /= 2;
+    if (dtype == NSK_BF16 && g == 2) g = 1;
+    return g > 1 && whole_chip(stream, c) ? g : 1;
+}
+
+// Parts in registers and in LDS: what the register file takes without spilling (512 threads: 256 registers each, with the polling
+// wavefronts 168).  fp32 at H > 192 and G = 1, forward / backward in us: 5 parts in registers 705 / 619, 4 parts 775 / 691, 3 parts
+// 893 / 784; 6 spill: 807 / 862.  Thirty-two slots of twice the units (four wavefronts, one per SIMD, so that the gates' code
+// is issued once per SIMD) are faster where they need no more than half of the registers: bf16, 50 samples, 64 / 128 units
+// 143 / 111 and 158 / 169 -> 104 / 96 and 143 / 143, split at 256 units 248 / 298 -> 228 / 276; fp32, 64 units 114 / 105 -> 106 / 105,
+// but 128 units 173 / 192 -> 199 / 196.
+template <typename T, bool BWD, int M> int dispatch(GruSeqArgs &a, hipStream_t stream)
+{
+    constexpr bool F = sizeof(T) == 4;
+    a.HU = ceil_div(a.H, a.G);
+    if constexpr (M == 8) {
+        if constexpr (F) {
+            if (a.G == 4) return launch<T, BWD, 1, M, 3, 0, 64, true>(a, stream);
+            if (a.G == 2) return launch<T, BWD, 2, M, 4, 2, 64, true>(a, stream);
+        } else if (a.G == 4) {
+            return launch<T, BWD, 2, M, 6, 0, 32, true>(a, stream);
+        }
+        return launch<T, BWD, 4, M, F ? 5 : 9, F ? 2 : 3, 64, false>(a, stream);
+    } else if constexpr (M == 6) {
+        return launch<T, BWD, 3, M, F ? 7 : 9, F ? 2 : 0, 64, false>(a, stream);
+    } else if constexpr (M == 4 && F) {
+        return launch<T, BWD, 2, M, 6, 0, 64, false>(a, stream);
+    } else {
+        return launch<T, BWD, M, M, 3 * M, 0, 32, false>(a, stream);
+    }
+}
+template <bool BWD> int dispatch(int dtype, GruSeqArgs &a, hipStream_t stream)
 {
     const int m = (a.H + 63) / 64;
     if (dtype == NSK_BF16) {
         switch (m) {
-        case 1: return launch<bf16_t, BWD, 1, 2, 3, 0>(a, stream);
-        case 2: return launch<bf16_t, BWD, 2, 4, 6, 0>(a, stream);
-        case 3: return launch<bf16_t, BWD, 3, 6, 9, 0>(a, stream);
-        default: return launch<bf16_t, BWD, 4, 8, 9, 3>(a, stream);
+        case 1: return dispatch<bf16_t, BWD, 2>(a, stream);
+        case 2: return dispatch<bf16_t, BWD, 4>(a, stream);
+        case 3: return dispatch<bf16_t, BWD, 6>(a, stream);
+        default: return dispatch<bf16_t, BWD, 8>(a, stream);
         }
     }
     switch (m) {
-    case 1: return launch<float, BWD, 1, 2, 3, 0>(a, stream);
-    case 2: return launch<float, BWD, 2, 4, 6, 0>(a, stream);
-    case 3: return launch<float, BWD, 3, 6, 7, 2>(a, stream);
-    default: return launch<float, BWD, 4, 8, 5, 2>(a, stream);
+    case 1: return dispatch<float, BWD, 2>(a, stream);
+    case 2: return dispatch<float, BWD, 4>(a, stream);
+    case 3: return dispatch<float, BWD, 6>(a, stream);
+    default: return dispatch<float, BWD, 8>(a, stream);
     }
 }
 
-// One block holds a CU for the whole sequence.  Above 256 units a block would read nearly all of the weight again in every step,
-// which the step launches spread over the chip; N is at most the 256 that the step calls take, so one wave of blocks.
+// Above 256 units a block would read nearly all of the weight again in every step, which the step launches spread over the chip; N
+// is at most the 256 that the step calls take, so one wave of blocks.
 bool seq_kernel_takes(int H) { return H <= 256; }
 
 }  // namespace
@@ -289,6 +512,7 @@ int nsk_gru_seq_fwd(int dtype, int T, int N, int H, const void *gi, const void *
     if (!nsk_gru_step_supported(N, H)) return NSK_ERR_UNSUPPORTED;
     if (seq_kernel_takes(H)) {
         GruSeqArgs a{};
+        a.G = split_of(dtype, N, H, (hipStream_t)stream);
         a.gi = gi; a.w = w_hh; a.b_ih = b_ih; a.b_hh = b_hh; a.h = h; a.saved = saved;
         a.T = T; a.N = N; a.H = H;
         return dispatch<false>(dtype, a, (hipStream_t)stream);
@@ -314,6 +538,7 @@ int nsk_gru_seq_bwd(int dtype, int T, int N, int H, const void *saved, const voi
     if (!nsk_gru_step_supported(N, H)) return NSK_ERR_UNSUPPORTED;
     if (seq_kernel_takes(H)) {
         GruSeqArgs a{};
+        a.G = split_of(dtype, N, H, (hipStream_t)stream);
         a.saved_in = saved; a.h = (void *)h; a.dh_top = dh_top; a.w = w_hh_t; a.dgi = dgi; a.dgh = dgh;
         a.T = T; a.N = N; a.H = H;
         return dispatch<true>(dtype, a, (hipStream_t)stream);

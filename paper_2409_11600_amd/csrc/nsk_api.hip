@@ -448,6 +448,8 @@ void read_hooks()
     h.wh_min_rows = num("NSK_WH_MIN_ROWS");
     const long long tile = num("NSK_IGEMM_TILE");
     h.igemm_tile = tile > 0 ? (int)tile : 0;
+    const long long split = num("NSK_GRU_SPLIT");
+    h.gru_split = split > 0 ? (int)split : 0;
     g_hooks = h;
     g_hooks_read = true;
 }

@@ -77,7 +77,7 @@ struct TestHooks {
         no_tiny, no_depthwise, no_grouped8, no_pad, depthwise_no_rows, depthwise_no_cols, pool_general, reduce4,
         wh_no_split;
     long long pw_min_rows, wh_min_rows;   // -1: not set
-    int igemm_tile;                                         // 0: not set
+    int igemm_tile, gru_split;                              // 0: not set
 };
 const TestHooks &hooks();
 

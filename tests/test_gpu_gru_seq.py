@@ -78,3 +78,97 @@ def test_sequence_calls_refuse_what_the_step_calls_refuse():
         zb = lambda *s: torch.zeros(s, device="cuda:0", dtype=torch.bfloat16)
         B.gru_seq_fwd(zb(2, 1, 12), zb(12, 4), z(12), z(12), zb(3, 1, 4), zb(2, 1, 16))
     assert e.value.status == B.NSK_ERR_ALIGNMENT
+
+
+def _sequence(T, N, H, dtype, seed, bad=None):
+    """Operands of both calls and a function that makes the calls; `bad`: a value for one element of the initial state."""
+    dt = torch_dtype(dtype)
+    g = torch.Generator(device="cuda:0").manual_seed(seed)
+    r = lambda *s, k=1.0: (torch.randn(s, generator=g, device="cuda:0") * k).to(dt)
+    gi, w, h0, top = r(T, N, 3 * H), r(3 * H, H, k=H ** -0.5), r(N, H), r(N, H)
+    b = [0.3 * torch.randn(3 * H, generator=g, device="cuda:0") for _ in range(2)]
+    wt = w.t().contiguous()
+    if bad is not None:
+        h0[0, 1] = bad
+    h, saved = torch.empty((T + 1, N, H), dtype=dt, device="cuda:0"), torch.empty((T, N, 4 * H), dtype=dt, device="cuda:0")
+    h[0] = h0
+    dgi, dgh = (torch.empty((T, N, 3 * H), dtype=dt, device="cuda:0") for _ in range(2))
+    scratch = torch.empty((2, N, H), dtype=dt, device="cuda:0")
+
+    def run():
+        B.gru_seq_fwd(gi, w, *b, h, saved)
+        B.gru_seq_bwd(saved, h, top, wt, dgi, dgh, scratch)
+
+    return run, (h, saved, dgi, dgh)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T,N,H", [(1, 2, 256), (2, 1, 200), (7, 9, 256), (3, 64, 248), (3, 65, 208), (2, 128, 256), (2, 129, 256)])
+def test_blocks_that_share_a_sample(T, N, H, dtype, nsk_env):
+    """Several blocks per sample (as many as the sizes allow, and at most two) add in the order of one: the same bits.  Sizes:
+    a step without an exchange, part of a last block, all eight XCDs full at four and at two blocks, and one sample more."""
+    print(f"gru split T={T} N={N} H={H} {dtype}", flush=True)
+    run, out = _sequence(T, N, H, dtype, 8900 + H)
+    nsk_env("NSK_GRU_SPLIT", "1")
+    run()
+    want = [o.clone() for o in out]
+    for most in (None, "2"):
+        nsk_env("NSK_GRU_SPLIT", most)
+        for o in (out[0][1:], *out[1:]):
+            o.zero_()
+        run()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_blocks_that_share_a_sample_with_nan(dtype):
+    """A state that holds the very NaN that stands for "not there yet" (all ones), and infinity: the calls end, the sample's later
+    states hold NaN, the other samples' values are those without it."""
+    T, N, H = 3, 3, 256
+    run, clean = _sequence(T, N, H, dtype, 8901)
+    run()
+    ones = torch.tensor([-1], dtype=torch.int32 if dtype == "f32" else torch.int16).view(torch_dtype(dtype))[0]
+    for bad in (ones, float("inf")):
+        run, out = _sequence(T, N, H, dtype, 8901, bad)
+        run()
+        torch.cuda.synchronize()
+        assert torch.isnan(out[0][T, 0]).any()
+        assert all(torch.equal(a[:, 1:], b[:, 1:]) for a, b in zip(out, clean))
+
+
+def test_blocks_that_share_a_sample_in_a_graph():
+    """Captured: every replay gives what the eager calls give."""
+    run, out = _sequence(5, 50, 256, "f32", 8902)
+    run()
+    torch.cuda.synchronize()
+    want = [o.clone() for o in out]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        run()
+    for _ in range(3):
+        for o in (out[0][1:], *out[1:]):
+            o.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want))
+
+
+@pytest.mark.parametrize("H", [64, 256])
+def test_gates_at_the_ends_of_their_range(H):
+    """Pre-activations from -inf to inf, where exp would overflow, around the seam of tanh's two forms, and NaN: r, z and n against
+    torch in 64 bits (the gates' own arithmetic, no products: a zero state).  4 ulp of fp32 next to values of at most one."""
+    a = torch.tensor([0.0, -0.0, 1e-30, 1e-4, 0.7499999, 0.75, 0.7500001, 1.0, 8.9, 20.0, 43.9, 44.1, 87.0, 88.5, 104.0, 1e30, float("inf"), float("nan")])
+    a = torch.cat([a, -a]).double()
+    N = 4
+    gi = a[torch.arange(N * 3 * H) % a.numel()].view(1, N, 3 * H).float().cuda()
+    zero = lambda *s: torch.zeros(s, device="cuda:0")
+    h, saved = zero(2, N, H), zero(1, N, 4 * H)
+    B.gru_seq_fwd(gi, zero(3 * H, H), zero(3 * H), zero(3 * H), h, saved)
+    torch.cuda.synchronize()
+    x, got = gi[0].double().cpu(), saved[0].double().cpu()
+    for k, f in enumerate((torch.sigmoid, torch.sigmoid, torch.tanh)):
+        # n adds r times a product of zeros to its own argument: NaN where r is
+        want, have = f(x[:, k * H:(k + 1) * H] + (0 * torch.sigmoid(x[:, :H]) if k == 2 else 0)), got[:, k * H:(k + 1) * H]
+        assert torch.equal(torch.isnan(want), torch.isnan(have))
+        assert ((want - have).nan_to_num().abs() <= 2.0 ** -22 * want.nan_to_num().abs() + 2.0 ** -126).all()
