@@ -12,6 +12,7 @@ raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Tuple
 
@@ -206,6 +207,14 @@ def lib() -> ctypes.CDLL:
         L.nsk_pool_stats.argtypes = [vp, szp, szp, szp, szp]
         L.nsk_pool_destroy.restype = ci
         L.nsk_pool_destroy.argtypes = [vp]
+        reload = L.nsk_test_hooks_reload
+
+        def reload_and_forget():       # the switches decide what the cached queries below answer
+            reload()
+            for f in (_conv_call, _grouped_call, _bn_call, _pool_call, _linear_call):
+                f.cache_clear()
+
+        L.nsk_test_hooks_reload = reload_and_forget
         _lib = L
     return _lib
 
@@ -251,11 +260,13 @@ def _ptr(t: Optional[torch.Tensor]):
         return None
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("tensors handed to libnsk must be contiguous CUDA tensors")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The raw handle of the current device's current stream (torch.cuda.current_stream() builds an object for it: 2.8 us of
+    the 11 us that a small convolution call took; this takes 0.1)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _pair(v) -> Tuple[int, int]:
@@ -275,7 +286,7 @@ class Workspace:
             return None, 0
         if self.buf is None or self.buf.numel() < nbytes:
             self.buf = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
-        return ctypes.c_void_p(self.buf.data_ptr()), self.buf.numel()
+        return self.buf.data_ptr(), self.buf.numel()
 
 
 def conv_desc(act_dims, filt_dims, stride, pad, dilation, dtype_code, layout) -> nsk_conv_desc_t:
@@ -320,17 +331,54 @@ def conv2d_out_dims(desc: nsk_conv_desc_t) -> Tuple[int, int]:
     return P.value, Q.value
 
 
+# What a call asks the library about its sizes before it launches anything: the descriptor (by reference), the workspace and, forward,
+# the output extent or the rows of statistics.  The answers depend on the sizes alone, so they are kept for the sizes seen last
+# (a query and its ctypes objects take 0.3-0.9 us each; typed: 2.0 is not taken for the 2 of an earlier call).
+
+@functools.lru_cache(maxsize=1024, typed=True)
+def _conv_call(N, C, H, W, K, R, S, stride, pad, dilation, dtype, layout, which):
+    d = conv_desc((N, C, H, W), (K, R, S), stride, pad, dilation, dtype, layout)
+    ref = ctypes.byref(d)
+    P, Q = conv2d_out_dims(d) if which == NSK_PASS_FWD else (0, 0)
+    rows = int(lib().nsk_conv2d_stats_rows(ref)) if which == NSK_PASS_FWD else 0
+    return ref, P, Q, rows, lib().nsk_conv2d_workspace_bytes(ref, which)
+
+
+@functools.lru_cache(maxsize=1024, typed=True)
+def _grouped_call(N, C, H, W, K, R, S, stride, pad, dilation, dtype, layout, which, groups):
+    d = conv_desc((N, C, H, W), (K, R, S), stride, pad, dilation, dtype, layout)
+    ref = ctypes.byref(d)
+    P, Q = conv2d_out_dims(d) if which == NSK_PASS_FWD else (0, 0)
+    return ref, P, Q, lib().nsk_conv2d_grouped_workspace_bytes(ref, groups, which)
+
+
+@functools.lru_cache(maxsize=1024, typed=True)
+def _bn_call(N, C, H, W, dtype, layout, eps, momentum, relu, which):
+    ref = ctypes.byref(nsk_bn_desc_t(N, C, H, W, dtype, layout, eps, momentum, relu))
+    return ref, lib().nsk_bn_workspace_bytes(ref, which)
+
+
+@functools.lru_cache(maxsize=1024, typed=True)
+def _pool_call(N, C, H, W, window, stride, pad, dtype, layout):
+    return ctypes.byref(nsk_pool_desc_t(N, C, H, W, *window, *stride, *pad, dtype, layout))
+
+
+@functools.lru_cache(maxsize=1024, typed=True)
+def _linear_call(N, C, K, dtype, which):
+    ref = ctypes.byref(nsk_linear_desc_t(N, C, K, dtype))
+    return ref, lib().nsk_linear_workspace_bytes(ref, which)
+
+
 def conv2d_fwd(x, w, stride=1, pad=0, dilation=1, layout=NSK_NHWC, out=None, ws: Optional[Workspace] = None):
     N, C, H, W = _logical(x, layout)
     K, Cw, R, S = _filter_logical(w, layout)
     assert Cw == C and w.dtype == x.dtype
-    d = conv_desc((N, C, H, W), (K, R, S), stride, pad, dilation, _dtype_code(x), layout)
-    P, Q = conv2d_out_dims(d)
+    d, P, Q, _, need = _conv_call(N, C, H, W, K, R, S, _pair(stride), _pair(pad), _pair(dilation), _dtype_code(x), layout, NSK_PASS_FWD)
     if out is None:
         out = torch.empty(_act_shape(N, K, P, Q, layout), dtype=x.dtype, device=x.device)
     ws = ws or Workspace(x.device)
-    wp, wb = ws.get(lib().nsk_conv2d_workspace_bytes(ctypes.byref(d), NSK_PASS_FWD))
-    _check(lib().nsk_conv2d_fwd(ctypes.byref(d), _ptr(x), _ptr(w), _ptr(out), wp, wb, _stream()), "nsk_conv2d_fwd")
+    wp, wb = ws.get(need)
+    _check(lib().nsk_conv2d_fwd(d, _ptr(x), _ptr(w), _ptr(out), wp, wb, _stream()), "nsk_conv2d_fwd")
     return out
 
 
@@ -341,18 +389,16 @@ def conv2d_fwd_stats(x, w, stride=1, pad=0, dilation=1, layout=NSK_NHWC, out=Non
     N, C, H, W = _logical(x, layout)
     K, Cw, R, S = _filter_logical(w, layout)
     assert Cw == C and w.dtype == x.dtype
-    d = conv_desc((N, C, H, W), (K, R, S), stride, pad, dilation, _dtype_code(x), layout)
-    P, Q = conv2d_out_dims(d)
+    d, P, Q, rows, need = _conv_call(N, C, H, W, K, R, S, _pair(stride), _pair(pad), _pair(dilation), _dtype_code(x), layout, NSK_PASS_FWD)
     if out is None:
         out = torch.empty(_act_shape(N, K, P, Q, layout), dtype=x.dtype, device=x.device)
-    rows = int(lib().nsk_conv2d_stats_rows(ctypes.byref(d)))
     assert rows > 0
     if stats is None:
         stats = torch.empty((2, rows, K), dtype=torch.float32, device=x.device)
     assert stats.numel() == 2 * rows * K and stats.dtype == torch.float32
     ws = ws or Workspace(x.device)
-    wp, wb = ws.get(lib().nsk_conv2d_workspace_bytes(ctypes.byref(d), NSK_PASS_FWD))
-    _check(lib().nsk_conv2d_fwd_stats(ctypes.byref(d), _ptr(x), _ptr(w), _ptr(out), _ptr(stats), wp, wb, _stream()),
+    wp, wb = ws.get(need)
+    _check(lib().nsk_conv2d_fwd_stats(d, _ptr(x), _ptr(w), _ptr(out), _ptr(stats), wp, wb, _stream()),
            "nsk_conv2d_fwd_stats")
     return out, stats
 
@@ -363,13 +409,13 @@ def conv2d_dgrad(dy, w, x_logical, stride=1, pad=0, dilation=1, layout=NSK_NHWC,
     N, C, H, W = x_logical
     K, Cw, R, S = _filter_logical(w, layout)
     assert Cw == C and w.dtype == dy.dtype
-    d = conv_desc((N, C, H, W), (K, R, S), stride, pad, dilation, _dtype_code(dy), layout)
+    d, _, _, _, need = _conv_call(N, C, H, W, K, R, S, _pair(stride), _pair(pad), _pair(dilation), _dtype_code(dy), layout, NSK_PASS_DGRAD)
     if out is None:
         assert not accumulate
         out = torch.empty(_act_shape(N, C, H, W, layout), dtype=dy.dtype, device=dy.device)
     ws = ws or Workspace(dy.device)
-    wp, wb = ws.get(lib().nsk_conv2d_workspace_bytes(ctypes.byref(d), NSK_PASS_DGRAD))
-    _check(lib().nsk_conv2d_dgrad(ctypes.byref(d), _ptr(dy), _ptr(w), _ptr(out), int(bool(accumulate)), wp, wb,
+    wp, wb = ws.get(need)
+    _check(lib().nsk_conv2d_dgrad(d, _ptr(dy), _ptr(w), _ptr(out), int(bool(accumulate)), wp, wb,
                                   _stream()), "nsk_conv2d_dgrad")
     return out
 
@@ -380,15 +426,15 @@ def conv2d_wgrad(x, dy, filt_logical, stride=1, pad=0, dilation=1, layout=NSK_NH
     N, C, H, W = _logical(x, layout)
     K, Cw, R, S = filt_logical
     assert Cw == C and x.dtype == dy.dtype
-    d = conv_desc((N, C, H, W), (K, R, S), stride, pad, dilation, _dtype_code(x), layout)
+    d, _, _, _, need = _conv_call(N, C, H, W, K, R, S, _pair(stride), _pair(pad), _pair(dilation), _dtype_code(x), layout, NSK_PASS_WGRAD)
     if out is None:
         assert not accumulate
         shape = (K, R, S, C) if layout == NSK_NHWC else (K, C, R, S)
         out = torch.empty(shape, dtype=torch.float32, device=x.device)
     assert out.dtype == torch.float32
     ws = ws or Workspace(x.device)
-    wp, wb = ws.get(lib().nsk_conv2d_workspace_bytes(ctypes.byref(d), NSK_PASS_WGRAD))
-    _check(lib().nsk_conv2d_wgrad(ctypes.byref(d), _ptr(x), _ptr(dy), _ptr(out), int(bool(accumulate)), wp, wb,
+    wp, wb = ws.get(need)
+    _check(lib().nsk_conv2d_wgrad(d, _ptr(x), _ptr(dy), _ptr(out), int(bool(accumulate)), wp, wb,
                                   _stream()), "nsk_conv2d_wgrad")
     return out
 
@@ -399,13 +445,13 @@ def conv2d_grouped_fwd(x, w, groups, stride=1, pad=0, dilation=1, layout=NSK_NHW
     N, C, H, W = _logical(x, layout)
     K, Cw, R, S = _filter_logical(w, layout)
     assert Cw * groups == C and w.dtype == x.dtype
-    d = conv_desc((N, C, H, W), (K, R, S), stride, pad, dilation, _dtype_code(x), layout)
-    P, Q = conv2d_out_dims(d)
+    d, P, Q, need = _grouped_call(N, C, H, W, K, R, S, _pair(stride), _pair(pad), _pair(dilation), _dtype_code(x), layout, NSK_PASS_FWD,
+                                  int(groups))
     if out is None:
         out = torch.empty(_act_shape(N, K, P, Q, layout), dtype=x.dtype, device=x.device)
     ws = ws or Workspace(x.device)
-    wp, wb = ws.get(lib().nsk_conv2d_grouped_workspace_bytes(ctypes.byref(d), int(groups), NSK_PASS_FWD))
-    _check(lib().nsk_conv2d_grouped_fwd(ctypes.byref(d), int(groups), _ptr(x), _ptr(w), _ptr(out), wp, wb, _stream()),
+    wp, wb = ws.get(need)
+    _check(lib().nsk_conv2d_grouped_fwd(d, int(groups), _ptr(x), _ptr(w), _ptr(out), wp, wb, _stream()),
            "nsk_conv2d_grouped_fwd")
     return out
 
@@ -416,13 +462,14 @@ def conv2d_grouped_dgrad(dy, w, x_logical, groups, stride=1, pad=0, dilation=1, 
     N, C, H, W = x_logical
     K, Cw, R, S = _filter_logical(w, layout)
     assert Cw * groups == C and w.dtype == dy.dtype
-    d = conv_desc((N, C, H, W), (K, R, S), stride, pad, dilation, _dtype_code(dy), layout)
+    d, _, _, need = _grouped_call(N, C, H, W, K, R, S, _pair(stride), _pair(pad), _pair(dilation), _dtype_code(dy), layout, NSK_PASS_DGRAD,
+                                  int(groups))
     if out is None:
         assert not accumulate
         out = torch.empty(_act_shape(N, C, H, W, layout), dtype=dy.dtype, device=dy.device)
     ws = ws or Workspace(dy.device)
-    wp, wb = ws.get(lib().nsk_conv2d_grouped_workspace_bytes(ctypes.byref(d), int(groups), NSK_PASS_DGRAD))
-    _check(lib().nsk_conv2d_grouped_dgrad(ctypes.byref(d), int(groups), _ptr(dy), _ptr(w), _ptr(out),
+    wp, wb = ws.get(need)
+    _check(lib().nsk_conv2d_grouped_dgrad(d, int(groups), _ptr(dy), _ptr(w), _ptr(out),
                                           int(bool(accumulate)), wp, wb, _stream()), "nsk_conv2d_grouped_dgrad")
     return out
 
@@ -433,15 +480,16 @@ def conv2d_grouped_wgrad(x, dy, filt_logical, groups, stride=1, pad=0, dilation=
     N, C, H, W = _logical(x, layout)
     K, Cw, R, S = filt_logical
     assert Cw * groups == C and x.dtype == dy.dtype
-    d = conv_desc((N, C, H, W), (K, R, S), stride, pad, dilation, _dtype_code(x), layout)
+    d, _, _, need = _grouped_call(N, C, H, W, K, R, S, _pair(stride), _pair(pad), _pair(dilation), _dtype_code(x), layout, NSK_PASS_WGRAD,
+                                  int(groups))
     if out is None:
         assert not accumulate
         shape = (K, R, S, Cw) if layout == NSK_NHWC else (K, Cw, R, S)
         out = torch.empty(shape, dtype=torch.float32, device=x.device)
     assert out.dtype == torch.float32
     ws = ws or Workspace(x.device)
-    wp, wb = ws.get(lib().nsk_conv2d_grouped_workspace_bytes(ctypes.byref(d), int(groups), NSK_PASS_WGRAD))
-    _check(lib().nsk_conv2d_grouped_wgrad(ctypes.byref(d), int(groups), _ptr(x), _ptr(dy), _ptr(out),
+    wp, wb = ws.get(need)
+    _check(lib().nsk_conv2d_grouped_wgrad(d, int(groups), _ptr(x), _ptr(dy), _ptr(out),
                                           int(bool(accumulate)), wp, wb, _stream()), "nsk_conv2d_grouped_wgrad")
     return out
 
@@ -463,8 +511,8 @@ def bn_relu_add_fwd(x, gamma, beta, residual=None, eps=1e-5, relu=True, layout=N
     """Returns (out, save_mean, save_invstd).  With relu_mask (uint8 tensor of bn_mask_bytes(x) bytes) the ReLU
     mask is written there for bn_relu_add_bwd(..., relu_mask=...).  With stats ([2, rows, C] float32 partial sums of
     x and x*x, as returned by conv2d_fwd_stats) the statistics pass over x is skipped."""
-    d = bn_desc(x, layout, eps, momentum, relu)
-    C = d.C
+    N, C, H, W = _logical(x, layout)
+    d, need = _bn_call(N, C, H, W, _dtype_code(x), layout, float(eps), float(momentum), int(bool(relu)), NSK_BN_FWD)
     if out is None:
         out = torch.empty_like(x)
     if save_mean is None:
@@ -472,19 +520,19 @@ def bn_relu_add_fwd(x, gamma, beta, residual=None, eps=1e-5, relu=True, layout=N
     if save_invstd is None:
         save_invstd = torch.empty(C, dtype=torch.float32, device=x.device)
     ws = ws or Workspace(x.device)
-    wp, wb = ws.get(lib().nsk_bn_workspace_bytes(ctypes.byref(d), NSK_BN_FWD))
+    wp, wb = ws.get(need)
     if stats is not None:
-        _check(lib().nsk_bn_relu_add_fwd_stats(ctypes.byref(d), _ptr(x), _ptr(residual), _ptr(gamma), _ptr(beta), _ptr(out),
+        _check(lib().nsk_bn_relu_add_fwd_stats(d, _ptr(x), _ptr(residual), _ptr(gamma), _ptr(beta), _ptr(out),
                                                _ptr(relu_mask), _ptr(save_mean), _ptr(save_invstd), _ptr(running_mean),
                                                _ptr(running_var), _ptr(stats), int(stats.shape[1]), wp, wb, _stream()),
                "nsk_bn_relu_add_fwd_stats")
         return out, save_mean, save_invstd
     if relu_mask is not None:
-        _check(lib().nsk_bn_relu_add_fwd_mask(ctypes.byref(d), _ptr(x), _ptr(residual), _ptr(gamma), _ptr(beta), _ptr(out),
+        _check(lib().nsk_bn_relu_add_fwd_mask(d, _ptr(x), _ptr(residual), _ptr(gamma), _ptr(beta), _ptr(out),
                                               _ptr(relu_mask), _ptr(save_mean), _ptr(save_invstd), _ptr(running_mean),
                                               _ptr(running_var), wp, wb, _stream()), "nsk_bn_relu_add_fwd_mask")
         return out, save_mean, save_invstd
-    _check(lib().nsk_bn_relu_add_fwd(ctypes.byref(d), _ptr(x), _ptr(residual), _ptr(gamma), _ptr(beta), _ptr(out),
+    _check(lib().nsk_bn_relu_add_fwd(d, _ptr(x), _ptr(residual), _ptr(gamma), _ptr(beta), _ptr(out),
                                      _ptr(save_mean), _ptr(save_invstd), _ptr(running_mean), _ptr(running_var),
                                      wp, wb, _stream()), "nsk_bn_relu_add_fwd")
     return out, save_mean, save_invstd
@@ -579,8 +627,8 @@ def bn_relu_add_bwd(x, out, dout, gamma, save_mean, save_invstd, relu=True, layo
                     ws: Optional[Workspace] = None, relu_mask=None):
     """Returns (dx, dresidual or None, dgamma, dbeta).  With relu_mask (as written by bn_relu_add_fwd) `out` is
     not read and may be None."""
-    d = bn_desc(x, layout, eps, 0.1, relu)
-    C = d.C
+    N, C, H, W = _logical(x, layout)
+    d, need = _bn_call(N, C, H, W, _dtype_code(x), layout, float(eps), 0.1, int(bool(relu)), NSK_BN_BWD)
     if dx is None:
         dx = torch.empty_like(x)
     if dresidual is None and want_dresidual:
@@ -590,13 +638,13 @@ def bn_relu_add_bwd(x, out, dout, gamma, save_mean, save_invstd, relu=True, layo
     if dbeta is None:
         dbeta = torch.empty(C, dtype=torch.float32, device=x.device)
     ws = ws or Workspace(x.device)
-    wp, wb = ws.get(lib().nsk_bn_workspace_bytes(ctypes.byref(d), NSK_BN_BWD))
+    wp, wb = ws.get(need)
     if relu_mask is not None:
-        _check(lib().nsk_bn_relu_add_bwd_mask(ctypes.byref(d), _ptr(x), _ptr(relu_mask), _ptr(dout), _ptr(gamma),
+        _check(lib().nsk_bn_relu_add_bwd_mask(d, _ptr(x), _ptr(relu_mask), _ptr(dout), _ptr(gamma),
                                               _ptr(save_mean), _ptr(save_invstd), _ptr(dx), _ptr(dresidual), _ptr(dgamma),
                                               _ptr(dbeta), wp, wb, _stream()), "nsk_bn_relu_add_bwd_mask")
         return dx, dresidual, dgamma, dbeta
-    _check(lib().nsk_bn_relu_add_bwd(ctypes.byref(d), _ptr(x), _ptr(out), _ptr(dout), _ptr(gamma), _ptr(save_mean),
+    _check(lib().nsk_bn_relu_add_bwd(d, _ptr(x), _ptr(out), _ptr(dout), _ptr(gamma), _ptr(save_mean),
                                      _ptr(save_invstd), _ptr(dx), _ptr(dresidual), _ptr(dgamma), _ptr(dbeta),
                                      wp, wb, _stream()), "nsk_bn_relu_add_bwd")
     return dx, dresidual, dgamma, dbeta
@@ -626,13 +674,10 @@ def maxpool2d_fwd(x, window=3, stride=2, pad=1, layout=NSK_NHWC, out=None, idx=N
 
 def maxpool2d_bwd(dy, idx, x_logical, window=3, stride=2, pad=1, layout=NSK_NHWC, out=None):
     N, C, H, W = x_logical
-    R, S = _pair(window)
-    sh, sw = _pair(stride)
-    ph, pw = _pair(pad)
-    d = nsk_pool_desc_t(N, C, H, W, R, S, sh, sw, ph, pw, _dtype_code(dy), layout)
+    d = _pool_call(N, C, H, W, _pair(window), _pair(stride), _pair(pad), _dtype_code(dy), layout)
     if out is None:
         out = torch.empty(_act_shape(N, C, H, W, layout), dtype=dy.dtype, device=dy.device)
-    _check(lib().nsk_maxpool2d_bwd(ctypes.byref(d), _ptr(dy), _ptr(idx), _ptr(out), _stream()), "nsk_maxpool2d_bwd")
+    _check(lib().nsk_maxpool2d_bwd(d, _ptr(dy), _ptr(idx), _ptr(out), _stream()), "nsk_maxpool2d_bwd")
     return out
 
 
@@ -657,20 +702,16 @@ def global_avgpool_bwd(dy, x_logical, layout=NSK_NHWC, out=None, accumulate=Fals
     return out
 
 
-def _linear_desc(N, C, K, t):
-    return nsk_linear_desc_t(int(N), int(C), int(K), _dtype_code(t))
-
-
 def linear_fwd(x, w, bias=None, out=None, ws: Optional[Workspace] = None):
     """y = x @ w^T (+ bias): x [N,C], w [K,C], bias float [K]."""
     (N, C), (K, Cw) = x.shape, w.shape
     assert C == Cw and w.dtype == x.dtype
-    d = _linear_desc(N, C, K, x)
+    d, need = _linear_call(N, C, K, _dtype_code(x), NSK_PASS_FWD)
     if out is None:
         out = torch.empty((N, K), dtype=x.dtype, device=x.device)
     ws = ws or Workspace(x.device)
-    wp, wb = ws.get(lib().nsk_linear_workspace_bytes(ctypes.byref(d), NSK_PASS_FWD))
-    _check(lib().nsk_linear_fwd(ctypes.byref(d), _ptr(x), _ptr(w), _ptr(bias), _ptr(out), wp, wb, _stream()),
+    wp, wb = ws.get(need)
+    _check(lib().nsk_linear_fwd(d, _ptr(x), _ptr(w), _ptr(bias), _ptr(out), wp, wb, _stream()),
            "nsk_linear_fwd")
     return out
 
@@ -678,13 +719,13 @@ def linear_fwd(x, w, bias=None, out=None, ws: Optional[Workspace] = None):
 def linear_dgrad(dy, w, out=None, accumulate=False, ws: Optional[Workspace] = None):
     (N, K), (Kw, C) = dy.shape, w.shape
     assert K == Kw and w.dtype == dy.dtype
-    d = _linear_desc(N, C, K, dy)
+    d, need = _linear_call(N, C, K, _dtype_code(dy), NSK_PASS_DGRAD)
     if out is None:
         assert not accumulate
         out = torch.empty((N, C), dtype=dy.dtype, device=dy.device)
     ws = ws or Workspace(dy.device)
-    wp, wb = ws.get(lib().nsk_linear_workspace_bytes(ctypes.byref(d), NSK_PASS_DGRAD))
-    _check(lib().nsk_linear_dgrad(ctypes.byref(d), _ptr(dy), _ptr(w), _ptr(out), int(accumulate), wp, wb, _stream()),
+    wp, wb = ws.get(need)
+    _check(lib().nsk_linear_dgrad(d, _ptr(dy), _ptr(w), _ptr(out), int(accumulate), wp, wb, _stream()),
            "nsk_linear_dgrad")
     return out
 
@@ -692,7 +733,7 @@ def linear_dgrad(dy, w, out=None, accumulate=False, ws: Optional[Workspace] = No
 def linear_wgrad(x, dy, dw=None, db=None, accumulate=False, want_db=True, ws: Optional[Workspace] = None):
     (N, C), (Nd, K) = x.shape, dy.shape
     assert N == Nd and x.dtype == dy.dtype
-    d = _linear_desc(N, C, K, x)
+    d, need = _linear_call(N, C, K, _dtype_code(x), NSK_PASS_WGRAD)
     if dw is None:
         assert not accumulate
         dw = torch.empty((K, C), dtype=torch.float32, device=x.device)
@@ -700,8 +741,8 @@ def linear_wgrad(x, dy, dw=None, db=None, accumulate=False, want_db=True, ws: Op
         assert not accumulate
         db = torch.empty((K,), dtype=torch.float32, device=x.device)
     ws = ws or Workspace(x.device)
-    wp, wb = ws.get(lib().nsk_linear_workspace_bytes(ctypes.byref(d), NSK_PASS_WGRAD))
-    _check(lib().nsk_linear_wgrad(ctypes.byref(d), _ptr(x), _ptr(dy), _ptr(dw), _ptr(db), int(accumulate), wp, wb,
+    wp, wb = ws.get(need)
+    _check(lib().nsk_linear_wgrad(d, _ptr(x), _ptr(dy), _ptr(dw), _ptr(db), int(accumulate), wp, wb,
                                   _stream()), "nsk_linear_wgrad")
     return dw, db
 

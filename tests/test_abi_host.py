@@ -220,3 +220,21 @@ def test_the_tests_set_only_switches_that_the_library_reads():
         if name.startswith("test_gpu") and name.endswith(".py"):
             text = open(os.path.join(here, name)).read()
             assert set(re.findall(r'(?:nsk_env\(|[{ ])"(NSK_[A-Z0-9_]+)"', text)) <= nsk_switches(), name
+
+
+def test_kept_queries_follow_the_test_switches(nsk_env):
+    """The binding keeps what the library answered for the sizes seen last: the same answer as asking again, an invalid size is
+    refused every time, and a change of the switches (which may change the answer) is seen."""
+    L = B.lib()
+    args = (4, 6, 9, 9, 16, 3, 3, (1, 1), (1, 1), (1, 1), B.NSK_BF16, B.NSK_NHWC)
+    d = B.conv_desc((4, 6, 9, 9), (16, 3, 3), 1, 1, 1, B.NSK_BF16, B.NSK_NHWC)
+    for which in (B.NSK_PASS_FWD, B.NSK_PASS_DGRAD, B.NSK_PASS_WGRAD):
+        for _ in range(2):
+            assert B._conv_call(*args, which)[4] == L.nsk_conv2d_workspace_bytes(ctypes.byref(d), which)
+    for _ in range(2):
+        with pytest.raises(B.NskError):
+            B._conv_call(4, 0, 9, 9, *args[4:], B.NSK_PASS_FWD)
+    padded = B._conv_call(*args, B.NSK_PASS_FWD)[4]
+    nsk_env("NSK_NO_PAD", "1")
+    plain = B._conv_call(*args, B.NSK_PASS_FWD)[4]
+    assert plain == L.nsk_conv2d_workspace_bytes(ctypes.byref(d), B.NSK_PASS_FWD) and plain != padded
