@@ -854,9 +854,12 @@ dim3 fast_apply_grid(const nsk_bn_desc_t &d, const Geom &g)
     const long passes = (g.M + fast_rows_at_once(d, g.vec) - 1) / fast_rows_at_once(d, g.vec);
     return dim3((unsigned)std::max(1L, std::min<long>(passes, 256 / fast_chunks(d))), fast_chunks(d));
 }
-// More rows of statistics than a block reads beside its work (400 KB: 4 us) are folded first, into few rows by enough blocks
-bool fold_first(int stats_rows, const nsk_bn_desc_t &d, const Geom &g) { return (long)stats_rows * fast_chunk(d) * 8 > (400L << 10) && g.G >= 16; }
-
+// More rows of statistics than an apply block reads beside its work (512 KB: 5 us), or than a launch between finishes column by column,
+// are folded first, into at most 64 rows by enough blocks
+bool fold_first(int stats_rows, const nsk_bn_desc_t &d, const Geom &g)
+{
+    return g.G >= 16 && (apply_finishes(d, g) ? (long)stats_rows * fast_chunk(d) * 8 > (512L << 10) : stats_rows > 1024);
+}
 template <typename T, int MODE, int THREADS>
 void launch_sums_fast(const nsk_bn_desc_t &d, const Geom &g, int G, const T *x, const T *out, const T *dout, const float *mean, const float *invstd,
                       float *p0, float *p1, unsigned char *mask, const unsigned char *mask_in, const float *act, float *shift, hipStream_t stream)
