@@ -76,11 +76,11 @@ bool conv_pw_applicable(int dtype, const IgemmArgs &a)
     return a.M >= min_rows;
 }
 
-// one row per wavefront of every row share (the column groups of a split output write different columns of a row)
+// one row per block, or per wavefront of every row share where the columns are split (the groups write different columns of a row)
 int conv_pw_stats_rows(const IgemmArgs &a)
 {
     const int cols = pw_cols(a);
-    return cols > 0 ? kPwGrid * 4 / (a.Ngemm / cols) : kPwGrid * 4;
+    return cols > 0 && cols < a.Ngemm ? kPwGrid * 4 / (a.Ngemm / cols) : pw_grid(a);
 }
 
 int launch_conv_pw(const IgemmArgs &a, hipStream_t stream)

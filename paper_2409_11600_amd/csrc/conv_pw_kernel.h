@@ -34,14 +34,17 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kPwGrid = 256;            // blocks; fixed so that the number of statistics rows is a shape property
+constexpr int kPwGrid = 256;            // blocks (see pw_grid); a shape property, as the number of statistics rows is
 constexpr unsigned PW_OOB = 0xF0000000u;  // beyond every buffer: loads return zero, stores are dropped
 constexpr int PW_MAX_NCH = 4;           // column chunks of 64 (Ngemm <= 256)
 
+constexpr int pw_blocks_per_cu(int ks, int fm, int nw) { return nw >= 64 || ks * fm > 18 ? 1 : ks * fm > 9 ? 2 : 4; }
+
 template <int KS, int FM, int TAPS, bool ACC, int NW>
-__global__ __launch_bounds__(256, 1) void conv_pw_kernel(const PwArgs pa)
+__global__ __launch_bounds__(256, pw_blocks_per_cu(KS, FM, NW)) void conv_pw_kernel(const PwArgs pa)
 {
     const IgemmArgs &a = pa.g;
+    constexpr int NCH = NW == 64 ? PW_MAX_NCH : 1;   // chunks
     constexpr int TM = 32 * FM;                      // pixels per wavefront tile
     constexpr int RPL = (TM + 63) / 64;              // tile rows decoded per lane
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -74,12 +77,18 @@ __global__ __launch_bounds__(256, 1) void conv_pw_kernel(const PwArgs pa)
     const int rb = ((int)blockIdx.x & 7) + 8 * (((int)blockIdx.x >> 3) / pa.col_groups);
     const int n_rb = (int)gridDim.x / pa.col_groups;      // row shares
     const int col0 = cg * pa.cols;                        // first output channel of this block
-    for (int idx = tid; idx < w_rows * (2 * KS); idx += 256) {
+    // (the first pieces are requested here and stored behind the request of the first tile, so that a block waits for memory once)
+    constexpr int FL = 6;
+    u32x4 fv[FL];
+    auto filter_at = [&](int idx) -> u32x4 {
         const int n = idx / (2 * KS), ch = idx % (2 * KS);
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(wpk_rsrc, n < pa.cols ? (unsigned)(((col0 + n) * KS * 16 + ch * 8) * 2) : PW_OOB, 0, 0);
-        *(u32x4 *)(w_lds + n * WROW + ch * 16) = v;
-    }
-    __syncthreads();
+        return __builtin_amdgcn_raw_buffer_load_b128(wpk_rsrc, n < pa.cols ? (unsigned)(((col0 + n) * KS * 16 + ch * 8) * 2) : PW_OOB, 0, 0);
+    };
+    auto filter_to_lds = [&](int idx, u32x4 v) {
+        if (idx < w_rows * (2 * KS)) *(u32x4 *)(w_lds + idx / (2 * KS) * WROW + idx % (2 * KS) * 16) = v;
+    };
+#pragma unroll
+    for (int i = 0; i < FL; ++i) fv[i] = filter_at(tid + 256 * i);
 
     const int per_img = a.Mi * a.Mj;
     // Source (per tap) and output byte offsets of the tile's pixels (PW_OOB for rows past the end and for source
@@ -142,9 +151,9 @@ __global__ __launch_bounds__(256, 1) void conv_pw_kernel(const PwArgs pa)
             }
     };
 
-    float ssum[PW_MAX_NCH][8], ssq[PW_MAX_NCH][8];
+    float ssum[NCH][8], ssq[NCH][8];
 #pragma unroll
-    for (int nc = 0; nc < PW_MAX_NCH; ++nc)
+    for (int nc = 0; nc < NCH; ++nc)
 #pragma unroll
         for (int e = 0; e < 8; ++e) ssum[nc][e] = ssq[nc][e] = 0.f;
     const int nch = pa.cols / NW;
@@ -152,7 +161,7 @@ __global__ __launch_bounds__(256, 1) void conv_pw_kernel(const PwArgs pa)
 
     auto compute = [&](const u32x4 (&A)[FM][KS], int par, bool has_next) {
 #pragma unroll
-        for (int nc = 0; nc < PW_MAX_NCH; ++nc) {
+        for (int nc = 0; nc < NCH; ++nc) {
             if (nc >= nch) break;
             if constexpr (ACC) {
                 if (nc + 1 < nch) issue_old(O[(nc + 1) & 1], par, nc + 1);
@@ -252,6 +261,15 @@ __global__ __launch_bounds__(256, 1) void conv_pw_kernel(const PwArgs pa)
         if constexpr (ACC) issue_old(O[0], 0, 0);
         issue(A0, 0);
     }
+    for (int at = tid;;) {
+#pragma unroll
+        for (int i = 0; i < FL; ++i) filter_to_lds(at + 256 * i, fv[i]);
+        at += 256 * FL;
+        if (at - tid >= w_rows * (2 * KS)) break;
+#pragma unroll
+        for (int i = 0; i < FL; ++i) fv[i] = filter_at(at + 256 * i);
+    }
+    lds_barrier();
     while (t < pa.tiles) {
         bool has_next = t + stride < pa.tiles;
         if (has_next) {
@@ -275,10 +293,12 @@ __global__ __launch_bounds__(256, 1) void conv_pw_kernel(const PwArgs pa)
     }
 
     if (!ACC && want_stats) {
-        // lanes with equal (lane % CPP) hold the same channels: add them up, one row of partial sums per wavefront
-        const int row = rb * 4 + wave, ck = lane % CPP;
+        // lanes with equal (lane % CPP) hold the same channels: add them up; then the wavefronts' sums through their strips, in
+        // order: one row of partial sums per block where it has all columns
+        const int ck = lane % CPP;
+        float *const mine = (float *)my_st;              // [2][cols]
 #pragma unroll
-        for (int nc = 0; nc < PW_MAX_NCH; ++nc) {
+        for (int nc = 0; nc < NCH; ++nc) {
             if (nc >= nch) break;
 #pragma unroll
             for (int e = 0; e < 8; ++e)
@@ -288,12 +308,24 @@ __global__ __launch_bounds__(256, 1) void conv_pw_kernel(const PwArgs pa)
                     ssq[nc][e] += __shfl_xor(ssq[nc][e], o, 64);
                 }
             if (lane < CPP) {
-                float *r0 = a.stats + (size_t)row * a.Ngemm + col0 + nc * NW + ck * 8;
-                float *r1 = r0 + (size_t)a.stats_rows * a.Ngemm;
+                float *r0 = mine + nc * NW + ck * 8, *r1 = r0 + pa.cols;
                 *(f32x4 *)r0 = f32x4{ssum[nc][0], ssum[nc][1], ssum[nc][2], ssum[nc][3]};
                 *(f32x4 *)(r0 + 4) = f32x4{ssum[nc][4], ssum[nc][5], ssum[nc][6], ssum[nc][7]};
                 *(f32x4 *)r1 = f32x4{ssq[nc][0], ssq[nc][1], ssq[nc][2], ssq[nc][3]};
                 *(f32x4 *)(r1 + 4) = f32x4{ssq[nc][4], ssq[nc][5], ssq[nc][6], ssq[nc][7]};
+            }
+        }
+        lds_barrier();
+        const int pitch = (STRIP + (2 * TAPS + 2) * TM * 4) / 4;
+        const float *first = (const float *)(smem + (size_t)w_rows * WROW);
+        for (int c = tid; c < 2 * pa.cols; c += 256) {
+            const int which = c >= pa.cols;
+            float *to = a.stats + (size_t)which * a.stats_rows * a.Ngemm + col0 + c - which * pa.cols;
+            if (pa.col_groups > 1) {       // (few row shares: a row per wavefront)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) to[(size_t)(4 * rb + w) * a.Ngemm] = first[c + w * pitch];
+            } else {
+                to[(size_t)rb * a.Ngemm] = (first[c] + first[c + pitch]) + (first[c + 2 * pitch] + first[c + 3 * pitch]);
             }
         }
     }
@@ -316,6 +348,16 @@ inline int pw_cols(const IgemmArgs &a)
     return 0;
 }
 
+// Blocks of a launch: one a CU, two for the 3x3 filters of narrow outputs where every wavefront then still has a tile (their registers
+// allow it, and four wavefronts a CU leave most of the wait for the nine taps' loads exposed).  us, one / two: 16 -> 16 256 images
+// of 32x32 10.4 / 8.9, 128 of 56x56 14.6 / 11.5 (four blocks of 32-pixel tiles 11.2, but 14.4 with statistics against 13.4),
+// 32 -> 32 64 of 56x56 17.4 / 13.6.
+inline int pw_tile_rows(const IgemmArgs &a) { return a.Ngemm <= 32 && a.ntaps == 9 && a.Ktot == 288 ? 32 : 64; }
+inline int pw_grid(const IgemmArgs &a)
+{
+    return a.Ngemm <= 32 && a.ntaps == 9 && ceil_div(a.M, pw_tile_rows(a)) >= 2 * kPwGrid * 4 ? 2 * kPwGrid : kPwGrid;
+}
+
 inline size_t pw_smem(const IgemmArgs &a, int tm)
 {
     const int nw = pw_chunk(a), cols = pw_cols(a);
@@ -328,9 +370,9 @@ template <int KS, int FM, int TAPS, bool ACC, int NW> int launch_pw_acc(PwArgs p
     pa.tiles = ceil_div(pa.g.M, 32 * FM);
     pa.cols = pw_cols(pa.g);
     pa.col_groups = pa.g.Ngemm / pa.cols;
-    // at least half of a CU's LDS, so that the 256 blocks land on 256 different CUs
+    // at least half of a CU's LDS, so that 256 blocks land on 256 different CUs
     size_t smem = pw_smem(pa.g, 32 * FM);
-    if (smem < 84 * 1024) smem = 84 * 1024;
+    if (pw_grid(pa.g) == kPwGrid && smem < 84 * 1024) smem = 84 * 1024;
     static bool configured = false;   // the attribute is a property of the function, set once per process
     if (!configured) {
         const hipError_t e = hipFuncSetAttribute((const void *)conv_pw_kernel<KS, FM, TAPS, ACC, NW>,
@@ -341,7 +383,7 @@ template <int KS, int FM, int TAPS, bool ACC, int NW> int launch_pw_acc(PwArgs p
         }
         configured = true;
     }
-    hipLaunchKernelGGL((conv_pw_kernel<KS, FM, TAPS, ACC, NW>), dim3(kPwGrid), dim3(256), smem, stream, pa);
+    hipLaunchKernelGGL((conv_pw_kernel<KS, FM, TAPS, ACC, NW>), dim3(pw_grid(pa.g)), dim3(256), smem, stream, pa);
     return check_launch();
 }
 

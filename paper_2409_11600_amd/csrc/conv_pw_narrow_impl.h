@@ -21,7 +21,7 @@ int PW_CAT(launch_conv_pw_narrow, PW_NARROW_NW)(const PwArgs &pa, hipStream_t st
     case 2 * 16 + 1: return launch_pw<2, 2, 1, NW>(pa, stream);
     case 4 * 16 + 2: return launch_pw<4, 2, 2, NW>(pa, stream);
     case 8 * 16 + 4: return launch_pw<8, 2, 4, NW>(pa, stream);
-    case 18 * 16 + 9: return launch_pw<18, 2, 9, NW>(pa, stream);
+    case 18 * 16 + 9: return launch_pw<18, 1, 9, NW>(pa, stream);      // (32-pixel tiles: pw_tile_rows)
     case 4 * 16 + 1: return launch_pw<4, 2, 1, NW>(pa, stream);
     case 8 * 16 + 2: return launch_pw<8, 2, 2, NW>(pa, stream);
     case 16 * 16 + 4: return launch_pw<16, 1, 4, NW>(pa, stream);

@@ -1,0 +1,37 @@
+"""The 3x3 filters of 16- and 32-channel outputs on the short-reduction kernel: sizes around the line between one and two blocks a CU, ragged
+last tiles, with statistics, against torch in 64 bits on the device."""
+import pytest
+import torch
+
+from paper_2409_11600_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def conv64(x, w):
+    xp = torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1))
+    N, H, W, _ = x.shape
+    return sum(xp[:, r:r + H, s:s + W] @ w[:, r, s].double().t() for r in range(3) for s in range(3))
+
+
+@pytest.mark.parametrize("N,H,W,C,K", [(128, 32, 32, 16, 16), (127, 32, 32, 16, 16), (128, 31, 33, 32, 16), (64, 32, 32, 32, 32), (63, 33, 31, 32, 32),
+                                       (131, 32, 32, 16, 32), (9, 31, 30, 16, 16)])
+def test_forward_backward_data_and_statistics(N, H, W, C, K):
+    print(f"narrow {N}x{H}x{W} {C}->{K}", flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(N + H)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda:0")
+    x, w, dy, old = r(N, H, W, C).bfloat16(), (r(K, 3, 3, C) / (9 * C) ** 0.5).bfloat16(), r(N, H, W, K).bfloat16(), r(N, H, W, C).bfloat16()
+    want = conv64(x, w)
+    y, stats = B.conv2d_fwd_stats(x, w, 1, 1)
+    dx = B.conv2d_dgrad(dy, w, (N, C, H, W), 1, 1)
+    acc = B.conv2d_dgrad(dy, w, (N, C, H, W), 1, 1, out=old.clone(), accumulate=True)
+    torch.cuda.synchronize()
+    # one rounding to bf16 (2^-9 of the value) and fp32 sums of 9*C products
+    near = lambda a, b: ((a.double() - b).abs() <= 2.0 ** -8 * b.abs() + 1e-5).all()
+    assert near(y, want)
+    dx64 = conv64(dy, w.flip(1, 2).permute(3, 1, 2, 0).contiguous())
+    assert near(dx, dx64) and near(acc, dx64 + old.double())
+    Y = y.double().reshape(-1, K)
+    # sums of the values as stored: float chains of a few hundred
+    assert ((stats[0].double().sum(0) - Y.sum(0)).abs() <= 2e-5 * Y.abs().sum(0)).all()
+    assert ((stats[1].double().sum(0) - (Y * Y).sum(0)).abs() <= 2e-5 * (Y * Y).sum(0)).all()
