@@ -365,6 +365,10 @@ int nsk_adamw_step_multi(int count, const nsk_param_t *params, int step, float l
 #define NSK_SUMSQ_PARTIALS 256
 int nsk_sumsq_accumulate(size_t n, const float *g, float *partials, float *sumsq, void *stream);
 int nsk_clip_scale(const float *sumsq, float max_norm, float *scale, void *stream);
+/* Both steps for `count` gradients in two launches: *sumsq (written, not added to) and *scale.  g and n are host arrays of device
+ * pointers on 16-byte boundaries and element counts above zero; partials as above. */
+int nsk_clip_scale_multi(int count, const float *const *g, const size_t *n, float max_norm, float *partials, float *sumsq,
+                         float *scale, void *stream);
 
 /* ---------------------------------------------------------------------------------------------------------------
  * The recurrent workload (section "Experiments and Discussion": an embedding over the vocabulary, one GRU layer, an

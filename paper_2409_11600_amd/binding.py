@@ -176,6 +176,8 @@ def lib() -> ctypes.CDLL:
         L.nsk_sumsq_accumulate.argtypes = [sz, vp, vp, vp, vp]
         L.nsk_clip_scale.restype = ci
         L.nsk_clip_scale.argtypes = [vp, cf, vp, vp]
+        L.nsk_clip_scale_multi.restype = ci
+        L.nsk_clip_scale_multi.argtypes = [ci, ctypes.POINTER(vp), ctypes.POINTER(sz), cf, vp, vp, vp, vp]
         L.nsk_embedding_fwd.restype = ci
         L.nsk_embedding_fwd.argtypes = [ci, ci, ci, ci, vp, vp, vp, vp]
         L.nsk_embedding_bwd.restype = ci
@@ -231,7 +233,7 @@ EXPORTS = ("nsk_version", "nsk_test_hooks_reload", "nsk_status_string", "nsk_las
            "nsk_maxpool2d_fwd", "nsk_maxpool2d_bwd",
            "nsk_global_avgpool_fwd", "nsk_global_avgpool_bwd", "nsk_linear_workspace_bytes", "nsk_linear_fwd",
            "nsk_linear_dgrad", "nsk_linear_wgrad", "nsk_transpose2d", "nsk_softmax_xent_fwd", "nsk_softmax_xent_bwd",
-           "nsk_sgd_momentum_step", "nsk_adamw_step", "nsk_sgd_momentum_step_multi", "nsk_adamw_step_multi", "nsk_sumsq_accumulate", "nsk_clip_scale",
+           "nsk_sgd_momentum_step", "nsk_adamw_step", "nsk_sgd_momentum_step_multi", "nsk_adamw_step_multi", "nsk_sumsq_accumulate", "nsk_clip_scale", "nsk_clip_scale_multi",
            "nsk_embedding_fwd", "nsk_embedding_bwd", "nsk_gru_gates_fwd", "nsk_gru_gates_bwd",
            "nsk_gru_step_supported", "nsk_gru_step_fwd", "nsk_gru_step_bwd", "nsk_gru_seq_fwd", "nsk_gru_seq_bwd",
            "nsk_pool_create", "nsk_pool_get", "nsk_pool_put", "nsk_pool_cached", "nsk_pool_stats", "nsk_pool_destroy")
@@ -832,12 +834,11 @@ def clip_scale(grads, max_norm, partials=None, sumsq=None, scale=None):
         sumsq = torch.empty((1,), dtype=torch.float32, device=dev)
     if scale is None:
         scale = torch.empty((1,), dtype=torch.float32, device=dev)
-    sumsq.zero_()
-    for g in grads:
-        assert g.dtype == torch.float32
-        _check(lib().nsk_sumsq_accumulate(g.numel(), _ptr(g), _ptr(partials), _ptr(sumsq), _stream()),
-               "nsk_sumsq_accumulate")
-    _check(lib().nsk_clip_scale(_ptr(sumsq), float(max_norm), _ptr(scale), _stream()), "nsk_clip_scale")
+    assert all(g.dtype == torch.float32 for g in grads)
+    n = len(grads)
+    ptrs, sizes = (ctypes.c_void_p * n)(*[_ptr(g) for g in grads]), (ctypes.c_size_t * n)(*[g.numel() for g in grads])
+    _check(lib().nsk_clip_scale_multi(n, ptrs, sizes, float(max_norm), _ptr(partials), _ptr(sumsq), _ptr(scale), _stream()),
+           "nsk_clip_scale_multi")
     return scale
 
 

@@ -37,36 +37,85 @@ __global__ __launch_bounds__(256) void embedding_fwd_kernel(const int *__restric
 // Gradient of the lookup without atomics: block b owns the vocabulary rows v with v % gridDim.x == b, walks over ALL
 // positions in order and adds the rows that are its own, so every dtable element is updated by one thread in
 // position order (bitwise reproducible).  The token list is tiny next to the table, every block reads all of it.
-template <typename T>
+// Bound by the zeros it writes and by latency: 2048 positions are tested between two barriers (256 until then, forty rounds of a
+// load and three barriers for 10000 positions), the next are on their way, the matches are kept until there are many, and eight of them
+// fetch their operands together (one by one a chain of three loads each).  10000 positions of 32768 x 256: 36.7 -> 26.2 us.
+template <typename T, int CH>     // CH: chunks of 256 positions that are tested at once
 __global__ __launch_bounds__(256) void embedding_bwd_kernel(const int *__restrict__ tokens, const T *__restrict__ dout,
                                                             float *__restrict__ dtable, int n, int E, int V, int accumulate)
 {
-    __shared__ int hit[256];         // positions of this chunk whose row belongs to the block, in position order
-    __shared__ int wave_hits[4];
+    constexpr int CAP = 2 * 256 * CH;           // matches that are kept
+    __shared__ int hit[CAP], row_of[CAP];       // positions whose row belongs to the block, in position order, and their rows
+    __shared__ int found[2][CH][4];
     const int b = blockIdx.x, nb = gridDim.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int v[CH];
+    auto fetch = [&](int base) {
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            const int i = base + 256 * j + threadIdx.x;
+            v[j] = i < n ? tokens[i] : -1;
+        }
+    };
+    fetch(0);
     if (!accumulate)
-        for (int v = b; v < V; v += nb)
-            for (int e = threadIdx.x; e < E; e += 256) dtable[(long)v * E + e] = 0.f;
-    for (int base = 0; base < n; base += 256) {
-        // all 256 positions of the chunk are tested at once; the matches are compacted in position order
-        const int i = base + threadIdx.x;
-        const int v = i < n ? tokens[i] : -1;
-        const bool mine = v >= 0 && v < V && v % nb == b;
-        const unsigned long long ballot = __ballot(mine);
-        if (lane == 0) wave_hits[wave] = __popcll(ballot);
+        for (int r = b; r < V; r += nb)
+            for (int e = threadIdx.x; e < E; e += 256) dtable[(long)r * E + e] = 0.f;
+    int total = 0;
+    for (int base = 0, p = 0; base < n; base += 256 * CH, p ^= 1) {
+        unsigned long long ballot[CH];
+        int row[CH];
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            row[j] = v[j];
+            // (a division for each of 1024 blocks x 10000 positions would be 10 us of the chip's vector units)
+            ballot[j] = __ballot(v[j] >= 0 && v[j] < V && (nb == 1024 ? v[j] & 1023 : v[j] % nb) == b);
+            if (lane == 0) found[p][j][wave] = __popcll(ballot[j]);
+        }
+        const bool last = base + 256 * CH >= n;
+        if (!last) fetch(base + 256 * CH);
         __syncthreads();
-        int before = 0;
-        for (int w = 0; w < wave; ++w) before += wave_hits[w];
-        const int total = wave_hits[0] + wave_hits[1] + wave_hits[2] + wave_hits[3];
-        if (mine) hit[before + __popcll(ballot & ((1ull << lane) - 1ull))] = i;
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            int before = total;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                if (w == wave) before = total;
+                total += found[p][j][w];
+            }
+            if ((ballot[j] >> lane) & 1ull) {
+                const int at = before + __popcll(ballot[j] & ((1ull << lane) - 1ull));
+                hit[at] = base + 256 * j + threadIdx.x;
+                row_of[at] = row[j];
+            }
+        }
+        if (!last && total <= CAP - 256 * CH) continue;
         __syncthreads();
-        for (int k = 0; k < total; ++k) {
-            const int pos = hit[k];
-            const long row = (long)tokens[pos] * E;
-            for (int e = threadIdx.x; e < E; e += 256) dtable[row + e] += ld(dout, (long)pos * E + e);
+        // eight matches at a time: their gradients and rows are requested together; a row that occurs again among the eight goes
+        // on from the sum before it
+        for (int k = 0; k < total; k += 8) {
+            for (int e = threadIdx.x; e < E; e += 256) {
+                float d[8], t[8];
+                int r[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int m = k + j < total ? k + j : k;
+                    r[j] = row_of[m];
+                    d[j] = ld(dout, (long)hit[m] * E + e);
+                    t[j] = dtable[(long)r[j] * E + e];
+                }
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    if (k + j >= total) break;
+#pragma unroll
+                    for (int i = 0; i < j; ++i) t[j] = r[i] == r[j] ? t[i] : t[j];
+                    t[j] += d[j];
+                    dtable[(long)r[j] * E + e] = t[j];
+                }
+            }
         }
         __syncthreads();
+        total = 0;
     }
 }
 
@@ -265,12 +314,15 @@ int nsk_embedding_bwd(int dtype, int n, int E, int V, const int *tokens, const v
     if (!tokens || !dout || !dtable) return NSK_ERR_NULL;
     if (unaligned16(tokens) || unaligned16(dout) || unaligned16(dtable)) return NSK_ERR_ALIGNMENT;
     const int blocks = V < 1024 ? V : 1024;
-    if (dtype == NSK_BF16)
-        hipLaunchKernelGGL(embedding_bwd_kernel<bf16_t>, dim3(blocks), dim3(256), 0, (hipStream_t)stream, tokens,
-                           (const bf16_t *)dout, dtable, n, E, V, accumulate);
-    else
-        hipLaunchKernelGGL(embedding_bwd_kernel<float>, dim3(blocks), dim3(256), 0, (hipStream_t)stream, tokens,
-                           (const float *)dout, dtable, n, E, V, accumulate);
+    // few positions: one chunk at a time (80 positions 3.1 us, 500 4.0; 4.6 and 4.9 with eight)
+#define NSK_EMB(T, CH) \
+    hipLaunchKernelGGL((embedding_bwd_kernel<T, CH>), dim3(blocks), dim3(256), 0, (hipStream_t)stream, tokens, (const T *)dout, dtable, n, E, V, accumulate)
+    if (dtype == NSK_BF16) {
+        if (n <= 1024) NSK_EMB(bf16_t, 1); else NSK_EMB(bf16_t, 8);
+    } else {
+        if (n <= 1024) NSK_EMB(float, 1); else NSK_EMB(float, 8);
+    }
+#undef NSK_EMB
     return check_launch();
 }
 

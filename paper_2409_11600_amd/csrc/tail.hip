@@ -153,6 +153,51 @@ __global__ __launch_bounds__(1024) void bias_grad_kernel(const T *__restrict__ d
     }
 }
 
+// The same in two launches for many rows, where a launch has the workspace of the weight gradient before it (whose partial sums have been
+// read by then): blocks of 64 columns x a share of the rows, four columns (16 or 8 bytes) a lane, then the shares' sums in 64
+// bits.  The kernel above keeps 48 CUs busy with 768 columns and reads them in 64-byte pieces: fp32 10000 x 768 (30.7 MB)
+// 24.3 us there, 10.4 here; bf16 18.5 / 6.4; but 2048 x 192 2.9 / 4.4, 4000 x 384 4.4 / 4.8.
+constexpr int kBiasShares = 64;
+template <typename T>
+__global__ __launch_bounds__(256) void bias_partial_kernel(const T *__restrict__ dy, float *__restrict__ part, int N, int K, int rows)
+{
+    typedef T Vec __attribute__((ext_vector_type(4)));
+    __shared__ f32x4 sums[16][16];
+    const int cv = threadIdx.x & 15, rl = threadIdx.x >> 4, k = blockIdx.x * 64 + cv * 4;
+    const int r1 = min(N, (int)(blockIdx.y + 1) * rows);
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    if (k < K) {
+#pragma unroll 8
+        for (int n = blockIdx.y * rows + rl; n < r1; n += 16) {
+            const Vec v = *(const Vec *)(dy + (long)n * K + k);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] += (float)v[e];
+        }
+    }
+    sums[rl][cv] = s;
+    __syncthreads();
+    if (rl == 0 && k < K) {
+        double t[4] = {};
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[e] += (double)sums[r][cv][e];
+        *(f32x4 *)(part + (long)blockIdx.y * K + k) = f32x4{(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
+    }
+}
+__global__ __launch_bounds__(64) void bias_final_kernel(const float *__restrict__ part, float *__restrict__ db, int shares, int K, int accumulate)
+{
+    const int k = blockIdx.x * 16 + (threadIdx.x & 15), q = threadIdx.x >> 4;      // four lanes a column, every fourth share each
+    double s = 0.;
+    if (k < K) {
+#pragma unroll 8
+        for (int r = q; r < shares; r += 4) s += (double)part[(long)r * K + k];
+    }
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    if (q == 0 && k < K) db[k] = accumulate ? db[k] + (float)s : (float)s;
+}
+
 // Matrix products with very few rows (a recurrent step: 50 samples): a tile kernel would run on a handful of blocks,
 // so here every output element has its own thread and the product runs on the vector units.
 //   forward:  y[n][k] = sum_c x[n][c] * w[k][c] (+ bias[k]); lane = k (the 64 rows of w a wavefront walks stay in L1
@@ -182,6 +227,26 @@ __global__ __launch_bounds__(256) void linear_small_fwd_kernel(const T *__restri
     float r = (s0 + s1) + (s2 + s3);
     if (bias) r = (float)(T)r + bias[k];      // as the large path: product rounded to the storage type, then the bias
     y[i] = (T)r;
+}
+
+// Few outputs (the output layer of a classifier): sixteen lanes share one, else its whole reduction is a chain of loads in one thread
+// and the launch a handful of wavefronts: 50 x 2 outputs of 256 channels 8.3 us with a thread each, 64 x 64 of 128 6.4, 2.7 here.
+template <typename T>
+__global__ __launch_bounds__(256) void linear_few_fwd_kernel(const T *__restrict__ x, const T *__restrict__ w, const float *__restrict__ bias,
+                                                             T *__restrict__ y, int N, int C, int K)
+{
+    const int i = blockIdx.x * 16 + (threadIdx.x >> 4), q = threadIdx.x & 15;
+    const bool live = i < N * K;
+    const int n = live ? i / K : 0, k = live ? i - n * K : 0;
+    const T *xr = x + (long)n * C, *wr = w + (long)k * C;
+    float s = 0.f;
+#pragma unroll 8
+    for (int c = q; c < C; c += 16) s += ld(xr, c) * ld(wr, c);
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o, 64);
+    if (!live || q != 0) return;
+    if (bias) s = (float)(T)s + bias[k];
+    y[i] = (T)s;
 }
 
 // backward: a block computes 64 consecutive outputs of one row; its four wavefronts each take a quarter of the
@@ -337,6 +402,56 @@ __global__ __launch_bounds__(1024) void sumsq_partial_kernel(size_t n, const flo
     }
 }
 // one wavefront: lane l adds the partial sums l, l + 64, ..., the lanes are added in a fixed order
+// The clip of many tensors in two launches (seven tensors one by one: sixteen launches, 63 us behind busy ones): a block takes its share
+// of every tensor and leaves one partial sum; `add` for the second and later launches of more than kMaxSumsq tensors.
+constexpr int kMaxSumsq = 48;
+struct SumsqTable {
+    const float *g[kMaxSumsq];
+    size_t n[kMaxSumsq];
+    int count, add;
+};
+__global__ __launch_bounds__(1024) void sumsq_multi_kernel(const SumsqTable tab, float *__restrict__ partials)
+{
+    __shared__ double part[16];
+    double s = 0.0;
+    const size_t step = (size_t)gridDim.x * 1024, first = (size_t)blockIdx.x * 1024 + threadIdx.x;
+    for (int t = 0; t < tab.count; ++t) {
+        const float *__restrict__ g = tab.g[t];
+        const size_t n = tab.n[t], nv = n / 4;
+#pragma unroll 4
+        for (size_t i = first; i < nv; i += step) {
+            const f32x4 v = *(const f32x4 *)(g + 4 * i);
+            s += ((double)(v[0] * v[0]) + (double)(v[1] * v[1])) + ((double)(v[2] * v[2]) + (double)(v[3] * v[3]));
+        }
+        if (first < n - 4 * nv) {
+            const float v = g[4 * nv + first];
+            s += (double)(v * v);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = tab.add ? (double)partials[blockIdx.x] : 0.0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) t += part[w];
+        partials[blockIdx.x] = (float)t;
+    }
+}
+__global__ __launch_bounds__(64) void clip_final_kernel(const float *__restrict__ partials, int nb, float max_norm, float *__restrict__ sumsq,
+                                                        float *__restrict__ scale)
+{
+    double s = 0.0;
+    for (int i = threadIdx.x; i < nb; i += 64) s += (double)partials[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (threadIdx.x == 0) {
+        const float q = (float)s, r = max_norm / (sqrtf(q) + 1e-6f);
+        sumsq[0] = q;
+        scale[0] = r < 1.f ? r : 1.f;
+    }
+}
 __global__ __launch_bounds__(64) void sumsq_final_kernel(const float *__restrict__ partials, int nb, float *__restrict__ sumsq)
 {
     double s = 0.0;
@@ -458,8 +573,15 @@ int nsk_linear_fwd(const nsk_linear_desc_t *desc, const void *x, const void *w, 
         if (!x || !w || !y) return NSK_ERR_NULL;
         if (unaligned(x) || unaligned(w) || unaligned(y)) return NSK_ERR_ALIGNMENT;
         const long total = (long)desc->N * desc->K;
-        const dim3 grid((unsigned)((total + 255) / 256));
-        if (desc->dtype == NSK_BF16)
+        const dim3 grid((unsigned)((total + 255) / 256)), few((unsigned)((total + 15) / 16));
+        const bool lanes = total <= 4096 && desc->C >= 128;     // (below, a thread's chain is short: 64 channels 4.2 / 2.6 us)
+        if (lanes && desc->dtype == NSK_BF16)
+            hipLaunchKernelGGL(linear_few_fwd_kernel<bf16_t>, few, dim3(256), 0, (hipStream_t)stream, (const bf16_t *)x, (const bf16_t *)w, bias,
+                               (bf16_t *)y, desc->N, desc->C, desc->K);
+        else if (lanes)
+            hipLaunchKernelGGL(linear_few_fwd_kernel<float>, few, dim3(256), 0, (hipStream_t)stream, (const float *)x, (const float *)w, bias,
+                               (float *)y, desc->N, desc->C, desc->K);
+        else if (desc->dtype == NSK_BF16)
             hipLaunchKernelGGL(linear_small_fwd_kernel<bf16_t>, grid, dim3(256), 0, (hipStream_t)stream, (const bf16_t *)x,
                                (const bf16_t *)w, bias, (bf16_t *)y, desc->N, desc->C, desc->K);
         else
@@ -510,6 +632,17 @@ int nsk_linear_wgrad(const nsk_linear_desc_t *desc, const void *x, const void *d
     const nsk_conv_desc_t c = linear_as_conv(desc);
     TAIL_TRY(nsk_conv2d_wgrad(&c, x, dy, dw, accumulate, workspace, workspace_bytes, stream));
     if (db) {
+        const size_t need = (size_t)kBiasShares * desc->K * sizeof(float);
+        if (desc->N >= 6000 && desc->K >= 64 && desc->K % 4 == 0 && workspace && workspace_bytes >= need && !((uintptr_t)workspace & 15)) {
+            const int rows = (desc->N + kBiasShares - 1) / kBiasShares, shares = (desc->N + rows - 1) / rows;
+            const dim3 grid((unsigned)((desc->K + 63) / 64), (unsigned)shares);
+            if (desc->dtype == NSK_BF16)
+                hipLaunchKernelGGL(bias_partial_kernel<bf16_t>, grid, dim3(256), 0, (hipStream_t)stream, (const bf16_t *)dy, (float *)workspace, desc->N, desc->K, rows);
+            else
+                hipLaunchKernelGGL(bias_partial_kernel<float>, grid, dim3(256), 0, (hipStream_t)stream, (const float *)dy, (float *)workspace, desc->N, desc->K, rows);
+            hipLaunchKernelGGL(bias_final_kernel, dim3((unsigned)((desc->K + 15) / 16)), dim3(64), 0, (hipStream_t)stream, (const float *)workspace, db, shares, desc->K, accumulate);
+            return check_launch();
+        }
 #define NSK_BIAS(T, CB)                                                                                                  \
     hipLaunchKernelGGL((bias_grad_kernel<T, CB>), dim3((unsigned)((desc->K + CB - 1) / CB)), dim3(1024), 0, (hipStream_t)stream, \
                        (const T *)dy, db, desc->N, desc->K, accumulate)
@@ -656,6 +789,34 @@ int nsk_sumsq_accumulate(size_t n, const float *g, float *partials, float *sumsq
     if (nb > NSK_SUMSQ_PARTIALS) nb = NSK_SUMSQ_PARTIALS;
     hipLaunchKernelGGL(sumsq_partial_kernel, dim3((unsigned)nb), dim3(1024), 0, (hipStream_t)stream, n, g, partials);
     hipLaunchKernelGGL(sumsq_final_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, partials, (int)nb, sumsq);
+    return check_launch();
+}
+
+int nsk_clip_scale_multi(int count, const float *const *g, const size_t *n, float max_norm, float *partials, float *sumsq, float *scale, void *stream)
+{
+    if (count <= 0 || !(max_norm > 0.f)) return NSK_ERR_BAD_DESC;
+    if (!g || !n || !partials || !sumsq || !scale) return NSK_ERR_NULL;
+    if (unaligned(partials) || ((uintptr_t)sumsq & 3) || ((uintptr_t)scale & 3)) return NSK_ERR_ALIGNMENT;
+    size_t most = 0;
+    for (int i = 0; i < count; ++i) {
+        if (n[i] == 0) return NSK_ERR_BAD_DESC;
+        if (!g[i]) return NSK_ERR_NULL;
+        if (unaligned(g[i])) return NSK_ERR_ALIGNMENT;
+        if (n[i] > most) most = n[i];
+    }
+    size_t nb = (most + 1023) / 1024;
+    if (nb > NSK_SUMSQ_PARTIALS) nb = NSK_SUMSQ_PARTIALS;
+    for (int at = 0; at < count; at += kMaxSumsq) {
+        SumsqTable t{};
+        t.count = count - at < kMaxSumsq ? count - at : kMaxSumsq;
+        t.add = at > 0;
+        for (int i = 0; i < t.count; ++i) {
+            t.g[i] = g[at + i];
+            t.n[i] = n[at + i];
+        }
+        hipLaunchKernelGGL(sumsq_multi_kernel, dim3((unsigned)nb), dim3(1024), 0, (hipStream_t)stream, t, partials);
+    }
+    hipLaunchKernelGGL(clip_final_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, partials, (int)nb, max_norm, sumsq, scale);
     return check_launch();
 }
 

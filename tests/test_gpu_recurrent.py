@@ -208,3 +208,19 @@ def test_bf16_gru_classifier_tracks_the_oracle_and_learns():
     assert np.all(np.isfinite(losses)) and losses[-1] < 0.7 * losses[0]
     for k in ("table", "w_ih", "w_hh", "w_out"):
         assert torch.equal(m.w[k], m.master[k].to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("n,V", [(1024, 1500), (1025, 1500), (2048, 7), (9000, 1), (10000, 40000), (4097, 1024)])
+def test_embedding_gradient_with_many_matches(n, V):
+    """Around the line between one and eight chunks at a time, one row for everything (more matches than are kept at once), a vocabulary
+    that is no multiple of the blocks: the sum in position order, bit for bit."""
+    E = 40
+    g = torch.Generator().manual_seed(n + V)
+    tokens = torch.randint(0, V, (n,), generator=g, dtype=torch.int32)
+    dout = torch.randn((n, E), generator=g)
+    want = torch.zeros((V, E)).numpy()
+    for i, v in enumerate(tokens.tolist()):
+        want[v] += dout[i].numpy()
+    got = B.embedding_bwd(tokens.cuda(), dout.cuda(), V)
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), want)

@@ -297,3 +297,47 @@ def test_transpose2d_is_an_exact_copy(rows, cols, dtype):
     torch.cuda.synchronize()
     check()
     assert np.array_equal(host(view), a.T.astype(np.float64))
+
+
+@pytest.mark.parametrize("sizes", [(1,), (3, 5, 1024, 1025, 4099), tuple(range(1, 120))])
+def test_clip_of_many_tensors(sizes):
+    """One call for all gradients (two launches, more from 48 tensors on): the norm against 64 bits, the scale on both sides of one."""
+    grads = [torch.randn(n, device="cuda:0") for n in sizes]
+    norm = sum(float((g.double() ** 2).sum()) for g in grads) ** 0.5
+    for factor in (0.25, 4.0):
+        sumsq = torch.full((1,), float("nan"), device="cuda:0")
+        scale = B.clip_scale(grads, factor * norm, sumsq=sumsq)
+        torch.cuda.synchronize()
+        # squares in fp32, sums in 64 bits, two roundings on the way: 4 * 2^-24
+        assert abs(float(sumsq) - norm ** 2) <= 2.4e-7 * norm ** 2
+        assert abs(float(scale) - min(1.0, factor)) <= 5e-7
+    with pytest.raises(B.NskError):
+        B.clip_scale(grads + [torch.empty(0, device="cuda:0")], 1.0)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,K", [(5999, 64), (6000, 64), (6001, 100), (7000, 68), (9999, 772)])
+def test_bias_gradient_of_many_rows(N, K, dtype):
+    """Around the line from which the column sums take two launches: ragged shares of rows, columns that no block of 64 divides."""
+    g = torch.Generator(device="cuda:0").manual_seed(N)
+    x, dy = (torch.randn((N, c), generator=g, device="cuda:0").to(torch.bfloat16 if dtype == "bf16" else torch.float32) for c in (64, K))
+    want, size = dy.double().sum(0), dy.double().abs().sum(0)
+    dw, db = B.linear_wgrad(x, dy)
+    base = torch.randn(K, generator=g, device="cuda:0")
+    acc = base.clone()
+    B.linear_wgrad(x, dy, dw=dw.clone(), db=acc, accumulate=True)
+    torch.cuda.synchronize()
+    # float chains of at most 10 of the terms, the rest in 64 bits
+    assert ((db.double() - want).abs() <= 6e-7 * size).all()
+    assert ((acc.double() - base.double() - want).abs() <= 6e-7 * size + 1e-6).all()
+    assert (dw.double() - dy.double().t() @ x.double()).abs().max() <= 1e-5 * (dy.double().abs().t() @ x.double().abs()).max()
+
+
+@pytest.mark.parametrize("N,C,K", [(1, 128, 1), (3, 127, 5), (3, 129, 5), (64, 256, 64), (64, 200, 65), (50, 256, 2)])
+def test_few_outputs(N, C, K):
+    """Around the lines (4096 outputs, 128 channels) up to and from which sixteen lanes share an output."""
+    x, w, b = torch.randn(N, C, device="cuda:0"), torch.randn(K, C, device="cuda:0"), torch.randn(K, device="cuda:0")
+    y = B.linear_fwd(x, w, b)
+    torch.cuda.synchronize()
+    want = x.double() @ w.double().t() + b.double()
+    assert ((y.double() - want).abs() <= 2e-6 * (x.double().abs() @ w.double().abs().t() + b.double().abs())).all()
