@@ -10,8 +10,8 @@
 // which at 5 us of MFMA time does not matter.  No zero weight ever meets a real pixel (the fourth pixel is read from a
 // row of zeros, and so is everything past the end of a strip), so infinities stay where they belong.
 //
-// Measured (us, 256 channels at 28x28, N=128; direct kernels -> these): forward and backward-data 84.6 -> 30-35 (103 MB:
-// 3.0-3.4 TB/s), backward-weight 153.5 + 8.2 -> 45.0 + 4.8.
+// Measured (us, 256 channels at 28x28, N=128; direct kernels -> these): forward and backward-data 84.6 -> 31-34 (103 MB:
+// 3.0-3.4 TB/s; 14x14x512 16.2 -> 13.1 with eight wavefronts a block for four), backward-weight 153.5 + 8.2 -> 41 + 4.8.
 //
 // Work: a block is 64 channels (eight groups, two per wavefront) of a strip of full image rows.
 #include "nsk_internal.h"
@@ -22,6 +22,13 @@ namespace {
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// Eight wavefronts: four take two groups each, on every other run of pixels.  A run is a chain (addresses, LDS, three products,
+// rounding) that four wavefronts a block, two blocks a CU, do not fill (two runs at a time in four wavefronts 32.8 us, one 33.7,
+// eight wavefronts 31.4; sixteen 30.8, but 15.2 against 13.2 at 14x14).
+constexpr int G8_THREADS = 512;
 constexpr int G8_ENTRIES = 480;        // pixels of a strip with halo: 60 KB of LDS, two blocks per CU
 constexpr int G8_WG_ENTRIES = 600;     // backward-weight: with the strip of dy 75 KB, two blocks per CU
 
@@ -31,14 +38,13 @@ struct G8Args {
     int H, W, C, rows, strips, chunks;     // rows of a strip, strips of an image, 64-channel chunks
     unsigned src_bytes, wpk_bytes, out_bytes;
     unsigned long long taps;               // tap of window position 3*r + s, four bits each
-    int accumulate;
     Div by_pw, by_w;                       // W + 2, W
 };
 
 // The strip with its halo, rows of eight 16-byte pieces per pixel: piece p of entry e lies at p ^ swap(e).
-template <typename F> __device__ inline void stage(__amdgpu_buffer_rsrc_t rsrc, unsigned char *lds, int entries, int wave, int lane, F offset_of)
+template <int WAVES, typename F> __device__ inline void stage(__amdgpu_buffer_rsrc_t rsrc, unsigned char *lds, int entries, int wave, int lane, F offset_of)
 {
-    for (int i = wave; i * 8 < entries; i += 4) {
+    for (int i = wave; i * 8 < entries; i += WAVES) {
         const int e = i * 8 + (lane >> 3);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(lds + i * 1024), 16, (int)offset_of(e, lane & 7), 0, 0, 0);
     }
@@ -51,11 +57,11 @@ __device__ inline void direct_loads_done()
     __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void grouped8_kernel(const G8Args a)
+template <bool ACC> __global__ __launch_bounds__(G8_THREADS) void grouped8_kernel(const G8Args a)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int mover = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), wave = mover & 3;
     const int chunk = blockIdx.x % a.chunks, rest = blockIdx.x / a.chunks;
     const int strip = rest % a.strips, img = rest / a.strips;
     const int h0 = strip * a.rows, rows = min(a.rows, a.H - h0), PW = a.W + 2;
@@ -64,7 +70,7 @@ __global__ __launch_bounds__(256) void grouped8_kernel(const G8Args a)
     const __amdgpu_buffer_rsrc_t wpk_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.wpk, 0, a.wpk_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t out_rsrc = __builtin_amdgcn_make_buffer_rsrc(a.out, 0, a.out_bytes, 0x00020000);
     // sixteen neighbouring pixels are read at once: their pieces are exchanged so that they cover all banks
-    stage(src_rsrc, smem, entries, wave, lane, [&](int e, int slot) {
+    stage<G8_THREADS / 64>(src_rsrc, smem, entries, mover, lane, [&](int e, int slot) {
         const int er = divide(e, a.by_pw), h = h0 - 1 + er, w = e - er * PW - 1;
         const int ch = chunk * 64 + ((slot ^ (e >> 1)) & 7) * 8;
         const unsigned bad = (unsigned)((h | (a.H - 1 - h) | w | (a.W - 1 - w) | (a.C - 1 - ch) | (entries - 1 - e)) >> 31);
@@ -89,43 +95,49 @@ __global__ __launch_bounds__(256) void grouped8_kernel(const G8Args a)
     const int pixels = rows * a.W;
     const int ch = chunk * 64 + wave * 16 + (c & 1) * 4;                     // of the first group's results
     const unsigned pix0 = (unsigned)((img * a.H + h0) * a.W);
-    for (int l0 = 0; l0 < pixels; l0 += 16) {
+    const int first = chunk * 64 + wave * 16 + (c & 1) * 8;                  // of the channels that this lane stores
+    for (int l0 = (mover >> 2) * 16; l0 < pixels; l0 += G8_THREADS / 256 * 16) {
         const int l = l0 + m, row = divide(l, a.by_w), e0 = row * PW + (l - row * a.W) + c;
         const bool real = c < 3 && l < pixels;
-        const unsigned base = (pix0 + (unsigned)l) * (unsigned)a.C + (unsigned)ch;
-        unsigned at[2];
+        const unsigned pixel = (pix0 + (unsigned)l) * (unsigned)a.C;
         f32x4 acc[2];
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
-            at[g] = c < 2 && l < pixels && ch + 8 * g < a.C ? (base + 8u * g) * 2u : ~0u;
             acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        if (a.accumulate) {     // start from the old values: one rounding
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                const bf16x4 old = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(out_rsrc, (int)at[g], 0, 0));
+            if (ACC) {     // start from the old values: one rounding
+                const unsigned at = c < 2 && l < pixels && ch + 8 * g < a.C ? (pixel + (unsigned)(ch + 8 * g)) * 2u : ~0u;
+                const bf16x4 old = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(out_rsrc, (int)at, 0, 0));
 #pragma unroll
                 for (int j = 0; j < 4; ++j) acc[g][j] = (float)old[j];
             }
         }
+        bf16x8 b[3][2];
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
             const int e = real ? e0 + r * PW : zero;
             const unsigned char *p = smem + e * 128 + (((wave * 2) ^ (e >> 1)) & 7) * 16;
-            const bf16x8 b0 = *(const bf16x8 *)p;
-            const bf16x8 b1 = *(const bf16x8 *)(smem + ((unsigned)(p - smem) ^ 16u));
-            acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[0][r], b0, acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[1][r], b1, acc[1], 0, 0, 0);
+            b[r][0] = *(const bf16x8 *)p;
+            b[r][1] = *(const bf16x8 *)(smem + ((unsigned)(p - smem) ^ 16u));
         }
-        // lane (pixel, quarter): rows 4*quarter .. of the result; quarters 2 and 3 hold nothing
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int g = 0; g < 2; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[g][r], b[r][g], acc[g], 0, 0, 0);
+        // lane (pixel, quarter): rows 4*quarter .. of the result; quarters 2 and 3 hold nothing.  The halves of the two groups change
+        // places between quarters 0 and 1, so that a lane stores the eight channels of one group: a pixel's 32 bytes from this
+        // wavefront in one instruction
+        u32x2 o[2];
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
-            bf16x4 o;
+            bf16x4 r;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o[j] = (bf16_t)acc[g][j];
-            typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), out_rsrc, (int)at[g], 0, 0);
+            for (int j = 0; j < 4; ++j) r[j] = (bf16_t)acc[g][j];
+            o[g] = __builtin_bit_cast(u32x2, r);
         }
+        const u32x2 lo = __builtin_amdgcn_permlane16_swap(o[0][0], o[1][0], false, false);
+        const u32x2 hi = __builtin_amdgcn_permlane16_swap(o[0][1], o[1][1], false, false);
+        const unsigned to = c < 2 && l < pixels && first < a.C ? (pixel + (unsigned)first) * 2u : ~0u;
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{lo[0], hi[0], lo[1], hi[1]}, out_rsrc, (int)to, 0, 0);
     }
 }
 
@@ -144,11 +156,11 @@ struct G8WArgs {
 // within 32 lanes a transposing read serves the pixels 0..3 and 8..11 of a run, 32 bytes each: spread over all banks
 __device__ inline int g8_swap(int e) { return (e & 2) | ((e >> 1) & 4); }
 
-__global__ __launch_bounds__(256) void grouped8_wgrad_kernel(const G8WArgs a)
+__global__ __launch_bounds__(G8_THREADS) void grouped8_wgrad_kernel(const G8WArgs a)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int mover = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), wave = mover & 3, half = mover >> 2;
     const int chunk = blockIdx.x % a.chunks, split = blockIdx.x / a.chunks, PW = a.W + 2;
     const int dy_at = (((a.rows + 2) * PW + 7) & ~7) * 128, zero = dy_at + ((a.rows * a.W + 7) & ~7) * 128;   // bytes
     const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, a.x_bytes, 0x00020000);
@@ -164,14 +176,14 @@ __global__ __launch_bounds__(256) void grouped8_wgrad_kernel(const G8WArgs a)
         const int img = divide(tile, a.by_strips), h0 = (tile - img * a.strips) * a.rows, rows = min(a.rows, a.H - h0);
         const int entries = (rows + 2) * PW, pixels = rows * a.W;
         __syncthreads();   // everybody has read the strip before
-        for (int i = wave; i * 8 < entries; i += 4) {
+        for (int i = mover; i * 8 < entries; i += G8_THREADS / 64) {
             const int e = i * 8 + (lane >> 3), er = divide(e, a.by_pw), h = h0 - 1 + er, w = e - er * PW - 1;
             const int ch = chunk * 64 + ((lane & 7) ^ g8_swap(e)) * 8;
             const unsigned bad = (unsigned)((h | (a.H - 1 - h) | w | (a.W - 1 - w) | (a.C - 1 - ch) | (entries - 1 - e)) >> 31);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_void *)(smem + i * 1024), 16,
                                                      (int)(((unsigned)(((img * a.H + h) * a.W + w) * a.C + ch) * 2u) | bad), 0, 0, 0);
         }
-        for (int i = wave; i * 8 < pixels; i += 4) {
+        for (int i = mover; i * 8 < pixels; i += G8_THREADS / 64) {
             const int e = i * 8 + (lane >> 3);
             const int ch = chunk * 64 + ((lane & 7) ^ g8_swap(e)) * 8;
             const unsigned bad = (unsigned)(((a.C - 1 - ch) | (pixels - 1 - e)) >> 31);
@@ -182,7 +194,7 @@ __global__ __launch_bounds__(256) void grouped8_wgrad_kernel(const G8WArgs a)
         f32x4 acc[9];
 #pragma unroll
         for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int l0 = 0; l0 < pixels; l0 += 32) {
+        for (int l0 = 32 * half; l0 < pixels; l0 += 64) {
             bf16x4 d[2];
             int e[2];
             bool real[2];
@@ -210,6 +222,17 @@ __global__ __launch_bounds__(256) void grouped8_wgrad_kernel(const G8WArgs a)
 #pragma unroll
         for (int t = 0; t < 9; ++t) sum[t] += acc[t];      // (a strip's sum at a time: the chains stay short)
     }
+    // the second four wavefronts' sums through LDS
+    __syncthreads();
+    f32x4 *const other = (f32x4 *)smem + (size_t)(wave * 64 + lane);
+    if (half) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t) other[t * 256] = sum[t];
+    }
+    __syncthreads();
+    if (half) return;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) sum[t] += other[t * 256];
     // result rows 4*q + j = dy channel, column i16 = x channel of the wavefront's sixteen: same group on the diagonal blocks
     if ((q >> 1) == (i16 >> 3)) {
 #pragma unroll
@@ -278,11 +301,14 @@ int launch_grouped8(const IgemmArgs &a, hipStream_t stream)
     g.wpk_bytes = (unsigned)(g.C * 72 * 2);
     g.out_bytes = (unsigned)((long)a.Nimg * a.Ho * a.Wo * a.Co * 2);
     window_taps(a, a.add_h, a.add_w, &g.taps);
-    g.accumulate = a.accumulate;
     g.by_pw = make_div(g.W + 2);
     g.by_w = make_div(g.W);
     const size_t smem = (size_t)((((g.rows + 2) * (g.W + 2) + 7) & ~7) + 1) * 128;
-    hipLaunchKernelGGL(grouped8_kernel, dim3((unsigned)(a.Nimg * g.strips * g.chunks)), dim3(256), smem, stream, g);
+    const dim3 grid((unsigned)(a.Nimg * g.strips * g.chunks));
+    if (a.accumulate)
+        hipLaunchKernelGGL(grouped8_kernel<true>, grid, dim3(G8_THREADS), smem, stream, g);
+    else
+        hipLaunchKernelGGL(grouped8_kernel<false>, grid, dim3(G8_THREADS), smem, stream, g);
     return check_launch();
 }
 
@@ -320,11 +346,12 @@ int launch_grouped8_wgrad(const WgradArgs &a, hipStream_t stream)
     g.by_pw = make_div(g.W + 2);
     g.by_w = make_div(g.W);
     g.by_strips = make_div(g.strips);
-    const size_t smem = (size_t)((((g.rows + 2) * (g.W + 2) + 7) & ~7) + ((g.rows * g.W + 7) & ~7) + 1) * 128;
+    size_t smem = (size_t)((((g.rows + 2) * (g.W + 2) + 7) & ~7) + ((g.rows * g.W + 7) & ~7) + 1) * 128;
+    if (smem < 9 * 256 * sizeof(f32x4)) smem = 9 * 256 * sizeof(f32x4);      // the sums of half of the wavefronts
     static std::atomic<unsigned long long> done{0};
     const int rc = allow_lds((const void *)grouped8_wgrad_kernel, 80 * 1024, done);
     if (rc != NSK_OK) return rc;
-    hipLaunchKernelGGL(grouped8_wgrad_kernel, dim3((unsigned)(g.chunks * g.splits)), dim3(256), smem, stream, g);
+    hipLaunchKernelGGL(grouped8_wgrad_kernel, dim3((unsigned)(g.chunks * g.splits)), dim3(G8_THREADS), smem, stream, g);
     return check_launch();
 }
 
