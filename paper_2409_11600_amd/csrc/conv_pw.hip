@@ -18,8 +18,8 @@
 //     fp32 sums before the single rounding;
 //   * a forward launch can leave per-channel partial sums for the batch-norm behind it, and the launch for the one
 //     live class of a 1x1 stride-2 backward-data pass also writes the zeros of the other three pixels of each cell.
-// One block of 4 wavefronts per CU (the register file then allows two tiles of up to 256 channels per lane);
-// 256 persistent blocks.  This file holds the 64-channel-chunk instances, conv_pw_narrow16/32.hip the narrow ones.
+// One block of 4 wavefronts per CU (the register file then allows two tiles of up to 256 channels per lane), two for some
+// short reductions (pw_grid); 256 or 512 persistent blocks.  This file holds the 64-channel-chunk instances, conv_pw_narrow16/32.hip the narrow ones.
 #include <limits.h>
 
 #include "conv_pw_kernel.h"

@@ -348,21 +348,29 @@ inline int pw_cols(const IgemmArgs &a)
     return 0;
 }
 
-// Blocks of a launch: one a CU, two for the 3x3 filters of narrow outputs where every wavefront then still has a tile (their registers
-// allow it, and four wavefronts a CU leave most of the wait for the nine taps' loads exposed).  us, one / two: 16 -> 16 256 images
-// of 32x32 10.4 / 8.9, 128 of 56x56 14.6 / 11.5 (four blocks of 32-pixel tiles 11.2, but 14.4 with statistics against 13.4),
-// 32 -> 32 64 of 56x56 17.4 / 13.6.
 inline int pw_tile_rows(const IgemmArgs &a) { return a.Ngemm <= 32 && a.ntaps == 9 && a.Ktot == 288 ? 32 : 64; }
-inline int pw_grid(const IgemmArgs &a)
-{
-    return a.Ngemm <= 32 && a.ntaps == 9 && ceil_div(a.M, pw_tile_rows(a)) >= 2 * kPwGrid * 4 ? 2 * kPwGrid : kPwGrid;
-}
 
 inline size_t pw_smem(const IgemmArgs &a, int tm)
 {
     const int nw = pw_chunk(a), cols = pw_cols(a);
     return (size_t)(cols < 32 ? 32 : cols) * (a.Ktot * 2 + 16) +
            4 * (size_t)(32 * (a.accumulate ? nw * 4 + 16 : nw * 2 + 16) + (2 * a.ntaps + 2) * tm * 4);
+}
+
+// Blocks of a launch: one a CU, or two, where registers and LDS allow it, as four wavefronts a CU leave part of the load, multiply and
+// store phases of a tile exposed:
+//   * 3x3 filters of narrow outputs, while every wavefront then still has a tile.  us, one / two: 16 -> 16 256 images
+//     of 32x32 10.4 / 8.9, 128 of 56x56 14.6 / 11.5 (four blocks of 32-pixel tiles 11.2, but 14.4 with statistics against 13.4),
+//     32 -> 32 64 of 56x56 17.4 / 13.6;
+//   * one tap of at most 64 channels, from one tile per wavefront of the smaller grid.  us, one / two, with statistics, 56x56: 64 -> 64 21
+//     images 9.0 / 8.1, 64 images 16.3 / 14.3; 64 -> 256 64 images 42.9 / 33.5, 128 images 66.5 / 58.8; 32 -> 64 128 images
+//     19.6 / 15.5.  Operands beyond 300 MB stream better to one block a CU (64 -> 64 410 MB 76.3 / 77.4, 64 -> 128 617 MB 120 / 126), as do
+//     128 channels (128 -> 64 128 images 36.7 / 40.1).
+inline int pw_grid(const IgemmArgs &a)
+{
+    if (a.Ngemm <= 32) return a.ntaps == 9 && ceil_div(a.M, pw_tile_rows(a)) >= 2 * kPwGrid * 4 ? 2 * kPwGrid : kPwGrid;
+    const bool streams = (long)a.Nimg * a.Ho * a.Wo * a.Co * 2 + (long)a.src_bytes > 300000000L;
+    return a.ntaps == 1 && a.Ktot <= 64 && pw_cols(a) == a.Ngemm && ceil_div(a.M, 64) >= kPwGrid * 4 && !streams ? 2 * kPwGrid : kPwGrid;
 }
 
 template <int KS, int FM, int TAPS, bool ACC, int NW> int launch_pw_acc(PwArgs pa, hipStream_t stream)

@@ -1,5 +1,5 @@
-"""The 3x3 filters of 16- and 32-channel outputs on the short-reduction kernel: sizes around the line between one and two blocks a CU, ragged
-last tiles, with statistics, against torch in 64 bits on the device."""
+"""The short-reduction kernel around the lines between one and two blocks a CU: 3x3 filters of 16- and 32-channel outputs and 1x1 filters of 32 and
+64 channels, ragged last tiles, with statistics, against torch in 64 bits on the device."""
 import pytest
 import torch
 
@@ -33,5 +33,30 @@ def test_forward_backward_data_and_statistics(N, H, W, C, K):
     assert near(dx, dx64) and near(acc, dx64 + old.double())
     Y = y.double().reshape(-1, K)
     # sums of the values as stored: float chains of a few hundred
+    assert ((stats[0].double().sum(0) - Y.sum(0)).abs() <= 2e-5 * Y.abs().sum(0)).all()
+    assert ((stats[1].double().sum(0) - (Y * Y).sum(0)).abs() <= 2e-5 * (Y * Y).sum(0)).all()
+
+
+@pytest.mark.parametrize("N,H,W,C,K", [(21, 56, 56, 64, 64), (1, 257, 255, 64, 64), (1, 257, 255, 32, 128),    # one tile under and over the line
+                                       (32, 56, 57, 64, 256), (43, 57, 55, 64, 192), (64, 56, 56, 32, 64), (9, 113, 111, 256, 64),
+                                       (2, 181, 183, 64, 512)])                                              # 512: columns split
+def test_one_tap(N, H, W, C, K):
+    print(f"one tap {N}x{H}x{W} {C}->{K}", flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(N + H)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda:0")
+    x, w, dy, old = r(N, H, W, C).bfloat16(), (r(K, 1, 1, C) / C ** 0.5).bfloat16(), r(N, H, W, K).bfloat16(), r(N, H, W, C).bfloat16()
+    y, stats = B.conv2d_fwd_stats(x, w, 1, 0)
+    plain = B.conv2d_fwd(x, w, 1, 0)
+    dx = B.conv2d_dgrad(dy, w, (N, C, H, W), 1, 0)
+    acc = B.conv2d_dgrad(dy, w, (N, C, H, W), 1, 0, out=old.clone(), accumulate=True)
+    torch.cuda.synchronize()
+    assert torch.equal(y, plain)
+    w64 = w[:, 0, 0].double()
+    # one rounding to bf16 and fp32 sums of C (K) products
+    near = lambda a, b: ((a.double() - b).abs() <= 2.0 ** -8 * b.abs() + 1e-5).all()
+    assert near(y, x.double() @ w64.t())
+    dx64 = dy.double() @ w64
+    assert near(dx, dx64) and near(acc, dx64 + old.double())
+    Y = y.double().reshape(-1, K)
     assert ((stats[0].double().sum(0) - Y.sum(0)).abs() <= 2e-5 * Y.abs().sum(0)).all()
     assert ((stats[1].double().sum(0) - (Y * Y).sum(0)).abs() <= 2e-5 * (Y * Y).sum(0)).all()
