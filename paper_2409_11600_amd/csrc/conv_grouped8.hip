@@ -1,5 +1,5 @@
 // Grouped 3x3 stride-1 layers with eight channels per group on both sides, bf16 (32 groups of 8 and their like): forward,
-// backward-data and backward-weight on the matrix units.
+// backward-data and backward-weight on the matrix units; and backward-weight of plain layers with 16 channels, by the same means.
 //
 // What bounds them: memory (the contraction is 72 indices long).  The direct kernels of conv_depthwise.hip do 2 x 72
 // two-element dot products per eight outputs and read every input vector nine times through the L1: 84 us per data pass
@@ -247,6 +247,106 @@ __global__ __launch_bounds__(G8_THREADS) void grouped8_wgrad_kernel(const G8WArg
     }
 }
 
+// ---- backward-weight of plain layers with 16 channels in and out: a wavefront's product above is then the layer's own, and the
+// pipelined split-K kernel, which stages every pixel of x once per tap and fills a quarter of its 64 rows, is bound by what
+// it stages.  Here a strip of x with its halo and the strip of dy lie in LDS once ([pixel][channel], 32 bytes a pixel, so that the
+// eight consecutive pixels that a transposing read serves at once are 256 bytes), and the eight wavefronts share the strip's runs
+// of 32 pixels.  What is left is a chain: launch, one load of a strip, 40 reads and 18 products a run, the sums through
+// LDS.  256 images of 32x32 with the reduction 19.5 -> 12.7 us, 512 images 29.9 -> 15.6 us.  (With 32 channels the partial sums are
+// four times as many: 256 images of 16x16 13.7 / 20.4 us, so these layers stay there.)
+struct NarrowWArgs {
+    const void *x, *dy;
+    float *part;
+    int H, W, rows, strips, tiles, splits;
+    unsigned bytes;
+    unsigned long long taps;
+    Div by_pw, by_w, by_strips;
+};
+
+constexpr int strip16(int entries) { return (entries * 32 + 1023) & ~1023; }     // bytes in LDS: whole direct loads
+
+__global__ __launch_bounds__(G8_THREADS) void narrow_wgrad_kernel(const NarrowWArgs a)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), PW = a.W + 2;
+    const int dy_at = strip16((a.rows + 2) * PW), zero = dy_at + strip16(a.rows * a.W);   // bytes
+    const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, a.bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t dy_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.dy, 0, a.bytes, 0x00020000);
+    if (threadIdx.x < 2) *(f32x4 *)(smem + zero + threadIdx.x * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const int q = lane >> 4, i16 = lane & 15, inner = (i16 & 3) * 8;
+    f32x4 sum[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) sum[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int tile = blockIdx.x; tile < a.tiles; tile += a.splits) {
+        const int img = divide(tile, a.by_strips), h0 = (tile - img * a.strips) * a.rows, rows = min(a.rows, a.H - h0);
+        const int entries = (rows + 2) * PW, pixels = rows * a.W;
+        __syncthreads();   // everybody has read the strip before
+        for (int i = wave; i * 32 < entries; i += G8_THREADS / 64) {
+            const int e = i * 32 + (lane >> 1), er = divide(e, a.by_pw), h = h0 - 1 + er, w = e - er * PW - 1;
+            const unsigned bad = (unsigned)((h | (a.H - 1 - h) | w | (a.W - 1 - w) | (entries - 1 - e)) >> 31);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_void *)(smem + i * 1024), 16,
+                                                     (int)((unsigned)(((img * a.H + h) * a.W + w) * 32 + (lane & 1) * 16) | bad), 0, 0, 0);
+        }
+        for (int i = wave; i * 32 < pixels; i += G8_THREADS / 64) {
+            const int e = i * 32 + (lane >> 1);
+            const unsigned bad = (unsigned)((pixels - 1 - e) >> 31);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(dy_rsrc, (lds_void *)(smem + dy_at + i * 1024), 16,
+                                                     (int)((unsigned)(((img * a.H + h0) * a.W + e) * 32 + (lane & 1) * 16) | bad), 0, 0, 0);
+        }
+        direct_loads_done();
+        f32x4 acc[9];
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int l0 = 32 * wave; l0 < pixels; l0 += G8_THREADS / 2) {
+            bf16x4 d[2];
+            int e[2];
+            bool real[2];
+#pragma unroll
+            for (int hi = 0; hi < 2; ++hi) {
+                const int l = l0 + 16 * hi + 4 * q + (i16 >> 2), row = divide(l, a.by_w);
+                real[hi] = l < pixels;
+                e[hi] = row * PW + (l - row * a.W);
+                d[hi] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(smem + (real[hi] ? dy_at + l * 32 : zero) + inner));
+            }
+            const bf16x8 af = __builtin_shufflevector(d[0], d[1], 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                bf16x4 b[2];
+#pragma unroll
+                for (int hi = 0; hi < 2; ++hi) {
+                    const int at = real[hi] ? (e[hi] + (t / 3) * PW + t % 3) * 32 : zero;
+                    b[hi] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(smem + at + inner));
+                }
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, __builtin_shufflevector(b[0], b[1], 0, 1, 2, 3, 4, 5, 6, 7), acc[t], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 9; ++t) sum[t] += acc[t];      // (a strip's sum at a time: the chains stay short)
+    }
+    // the wavefronts' sums through LDS: the second four add to the first four, then all threads add up those
+    f32x4 *const red = (f32x4 *)smem, *const mine = red + (wave & 3) * 576 + lane;
+    __syncthreads();
+    if (wave >= 4) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t) mine[t * 64] = sum[t];
+    }
+    __syncthreads();
+    if (wave < 4) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t) mine[t * 64] += sum[t];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 576; i += G8_THREADS) {
+        const f32x4 v = (red[i] + red[576 + i]) + (red[2 * 576 + i] + red[3 * 576 + i]);
+        // rows 4 * (lane / 16) + j = dy channel, column lane % 16 = x channel
+        const int l = i & 63, tap = (int)(a.taps >> (4 * (i >> 6))) & 15;
+        float *const to = a.part + ((size_t)blockIdx.x * 16 + (l >> 4) * 4) * 144 + tap * 16 + (l & 15);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) to[j * 144] = v[j];
+    }
+}
+
 // Rows of a strip so that `per_row` * rows + `fixed` entries stay within `most`; balanced over the image.
 int strip_rows(int H, int per_row, int fixed, int most)
 {
@@ -352,6 +452,54 @@ int launch_grouped8_wgrad(const WgradArgs &a, hipStream_t stream)
     const int rc = allow_lds((const void *)grouped8_wgrad_kernel, 80 * 1024, done);
     if (rc != NSK_OK) return rc;
     hipLaunchKernelGGL(grouped8_wgrad_kernel, dim3((unsigned)(g.chunks * g.splits)), dim3(G8_THREADS), smem, stream, g);
+    return check_launch();
+}
+
+// Rows of a strip of a plain layer: two blocks' strips fit a CU, and there are no fewer strips than CUs
+static int narrow_rows(const WgradArgs &a)
+{
+    const int rows = strip_rows(a.H, (2 * a.W + 2) * 32, 2 * (a.W + 2) * 32 + 3 * 1024, 78 * 1024), strips = ceil_div(256, a.Nimg);
+    return ceil_div(a.H, strips) < rows ? ceil_div(a.H, strips) : rows;
+}
+
+// From 65536 pixels in strips of at least 256 on (us with the reduction, here / pipelined kernel: 64 images of 32x32 8.3 / 10.1, 32
+// images 8.0 / 7.9, 4 of 112x112 8.5 / 8.7, 256 of 16x16 8.4 / 10.1, 2048 of 8x8 14.4 / 13.1).
+bool narrow_wgrad_applicable(int dtype, const WgradArgs &a)
+{
+    unsigned long long taps;
+    if (dtype != NSK_BF16 || a.groups > 1 || a.C != 16 || a.K != 16 || a.act || hooks().no_grouped8) return false;
+    if (a.sh != 1 || a.sw != 1 || a.P != a.H || a.Q != a.W || (long)a.L * 32 >= 0xF0000000L) return false;
+    return window_taps(a, -a.ph, -a.pw, &taps) && a.L >= 65536 && narrow_rows(a) * a.W >= 256 && al16(a.x) && al16(a.dy);
+}
+
+// A block a CU; up to 131072 pixels half as many, whose partial sums are half as long (64 images of 32x32 9.0 / 8.3 us, 128 images
+// 9.8 / 9.4, 256 images 12.7 / 13.2).
+int narrow_wgrad_splits(const WgradArgs &a)
+{
+    const int tiles = a.Nimg * ceil_div(a.H, narrow_rows(a)), most = a.L <= 131072 ? 128 : 256;
+    return tiles < most ? tiles : most;
+}
+
+int launch_narrow_wgrad(const WgradArgs &a, hipStream_t stream)
+{
+    NarrowWArgs g{};
+    g.x = a.x; g.dy = a.dy; g.part = a.part;
+    g.H = a.H; g.W = a.W;
+    g.rows = narrow_rows(a);
+    g.strips = ceil_div(a.H, g.rows);
+    g.tiles = a.Nimg * g.strips;
+    g.splits = a.splits;
+    g.bytes = (unsigned)((long)a.L * 32);
+    window_taps(a, -a.ph, -a.pw, &g.taps);
+    g.by_pw = make_div(g.W + 2);
+    g.by_w = make_div(g.W);
+    g.by_strips = make_div(g.strips);
+    size_t smem = (size_t)strip16((g.rows + 2) * (g.W + 2)) + strip16(g.rows * g.W) + 32;
+    if (smem < 4 * 576 * sizeof(f32x4)) smem = 4 * 576 * sizeof(f32x4);      // the sums of half of the wavefronts
+    static std::atomic<unsigned long long> done{0};
+    const int rc = allow_lds((const void *)narrow_wgrad_kernel, 80 * 1024, done);
+    if (rc != NSK_OK) return rc;
+    hipLaunchKernelGGL(narrow_wgrad_kernel, dim3((unsigned)g.splits), dim3(G8_THREADS), smem, stream, g);
     return check_launch();
 }
 

@@ -121,6 +121,7 @@ struct ConvPlan {
     bool halo = false;   // wgrad: the 3x3 64->64 kernel writes one partial per block
     bool pipe = false;   // wgrad: the pipelined kernel
     bool grouped8 = false;   // wgrad: the kernel for groups of eight channels
+    bool narrow = false;     // wgrad: the 3x3 kernel for 16 channels
     bool stem = false;   // the space-to-depth path plans its own workspace
     size_t act_tmp = 0;  // fused-activation calls on a kernel without the fused load: the applied activation
     bool act_fused = false;
@@ -189,10 +190,13 @@ ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = fal
             one.groups = groups; one.ldx = g.C; one.ldy = g.K;
             one.splits = 1;
             p.grouped8 = grouped8_wgrad_applicable(g.dtype, one);
-            const bool direct = p.grouped8 || tiny_wgrad_applicable(g.dtype, one) || (!hooks().no_depthwise && depthwise_wgrad_applicable(g.dtype, one));
+            p.narrow = narrow_wgrad_applicable(g.dtype, one);
+            const bool direct = p.grouped8 || p.narrow || tiny_wgrad_applicable(g.dtype, one) || (!hooks().no_depthwise && depthwise_wgrad_applicable(g.dtype, one));
             p.pipe = !direct && wgrad_pipe_applicable(g.dtype, one.C, one.K, groups);
             if (p.grouped8)
                 p.splits = grouped8_wgrad_splits(one);
+            else if (p.narrow)
+                p.splits = narrow_wgrad_splits(one);
             else if (p.pipe)
                 p.rows_per_split = wgrad_pipe_rows_per_split(g.dtype, one.L, one.K, one.ntaps * one.C, groups, &p.splits);
             else
@@ -730,6 +734,8 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
         NSK_TRY(launch_wgrad_pipe(g.dtype, a, st));
     else if (p.grouped8)
         NSK_TRY(launch_grouped8_wgrad(a, st));
+    else if (p.narrow)
+        NSK_TRY(launch_narrow_wgrad(a, st));
     else
         NSK_TRY(launch_wgrad(g.dtype, a, st));
     const long RS = (long)g.R * g.S;

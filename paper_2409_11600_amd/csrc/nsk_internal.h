@@ -265,6 +265,10 @@ int launch_depthwise_wgrad(int dtype, const WgradArgs &a, hipStream_t stream);
 bool grouped8_wgrad_applicable(int dtype, const WgradArgs &a);
 int grouped8_wgrad_splits(const WgradArgs &a);
 int launch_grouped8_wgrad(const WgradArgs &a, hipStream_t stream);
+// plain bf16 3x3 stride-1 layers with 16 channels in and out: likewise
+bool narrow_wgrad_applicable(int dtype, const WgradArgs &a);
+int narrow_wgrad_splits(const WgradArgs &a);
+int launch_narrow_wgrad(const WgradArgs &a, hipStream_t stream);
 // dw[k*sk + t*st + c*sc] (=|+=) sum_s part[s][k][t][c], k < K, c < C, fixed order; part is [splits][Kp][ntaps][Cp].
 int launch_wgrad_reduce(const float *part, float *dw, int splits, int K, int Kp, int ntaps, int C, int Cp,
                         long sk, long st, long sc, int accumulate, hipStream_t stream);
