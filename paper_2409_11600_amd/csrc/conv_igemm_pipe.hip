@@ -95,16 +95,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
     // 32 images 22.6 / 20.2, 29.1 / 23.0; 64 images, filter 1.5 times src, 29.2 / 29.5, 33.9 / 31.8).
     int bm, bn;
     {
-        const int total = tiles_m * tiles_n, x = blockIdx.x & 7, i = blockIdx.x >> 3;
+        const int total = tiles_m * tiles_n, x = blockIdx.x & 7;
         const int q = total >> 3, r = total & 7;
-        const int t = x * q + min(x, r) + i;
-        if (a.wpk_bytes > a.src_bytes && tiles_n >= 8) {
-            bn = t / tiles_m;
-            bm = t - bn * tiles_m;
-        } else {
-            bm = t / tiles_n;
-            bn = t - bm * tiles_n;
-        }
+        const int t = x * q + min(x, r) + ((int)blockIdx.x >> 3);
+        const bool cols = a.wpk_bytes > a.src_bytes && tiles_n >= 8;
+        const int n = cols ? tiles_m : tiles_n, o = t / n, i = t - o * n;
+        bm = cols ? i : o;
+        bn = cols ? o : i;
     }
     const int m0 = bm * BM, n0 = bn * BN;
     const int grp = blockIdx.z, ld = a.src_ld;
