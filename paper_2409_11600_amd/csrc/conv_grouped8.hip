@@ -10,8 +10,8 @@
 // which at 5 us of MFMA time does not matter.  No zero weight ever meets a real pixel (the fourth pixel is read from a
 // row of zeros, and so is everything past the end of a strip), so infinities stay where they belong.
 //
-// Measured (us, 256 channels at 28x28, N=128; direct kernels -> these): forward and backward-data 84.6 -> 31-34 (103 MB:
-// 3.0-3.4 TB/s; 14x14x512 16.2 -> 13.1 with eight wavefronts a block for four), backward-weight 153.5 + 8.2 -> 41 + 4.8.
+// Measured (us, 256 channels at 28x28, N=128; direct kernels -> these): forward and backward-data 84.6 -> 25 (107 MB:
+// 4.3 TB/s; 14x14x512 16.2 -> 13.1 with eight wavefronts a block for four), backward-weight 153.5 + 8.2 -> 38.6 + 4.9.
 //
 // Work: a block is 64 channels (eight groups, two per wavefront) of a strip of full image rows.
 #include "nsk_internal.h"
