@@ -38,10 +38,10 @@ constexpr int kPwGrid = 256;            // blocks (see pw_grid); a shape propert
 constexpr unsigned PW_OOB = 0xF0000000u;  // beyond every buffer: loads return zero, stores are dropped
 constexpr int PW_MAX_NCH = 4;           // column chunks of 64 (Ngemm <= 256)
 
-constexpr int pw_blocks_per_cu(int ks, int fm, int nw) { return nw >= 64 || ks * fm > 18 ? 1 : ks * fm > 9 ? 2 : 4; }
+constexpr int pw_blocks_per_cu(int taps, int nw) { return nw < 64 && taps == 9 ? 2 : 1; }   // (the registers they may have)
 
 template <int KS, int FM, int TAPS, bool ACC, int NW>
-__global__ __launch_bounds__(256, pw_blocks_per_cu(KS, FM, NW)) void conv_pw_kernel(const PwArgs pa)
+__global__ __launch_bounds__(256, pw_blocks_per_cu(TAPS, NW)) void conv_pw_kernel(const PwArgs pa)
 {
     const IgemmArgs &a = pa.g;
     constexpr int NCH = NW == 64 ? PW_MAX_NCH : 1;   // chunks
@@ -77,18 +77,27 @@ __global__ __launch_bounds__(256, pw_blocks_per_cu(KS, FM, NW)) void conv_pw_ker
     const int rb = ((int)blockIdx.x & 7) + 8 * (((int)blockIdx.x >> 3) / pa.col_groups);
     const int n_rb = (int)gridDim.x / pa.col_groups;      // row shares
     const int col0 = cg * pa.cols;                        // first output channel of this block
-    // (the first pieces are requested here and stored behind the request of the first tile, so that a block waits for memory once)
+    // Nine taps, and wide filters: the first pieces are requested here and stored behind the request of the first tile, so that a block
+    // waits for memory once (64 -> 256 1x1, 64 images of 56x56, 31.1 -> 30.1 us).  With small filters that order is slower (64 -> 32
+    // 1x1, 256 images of 32x32, 11.4 -> 12.2 us).
+    constexpr bool EARLY = TAPS == 9 || (NW == 64 && KS >= 4);
     constexpr int FL = 6;
+    const int pieces = w_rows * (2 * KS);
     u32x4 fv[FL];
     auto filter_at = [&](int idx) -> u32x4 {
         const int n = idx / (2 * KS), ch = idx % (2 * KS);
         return __builtin_amdgcn_raw_buffer_load_b128(wpk_rsrc, n < pa.cols ? (unsigned)(((col0 + n) * KS * 16 + ch * 8) * 2) : PW_OOB, 0, 0);
     };
     auto filter_to_lds = [&](int idx, u32x4 v) {
-        if (idx < w_rows * (2 * KS)) *(u32x4 *)(w_lds + idx / (2 * KS) * WROW + idx % (2 * KS) * 16) = v;
+        if (idx < pieces) *(u32x4 *)(w_lds + idx / (2 * KS) * WROW + idx % (2 * KS) * 16) = v;
     };
+    if constexpr (EARLY) {
 #pragma unroll
-    for (int i = 0; i < FL; ++i) fv[i] = filter_at(tid + 256 * i);
+        for (int i = 0; i < FL; ++i) fv[i] = filter_at(tid + 256 * i);
+    } else {
+        for (int idx = tid; idx < pieces; idx += 256) filter_to_lds(idx, filter_at(idx));
+        lds_barrier();
+    }
 
     const int per_img = a.Mi * a.Mj;
     // Source (per tap) and output byte offsets of the tile's pixels (PW_OOB for rows past the end and for source
@@ -261,15 +270,17 @@ __global__ __launch_bounds__(256, pw_blocks_per_cu(KS, FM, NW)) void conv_pw_ker
         if constexpr (ACC) issue_old(O[0], 0, 0);
         issue(A0, 0);
     }
-    for (int at = tid;;) {
+    if constexpr (EARLY) {
+        for (int at = tid;;) {
 #pragma unroll
-        for (int i = 0; i < FL; ++i) filter_to_lds(at + 256 * i, fv[i]);
-        at += 256 * FL;
-        if (at - tid >= w_rows * (2 * KS)) break;
+            for (int i = 0; i < FL; ++i) filter_to_lds(at + 256 * i, fv[i]);
+            at += 256 * FL;
+            if (at - tid >= pieces) break;
 #pragma unroll
-        for (int i = 0; i < FL; ++i) fv[i] = filter_at(at + 256 * i);
+            for (int i = 0; i < FL; ++i) fv[i] = filter_at(at + 256 * i);
+        }
+        lds_barrier();
     }
-    lds_barrier();
     while (t < pa.tiles) {
         bool has_next = t + stride < pa.tiles;
         if (has_next) {

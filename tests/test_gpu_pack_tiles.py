@@ -1,5 +1,6 @@
-"""The filter packing of backward-data by tiles (both channel counts of at least 32 and whole vectors): channel counts that no tile
-divides, every residue class of a strided filter, grouped filters, against torch in 64 bits on the CPU."""
+"""The filter packing of backward-data by tiles (both channel counts of at least 32 and whole vectors, large filters) and by the gather
+(small ones): channel counts that no tile divides, every residue class of a strided filter, grouped filters, against torch in 64 bits
+on the CPU."""
 import pytest
 import torch
 
@@ -10,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("C,K,R,stride,groups", [(32, 32, 1, 1, 1), (40, 72, 3, 1, 1), (136, 40, 3, 2, 1), (64, 200, 2, 2, 1), (80, 64, 3, 1, 2),
+@pytest.mark.parametrize("C,K,R,stride,groups", [(32, 32, 1, 1, 1), (40, 72, 3, 1, 1), (136, 40, 3, 2, 1), (64, 200, 2, 2, 1), (80, 64, 3, 1, 2), (136, 144, 3, 1, 1), (520, 408, 2, 2, 1), (136, 120, 3, 1, 2),
                                                  (72, 32, 1, 2, 1), (24, 64, 3, 1, 1)])
 def test_backward_data(C, K, R, stride, groups, dtype):
     print(f"pack tiles {C}->{K} {R}x{R} stride {stride} groups {groups} {dtype}", flush=True)
