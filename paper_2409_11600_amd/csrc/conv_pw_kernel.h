@@ -336,7 +336,8 @@ __global__ __launch_bounds__(256, pw_blocks_per_cu(TAPS, NW)) void conv_pw_kerne
 #pragma unroll
                 for (int w = 0; w < 4; ++w) to[(size_t)(4 * rb + w) * a.Ngemm] = first[c + w * pitch];
             } else {
-                to[(size_t)rb * a.Ngemm] = (first[c] + first[c + pitch]) + (first[c + 2 * pitch] + first[c + 3 * pitch]);
+                // (in fp64, rounded once: sums in fp32 go no further than a wavefront's own pixels)
+                to[(size_t)rb * a.Ngemm] = (float)(((double)first[c] + (double)first[c + pitch]) + ((double)first[c + 2 * pitch] + (double)first[c + 3 * pitch]));
             }
         }
     }

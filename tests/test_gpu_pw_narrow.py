@@ -60,3 +60,19 @@ def test_one_tap(N, H, W, C, K):
     Y = y.double().reshape(-1, K)
     assert ((stats[0].double().sum(0) - Y.sum(0)).abs() <= 2e-5 * Y.abs().sum(0)).all()
     assert ((stats[1].double().sum(0) - (Y * Y).sum(0)).abs() <= 2e-5 * (Y * Y).sum(0)).all()
+
+
+@pytest.mark.parametrize("C,K,R,rows", [(64, 64, 1, 64), (16, 16, 3, 64), (32, 32, 3, 32)])
+def test_a_block_adds_its_wavefronts_in_64_bits(C, K, R, rows):
+    """A block's four wavefronts (tiles of `rows` pixels, one after the other) leave 2^24, 1, -2^24 and 0 in its row of statistics: in fp32 the
+    1 would be lost, in 64 bits nothing is."""
+    N, H, W = 128, 32, 32
+    big = 2.0 ** 24 / rows
+    x = torch.zeros(N * H * W // (4 * rows), 4, rows, C, dtype=torch.bfloat16, device="cuda:0")
+    x[:, 0], x[:, 1, 5], x[:, 2] = big, 1.0, -big
+    w = torch.zeros(K, R, R, C, dtype=torch.bfloat16, device="cuda:0")
+    w[:, R // 2, R // 2] = torch.eye(K)
+    y, stats = B.conv2d_fwd_stats(x.view(N, H, W, C), w, 1, R // 2)
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(-1), x.view(-1))
+    assert (stats[0].double().sum(0) == x.shape[0]).all()
