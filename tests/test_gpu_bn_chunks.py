@@ -112,3 +112,18 @@ def test_in_place(shape):
         dx2, _, dg2, db2 = B.bn_relu_add_bwd(x, out, g, gamma, m, i, dx=g)
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in ((out, out2), (m, m2), (i, i2), (dx, dx2), (dg, dg2), (db, db2)))
+
+
+def test_float_chains_of_a_large_tensor():
+    """Values v = 1 + 2^-10 behind a first row of zeros: v and v*v add up without an error in fp32 chains of 16 terms, not of 32 (v*v has 20
+    bits behind the point).  The variance is v*v / M (1 - 1/M), 5e5 times smaller than the sums it comes from: with chains of at
+    most 16 only the block with the first row rounds (2^-24 of 2048 / M of the sum: 1.2e-4 of the variance)."""
+    N, H, W, C = 128, 64, 64, 64
+    M, v = N * H * W, 1 + 2.0 ** -10
+    x = torch.full((N, H, W, C), v, device="cuda:0")
+    x[0, 0, 0] = 0
+    _, m, i = B.bn_relu_add_fwd(x, torch.ones(C, device="cuda:0"), torch.zeros(C, device="cuda:0"), eps=0.0)
+    torch.cuda.synchronize()
+    assert torch.allclose(m.double(), torch.full_like(m, 1.0).double() * v * (1 - 1 / M), rtol=1e-6)
+    want = (v * v / M * (1 - 1 / M)) ** -0.5
+    assert ((i.double() - want).abs() <= 1e-3 * want).all()
