@@ -108,7 +108,8 @@ int nsk_last_hip_error(void);
  *   NSK_HALO_WIDE_ALWAYS, NSK_HALO64_ALWAYS (set = chosen also where it does not pay);
  *   NSK_PW_MIN_ROWS, NSK_WH_MIN_ROWS = n   (size threshold of a special kernel);
  *   NSK_IGEMM_TILE = 1..6                           (tile shape of the generic kernel, which then takes every plain layer);
- *   NSK_GRU_SPLIT = 1, 2, 4                         (most blocks that share a sample of nsk_gru_seq_*). */
+ *   NSK_GRU_SPLIT = 1, 2, 4                         (most blocks that share a sample of nsk_gru_seq_*);
+ *   NSK_GRU_POLLS = n                               (failed polls after which such a block gives up; 0: at its first wait). */
 void nsk_test_hooks_reload(void);
 
 /* Output extent of a convolution.  Host only.  NSK_ERR_BAD_DESC if the descriptor is invalid
@@ -422,10 +423,15 @@ int nsk_gru_step_bwd(int dtype, int N, int H, const void *saved, const void *h_p
 /* All T steps of the recurrence, forward and backward, in one call each (same gate convention, layouts and sizes as the
  * step calls, whose nsk_gru_step_supported also speaks for these; N*H elements must be a multiple of 16 bytes so that every
  * step's rows are aligned).  Up to 256 hidden units a call is a single launch in which a block runs one sample through all
- * steps or, above 192 units and for few samples, two or four blocks share one (a second launch before it then fills h[1..T],
- * or dgh, with the mark that the blocks wait on); above 256, it issues the T step launches.
+ * steps or, above 192 units and for few samples, two or four blocks share one (a launch before it then fills h[1..T],
+ * or dgh, with the mark that the blocks wait on); above 256, it issues the T step launches.  Blocks that share a sample have to be
+ * on the chip together.  With up to ten such launches at a time on one card they always get there; beyond, or where other work holds the
+ * compute units, a block that has waited about a second ends, and a launch behind runs its sample again in one block: the
+ * results are the same, the call takes that much longer.
+ * nsk_gru_seq_blocks: the blocks that share a sample of such a call on this stream now (1, 2, 4), 0 for sizes that are not one launch.
  * forward: gi [T,N,3H]; h [T+1,N,H] holds the initial state in h[0] and receives h[1..T]; saved [T,N,4H].
  * backward: dh_top [N,H] is the gradient of h[T]; dgi, dgh [T,N,3H] are written; dh_scratch [2,N,H] of `dtype` is scratch. */
+int nsk_gru_seq_blocks(int dtype, int N, int H, void *stream);
 int nsk_gru_seq_fwd(int dtype, int T, int N, int H, const void *gi, const void *w_hh, const float *b_ih, const float *b_hh,
                     void *h, void *saved, void *stream);
 int nsk_gru_seq_bwd(int dtype, int T, int N, int H, const void *saved, const void *h, const void *dh_top, const void *w_hh_t,

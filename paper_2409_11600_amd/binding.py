@@ -192,6 +192,8 @@ def lib() -> ctypes.CDLL:
         L.nsk_gru_step_fwd.argtypes = [ci, ci, ci, vp, vp, vp, vp, vp, vp, vp, vp]
         L.nsk_gru_step_bwd.restype = ci
         L.nsk_gru_step_bwd.argtypes = [ci, ci, ci, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+        L.nsk_gru_seq_blocks.restype = ci
+        L.nsk_gru_seq_blocks.argtypes = [ci, ci, ci, vp]
         L.nsk_gru_seq_fwd.restype = ci
         L.nsk_gru_seq_fwd.argtypes = [ci, ci, ci, ci, vp, vp, vp, vp, vp, vp, vp]
         L.nsk_gru_seq_bwd.restype = ci
@@ -235,7 +237,7 @@ EXPORTS = ("nsk_version", "nsk_test_hooks_reload", "nsk_status_string", "nsk_las
            "nsk_linear_dgrad", "nsk_linear_wgrad", "nsk_transpose2d", "nsk_softmax_xent_fwd", "nsk_softmax_xent_bwd",
            "nsk_sgd_momentum_step", "nsk_adamw_step", "nsk_sgd_momentum_step_multi", "nsk_adamw_step_multi", "nsk_sumsq_accumulate", "nsk_clip_scale", "nsk_clip_scale_multi",
            "nsk_embedding_fwd", "nsk_embedding_bwd", "nsk_gru_gates_fwd", "nsk_gru_gates_bwd",
-           "nsk_gru_step_supported", "nsk_gru_step_fwd", "nsk_gru_step_bwd", "nsk_gru_seq_fwd", "nsk_gru_seq_bwd",
+           "nsk_gru_step_supported", "nsk_gru_step_fwd", "nsk_gru_step_bwd", "nsk_gru_seq_blocks", "nsk_gru_seq_fwd", "nsk_gru_seq_bwd",
            "nsk_pool_create", "nsk_pool_get", "nsk_pool_put", "nsk_pool_cached", "nsk_pool_stats", "nsk_pool_destroy")
 NSK_POOL_DEVICE, NSK_POOL_HOST = 0, 1
 NSK_SUMSQ_PARTIALS = 256
@@ -911,6 +913,11 @@ def gru_step_bwd(saved, h_prev, w_hh_t, dh_a=None, dh_direct_next=None, dgh_next
                                   _ptr(dh_direct_next), _ptr(dgh_next), _ptr(w_hh_t), _ptr(dgi), _ptr(dgh), _ptr(dh_direct),
                                   _stream()), "nsk_gru_step_bwd")
     return dgi, dgh, dh_direct
+
+
+def gru_seq_blocks(dtype: torch.dtype, N: int, H: int) -> int:
+    """Blocks that share a sample of gru_seq_fwd and gru_seq_bwd on the current stream; 0: not one launch (H > 256)."""
+    return int(lib().nsk_gru_seq_blocks(NSK_BF16 if dtype == torch.bfloat16 else NSK_F32, int(N), int(H), _stream()))
 
 
 def gru_seq_fwd(gi, w_hh, b_ih, b_hh, h, saved):

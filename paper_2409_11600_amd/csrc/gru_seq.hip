@@ -9,15 +9,19 @@
 // for all T steps, some of it lies in LDS, and in fp32 above H = 192 the rest is read from L2 again in every step, while the
 // resident part is multiplied.
 //
-// G = 2, 4 or 8 (few samples): each block owns H/G of the hidden units, so its part of the weight stays on the CU and a step's
+// G = 2 or 4 (few samples): each block owns H/G of the hidden units, so its part of the weight stays on the CU and a step's
 // products take 1/G of the time; what it pays is an exchange per step.  The exchange goes through the output itself (h forward,
 // dgh backward): a fill launch puts a NaN that no step stores in front of it, a block's gate lanes store their units with
 // agent-scope atomics, and a wavefront of its own per vector polls the others' values until none of them is that NaN, so value
 // and flag arrive together (a store and the load that sees it take 0.5 us on one XCD, 0.6 us across; the members of a group
 // are blocks b, b + 8, ..: one XCD when blocks go round the eight).  The pollers are wavefronts of their own because a
 // wavefront's loads return in order: behind the elementwise operands, which come from HBM, every poll would wait for those.
-// Waiting ends: members of a group are dispatched one after the other and hold no more CUs than the XCD has (split_of), other
-// groups of the launch wait for nobody here, and a poller that has seen 2^24 polls fail in all goes on with NaN.
+// Waiting ends: members of a group are dispatched one after the other and hold no more CUs than the XCD has (split_of), and whole
+// groups wait for nobody else.  So of each launch at most one group an XCD, G - 1 blocks, waits for a block that has no CU yet: ten launches
+// at a time on one card leave CUs free for those.  With more, or where others hold the CUs for long, a poller that has seen kPolls polls
+// fail gives up and its block ends, which leaves the mark in that sample's last row; the others of the group then end the
+// same way.  A launch of the G = 1 kernel behind looks at the last rows and runs the samples that are not whole, from their first step:
+// same bits, so the call is right in any case, and such a sample costs that wait and the time without a split.
 //
 // Work inside a block of 512 (32 units: 256) multiplying threads: eight neighbouring lanes q share a hidden unit's dot products
 // (lane q takes the columns 4*(q + 8*m) ..), 64 (32) groups of lanes hold the units slot, slot + 64, ...; the lane sums run over
@@ -98,7 +102,7 @@ template <> struct SeqT<bf16_t> {
 };
 
 constexpr unsigned kUnset = 0xffffffffu;      // a NaN in fp32 and, twice, in bf16; NaNs that a step stores are 0x7fc0(0000)
-constexpr int kPolls = 1 << 24;               // failed polls of a wavefront before it gives up: several seconds
+constexpr int kPolls = 1 << 20;               // failed polls of a wavefront before it gives up: about a second
 // Polls cross the chip (650 ns there and back, whoever stores) and slow the stores that they wait for: a poll that comes too early
 // costs a second one, four on their way at a time cost 487 / 690 us where one alone costs 371 / 466.  So a poller sleeps before
 // its first poll of a step, in quarters of 64 clocks: 16 more after a first poll that failed, one less after every step
@@ -145,6 +149,8 @@ struct GruSeqArgs {
     void *h, *saved, *dgi, *dgh;
     int T, N, H;
     int G, HU;       // blocks per sample and units per block (1 and H where a block has the sample to itself)
+    int polls;       // failed polls of a wavefront before it gives up
+    bool unfinished; // G = 1: only the samples whose last row still holds the mark
 };
 
 // IU = units per thread, M = 4-column pieces per lane and gate; of the 3*IU (unit, gate) parts RS stay in registers, LS in LDS;
@@ -165,35 +171,49 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
     const int u0 = SPLIT ? blockIdx.x % (8 * a.G) / 8 * a.HU : 0, u1 = SPLIT ? min(u0 + a.HU, H) : H;
     if (SPLIT && n >= N) return;
     const long NH = (long)N * H;
+    __shared__ int halt[2];        // SPLIT: a poller gave up in a step (even, odd)
+    if constexpr (!SPLIT) {
+        if (a.unfinished) {
+            const int words = (BWD ? 3 : 1) * H * (int)sizeof(T) / 8;      // of the row that the last step leaves
+            const u64 *last = (const u64 *)(BWD ? (const T *)a.dgh + (long)n * 3 * H : (const T *)a.h + (long)a.T * NH + (long)n * H);
+            bool un = false;
+            for (int i = tid; i < words; i += MT) un |= unset<T>(last[i]);
+            if (!__syncthreads_or(un)) return;
+        }
+    }
 
     if (SPLIT && tid >= MT) {
         // a polling wavefront: vector g of the step, four columns per lane
         const int g = (tid - MT) >> 6, c = 4 * (tid & 63);
         const bool live = c < H;
-        int left = kPolls, wait = 0;
+        int left = a.polls, wait = 0;
         for (int step = 0; step < a.T; ++step) {
             if (step > 0 && live) {
                 const int t = BWD ? a.T - step : step;          // the row that the step before this one has left
                 const T *src = BWD ? (const T *)a.dgh + (long)t * 3 * NH + (long)n * 3 * H + g * H + c : (const T *)a.h + (long)t * NH + (long)n * H + c;
                 constexpr int W = sizeof(T) / 2;
-                u64 v[W];
+                u64 v[W] = {};
                 for (int i = 0; i < wait / 4; ++i) __builtin_amdgcn_s_sleep(1);
-                bool un, first = true;
-                do {
-                    un = false;
+                bool missing = true;
+                for (bool first = true; missing && left > 0; first = false) {
+                    bool un = false;
 #pragma unroll
                     for (int e = 0; e < W; ++e) v[e] = seen((const char *)src + 8 * e);
 #pragma unroll
                     for (int e = 0; e < W; ++e) un |= unset<T>(v[e]);
-                    un = __any(un) && --left > 0;
-                    if (un && first) wait = min(wait + kSleepUp, kSleepMost);
-                    first = false;
-                } while (un);
+                    missing = __any(un);
+                    if (missing) {
+                        --left;
+                        if (first) wait = min(wait + kSleepUp, kSleepMost);
+                    }
+                }
                 if (wait > 0) wait -= 1;
+                if (missing && c == 0) halt[step & 1] = 1;
 #pragma unroll
                 for (int e = 0; e < W; ++e) *(u64 *)((char *)(vec + (step & 1) * NV * HP + g * HP + c) + 8 * e) = v[e];
             }
             lds_barrier();
+            if (halt[step & 1]) return;
         }
         return;
     }
@@ -232,6 +252,7 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
     // (SPLIT: the second half is the pollers', who fill its first H columns at the second step; all read those past H)
     for (int i = tid; i < 2 * NV * HP; i += MT)
         if (!SPLIT || i < NV * HP || i % HP >= H) vec[i] = !BWD && SPLIT && i < H ? ((const T *)a.h)[(long)n * H + i] : (T)0.f;
+    if (SPLIT && tid < 2) halt[tid] = 0;
     if constexpr (!SPLIT) __syncthreads();
 
     // this lane's unit in the elementwise part
@@ -282,6 +303,7 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
         if constexpr (D == 1 || SPLIT) take();     // (waits here for what was requested; without a split the products come first)
         if constexpr (D == 1) operands(e[k], min(step + 1, a.T - 1));
         if constexpr (SPLIT) lds_barrier();
+        const int stop = SPLIT ? halt[buf] : 0;
         float acc[S];
 #pragma unroll
         for (int p = 0; p < S; ++p) acc[p] = 0.f;
@@ -314,6 +336,7 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
         constexpr int R = BWD ? IU : S;
 #pragma unroll
         for (int p = 0; p < R; ++p) acc[p] = sum8(acc[p]);
+        if (SPLIT && __builtin_amdgcn_readfirstlane(stop)) return;
         if constexpr (!(D == 1 || SPLIT)) take();
         T *vn = vec + (buf ^ 1) * NV * HP;
         if constexpr (!BWD) {
@@ -455,11 +478,16 @@ template <typename T, bool BWD, int M> int dispatch(GruSeqArgs &a, hipStream_t s
     constexpr bool F = sizeof(T) == 4;
     a.HU = ceil_div(a.H, a.G);
     if constexpr (M == 8) {
-        if constexpr (F) {
-            if (a.G == 4) return launch<T, BWD, 1, M, 3, 0, 64, true>(a, stream);
-            if (a.G == 2) return launch<T, BWD, 2, M, 4, 2, 64, true>(a, stream);
-        } else if (a.G == 4) {
-            return launch<T, BWD, 2, M, 6, 0, 32, true>(a, stream);
+        if (a.G > 1) {
+            int rc;
+            if constexpr (F)
+                rc = a.G == 4 ? launch<T, BWD, 1, M, 3, 0, 64, true>(a, stream) : launch<T, BWD, 2, M, 4, 2, 64, true>(a, stream);
+            else
+                rc = launch<T, BWD, 2, M, 6, 0, 32, true>(a, stream);
+            if (rc != NSK_OK || a.T == 1) return rc;       // (one step exchanges nothing)
+            a.G = 1;
+            a.HU = a.H;
+            a.unfinished = true;
         }
         return launch<T, BWD, 4, M, F ? 5 : 9, F ? 2 : 3, 64, false>(a, stream);
     } else if constexpr (M == 6) {
@@ -500,6 +528,12 @@ using namespace nsk;
 
 extern "C" {
 
+int nsk_gru_seq_blocks(int dtype, int N, int H, void *stream)
+{
+    if (N <= 0 || H <= 0 || (dtype != NSK_F32 && dtype != NSK_BF16) || !nsk_gru_step_supported(N, H) || !seq_kernel_takes(H)) return 0;
+    return split_of(dtype, N, H, (hipStream_t)stream);
+}
+
 int nsk_gru_seq_fwd(int dtype, int T, int N, int H, const void *gi, const void *w_hh, const float *b_ih, const float *b_hh,
                     void *h, void *saved, void *stream)
 {
@@ -513,6 +547,7 @@ int nsk_gru_seq_fwd(int dtype, int T, int N, int H, const void *gi, const void *
     if (seq_kernel_takes(H)) {
         GruSeqArgs a{};
         a.G = split_of(dtype, N, H, (hipStream_t)stream);
+        a.polls = hooks().gru_polls >= 0 ? hooks().gru_polls : kPolls;
         a.gi = gi; a.w = w_hh; a.b_ih = b_ih; a.b_hh = b_hh; a.h = h; a.saved = saved;
         a.T = T; a.N = N; a.H = H;
         return dispatch<false>(dtype, a, (hipStream_t)stream);
@@ -539,6 +574,7 @@ int nsk_gru_seq_bwd(int dtype, int T, int N, int H, const void *saved, const voi
     if (seq_kernel_takes(H)) {
         GruSeqArgs a{};
         a.G = split_of(dtype, N, H, (hipStream_t)stream);
+        a.polls = hooks().gru_polls >= 0 ? hooks().gru_polls : kPolls;
         a.saved_in = saved; a.h = (void *)h; a.dh_top = dh_top; a.w = w_hh_t; a.dgi = dgi; a.dgh = dgh;
         a.T = T; a.N = N; a.H = H;
         return dispatch<true>(dtype, a, (hipStream_t)stream);

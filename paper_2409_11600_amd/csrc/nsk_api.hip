@@ -454,6 +454,8 @@ void read_hooks()
     h.igemm_tile = tile > 0 ? (int)tile : 0;
     const long long split = num("NSK_GRU_SPLIT");
     h.gru_split = split > 0 ? (int)split : 0;
+    const long long polls = num("NSK_GRU_POLLS");
+    h.gru_polls = polls >= 0 && polls <= INT_MAX ? (int)polls : -1;
     g_hooks = h;
     g_hooks_read = true;
 }

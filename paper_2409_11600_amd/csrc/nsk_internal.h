@@ -78,6 +78,7 @@ struct TestHooks {
         wh_no_split;
     long long pw_min_rows, wh_min_rows;   // -1: not set
     int igemm_tile, gru_split;                              // 0: not set
+    int gru_polls;                                          // -1: not set
 };
 const TestHooks &hooks();
 

@@ -121,6 +121,27 @@ def test_blocks_that_share_a_sample(T, N, H, dtype, nsk_env):
         assert all(torch.equal(a, b) for a, b in zip(out, want))
 
 
+@pytest.mark.parametrize("polls", ["0", "3", "40"])
+@pytest.mark.parametrize("dtype,T,N,H", [("f32", 9, 50, 256), ("f32", 5, 70, 200), ("bf16", 9, 33, 256), ("bf16", 2, 3, 224), ("f32", 1, 3, 256)])
+def test_blocks_that_give_up_waiting(dtype, T, N, H, polls, nsk_env):
+    """A block that has waited too long ends (with a bound of 0 polls every block does, at its second step; with 3 and 40 some do, some
+    later, some never), and the call still gives every sample what one block computes: the same bits."""
+    print(f"gru give-up T={T} N={N} H={H} {dtype} polls={polls}", flush=True)
+    run, out = _sequence(T, N, H, dtype, 8910 + H)
+    nsk_env("NSK_GRU_SPLIT", "1")
+    run()
+    want = [o.clone() for o in out]
+    nsk_env("NSK_GRU_SPLIT", None)
+    nsk_env("NSK_GRU_POLLS", polls)
+    assert B.gru_seq_blocks(torch_dtype(dtype), N, H) > 1
+    for _ in range(3):
+        for o in (out[0][1:], *out[1:]):
+            o.zero_()
+        run()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, want))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_blocks_that_share_a_sample_with_nan(dtype):
     """A state that holds the very NaN that stands for "not there yet" (all ones), and infinity: the calls end, the sample's later
