@@ -109,16 +109,27 @@ def test_blocks_that_share_a_sample(T, N, H, dtype, nsk_env):
     a step without an exchange, part of a last block, all eight XCDs full at four and at two blocks, and one sample more."""
     print(f"gru split T={T} N={N} H={H} {dtype}", flush=True)
     run, out = _sequence(T, N, H, dtype, 8900 + H)
+    blocks = lambda: B.gru_seq_blocks(torch_dtype(dtype), N, H)
     nsk_env("NSK_GRU_SPLIT", "1")
+    assert blocks() == 1
     run()
     want = [o.clone() for o in out]
     for most in (None, "2"):
         nsk_env("NSK_GRU_SPLIT", most)
+        # (the route that is meant is the one that runs: bf16 samples are not shared by two)
+        two = 1 if dtype == "bf16" or N > 128 else 2
+        assert blocks() == (4 if N <= 64 and most is None else two)
         for o in (out[0][1:], *out[1:]):
             o.zero_()
         run()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(out, want))
+
+
+def test_sizes_that_are_not_shared():
+    blocks = lambda N, H, dt=torch.float32: B.gru_seq_blocks(dt, N, H)
+    assert blocks(50, 192) == blocks(50, 252) == blocks(50, 64, torch.bfloat16) == 1     # the weight fits a CU; rows of no whole 8-byte words
+    assert blocks(50, 260) == blocks(300, 256) == 0                                     # step launches; refused
 
 
 @pytest.mark.parametrize("polls", ["0", "3", "40"])
@@ -147,6 +158,7 @@ def test_blocks_that_share_a_sample_with_nan(dtype):
     """A state that holds the very NaN that stands for "not there yet" (all ones), and infinity: the calls end, the sample's later
     states hold NaN, the other samples' values are those without it."""
     T, N, H = 3, 3, 256
+    assert B.gru_seq_blocks(torch_dtype(dtype), N, H) == 4
     run, clean = _sequence(T, N, H, dtype, 8901)
     run()
     ones = torch.tensor([-1], dtype=torch.int32 if dtype == "f32" else torch.int16).view(torch_dtype(dtype))[0]
@@ -166,7 +178,9 @@ def test_blocks_that_share_a_sample_in_a_graph():
     want = [o.clone() for o in out]
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
+        captured = B.gru_seq_blocks(torch.float32, 50, 256)
         run()
+    assert captured == B.gru_seq_blocks(torch.float32, 50, 256) == 4
     for _ in range(3):
         for o in (out[0][1:], *out[1:]):
             o.zero_()
