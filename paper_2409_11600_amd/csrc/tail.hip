@@ -6,6 +6,8 @@
 // streaming code.  The fully connected layer runs on the convolution kernels (1x1 filter, 1x1 image).
 #include <math.h>
 
+#include <algorithm>
+
 #include "nsk_internal.h"
 
 namespace nsk {
@@ -496,6 +498,10 @@ int linear_check(const nsk_linear_desc_t *d)
     return NSK_OK;
 }
 
+// Bias gradient in two launches (bias_partial_kernel): from 6000 rows on
+bool bias_in_shares(const nsk_linear_desc_t *d) { return d->N >= 6000 && d->K >= 64 && d->K % 4 == 0; }
+size_t bias_share_bytes(const nsk_linear_desc_t *d) { return (size_t)kBiasShares * d->K * sizeof(float); }
+
 }  // namespace
 }  // namespace nsk
 
@@ -561,7 +567,8 @@ size_t nsk_linear_workspace_bytes(const nsk_linear_desc_t *desc, int pass)
 {
     if (linear_check(desc) != NSK_OK) return 0;
     const nsk_conv_desc_t c = linear_as_conv(desc);
-    return nsk_conv2d_workspace_bytes(&c, pass);
+    const size_t conv = nsk_conv2d_workspace_bytes(&c, pass);
+    return pass == NSK_PASS_WGRAD && bias_in_shares(desc) ? std::max(conv, bias_share_bytes(desc)) : conv;
 }
 
 int nsk_linear_fwd(const nsk_linear_desc_t *desc, const void *x, const void *w, const float *bias, void *y,
@@ -632,8 +639,8 @@ int nsk_linear_wgrad(const nsk_linear_desc_t *desc, const void *x, const void *d
     const nsk_conv_desc_t c = linear_as_conv(desc);
     TAIL_TRY(nsk_conv2d_wgrad(&c, x, dy, dw, accumulate, workspace, workspace_bytes, stream));
     if (db) {
-        const size_t need = (size_t)kBiasShares * desc->K * sizeof(float);
-        if (desc->N >= 6000 && desc->K >= 64 && desc->K % 4 == 0 && workspace && workspace_bytes >= need && !((uintptr_t)workspace & 15)) {
+        // (the size query has room for the shares; a call with less than it asked for, but enough for dw, gets the one launch)
+        if (bias_in_shares(desc) && workspace && workspace_bytes >= bias_share_bytes(desc) && !((uintptr_t)workspace & 15)) {
             const int rows = (desc->N + kBiasShares - 1) / kBiasShares, shares = (desc->N + rows - 1) / rows;
             const dim3 grid((unsigned)((desc->K + 63) / 64), (unsigned)shares);
             if (desc->dtype == NSK_BF16)

@@ -2,6 +2,8 @@
 momentum, AdamW, gradient clip) against the oracle in oracle/train.py, element by element on the same seeded inputs.
 Tolerances: the path's stated bars (1e-4 fp32, 2e-2 bf16 on values stored in bf16); optimizer state is float on
 both sides of the ABI and is held to 1e-5 (a handful of float operations per element against float64)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -333,6 +335,23 @@ def test_bias_gradient_of_many_rows(N, K, dtype):
     assert ((db.double() - want).abs() <= 6e-7 * size).all()
     assert ((acc.double() - base.double() - want).abs() <= 6e-7 * size + 1e-6).all()
     assert (dw.double() - dy.double().t() @ x.double()).abs().max() <= 1e-5 * (dy.double().abs().t() @ x.double().abs()).max()
+
+
+@pytest.mark.parametrize("N,C,K,dtype", [(6000, 12, 4096, torch.float32), (6001, 1, 768, torch.float32), (7000, 8, 1024, torch.bfloat16)])
+def test_bias_gradient_depends_on_the_sizes_alone(N, C, K, dtype):
+    """Few input channels, where the partial sums of dw need less than the shares of db: exactly the bytes that the library asks for, and
+    many more, give the same bits."""
+    x, dy = torch.randn(N, C, device="cuda:0").to(dtype), torch.randn(N, K, device="cuda:0").to(dtype)
+    desc = B.nsk_linear_desc_t(N, C, K, B._dtype_code(x))
+    need = B.lib().nsk_linear_workspace_bytes(ctypes.byref(desc), B.NSK_PASS_WGRAD)
+    got = []
+    for size in (need, need + (8 << 20)):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda:0")
+        dw, db = torch.empty(K, C, device="cuda:0"), torch.empty(K, device="cuda:0")
+        B._check(B.lib().nsk_linear_wgrad(ctypes.byref(desc), B._ptr(x), B._ptr(dy), B._ptr(dw), B._ptr(db), 0, B._ptr(ws), size, B._stream()), "")
+        torch.cuda.synchronize()
+        got.append((dw, db))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
 
 
 @pytest.mark.parametrize("N,C,K", [(1, 128, 1), (3, 127, 5), (3, 129, 5), (64, 256, 64), (64, 200, 65), (50, 256, 2)])
