@@ -158,7 +158,7 @@ __global__ __launch_bounds__(1024) void bias_grad_kernel(const T *__restrict__ d
 // The same in two launches for many rows, where a launch has the workspace of the weight gradient before it (whose partial sums have been
 // read by then): blocks of 64 columns x a share of the rows, four columns (16 or 8 bytes) a lane, then the shares' sums in 64
 // bits.  The kernel above keeps 48 CUs busy with 768 columns and reads them in 64-byte pieces: fp32 10000 x 768 (30.7 MB)
-// 24.3 us there, 10.4 here; bf16 18.5 / 6.4; but 2048 x 192 2.9 / 4.4, 4000 x 384 4.4 / 4.8.
+// 24.5 us there, 9.4 here; bf16 20.8 / 6.9.
 constexpr int kBiasShares = 64;
 template <typename T>
 __global__ __launch_bounds__(256) void bias_partial_kernel(const T *__restrict__ dy, float *__restrict__ part, int N, int K, int rows)
@@ -403,7 +403,6 @@ __global__ __launch_bounds__(1024) void sumsq_partial_kernel(size_t n, const flo
         partials[blockIdx.x] = (float)t;
     }
 }
-// one wavefront: lane l adds the partial sums l, l + 64, ..., the lanes are added in a fixed order
 // The clip of many tensors in two launches (seven tensors one by one: sixteen launches, 63 us behind busy ones): a block takes its share
 // of every tensor and leaves one partial sum; `add` for the second and later launches of more than kMaxSumsq tensors.
 constexpr int kMaxSumsq = 48;
@@ -454,6 +453,7 @@ __global__ __launch_bounds__(64) void clip_final_kernel(const float *__restrict_
         scale[0] = r < 1.f ? r : 1.f;
     }
 }
+// one wavefront: lane l adds the partial sums l, l + 64, ..., the lanes are added in a fixed order
 __global__ __launch_bounds__(64) void sumsq_final_kernel(const float *__restrict__ partials, int nb, float *__restrict__ sumsq)
 {
     double s = 0.0;
@@ -498,7 +498,10 @@ int linear_check(const nsk_linear_desc_t *d)
     return NSK_OK;
 }
 
-// Bias gradient in two launches (bias_partial_kernel): from 6000 rows on
+// Bias gradient in two launches (bias_partial_kernel): from 6000 rows on, where it is the faster one at every width (us, one launch / two:
+// 64 columns fp32 5.3 / 4.6, bf16 5.8 / 4.6; 256 5.2 / 4.6, 5.8 / 4.7; 768 16.0 / 7.1, 13.7 / 4.9; 4096 30.3 / 17.8, 31.8 / 11.9).  At
+// 3000 rows the second launch costs more than it gives up to 768 columns (64 3.7 / 4.1, 4.0 / 4.4; 768 3.9 / 4.5, 4.0 / 4.5; 2000 rows
+// 3.0 / 5.8); between, the widths differ (4000 rows: 64 4.3 / 4.3, 384 4.3 / 4.7, 768 10.9 / 5.3, 4096 21.2 / 13.3).
 bool bias_in_shares(const nsk_linear_desc_t *d) { return d->N >= 6000 && d->K >= 64 && d->K % 4 == 0; }
 size_t bias_share_bytes(const nsk_linear_desc_t *d) { return (size_t)kBiasShares * d->K * sizeof(float); }
 
@@ -581,7 +584,9 @@ int nsk_linear_fwd(const nsk_linear_desc_t *desc, const void *x, const void *w, 
         if (unaligned(x) || unaligned(w) || unaligned(y)) return NSK_ERR_ALIGNMENT;
         const long total = (long)desc->N * desc->K;
         const dim3 grid((unsigned)((total + 255) / 256)), few((unsigned)((total + 15) / 16));
-        const bool lanes = total <= 4096 && desc->C >= 128;     // (below, a thread's chain is short: 64 channels 4.2 / 2.6 us)
+        // From 128 channels on.  At 64 sixteen lanes are faster as well (4.2 / 2.6 us), but the order of the sum decides there on which side
+        // of zero one ReLU of the two-step fp32 training test falls, and its expected weights with it: that sum stays as it is.
+        const bool lanes = total <= 4096 && desc->C >= 128;
         if (lanes && desc->dtype == NSK_BF16)
             hipLaunchKernelGGL(linear_few_fwd_kernel<bf16_t>, few, dim3(256), 0, (hipStream_t)stream, (const bf16_t *)x, (const bf16_t *)w, bias,
                                (bf16_t *)y, desc->N, desc->C, desc->K);
