@@ -286,13 +286,13 @@ __global__ __launch_bounds__(G8_THREADS) void narrow_wgrad_kernel(const NarrowWA
             const int e = i * 32 + (lane >> 1), er = divide(e, a.by_pw), h = h0 - 1 + er, w = e - er * PW - 1;
             const unsigned bad = (unsigned)((h | (a.H - 1 - h) | w | (a.W - 1 - w) | (entries - 1 - e)) >> 31);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_void *)(smem + i * 1024), 16,
-                                                     (int)((unsigned)(((img * a.H + h) * a.W + w) * 32 + (lane & 1) * 16) | bad), 0, 0, 0);
+                                                     (int)(((unsigned)((img * a.H + h) * a.W + w) * 32u + (lane & 1) * 16u) | bad), 0, 0, 0);
         }
         for (int i = wave; i * 32 < pixels; i += G8_THREADS / 64) {
             const int e = i * 32 + (lane >> 1);
             const unsigned bad = (unsigned)((pixels - 1 - e) >> 31);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(dy_rsrc, (lds_void *)(smem + dy_at + i * 1024), 16,
-                                                     (int)((unsigned)(((img * a.H + h0) * a.W + e) * 32 + (lane & 1) * 16) | bad), 0, 0, 0);
+                                                     (int)(((unsigned)((img * a.H + h0) * a.W + e) * 32u + (lane & 1) * 16u) | bad), 0, 0, 0);
         }
         direct_loads_done();
         f32x4 acc[9];
