@@ -77,10 +77,14 @@ __global__ __launch_bounds__(256, pw_blocks_per_cu(TAPS, NW)) void conv_pw_kerne
     const int rb = ((int)blockIdx.x & 7) + 8 * (((int)blockIdx.x >> 3) / pa.col_groups);
     const int n_rb = (int)gridDim.x / pa.col_groups;      // row shares
     const int col0 = cg * pa.cols;                        // first output channel of this block
-    // Nine taps, and wide filters: the first pieces are requested here and stored behind the request of the first tile, so that a block
-    // waits for memory once (64 -> 256 1x1, 64 images of 56x56, 31.1 -> 30.1 us).  With small filters that order is slower (64 -> 32
-    // 1x1, 256 images of 32x32, 11.4 -> 12.2 us).
-    constexpr bool EARLY = TAPS == 9 || (NW == 64 && KS >= 4);
+    // Wide filters, and 32 channels x nine taps just packed by the launch before (backward-data): the first pieces are requested here and
+    // stored behind the request of the first tile, so that a block waits for memory once (64 -> 256 1x1, 64 images of 56x56, 31.1 ->
+    // 30.1 us; backward-data of 16 -> 32 3x3, 128 and 256 images of 32x32, 12.5 -> 12.1, 18.8 -> 17.7; 32 -> 32 3x3, 64 images of 16x16, 7.5 ->
+    // 7.0).  With small filters, and with those that lie in the caches from the pass before, that order is slower: 64 -> 32 1x1, 256
+    // images of 32x32, 11.4 -> 12.2; forward 16 -> 32 3x3 stride 2, 256 images of 32x32, 6.3 -> 6.8; 16 -> 16 3x3, 64 images, 4.4 -> 4.9;
+    // 32 -> 32 3x3 stride 2, 128 images, 7.2 -> 7.5.
+    constexpr bool MAY_EARLY = (TAPS == 9 && KS == 18) || (NW == 64 && KS >= 4);
+    const bool early = MAY_EARLY && (TAPS != 9 || a.packed);
     constexpr int FL = 6;
     const int pieces = w_rows * (2 * KS);
     u32x4 fv[FL];
@@ -91,7 +95,7 @@ __global__ __launch_bounds__(256, pw_blocks_per_cu(TAPS, NW)) void conv_pw_kerne
     auto filter_to_lds = [&](int idx, u32x4 v) {
         if (idx < pieces) *(u32x4 *)(w_lds + idx / (2 * KS) * WROW + idx % (2 * KS) * 16) = v;
     };
-    if constexpr (EARLY) {
+    if (early) {
 #pragma unroll
         for (int i = 0; i < FL; ++i) fv[i] = filter_at(tid + 256 * i);
     } else {
@@ -270,7 +274,7 @@ __global__ __launch_bounds__(256, pw_blocks_per_cu(TAPS, NW)) void conv_pw_kerne
         if constexpr (ACC) issue_old(O[0], 0, 0);
         issue(A0, 0);
     }
-    if constexpr (EARLY) {
+    if (early) {
         for (int at = tid;;) {
 #pragma unroll
             for (int i = 0; i < FL; ++i) filter_to_lds(at + 256 * i, fv[i]);

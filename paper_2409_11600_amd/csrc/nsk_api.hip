@@ -638,6 +638,7 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
             // packed filter of this class: [c][tap][k] with element (c, t, k) = w[c*sn + tap_off[t] + k*sc]
             a.src = src; a.wpk = ws + filt_off; a.out = dst;
             a.zero_cell = zero_cell ? 1 : 0;
+            a.packed = true;
             if (may_merge) {
                 for (int t = 0; t < kMaxTaps; ++t) pk_taps[n_pending][t] = t < nt ? tap_off[t] : 0;
                 pk_nt[n_pending] = nt;

@@ -152,6 +152,7 @@ struct IgemmArgs {
     // writes zeros to the other (up to three) pixels of each row's 2x2 output cell.  Only the short-reduction kernel
     // honours it: set it only after conv_pw_applicable() said yes for these arguments.
     int zero_cell;
+    bool packed;      // wpk was written by the launch before this one (backward-data)
     // Grouped convolution (groups > 1; 0 or 1 = plain): the launch computes `groups` independent problems of the
     // shape above.  Group g reads channels [g*Cs, (g+1)*Cs) of source pixels that are src_ld channels apart, the filter
     // rows [g*Ngemm, (g+1)*Ngemm) of wpk, and writes columns [g*Ngemm, (g+1)*Ngemm) of the Co-channel output pixels.
