@@ -267,10 +267,16 @@ def _ptr(t: Optional[torch.Tensor]):
     return t.data_ptr()
 
 
+# torch's own names for the current stream's raw handle, where this version has them
+_raw_stream, _current_device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+
+
 def _stream():
     """The raw handle of the current device's current stream (torch.cuda.current_stream() builds an object for it: 2.8 us of
-    the 11 us that a small convolution call took; this takes 0.1)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    the 11 us that a small convolution call took; the private call takes 0.1)."""
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _pair(v) -> Tuple[int, int]:

@@ -238,3 +238,17 @@ def test_kept_queries_follow_the_test_switches(nsk_env):
     nsk_env("NSK_NO_PAD", "1")
     plain = B._conv_call(*args, B.NSK_PASS_FWD)[4]
     assert plain == L.nsk_conv2d_workspace_bytes(ctypes.byref(d), B.NSK_PASS_FWD) and plain != padded
+
+
+def test_the_stream_without_torchs_private_names(monkeypatch):
+    """A version of torch that has another name for the raw handle: the public call's."""
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    for name in ("_raw_stream", "_current_device"):
+        with monkeypatch.context() as m:
+            m.setattr(B, name, None)
+            assert B._stream() == 77
+    monkeypatch.setattr(B, "_raw_stream", lambda device: 100 + device)
+    monkeypatch.setattr(B, "_current_device", lambda: 3)
+    assert B._stream() == 103
