@@ -232,7 +232,7 @@ __global__ __launch_bounds__(256) void linear_small_fwd_kernel(const T *__restri
 }
 
 // Few outputs (the output layer of a classifier): sixteen lanes share one, else its whole reduction is a chain of loads in one thread
-// and the launch a handful of wavefronts: 50 x 2 outputs of 256 channels 8.3 us with a thread each, 64 x 64 of 128 6.4, 2.7 here.
+// and the launch a handful of wavefronts: 50 x 2 outputs of 256 channels 8.3 us with a thread each, 2.4 here.
 template <typename T>
 __global__ __launch_bounds__(256) void linear_few_fwd_kernel(const T *__restrict__ x, const T *__restrict__ w, const float *__restrict__ bias,
                                                              T *__restrict__ y, int N, int C, int K)
@@ -585,7 +585,10 @@ int nsk_linear_fwd(const nsk_linear_desc_t *desc, const void *x, const void *w, 
         const long total = (long)desc->N * desc->K;
         const dim3 grid((unsigned)((total + 255) / 256)), few((unsigned)((total + 15) / 16));
         // From 128 channels on.  At 64 sixteen lanes are faster as well (4.2 / 2.6 us), but the order of the sum decides there on which side
-        // of zero one ReLU of the two-step fp32 training test falls, and its expected weights with it: that sum stays as it is.
+        // of zero one ReLU of the two-step fp32 training test falls, and its expected weights with it: that sum stays as it is.  Up to
+        // 4096 outputs, what the kernel was built for; beyond it would be faster too (us, a thread each / sixteen lanes, fp32: 64 x 64
+        // outputs of 128, 256, 1024 channels 6.3 / 2.5, 10.6 / 2.7, 36.8 / 4.0; 64 x 256 6.7 / 2.8, 11.5 / 3.3, 40.8 / 6.6; 64 x 1000 7.9 / 4.6, 13.1 / 6.4,
+        // 50.1 / 18.2; bf16 the same within 10%).
         const bool lanes = total <= 4096 && desc->C >= 128;
         if (lanes && desc->dtype == NSK_BF16)
             hipLaunchKernelGGL(linear_few_fwd_kernel<bf16_t>, few, dim3(256), 0, (hipStream_t)stream, (const bf16_t *)x, (const bf16_t *)w, bias,
