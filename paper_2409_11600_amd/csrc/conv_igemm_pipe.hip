@@ -53,6 +53,8 @@ constexpr int kMaxProblems = 4;
 template <int NP> struct PipeProblems {   // NP = 1 or kMaxProblems: a plain launch carries 400 bytes of arguments, not 1.7 KB
     IgemmArgs a[NP];
     int tiles_m[NP];
+    int cols[NP];      // the tiles of one column block follow each other, not those of one row block
+    Div by[NP];        // tiles_m or tiles_n accordingly
     int tiles_n;
 };
 
@@ -92,14 +94,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
     // the activation rows they share.  Where the filter is the larger operand, tiles of one column block: an XCD then reads
     // its columns' filter and all of src instead of the whole filter (3x3 on 7x7 images, rows / columns first, us: 1024
     // channels, 8 images 40.9 / 33.3 forward; 512 channels, 8 .. 16 images 22.4 / 16.5 forward, 29.2 / 20.8 backward-data;
-    // 32 images 22.6 / 20.2, 29.1 / 23.0; 64 images, filter 1.5 times src, 29.2 / 29.5, 33.9 / 31.8).
+    // 32 images 22.6 / 20.2, 29.1 / 23.0; 64 images, filter 1.5 times src, 29.2 / 29.5, 33.9 / 31.8).  Order and divisor come from the host: found
+    // here, with a division, they were 5% of a launch of many short blocks (backward-data of 16 -> 16 3x3 stride 2, 256 images of 32x32,
+    // 17.4 us; the division by tiles_n alone, without the second order, 16.4; this 16.2).
     int bm, bn;
     {
         const int total = tiles_m * tiles_n, x = blockIdx.x & 7;
         const int q = total >> 3, r = total & 7;
         const int t = x * q + min(x, r) + ((int)blockIdx.x >> 3);
-        const bool cols = a.wpk_bytes > a.src_bytes && tiles_n >= 8;
-        const int n = cols ? tiles_m : tiles_n, o = t / n, i = t - o * n;
+        const bool cols = pp.cols[prob] != 0;
+        const int n = cols ? tiles_m : tiles_n, o = divide(t, pp.by[prob]), i = t - o * n;
         bm = cols ? i : o;
         bn = cols ? o : i;
     }
@@ -508,6 +512,8 @@ template <typename T, int BM, int BN, int WM, int WN, int WK, int ST, int NP> in
     for (int j = 0; j < count; ++j) {
         pp.a[j] = a[j];
         pp.tiles_m[j] = ceil_div(a[j].M, BM);
+        pp.cols[j] = a[j].wpk_bytes > a[j].src_bytes && pp.tiles_n >= 8;
+        pp.by[j] = make_div(pp.cols[j] ? pp.tiles_m[j] : pp.tiles_n);
         if (pp.tiles_m[j] > most) most = pp.tiles_m[j];
     }
     hipLaunchKernelGGL((igemm_pipe_kernel<T, BM, BN, WM, WN, WK, ST, NP>), dim3((unsigned)most * pp.tiles_n, count, a[0].groups),
