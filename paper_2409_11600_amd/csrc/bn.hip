@@ -871,11 +871,27 @@ dim3 fast_apply_grid(const nsk_bn_desc_t &d, const Geom &g)
     const long passes = (g.M + fast_rows_at_once(d, g.vec) - 1) / fast_rows_at_once(d, g.vec);
     return dim3((unsigned)std::max(1L, std::min<long>(passes, 256 / fast_chunks(d))), fast_chunks(d));
 }
-// More rows of statistics than an apply block reads beside its work (512 KB: 5 us), or than a launch between finishes column by column,
-// are folded first, into at most 64 rows by enough blocks
+// Forward, its own statistics: the sums in chunks pay where 512 blocks over whole rows would leave many of them to the launch between, or
+// the tensor is large; below, two launches of 1024 threads a block with their sums in LDS take longer than the three of the other
+// channel counts (us, those / these: bf16 64 channels 0.4, 1.6, 6 MB 8.4 / 9.2, 9.3 / 10.2, 11.8 / 13.1, 24 MB 24.5 / 21.3; 256 channels 0.4, 6, 12 MB
+// 8.4 / 10.3, 12.9 / 14.3, 17.4 / 17.2; 512 channels 3, 6 MB 11.7 / 12.1, 15.4 / 13.8; 1024 channels 0.4, 1.5 MB 9.8 / 9.9, 11.7 / 10.7; fp32 64
+// channels 3, 12 MB 8.4 / 9.9, 13.3 / 13.9; 256 channels 6, 12 MB 11.2 / 12.0, 15.5 / 14.0; 512 channels 3 MB 10.0 / 9.8)
+bool own_sums_fast(const nsk_bn_desc_t &d, const Geom &g)
+{
+    const long bytes = g.total * (long)elem_size(d.dtype), mb = 1L << 20;
+    return bytes > 16 * mb || d.C >= 1024 || bytes >= (d.C >= 512 ? 4 * mb : d.C >= 128 ? 12 * mb : 16 * mb);
+}
+// Statistics of a convolution: every apply block reads the sums of its chunk, so they must be few; up to 100 KB a chunk that beats the
+// launch between (0.78-1.04 of its time), 200 KB up to 32 channels, 512 KB from 1024 channels on, where that launch reads column by column
+// for long (us, launch between / apply pass: bf16 64 channels, 1.6 MB, 64, 196, 256, 784 rows 4.9 / 4.3, 5.3 / 5.1, 5.5 / 5.1, 6.0 / 7.3; 256
+// channels, 3 MB, 64, 256, 784 rows 5.9 / 5.6, 6.1 / 6.7, 7.3 / 8.6; 1024 channels, 6 MB, 256 rows 9.2 / 9.0; 16 channels, 784 rows 5.4 / 5.2)
+bool rows_fit_apply(int rows, const nsk_bn_desc_t &d) { return (long)rows * fast_chunk(d) * 8 <= (d.C >= 1024 ? 512L << 10 : d.C <= 32 ? 200L << 10 : 100L << 10); }
+// Above 1024 rows (512 channels and more: 512) they are folded first, into at most 64 rows by enough blocks, if the apply pass cannot read
+// them (launch between / fold and apply pass, us: 64 channels, 3 MB, 784, 1568 rows 6.4 / 7.9, 8.0 / 7.2; 512 channels, 6 MB, 784 rows
+// 10.5 / 10.4; 12 MB, 1024 rows 15.0 / 12.3)
 bool fold_first(int stats_rows, const nsk_bn_desc_t &d, const Geom &g)
 {
-    return g.G >= 16 && (apply_finishes(d, g) ? (long)stats_rows * fast_chunk(d) * 8 > (512L << 10) : stats_rows > 1024);
+    return g.G >= 16 && stats_rows > (d.C >= 512 ? 512 : 1024) && !(apply_finishes(d, g) && rows_fit_apply(stats_rows, d));
 }
 template <typename T, int MODE, int THREADS>
 void launch_sums_fast(const nsk_bn_desc_t &d, const Geom &g, int G, const T *x, const T *out, const T *dout, const float *mean, const float *invstd,
@@ -923,7 +939,8 @@ int bn_fwd_typed(const nsk_bn_desc_t &d, const T *x, const T *res, const float *
                  unsigned char *relu_mask, const float *stats, int stats_rows, hipStream_t stream)
 {
     const Geom g = geometry(d, false);
-    const bool fast = nhwc_fast(d), finish = fast && apply_finishes(d, g);
+    const bool fast = nhwc_fast(d) && (stats || own_sums_fast(d, g));
+    bool finish = fast && apply_finishes(d, g);
     float *p0 = ws, *p1 = ws + (long)g.G * d.C, *scale = p1 + (long)g.G * d.C, *bias = scale + d.C;
     const float *q0 = p0, *q1 = p1;
     int rows = fast ? fast_sum_blocks(d, g) : g.G;
@@ -941,6 +958,7 @@ int bn_fwd_typed(const nsk_bn_desc_t &d, const T *x, const T *res, const float *
             q0 = p0;
             q1 = p0 + (long)rows * d.C;
         }
+        finish = finish && rows_fit_apply(rows, d);
     } else if (fast) {
         launch_sums_fast<T, 0, kBnThreads>(d, g, rows, x, nullptr, nullptr, nullptr, nullptr, p0, p1, nullptr, nullptr, nullptr, scale, stream);
     } else if (g.vec) {

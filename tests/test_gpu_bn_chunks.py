@@ -127,3 +127,38 @@ def test_float_chains_of_a_large_tensor():
     assert torch.allclose(m.double(), torch.full_like(m, 1.0).double() * v * (1 - 1 / M), rtol=1e-6)
     want = (v * v / M * (1 - 1 / M)) ** -0.5
     assert ((i.double() - want).abs() <= 1e-3 * want).all()
+
+
+@pytest.mark.parametrize("M,C,dtype,rows", [
+    (3200, 64, "bf16", (200, 201, 1024, 1025)),        # 100 KB of sums a chunk; the line of the fold
+    (12900, 16, "bf16", (1600, 1601)),                 # 200 KB up to 32 channels
+    (3200, 256, "f32", (100, 101)),                    # two chunks of 128 channels
+    (2100, 512, "bf16", (100, 101, 512, 513)),
+    (1100, 1024, "f32", (512, 513)),
+    (4096, 512, "bf16", (None,)), (4095, 512, "bf16", (None,)),          # 4 MB: own sums in chunks, or over whole rows
+    (1024, 1024, "bf16", (None,)), (24576, 128, "f32", (None,)), (24575, 128, "f32", (None,)),      # 12 MB
+])
+def test_forward_routes(M, C, dtype, rows):
+    """Both sides of the lines between the forward routes: statistics of a convolution that the apply pass reads, that a launch between
+    finishes, that are folded first; own statistics by either kernel.  Against torch in 64 bits."""
+    dt = torch_dtype(dtype)
+    g = torch.Generator(device="cuda:0").manual_seed(M + C)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda:0")
+    x, gamma, beta = (0.3 + r(M, 1, 1, C)).to(dt), 1 + 0.2 * r(C), 0.2 * r(C)
+    X = x.double().reshape(M, C)
+    mean, var = X.mean(0), X.var(0, unbiased=False)
+    invstd = torch.rsqrt(var + 1e-5)
+    for n in rows:
+        print(f"bn forward routes {M}x{C} {dtype} rows {n}", flush=True)
+        stats = None
+        if n is not None:
+            at = torch.arange(M, device="cuda:0") * n // M                  # disjoint shares of the rows
+            stats = torch.stack([torch.zeros(n, C, dtype=torch.float64, device="cuda:0").index_add_(0, at, v) for v in (X, X * X)]).float()
+        out, m, i = B.bn_relu_add_fwd(x, gamma, beta, stats=stats)
+        torch.cuda.synchronize()
+        # rows rounded to float (exact sums otherwise), or float chains of at most 100 terms; then E[x^2] - E[x]^2 in 64 bits
+        assert ((m.double() - mean).abs() <= 6e-6 * X.abs().mean(0)).all()
+        assert ((i.double() - invstd).abs() <= 1.4e-5 * invstd).all()
+        want = torch.relu((X - m.double()) * (i.double() * gamma.double()) + beta.double()).view_as(out)
+        scale = float(((X.abs() + m.double().abs()) * (i * gamma).abs().double() + beta.abs().double()).max())
+        _bound_values(out, want, dtype, scale)
