@@ -873,19 +873,27 @@ dim3 fast_apply_grid(const nsk_bn_desc_t &d, const Geom &g)
 }
 // Forward, its own statistics: the sums in chunks pay where 512 blocks over whole rows would leave many of them to the launch between, or
 // the tensor is large; below, two launches of 1024 threads a block with their sums in LDS take longer than the three of the other
-// channel counts (us, those / these: bf16 64 channels 0.4, 1.6, 6 MB 8.4 / 9.2, 9.3 / 10.2, 11.8 / 13.1, 24 MB 24.5 / 21.3; 256 channels 0.4, 6, 12 MB
-// 8.4 / 10.3, 12.9 / 14.3, 17.4 / 17.2; 512 channels 3, 6 MB 11.7 / 12.1, 15.4 / 13.8; 1024 channels 0.4, 1.5 MB 9.8 / 9.9, 11.7 / 10.7; fp32 64
-// channels 3, 12 MB 8.4 / 9.9, 13.3 / 13.9; 256 channels 6, 12 MB 11.2 / 12.0, 15.5 / 14.0; 512 channels 3 MB 10.0 / 9.8)
+// channel counts (us, those / these: bf16 64 channels 0.4, 1.6, 4, 11 MB 8.4 / 9.2, 9.3 / 10.2, 10.1 / 10.9, 14.9 / 14.7; 256 channels 0.4, 4, 8, 12
+// MB 8.4 / 10.3, 10.6 / 12.1, 14.4 / 14.7, 17.1 / 16.4; 512 channels 3, 6 MB 11.7 / 12.1, 15.4 / 13.8; 1024 channels 0.4, 1.5 MB 9.8 / 9.9, 11.7 / 10.7;
+// fp32 64 channels 4, 8, 11 MB 8.6 / 9.9, 10.9 / 11.8, 12.7 / 13.1; 256 channels 8, 11 MB 12.5 / 12.6, 14.9 / 13.6)
+// At 16 MB sharp, a common size, blocks' shares of a power of two rows meet in the same memory channels: up to 128 channels the three
+// launches again (64 channels, those / sums in chunks with a launch between / finished by the apply pass: bf16 16.7 / 18.2 / 19.1, fp32 14.4 / 15.8 /
+// 16.1; 256 channels 19.4 / 19.0 / 20.5, 17.1 / 15.9 / 16.2).
 bool own_sums_fast(const nsk_bn_desc_t &d, const Geom &g)
 {
-    const long bytes = g.total * (long)elem_size(d.dtype), mb = 1L << 20;
-    return bytes > 16 * mb || d.C >= 1024 || bytes >= (d.C >= 512 ? 4 * mb : d.C >= 128 ? 12 * mb : 16 * mb);
+    const long bytes = g.total * (long)elem_size(d.dtype);
+    return bytes >= (d.C >= 1024 ? 0L : d.C >= 512 ? 4L << 20 : 10L << 20) && (bytes != 16L << 20 || d.C > 128);
 }
 // Statistics of a convolution: every apply block reads the sums of its chunk, so they must be few; up to 100 KB a chunk that beats the
-// launch between (0.78-1.04 of its time), 200 KB up to 32 channels, 512 KB from 1024 channels on, where that launch reads column by column
-// for long (us, launch between / apply pass: bf16 64 channels, 1.6 MB, 64, 196, 256, 784 rows 4.9 / 4.3, 5.3 / 5.1, 5.5 / 5.1, 6.0 / 7.3; 256
-// channels, 3 MB, 64, 256, 784 rows 5.9 / 5.6, 6.1 / 6.7, 7.3 / 8.6; 1024 channels, 6 MB, 256 rows 9.2 / 9.0; 16 channels, 784 rows 5.4 / 5.2)
-bool rows_fit_apply(int rows, const nsk_bn_desc_t &d) { return (long)rows * fast_chunk(d) * 8 <= (d.C >= 1024 ? 512L << 10 : d.C <= 32 ? 200L << 10 : 100L << 10); }
+// launch between (0.78-1.04 of its time), 200 KB up to 32 channels, 220 KB from 512, 512 KB from 1024 channels on, where that launch reads
+// column by column for long (us, launch between / apply pass: bf16 64 channels, 1.6 MB, 64, 196, 256, 784 rows 4.9 / 4.3, 5.3 / 5.1, 5.5 / 5.1, 6.0 /
+// 7.3; 256 channels, 3 MB, 64, 256, 784 rows 5.9 / 5.6, 6.1 / 6.7, 7.3 / 8.6; 1024 channels, 6 MB, 256 rows 9.2 / 9.0; 16 channels, 784 rows 5.4 /
+// 5.2; with the convolution in front, 512 channels, 12 MB, 196 rows 29.0 / 27.1, 256 channels, 3 MB, 196 rows 13.4 / 13.9)
+bool rows_fit_apply(int rows, const nsk_bn_desc_t &d)
+{
+    const long kb = d.C >= 1024 ? 512 : d.C >= 512 ? 220 : d.C > 32 ? 100 : 200;
+    return (long)rows * fast_chunk(d) * 8 <= kb << 10;
+}
 // Above 1024 rows (512 channels and more: 512) they are folded first, into at most 64 rows by enough blocks, if the apply pass cannot read
 // them (launch between / fold and apply pass, us: 64 channels, 3 MB, 784, 1568 rows 6.4 / 7.9, 8.0 / 7.2; 512 channels, 6 MB, 784 rows
 // 10.5 / 10.4; 12 MB, 1024 rows 15.0 / 12.3)
@@ -940,7 +948,8 @@ int bn_fwd_typed(const nsk_bn_desc_t &d, const T *x, const T *res, const float *
 {
     const Geom g = geometry(d, false);
     const bool fast = nhwc_fast(d) && (stats || own_sums_fast(d, g));
-    bool finish = fast && apply_finishes(d, g);
+    // (with its own statistics at 16 MB sharp no longer: own_sums_fast)
+    bool finish = fast && apply_finishes(d, g) && (stats || g.total * (long)sizeof(T) < (16L << 20));
     float *p0 = ws, *p1 = ws + (long)g.G * d.C, *scale = p1 + (long)g.G * d.C, *bias = scale + d.C;
     const float *q0 = p0, *q1 = p1;
     int rows = fast ? fast_sum_blocks(d, g) : g.G;

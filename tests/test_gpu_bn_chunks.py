@@ -133,10 +133,11 @@ def test_float_chains_of_a_large_tensor():
     (3200, 64, "bf16", (200, 201, 1024, 1025)),        # 100 KB of sums a chunk; the line of the fold
     (12900, 16, "bf16", (1600, 1601)),                 # 200 KB up to 32 channels
     (3200, 256, "f32", (100, 101)),                    # two chunks of 128 channels
-    (2100, 512, "bf16", (100, 101, 512, 513)),
+    (2100, 512, "bf16", (220, 221, 512, 513)),
     (1100, 1024, "f32", (512, 513)),
     (4096, 512, "bf16", (None,)), (4095, 512, "bf16", (None,)),          # 4 MB: own sums in chunks, or over whole rows
-    (1024, 1024, "bf16", (None,)), (24576, 128, "f32", (None,)), (24575, 128, "f32", (None,)),      # 12 MB
+    (1024, 1024, "bf16", (None,)), (20480, 128, "f32", (None,)), (20479, 128, "f32", (None,)),      # 10 MB
+    (131072, 64, "bf16", (None,)), (131071, 64, "bf16", (None,)),                                   # 16 MB: its finish
 ])
 def test_forward_routes(M, C, dtype, rows):
     """Both sides of the lines between the forward routes: statistics of a convolution that the apply pass reads, that a launch between
