@@ -876,8 +876,8 @@ dim3 fast_apply_grid(const nsk_bn_desc_t &d, const Geom &g)
 // channel counts (us, those / these: bf16 64 channels 0.4, 1.6, 4, 11 MB 8.4 / 9.2, 9.3 / 10.2, 10.1 / 10.9, 14.9 / 14.7; 256 channels 0.4, 4, 8, 12
 // MB 8.4 / 10.3, 10.6 / 12.1, 14.4 / 14.7, 17.1 / 16.4; 512 channels 3, 6 MB 11.7 / 12.1, 15.4 / 13.8; 1024 channels 0.4, 1.5 MB 9.8 / 9.9, 11.7 / 10.7;
 // fp32 64 channels 4, 8, 11 MB 8.6 / 9.9, 10.9 / 11.8, 12.7 / 13.1; 256 channels 8, 11 MB 12.5 / 12.6, 14.9 / 13.6)
-// At 16 MB sharp, a common size, blocks' shares of a power of two rows meet in the same memory channels: up to 128 channels the three
-// launches again (64 channels, those / sums in chunks with a launch between / finished by the apply pass: bf16 16.7 / 18.2 / 19.1, fp32 14.4 / 15.8 /
+// At 16 MB sharp, a common size, they are slower than at 15 and 17 MB (64 channels bf16 16.6 and 17.7 us), the cause not known: up to 128
+// channels the three launches again (64 channels, those / sums in chunks with a launch between / finished by the apply pass: bf16 16.7 / 18.2 / 19.1, fp32 14.4 / 15.8 /
 // 16.1; 256 channels 19.4 / 19.0 / 20.5, 17.1 / 15.9 / 16.2).
 bool own_sums_fast(const nsk_bn_desc_t &d, const Geom &g)
 {

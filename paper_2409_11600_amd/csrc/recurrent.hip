@@ -37,14 +37,48 @@ __global__ __launch_bounds__(256) void embedding_fwd_kernel(const int *__restric
 // Gradient of the lookup without atomics: block b owns the vocabulary rows v with v % gridDim.x == b, walks over ALL
 // positions in order and adds the rows that are its own, so every dtable element is updated by one thread in
 // position order (bitwise reproducible).  The token list is tiny next to the table, every block reads all of it.
-// Bound by the zeros it writes and by latency: 2048 positions are tested between two barriers (256 until then, forty rounds of a
-// load and three barriers for 10000 positions), the next are on their way, the matches are kept until there are many, and eight of them
-// fetch their operands together (one by one a chain of three loads each).  10000 positions of 32768 x 256: 36.7 -> 26.2 us.
-template <typename T, int CH>     // CH: chunks of 256 positions that are tested at once
+template <typename T>
 __global__ __launch_bounds__(256) void embedding_bwd_kernel(const int *__restrict__ tokens, const T *__restrict__ dout,
                                                             float *__restrict__ dtable, int n, int E, int V, int accumulate)
 {
-    constexpr int CAP = 2 * 256 * CH;           // matches that are kept
+    __shared__ int hit[256];         // positions of this chunk whose row belongs to the block, in position order
+    __shared__ int wave_hits[4];
+    const int b = blockIdx.x, nb = gridDim.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (!accumulate)
+        for (int v = b; v < V; v += nb)
+            for (int e = threadIdx.x; e < E; e += 256) dtable[(long)v * E + e] = 0.f;
+    for (int base = 0; base < n; base += 256) {
+        // all 256 positions of the chunk are tested at once; the matches are compacted in position order
+        const int i = base + threadIdx.x;
+        const int v = i < n ? tokens[i] : -1;
+        const bool mine = v >= 0 && v < V && v % nb == b;
+        const unsigned long long ballot = __ballot(mine);
+        if (lane == 0) wave_hits[wave] = __popcll(ballot);
+        __syncthreads();
+        int before = 0;
+        for (int w = 0; w < wave; ++w) before += wave_hits[w];
+        const int total = wave_hits[0] + wave_hits[1] + wave_hits[2] + wave_hits[3];
+        if (mine) hit[before + __popcll(ballot & ((1ull << lane) - 1ull))] = i;
+        __syncthreads();
+        for (int k = 0; k < total; ++k) {
+            const int pos = hit[k];
+            const long row = (long)tokens[pos] * E;
+            for (int e = threadIdx.x; e < E; e += 256) dtable[row + e] += ld(dout, (long)pos * E + e);
+        }
+        __syncthreads();
+    }
+}
+
+// The same for many positions, where that kernel is bound by latency: 2048 positions are tested between two barriers (256 there, forty
+// rounds of a load and three barriers for 10000 positions), the next are on their way, the matches are kept until there are
+// many, and eight of them fetch their operands together (one by one a chain of three loads each).  10000 positions of 32768 x 256:
+// 36.7 -> 26.2 us.
+template <typename T>
+__global__ __launch_bounds__(256) void embedding_bwd_many_kernel(const int *__restrict__ tokens, const T *__restrict__ dout,
+                                                            float *__restrict__ dtable, int n, int E, int V, int accumulate)
+{
+    constexpr int CH = 8, CAP = 2 * 256 * CH;   // chunks of 256 positions that are tested at once; matches that are kept
     __shared__ int hit[CAP], row_of[CAP];       // positions whose row belongs to the block, in position order, and their rows
     __shared__ int found[2][CH][4];
     const int b = blockIdx.x, nb = gridDim.x;
@@ -314,13 +348,17 @@ int nsk_embedding_bwd(int dtype, int n, int E, int V, const int *tokens, const v
     if (!tokens || !dout || !dtable) return NSK_ERR_NULL;
     if (unaligned16(tokens) || unaligned16(dout) || unaligned16(dtable)) return NSK_ERR_ALIGNMENT;
     const int blocks = V < 1024 ? V : 1024;
-    // few positions: one chunk at a time (80 positions 3.1 us, 500 4.0; 4.6 and 4.9 with eight)
-#define NSK_EMB(T, CH) \
-    hipLaunchKernelGGL((embedding_bwd_kernel<T, CH>), dim3(blocks), dim3(256), 0, (hipStream_t)stream, tokens, (const T *)dout, dtable, n, E, V, accumulate)
+    // Eight at a time from 1536 positions and 500 rows, or 2048 and 100, on, for rows that a block takes in one go: few positions are a round or
+    // two, and a few rows with many matches each are bound by what is done for a match, one by one or not (us, a chunk and a match at
+    // a time / eight, fp32 256 wide: 500 positions of 1000 rows 3.8 / 5.1, 1024 5.1 / 5.7, 1536 -2%, 2048 -8%, 10000 28.5 / 22.8; of 50 rows
+    // 78.6 / 76, of 20 rows +10%).  Wider rows: from 1000 on up to 384 (300 wide: 2048 positions of 50, 200, 1000, 2000 rows +28, +3, -10, -19%; 512
+    // wide +15, +3, -6, -7%, 1024 wide +26, +18, +17, -1%).
+    const bool many = E <= 256 ? (V >= 500 && n >= 1536) || (V >= 100 && n >= 2048) : E <= 384 && V >= 1000 && n >= 2048;
+#define NSK_EMB(K, T) hipLaunchKernelGGL(K<T>, dim3(blocks), dim3(256), 0, (hipStream_t)stream, tokens, (const T *)dout, dtable, n, E, V, accumulate)
     if (dtype == NSK_BF16) {
-        if (n <= 1024) NSK_EMB(bf16_t, 1); else NSK_EMB(bf16_t, 8);
+        if (many) NSK_EMB(embedding_bwd_many_kernel, bf16_t); else NSK_EMB(embedding_bwd_kernel, bf16_t);
     } else {
-        if (n <= 1024) NSK_EMB(float, 1); else NSK_EMB(float, 8);
+        if (many) NSK_EMB(embedding_bwd_many_kernel, float); else NSK_EMB(embedding_bwd_kernel, float);
     }
 #undef NSK_EMB
     return check_launch();

@@ -224,3 +224,21 @@ def test_embedding_gradient_with_many_matches(n, V):
     got = B.embedding_bwd(tokens.cuda(), dout.cuda(), V)
     torch.cuda.synchronize()
     assert np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n,E,V", [(1535, 256, 500), (1536, 256, 500), (2047, 64, 499), (2048, 64, 499), (2048, 64, 100), (2048, 64, 99),
+                                   (2048, 300, 1000), (2048, 300, 999), (2048, 385, 1000)])
+def test_embedding_gradient_around_the_line_of_many_positions(n, E, V):
+    """Both kernels, on both sides of every line between them: the sum in position order, bit for bit; with `accumulate` behind the old values."""
+    g = torch.Generator().manual_seed(n + E + V)
+    tokens = torch.randint(0, V, (n,), generator=g, dtype=torch.int32)
+    dout, old = torch.randn((n, E), generator=g), torch.randn((V, E), generator=g)
+    want, more = np.zeros((V, E), np.float32), old.numpy().copy()
+    for i, v in enumerate(tokens.tolist()):
+        want[v] += dout[i].numpy()
+        more[v] += dout[i].numpy()
+    got = B.embedding_bwd(tokens.cuda(), dout.cuda(), V)
+    acc = old.cuda()
+    B.embedding_bwd(tokens.cuda(), dout.cuda(), V, dtable=acc, accumulate=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), want) and np.array_equal(acc.cpu().numpy(), more)
