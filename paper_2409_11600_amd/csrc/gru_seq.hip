@@ -19,9 +19,10 @@
 // Waiting ends: members of a group are dispatched one after the other and hold no more CUs than the XCD has (split_of), and whole
 // groups wait for nobody else.  So of each launch at most one group an XCD, G - 1 blocks, waits for a block that has no CU yet: ten launches
 // at a time on one card leave CUs free for those.  With more, or where others hold the CUs for long, a poller that has seen kPolls polls
-// fail gives up and its block ends, which leaves the mark in that sample's last row; the others of the group then end the
-// same way.  A launch of the G = 1 kernel behind looks at the last rows and runs the samples that are not whole, from their first step:
-// same bits, so the call is right in any case, and such a sample costs that wait and the time without a split.
+// fail gives up: its block goes on with what it has, and in the end puts the mark back into that sample's last row.  A launch of the
+// G = 1 kernel behind looks at the last rows and runs the samples that have the mark, from their first step: same bits, so
+// the call is right in any case, and such a sample costs that wait and the time without a split.  (Ending such a block at once, by a
+// word in LDS that every step looks at, cost the two-block kernel 28 bytes of scratch a thread: 57 / 59 -> 76 / 72 us for 20 steps.)
 //
 // Work inside a block of 512 (32 units: 256) multiplying threads: eight neighbouring lanes q share a hidden unit's dot products
 // (lane q takes the columns 4*(q + 8*m) ..), 64 (32) groups of lanes hold the units slot, slot + 64, ...; the lane sums run over
@@ -82,6 +83,7 @@ typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
 template <typename T> struct SeqT;
 template <> struct SeqT<float> {
     typedef f32x4 V;
+    typedef unsigned U;
     static __device__ inline float mac(float a, V w, V v)
     {
         float t = w[0] * v[0];      // four products at a time: chains of 4 and 8 roundings, not one of 32
@@ -93,6 +95,7 @@ template <> struct SeqT<float> {
 };
 template <> struct SeqT<bf16_t> {
     typedef bf16x4 V;
+    typedef unsigned short U;
     static __device__ inline float mac(float a, V w, V v)
     {
         a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(w, w, 0, 1), __builtin_shufflevector(v, v, 0, 1), a, false);
@@ -171,7 +174,6 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
     const int u0 = SPLIT ? blockIdx.x % (8 * a.G) / 8 * a.HU : 0, u1 = SPLIT ? min(u0 + a.HU, H) : H;
     if (SPLIT && n >= N) return;
     const long NH = (long)N * H;
-    __shared__ int halt[2];        // SPLIT: a poller gave up in a step (even, odd)
     if constexpr (!SPLIT) {
         if (a.unfinished) {
             const int words = (BWD ? 3 : 1) * H * (int)sizeof(T) / 8;      // of the row that the last step leaves
@@ -187,6 +189,7 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
         const int g = (tid - MT) >> 6, c = 4 * (tid & 63);
         const bool live = c < H;
         int left = a.polls, wait = 0;
+        bool gave_up = false;
         for (int step = 0; step < a.T; ++step) {
             if (step > 0 && live) {
                 const int t = BWD ? a.T - step : step;          // the row that the step before this one has left
@@ -208,12 +211,16 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
                     }
                 }
                 if (wait > 0) wait -= 1;
-                if (missing && c == 0) halt[step & 1] = 1;
+                gave_up |= missing;
 #pragma unroll
                 for (int e = 0; e < W; ++e) *(u64 *)((char *)(vec + (step & 1) * NV * HP + g * HP + c) + 8 * e) = v[e];
             }
             lds_barrier();
-            if (halt[step & 1]) return;
+        }
+        __syncthreads();           // (the block's units of the last row are stored)
+        if (gave_up && c == 0) {
+            T *last = BWD ? (T *)a.dgh + (long)n * 3 * H + u0 : (T *)a.h + (long)a.T * NH + (long)n * H + u0;
+            *(typename ST::U *)last = (typename ST::U)kUnset;
         }
         return;
     }
@@ -252,7 +259,6 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
     // (SPLIT: the second half is the pollers', who fill its first H columns at the second step; all read those past H)
     for (int i = tid; i < 2 * NV * HP; i += MT)
         if (!SPLIT || i < NV * HP || i % HP >= H) vec[i] = !BWD && SPLIT && i < H ? ((const T *)a.h)[(long)n * H + i] : (T)0.f;
-    if (SPLIT && tid < 2) halt[tid] = 0;
     if constexpr (!SPLIT) __syncthreads();
 
     // this lane's unit in the elementwise part
@@ -303,7 +309,6 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
         if constexpr (D == 1 || SPLIT) take();     // (waits here for what was requested; without a split the products come first)
         if constexpr (D == 1) operands(e[k], min(step + 1, a.T - 1));
         if constexpr (SPLIT) lds_barrier();
-        const int stop = SPLIT ? halt[buf] : 0;
         float acc[S];
 #pragma unroll
         for (int p = 0; p < S; ++p) acc[p] = 0.f;
@@ -336,7 +341,6 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
         constexpr int R = BWD ? IU : S;
 #pragma unroll
         for (int p = 0; p < R; ++p) acc[p] = sum8(acc[p]);
-        if (SPLIT && __builtin_amdgcn_readfirstlane(stop)) return;
         if constexpr (!(D == 1 || SPLIT)) take();
         T *vn = vec + (buf ^ 1) * NV * HP;
         if constexpr (!BWD) {
@@ -401,6 +405,10 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
         }
         if constexpr (D > 1) operands(e[k], min(step + D, a.T - 1));
         if constexpr (!SPLIT) lds_barrier();
+    }
+    if constexpr (SPLIT) {         // a poller that gave up writes over what is stored here
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
     }
 }
 
