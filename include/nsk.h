@@ -431,7 +431,7 @@ int nsk_gru_step_bwd(int dtype, int N, int H, const void *saved, const void *h_p
  * nsk_gru_seq_blocks: the blocks that share a sample of such a call on this stream now (1, 2, 4), 0 for sizes that are not one launch.
  * forward: gi [T,N,3H]; h [T+1,N,H] holds the initial state in h[0] and receives h[1..T]; saved [T,N,4H].
  * backward: dh_top [N,H] is the gradient of h[T]; dgi, dgh [T,N,3H] are written; dh_scratch [2,N,H] of `dtype` is scratch. */
-int nsk_gru_seq_blocks(int dtype, int N, int H, void *stream);
+int nsk_gru_seq_blocks(int dtype, int T, int N, int H, void *stream);
 int nsk_gru_seq_fwd(int dtype, int T, int N, int H, const void *gi, const void *w_hh, const float *b_ih, const float *b_hh,
                     void *h, void *saved, void *stream);
 int nsk_gru_seq_bwd(int dtype, int T, int N, int H, const void *saved, const void *h, const void *dh_top, const void *w_hh_t,

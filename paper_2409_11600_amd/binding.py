@@ -193,7 +193,7 @@ def lib() -> ctypes.CDLL:
         L.nsk_gru_step_bwd.restype = ci
         L.nsk_gru_step_bwd.argtypes = [ci, ci, ci, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.nsk_gru_seq_blocks.restype = ci
-        L.nsk_gru_seq_blocks.argtypes = [ci, ci, ci, vp]
+        L.nsk_gru_seq_blocks.argtypes = [ci, ci, ci, ci, vp]
         L.nsk_gru_seq_fwd.restype = ci
         L.nsk_gru_seq_fwd.argtypes = [ci, ci, ci, ci, vp, vp, vp, vp, vp, vp, vp]
         L.nsk_gru_seq_bwd.restype = ci
@@ -921,9 +921,9 @@ def gru_step_bwd(saved, h_prev, w_hh_t, dh_a=None, dh_direct_next=None, dgh_next
     return dgi, dgh, dh_direct
 
 
-def gru_seq_blocks(dtype: torch.dtype, N: int, H: int) -> int:
+def gru_seq_blocks(dtype: torch.dtype, T: int, N: int, H: int) -> int:
     """Blocks that share a sample of gru_seq_fwd and gru_seq_bwd on the current stream; 0: not one launch (H > 256)."""
-    return int(lib().nsk_gru_seq_blocks(NSK_BF16 if dtype == torch.bfloat16 else NSK_F32, int(N), int(H), _stream()))
+    return int(lib().nsk_gru_seq_blocks(NSK_BF16 if dtype == torch.bfloat16 else NSK_F32, int(T), int(N), int(H), _stream()))
 
 
 def gru_seq_fwd(gi, w_hh, b_ih, b_hh, h, saved):

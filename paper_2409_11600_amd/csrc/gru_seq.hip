@@ -84,19 +84,20 @@ template <typename T> struct SeqT;
 template <> struct SeqT<float> {
     typedef f32x4 V;
     typedef unsigned U;
-    static __device__ inline float mac(float a, V w, V v)
+    // FOUR: four products at a time, chains of 4 and 8 roundings and not one of 32, for a fifth instruction
+    template <bool FOUR> static __device__ inline float mac(float a, V w, V v)
     {
-        float t = w[0] * v[0];      // four products at a time: chains of 4 and 8 roundings, not one of 32
+        float t = FOUR ? w[0] * v[0] : fmaf(w[0], v[0], a);
 #pragma unroll
         for (int e = 1; e < 4; ++e) t = fmaf(w[e], v[e], t);
-        return a + t;
+        return FOUR ? a + t : t;
     }
     static __device__ inline V fetch(__amdgpu_buffer_rsrc_t r, unsigned at) { return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)at, 0, 0)); }
 };
 template <> struct SeqT<bf16_t> {
     typedef bf16x4 V;
     typedef unsigned short U;
-    static __device__ inline float mac(float a, V w, V v)
+    template <bool FOUR> static __device__ inline float mac(float a, V w, V v)
     {
         a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(w, w, 0, 1), __builtin_shufflevector(v, v, 0, 1), a, false);
         return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(w, w, 2, 3), __builtin_shufflevector(v, v, 2, 3), a, false);
@@ -164,6 +165,7 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
     typedef SeqT<T> ST;
     typedef typename ST::V V;
     constexpr int S = 3 * IU, SS = S - RS - LS, HP = 32 * M, NV = BWD ? 3 : 1, MT = 8 * SLOTS;
+    constexpr bool FOUR = !(BWD && M == 4);     // (the chain of 16 there is as long as it was; 128 units, 50 samples, 200 steps 199 -> 191 us)
     static_assert(SS >= 0, "parts");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     T *const vec = (T *)smem;                                   // [2][NV][HP]: what the step multiplies
@@ -312,7 +314,8 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
         float acc[S];
 #pragma unroll
         for (int p = 0; p < S; ++p) acc[p] = 0.f;
-        {
+        // (no step comes after the last one, whose products are skipped; in fp32 that branch would spill, and they are dropped)
+        if (!BWD || sizeof(T) == 4 || step > 0) {
             const T *v0 = vec + buf * NV * HP;
 #pragma unroll
             for (int m = 0; m < M; ++m) {
@@ -321,13 +324,13 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
                 for (int g = 0; g < NV; ++g) v[g] = *(const V *)(v0 + g * HP + column(m));
 #pragma unroll
                 for (int p = 0; p < SS; ++p) {
-                    acc[RS + LS + p] = ST::mac(acc[RS + LS + p], sw[p], v[BWD ? (RS + LS + p) % 3 : 0]);
+                    acc[RS + LS + p] = ST::template mac<FOUR>(acc[RS + LS + p], sw[p], v[BWD ? (RS + LS + p) % 3 : 0]);
                     sw[p] = load(rs[p], (m + 1) % M);
                 }
 #pragma unroll
-                for (int p = 0; p < RS; ++p) acc[p] = ST::mac(acc[p], wr[p][m], v[BWD ? p % 3 : 0]);
+                for (int p = 0; p < RS; ++p) acc[p] = ST::template mac<FOUR>(acc[p], wr[p][m], v[BWD ? p % 3 : 0]);
 #pragma unroll
-                for (int p = 0; p < LS; ++p) acc[RS + p] = ST::mac(acc[RS + p], lw[(p * M + m) * MT + tid], v[BWD ? (RS + p) % 3 : 0]);
+                for (int p = 0; p < LS; ++p) acc[RS + p] = ST::template mac<FOUR>(acc[RS + p], lw[(p * M + m) * MT + tid], v[BWD ? (RS + p) % 3 : 0]);
                 if constexpr (SS > 0) __builtin_amdgcn_sched_barrier(0);     // (or every piece of the step is fetched ahead, into scratch)
             }
         }
@@ -335,7 +338,7 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
 #pragma unroll
             for (int i = 0; i < IU; ++i) {
                 acc[i] = (acc[3 * i] + acc[3 * i + 1]) + acc[3 * i + 2];
-                acc[i] = step > 0 ? acc[i] : 0.f;    // (no step comes after the last one)
+                if (sizeof(T) == 4) acc[i] = step > 0 ? acc[i] : 0.f;
             }
         }
         constexpr int R = BWD ? IU : S;
@@ -457,7 +460,9 @@ bool whole_chip(hipStream_t stream, int cus)
 // one CU cannot hold the weight, above 192 units: us for T = 200, forward / backward, without -> with: fp32, 50 samples of 256
 // units 566 / 594 -> 287 / 333 (G = 4; G = 8, 32 samples: 313 / 293 but unsteady), 100 samples 566 / 594 -> 448 / 447 (G = 2);
 // bf16, 50 samples 316 / 285 -> 228 / 276, but G = 2 293 / 334; 192 units: fp32 274 / 274 -> 252 / 292, bf16 215 / 205 -> 217 / 263.
-int split_of(int dtype, int N, int H, hipStream_t stream)
+// The launches before and behind are paid back from the first steps on with G = 4, with G = 2 from 16 on (100 samples, 2, 8, 16 steps, without /
+// with: 11.7 / 14.1, 28.8 / 30.3, 51.7 / 50.0; a single step has no launch behind).
+int split_of(int dtype, int T, int N, int H, hipStream_t stream)
 {
     if (H % 8 != 0 || H <= 192) return 1;    // (polled in whole 8-byte words)
     static std::atomic<int> cus[64];         // of each device, once known
@@ -471,7 +476,7 @@ int split_of(int dtype, int N, int H, hipStream_t stream)
     const int forced = hooks().gru_split;
     int g = 4;
     while (g > 1 && (ceil_div(N, 8) * g > c / 8 || (forced > 0 && g > forced))) g /= 2;
-    if (dtype == NSK_BF16 && g == 2) g = 1;
+    if (g == 2 && (dtype == NSK_BF16 || (T > 1 && T < 16))) g = 1;
     return g > 1 && whole_chip(stream, c) ? g : 1;
 }
 
@@ -536,10 +541,10 @@ using namespace nsk;
 
 extern "C" {
 
-int nsk_gru_seq_blocks(int dtype, int N, int H, void *stream)
+int nsk_gru_seq_blocks(int dtype, int T, int N, int H, void *stream)
 {
-    if (N <= 0 || H <= 0 || (dtype != NSK_F32 && dtype != NSK_BF16) || !nsk_gru_step_supported(N, H) || !seq_kernel_takes(H)) return 0;
-    return split_of(dtype, N, H, (hipStream_t)stream);
+    if (T <= 0 || N <= 0 || H <= 0 || (dtype != NSK_F32 && dtype != NSK_BF16) || !nsk_gru_step_supported(N, H) || !seq_kernel_takes(H)) return 0;
+    return split_of(dtype, T, N, H, (hipStream_t)stream);
 }
 
 int nsk_gru_seq_fwd(int dtype, int T, int N, int H, const void *gi, const void *w_hh, const float *b_ih, const float *b_hh,
@@ -554,7 +559,7 @@ int nsk_gru_seq_fwd(int dtype, int T, int N, int H, const void *gi, const void *
     if (!nsk_gru_step_supported(N, H)) return NSK_ERR_UNSUPPORTED;
     if (seq_kernel_takes(H)) {
         GruSeqArgs a{};
-        a.G = split_of(dtype, N, H, (hipStream_t)stream);
+        a.G = split_of(dtype, T, N, H, (hipStream_t)stream);
         a.polls = hooks().gru_polls >= 0 ? hooks().gru_polls : kPolls;
         a.gi = gi; a.w = w_hh; a.b_ih = b_ih; a.b_hh = b_hh; a.h = h; a.saved = saved;
         a.T = T; a.N = N; a.H = H;
@@ -581,7 +586,7 @@ int nsk_gru_seq_bwd(int dtype, int T, int N, int H, const void *saved, const voi
     if (!nsk_gru_step_supported(N, H)) return NSK_ERR_UNSUPPORTED;
     if (seq_kernel_takes(H)) {
         GruSeqArgs a{};
-        a.G = split_of(dtype, N, H, (hipStream_t)stream);
+        a.G = split_of(dtype, T, N, H, (hipStream_t)stream);
         a.polls = hooks().gru_polls >= 0 ? hooks().gru_polls : kPolls;
         a.saved_in = saved; a.h = (void *)h; a.dh_top = dh_top; a.w = w_hh_t; a.dgi = dgi; a.dgh = dgh;
         a.T = T; a.N = N; a.H = H;

@@ -103,13 +103,13 @@ def _sequence(T, N, H, dtype, seed, bad=None):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("T,N,H", [(1, 2, 256), (2, 1, 200), (7, 9, 256), (3, 64, 248), (3, 65, 208), (2, 128, 256), (2, 129, 256)])
+@pytest.mark.parametrize("T,N,H", [(1, 2, 256), (2, 1, 200), (7, 9, 256), (3, 64, 248), (16, 65, 208), (16, 128, 256), (15, 128, 256), (1, 70, 256), (16, 129, 256)])
 def test_blocks_that_share_a_sample(T, N, H, dtype, nsk_env):
     """Several blocks per sample (as many as the sizes allow, and at most two) add in the order of one: the same bits.  Sizes:
     a step without an exchange, part of a last block, all eight XCDs full at four and at two blocks, and one sample more."""
     print(f"gru split T={T} N={N} H={H} {dtype}", flush=True)
     run, out = _sequence(T, N, H, dtype, 8900 + H)
-    blocks = lambda: B.gru_seq_blocks(torch_dtype(dtype), N, H)
+    blocks = lambda: B.gru_seq_blocks(torch_dtype(dtype), T, N, H)
     nsk_env("NSK_GRU_SPLIT", "1")
     assert blocks() == 1
     run()
@@ -117,7 +117,7 @@ def test_blocks_that_share_a_sample(T, N, H, dtype, nsk_env):
     for most in (None, "2"):
         nsk_env("NSK_GRU_SPLIT", most)
         # (the route that is meant is the one that runs: bf16 samples are not shared by two)
-        two = 1 if dtype == "bf16" or N > 128 else 2
+        two = 1 if dtype == "bf16" or N > 128 or 1 < T < 16 else 2
         assert blocks() == (4 if N <= 64 and most is None else two)
         for o in (out[0][1:], *out[1:]):
             o.zero_()
@@ -127,13 +127,13 @@ def test_blocks_that_share_a_sample(T, N, H, dtype, nsk_env):
 
 
 def test_sizes_that_are_not_shared():
-    blocks = lambda N, H, dt=torch.float32: B.gru_seq_blocks(dt, N, H)
+    blocks = lambda N, H, dt=torch.float32: B.gru_seq_blocks(dt, 20, N, H)
     assert blocks(50, 192) == blocks(50, 252) == blocks(50, 64, torch.bfloat16) == 1     # the weight fits a CU; rows of no whole 8-byte words
     assert blocks(50, 260) == blocks(300, 256) == 0                                     # step launches; refused
 
 
 @pytest.mark.parametrize("polls", ["0", "3", "40"])
-@pytest.mark.parametrize("dtype,T,N,H", [("f32", 9, 50, 256), ("f32", 5, 70, 200), ("bf16", 9, 33, 256), ("bf16", 2, 3, 224), ("f32", 1, 3, 256)])
+@pytest.mark.parametrize("dtype,T,N,H", [("f32", 9, 50, 256), ("f32", 17, 70, 200), ("bf16", 9, 33, 256), ("bf16", 2, 3, 224), ("f32", 1, 3, 256)])
 def test_blocks_that_give_up_waiting(dtype, T, N, H, polls, nsk_env):
     """A block that has waited too long ends (with a bound of 0 polls every block does, at its second step; with 3 and 40 some do, some
     later, some never), and the call still gives every sample what one block computes: the same bits."""
@@ -144,7 +144,7 @@ def test_blocks_that_give_up_waiting(dtype, T, N, H, polls, nsk_env):
     want = [o.clone() for o in out]
     nsk_env("NSK_GRU_SPLIT", None)
     nsk_env("NSK_GRU_POLLS", polls)
-    assert B.gru_seq_blocks(torch_dtype(dtype), N, H) > 1
+    assert B.gru_seq_blocks(torch_dtype(dtype), T, N, H) > 1
     for _ in range(3):
         for o in (out[0][1:], *out[1:]):
             o.zero_()
@@ -158,7 +158,7 @@ def test_blocks_that_share_a_sample_with_nan(dtype):
     """A state that holds the very NaN that stands for "not there yet" (all ones), and infinity: the calls end, the sample's later
     states hold NaN, the other samples' values are those without it."""
     T, N, H = 3, 3, 256
-    assert B.gru_seq_blocks(torch_dtype(dtype), N, H) == 4
+    assert B.gru_seq_blocks(torch_dtype(dtype), T, N, H) == 4
     run, clean = _sequence(T, N, H, dtype, 8901)
     run()
     ones = torch.tensor([-1], dtype=torch.int32 if dtype == "f32" else torch.int16).view(torch_dtype(dtype))[0]
@@ -178,9 +178,9 @@ def test_blocks_that_share_a_sample_in_a_graph():
     want = [o.clone() for o in out]
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
-        captured = B.gru_seq_blocks(torch.float32, 50, 256)
+        captured = B.gru_seq_blocks(torch.float32, 5, 50, 256)
         run()
-    assert captured == B.gru_seq_blocks(torch.float32, 50, 256) == 4
+    assert captured == B.gru_seq_blocks(torch.float32, 5, 50, 256) == 4
     for _ in range(3):
         for o in (out[0][1:], *out[1:]):
             o.zero_()
