@@ -894,12 +894,11 @@ bool rows_fit_apply(int rows, const nsk_bn_desc_t &d)
     const long kb = d.C >= 1024 ? 512 : d.C >= 512 ? 220 : d.C > 32 ? 100 : 200;
     return (long)rows * fast_chunk(d) * 8 <= kb << 10;
 }
-// Above 1024 rows (512 channels and more: 512) they are folded first, into at most 64 rows by enough blocks, if the apply pass cannot read
-// them (launch between / fold and apply pass, us: 64 channels, 3 MB, 784, 1568 rows 6.4 / 7.9, 8.0 / 7.2; 512 channels, 6 MB, 784 rows
+// Above 1024 rows (512 channels and more: 512) they are folded first, by enough blocks, if the apply pass cannot read them (launch between / fold and apply pass, us: 64 channels, 3 MB, 784, 1568 rows 6.4 / 7.9, 8.0 / 7.2; 512 channels, 6 MB, 784 rows
 // 10.5 / 10.4; 12 MB, 1024 rows 15.0 / 12.3)
 bool fold_first(int stats_rows, const nsk_bn_desc_t &d, const Geom &g)
 {
-    return g.G >= 16 && stats_rows > (d.C >= 512 ? 512 : 1024) && !(apply_finishes(d, g) && rows_fit_apply(stats_rows, d));
+    return g.G >= 16 && stats_rows > (d.C >= 512 ? 512 : 1024) && !rows_fit_apply(stats_rows, d);
 }
 template <typename T, int MODE, int THREADS>
 void launch_sums_fast(const nsk_bn_desc_t &d, const Geom &g, int G, const T *x, const T *out, const T *dout, const float *mean, const float *invstd,
@@ -960,8 +959,10 @@ int bn_fwd_typed(const nsk_bn_desc_t &d, const T *x, const T *res, const float *
         q0 = stats;
         q1 = stats + (long)stats_rows * d.C;
         rows = stats_rows;
-        if (fast ? fold_first(stats_rows, d, g) : fold_pays(stats_rows, d.C, g)) {
-            const int run = ceil_div(stats_rows, fast ? std::min(g.G, 64) : g.G);
+        if (finish ? fold_first(stats_rows, d, g) : fold_pays(stats_rows, d.C, g)) {
+            // few rows for the launch behind, but 64 of them at most for a block here (64 MB of 256 channels, 3136 rows into 512 / 64 39.7 / 31.2 us;
+            // 24 MB of 16 channels, 16384 rows 16.1 / 20.1)
+            const int run = ceil_div(stats_rows, fast ? std::min(g.G, std::max(64, ceil_div(stats_rows, 64))) : g.G);
             rows = ceil_div(stats_rows, run);
             hipLaunchKernelGGL(bn_stats_fold, dim3(rows, ceil_div(2 * d.C, 256)), dim3(256), 0, stream, stats, stats_rows, d.C, run, p0, rows);
             q0 = p0;

@@ -94,7 +94,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
     // the activation rows they share.  Where the filter is the larger operand, tiles of one column block: an XCD then reads
     // its columns' filter and all of src instead of the whole filter (3x3 on 7x7 images, rows / columns first, us: 1024
     // channels, 8 images 40.9 / 33.3 forward; 512 channels, 8 .. 16 images 22.4 / 16.5 forward, 29.2 / 20.8 backward-data;
-    // 32 images 22.6 / 20.2, 29.1 / 23.0; 64 images, filter 1.5 times src, 29.2 / 29.5, 33.9 / 31.8).  Order and divisor come from the host: found
+    // 32 images 22.6 / 20.2, 29.1 / 23.0; 64 images, filter 1.5 times src, 29.2 / 29.5, 33.9 / 31.8), while src fits an L2 of 4 MB (1024 -> 512, 64
+    // images of 7x7, 6.4 MB, 45.9 / 55.0; 1024 -> 1024, 128 images, 114.9 / 123.3).  Order and divisor come from the host: found
     // here, with a division, they were 5% of a launch of many short blocks (backward-data of 16 -> 16 3x3 stride 2, 256 images of 32x32,
     // 17.4 us; the division by tiles_n alone, without the second order, 16.4; this 16.2).
     int bm, bn;
@@ -512,7 +513,7 @@ template <typename T, int BM, int BN, int WM, int WN, int WK, int ST, int NP> in
     for (int j = 0; j < count; ++j) {
         pp.a[j] = a[j];
         pp.tiles_m[j] = ceil_div(a[j].M, BM);
-        pp.cols[j] = a[j].wpk_bytes > a[j].src_bytes && pp.tiles_n >= 8;
+        pp.cols[j] = a[j].wpk_bytes > a[j].src_bytes && a[j].src_bytes <= (4u << 20) && pp.tiles_n >= 8;
         pp.by[j] = make_div(pp.cols[j] ? pp.tiles_m[j] : pp.tiles_n);
         if (pp.tiles_m[j] > most) most = pp.tiles_m[j];
     }
