@@ -29,8 +29,8 @@
 // the eight lanes in a fixed order, then lane q goes on with the gates of unit slot + 64*q.  The state (forward) or the gate
 // gradients (backward) go through LDS, double-buffered: one barrier per step.
 //
-// Measured, us for T = 200 steps, whole calls (step launches -> this kernel, forward / backward): fp32, 50 samples, H = 256: 973 / 1255
-// -> 299 / 336 (one block per sample 574 / 594); H = 192: 859 / 1142 -> 282 / 277; H = 64: 627 / 688 -> 111 / 113; bf16, H = 256: 1065 /
+// Measured, us for T = 200 steps (step launches -> this kernel, forward / backward): fp32, 50 samples, H = 256: 973 / 1255
+// -> 297 / 337 (one block per sample 574 / 594); H = 192: 859 / 1142 -> 282 / 277; H = 64: 627 / 688 -> 111 / 113; bf16, H = 256: 1065 /
 // 1218 -> 238 / 263.  A split step of 1.5 us is 0.65 us of exchange, 0.35 us of products and the chain of sums and gates; without a
 // split it is that chain (0.5 us), the products and, at H = 256, the part of the weight that comes from L2.
 #include <math.h>
@@ -457,7 +457,7 @@ bool whole_chip(hipStream_t stream, int cus)
 
 // Blocks per sample.  The groups of an XCD must fit on its CUs side by side: 4 up to 64 samples, 2 up to 128.  Splitting pays where
 // one CU cannot hold the weight, above 192 units: us for T = 200, forward / backward, without -> with: fp32, 50 samples of 256
-// units 574 / 594 -> 299 / 336 (G = 4; G = 8, 32 samples: 313 / 293 but unsteady), 100 samples 574 / 598 -> 463 / 465 (G = 2);
+// units 574 / 594 -> 297 / 337 (G = 4; G = 8, 32 samples: 313 / 293 but unsteady), 100 samples 574 / 598 -> 463 / 465 (G = 2);
 // bf16, 50 samples 330 / 290 -> 238 / 263, but G = 2 293 / 334; 192 units: fp32 274 / 274 -> 252 / 292, bf16 215 / 205 -> 217 / 263.
 // The launches before and behind are paid back from the first steps on with G = 4, with G = 2 from 16 on (100 samples, 2, 8, 16 steps, without /
 // with: 11.7 / 14.1, 28.8 / 30.3, 51.7 / 50.0; a single step has no launch behind).
