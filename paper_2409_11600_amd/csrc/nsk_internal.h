@@ -144,6 +144,7 @@ struct IgemmArgs {
     // igemm_stats_rows() named the row count for exactly this launch.
     float *stats;
     int stats_rows;
+    bool packed;      // wpk was written by the launch before this one (backward-data)
     // Forward with the producing batch-norm and ReLU applied to the input on load: src holds the RAW output of the
     // previous convolution and the kernel multiplies relu(act[c]*src + act[Cs + c]) (zero padding stays zero).  Only
     // kernels for which igemm_act_fused() says yes take it; nullptr otherwise.
@@ -152,7 +153,6 @@ struct IgemmArgs {
     // writes zeros to the other (up to three) pixels of each row's 2x2 output cell.  Only the short-reduction kernel
     // honours it: set it only after conv_pw_applicable() said yes for these arguments.
     int zero_cell;
-    bool packed;      // wpk was written by the launch before this one (backward-data)
     // Grouped convolution (groups > 1; 0 or 1 = plain): the launch computes `groups` independent problems of the
     // shape above.  Group g reads channels [g*Cs, (g+1)*Cs) of source pixels that are src_ld channels apart, the filter
     // rows [g*Ngemm, (g+1)*Ngemm) of wpk, and writes columns [g*Ngemm, (g+1)*Ngemm) of the Co-channel output pixels.
