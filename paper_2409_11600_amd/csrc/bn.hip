@@ -301,6 +301,20 @@ template <int VEC, int THREADS = kBnThreads> __device__ inline Chunk chunk_of(in
     return k;
 }
 
+// Rows of a block: r = first + rr, first + rr + step, ... < end.  XCD: eighth e of the rows goes to the blocks that run on XCD e (blocks go to
+// the eight in turn, and gridDim.x is a multiple of eight), in the sums and in the apply pass, so that what the sums have read of a tensor is
+// still in that XCD's L2; the pipelined convolution kernels hand out their tiles alike.  Else the sums take their rows in one piece, the apply
+// pass in turn.  Backward, both passes, bf16, 64 images of 28x28x128 (12.8 MB each of x and dout) 18.4 -> 13.9 us.
+struct Walk {
+    long first, end, step;
+};
+template <bool XCD> __device__ inline Walk walk_rows(long M, int per)
+{
+    if (!XCD) return {(long)blockIdx.x * per, M, (long)gridDim.x * per};
+    const long share = (M + 7) >> 3, start = (long)(blockIdx.x & 7) * share;
+    return {start + (long)(blockIdx.x >> 3) * per, min(M, start + share), (long)(gridDim.x >> 3) * per};
+}
+
 // buf[g][o], g < n groups, o < W columns (n * W = `slots` threads' worth, both powers of two) -> buf[0][o], eight groups at a time, fixed order
 __device__ inline void fold_groups(double *buf, int n, int W)      // (n * W / 8 is at most the threads of the block)
 {
@@ -349,7 +363,7 @@ __device__ inline void chunk_sums(const float *__restrict__ p0, const float *__r
 
 // As bn_reduce_nhwc: per channel sum(f0) and sum(f1) over the rows of this block.  The ReLU mask of the backward pass is one byte per
 // vector: read (mask_in), or found from `out` (MODE 1) or from the coefficients `act` of an activation that was never stored (2), and kept.
-template <typename T, int VEC, int MODE, int THREADS>
+template <typename T, int VEC, int MODE, int THREADS, bool XCD>
 __global__ __launch_bounds__(THREADS) void bn_sums_fast(const T *__restrict__ x, const T *__restrict__ out, const T *__restrict__ dout,
                                                            const float *__restrict__ mean, const float *__restrict__ invstd, int relu,
                                                            long M, int C, long rows_per_block, float *__restrict__ p0, float *__restrict__ p1,
@@ -371,7 +385,9 @@ __global__ __launch_bounds__(THREADS) void bn_sums_fast(const T *__restrict__ x,
         // (the apply pass needs it in every block, and may be overwriting x)
         if (MODE == 0 && blockIdx.x == 0 && k.rr == 0) shift[ch + e] = sh[e];
     }
-    const long r_begin = (long)blockIdx.x * rows_per_block, r_end = min(M, r_begin + rows_per_block);
+    const Walk w = XCD ? walk_rows<true>(M, k.RP)
+                       : Walk{(long)blockIdx.x * rows_per_block, min(M, (long)(blockIdx.x + 1) * rows_per_block), k.RP};
+    const long step = XCD ? w.step : k.RP;
     if constexpr (MODE == 0) {
         // two chains, every other row each: beyond 16 M elements, where blocks of 256 threads would have been 2048, one chain would be twice as
         // long as theirs (invstd of 128 images of 112x112x128, bf16, against 64 bits: 2.9e-7 with one chain, 1.2e-7 with two, as with those blocks)
@@ -384,14 +400,14 @@ __global__ __launch_bounds__(THREADS) void bn_sums_fast(const T *__restrict__ x,
                 b[e] += dlt * dlt;
             }
         };
-        long r = r_begin + k.rr;
+        long r = w.first + k.rr;
 #pragma unroll 2
-        for (; r + k.RP < r_end; r += 2 * k.RP) {
-            const Vec even = *(const Vec *)(x + r * C + ch), odd = *(const Vec *)(x + (r + k.RP) * C + ch);
+        for (; r + step < w.end; r += 2 * step) {
+            const Vec even = *(const Vec *)(x + r * C + ch), odd = *(const Vec *)(x + (r + step) * C + ch);
             add(even, s0, s1);
             add(odd, t0, t1);
         }
-        if (r < r_end) add(*(const Vec *)(x + r * C + ch), s0, s1);
+        if (r < w.end) add(*(const Vec *)(x + r * C + ch), s0, s1);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
             s0[e] += t0[e];
@@ -399,7 +415,7 @@ __global__ __launch_bounds__(THREADS) void bn_sums_fast(const T *__restrict__ x,
         }
     } else {
 #pragma unroll 4
-        for (long r = r_begin + k.rr; r < r_end; r += k.RP) {
+        for (long r = w.first + k.rr; r < w.end; r += step) {
             const long off = r * C + ch;
             const Vec xv = *(const Vec *)(x + off), gv = *(const Vec *)(dout + off);
             unsigned bits = 0;
@@ -471,7 +487,7 @@ __device__ inline void finish_fwd(const BnFwdFinish &f, int c, double S, double 
     }
 }
 
-template <typename T, int VEC, bool HAS_RES, bool RELU>
+template <typename T, int VEC, bool HAS_RES, bool RELU, bool XCD>
 __global__ __launch_bounds__(kBnThreads) void bn_apply_fast(const T *__restrict__ x, const T *__restrict__ res, T *__restrict__ out, long M,
                                                             int C, unsigned char *__restrict__ mask, const BnFwdFinish f)
 {
@@ -489,8 +505,9 @@ __global__ __launch_bounds__(kBnThreads) void bn_apply_fast(const T *__restrict_
         sc[e] = coef[0][k.cv * VEC + e];
         bi[e] = coef[1][k.cv * VEC + e];
     }
+    const Walk w = walk_rows<XCD>(M, k.RP);
 #pragma unroll 2
-    for (long r = (long)blockIdx.x * k.RP + k.rr; r < M; r += (long)gridDim.x * k.RP) {
+    for (long r = w.first + k.rr; r < w.end; r += w.step) {
         const long off = r * C + k.c0 + k.cv * VEC;
         const Vec xv = __builtin_nontemporal_load((const Vec *)(x + off));
         Vec rv;
@@ -518,7 +535,7 @@ struct BnBwdFinish {
 };
 
 // dx = a*(dz - b - xhat*cc) with a = gamma*invstd, b = dbeta/M, cc = dgamma/M ; dres = dz
-template <typename T, int VEC, bool HAS_RES, bool RELU>
+template <typename T, int VEC, bool HAS_RES, bool RELU, bool XCD>
 __global__ __launch_bounds__(kBnThreads) void bn_bwd_apply_fast(const T *__restrict__ x, const T *__restrict__ dout, T *__restrict__ dx,
                                                                 T *__restrict__ dres, long M, int C, const unsigned char *__restrict__ mask,
                                                                 const BnBwdFinish f)
@@ -552,8 +569,9 @@ __global__ __launch_bounds__(kBnThreads) void bn_bwd_apply_fast(const T *__restr
         kb[e] = coef[3][c];
         kc[e] = coef[4][c];
     }
+    const Walk w = walk_rows<XCD>(M, k.RP);
 #pragma unroll 2
-    for (long r = (long)blockIdx.x * k.RP + k.rr; r < M; r += (long)gridDim.x * k.RP) {
+    for (long r = w.first + k.rr; r < w.end; r += w.step) {
         const long off = r * C + k.c0 + k.cv * VEC;
         const Vec xv = __builtin_nontemporal_load((const Vec *)(x + off));
         const Vec gv = __builtin_nontemporal_load((const Vec *)(dout + off));
@@ -849,11 +867,12 @@ template <typename T, typename F> void with_vec(const Geom &g, F f)
 int fast_chunk(const nsk_bn_desc_t &d) { return std::min(d.C, d.C > 128 ? kBnChunk : 64); }
 int fast_chunks(const nsk_bn_desc_t &d) { return d.C / fast_chunk(d); }
 int fast_rows_at_once(const nsk_bn_desc_t &d, int vec) { return kBnThreads / (fast_chunk(d) / vec); }
-// Up to 16 MB a tensor the apply blocks finish the sums; larger ones stream better through the many small blocks of the other channel
+// Up to 16 MB a tensor (backward 26) the apply blocks finish the sums; larger ones stream better through the many small blocks of the other channel
 // counts, which a block of 1024 threads per CU does not replace (both passes of a direction, us, finished in a launch of
 // its own / by the apply pass: forward behind a convolution bf16 2 MB 5.5 / 4.9, 13 MB 10.4 / 9.9, 26 MB 13.7 / 14.4, 51 MB 23.4 / 24.9;
-// backward with a mask 2 MB 11.3 / 9.8, 4 MB 14.2 / 10.5, 13 MB 21.0 / 19.2, 26 MB 29.4 / 29.1, 51 MB 50.4 / 51.7)
-bool apply_finishes(const nsk_bn_desc_t &d, const Geom &g) { return g.total * (long)elem_size(d.dtype) <= (16L << 20); }
+// backward with a mask, by_xcd, 64 .. 1024 channels bf16 16 MB 27.4-31.1 / 21.7-22.9, 20 MB 30.2-32.0 / 26.0-27.5, 25 MB 33.6-35.6 / 31.4-34.4, 32 MB 41.0-44.2 /
+// 38.5-46.2; fp32 20 MB 27.6-29.7 / 24.8-25.9, 25 MB 31.5-32.9 / 29.6-32.1, 32 MB 38.9-41.1 / 39.0-44.7)
+bool apply_finishes(const nsk_bn_desc_t &d, const Geom &g, bool backward) { return g.total * (long)elem_size(d.dtype) <= (backward ? 26L << 20 : 16L << 20); }
 int fast_sum_blocks(const nsk_bn_desc_t &d, const Geom &g)
 {
     const long passes = (g.M + fast_rows_at_once(d, g.vec) - 1) / fast_rows_at_once(d, g.vec);
@@ -900,42 +919,63 @@ bool fold_first(int stats_rows, const nsk_bn_desc_t &d, const Geom &g)
 {
     return g.G >= 16 && stats_rows > (d.C >= 512 ? 512 : 1024) && !rows_fit_apply(stats_rows, d);
 }
+// Sums and apply pass by eighths of the rows (walk_rows), where there are sums and the apply pass finishes them: from 4.1 MB on, where the apply pass
+// begins to miss what it needs in its own L2 (backward, 64 .. 1024 channels, us, rows in one piece / by eighths: bf16 4.0 MB 10.4-11.6 / 10.5-11.6, 4.2 MB
+// 14.0-14.9 / 10.8-12.7, 6 MB 15.4-16.3 / 11.6-12.4, 8 MB 16.2-17.9 / 11.9-12.9, 12 MB 20.4-21.4 / 14.3-15.6, 15.9 MB 27.6-30.2 / 21.5-23.2; fp32 4.0 MB 9.2-10.4 /
+// 9.2-10.5, 4.6 MB 12.5-13.3 / 10.1-10.9, 12 MB 18.2-19.3 / 12.8-14.2; forward with its own statistics, 12 MB 14.3-17.6 / 13.7-17.1, 15.9 MB 17.0-20.9 /
+// 15.3-18.9; behind a convolution, whose own blocks wrote x, no difference)
+bool by_xcd(const nsk_bn_desc_t &d, const Geom &g, bool finish)
+{
+    return finish && g.total * (long)elem_size(d.dtype) >= (4200L << 10) && fast_sum_blocks(d, g) % 8 == 0 && fast_apply_grid(d, g).x % 8 == 0;
+}
 template <typename T, int MODE, int THREADS>
-void launch_sums_fast(const nsk_bn_desc_t &d, const Geom &g, int G, const T *x, const T *out, const T *dout, const float *mean, const float *invstd,
+void launch_sums_fast(const nsk_bn_desc_t &d, const Geom &g, int G, bool xcd, const T *x, const T *out, const T *dout, const float *mean, const float *invstd,
                       float *p0, float *p1, unsigned char *mask, const unsigned char *mask_in, const float *act, float *shift, hipStream_t stream)
 {
     constexpr int VEC = 16 / (int)sizeof(T);
     const size_t lds = (size_t)THREADS * VEC * 2 * sizeof(float);
-    hipLaunchKernelGGL((bn_sums_fast<T, VEC, MODE, THREADS>), dim3(G, fast_chunks(d)), dim3(THREADS), lds, stream, x, out, dout, mean,
-                       invstd, d.relu, g.M, d.C, (g.M + G - 1) / G, p0, p1, mask, mask_in, act, shift);
+    auto go = [&](auto X) {
+        hipLaunchKernelGGL((bn_sums_fast<T, VEC, MODE, THREADS, X.value>), dim3(G, fast_chunks(d)), dim3(THREADS), lds, stream, x, out, dout, mean,
+                           invstd, d.relu, g.M, d.C, (g.M + G - 1) / G, p0, p1, mask, mask_in, act, shift);
+    };
+    if constexpr (THREADS == kBnThreads) {
+        if (xcd) return go(std::true_type{});
+    }
+    go(std::false_type{});
 }
 
 template <typename T>
-int bn_fwd_fast(const nsk_bn_desc_t &d, const Geom &g, const T *x, const T *res, T *out, unsigned char *relu_mask, const BnFwdFinish &f, hipStream_t stream)
+int bn_fwd_fast(const nsk_bn_desc_t &d, const Geom &g, bool xcd, const T *x, const T *res, T *out, unsigned char *relu_mask, const BnFwdFinish &f, hipStream_t stream)
 {
     constexpr int VEC = 16 / (int)sizeof(T);
 #define NSK_APPLY(R, L) \
-    hipLaunchKernelGGL((bn_apply_fast<T, VEC, R, L>), fast_apply_grid(d, g), dim3(kBnThreads), 0, stream, x, res, out, g.M, d.C, relu_mask, f)
-    if (res) {
-        if (d.relu) NSK_APPLY(true, true); else NSK_APPLY(true, false);
-    } else {
-        if (d.relu) NSK_APPLY(false, true); else NSK_APPLY(false, false);
-    }
+        hipLaunchKernelGGL((bn_apply_fast<T, VEC, R, L, X.value>), fast_apply_grid(d, g), dim3(kBnThreads), 0, stream, x, res, out, g.M, d.C, relu_mask, f)
+    auto go = [&](auto X) {
+        if (res) {
+            if (d.relu) NSK_APPLY(true, true); else NSK_APPLY(true, false);
+        } else {
+            if (d.relu) NSK_APPLY(false, true); else NSK_APPLY(false, false);
+        }
+    };
+    if (xcd) go(std::true_type{}); else go(std::false_type{});
 #undef NSK_APPLY
     return check_launch();
 }
 
 template <typename T>
-int bn_bwd_fast(const nsk_bn_desc_t &d, const Geom &g, const T *x, const T *dout, T *dx, T *dres, const unsigned char *mask, const BnBwdFinish &f, hipStream_t stream)
+int bn_bwd_fast(const nsk_bn_desc_t &d, const Geom &g, bool xcd, const T *x, const T *dout, T *dx, T *dres, const unsigned char *mask, const BnBwdFinish &f, hipStream_t stream)
 {
     constexpr int VEC = 16 / (int)sizeof(T);
 #define NSK_BAPPLY(R, L) \
-    hipLaunchKernelGGL((bn_bwd_apply_fast<T, VEC, R, L>), fast_apply_grid(d, g), dim3(kBnThreads), 0, stream, x, dout, dx, dres, g.M, d.C, mask, f)
-    if (dres) {
-        if (d.relu) NSK_BAPPLY(true, true); else NSK_BAPPLY(true, false);
-    } else {
-        if (d.relu) NSK_BAPPLY(false, true); else NSK_BAPPLY(false, false);
-    }
+        hipLaunchKernelGGL((bn_bwd_apply_fast<T, VEC, R, L, X.value>), fast_apply_grid(d, g), dim3(kBnThreads), 0, stream, x, dout, dx, dres, g.M, d.C, mask, f)
+    auto go = [&](auto X) {
+        if (dres) {
+            if (d.relu) NSK_BAPPLY(true, true); else NSK_BAPPLY(true, false);
+        } else {
+            if (d.relu) NSK_BAPPLY(false, true); else NSK_BAPPLY(false, false);
+        }
+    };
+    if (xcd) go(std::true_type{}); else go(std::false_type{});
 #undef NSK_BAPPLY
     return check_launch();
 }
@@ -948,8 +988,9 @@ int bn_fwd_typed(const nsk_bn_desc_t &d, const T *x, const T *res, const float *
     const Geom g = geometry(d, false);
     const bool fast = nhwc_fast(d) && (stats || own_sums_fast(d, g));
     // (with its own statistics at 16 MB sharp no longer: own_sums_fast)
-    bool finish = fast && apply_finishes(d, g) && (stats || g.total * (long)sizeof(T) < (16L << 20));
+    bool finish = fast && apply_finishes(d, g, false) && (stats || g.total * (long)sizeof(T) < (16L << 20));
     float *p0 = ws, *p1 = ws + (long)g.G * d.C, *scale = p1 + (long)g.G * d.C, *bias = scale + d.C;
+    const bool xcd = !stats && by_xcd(d, g, finish);
     const float *q0 = p0, *q1 = p1;
     int rows = fast ? fast_sum_blocks(d, g) : g.G;
     if (stats) {
@@ -970,7 +1011,7 @@ int bn_fwd_typed(const nsk_bn_desc_t &d, const T *x, const T *res, const float *
         }
         finish = finish && rows_fit_apply(rows, d);
     } else if (fast) {
-        launch_sums_fast<T, 0, kBnThreads>(d, g, rows, x, nullptr, nullptr, nullptr, nullptr, p0, p1, nullptr, nullptr, nullptr, scale, stream);
+        launch_sums_fast<T, 0, kBnThreads>(d, g, rows, xcd, x, nullptr, nullptr, nullptr, nullptr, p0, p1, nullptr, nullptr, nullptr, scale, stream);
     } else if (g.vec) {
         with_vec<T>(g, [&](auto V) {
             hipLaunchKernelGGL((bn_reduce_nhwc<T, V.value, 0>), dim3(g.G, g.chunks), dim3(256), 0, stream, x, (const T *)nullptr,
@@ -983,7 +1024,7 @@ int bn_fwd_typed(const nsk_bn_desc_t &d, const T *x, const T *res, const float *
                            g.sc, g.ss, g.npg, d.C, p0, p1);
     }
     const BnFwdFinish f{q0, q1, gamma, beta, stats ? nullptr : scale, save_mean, save_invstd, running_mean, running_var, (double)g.M, d.eps, d.momentum, rows};
-    if (finish) return bn_fwd_fast<T>(d, g, x, res, out, relu_mask, f, stream);
+    if (finish) return bn_fwd_fast<T>(d, g, xcd, x, res, out, relu_mask, f, stream);
     hipLaunchKernelGGL((bn_fwd_finalize<T>), dim3(d.C), dim3(256), 0, stream, q0, q1, rows, d.C, (double)g.M, stats ? (const T *)nullptr : x,
                        stats ? 0L : g.sc, gamma, beta, d.eps, d.momentum, save_mean, save_invstd, running_mean, running_var, scale, bias);
     if (g.vec) {
@@ -1023,14 +1064,15 @@ int bn_bwd_typed(const nsk_bn_desc_t &d, const T *x, const T *out, const T *dout
     // the ReLU mask bytes follow the float part of the workspace (see bn_mask_bytes)
     unsigned char *mask = (unsigned char *)ws + align_up((2 * (size_t)bn_partial_blocks(d) * d.C + 4 * (size_t)d.C) * sizeof(float));
     const unsigned char *kept = mask_in ? mask_in : mask;
-    const bool many = many_small_sums(d, g, mask_in != nullptr);
+    const bool finish = masked && apply_finishes(d, g, true), xcd = by_xcd(d, g, finish);
+    const bool many = !finish && many_small_sums(d, g, mask_in != nullptr);
     const int rows = masked && !many ? fast_sum_blocks(d, g) : many ? std::min(g.G, 512 / fast_chunks(d)) : g.G;
     if (masked && act) {
-        launch_sums_fast<T, 2, kBnThreads>(d, g, rows, x, out, dout, mean, invstd, p0, p1, mask, nullptr, act, nullptr, stream);
+        launch_sums_fast<T, 2, kBnThreads>(d, g, rows, xcd, x, out, dout, mean, invstd, p0, p1, mask, nullptr, act, nullptr, stream);
     } else if (masked && many) {
-        launch_sums_fast<T, 1, 256>(d, g, rows, x, out, dout, mean, invstd, p0, p1, mask, mask_in, nullptr, nullptr, stream);
+        launch_sums_fast<T, 1, 256>(d, g, rows, false, x, out, dout, mean, invstd, p0, p1, mask, mask_in, nullptr, nullptr, stream);
     } else if (masked) {
-        launch_sums_fast<T, 1, kBnThreads>(d, g, rows, x, out, dout, mean, invstd, p0, p1, mask, mask_in, nullptr, nullptr, stream);
+        launch_sums_fast<T, 1, kBnThreads>(d, g, rows, xcd, x, out, dout, mean, invstd, p0, p1, mask, mask_in, nullptr, nullptr, stream);
     } else if (g.vec) {
         with_vec<T>(g, [&](auto V) {
             hipLaunchKernelGGL((bn_reduce_nhwc<T, V.value, 1>), dim3(g.G, g.chunks), dim3(256), 0, stream, x, out, dout, mean, invstd,
@@ -1041,7 +1083,7 @@ int bn_bwd_typed(const nsk_bn_desc_t &d, const T *x, const T *out, const T *dout
                            invstd, d.relu, d.N, g.HW, g.sn, g.sc, g.ss, g.npg, d.C, p0, p1);
     }
     const BnBwdFinish f{p0, p1, gamma, mean, invstd, dgamma, dbeta, (double)g.M, rows};
-    if (masked && apply_finishes(d, g)) return bn_bwd_fast<T>(d, g, x, dout, dx, dres, kept, f, stream);
+    if (finish) return bn_bwd_fast<T>(d, g, xcd, x, dout, dx, dres, kept, f, stream);
     hipLaunchKernelGGL(bn_bwd_finalize, dim3(d.C), dim3(256), 0, stream, p0, p1, rows, d.C,
                        (double)g.M, gamma, invstd, dgamma, dbeta, coef);
     if (g.vec) {
