@@ -750,7 +750,7 @@ bool fs64_dgrad_s2_applicable(int dtype, const IgemmArgs *a, int count)
 bool fs64_fwd_s2_applicable(int dtype, const IgemmArgs &g)
 {
     if (dtype != NSK_BF16 || hooks().no_fs) return false;
-    if (g.Cs != 64 || g.Ngemm != 64 || g.Co != 64 || g.ntaps != 9 || g.Ktot != 576 || g.accumulate || g.zero_cell || g.groups > 1 || g.act) return false;
+    if (g.Cs != 64 || g.Ngemm != 64 || g.Co != 64 || g.ntaps != 9 || g.Ktot != 576 || g.accumulate || g.zero_cell || g.groups > 1) return false;
     if (g.mult_h != 2 || g.mult_w != 2 || g.add_h != -1 || g.add_w != -1 || g.osh != 1 || g.osw != 1 || g.oa != 0 || g.ob != 0) return false;
     if (g.Hs % 2 != 0 || g.Ws % 2 != 0 || g.Mi != g.Hs / 2 || g.Mj != g.Ws / 2 || g.Ho != g.Mi || g.Wo != g.Mj) return false;
     for (int t = 0; t < 9; ++t)

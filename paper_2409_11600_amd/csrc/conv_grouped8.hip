@@ -467,7 +467,7 @@ static int narrow_rows(const WgradArgs &a)
 bool narrow_wgrad_applicable(int dtype, const WgradArgs &a)
 {
     unsigned long long taps;
-    if (dtype != NSK_BF16 || a.groups > 1 || a.C != 16 || a.K != 16 || a.act || hooks().no_grouped8) return false;
+    if (dtype != NSK_BF16 || a.groups > 1 || a.C != 16 || a.K != 16 || hooks().no_grouped8) return false;
     if (a.sh != 1 || a.sw != 1 || a.P != a.H || a.Q != a.W || (long)a.L * 32 >= 0xF0000000L) return false;
     return window_taps(a, -a.ph, -a.pw, &taps) && a.L >= 65536 && narrow_rows(a) * a.W >= 256 && al16(a.x) && al16(a.dy);
 }

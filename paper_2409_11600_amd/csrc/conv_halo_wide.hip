@@ -804,7 +804,7 @@ IgemmArgs s2_as_plane_problem(const IgemmArgs &a)
 
 bool halo_wide_fwd_s2_applicable(int dtype, const IgemmArgs &a)
 {
-    if (dtype != NSK_BF16 || hooks().no_halo_wide || a.groups > 1 || a.accumulate || a.zero_cell || a.act) return false;
+    if (dtype != NSK_BF16 || hooks().no_halo_wide || a.groups > 1 || a.accumulate || a.zero_cell) return false;
     if (a.ntaps != 9 || (a.Cs != 128 && a.Cs != 256) || a.Ktot != 9 * a.Cs || a.Ngemm % 64 != 0 || a.Co % 8 != 0 || a.Co != a.Ngemm) return false;
     if (a.mult_h != 2 || a.mult_w != 2 || a.add_h != -1 || a.add_w != -1 || a.osh != 1 || a.osw != 1 || a.oa != 0 || a.ob != 0) return false;
     if (a.Hs % 2 != 0 || a.Ws % 2 != 0 || a.Mi != a.Hs / 2 || a.Mj != a.Ws / 2 || a.Ho != a.Mi || a.Wo != a.Mj || a.stats_rows < 0) return false;

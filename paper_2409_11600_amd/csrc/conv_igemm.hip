@@ -310,15 +310,6 @@ template <typename T> int launch_typed(const IgemmArgs &a, hipStream_t stream)
     }
 }
 
-// The fp32 64 -> 64 kernel gives every CU whole tiles of 8 image rows, 43 us each; the pipelined kernel takes 0.18 us a tile.
-// Measured (us, forward, 32x32): N=2 38.9 / 7.7, N=16 39.6 / 15.6, N=64 44.3 / 46, N=96 81.8 / 69, N=128 85-88 / 92.
-bool takes_halo64_f32(int dtype, const IgemmArgs &a)
-{
-    if (!halo64_f32_applicable(dtype, a)) return false;
-    const long tiles = (long)a.Nimg * (a.Hs / 8);
-    return hooks().halo64_always || (tiles + 255) / 256 * 256 * 100 <= tiles * 105;
-}
-
 }  // namespace
 
 int igemm_stats_rows(int dtype, const IgemmArgs &a)
@@ -330,7 +321,6 @@ int igemm_stats_rows(int dtype, const IgemmArgs &a)
     if (special) {
         if (tiny_src_applicable(dtype, a) || tiny_out_applicable(dtype, a)) return 0;   // no statistics epilogue there
         if (halo64_applicable(dtype, a)) return halo64_stats_rows(a);
-        if (takes_halo64_f32(dtype, a)) return halo64_f32_stats_rows(a);
         if (fs64_fwd_s2_applicable(dtype, a)) return fs64_fwd_s2_stats_rows(a);
         if (conv_pw_applicable(dtype, a)) return conv_pw_stats_rows(a);
         if (halo_wide_applicable(dtype, a)) return halo_wide_stats_rows(a);
@@ -341,14 +331,6 @@ int igemm_stats_rows(int dtype, const IgemmArgs &a)
     // 69.6 / 69.4, 64->128 1x1 stride 2 at 56x56 N=64 29.2 / 25.1, fp32 16->16 at 40x42 N=37 22.5 / 20.8, 72->104 at 29x37
     // N=20 34.0 / 20.5; 256->64 at 56x56 N=64, 3136 rows of sums, 50.1 / 51.5).
     return output_vectors(dtype, a) != 0 && vector_runs(dtype, a) ? igemm_pipe_stats_rows(dtype, a) : 0;
-}
-
-bool igemm_act_fused(int dtype, const IgemmArgs &a)
-{
-    // the same order of tests as launch_igemm, up to the kernels that have the fused load
-    if (a.M <= 0 || a.Ngemm <= 0 || a.accumulate || a.groups > 1 || a.zero_cell || hooks().igemm_tile != 0) return false;
-    if (tiny_src_applicable(dtype, a) || tiny_out_applicable(dtype, a) || halo64_applicable(dtype, a)) return false;
-    return takes_halo64_f32(dtype, a);   // (by size too: nsk_conv2d_stats_rows does not know of the activation)
 }
 
 // The residue classes of a strided backward-data pass in one launch of the pipelined kernel, if it is what each of them runs on.
@@ -381,7 +363,6 @@ int launch_igemm_pipe_multi(int dtype, const IgemmArgs *a, int count, hipStream_
 int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream)
 {
     if (a.M <= 0 || a.Ngemm <= 0) return NSK_OK;
-    if (a.act && !igemm_act_fused(dtype, a)) return NSK_ERR_BAD_DESC;   // the caller applies the activation itself
     const bool grouped = a.groups > 1;   // only the generic kernel knows about groups
     if (grouped && (a.groups > 65535 || a.src_ld != a.groups * a.Cs || a.zero_cell || a.stats)) return NSK_ERR_BAD_DESC;
     if (a.zero_cell) return launch_conv_pw(a, stream);   // the caller has checked that this kernel applies
@@ -389,7 +370,6 @@ int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream)
     if (special && tiny_src_applicable(dtype, a)) return launch_tiny_src(dtype, a, stream);
     if (special && tiny_out_applicable(dtype, a)) return launch_tiny_out(dtype, a, stream);
     if (special && halo64_applicable(dtype, a)) return launch_halo64(a, stream);
-    if (special && takes_halo64_f32(dtype, a)) return launch_halo64_f32(a, stream);
     if (special && fs64_fwd_s2_applicable(dtype, a)) return launch_fs64_fwd_s2(a, stream);
     if (special && conv_pw_applicable(dtype, a)) return launch_conv_pw(a, stream);
     if (special && halo_wide_applicable(dtype, a)) return launch_halo_wide(a, stream);

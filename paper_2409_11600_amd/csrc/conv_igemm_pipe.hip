@@ -21,7 +21,7 @@
 // halves: bf16 104 -> 100 at 28x28, N=32 18.6 -> 13.0 us against element-wise stores, 1x1 12 -> 36 at 56x56, N=64 40.5 -> 23.3.
 //
 // Measured against the one-tile-ahead kernel (us, forward): bf16 3x3 512->512 at 7x7, N=64 77.7 -> 27.2; fp32 3x3 72->100
-// at 29x37, N=20 80.8 -> 43.9; fp32 3x3 16->16 at 32x32, N=8 16.8 -> 5.7.  Without the exchange of pieces the first takes
+// at 29x37, N=20 80.8 -> 43.9 (and 33 on pieces, see the tiles); fp32 3x3 16->16 at 32x32, N=8 16.8 -> 5.7.  Without the exchange of pieces the first takes
 // 64 us (bank conflicts).
 #include <limits.h>
 
@@ -59,7 +59,7 @@ template <int NP> struct PipeProblems {   // NP = 1 or kMaxProblems: a plain lau
 };
 
 template <typename T, int BM, int BN, int WM, int WN, int WK, int ST, int NP>
-__global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const PipeProblems<NP> pp)
+__global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 4096 ? 2 : 1) void igemm_pipe_kernel(const PipeProblems<NP> pp)
 {
     const int prob = NP > 1 ? blockIdx.y : 0;   // (the problems of a launch differ in their pixels and taps)
     const IgemmArgs &a = pp.a[prob];
@@ -74,9 +74,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
     constexpr int LOADS = RA + RB;
     constexpr int TA = BM * PK_BYTES, TB = BN * PK_BYTES;
     constexpr int SROW = 32 * ES + 16;                  // epilogue: staged bytes per pixel (padded)
-    constexpr int EPI = NW * 32 * SROW + WM * WN * (WK - 1) * FM * FN * 4096;   // and the sums of the wavefronts wk > 0
-    constexpr int TA0 = TA > EPI ? TA : EPI;
+    constexpr int STRIPS = WM * WN * 32 * SROW, SUMS = WM * WN * (WK - 1) * FN * 4096;   // SUMS: of the wavefronts wk > 0
+    constexpr int EPI = STRIPS > SUMS ? STRIPS : SUMS, TA0 = TA > EPI ? TA : EPI;
     static_assert(ST == 3 || ST == 4, "stages");
+    constexpr bool SPLIT = ES == 4 && BM * BN >= 4096;   // fp32 products of bf16 pieces (small tiles make too little of each piece)
+    static_assert(!SPLIT || WK <= 2, "a k-tile of fp32 is two groups of 16");
 
     // one variable per stage and operand: the compiler keeps the reads of one apart from the direct loads into the others
     __shared__ __attribute__((aligned(1024))) unsigned char sa0[TA0], sa1[TA], sa2[TA], sa3[ST == 4 ? TA : 16];
@@ -131,11 +133,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
     }
     __syncthreads();
 
-    // This lane's rows of the activation tile: byte offset of the row's base pixel and one validity bit per tap.
+    // This lane's rows of the activation tile: byte offset of the row's base pixel and one bit per tap, set where the tap leaves the image.
+    // (Two words, not one of 64 bits: a 64-bit shift whose amount lies in the last register that the kernel has gave wrong masks in blocks
+    // that shared a CU.)
     const int lr = lane >> 3;
     const int piece = (lane & 7) ^ ((wave & 1) * 4 + (lr >> 1));
     unsigned a_base[RA];
-    unsigned long long a_mask[RA];
+    unsigned a_out[RA], a_out_hi[RA];                // taps 0..31, 32..63
     {
         int bh[RA], bw[RA];
 #pragma unroll
@@ -144,7 +148,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
             a_base[u] = s_base[row];
             bh[u] = s_bh[row];
             bw[u] = s_bw[row];
-            a_mask[u] = 0;
+            a_out[u] = a_out_hi[u] = 0;
         }
 #pragma unroll 1
         for (int t = 0; t < a.ntaps; ++t) {
@@ -152,17 +156,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
 #pragma unroll
             for (int u = 0; u < RA; ++u) {
                 const bool in = (unsigned)(bh[u] + oh) < (unsigned)a.Hs & (unsigned)(bw[u] + ow) < (unsigned)a.Ws;
-                a_mask[u] |= (unsigned long long)in << t;
+                const unsigned bit = in ? 0u : 1u << (t & 31);
+                a_out[u] |= t < 32 ? bit : 0u;
+                a_out_hi[u] |= t < 32 ? 0u : bit;
             }
         }
     }
     unsigned b_row[RB], b_bad[RB];
-#pragma unroll
-    for (int u = 0; u < RB; ++u) {
-        const int n = n0 + 8 * (wave + NW * u) + lr;
-        b_row[u] = (unsigned)((wrow0 + n) * a.Ktot * (long)ES) + (unsigned)(piece * 16);
-        b_bad[u] = n < a.Ngemm ? 0u : ~0u;
-    }
     const __amdgpu_buffer_rsrc_t src_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.src, 0, a.src_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t wpk_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a.wpk, 0, a.wpk_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t out_rsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -171,7 +171,17 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
     // position of this lane's piece inside (tap, channel), of the next k-tile to be requested; a k-tile further is
     // q_tap taps and r_c channels
     const int q_tap = BK / a.Cs, r_c = BK - q_tap * a.Cs;
-    int cur_tap = piece * VEC / a.Cs, cur_c = piece * VEC - cur_tap * a.Cs;
+    int cur_tap, cur_c;
+    auto start_requests = [&]() {
+        cur_tap = piece * VEC / a.Cs;
+        cur_c = piece * VEC - cur_tap * a.Cs;
+#pragma unroll
+        for (int u = 0; u < RB; ++u) {
+            const int n = n0 + 8 * (wave + NW * u) + lr;
+            b_row[u] = (unsigned)((wrow0 + n) * a.Ktot * (long)ES) + (unsigned)(piece * 16);
+            b_bad[u] = n < a.Ngemm ? 0u : ~0u;
+        }
+    };
     // Offsets are made out of range (reads: zeros, writes: dropped) with bit operations: a branch around a direct load
     // would split it in two.
     auto request = [&](auto S) {
@@ -181,7 +191,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
         const unsigned delta = s_delta[tap] + (unsigned)(cur_c * ES);
 #pragma unroll
         for (int u = 0; u < RA; ++u) {
-            const unsigned bad = ((unsigned)(a_mask[u] >> tap) & 1u) - 1u;
+            const unsigned bad = (unsigned)__builtin_amdgcn_sbfe((int)(tap & 32 ? a_out_hi[u] : a_out[u]), (unsigned)tap & 31u, 1u);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(src_rsrc, (lds_void *)&NSK_STAGE(I, sa)[(wave + NW * u) * 1024], 16,
                                                      (int)((a_base[u] + delta) | bad | k_bad), 0, 0, 0);
         }
@@ -204,42 +214,63 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
     const int frow = lane & 31, fk = lane >> 5, fsw = (frow >> 1) & 7;
     T *__restrict__ out = (T *)a.out;
     const int wcol0 = n0 + wn * (FN * 32), wrow = wm * (FM * 32);
-    f32x16 acc[FM][FN];
+    f32x16 acc[FM][FN], lo[FM][FN];    // lo: of the smaller products
+    auto start_sums = [&]() {
 #pragma unroll
-    for (int mi = 0; mi < FM; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < FN; ++ni)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
-    if (a.accumulate && a.vec_out && wk == 0) {
-        // start from the old values: the sum is then rounded to the storage type exactly once
-#pragma unroll
-        for (int mi = 0; mi < FM; ++mi) {
-            const unsigned off = s_out[wrow + mi * 32 + frow], off_bad = off == ~0u ? ~0u : 0u;
+        for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
             for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int col = wcol0 + ni * 32 + g * 8 + fk * 4;
-                    const int at = (int)((off + (unsigned)(col * ES)) | off_bad | (col < a.Ngemm ? 0u : ~0u));
-                    if constexpr (ES == 2) {
-                        const bf16x4 v = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(out_rsrc, at, 0, 0));
+                for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
+        if (a.accumulate && a.vec_out && wk == 0) {
+            // start from the old values: the sum is then rounded to the storage type exactly once
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) acc[mi][ni][g * 4 + j] = (float)v[j];
-                    } else {
-                        const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(out_rsrc, at, 0, 0));
+            for (int mi = 0; mi < FM; ++mi) {
+                const unsigned off = s_out[wrow + mi * 32 + frow], off_bad = off == ~0u ? ~0u : 0u;
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) acc[mi][ni][g * 4 + j] = v[j];
+                for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const int col = wcol0 + ni * 32 + g * 8 + fk * 4;
+                        const int at = (int)((off + (unsigned)(col * ES)) | off_bad | (col < a.Ngemm ? 0u : ~0u));
+                        if constexpr (ES == 2) {
+                            const bf16x4 v = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(out_rsrc, at, 0, 0));
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) acc[mi][ni][g * 4 + j] = (float)v[j];
+                        } else {
+                            const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(out_rsrc, at, 0, 0));
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) acc[mi][ni][g * 4 + j] = v[j];
+                        }
                     }
-                }
+            }
         }
-    }
+    };
 
     const int nk = (a.Ktot + BK - 1) / BK;
-    static_for<0, ST - 1>([&](auto S) { request(S); });   // (k-tiles past the end are requested out of range: zeros)
-    auto multiply = [&](auto S) {
+    // PIECES: fp32 products of bf16 pieces
+    auto multiply = [&](auto PIECES, auto S) {
         constexpr int I = S.value;
         const int oa = (wrow + frow) * PK_BYTES, ob = (wn * (FN * 32) + frow) * PK_BYTES;
+        if constexpr (decltype(PIECES)::value) {
+            // lane (row, half) holds two 16-byte pieces of a group of 16, the same two of both operands
+#pragma unroll
+            for (int i = 0; i < 2 / WK; ++i) {
+                const int g = wk * (2 / WK) + i, at0 = ((g * 4 + fk) ^ fsw) * 16, at1 = ((g * 4 + 2 + fk) ^ fsw) * 16;
+                auto split = [&](const unsigned char *row) {
+                    const f32x4 u = *(const f32x4 *)(row + at0), v = *(const f32x4 *)(row + at1);
+                    const float x[8] = {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
+                    return split3(x);
+                };
+                Pieces pa[FM], pb[FN];
+#pragma unroll
+                for (int mi = 0; mi < FM; ++mi) pa[mi] = split(&NSK_STAGE(I, sa)[oa + mi * 32 * PK_BYTES]);
+#pragma unroll
+                for (int ni = 0; ni < FN; ++ni) pb[ni] = split(&NSK_STAGE(I, sb)[ob + ni * 32 * PK_BYTES]);
+                multiply_pieces<true>(pb, pa, acc, lo);
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < 4 / WK; ++i) {
             const int ks = wk * (4 / WK) + i, at = (((ks * 2 + fk) ^ fsw) * 16);
@@ -266,66 +297,86 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
             }
         }
     };
-    // The loop body is ST steps without a branch, the remainder follows: where a step could leave the loop, the compiler
-    // would take the stage requested last for one that the first step reads, and wait for it.
+    auto products = [&](auto PIECES) {
+        start_requests();
+        start_sums();
+        static_for<0, ST - 1>([&](auto S) { request(S); });   // (k-tiles past the end are requested out of range: zeros)
+        // The loop body is ST steps without a branch, the remainder follows: where a step could leave the loop, the compiler
+        // would take the stage requested last for one that the first step reads, and wait for it.
 #define NSK_STEP(S)                                                                                              \
     wait_vm<(ST - 2) * LOADS>();  /* this wavefront's part of the k-tile has arrived */                          \
     __builtin_amdgcn_s_barrier(); /* everybody's has, and nobody reads the stage requested next any more */      \
     asm volatile("" ::: "memory");                                                                               \
     request(std::integral_constant<int, ((S) + ST - 1) % ST>{});                                                 \
-    multiply(std::integral_constant<int, (S)>{});
-    for (int n = nk / ST; n > 0; --n) {
-        NSK_STEP(0)
-        NSK_STEP(1)
-        NSK_STEP(2)
-        if constexpr (ST == 4) {
-            NSK_STEP(3)
+    multiply(PIECES, std::integral_constant<int, (S)>{});
+        for (int n = nk / ST; n > 0; --n) {
+            NSK_STEP(0)
+            NSK_STEP(1)
+            NSK_STEP(2)
+            if constexpr (ST == 4) {
+                NSK_STEP(3)
+            }
         }
-    }
 #undef NSK_STEP
-    // (the last ST - 1 k-tiles have been requested; what the loop requested past the end were zeros)
+        // (the last ST - 1 k-tiles have been requested; what the loop requested past the end were zeros)
 #define NSK_REST(S)                             \
     wait_vm<(ST - 2 - (S)) * LOADS>();          \
     __builtin_amdgcn_s_barrier();               \
     asm volatile("" ::: "memory");              \
-    multiply(std::integral_constant<int, (S)>{});
-    const int rest = nk % ST;
-    if (rest > 0) {
-        NSK_REST(0)
-    }
-    if (rest > 1) {
-        NSK_REST(1)
-    }
-    if constexpr (ST == 4) {
-        if (rest > 2) {
-            NSK_REST(2)
+    multiply(PIECES, std::integral_constant<int, (S)>{});
+        const int rest = nk % ST;
+        if (rest > 0) {
+            NSK_REST(0)
         }
-    }
+        if (rest > 1) {
+            NSK_REST(1)
+        }
+        if constexpr (ST == 4) {
+            if (rest > 2) {
+                NSK_REST(2)
+            }
+        }
 #undef NSK_REST
-    wait_vm<0>();          // (requests past the end still write zeros into LDS)
+        wait_vm<0>();          // (requests past the end still write zeros into LDS)
+    };
+    if constexpr (SPLIT) {
+#pragma unroll
+        for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) lo[mi][ni][v] = 0.f;
+    }
+    products(std::integral_constant<bool, SPLIT>{});
+    if constexpr (SPLIT) {
+#pragma unroll
+        for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[mi][ni][v] += lo[mi][ni][v];
+        if (__syncthreads_or(!plain_sums(acc))) products(std::integral_constant<bool, false>{});
+    }
     __syncthreads();
 
     if constexpr (WK > 1) {
-        // add the wavefronts of a group in a fixed order
-        float *red = (float *)(sa0 + NW * 32 * SROW);
-        static_assert(NW * 32 * SROW + WM * WN * (WK - 1) * FM * FN * 4 * 256 * (int)sizeof(float) <= (int)sizeof(sa0),
-                      "strips and partial sums lie inside the first stage");
+        // add the wavefronts of a group in a fixed order, one row of accumulator tiles at a time
+        float *red = (float *)sa0;
         const int slot = (wm * WN + wn) * (WK - 1);
-        if (wk > 0) {
 #pragma unroll
-            for (int mi = 0; mi < FM; ++mi)
+        for (int mi = 0; mi < FM; ++mi) {
+            if (mi > 0) __syncthreads();
+            if (wk > 0) {
 #pragma unroll
                 for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
                     for (int v = 0; v < 16; v += 4)
-                        *(f32x4 *)(red + ((((slot + wk - 1) * FM + mi) * FN + ni) * 4 + v / 4) * 256 + lane * 4) =
+                        *(f32x4 *)(red + (((slot + wk - 1) * FN + ni) * 4 + v / 4) * 256 + lane * 4) =
                             f32x4{acc[mi][ni][v], acc[mi][ni][v + 1], acc[mi][ni][v + 2], acc[mi][ni][v + 3]};
-        }
-        __syncthreads();
-        if (wk > 0) return;
-        // (0 + 1) + (2 + 3): two roundings deep, not three
-#pragma unroll
-        for (int mi = 0; mi < FM; ++mi)
+            }
+            __syncthreads();
+            if (wk > 0) continue;
+            // (0 + 1) + (2 + 3): two roundings deep, not three
 #pragma unroll
             for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
@@ -333,13 +384,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
                     f32x4 p[WK];
 #pragma unroll
                     for (int w = 1; w < WK; ++w)
-                        p[w] = *(const f32x4 *)(red + ((((slot + w - 1) * FM + mi) * FN + ni) * 4 + v / 4) * 256 + lane * 4);
+                        p[w] = *(const f32x4 *)(red + (((slot + w - 1) * FN + ni) * 4 + v / 4) * 256 + lane * 4);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         acc[mi][ni][v + j] += p[1][j];
                         if constexpr (WK == 4) acc[mi][ni][v + j] += p[2][j] + p[3][j];
                     }
                 }
+        }
+        __syncthreads();       // (the strips below lie where the sums were)
+        if (wk > 0) return;
     }
 
     if (a.vec_out) {
@@ -347,7 +401,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
         // the (now idle) first stage, and store 16 contiguous bytes per lane.
         typedef T T4 __attribute__((ext_vector_type(4)));
         constexpr int CPP = 32 * ES / 16;               // 16-byte chunks per pixel
-        unsigned char *my_st = sa0 + wave * (32 * SROW);
+        unsigned char *my_st = sa0 + (wm * WN + wn) * (32 * SROW);
         // Statistics epilogue (forward with a batch-norm behind it): a lane always reads back the same 16-byte piece
         // (VEC channels) of each staged row, so it adds those channels up over all the rows it stores; one cross-lane
         // reduction per block and one row of partial sums per wavefront row.
@@ -450,8 +504,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void igemm_pipe_kernel(const Pip
 // but the narrowest have eight.  128 x 64 has three stages, not four, where there are blocks enough to put two on a CU, which
 // fill while the other stores (median over those layers 0.76 of its time; 128 -> 64 on 75 k pixels 10.0 -> 7.5 us,
 // 256 -> 128 on 200 k 50 -> 35).
-// fp32 is bound by the matrix units (256 clocks per 32 x 32 and k-tile), so there small tiles, which spread evenly over
-// the CUs, win throughout.
+// fp32: tiles of 4096 outputs and more multiply bf16 pieces (nsk_internal.h), bound by the vector unit that makes them, so the sub-tile of a
+// wavefront is 64 x 64 or 64 x 32; smaller tiles, for layers that leave CUs idle otherwise, run on the fp32 matrix unit (256 clocks per 32 x 32
+// and k-tile).  Fitted to 260 forward passes of the same ranges: the choice is on average 1.8% off the best shape, 10% in the worst twentieth.
+// Forward, fp32 unit only / this, us: 3x3 64 -> 64 at 56x56, N=64 148 / 107; 128 -> 128 at 28x28, N=64 154 / 94; 72 -> 100 at 29x37,
+// N=20 45 / 33; 1x1 256 -> 768 on 10 k pixels 50 / 30; error against 64 bits 4.3e-7 / 1.0e-7, 4.2e-7 / 2.0e-7, 4.5e-7 / 1.0e-7, 2.9e-7 / 0.9e-7.
 struct PipeTile {
     int bm, bn, wm, wk;      // wm: wavefront rows = rows of statistics per tile; wk: parts a k-tile's sums are made in
     double step, rest, fixed, per_mb, stats;
@@ -459,8 +516,9 @@ struct PipeTile {
 constexpr PipeTile kTilesBf16[] = {{256, 128, 4, 1, 0.827, 4.71, 0.99, 0.017, 1.4}, {128, 128, 2, 1, 0.494, 3.15, 1.3, 0.219, 0},
                                    {256, 64, 4, 1, 0.587, 3.34, 0.92, 0.217, 0},    {128, 64, 4, 1, 0.302, 1.47, 2.96, 0.074, 0},
                                    {64, 64, 2, 2, 0.224, 2.12, 1.25, 0.251, 0},     {128, 32, 4, 1, 0.30, 0.9, 2.34, 0.162, 0}};
-constexpr PipeTile kTilesF32[] = {{64, 64, 2, 1, 0.575, 1.5, 0, 0, 0}, {128, 32, 4, 1, 0.575, 1.5, 0, 0, 0}, {64, 32, 2, 2, 0.29, 1.0, 0, 0, 0},
-                                  {32, 32, 1, 4, 0.145, 0.75, 0, 0, 0}};
+constexpr PipeTile kTilesF32[] = {{128, 64, 2, 2, 0.770, 1.96, 4.79, 0.238, 0}, {64, 64, 1, 2, 0.563, 0, 5.08, 0.361, 0},
+                                  {256, 128, 4, 1, 2.19, 6.83, 0, 0.039, 0},    {128, 32, 4, 1, 0.557, 1.01, 4.03, 0.255, 0},
+                                  {64, 32, 2, 2, 0.322, 0.73, 3.76, 0.258, 0},  {32, 32, 1, 4, 0.172, 0.68, 3.98, 0.23, 0}};
 
 long block_count(const PipeTile &t, const IgemmArgs *a, int count)
 {
@@ -549,9 +607,11 @@ int launch_igemm_pipe(int dtype, const IgemmArgs *a, int count, hipStream_t stre
         }
     }
     switch (cheapest(kTilesF32, 4, a, count, a->stats != nullptr)) {
-    case 0: return launch<float, 64, 64, 2, 2, 1, 4>(a, count, stream);
-    case 1: return launch<float, 128, 32, 4, 1, 1, 3>(a, count, stream);
-    case 2: return launch<float, 64, 32, 2, 1, 2, 4>(a, count, stream);
+    case 0: return launch<float, 128, 64, 2, 1, 2, 3>(a, count, stream);
+    case 1: return launch<float, 64, 64, 1, 2, 2, 3>(a, count, stream);
+    case 2: return launch<float, 256, 128, 4, 2, 1, 3>(a, count, stream);
+    case 3: return launch<float, 128, 32, 4, 1, 1, 3>(a, count, stream);
+    case 4: return launch<float, 64, 32, 2, 1, 2, 4>(a, count, stream);
     default: return launch<float, 32, 32, 1, 1, 4, 4>(a, count, stream);
     }
 }

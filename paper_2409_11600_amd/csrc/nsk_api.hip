@@ -68,15 +68,12 @@ void wgrad_geometry(const ConvGeo &g, WgradArgs *a)
         }
 }
 
-// The 3x3 64->64 kernels write 147 KB of partial sums per block, which only a long reduction pays for.  Measured against
-// the pipelined kernel (us): bf16 100 k rows 23.3 / 21.4, 200 k 30.0 / 32.7, 400 k 44 / 56; fp32 on 32-wide images 16 k
-// rows 29.6 / 21.9, 49 k 44.9 / 43.8, 66 k 53.0 / 55.0, 131 k 87 / 101.  act: the call applies a batch-norm on load,
-// which only these kernels do (elsewhere it costs a pass of its own).
-bool use_wgrad_halo(const ConvGeo &g, const WgradArgs &a, bool act)
+// The bf16 3x3 64->64 kernel writes 147 KB of partial sums per block, which only a long reduction pays for.  Measured against
+// the pipelined kernel (us): 100 k rows 23.3 / 21.4, 200 k 30.0 / 32.7, 400 k 44 / 56.
+bool use_wgrad_halo(const ConvGeo &g, const WgradArgs &a)
 {
     if (!wgrad_halo64_applicable(g.dtype, a) || hooks().no_halo) return false;
-    if (act && wgrad_halo64_act_fused(g.dtype, a)) return true;
-    return a.L >= (hooks().wh_min_rows >= 0 ? hooks().wh_min_rows : g.dtype == NSK_BF16 ? 150000 : 55000);
+    return hooks().halo64_always || a.L >= (hooks().wh_min_rows >= 0 ? hooks().wh_min_rows : 150000);
 }
 
 bool whole_vectors(const ConvGeo &g, int channels) { return channels % (g.dtype == NSK_BF16 ? 8 : 4) == 0; }
@@ -123,16 +120,14 @@ struct ConvPlan {
     bool grouped8 = false;   // wgrad: the kernel for groups of eight channels
     bool narrow = false;     // wgrad: the 3x3 kernel for 16 channels
     bool stem = false;   // the space-to-depth path plans its own workspace
-    size_t act_tmp = 0;  // fused-activation calls on a kernel without the fused load: the applied activation
-    bool act_fused = false;
+    size_t act_tmp = 0;  // calls that take a raw input: the applied activation
 };
 
 // groups > 1: grouped convolution (the filter holds C/groups input channels per output channel and only the generic
 // kernels run it).
 void fwd_geometry(const ConvGeo &g, IgemmArgs *a);
 
-// act: the call applies a batch-norm + ReLU to x on load (NHWC, one group); where the kernel that takes the layer has no
-// fused load the activation is applied into the workspace first.
+// act: the call applies a batch-norm + ReLU to x (NHWC, one group), into the workspace.
 ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = false, bool pad = true)
 {
     ConvPlan p;
@@ -147,19 +142,7 @@ ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = fal
         off += align_up(bytes);
         return at;
     };
-    if (act) {
-        // (the pointers only matter for alignment tests: every tensor of these calls is 16-byte aligned)
-        if (pass == NSK_PASS_FWD && !p.stem) {
-            IgemmArgs a{};
-            fwd_geometry(g, &a);
-            p.act_fused = igemm_act_fused(g.dtype, a);
-        } else if (pass == NSK_PASS_WGRAD && !p.stem) {
-            WgradArgs wa{};
-            wgrad_geometry(g, &wa);
-            p.act_fused = use_wgrad_halo(g, wa, true) && wgrad_halo64_act_fused(g.dtype, wa);
-        }
-        if (!p.act_fused) p.act_tmp = take(desc.x_elems * g.es);
-    }
+    if (act) p.act_tmp = take(desc.x_elems * g.es);
     if (p.stem) {
         p.total = off + stem_workspace_bytes(g, pass);
         return p;
@@ -181,9 +164,9 @@ ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = fal
         if (nchw || pad_k) p.act_in2 = take(g.y_elems * g.es);
         WgradArgs wa{};
         wgrad_geometry(g, &wa);
-        p.halo = groups == 1 && use_wgrad_halo(g, wa, act);
+        p.halo = groups == 1 && use_wgrad_halo(g, wa);
         if (p.halo)
-            p.splits = wgrad_halo64_partials(g.dtype, wa, nullptr);
+            p.splits = wgrad_halo64_partials(wa, nullptr);
         else {
             WgradArgs one = wa;   // one group's problem (aligned pointers and a split count stand for every launch)
             one.C = g.C / groups; one.K = g.K / groups;
@@ -327,7 +310,7 @@ int check_groups(const ConvGeo &g, int groups)
     return NSK_OK;
 }
 
-// The input of a fused-activation call as a batch-norm descriptor (for the apply pass of the unfused route).
+// The input of a fused-activation call as a batch-norm descriptor.
 nsk_bn_desc_t input_as_bn(const ConvGeo &g)
 {
     nsk_bn_desc_t d{};
@@ -360,10 +343,9 @@ int conv_fwd_impl(const nsk_conv_desc_t *desc, int groups, const void *x, const 
     NSK_TRY(check_ws(workspace, workspace_bytes, p.total));
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
-    if (act && !p.act_fused) {   // the kernel for this layer has no fused load: apply the activation first
+    if (act) {   // apply the activation first
         NSK_TRY(launch_bn_act(input_as_bn(g), x, act, ws + p.act_tmp, st));
         x = ws + p.act_tmp;
-        act = nullptr;
         if (p.stem) ws += align_up(g.x_elems * g.es);
     }
     bool fused = false;
@@ -408,7 +390,6 @@ int conv_fwd_impl(const nsk_conv_desc_t *desc, int groups, const void *x, const 
         a.stats = stats;
         a.stats_rows = rows;
     }
-    a.act = act;
     NSK_TRY(launch_igemm(g.dtype, a, st));
     if (stats && !fused) NSK_TRY(launch_bn_stats(output_as_bn(g), dst, stats, rows, st));
     if (nchw) NSK_TRY(launch_nhwc_to_nchw(g.dtype, dst, y, g.N, g.K, g.P, g.Q, 0, st));
@@ -689,10 +670,9 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     NSK_TRY(check_ws(workspace, workspace_bytes, p.total));
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
-    if (act && !p.act_fused) {   // the kernel for this layer has no fused load: apply the activation first
+    if (act) {   // apply the activation first
         NSK_TRY(launch_bn_act(input_as_bn(g), x, act, ws + p.act_tmp, st));
         x = ws + p.act_tmp;
-        act = nullptr;
         if (p.stem) ws += align_up(g.x_elems * g.es);
     }
     const bool nchw = g.layout == NSK_NCHW;
@@ -711,7 +691,6 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     if (nchw || pad_k) dys = ws + p.act_in2;
     WgradArgs a{};
     a.x = xs; a.dy = dys; a.part = (float *)(ws + p.part);
-    a.act = act;
     wgrad_geometry(gp, &a);
     a.rows_per_split = p.rows_per_split;
     a.splits = p.splits;
@@ -732,7 +711,7 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
         return launch_wgrad_pipe(g.dtype, a, st);
     }
     if (p.halo)
-        NSK_TRY(launch_wgrad_halo64(g.dtype, a, st));
+        NSK_TRY(launch_wgrad_halo64(a, st));
     else if (p.pipe)
         NSK_TRY(launch_wgrad_pipe(g.dtype, a, st));
     else if (p.grouped8)

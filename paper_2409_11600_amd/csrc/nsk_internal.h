@@ -70,6 +70,78 @@ inline Div make_div(int d)
 }
 __device__ inline int divide(int n, const Div &d) { return (int)(((unsigned long long)(unsigned)n * d.mul) >> d.sh); }
 
+// fp32 products on the bf16 matrix unit.  x = h + m + l exactly, three bf16 pieces (h to nearest, m cut, l what is left: 8 + 8 + 8 bits),
+// and x*y = hh' + (hm' + mh') + (mm' + hl' + lh') + terms below 2^-23 of it whose signs are those of the rests and cancel: six bf16
+// products of 16 indices in place of eight fp32 ones of 2, in 192 clocks instead of 512, and with fewer roundings of the sums.  What the
+// vector unit spends on the pieces, 11 instructions for two values, bounds it instead: a wavefront should multiply each piece it makes
+// several times.  Registers and LDS only, 4000 steps (fp32 operations, TFLOP/s; the fp32 unit's limit is 157): sub-tile of 64 x 64 243,
+// 64 x 32 214, 32 x 32 184 with four wavefronts a SIMD and 135 with two.
+// Limits: |x| from 2^-110 on is exact (below, the last piece leaves the range of bf16), and a value that is not finite, or above the
+// largest bf16, makes NaN.  A kernel looks at its sums (plain_sums) and makes them again on the fp32 unit where they are not plain.
+struct Pieces {
+    bf16x8 h, m, l;
+};
+__device__ __forceinline__ Pieces split3(const float (&x)[8])
+{
+    typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
+    struct Quad {
+        unsigned q[4];
+    } h, m, l;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = x[2 * i], b = x[2 * i + 1];
+        bf16x2 p;
+        p[0] = (bf16_t)a;
+        p[1] = (bf16_t)b;
+        h.q[i] = __builtin_bit_cast(unsigned, p);
+        asm("" : "+v"(h.q[i]));     // (else the compiler rounds a second time instead of shifting)
+        float ra = a - __builtin_bit_cast(float, h.q[i] << 16), rb = b - __builtin_bit_cast(float, h.q[i] & 0xffff0000u);
+        const unsigned ua = __builtin_bit_cast(unsigned, ra), ub = __builtin_bit_cast(unsigned, rb);
+        m.q[i] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);        // the upper halves of both
+        ra -= __builtin_bit_cast(float, ua & 0xffff0000u);
+        rb -= __builtin_bit_cast(float, ub & 0xffff0000u);
+        l.q[i] = __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, rb), __builtin_bit_cast(unsigned, ra), 0x07060302u);
+    }
+    return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+// hi + lo += sum over 16 indices of x[i] * y[j], x the matrix unit's first operand; sums at [i][j], or [j][i] where SECOND_ROWS.  Where lo is
+// not hi, the large products have accumulators of their own: a sum is then rounded at its full size once in 16 indices, not six times.
+template <bool SECOND_ROWS, int FX, int FY, int R, int C>
+__device__ __forceinline__ void multiply_pieces(const Pieces (&x)[FX], const Pieces (&y)[FY], f32x16 (&hi)[R][C], f32x16 (&lo)[R][C])
+{
+    static_assert(R == (SECOND_ROWS ? FY : FX) && C == (SECOND_ROWS ? FX : FY), "one sum a pair");
+#define NSK_PRODUCT(P, Q, S) S[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[i].P, y[j].Q, S[r][c], 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const int c = r & 1 ? C - 1 - k : k, i = SECOND_ROWS ? c : r, j = SECOND_ROWS ? r : c;
+            NSK_PRODUCT(h, l, lo)
+            NSK_PRODUCT(h, h, hi)
+            NSK_PRODUCT(l, h, lo)
+            NSK_PRODUCT(m, m, lo)
+            NSK_PRODUCT(h, m, lo)
+            NSK_PRODUCT(m, h, lo)
+        }
+#undef NSK_PRODUCT
+}
+// This lane's sums are finite and not all so small that operands below 2^-110 may have made them.
+template <int FM, int FN> __device__ __forceinline__ bool plain_sums(const f32x16 (&acc)[FM][FN])
+{
+    // largest magnitude by bits: infinities and NaN above all numbers
+    unsigned top = 0;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const unsigned u = __builtin_bit_cast(unsigned, acc[i][j][v]) & 0x7fffffffu;
+                top = u > top ? u : top;
+            }
+    return top < 0x7f800000u && (top == 0 || top >= (47u << 23));   // 2^-80
+}
+
 // Test and A/B switches: environment variables NSK_*, read ONCE (first use, or nsk_test_hooks_reload()) and never on
 // the launch path.  Each one only narrows or widens the choice among kernels that all compute the same result.
 struct TestHooks {
@@ -145,10 +217,6 @@ struct IgemmArgs {
     float *stats;
     int stats_rows;
     bool packed;      // wpk was written by the launch before this one (backward-data)
-    // Forward with the producing batch-norm and ReLU applied to the input on load: src holds the RAW output of the
-    // previous convolution and the kernel multiplies relu(act[c]*src + act[Cs + c]) (zero padding stays zero).  Only
-    // kernels for which igemm_act_fused() says yes take it; nullptr otherwise.
-    const float *act;
     // Backward-data of a stride-2 layer whose taps all fall into residue class (0, 0): the launch for that class also
     // writes zeros to the other (up to three) pixels of each row's 2x2 output cell.  Only the short-reduction kernel
     // honours it: set it only after conv_pw_applicable() said yes for these arguments.
@@ -162,8 +230,6 @@ struct IgemmArgs {
     short off_w[kMaxTaps];
 };
 int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream);
-// True if the kernel launch_igemm picks for these arguments applies IgemmArgs::act while it stages its input.
-bool igemm_act_fused(int dtype, const IgemmArgs &a);
 // Rows of partial sums the kernel launch_igemm would pick writes from its epilogue; 0 if that kernel has no
 // statistics epilogue (the caller then runs a separate reduction pass).  Host only, depends on the shape alone.
 int igemm_stats_rows(int dtype, const IgemmArgs &a);
@@ -203,10 +269,6 @@ int launch_fs64_fwd_s2(const IgemmArgs &a, hipStream_t stream);
 // the residue classes of one strided backward-data pass of such a layer in one launch, sharing the staged tiles
 bool halo_wide_multi_applicable(int dtype, const IgemmArgs *a, int count);
 int launch_halo_wide_multi(const IgemmArgs *a, int count, hipStream_t stream);
-// fp32 sibling (filter streamed one tap at a time through LDS)
-bool halo64_f32_applicable(int dtype, const IgemmArgs &a);
-int launch_halo64_f32(const IgemmArgs &a, hipStream_t stream);
-int halo64_f32_stats_rows(const IgemmArgs &a);
 
 // layers with at most four channels on one side (the 3-channel stride-1 image stem): direct kernels, no MFMA
 bool tiny_src_applicable(int dtype, const IgemmArgs &a);    // few source channels (forward)
@@ -240,9 +302,6 @@ struct WgradArgs {
     // and writes rows [g*K, (g+1)*K) of part[split][groups*K][ntaps*C].  Only the generic kernel runs such launches;
     // ldx and ldy are ignored (taken as C and K) for plain ones.
     int groups, ldx, ldy;
-    // nullptr, or [2][C]: x holds the RAW output of the producing convolution and the kernel uses
-    // relu(act[c]*x + act[C + c]); only where wgrad_halo64_act_fused() says yes
-    const float *act;
     short off_h[kMaxTaps];
     short off_w[kMaxTaps];
 };
@@ -252,11 +311,10 @@ int launch_wgrad(int dtype, const WgradArgs &a, hipStream_t stream);
 bool wgrad_pipe_applicable(int dtype, int C, int K, int groups);
 int wgrad_pipe_rows_per_split(int dtype, int L, int K, int ntapsC, int groups, int *splits);
 int launch_wgrad_pipe(int dtype, const WgradArgs &a, hipStream_t stream);   // groups, ldx, ldy set
-// 3x3 stride-1 64->64 special case: one [K][taps][C] partial per block, `partials` of them
+// bf16 3x3 stride-1 64->64 special case: one [K][taps][C] partial per block, `partials` of them
 bool wgrad_halo64_applicable(int dtype, const WgradArgs &a);
-int wgrad_halo64_partials(int dtype, const WgradArgs &a, int *chunks_per_block);
-int launch_wgrad_halo64(int dtype, const WgradArgs &a, hipStream_t stream);
-bool wgrad_halo64_act_fused(int dtype, const WgradArgs &a);
+int wgrad_halo64_partials(const WgradArgs &a, int *chunks_per_block);
+int launch_wgrad_halo64(const WgradArgs &a, hipStream_t stream);
 // at most four input channels: partial sums in the layout of the generic kernel
 bool tiny_wgrad_applicable(int dtype, const WgradArgs &a);
 int launch_tiny_wgrad(int dtype, const WgradArgs &a, hipStream_t stream);
