@@ -461,24 +461,7 @@ __global__ __launch_bounds__(256) void conv_fs64_fwd_s2_kernel(const F2Args a)
     // lane (prow, chunk) has counted channels 8*chunk .. 8*chunk+7 of the rows it stored: add up over prow, one row
     // of partial sums per wavefront
     auto write_stats = [&]() {
-        if constexpr (STATS) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-#pragma unroll
-                for (int o = 8; o < 64; o <<= 1) {
-                    ssum[e] += __shfl_xor(ssum[e], o, 64);
-                    ssq[e] += __shfl_xor(ssq[e], o, 64);
-                }
-            if (lane < 8) {
-                float *r0 = a.stats + (size_t)(blockIdx.x * 4 + x) * 64 + lane * 8;
-                float *r1 = r0 + (size_t)a.stats_rows * 64;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    r0[e] = ssum[e];
-                    r1[e] = ssq[e];
-                }
-            }
-        }
+        if constexpr (STATS) store_folded<8>(ssum, ssq, a.stats + (size_t)(blockIdx.x * 4 + x) * 64, (size_t)a.stats_rows * 64);
     };
     if (n <= 0) {                                                // uniform for the block: no barrier is skipped
         write_stats();                                           // zeros: every row of the buffer is written

@@ -303,22 +303,7 @@ __global__ __launch_bounds__(512) void conv_halo64_pp_kernel(const HaloArgs a)
     for (int e = 0; e < 8; ++e) ssum[e] = ssq[e] = 0.f;
     auto write_stats = [&]() {
         if (!a.stats) return;
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-            for (int o = 8; o < 64; o <<= 1) {
-                ssum[e] += __shfl_xor(ssum[e], o, 64);
-                ssq[e] += __shfl_xor(ssq[e], o, 64);
-            }
-        if (lane < 8) {
-            float *r0 = a.stats + (size_t)(blockIdx.x * 8 + wave) * 64 + lane * 8;
-            float *r1 = r0 + (size_t)a.stats_rows * 64;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                r0[e] = ssum[e];
-                r1[e] = ssq[e];
-            }
-        }
+        store_folded<8>(ssum, ssq, a.stats + (size_t)(blockIdx.x * 8 + wave) * 64, (size_t)a.stats_rows * 64);
     };
     if (n <= 0) {                                                // uniform for the block: no barrier is skipped
         write_stats();                                           // zeros: every row of the buffer is written
@@ -669,22 +654,7 @@ __global__ __launch_bounds__(256) void conv_fs64_kernel(const HaloArgs a)
     for (int e = 0; e < 8; ++e) ssum[e] = ssq[e] = 0.f;
     auto write_stats = [&]() {
         if (!STATS) return;
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-            for (int o = 8; o < 64; o <<= 1) {
-                ssum[e] += __shfl_xor(ssum[e], o, 64);
-                ssq[e] += __shfl_xor(ssq[e], o, 64);
-            }
-        if (lane < 8) {
-            float *r0 = a.stats + (size_t)(blockIdx.x * 4 + x) * 64 + lane * 8;
-            float *r1 = r0 + (size_t)a.stats_rows * 64;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                r0[e] = ssum[e];
-                r1[e] = ssq[e];
-            }
-        }
+        store_folded<8>(ssum, ssq, a.stats + (size_t)(blockIdx.x * 4 + x) * 64, (size_t)a.stats_rows * 64);
     };
     if (n <= 0) {                                                // uniform for the block: no barrier is skipped
         write_stats();                                           // zeros: every row of the buffer is written

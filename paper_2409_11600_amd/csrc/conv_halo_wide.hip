@@ -364,24 +364,7 @@ __global__ __launch_bounds__((MW + (MERGE ? 2 : 1)) * 64) __attribute__((amdgpu_
             }
             if (p + 1 < NT) read_back(p + 1);
         }
-        if (STATS) {
-            // lanes with the same lane % 4 hold the same 8 channels
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-#pragma unroll
-                for (int o = 4; o < 64; o <<= 1) {
-                    ssum[e] += __shfl_xor(ssum[e], o, 64);
-                    ssq[e] += __shfl_xor(ssq[e], o, 64);
-                }
-            if (lane < 4) {
-                float *r0p = a.stats + (size_t)tile * a.K + wcol0 + lane * 8;
-                float *r1p = r0p + (size_t)a.stats_rows * a.K;
-                *(f32x4 *)r0p = f32x4{ssum[0], ssum[1], ssum[2], ssum[3]};
-                *(f32x4 *)(r0p + 4) = f32x4{ssum[4], ssum[5], ssum[6], ssum[7]};
-                *(f32x4 *)r1p = f32x4{ssq[0], ssq[1], ssq[2], ssq[3]};
-                *(f32x4 *)(r1p + 4) = f32x4{ssq[4], ssq[5], ssq[6], ssq[7]};
-            }
-        }
+        if (STATS) store_folded<4>(ssum, ssq, a.stats + (size_t)tile * a.K + wcol0, (size_t)a.stats_rows * a.K);
     };
 
     // ---- main loop over the pieces.  The pixel fragments of k-step s+1 are read one by one behind the MFMAs of k-step

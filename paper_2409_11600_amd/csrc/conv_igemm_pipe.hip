@@ -76,13 +76,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
     constexpr int SROW = 32 * ES + 16;                  // epilogue: staged bytes per pixel (padded)
     constexpr int STRIPS = WM * WN * 32 * SROW, SUMS = WM * WN * (WK - 1) * FN * 4096;   // SUMS: of the wavefronts wk > 0
     constexpr int EPI = STRIPS > SUMS ? STRIPS : SUMS, TA0 = TA > EPI ? TA : EPI;
-    static_assert(ST == 3 || ST == 4, "stages");
+    static_assert(ST >= 2 && ST <= 4, "stages");
     constexpr bool SPLIT = ES == 4 && BM * BN >= 4096;   // fp32 products of bf16 pieces (small tiles make too little of each piece)
     static_assert(!SPLIT || WK <= 2, "a k-tile of fp32 is two groups of 16");
 
     // one variable per stage and operand: the compiler keeps the reads of one apart from the direct loads into the others
-    __shared__ __attribute__((aligned(1024))) unsigned char sa0[TA0], sa1[TA], sa2[TA], sa3[ST == 4 ? TA : 16];
-    __shared__ __attribute__((aligned(1024))) unsigned char sb0[TB], sb1[TB], sb2[TB], sb3[ST == 4 ? TB : 16];
+    __shared__ __attribute__((aligned(1024))) unsigned char sa0[TA0], sa1[TA], sa2[ST > 2 ? TA : 16], sa3[ST == 4 ? TA : 16];
+    __shared__ __attribute__((aligned(1024))) unsigned char sb0[TB], sb1[TB], sb2[ST > 2 ? TB : 16], sb3[ST == 4 ? TB : 16];
     __shared__ unsigned s_base[BM], s_out[BM];   // byte offsets of a row's base pixel in src and of its pixel in out (~0: none)
     __shared__ int s_bh[BM], s_bw[BM];
     __shared__ int s_oh[kMaxTaps], s_ow[kMaxTaps];
@@ -312,7 +312,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
         for (int n = nk / ST; n > 0; --n) {
             NSK_STEP(0)
             NSK_STEP(1)
-            NSK_STEP(2)
+            if constexpr (ST > 2) {
+                NSK_STEP(2)
+            }
             if constexpr (ST == 4) {
                 NSK_STEP(3)
             }
@@ -320,7 +322,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
 #undef NSK_STEP
         // (the last ST - 1 k-tiles have been requested; what the loop requested past the end were zeros)
 #define NSK_REST(S)                             \
-    wait_vm<(ST - 2 - (S)) * LOADS>();          \
+    wait_vm<(ST - 2 - (S) > 0 ? ST - 2 - (S) : 0) * LOADS>();          \
     __builtin_amdgcn_s_barrier();               \
     asm volatile("" ::: "memory");              \
     multiply(PIECES, std::integral_constant<int, (S)>{});
@@ -328,8 +330,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
         if (rest > 0) {
             NSK_REST(0)
         }
-        if (rest > 1) {
-            NSK_REST(1)
+        if constexpr (ST > 2) {
+            if (rest > 1) {
+                NSK_REST(1)
+            }
         }
         if constexpr (ST == 4) {
             if (rest > 2) {
@@ -404,7 +408,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
         unsigned char *my_st = sa0 + (wm * WN + wn) * (32 * SROW);
         // Statistics epilogue (forward with a batch-norm behind it): a lane always reads back the same 16-byte piece
         // (VEC channels) of each staged row, so it adds those channels up over all the rows it stores; one cross-lane
-        // reduction per block and one row of partial sums per wavefront row.
+        // reduction per block and one row of partial sums per wavefront row.  With every value added across all lanes by itself
+        // (64 exchanges per 32 channels, now 15) 256 -> 1024 1x1 on 25 k pixels took 45 us with statistics and 34 without.
         float ssum[FN][VEC], ssq[FN][VEC];
 #pragma unroll
         for (int ni = 0; ni < FN; ++ni)
@@ -437,9 +442,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
                         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out_rsrc, (int)at, 0, 0);
                     }
                     if (a.stats) {
+                        u32x4 q = __builtin_bit_cast(u32x4, v);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) q[e] &= ~bad;
+                        const Vec kept = __builtin_bit_cast(Vec, q);
 #pragma unroll
                         for (int e = 0; e < VEC; ++e) {
-                            const float f = bad ? 0.f : to_f(v[e]);
+                            const float f = to_f(kept[e]);
                             ssum[ni][e] += f;
                             ssq[ni][e] += f * f;
                         }
@@ -447,28 +456,21 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
                 }
             }
         if (a.stats) {
-            const int row = bm * WM + wm, ck = lane % CPP;
+            // (VEC channels' sums and squares over the 64 / CPP lanes of a piece: as many values as lanes)
+            static_assert(2 * VEC * CPP == 64, "a value a lane");
+            const int row = bm * WM + wm, which = lane / 32, e = lane / CPP % VEC;
+            float *r = a.stats + ((size_t)which * a.stats_rows + row) * a.Ngemm;
 #pragma unroll
             for (int ni = 0; ni < FN; ++ni) {
+                float v[2 * VEC];
 #pragma unroll
-                for (int e = 0; e < VEC; ++e)
-#pragma unroll
-                    for (int o = CPP; o < 64; o <<= 1) {
-                        ssum[ni][e] += __shfl_xor(ssum[ni][e], o, 64);
-                        ssq[ni][e] += __shfl_xor(ssq[ni][e], o, 64);
-                    }
-                const int col = wcol0 + ni * 32 + ck * VEC;
-                if (lane < CPP && col < a.Ngemm) {
-                    // 16-byte stores: a handful of lanes writing single floats would cost one memory instruction each
-                    float *r0 = a.stats + (size_t)row * a.Ngemm + col;
-                    float *r1 = r0 + (size_t)a.stats_rows * a.Ngemm;
-#pragma unroll
-                    for (int e = 0; e < VEC; e += 4) {
-                        if (col + e >= a.Ngemm) continue;
-                        *(f32x4 *)(r0 + e) = f32x4{ssum[ni][e], ssum[ni][e + 1], ssum[ni][e + 2], ssum[ni][e + 3]};
-                        *(f32x4 *)(r1 + e) = f32x4{ssq[ni][e], ssq[ni][e + 1], ssq[ni][e + 2], ssq[ni][e + 3]};
-                    }
+                for (int i = 0; i < VEC; ++i) {
+                    v[i] = ssum[ni][i];
+                    v[VEC + i] = ssq[ni][i];
                 }
+                fold_lanes<CPP>(v);
+                const int col = wcol0 + ni * 32 + lane % CPP * VEC + e;
+                if (col < a.Ngemm) r[col] = v[0];
             }
         }
     } else {
@@ -515,7 +517,9 @@ struct PipeTile {
 };
 constexpr PipeTile kTilesBf16[] = {{256, 128, 4, 1, 0.827, 4.71, 0.99, 0.017, 1.4}, {128, 128, 2, 1, 0.494, 3.15, 1.3, 0.219, 0},
                                    {256, 64, 4, 1, 0.587, 3.34, 0.92, 0.217, 0},    {128, 64, 4, 1, 0.302, 1.47, 2.96, 0.074, 0},
-                                   {64, 64, 2, 2, 0.224, 2.12, 1.25, 0.251, 0},     {128, 32, 4, 1, 0.30, 0.9, 2.34, 0.162, 0}};
+                                   {64, 64, 2, 2, 0.224, 2.12, 1.25, 0.251, 0},     {128, 32, 4, 1, 0.30, 0.9, 2.34, 0.162, 0}, 
+                                   {128, 128, 2, 1, 0, 0, 1e9, 0, 0}};   // kShort (taken by a rule, see cheapest)
+constexpr int kShort = 6;
 constexpr PipeTile kTilesF32[] = {{128, 64, 2, 2, 0.770, 1.96, 4.79, 0.238, 0}, {64, 64, 1, 2, 0.563, 0, 5.08, 0.361, 0},
                                   {256, 128, 4, 1, 2.19, 6.83, 0, 0.039, 0},    {128, 32, 4, 1, 0.557, 1.01, 4.03, 0.255, 0},
                                   {64, 32, 2, 2, 0.322, 0.73, 3.76, 0.258, 0},  {32, 32, 1, 4, 0.172, 0.68, 3.98, 0.23, 0}};
@@ -556,11 +560,18 @@ template <int N> int cheapest(const PipeTile (&tiles)[N], int es, const IgemmArg
         cost[i] = tiles[i].fixed + (rounds > bytes ? rounds : bytes);
         if (cost[i] < cost[best]) best = i;
     }
-    if (es != 2 || !stats || tiles[best].wk > 1) return best;   // (fp32: no shape gained)
+    // At most four k-tiles: three stages of 256 x 128, one block a CU, leave the loads of a block exposed in front of its stores.  Two stages of
+    // 128 x 128 let two blocks share a CU, one loading while the other stores, once there are more than two rounds of the larger blocks
+    // (us, larger / these, with statistics: 256 -> 1024 1x1 on 25 k pixels 36.8 / 34.3, 192 -> 768 on 40 k 38.7 / 35.4, 128 -> 512 on 100 k
+    // 50.8 / 47.6; 256 -> 512 on 25 k, 392 blocks, 20.7 / 20.1, without statistics 19.2 / 19.5; eight k-tiles, 512 -> 2048 on 6 k, 25.3 / 27.2).
+    auto short_reduction = [&](int i) {
+        return es == 2 && i == 0 && a[0].Ktot * 2 <= 4 * PK_BYTES && block_count(tiles[0], a, count) > 512 ? kShort : i;
+    };
+    if (es != 2 || !stats || tiles[best].wk > 1) return short_reduction(best);   // (fp32: no shape gained)
     for (int i = 0; i < N; ++i) cost[i] += tiles[i].stats + 1.5e-3 * ceil_div(a[0].M, tiles[i].bm) * tiles[i].wm;
     for (int i = 0; i < N; ++i)
         if (tiles[i].wk == 1 && cost[i] < cost[best]) best = i;
-    return best;
+    return short_reduction(best);
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int WK, int ST, int NP> int launch_np(const IgemmArgs *a, int count, hipStream_t stream)
@@ -603,6 +614,7 @@ int launch_igemm_pipe(int dtype, const IgemmArgs *a, int count, hipStream_t stre
             return block_count(kTilesBf16[3], a, count) > 256 ? launch<bf16_t, 128, 64, 4, 2, 1, 3>(a, count, stream)
                                                              : launch<bf16_t, 128, 64, 4, 2, 1, 4>(a, count, stream);
         case 4: return launch<bf16_t, 64, 64, 2, 2, 2, 3>(a, count, stream);
+        case kShort: return launch<bf16_t, 128, 128, 2, 4, 1, 2>(a, count, stream);
         default: return launch<bf16_t, 128, 32, 4, 1, 1, 3>(a, count, stream);
         }
     }

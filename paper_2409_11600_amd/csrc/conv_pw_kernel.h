@@ -310,25 +310,11 @@ __global__ __launch_bounds__(256, pw_blocks_per_cu(TAPS, NW)) void conv_pw_kerne
     if (!ACC && want_stats) {
         // lanes with equal (lane % CPP) hold the same channels: add them up; then the wavefronts' sums through their strips, in
         // order: one row of partial sums per block where it has all columns
-        const int ck = lane % CPP;
         float *const mine = (float *)my_st;              // [2][cols]
 #pragma unroll
         for (int nc = 0; nc < NCH; ++nc) {
             if (nc >= nch) break;
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-#pragma unroll
-                for (int o = CPP; o < 64; o <<= 1) {
-                    ssum[nc][e] += __shfl_xor(ssum[nc][e], o, 64);
-                    ssq[nc][e] += __shfl_xor(ssq[nc][e], o, 64);
-                }
-            if (lane < CPP) {
-                float *r0 = mine + nc * NW + ck * 8, *r1 = r0 + pa.cols;
-                *(f32x4 *)r0 = f32x4{ssum[nc][0], ssum[nc][1], ssum[nc][2], ssum[nc][3]};
-                *(f32x4 *)(r0 + 4) = f32x4{ssum[nc][4], ssum[nc][5], ssum[nc][6], ssum[nc][7]};
-                *(f32x4 *)r1 = f32x4{ssq[nc][0], ssq[nc][1], ssq[nc][2], ssq[nc][3]};
-                *(f32x4 *)(r1 + 4) = f32x4{ssq[nc][4], ssq[nc][5], ssq[nc][6], ssq[nc][7]};
-            }
+            store_folded<CPP>(ssum[nc], ssq[nc], mine + nc * NW, (size_t)pa.cols);
         }
         lds_barrier();
         const int pitch = (STRIP + (2 * TAPS + 2) * TM * 4) / 4;

@@ -142,6 +142,50 @@ template <int FM, int FN> __device__ __forceinline__ bool plain_sums(const f32x1
     return top < 0x7f800000u && (top == 0 || top >= (47u << 23));   // 2^-80
 }
 
+// Sums of N values over the lanes with the same lane % CPP.  Each step halves what a lane still carries: it hands the half that the other
+// lane goes on with over for the half that it goes on with itself (N/2 + N/4 + ... exchanges, where adding every value across all lanes
+// takes N a step, each an LDS operation; the first two steps, lanes 32 and 16 apart, are swaps of registers).  Afterwards lane l holds
+// value l / (64 / N) (N <= 64 / CPP), or the values (l / CPP) * (N * CPP / 64) + 0, 1, ... of its lanes in v[0], v[1], ...
+template <int CPP, int N, int O = 32, int LEFT = N> __device__ __forceinline__ void fold_lanes(float (&v)[N])
+{
+    if constexpr (O >= CPP) {
+        constexpr int H = LEFT / 2;
+        if constexpr (LEFT == 1) {
+            v[0] += __shfl_xor(v[0], O, 64);
+        } else if constexpr (O >= 16) {
+#pragma unroll
+            for (int i = 0; i < H; ++i) {
+                const unsigned a = __builtin_bit_cast(unsigned, v[i]), b = __builtin_bit_cast(unsigned, v[i + H]);
+                const auto r = O == 32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false) : __builtin_amdgcn_permlane16_swap(a, b, false, false);
+                v[i] = __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+            }
+        } else {
+            const bool upper = (threadIdx.x & O) != 0;
+#pragma unroll
+            for (int i = 0; i < H; ++i) v[i] = (upper ? v[i + H] : v[i]) + __shfl_xor(upper ? v[i] : v[i + H], O, 64);
+        }
+        fold_lanes<CPP, N, O / 2, (H > 0 ? H : 1)>(v);
+    }
+}
+
+// Statistics of a block's or a wavefront's stores: lane l has added up the 8 channels (l % CPP) * 8 .. + 7 of its rows.  r: a row of partial
+// sums from the first of those channels on, its squares `squares` floats further.
+template <int CPP> __device__ __forceinline__ void store_folded(const float (&sum)[8], const float (&sq)[8], float *r, size_t squares)
+{
+    constexpr int PER = CPP < 4 ? 1 : CPP / 4;      // values a lane ends up with
+    const int lane = threadIdx.x & 63, first = PER == 1 ? lane / 4 : lane / CPP * PER;
+    float v[16];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        v[e] = sum[e];
+        v[8 + e] = sq[e];
+    }
+    fold_lanes<CPP>(v);
+    r += (first >= 8 ? squares : 0) + lane % CPP * 8 + first % 8;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) r[i] = v[i];
+}
+
 // Test and A/B switches: environment variables NSK_*, read ONCE (first use, or nsk_test_hooks_reload()) and never on
 // the launch path.  Each one only narrows or widens the choice among kernels that all compute the same result.
 struct TestHooks {

@@ -161,3 +161,27 @@ def test_f32_64_to_64_kernel_below_its_size(accumulate, nsk_env):
     want = oracle.conv2d_dgrad(dy, w, x.shape, 1, 1, 1) + (x if accumulate else 0)
     dx = B.conv2d_dgrad(gdy, gw, x.shape, 1, 1, out=gx.clone(), accumulate=accumulate)
     assert max_rel_err(to_host(dx, B.NSK_NHWC), want) <= TOL["f32"]
+
+
+# Statistics of every kernel that leaves them: sums over lanes that hold 8 (fp32 4) channels of 64, 32 or 16, and the two-stage tile for short
+# reductions, forced (7) and by its rule (513 blocks of 256 x 128 and more).  Float sums of n stored values: sqrt(n) roundings of the largest.
+@pytest.mark.parametrize("tile,dtype,N,C,H,K,R,stride", [
+    (7, "bf16", 3, 40, 13, 136, 1, 1), (7, "bf16", 2, 64, 11, 72, 3, 1), (7, "bf16", 2, 16, 9, 264, 3, 2), (0, "bf16", 43, 64, 56, 136, 1, 1),
+    (0, "bf16", 9, 16, 33, 16, 3, 1), (0, "bf16", 9, 32, 33, 32, 3, 1), (0, "bf16", 40, 64, 48, 256, 1, 1), (0, "bf16", 5, 64, 56, 64, 3, 1),
+    (0, "bf16", 4, 128, 28, 128, 3, 1), (0, "bf16", 6, 64, 56, 64, 3, 2), (0, "bf16", 3, 3, 64, 64, 7, 2), (0, "f32", 4, 64, 32, 64, 3, 1)])
+def test_statistics_of_every_kernel(tile, dtype, N, C, H, K, R, stride, nsk_env):
+    if tile:
+        nsk_env("NSK_IGEMM_TILE", str(tile))
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((N, H, H, C), generator=g, device="cuda").to(torch_dtype(dtype))
+    w = (torch.randn((K, R, R, C), generator=g, device="cuda") * (2.0 / (C * R * R)) ** 0.5).to(torch_dtype(dtype))
+    y, stats = B.conv2d_fwd_stats(x, w, stride, R // 2, 1, B.NSK_NHWC)
+    plain = B.conv2d_fwd(x, w, stride, R // 2)
+    want = torch.nn.functional.conv2d(x.permute(0, 3, 1, 2).cpu().double(), w.permute(0, 3, 1, 2).cpu().double(), stride=stride, padding=R // 2)
+    got = y.permute(0, 3, 1, 2).cpu().double()
+    assert max_rel_err(got.numpy(), want.numpy()) <= TOL[dtype]
+    assert torch.equal(y, plain)
+    sums, n = stats.double().sum(1).cpu(), got[:, 0].numel()
+    bar = 6e-8 * n ** 0.5
+    assert float((sums[0] - got.sum((0, 2, 3))).abs().max()) <= bar * float((got ** 2).sum((0, 2, 3)).max()) ** 0.5 * n ** 0.5
+    assert float(((sums[1] - (got ** 2).sum((0, 2, 3))) / (got ** 2).sum((0, 2, 3))).abs().max()) <= bar
