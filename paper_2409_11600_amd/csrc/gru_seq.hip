@@ -12,9 +12,11 @@
 // G = 2 or 4 (few samples): each block owns H/G of the hidden units, so its part of the weight stays on the CU and a step's
 // products take 1/G of the time; what it pays is an exchange per step.  The exchange goes through the output itself (h forward,
 // dgh backward): a fill launch puts a NaN that no step stores in front of it, a block's gate lanes store their units with
-// agent-scope atomics, and a wavefront of its own per vector polls the others' values until none of them is that NaN, so value
-// and flag arrive together (a store and the load that sees it take 0.5 us on one XCD, 0.6 us across; the members of a group
-// are blocks b, b + 8, ..: one XCD when blocks go round the eight).  The pollers are wavefronts of their own because a
+// atomics, and a wavefront of its own per vector polls the others' values until none of them is that NaN, so value
+// and flag arrive together (a store of agent scope and the load that sees it take 0.45 us on one XCD, 0.63 us across; a store into the L2 of
+// the XCD and an agent-scope load there 0.22 us).  The members of a group are blocks b, b + 8, ..: one XCD when blocks go round the eight.
+// They tell each other theirs at the first steps, and a block whose readers all share its XCD stores into the L2 from then on; where
+// that did not reach a reader, it would give up like any other.  The pollers are wavefronts of their own because a
 // wavefront's loads return in order: behind the elementwise operands, which come from HBM, every poll would wait for those.
 // Waiting ends: members of a group are dispatched one after the other and hold no more CUs than the XCD has (split_of), and whole
 // groups wait for nobody else.  So of each launch at most one group an XCD, G - 1 blocks, waits for a block that has no CU yet: ten launches
@@ -30,8 +32,8 @@
 // gradients (backward) go through LDS, double-buffered: one barrier per step.
 //
 // Measured, us for T = 200 steps (step launches -> this kernel, forward / backward): fp32, 50 samples, H = 256: 973 / 1255
-// -> 297 / 337 (one block per sample 574 / 594); H = 192: 859 / 1142 -> 282 / 277; H = 64: 627 / 688 -> 111 / 113; bf16, H = 256: 1065 /
-// 1218 -> 238 / 263.  A split step of 1.5 us is 0.65 us of exchange, 0.35 us of products and the chain of sums and gates; without a
+// -> 277 / 314 (one block per sample 574 / 594; 303 / 336 with every exchange through memory); H = 192: 859 / 1142 -> 282 / 277; H = 64:
+// 627 / 688 -> 111 / 113; bf16, H = 256: 1065 / 1218 -> 232 / 264.  A split step of 1.4 - 1.6 us is 0.5 us of exchange, 0.35 us of products and the chain of sums and gates; without a
 // split it is that chain (0.5 us), the products and, at H = 256, the part of the weight that comes from L2.
 #include <math.h>
 
@@ -109,8 +111,10 @@ constexpr int kPolls = 1 << 20;               // failed polls of a wavefront bef
 // Polls cross the chip (650 ns there and back, whoever stores) and slow the stores that they wait for: a poll that comes too early
 // costs a second one, four on their way at a time cost 487 / 690 us where one alone costs 371 / 466.  So a poller sleeps before
 // its first poll of a step, in quarters of 64 clocks: 16 more after a first poll that failed, one less after every step
-// (against it 6 and 1 whole units -2 / +30 us, eighths 40 and 1 +5 / -7 us but unsteady).
+// (against it 6 and 1 whole units -2 / +30 us, eighths 40 and 1 +5 / -7 us but unsteady).  Polls of a group that shares an XCD end in its L2,
+// and a poller there does not sleep (8 samples 256 / 270 us, with 8 quarters more after a failed poll 266 / 279).
 constexpr int kSleepUp = 16, kSleepMost = 256;
+constexpr int kNearSteps = 4;                 // shortest sequence whose blocks tell each other their XCD
 
 // sum over the eight lanes of a group, in every lane: neighbours 1 and 2 away, then the mirrored lane of the other four
 __device__ inline float sum8(float v)
@@ -124,16 +128,28 @@ __device__ inline float sum8(float v)
     return v;
 }
 
-// values that blocks exchange: stored and loaded at agent scope
-__device__ inline void publish(float *p, float v)
+// values that blocks exchange: loaded at agent scope, which passes the CU's own cache by, and stored at that scope, which goes to memory, or,
+// where the group's blocks share an XCD (near), into the L2 that they share
+template <typename U> __device__ inline void publish_bits(U *p, U b, bool near)
 {
-    const unsigned b = v != v ? 0x7fc00000u : __builtin_bit_cast(unsigned, v);
-    __hip_atomic_store((unsigned *)p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (near)
+        __hip_atomic_store(p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else
+        __hip_atomic_store(p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ inline void publish(bf16_t *p, bf16_t v)
+__device__ inline void publish(float *p, float v, bool near)
 {
-    const unsigned short b = (float)v != (float)v ? (unsigned short)0x7fc0 : __builtin_bit_cast(unsigned short, v);
-    __hip_atomic_store((unsigned short *)p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    publish_bits((unsigned *)p, v != v ? 0x7fc00000u : __builtin_bit_cast(unsigned, v), near);
+}
+__device__ inline void publish(bf16_t *p, bf16_t v, bool near)
+{
+    publish_bits((unsigned short *)p, (float)v != (float)v ? (unsigned short)0x7fc0 : __builtin_bit_cast(unsigned short, v), near);
+}
+// A block's XCD as a value that no step stores (a NaN of another payload), in its lowest 4 bits
+template <typename U> __device__ inline U xcd_code()
+{
+    const unsigned xcd = __builtin_amdgcn_s_getreg(20 | 3 << 11);      // HW_REG_XCC_ID, bits 0..3
+    return (U)((sizeof(U) == 4 ? 0x7fc1a500u : 0x7fd0u) | xcd);
 }
 typedef unsigned long long u64;
 __device__ inline u64 seen(const void *p) { return __hip_atomic_load((const u64 *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -169,6 +185,7 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     T *const vec = (T *)smem;                                   // [2][NV][HP]: what the step multiplies
     V *const lw = (V *)(smem + 2 * NV * HP * sizeof(T));        // [LS][M][MT]
+    int *const near_lds = (int *)(lw + LS * M * MT);            // SPLIT: the group's blocks share an XCD
     const int tid = threadIdx.x, q = tid & 7, slot = tid >> 3, H = a.H, N = a.N;
     // SPLIT: groups of G blocks that lie eight apart
     const int n = SPLIT ? blockIdx.x / (8 * a.G) * 8 + blockIdx.x % 8 : blockIdx.x;
@@ -190,8 +207,25 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
         const int g = (tid - MT) >> 6, c = 4 * (tid & 63);
         const bool live = c < H;
         int left = a.polls, wait = 0;
-        bool gave_up = false;
+        bool gave_up = false, near = false;
+        // The blocks' XCDs, by way of a place each that only the last step stores to: no block gets there before all have looked.
+        typedef typename ST::U U;
+        U *const codes = BWD ? (U *)a.dgi + (long)n * 3 * H : (U *)a.saved + (long)(a.T - 1) * 4 * NH + (long)n * 4 * H;
+        const U code = xcd_code<U>();
+        if (g == 0 && tid == MT) {
+            *near_lds = 0;
+            if (a.T >= kNearSteps) __hip_atomic_store(codes + u0, code, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         for (int step = 0; step < a.T; ++step) {
+            if (step == 1 && g == 0 && a.T >= kNearSteps) {
+                const U *other = codes + (tid & 63) % a.G * a.HU;
+                U v = 0;
+                for (int i = 0; i < 64 && __any((v & (U)~15u) != (code & (U)~15u)); ++i)
+                    v = __hip_atomic_load(other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                near = !__any(v != code);
+                if (tid == MT) *near_lds = near;
+            }
+            if (step == 2 && g > 0) near = *near_lds;
             if (step > 0 && live) {
                 const int t = BWD ? a.T - step : step;          // the row that the step before this one has left
                 const T *src = BWD ? (const T *)a.dgh + (long)t * 3 * NH + (long)n * 3 * H + g * H + c : (const T *)a.h + (long)t * NH + (long)n * H + c;
@@ -208,7 +242,7 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
                     missing = __any(un);
                     if (missing) {
                         --left;
-                        if (first) wait = min(wait + kSleepUp, kSleepMost);
+                        if (first && !near) wait = min(wait + kSleepUp, kSleepMost);
                     }
                 }
                 if (wait > 0) wait -= 1;
@@ -286,13 +320,17 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
     // 566 / 594 us at H = 256 without a split, 119 / 113 -> 95 / 88 at H = 40; only one ahead at 192 units in fp32, which
     // has no registers left for more (274 / 274, 288 / 288 with two).
     constexpr int NE = BWD ? 5 : 3, D = sizeof(T) == 4 && M == 6 ? 1 : 2;
-    T e[D][NE];
+    // Forward in fp32, four blocks: and the place that the step's value will go to, which brings its line into the XCD's L2 (50 samples of 256
+    // units 286 -> 273 us; backward 301 -> 332, bf16 224 -> 240 and two blocks 457 -> 473, which need the registers or the loads' time).
+    constexpr int NP = SPLIT && !BWD && sizeof(T) == 4 && IU == 1 ? 1 : 0;
+    T e[D][NE + NP];
     auto operands = [&](T *to, int step) {
         const int t = BWD ? a.T - 1 - step : step;
         const T *p = BWD ? (const T *)a.saved_in + (long)t * 4 * NH + (long)n * 4 * H + ue : (const T *)a.gi + (long)t * 3 * NH + (long)n * 3 * H + ue;
 #pragma unroll
         for (int i = 0; i < (BWD ? 4 : 3); ++i) to[i] = p[i * H];
         if constexpr (BWD) to[NE - 1] = ((const T *)a.h)[(long)t * NH + at];
+        if constexpr (NP > 0) to[NE] = ((const T *)a.h)[(long)(t + 1) * NH + at];
     };
 #pragma unroll
     for (int k = 0; k < D; ++k) operands(e[k], min(k, a.T - 1));
@@ -306,10 +344,12 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
         auto take = [&] {
 #pragma unroll
             for (int i = 0; i < NE; ++i) ec[i] = e[k][i];
+            if constexpr (NP > 0) asm volatile("" ::"v"(e[k][NE]));
         };
         if constexpr (D == 1 || SPLIT) take();     // (waits here for what was requested; without a split the products come first)
         if constexpr (D == 1) operands(e[k], min(step + 1, a.T - 1));
         if constexpr (SPLIT) lds_barrier();
+        const bool near = SPLIT && *near_lds;
         float acc[S];
 #pragma unroll
         for (int p = 0; p < S; ++p) acc[p] = 0.f;
@@ -362,7 +402,7 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
                 state = (float)hn;
                 T *const hp = (T *)a.h + (long)(t + 1) * NH + at;
                 if constexpr (SPLIT) {
-                    publish(hp, hn);
+                    publish(hp, hn, near);
                 } else {
                     vn[u] = hn;
                     *hp = hn;
@@ -389,9 +429,9 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
                 const long g0 = (long)t * 3 * NH + (long)n * 3 * H + u;
                 T *dgi = (T *)a.dgi + g0, *dgh = (T *)a.dgh + g0;
                 if constexpr (SPLIT) {
-                    publish(dgh, tr);
-                    publish(dgh + H, tz);
-                    publish(dgh + 2 * H, tn);
+                    publish(dgh, tr, near);
+                    publish(dgh + H, tz, near);
+                    publish(dgh + 2 * H, tn, near);
                 } else {
                     vn[u] = tr;
                     vn[HP + u] = tz;
@@ -422,7 +462,7 @@ __global__ void unset_kernel(u64 *p, size_t n)
 template <typename T, bool BWD, int IU, int M, int RS, int LS, int SLOTS, bool SPLIT> int launch(const GruSeqArgs &a, hipStream_t stream)
 {
     constexpr int MT = 8 * SLOTS;
-    const size_t smem = 2 * (BWD ? 3 : 1) * 32 * M * sizeof(T) + (size_t)LS * M * MT * 4 * sizeof(T);
+    const size_t smem = 2 * (BWD ? 3 : 1) * 32 * M * sizeof(T) + (size_t)LS * M * MT * 4 * sizeof(T) + (SPLIT ? 16 : 0);
     static std::atomic<unsigned long long> done{0};
     if (smem > 64 * 1024) {
         const int rc = allow_lds((const void *)gru_seq_kernel<T, BWD, IU, M, RS, LS, SLOTS, SPLIT>, smem, done);
@@ -457,7 +497,8 @@ bool whole_chip(hipStream_t stream, int cus)
 
 // Blocks per sample.  The groups of an XCD must fit on its CUs side by side: 4 up to 64 samples, 2 up to 128.  Splitting pays where
 // one CU cannot hold the weight, above 192 units: us for T = 200, forward / backward, without -> with: fp32, 50 samples of 256
-// units 574 / 594 -> 297 / 337 (G = 4; G = 8, 32 samples: 313 / 293 but unsteady), 100 samples 574 / 598 -> 463 / 465 (G = 2);
+// units 574 / 594 -> 277 / 314 (G = 4; all exchanges through memory 297 / 337, and so with G = 8, 32 samples: 313 / 293 but unsteady), 100
+// samples 574 / 598 -> 460 / 455 (G = 2);
 // bf16, 50 samples 330 / 290 -> 238 / 263, but G = 2 293 / 334; 192 units: fp32 274 / 274 -> 252 / 292, bf16 215 / 205 -> 217 / 263.
 // The launches before and behind are paid back from the first steps on with G = 4, with G = 2 from 16 on (100 samples, 2, 8, 16 steps, without /
 // with: 11.7 / 14.1, 28.8 / 30.3, 51.7 / 50.0; a single step has no launch behind).

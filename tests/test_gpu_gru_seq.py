@@ -207,3 +207,30 @@ def test_gates_at_the_ends_of_their_range(H):
         want, have = f(x[:, k * H:(k + 1) * H] + (0 * torch.sigmoid(x[:, :H]) if k == 2 else 0)), got[:, k * H:(k + 1) * H]
         assert torch.equal(torch.isnan(want), torch.isnan(have))
         assert ((want - have).nan_to_num().abs() <= 2.0 ** -22 * want.nan_to_num().abs() + 2.0 ** -126).all()
+
+
+# Blocks that share a sample: sequences too short to tell each other their XCD, the shortest that do, and longer ones, against one block a
+# sample.  (Forward the same products in the same order; the sums of the backward pass too.)
+@pytest.mark.parametrize("dtype,N,H", [("f32", 9, 256), ("f32", 70, 224), ("bf16", 5, 200)])
+@pytest.mark.parametrize("T", [2, 3, 4, 5, 17])
+def test_exchange_between_blocks(T, N, H, dtype, nsk_env):
+    dt = torch_dtype(dtype)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    r = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    gi, w, b_ih, b_hh = r(T, N, 3 * H).to(dt), (r(3 * H, H) / H ** 0.5).to(dt), 0.3 * r(3 * H), 0.3 * r(3 * H)
+    h0, dh, wt = r(N, H).to(dt), r(N, H).to(dt), None
+    wt = w.t().contiguous()
+    got = []
+    for split in (None, "1"):
+        nsk_env("NSK_GRU_SPLIT", split) if split else None
+        h = torch.full((T + 1, N, H), 7.0, device="cuda", dtype=dt)
+        h[0] = h0
+        saved = torch.full((T, N, 4 * H), 7.0, device="cuda", dtype=dt)
+        dgi, dgh, scratch = torch.full((T, N, 3 * H), 7.0, device="cuda", dtype=dt), torch.full((T, N, 3 * H), 7.0, device="cuda", dtype=dt), torch.empty((2, N, H), device="cuda", dtype=dt)
+        B.gru_seq_fwd(gi, w, b_ih, b_hh, h, saved)
+        B.gru_seq_bwd(saved, h, dh, wt, dgi, dgh, scratch)
+        torch.cuda.synchronize()
+        got.append((h, saved, dgi, dgh))
+    for a, b in zip(*got):
+        assert torch.isfinite(a.float()).all()
+        assert max_rel_err(host(a), host(b)) <= TOL[dtype]
