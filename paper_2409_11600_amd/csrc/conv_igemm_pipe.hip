@@ -215,7 +215,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
     T *__restrict__ out = (T *)a.out;
     const int wcol0 = n0 + wn * (FN * 32), wrow = wm * (FM * 32);
     f32x16 acc[FM][FN], lo[FM][FN];    // lo: of the smaller products
-    auto start_sums = [&]() {
+    auto start_sums = [&](float scale) {
 #pragma unroll
         for (int mi = 0; mi < FM; ++mi)
 #pragma unroll
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
                         } else {
                             const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(out_rsrc, at, 0, 0));
 #pragma unroll
-                            for (int j = 0; j < 4; ++j) acc[mi][ni][g * 4 + j] = v[j];
+                            for (int j = 0; j < 4; ++j) acc[mi][ni][g * 4 + j] = v[j] * scale;
                         }
                     }
             }
@@ -257,16 +257,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
 #pragma unroll
             for (int i = 0; i < 2 / WK; ++i) {
                 const int g = wk * (2 / WK) + i, at0 = ((g * 4 + fk) ^ fsw) * 16, at1 = ((g * 4 + 2 + fk) ^ fsw) * 16;
-                auto split = [&](const unsigned char *row) {
+                auto split = [&](const unsigned char *row, auto SCALED) {
                     const f32x4 u = *(const f32x4 *)(row + at0), v = *(const f32x4 *)(row + at1);
                     const float x[8] = {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
-                    return split3(x);
+                    return split3<decltype(SCALED)::value>(x);
                 };
                 Pieces pa[FM], pb[FN];
 #pragma unroll
-                for (int mi = 0; mi < FM; ++mi) pa[mi] = split(&NSK_STAGE(I, sa)[oa + mi * 32 * PK_BYTES]);
+                for (int mi = 0; mi < FM; ++mi) pa[mi] = split(&NSK_STAGE(I, sa)[oa + mi * 32 * PK_BYTES], std::true_type{});
 #pragma unroll
-                for (int ni = 0; ni < FN; ++ni) pb[ni] = split(&NSK_STAGE(I, sb)[ob + ni * 32 * PK_BYTES]);
+                for (int ni = 0; ni < FN; ++ni) pb[ni] = split(&NSK_STAGE(I, sb)[ob + ni * 32 * PK_BYTES], std::false_type{});
                 multiply_pieces<true>(pb, pa, acc, lo);
             }
             return;
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
     };
     auto products = [&](auto PIECES) {
         start_requests();
-        start_sums();
+        start_sums(decltype(PIECES)::value ? kPieceScale : 1.f);
         static_for<0, ST - 1>([&](auto S) { request(S); });   // (k-tiles past the end are requested out of range: zeros)
         // The loop body is ST steps without a branch, the remainder follows: where a step could leave the loop, the compiler
         // would take the stage requested last for one that the first step reads, and wait for it.
@@ -358,8 +358,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
 #pragma unroll
             for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[mi][ni][v] += lo[mi][ni][v];
-        if (__syncthreads_or(!plain_sums(acc))) products(std::integral_constant<bool, false>{});
+                for (int v = 0; v < 16; ++v) acc[mi][ni][v] = (acc[mi][ni][v] + lo[mi][ni][v]) * (1.f / kPieceScale);
+        if (__syncthreads_or(!finite_sums(acc))) products(std::integral_constant<bool, false>{});
     }
     __syncthreads();
 

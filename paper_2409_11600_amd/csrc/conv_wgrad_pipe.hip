@@ -172,16 +172,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WK == 2 ? 2 : 1) void wgrad_pipe
             // lane (channel, half) holds pixels half, half + 2, ... of its group of 16, the same of both operands
             Pieces pa[FM], pb[FN];
             const int g = wk * 16;
-            auto split = [&](const unsigned char *col, auto ROW) {
+            auto split = [&](const unsigned char *col, auto ROW, auto SCALED) {
                 float x[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) x[e] = *(const float *)(col + (g + 2 * e) * ROW.value);
-                return split3(x);
+                return split3<decltype(SCALED)::value>(x);
             };
 #pragma unroll
-            for (int i = 0; i < FM; ++i) pa[i] = split(&NSK_STAGE(I, sa)[fa[i]], std::integral_constant<int, RBA>{});
+            for (int i = 0; i < FM; ++i) pa[i] = split(&NSK_STAGE(I, sa)[fa[i]], std::integral_constant<int, RBA>{}, std::true_type{});
 #pragma unroll
-            for (int i = 0; i < FN; ++i) pb[i] = split(&NSK_STAGE(I, sx)[fx[i]], std::integral_constant<int, RBX>{});
+            for (int i = 0; i < FN; ++i) pb[i] = split(&NSK_STAGE(I, sx)[fx[i]], std::integral_constant<int, RBX>{}, std::false_type{});
             multiply_pieces<false>(pa, pb, acc[0], sum);
         } else if constexpr (ES == 2) {
 #pragma unroll
@@ -311,7 +311,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WK == 2 ? 2 : 1) void wgrad_pipe
     };
     products(std::integral_constant<bool, SPLIT>{});
     if constexpr (SPLIT) {
-        if (__syncthreads_or(!plain_sums(sum))) products(std::integral_constant<bool, false>{});
+#pragma unroll
+        for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < FN; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sum[mi][ni][v] *= 1.f / kPieceScale;
+        if (__syncthreads_or(!finite_sums(sum))) products(std::integral_constant<bool, false>{});
         // the second wavefront of a pair hands its sums to the first, one accumulator tile at a time
         static_assert(WM * WN * 4096 <= KT * RBX, "inside a stage");
         float *red = (float *)sx0 + (wm * WN + wn) * 1024 + lane * 4;

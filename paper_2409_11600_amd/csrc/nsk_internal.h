@@ -76,12 +76,15 @@ __device__ inline int divide(int n, const Div &d) { return (int)(((unsigned long
 // vector unit spends on the pieces, 11 instructions for two values, bounds it instead: a wavefront should multiply each piece it makes
 // several times.  Registers and LDS only, 4000 steps (fp32 operations, TFLOP/s; the fp32 unit's limit is 157): sub-tile of 64 x 64 243,
 // 64 x 32 214, 32 x 32 184 with four wavefronts a SIMD and 135 with two.
-// Limits: |x| from 2^-110 on is exact (below, the last piece leaves the range of bf16), and a value that is not finite, or above the
-// largest bf16, makes NaN.  A kernel looks at its sums (plain_sums) and makes them again on the fp32 unit where they are not plain.
+// Limits: |x| from 2^-110 on is exact (below, the last piece leaves the range of bf16).  Gradients that vanish over a long sequence get there,
+// so the activation or gradient of a pass is multiplied by 2^24 first (SCALED: exact from 2^-134 on; filters, and x in backward-weight, are
+// not) and its sums by 2^-24 at the end.  A value that is not finite, or too large for that, makes sums that are not finite: a kernel that
+// sees such (finite_sums) makes them again on the fp32 unit.
 struct Pieces {
     bf16x8 h, m, l;
 };
-__device__ __forceinline__ Pieces split3(const float (&x)[8])
+constexpr float kPieceScale = 16777216.f;
+template <bool SCALED> __device__ __forceinline__ Pieces split3(const float (&x)[8])
 {
     typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
     struct Quad {
@@ -89,7 +92,7 @@ __device__ __forceinline__ Pieces split3(const float (&x)[8])
     } h, m, l;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float a = x[2 * i], b = x[2 * i + 1];
+        const float a = SCALED ? x[2 * i] * kPieceScale : x[2 * i], b = SCALED ? x[2 * i + 1] * kPieceScale : x[2 * i + 1];
         bf16x2 p;
         p[0] = (bf16_t)a;
         p[1] = (bf16_t)b;
@@ -125,8 +128,8 @@ __device__ __forceinline__ void multiply_pieces(const Pieces (&x)[FX], const Pie
         }
 #undef NSK_PRODUCT
 }
-// This lane's sums are finite and not all so small that operands below 2^-110 may have made them.
-template <int FM, int FN> __device__ __forceinline__ bool plain_sums(const f32x16 (&acc)[FM][FN])
+// This lane's sums are all finite.
+template <int FM, int FN> __device__ __forceinline__ bool finite_sums(const f32x16 (&acc)[FM][FN])
 {
     // largest magnitude by bits: infinities and NaN above all numbers
     unsigned top = 0;
@@ -139,7 +142,7 @@ template <int FM, int FN> __device__ __forceinline__ bool plain_sums(const f32x1
                 const unsigned u = __builtin_bit_cast(unsigned, acc[i][j][v]) & 0x7fffffffu;
                 top = u > top ? u : top;
             }
-    return top < 0x7f800000u && (top == 0 || top >= (47u << 23));   // 2^-80
+    return top < 0x7f800000u;
 }
 
 // Sums of N values over the lanes with the same lane % CPP.  Each step halves what a lane still carries: it hands the half that the other
