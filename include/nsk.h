@@ -152,6 +152,32 @@ int nsk_conv2d_dgrad(const nsk_conv_desc_t *desc, const void *dy, const void *w,
 int nsk_conv2d_wgrad(const nsk_conv_desc_t *desc, const void *x, const void *dy, float *dw,
                      int accumulate, void *workspace, size_t workspace_bytes, void *stream);
 
+/* ---- The same for the many small layers of one backward pass: one launch packs the filters of all of them, one adds up the partial
+ * sums of all of them, where each layer's own calls launch both (2.5-4 us each, more than the work).  NHWC.  Results are bitwise
+ * those of nsk_conv2d_dgrad and nsk_conv2d_wgrad.
+ *
+ * nsk_conv2d_packed_filter_bytes / nsk_conv2d_wgrad_partial_bytes: size of a layer's packed filter / of its partial sums, or 0 if it
+ *   takes no part (other layouts, channel counts that are copied to whole vectors, the image stem, filters of 140000 elements and
+ *   more or of more than nine taps, strides with more than four residue classes; partial sums above 16 MB, or none): such a layer
+ *   keeps its own calls.  Host only.
+ * nsk_conv2d_pack_filters: items[i].dst (16-byte aligned, that many bytes) = the filter items[i].src of items[i].desc.  To be
+ *   called again whenever filters have changed.
+ * nsk_conv2d_dgrad_packed: nsk_conv2d_dgrad on such a packed filter.  No workspace.
+ * nsk_conv2d_wgrad_partial: the products of nsk_conv2d_wgrad into `partial` (16-byte aligned).  No workspace.
+ * nsk_conv2d_wgrad_reduce: items[i].dst = dw, or += with accumulate = 1, from the partial sums items[i].src. */
+typedef struct nsk_conv_item_t {
+    const nsk_conv_desc_t *desc;
+    const void *src;
+    void *dst;
+} nsk_conv_item_t;
+size_t nsk_conv2d_packed_filter_bytes(const nsk_conv_desc_t *desc);
+int nsk_conv2d_pack_filters(int count, const nsk_conv_item_t *items, void *stream);
+int nsk_conv2d_dgrad_packed(const nsk_conv_desc_t *desc, const void *dy, const void *packed, void *dx, int accumulate,
+                            void *stream);
+size_t nsk_conv2d_wgrad_partial_bytes(const nsk_conv_desc_t *desc);
+int nsk_conv2d_wgrad_partial(const nsk_conv_desc_t *desc, const void *x, const void *dy, float *partial, void *stream);
+int nsk_conv2d_wgrad_reduce(int count, const nsk_conv_item_t *items, int accumulate, void *stream);
+
 /* Grouped convolution (not used by the paper's networks; the residual-network family that the paper's recipe
  * belongs to has grouped and depthwise members, and the definition is the textbook one): the C input channels and
  * the K output channels are split into `groups` equal runs, output run g sees input run g only, and the filter is

@@ -35,6 +35,10 @@ class nsk_conv_desc_t(ctypes.Structure):
                  "dtype", "layout")]
 
 
+class nsk_conv_item_t(ctypes.Structure):
+    _fields_ = [("desc", ctypes.POINTER(nsk_conv_desc_t)), ("src", ctypes.c_void_p), ("dst", ctypes.c_void_p)]
+
+
 class nsk_bn_desc_t(ctypes.Structure):
     _fields_ = [("N", ctypes.c_int), ("C", ctypes.c_int), ("H", ctypes.c_int), ("W", ctypes.c_int),
                 ("dtype", ctypes.c_int), ("layout", ctypes.c_int), ("eps", ctypes.c_float),
@@ -96,6 +100,19 @@ def lib() -> ctypes.CDLL:
         L.nsk_conv2d_dgrad.argtypes = [cd, vp, vp, vp, ci, vp, sz, vp]
         L.nsk_conv2d_wgrad.restype = ci
         L.nsk_conv2d_wgrad.argtypes = [cd, vp, vp, vp, ci, vp, sz, vp]
+        it = ctypes.POINTER(nsk_conv_item_t)
+        L.nsk_conv2d_packed_filter_bytes.restype = sz
+        L.nsk_conv2d_packed_filter_bytes.argtypes = [cd]
+        L.nsk_conv2d_pack_filters.restype = ci
+        L.nsk_conv2d_pack_filters.argtypes = [ci, it, vp]
+        L.nsk_conv2d_dgrad_packed.restype = ci
+        L.nsk_conv2d_dgrad_packed.argtypes = [cd, vp, vp, vp, ci, vp]
+        L.nsk_conv2d_wgrad_partial_bytes.restype = sz
+        L.nsk_conv2d_wgrad_partial_bytes.argtypes = [cd]
+        L.nsk_conv2d_wgrad_partial.restype = ci
+        L.nsk_conv2d_wgrad_partial.argtypes = [cd, vp, vp, vp, vp]
+        L.nsk_conv2d_wgrad_reduce.restype = ci
+        L.nsk_conv2d_wgrad_reduce.argtypes = [ci, it, ci, vp]
         L.nsk_conv2d_grouped_workspace_bytes.restype = sz
         L.nsk_conv2d_grouped_workspace_bytes.argtypes = [cd, ci, ci]
         L.nsk_conv2d_grouped_fwd.restype = ci
@@ -225,7 +242,8 @@ def lib() -> ctypes.CDLL:
 
 EXPORTS = ("nsk_version", "nsk_test_hooks_reload", "nsk_status_string", "nsk_last_hip_error", "nsk_conv2d_out_dims",
            "nsk_conv2d_workspace_bytes", "nsk_conv2d_fwd", "nsk_conv2d_dgrad", "nsk_conv2d_wgrad",
-           "nsk_conv2d_grouped_workspace_bytes", "nsk_conv2d_grouped_fwd", "nsk_conv2d_grouped_dgrad",
+           "nsk_conv2d_packed_filter_bytes", "nsk_conv2d_pack_filters", "nsk_conv2d_dgrad_packed", "nsk_conv2d_wgrad_partial_bytes",
+    "nsk_conv2d_wgrad_partial", "nsk_conv2d_wgrad_reduce", "nsk_conv2d_grouped_workspace_bytes", "nsk_conv2d_grouped_fwd", "nsk_conv2d_grouped_dgrad",
            "nsk_conv2d_grouped_wgrad",
            "nsk_bn_workspace_bytes", "nsk_bn_relu_add_fwd", "nsk_bn_fwd_coeffs", "nsk_conv2d_act_supported", "nsk_conv2d_act_workspace_bytes",
            "nsk_conv2d_fwd_act", "nsk_conv2d_wgrad_act", "nsk_bn_relu_bwd_act", "nsk_static_scratch_bytes", "nsk_bn_relu_add_fwd_static",

@@ -282,6 +282,66 @@ __global__ __launch_bounds__(256) void wgrad_reduce16_kernel(const float *__rest
     *o = accumulate ? *o + r : r;
 }
 
+// The flat cases of the three above for many layers in one launch (a launch of its own takes a small layer 3.8 us for 1 us of sums).  kind: 4, 2
+// or 1 outputs a lane in four groups of splits, 16: sixteen groups.
+constexpr int kReduceMany = 64;
+struct ReduceMany {
+    ReduceItem e[kReduceMany];
+    int count, accumulate;
+};
+static_assert(sizeof(ReduceMany) <= 4096, "kernel arguments");
+template <int V> __device__ inline void reduce_flat(const ReduceItem &a, int block, int accumulate, float *lds)
+{
+    typedef float fv __attribute__((ext_vector_type(V)));
+    fv(*red)[64] = (fv(*)[64])lds;
+    const int g = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const long i = ((long)block * 64 + l) * V;
+    fv s;
+#pragma unroll
+    for (int e = 0; e < V; ++e) s[e] = 0.f;
+    if (i < a.total)
+#pragma unroll 8
+        for (int sp = g; sp < a.splits; sp += 4) s += *(const fv *)(a.part + (long)sp * a.total + i);
+    red[g][l] = s;
+    __syncthreads();
+    if (g != 0 || i >= a.total) return;
+    s = (red[0][l] + red[1][l]) + (red[2][l] + red[3][l]);
+    fv *o = (fv *)(a.dw + i);
+    *o = accumulate ? *o + s : s;
+}
+__global__ __launch_bounds__(256) void wgrad_reduce_many_kernel(const ReduceMany m)
+{
+    __shared__ __attribute__((aligned(16))) float lds[4 * 64 * 4];
+    int k = 0;
+    while (k + 1 < m.count && (int)blockIdx.x >= m.e[k + 1].first_block) ++k;
+    const ReduceItem &a = m.e[k];
+    const int block = (int)blockIdx.x - a.first_block;
+    if (a.kind == 4) return reduce_flat<4>(a, block, m.accumulate, lds);
+    if (a.kind == 2) return reduce_flat<2>(a, block, m.accumulate, lds);
+    if (a.kind == 1) return reduce_flat<1>(a, block, m.accumulate, lds);
+    float(*red)[16] = (float(*)[16])lds;
+    const int g = threadIdx.x >> 4, j = threadIdx.x & 15, i = block * 16 + j;
+    float s = 0.f;
+    if (i < a.total)
+#pragma unroll 4
+        for (int sp = g; sp < a.splits; sp += 16) s += a.part[(long)sp * a.total + i];
+    red[g][j] = s;
+    __syncthreads();
+    if (g != 0 || i >= a.total) return;
+    float r = 0.f;
+#pragma unroll
+    for (int q = 0; q < 16; q += 4) r += (red[q][j] + red[q + 1][j]) + (red[q + 2][j] + red[q + 3][j]);
+    a.dw[i] = m.accumulate ? a.dw[i] + r : r;
+}
+
+// Which of them a layer takes: enough blocks to cover the chip, and sixteen groups for few outputs with many splits.
+int reduce_kind(long total, int splits, bool flat)
+{
+    if (flat && total % 4 == 0 && total >= 4 * 64 * 512) return 4;
+    if (flat && total % 2 == 0 && total >= 2 * 64 * 256) return 2;
+    return total <= 16384 && splits >= 64 && !hooks().reduce4 ? 16 : 1;   // (the variable is an A/B hook)
+}
+
 int column_frags(int ntapsC) { return ntapsC % 192 == 0 ? 3 : 1; }
 
 }  // namespace
@@ -335,21 +395,44 @@ int launch_wgrad_reduce(const float *part, float *dw, int splits, int K, int Kp,
     // dw in the order of the partial sums: vector loads (bitwise the same sums); enough blocks to cover the chip
     const bool flat = C == Cp && K == Kp && sc == 1 && st == (long)C && sk == (long)ntaps * C && !hooks().reduce4 &&
                       (((uintptr_t)part | (uintptr_t)dw) & 15) == 0;
-    if (flat && total % 4 == 0 && total >= 4 * 64 * 512) {
+    const int kind = reduce_kind(total, splits, flat);
+    if (kind == 4) {
         hipLaunchKernelGGL(wgrad_reduce_vec_kernel<4>, dim3((unsigned)((total / 4 + 63) / 64)), dim3(256), 0, stream, part, dw, splits, total, accumulate);
         return check_launch();
     }
-    if (flat && total % 2 == 0 && total >= 2 * 64 * 256) {
+    if (kind == 2) {
         hipLaunchKernelGGL(wgrad_reduce_vec_kernel<2>, dim3((unsigned)((total / 2 + 63) / 64)), dim3(256), 0, stream, part, dw, splits, total, accumulate);
         return check_launch();
     }
-    if (total <= 16384 && splits >= 64 && !hooks().reduce4)   // (the variable is an A/B hook)
+    if (kind == 16)
         hipLaunchKernelGGL(wgrad_reduce16_kernel, dim3((unsigned)((total + 15) / 16)), dim3(256), 0, stream, part, dw,
                            splits, step, K, ntaps, C, Cp, sk, st, sc, accumulate);
     else
         hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)((total + 63) / 64)), dim3(256), 0, stream, part, dw,
                            splits, step, K, ntaps, C, Cp, sk, st, sc, accumulate);
     return check_launch();
+}
+
+int launch_wgrad_reduce_many(ReduceItem *items, int count, int accumulate, hipStream_t stream)
+{
+    for (int at = 0; at < count; at += kReduceMany) {
+        ReduceMany m{};
+        m.count = count - at < kReduceMany ? count - at : kReduceMany;
+        m.accumulate = accumulate;
+        int blocks = 0;
+        for (int k = 0; k < m.count; ++k) {
+            ReduceItem &e = items[at + k];
+            e.kind = reduce_kind(e.total, e.splits, !hooks().reduce4);
+            e.first_block = blocks;
+            blocks += ceil_div(e.total, e.kind == 16 ? 16 : 64 * e.kind);
+            m.e[k] = e;
+        }
+        if (blocks == 0) continue;
+        hipLaunchKernelGGL(wgrad_reduce_many_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, m);
+        const int rc = check_launch();
+        if (rc != NSK_OK) return rc;
+    }
+    return NSK_OK;
 }
 
 }  // namespace nsk

@@ -68,6 +68,24 @@ template <typename T> __global__ __launch_bounds__(256) void pack_filter_kernel(
     ((T *)a.out)[g * total + i] = c < a.Cr ? ((const T *)a.w)[g * a.w_gstep + n * a.sn + a.tap_off[t] + c * a.sc] : (T)0.f;
 }
 
+// The gather for the small filters of many layers (a launch of its own takes each of them 2.7 us, nearly all of it the launch).
+constexpr int kPackMany = 40;
+struct PackMany {
+    PackItem e[kPackMany];
+    int count;
+};
+static_assert(sizeof(PackMany) <= 4096, "kernel arguments");
+template <typename T> __global__ __launch_bounds__(256) void pack_many_kernel(const PackMany m)
+{
+    int k = 0;
+    while (k + 1 < m.count && (int)blockIdx.x >= m.e[k + 1].first_block) ++k;
+    const PackItem &a = m.e[k];
+    const int i = ((int)blockIdx.x - a.first_block) * 256 + (int)threadIdx.x;
+    if (i >= a.Nn * a.ntaps * a.Cs) return;
+    const int r = i / a.Cs, c = i - r * a.Cs, n = r / a.ntaps, t = r - n * a.ntaps;
+    ((T *)a.out)[i] = ((const T *)a.w)[n * a.sn + a.tap_off[t] + c * a.sc];
+}
+
 // The same where n runs along the source (sn = 1: backward-data of a KRSC filter), a transposition of every tap's [c][n] matrix: tiles
 // of 64 c x 64 n (fp32: 32 n) through LDS with 16-byte accesses on both sides.  The gather above fetches a line for each element that
 // a lane stores, 256 lines per block in flight: 512x512x9 bf16, 4.7 MB each way, 13.2 us there, 5.3 here.  Below 32 x 32
@@ -239,6 +257,28 @@ int launch_pack_filters_grouped(int dtype, int count, const void *w, void *const
     else
         hipLaunchKernelGGL((pack_filter_kernel<float>), grid, dim3(256), 0, stream, m);
     return check_launch();
+}
+
+int launch_pack_many(int dtype, PackItem *items, int count, hipStream_t stream)
+{
+    for (int at = 0; at < count; at += kPackMany) {
+        PackMany m{};
+        m.count = count - at < kPackMany ? count - at : kPackMany;
+        int blocks = 0;
+        for (int k = 0; k < m.count; ++k) {
+            items[at + k].first_block = blocks;
+            blocks += ceil_div(items[at + k].Nn * items[at + k].ntaps * items[at + k].Cs, 256);
+            m.e[k] = items[at + k];
+        }
+        if (blocks == 0) continue;
+        if (dtype == NSK_BF16)
+            hipLaunchKernelGGL((pack_many_kernel<bf16_t>), dim3((unsigned)blocks), dim3(256), 0, stream, m);
+        else
+            hipLaunchKernelGGL((pack_many_kernel<float>), dim3((unsigned)blocks), dim3(256), 0, stream, m);
+        const int rc = check_launch();
+        if (rc != NSK_OK) return rc;
+    }
+    return NSK_OK;
 }
 
 int launch_pack_filter(int dtype, const void *w, void *out, int Nn, int ntaps, int Cs, int Cr, long sn, long sc,

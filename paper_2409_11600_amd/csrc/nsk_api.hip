@@ -5,6 +5,8 @@
 #include <stdlib.h>
 
 #include <mutex>
+#include <new>
+#include <vector>
 
 #include "nsk_internal.h"
 
@@ -510,21 +512,38 @@ int nsk_conv2d_fwd_stats(const nsk_conv_desc_t *desc, const void *x, const void 
     return conv_fwd_impl(desc, 1, x, w, y, stats, workspace, workspace_bytes, stream);
 }
 
+// Layers whose filters are packed together (launch_pack_many) / whose partial sums are added up together: the calls below need no
+// workspace for them.
+static bool packs_with_others(const ConvGeo &g)
+{
+    const ConvPlan p = plan_conv(g, NSK_PASS_DGRAD);
+    return g.layout == NSK_NHWC && !p.stem && p.geo.C == g.C && p.geo.K == g.K && g.R * g.S <= 9 && g.sh * g.sw <= 4 && g.w_elems < 140000;
+}
+static bool reduces_with_others(const ConvGeo &g, const ConvPlan &p)
+{
+    return g.layout == NSK_NHWC && !p.stem && p.geo.C == g.C && p.geo.K == g.K && p.splits > 1 &&
+           (size_t)p.splits * g.w_elems * sizeof(float) <= (16u << 20);
+}
+
+// packed: the filter is there already (packs_with_others).  collect: nothing is launched, the packings of w into `packed` are appended.
 static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *dy, const void *w, void *dx,
-                           int accumulate, void *workspace, size_t workspace_bytes, void *stream)
+                           int accumulate, void *workspace, size_t workspace_bytes, void *stream, void *packed = nullptr,
+                           std::vector<PackItem> *collect = nullptr)
 {
     ConvGeo g;
     NSK_TRY(conv_geometry(desc, &g, true));
     NSK_TRY(check_groups(g, groups));
     if (!dy || !w || !dx) return NSK_ERR_NULL;
     if (accumulate != 0 && accumulate != 1) return NSK_ERR_BAD_DESC;
-    if (misaligned(dy) || misaligned(w) || misaligned(dx)) return NSK_ERR_ALIGNMENT;
+    if (misaligned(dy) || misaligned(w) || misaligned(dx) || misaligned(packed)) return NSK_ERR_ALIGNMENT;
+    if (packed && !packs_with_others(g)) return NSK_ERR_UNSUPPORTED;
     const ConvPlan p = plan_within(g, NSK_PASS_DGRAD, groups, false, workspace, workspace_bytes);
     const ConvGeo &gp = p.geo;
     const int cg = g.C / groups, kg = gp.K / groups;   // channels of one group (all of them for a plain convolution)
-    NSK_TRY(check_ws(workspace, workspace_bytes, p.total));
+    if (!packed) NSK_TRY(check_ws(workspace, workspace_bytes, p.total));
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
+    char *const filters = packed ? (char *)packed : ws + p.filt;
     const bool nchw = g.layout == NSK_NCHW;
     if (p.stem) return stem_dgrad(g, dy, w, dx, accumulate, ws, st);
 
@@ -584,7 +603,7 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
         bool others_empty = true;
         for (int c = 1; c < 4; ++c) others_empty = others_empty && class_args(c >> 1, c & 1, &a, tap_off) == 0;
         if (others_empty && class_args(0, 0, &a, tap_off) > 0) {
-            a.src = src; a.wpk = ws + p.filt; a.out = dst;
+            a.src = src; a.wpk = filters; a.out = dst;
             zero_cell = conv_pw_applicable(g.dtype, a);
         }
     }
@@ -592,7 +611,7 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     const long w_sn = nchw ? (long)g.R * g.S : 1L, w_sc = (long)g.R * g.S * cg;
     const int kr = g.K / groups;
     const long w_gstep = (long)kr * w_sc;
-    size_t filt_off = p.filt;
+    size_t filt_off = 0;
     // classes with taps: filters are packed first, then the launches follow (one for all classes where the pipelined
     // kernel takes them together)
     IgemmArgs pending[4], zeros[4];
@@ -609,7 +628,7 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
             if (nt == 0 && accumulate && !nchw) continue;  // nothing to add
             if (nt == 0) {   // no tap reaches this class: plain zero fill
                 if (may_merge) {
-                    a.src = src; a.wpk = ws + p.filt; a.out = dst;
+                    a.src = src; a.wpk = filters; a.out = dst;
                     if (!zero_cell) zeros[n_zeros++] = a;
                 } else {
                     NSK_TRY(launch_zero_class(g.dtype, dst, g.N, g.H, g.W, g.C, a.Mi, a.Mj, g.sh, ca, g.sw, cb, st));
@@ -617,25 +636,33 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
                 continue;
             }
             // packed filter of this class: [c][tap][k] with element (c, t, k) = w[c*sn + tap_off[t] + k*sc]
-            a.src = src; a.wpk = ws + filt_off; a.out = dst;
+            a.src = src; a.wpk = filters + filt_off; a.out = dst;
             a.zero_cell = zero_cell ? 1 : 0;
-            a.packed = true;
+            a.packed = !packed;
             if (may_merge) {
                 for (int t = 0; t < kMaxTaps; ++t) pk_taps[n_pending][t] = t < nt ? tap_off[t] : 0;
                 pk_nt[n_pending] = nt;
-                pk_out[n_pending] = ws + filt_off;
+                pk_out[n_pending] = filters + filt_off;
                 pending[n_pending++] = a;
             } else {
                 int taps1[1][kMaxTaps];
                 for (int t = 0; t < kMaxTaps; ++t) taps1[0][t] = t < nt ? tap_off[t] : 0;
-                void *out1[1] = {ws + filt_off};
+                void *out1[1] = {filters + filt_off};
                 NSK_TRY(launch_pack_filters_grouped(g.dtype, 1, w, out1, cg, &nt, kg, kr, w_sn, w_sc, taps1, groups, w_gstep, st));
                 NSK_TRY(launch_igemm(g.dtype, a, st));
             }
             filt_off += align_up((size_t)g.C * nt * kg * g.es);
         }
+    if (collect) {
+        for (int i = 0; i < n_pending; ++i) {
+            PackItem e{w, pk_out[i], cg, pk_nt[i], kg, (int)w_sn, (int)w_sc, 0, {}};
+            for (int t = 0; t < pk_nt[i]; ++t) e.tap_off[t] = pk_taps[i][t];
+            collect->push_back(e);
+        }
+        return NSK_OK;
+    }
     // one packing launch for all classes, then their multiplies
-    if (n_pending > 0)
+    if (n_pending > 0 && !packed)
         NSK_TRY(launch_pack_filters_grouped(g.dtype, n_pending, w, pk_out, cg, pk_nt, kg, kr, w_sn, w_sc, pk_taps, groups, w_gstep, st));
     if (n_pending == 4 && groups == 1 && fs64_dgrad_s2_applicable(g.dtype, pending, n_pending)) {
         NSK_TRY(launch_fs64_dgrad_s2(pending, n_pending, st));
@@ -656,7 +683,7 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
 
 static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *x, const void *dy, float *dw,
                            int accumulate, void *workspace, size_t workspace_bytes, void *stream,
-                           const float *act = nullptr)
+                           const float *act = nullptr, bool partial = false)   // partial: dw takes the partial sums
 {
     ConvGeo g;
     NSK_TRY(conv_geometry(desc, &g, true));
@@ -667,7 +694,8 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     NSK_TRY(check_act(g, groups, act));
     const ConvPlan p = plan_within(g, NSK_PASS_WGRAD, groups, act != nullptr, workspace, workspace_bytes);
     const int cg = g.C / groups, kg = g.K / groups;
-    NSK_TRY(check_ws(workspace, workspace_bytes, p.total));
+    if (partial && !reduces_with_others(g, p)) return NSK_ERR_UNSUPPORTED;
+    if (!partial) NSK_TRY(check_ws(workspace, workspace_bytes, p.total));
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
     if (act) {   // apply the activation first
@@ -690,7 +718,7 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     if (nchw || pad_c) xs = ws + p.act_in;
     if (nchw || pad_k) dys = ws + p.act_in2;
     WgradArgs a{};
-    a.x = xs; a.dy = dys; a.part = (float *)(ws + p.part);
+    a.x = xs; a.dy = dys; a.part = partial ? dw : (float *)(ws + p.part);
     wgrad_geometry(gp, &a);
     a.rows_per_split = p.rows_per_split;
     a.splits = p.splits;
@@ -720,6 +748,7 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
         NSK_TRY(launch_narrow_wgrad(a, st));
     else
         NSK_TRY(launch_wgrad(g.dtype, a, st));
+    if (partial) return NSK_OK;
     const long RS = (long)g.R * g.S;
     if (nchw)
         NSK_TRY(launch_wgrad_reduce(a.part, dw, p.splits, g.K, gp.K, a.ntaps, cg, gp.C / groups, (long)cg * RS, 1L, RS, accumulate, st));
@@ -738,6 +767,73 @@ int nsk_conv2d_wgrad(const nsk_conv_desc_t *desc, const void *x, const void *dy,
                      void *workspace, size_t workspace_bytes, void *stream)
 {
     return conv_wgrad_impl(desc, 1, x, dy, dw, accumulate, workspace, workspace_bytes, stream);
+}
+
+size_t nsk_conv2d_packed_filter_bytes(const nsk_conv_desc_t *desc)
+{
+    ConvGeo g;
+    if (conv_geometry(desc, &g, true) != NSK_OK || !packs_with_others(g)) return 0;
+    return align_up(g.w_elems * g.es + 256 * (size_t)g.sh * g.sw);
+}
+
+int nsk_conv2d_pack_filters(int count, const nsk_conv_item_t *items, void *stream)
+{
+    if (count < 0) return NSK_ERR_BAD_DESC;
+    if (count > 0 && !items) return NSK_ERR_NULL;
+    try {
+        std::vector<PackItem> of[2];   // by type
+        for (int i = 0; i < count; ++i) {
+            if (!items[i].desc || !items[i].src || !items[i].dst) return NSK_ERR_NULL;
+            // (stand-ins for the tensors that a packing does not read)
+            NSK_TRY(conv_dgrad_impl(items[i].desc, 1, items[i].dst, items[i].src, items[i].dst, 0, nullptr, 0, stream, items[i].dst,
+                                    &of[items[i].desc->dtype == NSK_BF16]));
+        }
+        for (int t = 0; t < 2; ++t) NSK_TRY(launch_pack_many(t ? NSK_BF16 : NSK_F32, of[t].data(), (int)of[t].size(), (hipStream_t)stream));
+    } catch (const std::bad_alloc &) {
+        return NSK_ERR_UNSUPPORTED;
+    }
+    return NSK_OK;
+}
+
+int nsk_conv2d_dgrad_packed(const nsk_conv_desc_t *desc, const void *dy, const void *packed, void *dx, int accumulate,
+                            void *stream)
+{
+    if (!packed) return NSK_ERR_NULL;
+    return conv_dgrad_impl(desc, 1, dy, packed, dx, accumulate, nullptr, 0, stream, const_cast<void *>(packed));
+}
+
+size_t nsk_conv2d_wgrad_partial_bytes(const nsk_conv_desc_t *desc)
+{
+    ConvGeo g;
+    if (conv_geometry(desc, &g, true) != NSK_OK) return 0;
+    const ConvPlan p = plan_conv(g, NSK_PASS_WGRAD);
+    return reduces_with_others(g, p) ? (size_t)p.splits * g.w_elems * sizeof(float) : 0;
+}
+
+int nsk_conv2d_wgrad_partial(const nsk_conv_desc_t *desc, const void *x, const void *dy, float *partial, void *stream)
+{
+    return conv_wgrad_impl(desc, 1, x, dy, partial, 0, nullptr, 0, stream, nullptr, true);
+}
+
+int nsk_conv2d_wgrad_reduce(int count, const nsk_conv_item_t *items, int accumulate, void *stream)
+{
+    if (count < 0 || (accumulate != 0 && accumulate != 1)) return NSK_ERR_BAD_DESC;
+    if (count > 0 && !items) return NSK_ERR_NULL;
+    try {
+        std::vector<ReduceItem> all;
+        for (int i = 0; i < count; ++i) {
+            ConvGeo g;
+            NSK_TRY(conv_geometry(items[i].desc, &g, true));
+            if (!items[i].src || !items[i].dst) return NSK_ERR_NULL;
+            if (misaligned(items[i].src) || misaligned(items[i].dst)) return NSK_ERR_ALIGNMENT;
+            const ConvPlan p = plan_conv(g, NSK_PASS_WGRAD);
+            if (!reduces_with_others(g, p)) return NSK_ERR_UNSUPPORTED;
+            all.push_back({(const float *)items[i].src, (float *)items[i].dst, p.splits, (int)g.w_elems, 0, 0});
+        }
+        return launch_wgrad_reduce_many(all.data(), (int)all.size(), accumulate, (hipStream_t)stream);
+    } catch (const std::bad_alloc &) {
+        return NSK_ERR_UNSUPPORTED;
+    }
 }
 
 int nsk_conv2d_wgrad_act(const nsk_conv_desc_t *desc, const void *x, const float *coeffs, const void *dy, float *dw,

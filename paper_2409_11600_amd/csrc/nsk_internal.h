@@ -380,6 +380,14 @@ int launch_narrow_wgrad(const WgradArgs &a, hipStream_t stream);
 int launch_wgrad_reduce(const float *part, float *dw, int splits, int K, int Kp, int ntaps, int C, int Cp,
                         long sk, long st, long sc, int accumulate, hipStream_t stream);
 
+// The same for many layers whose dw lies as their partial sums do (`total` outputs), in one launch; sums as above, bit by bit.
+struct ReduceItem {
+    const float *part;
+    float *dw;
+    int splits, total, kind, first_block;   // kind, first_block: set by the launcher
+};
+int launch_wgrad_reduce_many(ReduceItem *items, int count, int accumulate, hipStream_t stream);
+
 // ------------------------------------------------------------------ image stem
 // Stride-2 odd square filter with "same" padding on at most 4 input channels and even H, W: all three
 // passes run on a space-to-depth copy of the image (16 channels, stride 1).  `ws` must hold
@@ -417,6 +425,15 @@ int launch_pack_filter(int dtype, const void *w, void *out, int Nn, int ntaps, i
 int launch_pack_filters_grouped(int dtype, int count, const void *w, void *const *out, int Nn, const int *ntaps, int Cs, int Cr,
                                 long sn, long sc, const int (*tap_off_host)[kMaxTaps], int groups, long w_gstep,
                                 hipStream_t stream);
+
+// Small filters of many layers in one launch: out[n][t][c] = w[n*sn + tap_off[t] + c*sc], n < Nn, t < ntaps, c < Cs.
+struct PackItem {
+    const void *w;
+    void *out;
+    int Nn, ntaps, Cs, sn, sc, first_block;
+    int tap_off[9];
+};
+int launch_pack_many(int dtype, PackItem *items, int count, hipStream_t stream);   // sets first_block; any count
 
 // out[img][i*osh + oa][j*osw + ob][0..Co) = 0 for i < Mi, j < Mj (NHWC).
 int launch_zero_class(int dtype, void *out, int Nimg, int Ho, int Wo, int Co, int Mi, int Mj, int osh, int oa, int osw,

@@ -167,6 +167,8 @@ class GpuNetwork:
                                                          ptr(self.beta[name]), ptr(self.act[u["dst"]]), ptr(self.mean[name]),
                                                          ptr(self.invstd[name]), None, None), "ws"))
 
+        self.partial, self.packed = {}, {}    # partial sums of weight gradients, packed filters of small layers
+        filters, sums = [], []
         # backward: reverse walk; first contribution to a gradient overwrites, later ones accumulate
         for u in reversed(wl["units"]):
             name = u["name"]
@@ -214,22 +216,44 @@ class GpuNetwork:
             if producer:
                 bwd_plan.append((L.nsk_conv2d_wgrad_act, (ctypes.byref(cd), ptr(self.y[producer]), ptr(self.coeffs[producer]),
                                                           ptr(dy), ptr(self.dw[name]), 0), "side"))
+            elif L.nsk_conv2d_wgrad_partial_bytes(ctypes.byref(cd)):
+                self.partial[name] = torch.empty(L.nsk_conv2d_wgrad_partial_bytes(ctypes.byref(cd)) // 4, dtype=torch.float32, device=dev)
+                bwd_plan.append((L.nsk_conv2d_wgrad_partial, (ctypes.byref(cd), ptr(self.act[u["src"]]), ptr(dy),
+                                                              ptr(self.partial[name])), "side, no workspace"))
+                sums.append((cd, self.partial[name], self.dw[name]))
             else:
                 bwd_plan.append((L.nsk_conv2d_wgrad, (ctypes.byref(cd), ptr(self.act[u["src"]]), ptr(dy), ptr(self.dw[name]), 0),
                                  "side"))
             acc = 1 if u["src"] in written else 0
-            bwd_plan.append((L.nsk_conv2d_dgrad, (ctypes.byref(cd), ptr(dy), ptr(self.w[name]), ptr(self.grad[u["src"]]),
-                                                  acc), "ws"))
+            if L.nsk_conv2d_packed_filter_bytes(ctypes.byref(cd)):
+                self.packed[name] = torch.empty(L.nsk_conv2d_packed_filter_bytes(ctypes.byref(cd)), dtype=torch.uint8, device=dev)
+                bwd_plan.append((L.nsk_conv2d_dgrad_packed, (ctypes.byref(cd), ptr(dy), ptr(self.packed[name]), ptr(self.grad[u["src"]]),
+                                                             acc), None))
+                filters.append((cd, self.w[name], self.packed[name]))
+            else:
+                bwd_plan.append((L.nsk_conv2d_dgrad, (ctypes.byref(cd), ptr(dy), ptr(self.w[name]), ptr(self.grad[u["src"]]),
+                                                      acc), "ws"))
             written.add(u["src"])
+
+        # one launch for the filters of all small layers in front, one for the sums of their weight gradients behind
+        def items(of):
+            table = (B.nsk_conv_item_t * len(of))(*[(ctypes.pointer(d), s.data_ptr(), t.data_ptr()) for d, s, t in of])
+            self._keep.append(table)
+            return len(of), table
+
+        if filters:
+            bwd_plan.insert(0, (L.nsk_conv2d_pack_filters, items(filters), None))
+        if sums:
+            bwd_plan.append((L.nsk_conv2d_wgrad_reduce, items(sums) + (0,), "side, no workspace"))
 
         # two workspaces: calls issued on the side stream must not share scratch with the main stream's
         self.ws = torch.empty(max(int(ws_bytes), 256), dtype=torch.uint8, device=dev)
         self.ws_side = torch.empty(max(int(ws_bytes), 256), dtype=torch.uint8, device=dev)
         wsp, wsb = ctypes.c_void_p(self.ws.data_ptr()), ctypes.c_size_t(self.ws.numel())
         wsp2 = ctypes.c_void_p(self.ws_side.data_ptr())
-        fin = lambda plan: [(f, a + ((wsp2 if w == "side" else wsp, wsb) if w else ())) for f, a, w in plan]
+        fin = lambda plan: [(f, a + ((wsp2 if w == "side" else wsp, wsb) if w in ("ws", "side") else ())) for f, a, w in plan]
         self.fwd_calls, self.bwd_calls = fin(fwd_plan), fin(bwd_plan)
-        self.bwd_side = [w == "side" for _, _, w in bwd_plan]   # calls that may run on a side stream
+        self.bwd_side = [w in ("side", "side, no workspace") for _, _, w in bwd_plan]   # calls that may run on a side stream
 
     def _run(self, calls, side_flags=None, side_stream=None):
         main = torch.cuda.current_stream(self.device)
