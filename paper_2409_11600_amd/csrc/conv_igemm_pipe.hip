@@ -58,7 +58,8 @@ template <int NP> struct PipeProblems {   // NP = 1 or kMaxProblems: a plain lau
     int tiles_n;
 };
 
-template <typename T, int BM, int BN, int WM, int WN, int WK, int ST, int NP>
+// GATHER: the filter is fetched as the caller holds it (IgemmArgs::gather), four bytes a lane.
+template <typename T, int BM, int BN, int WM, int WN, int WK, int ST, int NP, bool GATHER>
 __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 4096 ? 2 : 1) void igemm_pipe_kernel(const PipeProblems<NP> pp)
 {
     const int prob = NP > 1 ? blockIdx.y : 0;   // (the problems of a launch differ in their pixels and taps)
@@ -71,7 +72,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
     static_assert((NW == 4 || NW == 8) && BM <= 64 * NW, "four or eight wavefronts per block");
     constexpr int FM = BM / WM / 32, FN = BN / WN / 32;
     constexpr int RA = BM / 8 / NW, RB = BN / 8 / NW;           // direct loads per wavefront and k-tile (eight rows each)
-    constexpr int LOADS = RA + RB;
+    constexpr int LOADS = RA + (GATHER ? 4 : 1) * RB;
+    static_assert(!GATHER || ES == 4, "one element a load");
     constexpr int TA = BM * PK_BYTES, TB = BN * PK_BYTES;
     constexpr int SROW = 32 * ES + 16;                  // epilogue: staged bytes per pixel (padded)
     constexpr int STRIPS = WM * WN * 32 * SROW, SUMS = WM * WN * (WK - 1) * FN * 4096;   // SUMS: of the wavefronts wk > 0
@@ -87,6 +89,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
     __shared__ int s_bh[BM], s_bw[BM];
     __shared__ int s_oh[kMaxTaps], s_ow[kMaxTaps];
     __shared__ unsigned s_delta[kMaxTaps];
+    __shared__ unsigned s_wtap[GATHER ? kMaxTaps : 1];
 #define NSK_STAGE(S, P) ((S) == 0 ? P##0 : (S) == 1 ? P##1 : (S) == 2 ? P##2 : P##3)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -120,6 +123,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
         s_oh[tid] = oh;
         s_ow[tid] = ow;
         s_delta[tid] = (unsigned)((oh * a.Ws + ow) * ld * ES);
+        if constexpr (GATHER) s_wtap[tid] = (unsigned)a.w_tap[tid] * (unsigned)(a.Ngemm * ES);
     }
     if (tid < BM) {
         const int m = m0 + tid, per_img = a.Mi * a.Mj;
@@ -172,9 +176,19 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
     // q_tap taps and r_c channels
     const int q_tap = BK / a.Cs, r_c = BK - q_tap * a.Cs;
     int cur_tap, cur_c;
+    // GATHER: of every eight rows a load brings two, dword by dword as they will lie, so a lane's reduction index differs from load to load
+    int g_tap[GATHER ? 4 : 1], g_c[GATHER ? 4 : 1];
     auto start_requests = [&]() {
         cur_tap = piece * VEC / a.Cs;
         cur_c = piece * VEC - cur_tap * a.Cs;
+        if constexpr (GATHER) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int k = ((((lane >> 2) & 7) ^ ((wave & 1) * 4 + q)) * 4) + (lane & 3);
+                g_tap[q] = k / a.Cs;
+                g_c[q] = k - g_tap[q] * a.Cs;
+            }
+        }
 #pragma unroll
         for (int u = 0; u < RB; ++u) {
             const int n = n0 + 8 * (wave + NW * u) + lr;
@@ -195,8 +209,26 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
             __builtin_amdgcn_raw_ptr_buffer_load_lds(src_rsrc, (lds_void *)&NSK_STAGE(I, sa)[(wave + NW * u) * 1024], 16,
                                                      (int)((a_base[u] + delta) | bad | k_bad), 0, 0, 0);
         }
+        if constexpr (GATHER) {
 #pragma unroll
-        for (int u = 0; u < RB; ++u) {
+            for (int q = 0; q < 4; ++q) {
+                const unsigned bad_k = (unsigned)((a.ntaps - 1 - g_tap[q]) >> 31);
+                const unsigned at = s_wtap[g_tap[q] & (kMaxTaps - 1)] + (unsigned)(g_c[q] * a.w_sc * ES);
+#pragma unroll
+                for (int u = 0; u < RB; ++u) {
+                    const int n = n0 + 8 * (wave + NW * u) + 2 * q + (lane >> 5);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(wpk_rsrc, (lds_void *)&NSK_STAGE(I, sb)[(wave + NW * u) * 1024 + q * 256], 4,
+                                                             (int)((at + (unsigned)(n * ES)) | bad_k | (n < a.Ngemm ? 0u : ~0u)), 0, 0, 0);
+                }
+                g_c[q] += r_c;
+                g_tap[q] += q_tap;
+                const bool w = g_c[q] >= a.Cs;
+                g_c[q] -= w ? a.Cs : 0;
+                g_tap[q] += w ? 1 : 0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < (GATHER ? 0 : RB); ++u) {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(wpk_rsrc, (lds_void *)&NSK_STAGE(I, sb)[(wave + NW * u) * 1024], 16,
                                                      (int)(b_row[u] | b_bad[u] | k_bad), 0, 0, 0);
             b_row[u] += PK_BYTES;
@@ -536,6 +568,7 @@ constexpr PipeTile kTilesBf16[] = {{256, 128, 1, 0.827, 4.71, 0.99, 0.017, 1.4},
                                    {64, 64, 2, 0.224, 2.12, 1.25, 0.251, 0},     {128, 32, 1, 0.30, 0.9, 2.34, 0.162, 0}, 
                                    {128, 128, 1, 0, 0, 1e9, 0, 0}};   // kShort (taken by a rule, see cheapest)
 constexpr int kShort = 6;
+constexpr int kSmallest = 5;
 constexpr PipeTile kTilesF32[] = {{128, 64, 2, 0.770, 1.96, 4.79, 0.238, 0}, {64, 64, 2, 0.563, 0, 5.08, 0.361, 0},
                                   {256, 128, 1, 2.19, 6.83, 0, 0.039, 0},    {128, 32, 1, 0.557, 1.01, 4.03, 0.255, 0},
                                   {64, 32, 2, 0.322, 0.73, 3.76, 0.258, 0},  {32, 32, 4, 0.172, 0.68, 3.98, 0.23, 0}};
@@ -590,7 +623,7 @@ template <int N> int cheapest(const PipeTile (&tiles)[N], int es, const IgemmArg
     return short_reduction(best);
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int WK, int ST, int NP> int launch_np(const IgemmArgs *a, int count, hipStream_t stream)
+template <typename T, int BM, int BN, int WM, int WN, int WK, int ST, int NP, bool GATHER> int launch_np(const IgemmArgs *a, int count, hipStream_t stream)
 {
     PipeProblems<NP> pp;
     int most = 0;
@@ -602,15 +635,15 @@ template <typename T, int BM, int BN, int WM, int WN, int WK, int ST, int NP> in
         pp.by[j] = make_div(pp.cols[j] ? pp.tiles_m[j] : pp.tiles_n);
         if (pp.tiles_m[j] > most) most = pp.tiles_m[j];
     }
-    hipLaunchKernelGGL((igemm_pipe_kernel<T, BM, BN, WM, WN, WK, ST, NP>), dim3((unsigned)most * pp.tiles_n, count, a[0].groups),
+    hipLaunchKernelGGL((igemm_pipe_kernel<T, BM, BN, WM, WN, WK, ST, NP, GATHER>), dim3((unsigned)most * pp.tiles_n, count, a[0].groups),
                        dim3(64 * WM * WN * WK), 0, stream, pp);
     return check_launch();
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int WK, int ST> int launch(const IgemmArgs *a, int count, hipStream_t stream)
+template <typename T, int BM, int BN, int WM, int WN, int WK, int ST, bool GATHER = false> int launch(const IgemmArgs *a, int count, hipStream_t stream)
 {
-    return count == 1 ? launch_np<T, BM, BN, WM, WN, WK, ST, 1>(a, 1, stream)
-                      : launch_np<T, BM, BN, WM, WN, WK, ST, kMaxProblems>(a, count, stream);
+    return count == 1 ? launch_np<T, BM, BN, WM, WN, WK, ST, 1, GATHER>(a, 1, stream)
+                      : launch_np<T, BM, BN, WM, WN, WK, ST, kMaxProblems, GATHER>(a, count, stream);
 }
 
 }  // namespace
@@ -634,6 +667,7 @@ int launch_igemm_pipe(int dtype, const IgemmArgs *a, int count, hipStream_t stre
         default: return launch<bf16_t, 128, 32, 4, 1, 1, 3>(a, count, stream);
         }
     }
+    if (a->gather) return launch<float, 32, 32, 1, 1, 4, 4, true>(a, count, stream);
     switch (cheapest(kTilesF32, 4, a, count, a->stats != nullptr)) {
     case 0: return launch<float, 128, 64, 2, 1, 2, 3>(a, count, stream);
     case 1: return launch<float, 64, 64, 1, 2, 2, 3>(a, count, stream);
@@ -642,6 +676,18 @@ int launch_igemm_pipe(int dtype, const IgemmArgs *a, int count, hipStream_t stre
     case 4: return launch<float, 64, 32, 2, 1, 2, 4>(a, count, stream);
     default: return launch<float, 32, 32, 1, 1, 4, 4>(a, count, stream);
     }
+}
+
+// The packing of a small filter is a launch (2.5 us, and as much on the host) for next to no work; fetched four bytes a lane, a k-tile of
+// the smallest shape takes 0.2 us more.  Up to eight k-tiles, us, packed / fetched, in a graph: 16 -> 16 3x3 at 32x32 N=8 8.1 / 7.2, 64 -> 64 1x1
+// at 56x56 6.7 / 5.3, 128 -> 128 1x1 stride 2 7.6 / 6.4, 256 -> 128 1x1 (eight) 8.1 / 8.3; 64 -> 64 3x3 (18) 10.5 / 13.1.  Launched one
+// by one, all three passes of the first 27.0 / 20.6.
+bool igemm_pipe_gathers(int dtype, const IgemmArgs *a, int count)
+{
+    if (dtype != NSK_F32 || count < 1 || count > kMaxProblems || a->groups > 1) return false;
+    for (int j = 0; j < count; ++j)
+        if (a[j].Ktot > 8 * PK_BYTES / 4) return false;
+    return cheapest(kTilesF32, 4, a, count, false) == kSmallest;
 }
 
 int igemm_pipe_stats_rows(int dtype, const IgemmArgs &a)

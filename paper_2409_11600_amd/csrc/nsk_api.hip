@@ -661,6 +661,22 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
         }
         return NSK_OK;
     }
+    // Small fp32 layers whose launch is that of the pipelined kernel: it fetches the filter itself, and no packing goes before it.
+    const bool one_launch = n_pending + n_zeros <= 4 && n_pending > 0 && !nchw && groups == 1 && !packed;
+    if (one_launch && igemm_pipe_multi_applicable(g.dtype, pending, n_pending) && igemm_pipe_gathers(g.dtype, pending, n_pending)) {
+        for (int i = 0; i < n_pending; ++i) {
+            pending[i].gather = 1;
+            pending[i].wpk = w;
+            pending[i].wpk_bytes = (unsigned)(g.w_elems * g.es);   // (channels added to whole vectors read zeros past the end)
+            pending[i].w_sc = (int)w_sc;
+            for (int t = 0; t < pk_nt[i]; ++t) pending[i].w_tap[t] = (unsigned char)(pk_taps[i][t] / cg);
+        }
+        for (int i = 0; i < n_zeros; ++i) {
+            zeros[i].gather = 1;
+            pending[n_pending + i] = zeros[i];
+        }
+        return launch_igemm_pipe_multi(g.dtype, pending, n_pending + n_zeros, st);
+    }
     // one packing launch for all classes, then their multiplies
     if (n_pending > 0 && !packed)
         NSK_TRY(launch_pack_filters_grouped(g.dtype, n_pending, w, pk_out, cg, pk_nt, kg, kr, w_sn, w_sc, pk_taps, groups, w_gstep, st));

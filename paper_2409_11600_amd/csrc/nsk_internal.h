@@ -275,6 +275,10 @@ struct IgemmArgs {
     int groups, src_ld;
     short off_h[kMaxTaps];
     short off_w[kMaxTaps];
+    // Backward-data straight from the caller's filter (igemm_pipe_gathers said so): element (n, tap t, channel c) lies at
+    // w_tap[t] * Ngemm + c * w_sc + n of wpk, where it would be packed to [n][t][c].
+    int gather, w_sc;
+    unsigned char w_tap[kMaxTaps];
 };
 int launch_igemm(int dtype, const IgemmArgs &a, hipStream_t stream);
 // Rows of partial sums the kernel launch_igemm would pick writes from its epilogue; 0 if that kernel has no
@@ -283,6 +287,8 @@ int igemm_stats_rows(int dtype, const IgemmArgs &a);
 // every layer whose channel runs are 16-byte granular and that has no kernel of its own (groups, src_ld, vec_out set)
 int launch_igemm_pipe(int dtype, const IgemmArgs *a, int count, hipStream_t stream);
 int igemm_pipe_stats_rows(int dtype, const IgemmArgs &a);
+// the residue classes of a backward-data pass (sizes only are looked at): small enough that the kernel fetches the filter itself
+bool igemm_pipe_gathers(int dtype, const IgemmArgs *a, int count);
 // the residue classes of one strided backward-data pass (up to four argument sets on the same tensors) in one launch of it; a
 // class that no tap reaches (ntaps = 0) is filled with zeros
 bool igemm_pipe_multi_applicable(int dtype, const IgemmArgs *a, int count);

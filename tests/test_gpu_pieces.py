@@ -105,3 +105,26 @@ def test_operands_beyond_the_pieces(what, tile, nsk_env):
         _same(to_host(B.conv2d_wgrad(gx, gone, w.shape, 1, 0), LAY)[:, :, 0, 0], dw_want, 1e-5)
         if what == "smallest":
             _same(to_host(B.conv2d_dgrad(gdy, gw, x.shape, 1, 0), LAY), np.einsum("nkhw,kc->nchw", dy64, w64), 2e-6)
+
+
+# Backward-data that fetches its filter without a packing: up to eight k-tiles on the smallest tile; taps inside k-tiles, strided classes (and
+# some without a tap), channel counts that are copied to whole vectors, one k-tile more (packed); the forced tile takes other problems too.
+@pytest.mark.parametrize("tile", [None, "6"])
+@pytest.mark.parametrize("N,C,H,W,K,R,S,st,pd", [(2, 16, 9, 11, 16, 3, 3, 1, 1), (1, 20, 12, 7, 28, 3, 3, 2, 1), (3, 36, 7, 7, 64, 1, 1, 2, 0), (2, 8, 10, 9, 4, 7, 7, 1, 3),
+                                                 (1, 40, 6, 6, 256, 1, 1, 1, 0), (1, 40, 6, 6, 260, 1, 1, 1, 0), (2, 30, 8, 8, 22, 3, 3, 1, 1), (1, 12, 9, 9, 12, 2, 2, 2, 0)])
+def test_filter_without_packing(N, C, H, W, K, R, S, st, pd, tile, nsk_env):
+    if tile:
+        nsk_env("NSK_IGEMM_TILE", tile)
+    w = gen.he_normal(1970, 1, (K, C, R, S))
+    P, Q = oracle.conv2d_out_dims((N, C, H, W), w.shape, st, pd, 1)
+    dy, old = gen.normal(1970, 2, (N, K, P, Q)), gen.normal(1970, 3, (N, C, H, W))
+    want = oracle.conv2d_dgrad(dy, w, (N, C, H, W), st, pd, 1)
+    gw, gdy, gold = (to_gpu(a, "f32", LAY) for a in (w, dy, old))
+    for accumulate in (False, True):
+        dx, check = guarded(gold.shape, torch.float32)
+        if accumulate:
+            dx.copy_(gold)
+        B.conv2d_dgrad(gdy, gw, (N, C, H, W), st, pd, out=dx, accumulate=accumulate)
+        torch.cuda.synchronize()
+        check()
+        assert max_rel_err(to_host(dx, LAY), want + old if accumulate else want) <= TOL["f32"]
