@@ -35,6 +35,12 @@ def _to_device(a: np.ndarray, dtype, layout, device, is_filter=False):
     return t.contiguous().to(device=device, dtype=dtype)
 
 
+class _Shared:
+    """A place in the buffer that the layers of a backward pass share."""
+    def __init__(self, offset):
+        self.offset = offset
+
+
 class GpuNetwork:
     def __init__(self, wl: dict, tensors: dict, layout: int = B.NSK_NHWC, device: str = "cuda:0", eps: float = 1e-5,
                  use_relu_mask: bool = True, use_fused_stats: bool = True, use_fused_act: bool = False):
@@ -167,8 +173,13 @@ class GpuNetwork:
                                                          ptr(self.beta[name]), ptr(self.act[u["dst"]]), ptr(self.mean[name]),
                                                          ptr(self.invstd[name]), None, None), "ws"))
 
-        self.partial, self.packed = {}, {}    # partial sums of weight gradients, packed filters of small layers
-        filters, sums = [], []
+        filters, sums, shared_bytes = [], [], 0    # small layers: packed filters, partial sums of weight gradients
+
+        def at(nbytes):
+            nonlocal shared_bytes
+            shared_bytes += (nbytes + 255) // 256 * 256
+            return _Shared(shared_bytes - (nbytes + 255) // 256 * 256)
+
         # backward: reverse walk; first contribution to a gradient overwrites, later ones accumulate
         for u in reversed(wl["units"]):
             name = u["name"]
@@ -216,28 +227,37 @@ class GpuNetwork:
             if producer:
                 bwd_plan.append((L.nsk_conv2d_wgrad_act, (ctypes.byref(cd), ptr(self.y[producer]), ptr(self.coeffs[producer]),
                                                           ptr(dy), ptr(self.dw[name]), 0), "side"))
-            elif L.nsk_conv2d_wgrad_partial_bytes(ctypes.byref(cd)):
-                self.partial[name] = torch.empty(L.nsk_conv2d_wgrad_partial_bytes(ctypes.byref(cd)) // 4, dtype=torch.float32, device=dev)
-                bwd_plan.append((L.nsk_conv2d_wgrad_partial, (ctypes.byref(cd), ptr(self.act[u["src"]]), ptr(dy),
-                                                              ptr(self.partial[name])), "side, no workspace"))
-                sums.append((cd, self.partial[name], self.dw[name]))
             else:
-                bwd_plan.append((L.nsk_conv2d_wgrad, (ctypes.byref(cd), ptr(self.act[u["src"]]), ptr(dy), ptr(self.dw[name]), 0),
-                                 "side"))
+                pb = L.nsk_conv2d_wgrad_partial_bytes(ctypes.byref(cd))
+                if pb:
+                    part = at(pb)
+                    bwd_plan.append((L.nsk_conv2d_wgrad_partial, (ctypes.byref(cd), ptr(self.act[u["src"]]), ptr(dy), part),
+                                     "side, no workspace"))
+                    sums.append((cd, part, self.dw[name].data_ptr()))
+                else:
+                    bwd_plan.append((L.nsk_conv2d_wgrad, (ctypes.byref(cd), ptr(self.act[u["src"]]), ptr(dy), ptr(self.dw[name]), 0),
+                                     "side"))
             acc = 1 if u["src"] in written else 0
-            if L.nsk_conv2d_packed_filter_bytes(ctypes.byref(cd)):
-                self.packed[name] = torch.empty(L.nsk_conv2d_packed_filter_bytes(ctypes.byref(cd)), dtype=torch.uint8, device=dev)
-                bwd_plan.append((L.nsk_conv2d_dgrad_packed, (ctypes.byref(cd), ptr(dy), ptr(self.packed[name]), ptr(self.grad[u["src"]]),
-                                                             acc), None))
-                filters.append((cd, self.w[name], self.packed[name]))
+            fb = L.nsk_conv2d_packed_filter_bytes(ctypes.byref(cd))
+            if fb:
+                packed = at(fb)
+                bwd_plan.append((L.nsk_conv2d_dgrad_packed, (ctypes.byref(cd), ptr(dy), packed, ptr(self.grad[u["src"]]), acc), None))
+                filters.append((cd, self.w[name].data_ptr(), packed))
             else:
                 bwd_plan.append((L.nsk_conv2d_dgrad, (ctypes.byref(cd), ptr(dy), ptr(self.w[name]), ptr(self.grad[u["src"]]),
                                                       acc), "ws"))
             written.add(u["src"])
 
-        # one launch for the filters of all small layers in front, one for the sums of their weight gradients behind
+        # one launch for the filters of all small layers in front, one for the sums of their weight gradients behind; what they
+        # leave for the layers' calls lies in one buffer
+        self.shared = torch.empty(max(shared_bytes, 16), dtype=torch.uint8, device=dev)
+        base = self.shared.data_ptr()
+        where = lambda v: ctypes.c_void_p(base + v.offset) if isinstance(v, _Shared) else v
+        bwd_plan = [(f, tuple(where(v) for v in args), w) for f, args, w in bwd_plan]
+
         def items(of):
-            table = (B.nsk_conv_item_t * len(of))(*[(ctypes.pointer(d), s.data_ptr(), t.data_ptr()) for d, s, t in of])
+            point = lambda v: base + v.offset if isinstance(v, _Shared) else v
+            table = (B.nsk_conv_item_t * len(of))(*[(ctypes.pointer(d), point(src), point(dst)) for d, src, dst in of])
             self._keep.append(table)
             return len(of), table
 
