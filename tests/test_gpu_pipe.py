@@ -185,3 +185,21 @@ def test_statistics_of_every_kernel(tile, dtype, N, C, H, K, R, stride, nsk_env)
     bar = 6e-8 * n ** 0.5
     assert float((sums[0] - got.sum((0, 2, 3))).abs().max()) <= bar * float((got ** 2).sum((0, 2, 3)).max()) ** 0.5 * n ** 0.5
     assert float(((sums[1] - (got ** 2).sum((0, 2, 3))) / (got ** 2).sum((0, 2, 3))).abs().max()) <= bar
+
+
+# Tiles of 256 positions of the padded coarse image (H / 2 + 3 rows of W / 2 + 3), a quarter of a thousand blocks: more than 1024 tiles give each block a run
+# of five and take its ring of 864 positions around more than once.  Narrowest, ordinary and widest rows, an image that ends inside a tile.
+@pytest.mark.parametrize("N,H,W", [(340, 400, 2), (64, 130, 130), (20, 226, 226), (3, 46, 30)])
+def test_image_stem_backward_data_over_runs_of_tiles(N, H, W):
+    print(f"stem backward-data {N} {H} {W}", flush=True)
+    g = torch.Generator().manual_seed(N)
+    w, dy = torch.randn(64, 3, 7, 7, generator=g).mul(0.1).bfloat16(), torch.randn(N, 64, H // 2, W // 2, generator=g).bfloat16()
+    nhwc = lambda t: t.permute(0, 2, 3, 1).contiguous().cuda()
+    got, check = guarded((N, H, W, 3), torch.bfloat16)
+    B.conv2d_dgrad(nhwc(dy), nhwc(w), (N, 3, H, W), 2, 3, out=got)
+    torch.cuda.synchronize()
+    check()
+    want = torch.nn.grad.conv2d_input((N, 3, H, W), w.double(), dy.double(), stride=2, padding=3)
+    err = (got.permute(0, 3, 1, 2).cpu().double() - want).abs()
+    # rounding to bf16: 2^-8 of the value; the sum of at most 1024 products in fp32: far below 2^-12 of its size, one unit of 6.4
+    assert bool((err <= want.abs() * 2.0 ** -8 + 2.0 ** -10).all())
