@@ -144,6 +144,9 @@ template <bool ACC> __global__ __launch_bounds__(G8_THREADS) void grouped8_kerne
 // ---- backward-weight: dw[k][tap][c] of a group = sum over pixels of dy[pixel][k] * x[pixel + tap][c].  A wavefront takes two
 // groups: rows of the MFMA = their sixteen dy channels, columns = their sixteen x channels of one tap (the two off-diagonal
 // blocks are not stored), reduction = 32 consecutive pixels of the strip, through the transposing LDS read.
+// The vector unit's addresses bounded it (0.87 of the clocks), so a pixel's pieces are swapped by two neighbouring bits of its index, which an AND
+// of its shifted byte offset yields, and runs whose 32 pixels are all there have no choice between a place and the zeros: 190 -> 113 instructions a
+// run, 37.9 -> 29.5 us for 128 images of 28x28x256, 123 MB.
 struct G8WArgs {
     const void *x, *dy;
     float *part;
@@ -153,8 +156,8 @@ struct G8WArgs {
     Div by_pw, by_w, by_strips;
 };
 
-// within 32 lanes a transposing read serves the pixels 0..3 and 8..11 of a run, 32 bytes each: spread over all banks
-__device__ inline int g8_swap(int e) { return (e & 2) | ((e >> 1) & 4); }
+// within 32 lanes a transposing read serves eight consecutive pixels, 32 bytes each: spread over all banks
+__device__ inline int g8_swap(int e) { return e & 6; }
 
 __global__ __launch_bounds__(G8_THREADS) void grouped8_wgrad_kernel(const G8WArgs a)
 {
@@ -168,7 +171,7 @@ __global__ __launch_bounds__(G8_THREADS) void grouped8_wgrad_kernel(const G8WArg
     if (threadIdx.x < 8) *(f32x4 *)(smem + zero + threadIdx.x * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int q = lane >> 4, i16 = lane & 15;
-    const int piece = wave * 2 + ((i16 & 3) >> 1), inner = (i16 & 1) * 8;
+    const int inner = (i16 & 1) * 8, mine = (wave * 2 + ((i16 & 3) >> 1)) * 16 + inner;   // a lane's place in a pixel before the swap
     f32x4 sum[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t) sum[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -194,31 +197,35 @@ __global__ __launch_bounds__(G8_THREADS) void grouped8_wgrad_kernel(const G8WArg
         f32x4 acc[9];
 #pragma unroll
         for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int l0 = 32 * half; l0 < pixels; l0 += 64) {
+        // 32 pixels; FULL: all of them are there, and no read has to choose between its place and the zeros
+        auto run = [&](auto full, int l0) {
+            constexpr bool FULL = decltype(full)::value;
             bf16x4 d[2];
-            int e[2];
+            int e[2];                                      // bytes
             bool real[2];
+            auto read = [&](int pixel, int base, bool is_real) {
+                const int at = ((pixel >> 3 & 96) ^ mine) + pixel + base;
+                return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(smem + (FULL || is_real ? at : zero + inner)));
+            };
 #pragma unroll
             for (int hi = 0; hi < 2; ++hi) {
-                const int l = l0 + 8 * q + 4 * hi + (i16 >> 2), row = divide(l, a.by_w);
+                const int l = l0 + 16 * hi + 4 * q + (i16 >> 2), row = divide(l, a.by_w);
                 real[hi] = l < pixels;
-                e[hi] = row * PW + (l - row * a.W);
-                const int at = real[hi] ? dy_at + l * 128 + (piece ^ g8_swap(l)) * 16 : zero;
-                d[hi] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(smem + at + inner));
+                e[hi] = (l + row * 2) * 128;               // (a row of x has two pixels more)
+                d[hi] = read(l * 128, dy_at, real[hi]);
             }
             const bf16x8 af = __builtin_shufflevector(d[0], d[1], 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
             for (int t = 0; t < 9; ++t) {
                 bf16x4 b[2];
 #pragma unroll
-                for (int hi = 0; hi < 2; ++hi) {
-                    const int en = e[hi] + (t / 3) * PW + t % 3;
-                    const int at = real[hi] ? en * 128 + (piece ^ g8_swap(en)) * 16 : zero;
-                    b[hi] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(smem + at + inner));
-                }
+                for (int hi = 0; hi < 2; ++hi) b[hi] = read(e[hi] + ((t / 3) * PW + t % 3) * 128, 0, real[hi]);
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, __builtin_shufflevector(b[0], b[1], 0, 1, 2, 3, 4, 5, 6, 7), acc[t], 0, 0, 0);
             }
-        }
+        };
+        int l0 = 32 * half;
+        for (; l0 + 32 <= pixels; l0 += 64) run(std::true_type{}, l0);
+        if (l0 < pixels) run(std::false_type{}, l0);
 #pragma unroll
         for (int t = 0; t < 9; ++t) sum[t] += acc[t];      // (a strip's sum at a time: the chains stay short)
     }
