@@ -11,7 +11,7 @@
 // row of zeros, and so is everything past the end of a strip), so infinities stay where they belong.
 //
 // Measured (us, 256 channels at 28x28, N=128; direct kernels -> these): forward and backward-data 84.6 -> 25 (107 MB:
-// 4.3 TB/s; 14x14x512 16.2 -> 13.1 with eight wavefronts a block for four), backward-weight 153.5 + 8.2 -> 38.6 + 4.9.
+// 4.3 TB/s; 14x14x512 16.2 -> 13.1 with eight wavefronts a block for four), backward-weight 153.5 + 8.2 -> 29.5 + 4.7.
 //
 // Work: a block is 64 channels (eight groups, two per wavefront) of a strip of full image rows.
 #include "nsk_internal.h"
