@@ -52,8 +52,28 @@ ImgStrides img_strides(int layout, int C, int H, int W)
     return {(long)H * W * C, 1L, (long)W * C, (long)C};
 }
 
+// Two neighbouring pixels of an image row, CC channels each and nothing between them, as whole words: what a thread of the copies below
+// reads or writes per row.  They are bound by the number of accesses (12 of 2 bytes each for an image of 3 channels in bf16, now 2 of 12
+// bytes): 64 images of 224x224, 45 MB, to depth 12.2 -> 11.1 us, back 13.9 -> 8.7.  Element by element where channels lie apart
+// (NCHW).  Tensors start on 16 bytes, and even H and W keep the offset of every second pixel whole.
+template <typename T, int CC> struct PixelPair {
+    unsigned w[2 * CC * sizeof(T) / 4];
+    __device__ T get(int e) const
+    {
+        if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, w[e]);
+        else return __builtin_bit_cast(T, (unsigned short)(w[e / 2] >> (16 * (e % 2))));
+    }
+    __device__ void set(int e, T v)   // in order of e
+    {
+        if constexpr (sizeof(T) == 4) w[e] = __builtin_bit_cast(unsigned, v);
+        else if (e % 2 == 0) w[e / 2] = __builtin_bit_cast(unsigned short, v);
+        else w[e / 2] |= (unsigned)__builtin_bit_cast(unsigned short, v) << 16;
+    }
+};
+bool pixel_pairs(const ImgStrides &xs, int C) { return xs.w == C && (C == 1 || xs.c == 1); }
+
 // x (either layout, CC <= 4 channels) -> x2 (N, H/2, W/2, 16) NHWC: one thread per coarse pixel
-template <typename T, int CC>
+template <typename T, int CC, bool ROWS>
 __global__ __launch_bounds__(256) void s2d_kernel(const T *__restrict__ x, T *__restrict__ x2, long total, int H, int W,
                                                   const ImgStrides xs)
 {
@@ -69,18 +89,24 @@ __global__ __launch_bounds__(256) void s2d_kernel(const T *__restrict__ x, T *__
 #pragma unroll
     for (int e = 0; e < SC; ++e) o[e] = (T)0.f;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 2; ++a) {
+        const T *p = x + n * xs.n + (2 * ii + a) * xs.h + 2 * j * xs.w;
+        if constexpr (ROWS) {
+            const PixelPair<T, CC> v = *(const PixelPair<T, CC> *)p;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const T *p = x + n * xs.n + (2 * ii + a) * xs.h + (2 * j + b) * xs.w;
+            for (int e = 0; e < 2 * CC; ++e) o[a * 2 * CC + e] = v.get(e);
+        } else {
 #pragma unroll
-            for (int c = 0; c < CC; ++c) o[(a * 2 + b) * CC + c] = p[c * xs.c];
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int c = 0; c < CC; ++c) o[(a * 2 + b) * CC + c] = p[b * xs.w + c * xs.c];
         }
+    }
     *(vec_t *)(x2 + i * SC) = o;
 }
 
 // dx (either layout, CC <= 4 channels) (=|+=) depth-to-space of dx2 (N, H/2, W/2, 16)
-template <typename T, int CC>
+template <typename T, int CC, bool ROWS>
 __global__ __launch_bounds__(256) void d2s_kernel(const T *__restrict__ dx2, T *__restrict__ dx, long total, int H, int W,
                                                   const ImgStrides xs, int accumulate)
 {
@@ -94,17 +120,30 @@ __global__ __launch_bounds__(256) void d2s_kernel(const T *__restrict__ dx2, T *
     typedef T vec_t __attribute__((ext_vector_type(SC)));
     const vec_t s = *(const vec_t *)(dx2 + i * SC);
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 2; ++a) {
+        T *p = dx + n * xs.n + (2 * ii + a) * xs.h + 2 * j * xs.w;
+        if constexpr (ROWS) {
+            PixelPair<T, CC> v, old;
+            if (accumulate) old = *(const PixelPair<T, CC> *)p;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            T *p = dx + n * xs.n + (2 * ii + a) * xs.h + (2 * j + b) * xs.w;
-#pragma unroll
-            for (int c = 0; c < CC; ++c) {
-                float v = (float)s[(a * 2 + b) * CC + c];
-                if (accumulate) v += (float)p[c * xs.c];
-                p[c * xs.c] = (T)v;
+            for (int e = 0; e < 2 * CC; ++e) {
+                float f = (float)s[a * 2 * CC + e];
+                if (accumulate) f += (float)old.get(e);
+                v.set(e, (T)f);
             }
+            *(PixelPair<T, CC> *)p = v;
+        } else {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int c = 0; c < CC; ++c) {
+                    float v = (float)s[(a * 2 + b) * CC + c];
+                    T *q = p + b * xs.w + c * xs.c;
+                    if (accumulate) v += (float)*q;
+                    *q = (T)v;
+                }
         }
+    }
 }
 
 // Filter in either layout (element (k,c,r,s) at k*sk + c*sc + r*sr + s*ss) -> packed for the x2 problem.
@@ -218,8 +257,12 @@ template <typename T, int CC>
 int s2d_cc(const ConvGeo &g, const StemGeo &s, const void *x, void *x2, hipStream_t st)
 {
     const long total = (long)s.N * s.H2 * s.W2;
-    hipLaunchKernelGGL((s2d_kernel<T, CC>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const T *)x, (T *)x2, total,
-                       s.H, s.W, img_strides(g.layout, s.C, s.H, s.W));
+    const ImgStrides xs = img_strides(g.layout, s.C, s.H, s.W);
+    const dim3 grid((unsigned)((total + 255) / 256));
+    if (pixel_pairs(xs, CC))
+        hipLaunchKernelGGL((s2d_kernel<T, CC, true>), grid, dim3(256), 0, st, (const T *)x, (T *)x2, total, s.H, s.W, xs);
+    else
+        hipLaunchKernelGGL((s2d_kernel<T, CC, false>), grid, dim3(256), 0, st, (const T *)x, (T *)x2, total, s.H, s.W, xs);
     return check_launch();
 }
 
@@ -243,8 +286,12 @@ template <typename T, int CC>
 int d2s_cc(const ConvGeo &g, const StemGeo &s, const void *dx2, void *dx, int accumulate, hipStream_t st)
 {
     const long total = (long)s.N * s.H2 * s.W2;
-    hipLaunchKernelGGL((d2s_kernel<T, CC>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const T *)dx2, (T *)dx, total,
-                       s.H, s.W, img_strides(g.layout, s.C, s.H, s.W), accumulate);
+    const ImgStrides xs = img_strides(g.layout, s.C, s.H, s.W);
+    const dim3 grid((unsigned)((total + 255) / 256));
+    if (pixel_pairs(xs, CC))
+        hipLaunchKernelGGL((d2s_kernel<T, CC, true>), grid, dim3(256), 0, st, (const T *)dx2, (T *)dx, total, s.H, s.W, xs, accumulate);
+    else
+        hipLaunchKernelGGL((d2s_kernel<T, CC, false>), grid, dim3(256), 0, st, (const T *)dx2, (T *)dx, total, s.H, s.W, xs, accumulate);
     return check_launch();
 }
 

@@ -203,3 +203,26 @@ def test_image_stem_backward_data_over_runs_of_tiles(N, H, W):
     err = (got.permute(0, 3, 1, 2).cpu().double() - want).abs()
     # rounding to bf16: 2^-8 of the value; the sum of at most 1024 products in fp32: far below 2^-12 of its size, one unit of 6.4
     assert bool((err <= want.abs() * 2.0 ** -8 + 2.0 ** -10).all())
+
+
+# The copies around a stem read and write two neighbouring pixels of an NHWC row as words, and NCHW images element by element.  Values
+# are only moved, so both give the same bits.
+@pytest.mark.parametrize("C,R", [(1, 3), (2, 5), (3, 7), (4, 3)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_image_stem_copies(dtype, C, R):
+    x, old = (on_grid(gen.normal(980 + C, k, (3, C, 18, 26)), dtype) for k in range(2))
+    w = on_grid(gen.he_normal(980 + C, 2, (64, C, R, R)), dtype)
+    y, dx = {}, {}
+    for lay in (B.NSK_NHWC, B.NSK_NCHW):
+        gw = to_gpu(w, dtype, lay)
+        gy = B.conv2d_fwd(to_gpu(x, dtype, lay), gw, 2, R // 2, 1, lay)
+        y[lay] = to_host(gy, lay)
+        for accumulate in (False, True):
+            got = B.conv2d_dgrad(gy, gw, x.shape, 2, R // 2, 1, lay, out=to_gpu(old, dtype, lay), accumulate=accumulate)
+            dx[lay, accumulate] = to_host(got, lay)
+    assert max_rel_err(y[B.NSK_NHWC], oracle.conv2d_fwd(x, w, 2, R // 2, 1)) <= TOL[dtype]
+    assert np.array_equal(y[B.NSK_NHWC], y[B.NSK_NCHW])
+    for accumulate in (False, True):
+        want = oracle.conv2d_dgrad(y[B.NSK_NHWC], w, x.shape, 2, R // 2, 1) + (old if accumulate else 0)
+        assert max_rel_err(dx[B.NSK_NHWC, accumulate], want) <= TOL[dtype]
+        assert np.array_equal(dx[B.NSK_NHWC, accumulate], dx[B.NSK_NCHW, accumulate])
