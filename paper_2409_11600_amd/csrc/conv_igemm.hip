@@ -326,7 +326,7 @@ int igemm_stats_rows(int dtype, const IgemmArgs &a)
         if (halo_wide_applicable(dtype, a)) return halo_wide_stats_rows(a);
         if (halo_wide_fwd_s2_applicable(dtype, a)) return halo_wide_fwd_s2_stats_rows(a);
     }
-    // The pipelined kernel needs 16-byte stores of the partial sums; one row for every row block.  Its epilogue beats
+    // The pipelined kernel needs 16-byte stores of the partial sums; one or two rows for every row block.  Its epilogue beats
     // the separate pass over y at every size (us, convolution + batch-norm, pass / epilogue: 256->1024 1x1 at 14x14 N=128
     // 69.6 / 69.4, 64->128 1x1 stride 2 at 56x56 N=64 29.2 / 25.1, fp32 16->16 at 40x42 N=37 22.5 / 20.8, 72->104 at 29x37
     // N=20 34.0 / 20.5; 256->64 at 56x56 N=64, 3136 rows of sums, 50.1 / 51.5).

@@ -440,7 +440,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
         unsigned char *my_st = sa0 + (wm * WN + wn) * (32 * SROW);
         // Statistics epilogue (forward with a batch-norm behind it): a lane always reads back the same 16-byte piece
         // (VEC channels) of each staged row, so it adds those channels up over all the rows it stores; one cross-lane
-        // reduction per block and one row of partial sums.  With every value added across all lanes by itself
+        // reduction per block and at most two rows of partial sums.  With every value added across all lanes by itself
         // (64 exchanges per 32 channels, now 15) 256 -> 1024 1x1 on 25 k pixels took 45 us with statistics and 34 without.
         float ssum[FN][VEC], ssq[FN][VEC];
 #pragma unroll
@@ -491,7 +491,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
             // (VEC channels' sums and squares over the 64 / CPP lanes of a piece: as many values as lanes)
             static_assert(2 * VEC * CPP == 64, "a value a lane");
             static_assert(WM * WN * FN * 256 <= TB, "inside a stage");
-            // and over the wavefront rows through LDS, in fp64 and rounded once: one row of partial sums a block
+            static_assert(WM == 1 || WM == 2 || WM == 4, "wavefront rows");
+            // Four wavefront rows are added through LDS, in fp64, and leave two rows, the sum and what rounding it cuts off: as exact as a row
+            // each, half as many for the batch-norm behind to read.  (One rounded row moved means by up to 0.4 of their error against 64 bits.)
             float *part = (float *)sb0 + lane;
             float mine[FN];
 #pragma unroll
@@ -504,21 +506,25 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
                 }
                 fold_lanes<CPP>(v);
                 mine[ni] = v[0];
-                if (WM > 1 && wm > 0) part[((wm * WN + wn) * FN + ni) * 64] = v[0];
+                if (WM == 4 && wm > 0) part[((wm * WN + wn) * FN + ni) * 64] = v[0];
             }
-            if constexpr (WM > 1) {
+            if constexpr (WM == 4) {
                 lds_barrier();
                 if (wm > 0) return;
             }
-            const int e = lane / CPP % VEC;
-            float *r = a.stats + ((size_t)(lane / 32) * a.stats_rows + bm) * a.Ngemm;
+            const int e = lane / CPP % VEC, row = WM == 4 ? 2 * bm : bm * WM + wm;
+            float *r = a.stats + ((size_t)(lane / 32) * a.stats_rows + row) * a.Ngemm;
 #pragma unroll
             for (int ni = 0; ni < FN; ++ni) {
-                double sum = mine[ni];
-#pragma unroll
-                for (int w = 1; w < WM; ++w) sum += (double)part[((w * WN + wn) * FN + ni) * 64];
                 const int col = wcol0 + ni * 32 + lane % CPP * VEC + e;
-                if (col < a.Ngemm) r[col] = (float)sum;
+                if constexpr (WM == 4) {
+                    double sum = mine[ni];
+#pragma unroll
+                    for (int w = 1; w < WM; ++w) sum += (double)part[((w * WN + wn) * FN + ni) * 64];
+                    mine[ni] = (float)sum;
+                    if (col < a.Ngemm) r[a.Ngemm + col] = mine[ni] - mine[ni] == 0.f ? (float)(sum - (double)mine[ni]) : 0.f;
+                }
+                if (col < a.Ngemm) r[col] = mine[ni];
             }
         }
     } else {
@@ -560,18 +566,18 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
 // Forward, fp32 unit only / this, us: 3x3 64 -> 64 at 56x56, N=64 148 / 107; 128 -> 128 at 28x28, N=64 154 / 94; 72 -> 100 at 29x37,
 // N=20 45 / 33; 1x1 256 -> 768 on 10 k pixels 50 / 30; error against 64 bits 4.3e-7 / 1.0e-7, 4.2e-7 / 2.0e-7, 4.5e-7 / 1.0e-7, 2.9e-7 / 0.9e-7.
 struct PipeTile {
-    int bm, bn, wk;      // wk: parts a k-tile's sums are made in
+    int bm, bn, rows, wk;      // rows: of statistics; wk: parts a k-tile's sums are made in
     double step, rest, fixed, per_mb, stats;
 };
-constexpr PipeTile kTilesBf16[] = {{256, 128, 1, 0.827, 4.71, 0.99, 0.017, 1.4}, {128, 128, 1, 0.494, 3.15, 1.3, 0.219, 0},
-                                   {256, 64, 1, 0.587, 3.34, 0.92, 0.217, 0},    {128, 64, 1, 0.302, 1.47, 2.96, 0.074, 0},
-                                   {64, 64, 2, 0.224, 2.12, 1.25, 0.251, 0},     {128, 32, 1, 0.30, 0.9, 2.34, 0.162, 0}, 
-                                   {128, 128, 1, 0, 0, 1e9, 0, 0}};   // kShort (taken by a rule, see cheapest)
+constexpr PipeTile kTilesBf16[] = {{256, 128, 2, 1, 0.827, 4.71, 0.99, 0.017, 1.4}, {128, 128, 2, 1, 0.494, 3.15, 1.3, 0.219, 0},
+                                   {256, 64, 2, 1, 0.587, 3.34, 0.92, 0.217, 0},    {128, 64, 2, 1, 0.302, 1.47, 2.96, 0.074, 0},
+                                   {64, 64, 2, 2, 0.224, 2.12, 1.25, 0.251, 0},     {128, 32, 2, 1, 0.30, 0.9, 2.34, 0.162, 0},
+                                   {128, 128, 2, 1, 0, 0, 1e9, 0, 0}};   // kShort (taken by a rule, see cheapest)
 constexpr int kShort = 6;
 constexpr int kSmallest = 5;
-constexpr PipeTile kTilesF32[] = {{128, 64, 2, 0.770, 1.96, 4.79, 0.238, 0}, {64, 64, 2, 0.563, 0, 5.08, 0.361, 0},
-                                  {256, 128, 1, 2.19, 6.83, 0, 0.039, 0},    {128, 32, 1, 0.557, 1.01, 4.03, 0.255, 0},
-                                  {64, 32, 2, 0.322, 0.73, 3.76, 0.258, 0},  {32, 32, 4, 0.172, 0.68, 3.98, 0.23, 0}};
+constexpr PipeTile kTilesF32[] = {{128, 64, 2, 2, 0.770, 1.96, 4.79, 0.238, 0}, {64, 64, 1, 2, 0.563, 0, 5.08, 0.361, 0},
+                                  {256, 128, 2, 1, 2.19, 6.83, 0, 0.039, 0},    {128, 32, 2, 1, 0.557, 1.01, 4.03, 0.255, 0},
+                                  {64, 32, 2, 2, 0.322, 0.73, 3.76, 0.258, 0},  {32, 32, 1, 4, 0.172, 0.68, 3.98, 0.23, 0}};
 
 long block_count(const PipeTile &t, const IgemmArgs *a, int count)
 {
@@ -617,7 +623,7 @@ template <int N> int cheapest(const PipeTile (&tiles)[N], int es, const IgemmArg
         return es == 2 && i == 0 && a[0].Ktot * 2 <= 4 * PK_BYTES && block_count(tiles[0], a, count) > 512 ? kShort : i;
     };
     if (es != 2 || !stats || tiles[best].wk > 1) return short_reduction(best);   // (fp32: no shape gained)
-    for (int i = 0; i < N; ++i) cost[i] += tiles[i].stats + 1.5e-3 * ceil_div(a[0].M, tiles[i].bm);
+    for (int i = 0; i < N; ++i) cost[i] += tiles[i].stats + 1.5e-3 * ceil_div(a[0].M, tiles[i].bm) * tiles[i].rows;
     for (int i = 0; i < N; ++i)
         if (tiles[i].wk == 1 && cost[i] < cost[best]) best = i;
     return short_reduction(best);
@@ -693,7 +699,7 @@ bool igemm_pipe_gathers(int dtype, const IgemmArgs *a, int count)
 int igemm_pipe_stats_rows(int dtype, const IgemmArgs &a)
 {
     const PipeTile &t = dtype == NSK_BF16 ? kTilesBf16[cheapest(kTilesBf16, 2, &a, 1, true)] : kTilesF32[cheapest(kTilesF32, 4, &a, 1, true)];
-    return ceil_div(a.M, t.bm);
+    return ceil_div(a.M, t.bm) * t.rows;
 }
 
 }  // namespace nsk

@@ -145,29 +145,41 @@ template <int FM, int FN> __device__ __forceinline__ bool finite_sums(const f32x
     return top < 0x7f800000u;
 }
 
+// The value of lane ^ O: O = 2, 4, 8 within a row of 16 lanes, on the vector unit.
+template <int O> __device__ __forceinline__ float lane_xor(float v)
+{
+    auto moved = [](float x, auto ctl) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctl)::value, 0xf, 0xf, true));
+    };
+    static_assert(O == 2 || O == 4 || O == 8, "within a row");
+    if constexpr (O == 2) return moved(v, std::integral_constant<int, 0x4e>{});      // quad_perm 2,3,0,1
+    else if constexpr (O == 8) return moved(v, std::integral_constant<int, 0x128>{});     // row_ror 8
+    else return moved(moved(v, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1b>{});     // row_half_mirror, quad_perm 3,2,1,0
+}
 // Sums of N values over the lanes with the same lane % CPP.  Each step halves what a lane still carries: it hands the half that the other
 // lane goes on with over for the half that it goes on with itself (N/2 + N/4 + ... exchanges, where adding every value across all lanes
-// takes N a step, each an LDS operation; the first two steps, lanes 32 and 16 apart, are swaps of registers).  Afterwards lane l holds
-// value l / (64 / N) (N <= 64 / CPP), or the values (l / CPP) * (N * CPP / 64) + 0, 1, ... of its lanes in v[0], v[1], ...
-template <int CPP, int N, int O = 32, int LEFT = N> __device__ __forceinline__ void fold_lanes(float (&v)[N])
+// takes N a step, each an LDS operation; those of lanes 32 and 16 apart are swaps of registers).  Neighbours first: the same sums bit by bit
+// as v += v of lane ^ CPP, then of lane ^ 2 * CPP, up to lane ^ 32.  Afterwards lane l holds value l / CPP % (64 / CPP) of its lanes in v[0], that plus 64 / CPP in
+// v[1], and so on (N < 64 / CPP: value l / CPP % N).
+template <int CPP, int N, int O = CPP, int LEFT = N> __device__ __forceinline__ void fold_lanes(float (&v)[N])
 {
-    if constexpr (O >= CPP) {
+    if constexpr (O < 64) {
         constexpr int H = LEFT / 2;
-        if constexpr (LEFT == 1) {
-            v[0] += __shfl_xor(v[0], O, 64);
-        } else if constexpr (O >= 16) {
+        if constexpr (O >= 16) {
 #pragma unroll
-            for (int i = 0; i < H; ++i) {
-                const unsigned a = __builtin_bit_cast(unsigned, v[i]), b = __builtin_bit_cast(unsigned, v[i + H]);
+            for (int i = 0; i < (H > 0 ? H : 1); ++i) {
+                const unsigned a = __builtin_bit_cast(unsigned, v[H > 0 ? 2 * i : 0]), b = __builtin_bit_cast(unsigned, v[H > 0 ? 2 * i + 1 : 0]);
                 const auto r = O == 32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false) : __builtin_amdgcn_permlane16_swap(a, b, false, false);
                 v[i] = __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
             }
+        } else if constexpr (LEFT == 1) {
+            v[0] += lane_xor<O>(v[0]);
         } else {
             const bool upper = (threadIdx.x & O) != 0;
 #pragma unroll
-            for (int i = 0; i < H; ++i) v[i] = (upper ? v[i + H] : v[i]) + __shfl_xor(upper ? v[i] : v[i + H], O, 64);
+            for (int i = 0; i < H; ++i) v[i] = (upper ? v[2 * i + 1] : v[2 * i]) + lane_xor<O>(upper ? v[2 * i] : v[2 * i + 1]);
         }
-        fold_lanes<CPP, N, O / 2, (H > 0 ? H : 1)>(v);
+        fold_lanes<CPP, N, O * 2, (H > 0 ? H : 1)>(v);
     }
 }
 
@@ -175,8 +187,8 @@ template <int CPP, int N, int O = 32, int LEFT = N> __device__ __forceinline__ v
 // sums from the first of those channels on, its squares `squares` floats further.
 template <int CPP> __device__ __forceinline__ void store_folded(const float (&sum)[8], const float (&sq)[8], float *r, size_t squares)
 {
-    constexpr int PER = CPP < 4 ? 1 : CPP / 4;      // values a lane ends up with
-    const int lane = threadIdx.x & 63, first = PER == 1 ? lane / 4 : lane / CPP * PER;
+    constexpr int LANES = CPP < 4 ? 16 : 64 / CPP, PER = 16 / LANES;      // values a lane ends up with
+    const int lane = threadIdx.x & 63;
     float v[16];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -184,9 +196,11 @@ template <int CPP> __device__ __forceinline__ void store_folded(const float (&su
         v[8 + e] = sq[e];
     }
     fold_lanes<CPP>(v);
-    r += (first >= 8 ? squares : 0) + lane % CPP * 8 + first % 8;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) r[i] = v[i];
+    for (int i = 0; i < PER; ++i) {
+        const int value = lane / CPP % LANES + i * LANES;
+        r[(value >= 8 ? squares : 0) + lane % CPP * 8 + value % 8] = v[i];
+    }
 }
 
 // Test and A/B switches: environment variables NSK_*, read ONCE (first use, or nsk_test_hooks_reload()) and never on

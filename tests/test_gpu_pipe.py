@@ -226,3 +226,27 @@ def test_image_stem_copies(dtype, C, R):
         want = oracle.conv2d_dgrad(y[B.NSK_NHWC], w, x.shape, 2, R // 2, 1) + (old if accumulate else 0)
         assert max_rel_err(dx[B.NSK_NHWC, accumulate], want) <= TOL[dtype]
         assert np.array_equal(dx[B.NSK_NHWC, accumulate], dx[B.NSK_NCHW, accumulate])
+
+
+# A row of sums a wavefront row, or the sum of four and what rounding it cut off: 32 pixels of 2^19 in the first wavefront row and a 1 in a later one
+# add up to 2^24 + 1 (squares 2^43 + 1), which no single float holds.
+@pytest.mark.parametrize("dtype,tile", [("bf16", t) for t in range(1, 8)] + [("f32", t) for t in range(1, 7)])
+def test_statistics_round_no_block(dtype, tile, nsk_env):
+    nsk_env("NSK_IGEMM_TILE", str(tile))
+    x, w = torch.zeros(1, 16, 16, 8, device="cuda"), torch.zeros(8, 1, 1, 8, device="cuda")
+    x.view(256, 8)[:32, 0], x.view(256, 8)[64, 0], w[:, 0, 0, 0] = 2.0 ** 19, 1.0, 1.0
+    y, stats = B.conv2d_fwd_stats(x.to(torch_dtype(dtype)), w.to(torch_dtype(dtype)), 1, 0)
+    assert torch.equal(stats[0].double().sum(0).cpu(), torch.full((8,), 2.0 ** 24 + 1, dtype=torch.float64))
+    assert torch.equal(stats[1].double().sum(0).cpu(), torch.full((8,), 2.0 ** 43 + 1, dtype=torch.float64))
+
+
+# The order of those sums, on one block of 32 pixels: a lane adds up every eighth, then neighbours, pairs and halves come together.
+def test_order_of_the_statistics(nsk_env):
+    nsk_env("NSK_IGEMM_TILE", "6")
+    x, w = gen.normal(985, 0, (1, 8, 4, 8)), gen.he_normal(985, 1, (32, 8, 1, 1))
+    y, stats = B.conv2d_fwd_stats(to_gpu(x, "f32", B.NSK_NHWC), to_gpu(w, "f32", B.NSK_NHWC), 1, 0)
+    p = y.reshape(4, 8, 32).cpu().numpy()
+    s = ((p[0] + p[1]) + p[2]) + p[3]
+    s = s[0::2] + s[1::2]
+    s = s[0::2] + s[1::2]
+    assert np.array_equal((s[0] + s[1]).astype(np.float32), stats[0, 0].cpu().numpy())
