@@ -21,7 +21,7 @@
 // halves: bf16 104 -> 100 at 28x28, N=32 18.6 -> 13.0 us against element-wise stores, 1x1 12 -> 36 at 56x56, N=64 40.5 -> 23.3.
 //
 // Measured against the one-tile-ahead kernel (us, forward): bf16 3x3 512->512 at 7x7, N=64 77.7 -> 27.2; fp32 3x3 72->100
-// at 29x37, N=20 80.8 -> 43.9 (and 33 on pieces, see the tiles); fp32 3x3 16->16 at 32x32, N=8 16.8 -> 5.7.  Without the exchange of pieces the first takes
+// at 29x37, N=20 80.8 -> 43.9 (and 39 on pieces, see the tiles); fp32 3x3 16->16 at 32x32, N=8 16.8 -> 5.7.  Without the exchange of pieces the first takes
 // 64 us (bank conflicts).
 #include <limits.h>
 
@@ -289,16 +289,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
 #pragma unroll
             for (int i = 0; i < 2 / WK; ++i) {
                 const int g = wk * (2 / WK) + i, at0 = ((g * 4 + fk) ^ fsw) * 16, at1 = ((g * 4 + 2 + fk) ^ fsw) * 16;
-                auto split = [&](const unsigned char *row, auto SCALED) {
+                auto split = [&](const unsigned char *row) {
                     const f32x4 u = *(const f32x4 *)(row + at0), v = *(const f32x4 *)(row + at1);
                     const float x[8] = {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
-                    return split3<decltype(SCALED)::value>(x);
+                    return split3(x);
                 };
                 Pieces pa[FM], pb[FN];
 #pragma unroll
-                for (int mi = 0; mi < FM; ++mi) pa[mi] = split(&NSK_STAGE(I, sa)[oa + mi * 32 * PK_BYTES], std::true_type{});
+                for (int mi = 0; mi < FM; ++mi) pa[mi] = split(&NSK_STAGE(I, sa)[oa + mi * 32 * PK_BYTES]);
 #pragma unroll
-                for (int ni = 0; ni < FN; ++ni) pb[ni] = split(&NSK_STAGE(I, sb)[ob + ni * 32 * PK_BYTES], std::false_type{});
+                for (int ni = 0; ni < FN; ++ni) pb[ni] = split(&NSK_STAGE(I, sb)[ob + ni * 32 * PK_BYTES]);
                 multiply_pieces<true>(pb, pa, acc, lo);
             }
             return;
@@ -331,7 +331,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
     };
     auto products = [&](auto PIECES) {
         start_requests();
-        start_sums(decltype(PIECES)::value ? kPieceScale : 1.f);
+        start_sums(decltype(PIECES)::value ? kSumScale : 1.f);
         static_for<0, ST - 1>([&](auto S) { request(S); });   // (k-tiles past the end are requested out of range: zeros)
         // The loop body is ST steps without a branch, the remainder follows: where a step could leave the loop, the compiler
         // would take the stage requested last for one that the first step reads, and wait for it.
@@ -390,7 +390,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
 #pragma unroll
             for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[mi][ni][v] = (acc[mi][ni][v] + lo[mi][ni][v]) * (1.f / kPieceScale);
+                for (int v = 0; v < 16; ++v) acc[mi][ni][v] = (acc[mi][ni][v] + lo[mi][ni][v]) * (1.f / kSumScale);
         if (__syncthreads_or(!finite_sums(acc))) products(std::integral_constant<bool, false>{});
     }
     __syncthreads();
@@ -562,9 +562,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
 // 256 -> 128 on 200 k 50 -> 35).
 // fp32: tiles of 4096 outputs and more multiply bf16 pieces (nsk_internal.h), bound by the vector unit that makes them, so the sub-tile of a
 // wavefront is 64 x 64 or 64 x 32; smaller tiles, for layers that leave CUs idle otherwise, run on the fp32 matrix unit (256 clocks per 32 x 32
-// and k-tile).  Fitted to 260 forward passes of the same ranges: the choice is on average 1.8% off the best shape, 10% in the worst twentieth.
-// Forward, fp32 unit only / this, us: 3x3 64 -> 64 at 56x56, N=64 148 / 107; 128 -> 128 at 28x28, N=64 154 / 94; 72 -> 100 at 29x37,
-// N=20 45 / 33; 1x1 256 -> 768 on 10 k pixels 50 / 30; error against 64 bits 4.3e-7 / 1.0e-7, 4.2e-7 / 2.0e-7, 4.5e-7 / 1.0e-7, 2.9e-7 / 0.9e-7.
+// and k-tile).  Fitted to 260 forward passes of the same ranges, with six products a pair of pieces; the eight take the pieces' shapes 10-20%
+// longer.  The line stays where it was, since their errors are half: costs fitted anew would win 4% over 90 passes by handing layers to the fp32 unit
+// (backward-data of the ragged unit 72 -> 100 at 29x37, NCHW: 45 / 42 us, error of the unit 2.0e-7 / 3.8e-7).
+// Forward, fp32 unit only / this, us: 3x3 64 -> 64 at 56x56, N=64 156 / 134; 128 -> 128 at 28x28, N=64 142 / 131; 72 -> 100 at 29x37,
+// N=20 45 / 39; 1x1 256 -> 768 on 10 k pixels 48 / 35; error against 64 bits 3.0e-7 / 1.0e-7, 4.2e-7 / 2.0e-7, 3.2e-7 / 1.0e-7, 2.1e-7 / 0.9e-7.
 struct PipeTile {
     int bm, bn, rows, wk;      // rows: of statistics; wk: parts a k-tile's sums are made in
     double step, rest, fixed, per_mb, stats;

@@ -26,12 +26,12 @@
 // up to 3% more in fp32, 1-3% less in bf16.
 //
 // fp32 from about 1 GFLOP on: products of bf16 pieces (nsk_internal.h), 64 x 64 outputs a wavefront so that each piece is used twice, the
-// k-tile's two groups of 16 pixels to a pair of wavefronts whose sums meet in LDS at the end.  Bound by the vector unit (176 instructions
-// for the pieces and about 80 of addresses for 24 products of 32 clocks).  One chain for the large products and one for the small, no
+// k-tile's two groups of 16 pixels to a pair of wavefronts whose sums meet in LDS at the end.  The vector unit (208 instructions
+// for the pieces and about 80 of addresses) and the 32 products of 32 clocks share the bound.  One chain for the large products and one for the small, no
 // banking (a third set of sums does not fit in the registers of two wavefronts a SIMD), so splits are at most kPieces k-tiles.  Fp32 unit /
-// this, us with the reduction, and error: 128->128 3x3 at 28x28 N=64 174 / 98, 2.3e-7 / 1.8e-7; 256->256 at 14x14 N=32 84 / 54, 2.0e-7 /
-// 1.3e-7; 72->100 at 29x37 N=20 50.6 / 37, 2.1e-7 / 1.2e-7; 64->64 at 32x32 N=128 (a halo kernel on the fp32 unit) 95 / 84, 4.2e-7 / 1.8e-7.
-// With products of both sizes in one chain, banked every three k-tiles, errors were 3.1e-7, 1.7e-7, 2.3e-7 and times 4-7% longer.
+// this, us with the reduction, and error: 128->128 3x3 at 28x28 N=64 140 / 114, 2.2e-7 / 1.8e-7; 256->256 at 14x14 N=32 77 / 63, 2.0e-7 /
+// 1.3e-7; 72->100 at 29x37 N=20 44 / 41, 2.0e-7 / 1.2e-7; 64->64 at 32x32 N=128 95 / 92, 2.2e-7 / 1.8e-7.  (With six products a pair of pieces, less
+// exact for sums of few products, 97, 55, 39 and 81.)
 #include "nsk_internal.h"
 
 namespace nsk {
@@ -172,16 +172,16 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WK == 2 ? 2 : 1) void wgrad_pipe
             // lane (channel, half) holds pixels half, half + 2, ... of its group of 16, the same of both operands
             Pieces pa[FM], pb[FN];
             const int g = wk * 16;
-            auto split = [&](const unsigned char *col, auto ROW, auto SCALED) {
+            auto split = [&](const unsigned char *col, auto ROW) {
                 float x[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) x[e] = *(const float *)(col + (g + 2 * e) * ROW.value);
-                return split3<decltype(SCALED)::value>(x);
+                return split3(x);
             };
 #pragma unroll
-            for (int i = 0; i < FM; ++i) pa[i] = split(&NSK_STAGE(I, sa)[fa[i]], std::integral_constant<int, RBA>{}, std::true_type{});
+            for (int i = 0; i < FM; ++i) pa[i] = split(&NSK_STAGE(I, sa)[fa[i]], std::integral_constant<int, RBA>{});
 #pragma unroll
-            for (int i = 0; i < FN; ++i) pb[i] = split(&NSK_STAGE(I, sx)[fx[i]], std::integral_constant<int, RBX>{}, std::false_type{});
+            for (int i = 0; i < FN; ++i) pb[i] = split(&NSK_STAGE(I, sx)[fx[i]], std::integral_constant<int, RBX>{});
             multiply_pieces<false>(pa, pb, acc[0], sum);
         } else if constexpr (ES == 2) {
 #pragma unroll
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WK == 2 ? 2 : 1) void wgrad_pipe
 #pragma unroll
             for (int ni = 0; ni < FN; ++ni)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) sum[mi][ni][v] *= 1.f / kPieceScale;
+                for (int v = 0; v < 16; ++v) sum[mi][ni][v] *= 1.f / kSumScale;
         if (__syncthreads_or(!finite_sums(sum))) products(std::integral_constant<bool, false>{});
         // the second wavefront of a pair hands its sums to the first, one accumulator tile at a time
         static_assert(WM * WN * 4096 <= KT * RBX, "inside a stage");
@@ -362,10 +362,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WK == 2 ? 2 : 1) void wgrad_pipe
 
 // Measured (us, with the reduction): bf16 3x3 512->512 at 7x7 N=64 66.8 -> 32; 3x3 stride 2 64->128 at 56x56 N=64 38.9 ->
 // 21; 1x1 256->1024 at 14x14 N=128 33 -> 26 (a 256 x 128 tile with separate moving wavefronts); 3x3 16->16 at 32x32 N=256
-// 21.8 -> 17; fp32 3x3 128->128 at 28x28 N=64 197 -> 150; fp32 72->100 at 29x37 N=20 65 -> 46 (37 on pieces).
+// 21.8 -> 17; fp32 3x3 128->128 at 28x28 N=64 197 -> 150; fp32 72->100 at 29x37 N=20 65 -> 46 (41 on pieces).
 //
 // Tile shapes with what a k-tile, the rest of a block and the launch cost in shader clocks (bf16 measured on 35 problems, where the launch is
-// left out; fp32 fitted to 260 problems of 16 to 1024 channels, 50 to 400 k pixels: 3-5% off, and the choice 0.1% off the best shape on average).
+// left out; fp32 fitted to 260 problems of 16 to 1024 channels, 50 to 400 k pixels, with six products a pair of pieces; the eight take longer, and the lines stay, as the pieces' errors are the smaller).
 // bf16 is bound by the fill of LDS (a 128 x 128 tile brings in 32 KB per k-tile at 38 B/clk), fp32 by the matrix and vector units.
 struct Shape {
     int bm, bn, kt;

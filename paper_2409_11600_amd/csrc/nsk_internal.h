@@ -71,20 +71,19 @@ inline Div make_div(int d)
 __device__ inline int divide(int n, const Div &d) { return (int)(((unsigned long long)(unsigned)n * d.mul) >> d.sh); }
 
 // fp32 products on the bf16 matrix unit.  x = h + m + l exactly, three bf16 pieces (h to nearest, m cut, l what is left: 8 + 8 + 8 bits),
-// and x*y = hh' + (hm' + mh') + (mm' + hl' + lh') + terms below 2^-23 of it whose signs are those of the rests and cancel: six bf16
-// products of 16 indices in place of eight fp32 ones of 2, in 192 clocks instead of 512, and with fewer roundings of the sums.  What the
-// vector unit spends on the pieces, 11 instructions for two values, bounds it instead: a wavefront should multiply each piece it makes
-// several times.  Registers and LDS only, 4000 steps (fp32 operations, TFLOP/s; the fp32 unit's limit is 157): sub-tile of 64 x 64 243,
-// 64 x 32 214, 32 x 32 184 with four wavefronts a SIMD and 135 with two.
-// Limits: |x| from 2^-110 on is exact (below, the last piece leaves the range of bf16).  Gradients that vanish over a long sequence get there,
-// so the activation or gradient of a pass is multiplied by 2^24 first (SCALED: exact from 2^-134 on; filters, and x in backward-weight, are
-// not) and its sums by 2^-24 at the end.  A value that is not finite, or too large for that, makes sums that are not finite: a kernel that
-// sees such (finite_sums) makes them again on the fp32 unit.
+// and x*y is the sum of the products of the pieces: eight bf16 products of 16 indices in place of eight fp32 ones of 2, in 256 clocks instead
+// of 512, and with fewer roundings of the sums.  The ninth, l*l', lies below 2^-32 of x*y.  (Without m*l' and l*m', six products, a sum of one or
+// two products was off by up to 1.3e-7 of them, where the fp32 unit rounds to 0.6e-7.)  What the vector unit spends on the pieces, 13 instructions
+// for two values, bounds it beside the products: a wavefront should multiply each piece it makes several times.
+// Both operands are multiplied by 2^24 first and the sums by 2^-48 at the end: the last bit of the smallest float, 2^-149, then is a whole bf16,
+// 2^-125, and every finite operand has exact pieces (unscaled, the last piece of |x| < 2^-110 leaves the range of bf16, and gradients that
+// vanish over a long sequence, or decayed filters, get there).  A value that is not finite or too large for that (2^104, products 2^80) makes sums
+// that are not finite: a kernel that sees such (finite_sums) makes them again on the fp32 unit.
 struct Pieces {
     bf16x8 h, m, l;
 };
-constexpr float kPieceScale = 16777216.f;
-template <bool SCALED> __device__ __forceinline__ Pieces split3(const float (&x)[8])
+constexpr float kPieceScale = 16777216.f, kSumScale = kPieceScale * kPieceScale;
+__device__ __forceinline__ Pieces split3(const float (&x)[8])
 {
     typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
     struct Quad {
@@ -92,7 +91,7 @@ template <bool SCALED> __device__ __forceinline__ Pieces split3(const float (&x)
     } h, m, l;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float a = SCALED ? x[2 * i] * kPieceScale : x[2 * i], b = SCALED ? x[2 * i + 1] * kPieceScale : x[2 * i + 1];
+        const float a = x[2 * i] * kPieceScale, b = x[2 * i + 1] * kPieceScale;
         bf16x2 p;
         p[0] = (bf16_t)a;
         p[1] = (bf16_t)b;
@@ -108,7 +107,7 @@ template <bool SCALED> __device__ __forceinline__ Pieces split3(const float (&x)
     return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
 }
 // hi + lo += sum over 16 indices of x[i] * y[j], x the matrix unit's first operand; sums at [i][j], or [j][i] where SECOND_ROWS.  Where lo is
-// not hi, the large products have accumulators of their own: a sum is then rounded at its full size once in 16 indices, not six times.
+// not hi, the large products have accumulators of their own: a sum is then rounded at its full size once in 16 indices, not eight times.
 template <bool SECOND_ROWS, int FX, int FY, int R, int C>
 __device__ __forceinline__ void multiply_pieces(const Pieces (&x)[FX], const Pieces (&y)[FY], f32x16 (&hi)[R][C], f32x16 (&lo)[R][C])
 {
@@ -119,6 +118,8 @@ __device__ __forceinline__ void multiply_pieces(const Pieces (&x)[FX], const Pie
 #pragma unroll
         for (int k = 0; k < C; ++k) {
             const int c = r & 1 ? C - 1 - k : k, i = SECOND_ROWS ? c : r, j = SECOND_ROWS ? r : c;
+            NSK_PRODUCT(m, l, lo)
+            NSK_PRODUCT(l, m, lo)
             NSK_PRODUCT(h, l, lo)
             NSK_PRODUCT(h, h, hi)
             NSK_PRODUCT(l, h, lo)

@@ -46,6 +46,52 @@ def test_every_tile(i, tile, nsk_env):
     assert max_rel_err(to_host(dx, LAY), oracle.conv2d_dgrad(dy, w, x.shape, st, R // 2, 1) + old) <= TOL["f32"]
 
 
+# What decayed filters and vanishing gradients come to: the last bits of either operand below what a bf16 can hold by itself (2^-133) from 2^-110
+# on, subnormal floats at 2^-126.  The other operand is of ordinary size, and the results are floats; one tolerance for all passes.
+@pytest.mark.parametrize("tile", [1, 2, 3, 4])
+@pytest.mark.parametrize("exponent", [-112, -120, -126])
+def test_tiny_operands(exponent, tile, nsk_env):
+    nsk_env("NSK_IGEMM_TILE", str(tile))
+    N, C, H, W, K = 2, 40, 12, 11, 72
+    tiny = np.float32(2.0 ** exponent)
+    x, w, dy = gen.normal(1960, 0, (N, C, H, W)), gen.he_normal(1960, 1, (K, C, 1, 1)), gen.normal(1960, 2, (N, K, H, W))
+    calls = {
+        "forward": (x, w, "nchw,kc->nkhw", lambda a, b: B.conv2d_fwd(a, b, 1, 0)),
+        "backward-data": (dy, w, "nkhw,kc->nchw", lambda a, b: B.conv2d_dgrad(a, b, x.shape, 1, 0)),
+        "backward-weight": (x, dy, "nchw,nkhw->kc", lambda a, b: B.conv2d_wgrad(a, b, w.shape, 1, 0)),
+    }
+    for name, (a, b, product, call) in calls.items():
+        for a_, b_ in ((a * tiny, b), (a, b * tiny)):
+            flat = [v[:, :, 0, 0] if v.shape[2:] == (1, 1) else v for v in (a_.astype(np.float64), b_.astype(np.float64))]
+            want = np.einsum(product, *flat)
+            got = to_host(call(to_gpu(a_, "f32", LAY), to_gpu(b_, "f32", LAY)), LAY).reshape(want.shape)
+            assert np.max(np.abs(got - want)) <= 2e-6 * np.sqrt(np.mean(want ** 2)), (name, a_ is a)
+
+
+# A sum with one product in it (one channel, one pixel, one output channel that is not zero) is that product rounded once, 2^-24 of it; what
+# the sums of the smaller pieces round and the product of the last ones, which is left out, add less than 2^-29.
+@pytest.mark.parametrize("tile", [1, 2, 3, 4])
+def test_one_product_is_rounded_once(tile, nsk_env):
+    nsk_env("NSK_IGEMM_TILE", str(tile))
+    N, C, H, W, K = 2, 36, 16, 16, 68
+    r = np.random.default_rng(9)
+    mantissas = lambda *shape: (r.integers(1 << 23, 1 << 24, shape) * 2.0 ** -23).astype(np.float32)
+    x, w, dy = np.zeros((N, C, H, W), np.float32), mantissas(K, C, 1, 1), np.zeros((N, K, H, W), np.float32)
+    n, h, v = np.meshgrid(np.arange(N), np.arange(H), np.arange(W), indexing="ij")
+    x[n, (5 * n + 3 * h + v) % C, h, v] = mantissas(N, H, W)
+    dy[n, (n + 7 * h + v) % K, h, v] = mantissas(N, H, W)
+    x1, dy1 = np.zeros_like(x), np.zeros_like(dy)       # backward-weight: one pixel
+    x1[1, :, 7, 9], dy1[1, :, 7, 9] = mantissas(C), mantissas(K)
+    d = lambda a: a.astype(np.float64)
+    for name, got, want in (
+            ("forward", B.conv2d_fwd(to_gpu(x, "f32", LAY), to_gpu(w, "f32", LAY), 1, 0), np.einsum("nchw,kc->nkhw", d(x), d(w[:, :, 0, 0]))),
+            ("backward-data", B.conv2d_dgrad(to_gpu(dy, "f32", LAY), to_gpu(w, "f32", LAY), x.shape, 1, 0), np.einsum("nkhw,kc->nchw", d(dy), d(w[:, :, 0, 0]))),
+            ("backward-weight", B.conv2d_wgrad(to_gpu(x1, "f32", LAY), to_gpu(dy1, "f32", LAY), w.shape, 1, 0), np.einsum("nchw,nkhw->kc", d(x1), d(dy1)))):
+        got = to_host(got, LAY).reshape(want.shape)
+        worst = float(np.max(np.abs(got - want) / np.where(want == 0, 1, want)))
+        assert worst <= 2.0 ** -24 * (1 + 2.0 ** -5), (name, worst)
+
+
 # One rounding of a sum is 2.5e-8 (rms) of its size, n of them in a row 2.5e-8 * sqrt(n / 2).  A product of 16 indices rounds its large sum
 # twice (eight indices at a time): 288 roundings for 2304 indices, 3.0e-7, and what the smaller products, the last additions and the splits add,
 # below 0.8e-7, makes 3.1e-7 in quadrature; where two wavefronts share the reduction 144 of them, 2.3e-7.
