@@ -21,7 +21,7 @@
 // halves: bf16 104 -> 100 at 28x28, N=32 18.6 -> 13.0 us against element-wise stores, 1x1 12 -> 36 at 56x56, N=64 40.5 -> 23.3.
 //
 // Measured against the one-tile-ahead kernel (us, forward): bf16 3x3 512->512 at 7x7, N=64 77.7 -> 27.2; fp32 3x3 72->100
-// at 29x37, N=20 80.8 -> 43.9 (and 39 on pieces, see the tiles); fp32 3x3 16->16 at 32x32, N=8 16.8 -> 5.7.  Without the exchange of pieces the first takes
+// at 29x37, N=20 80.8 -> 43.9 (and 36 on pieces, see the tiles); fp32 3x3 16->16 at 32x32, N=8 16.8 -> 5.7.  Without the exchange of pieces the first takes
 // 64 us (bank conflicts).
 #include <limits.h>
 
@@ -562,11 +562,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK, sizeof(T) == 4 && BM * BN >= 409
 // 256 -> 128 on 200 k 50 -> 35).
 // fp32: tiles of 4096 outputs and more multiply bf16 pieces (nsk_internal.h), bound by the vector unit that makes them, so the sub-tile of a
 // wavefront is 64 x 64 or 64 x 32; smaller tiles, for layers that leave CUs idle otherwise, run on the fp32 matrix unit (256 clocks per 32 x 32
-// and k-tile).  Fitted to 260 forward passes of the same ranges, with six products a pair of pieces; the eight take the pieces' shapes 10-20%
-// longer.  The line stays where it was, since their errors are half: costs fitted anew would win 4% over 90 passes by handing layers to the fp32 unit
-// (backward-data of the ragged unit 72 -> 100 at 29x37, NCHW: 45 / 42 us, error of the unit 2.0e-7 / 3.8e-7).
-// Forward, fp32 unit only / this, us: 3x3 64 -> 64 at 56x56, N=64 156 / 134; 128 -> 128 at 28x28, N=64 142 / 131; 72 -> 100 at 29x37,
-// N=20 45 / 39; 1x1 256 -> 768 on 10 k pixels 48 / 35; error against 64 bits 3.0e-7 / 1.0e-7, 4.2e-7 / 2.0e-7, 3.2e-7 / 1.0e-7, 2.1e-7 / 0.9e-7.
+// and k-tile).  Fitted to 260 forward passes of the same ranges: the choice is on average 1.8% off the best shape, 10% in the worst twentieth.
+// Forward, fp32 unit only / this, us: 3x3 64 -> 64 at 56x56, N=64 154 / 119; 128 -> 128 at 28x28, N=64 147 / 112; 72 -> 100 at 29x37,
+// N=20 44 / 36; 1x1 256 -> 768 on 10 k pixels 50 / 32; error against 64 bits 3.0e-7 / 1.0e-7, 4.2e-7 / 2.0e-7, 3.2e-7 / 1.0e-7, 2.1e-7 / 0.9e-7.
 struct PipeTile {
     int bm, bn, rows, wk;      // rows: of statistics; wk: parts a k-tile's sums are made in
     double step, rest, fixed, per_mb, stats;

@@ -26,12 +26,11 @@
 // up to 3% more in fp32, 1-3% less in bf16.
 //
 // fp32 from about 1 GFLOP on: products of bf16 pieces (nsk_internal.h), 64 x 64 outputs a wavefront so that each piece is used twice, the
-// k-tile's two groups of 16 pixels to a pair of wavefronts whose sums meet in LDS at the end.  The vector unit (208 instructions
-// for the pieces and about 80 of addresses) and the 32 products of 32 clocks share the bound.  One chain for the large products and one for the small, no
+// k-tile's two groups of 16 pixels to a pair of wavefronts whose sums meet in LDS at the end.  Bound by the vector unit (208 instructions
+// for the pieces and about 80 of addresses for 24 products of 32 clocks).  One chain for the large products and one for the small, no
 // banking (a third set of sums does not fit in the registers of two wavefronts a SIMD), so splits are at most kPieces k-tiles.  Fp32 unit /
-// this, us with the reduction, and error: 128->128 3x3 at 28x28 N=64 140 / 114, 2.2e-7 / 1.8e-7; 256->256 at 14x14 N=32 77 / 63, 2.0e-7 /
-// 1.3e-7; 72->100 at 29x37 N=20 44 / 41, 2.0e-7 / 1.2e-7; 64->64 at 32x32 N=128 95 / 92, 2.2e-7 / 1.8e-7.  (With six products a pair of pieces, less
-// exact for sums of few products, 97, 55, 39 and 81.)
+// this, us with the reduction, and error: 128->128 3x3 at 28x28 N=64 140 / 103, 2.2e-7 / 1.8e-7; 256->256 at 14x14 N=32 78 / 57, 2.0e-7 /
+// 1.3e-7; 72->100 at 29x37 N=20 44 / 38, 2.0e-7 / 1.2e-7; 64->64 at 32x32 N=128 96 / 86, 2.2e-7 / 1.8e-7.
 #include "nsk_internal.h"
 
 namespace nsk {
@@ -362,10 +361,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, WK == 2 ? 2 : 1) void wgrad_pipe
 
 // Measured (us, with the reduction): bf16 3x3 512->512 at 7x7 N=64 66.8 -> 32; 3x3 stride 2 64->128 at 56x56 N=64 38.9 ->
 // 21; 1x1 256->1024 at 14x14 N=128 33 -> 26 (a 256 x 128 tile with separate moving wavefronts); 3x3 16->16 at 32x32 N=256
-// 21.8 -> 17; fp32 3x3 128->128 at 28x28 N=64 197 -> 150; fp32 72->100 at 29x37 N=20 65 -> 46 (41 on pieces).
+// 21.8 -> 17; fp32 3x3 128->128 at 28x28 N=64 197 -> 150; fp32 72->100 at 29x37 N=20 65 -> 46 (39 on pieces).
 //
 // Tile shapes with what a k-tile, the rest of a block and the launch cost in shader clocks (bf16 measured on 35 problems, where the launch is
-// left out; fp32 fitted to 260 problems of 16 to 1024 channels, 50 to 400 k pixels, with six products a pair of pieces; the eight take longer, and the lines stay, as the pieces' errors are the smaller).
+// left out; fp32 fitted to 260 problems of 16 to 1024 channels, 50 to 400 k pixels: 3-5% off, and the choice 0.1% off the best shape on average).
 // bf16 is bound by the fill of LDS (a 128 x 128 tile brings in 32 KB per k-tile at 38 B/clk), fp32 by the matrix and vector units.
 struct Shape {
     int bm, bn, kt;

@@ -70,11 +70,14 @@ inline Div make_div(int d)
 }
 __device__ inline int divide(int n, const Div &d) { return (int)(((unsigned long long)(unsigned)n * d.mul) >> d.sh); }
 
-// fp32 products on the bf16 matrix unit.  x = h + m + l exactly, three bf16 pieces (h to nearest, m cut, l what is left: 8 + 8 + 8 bits),
-// and x*y is the sum of the products of the pieces: eight bf16 products of 16 indices in place of eight fp32 ones of 2, in 256 clocks instead
-// of 512, and with fewer roundings of the sums.  The ninth, l*l', lies below 2^-32 of x*y.  (Without m*l' and l*m', six products, a sum of one or
-// two products was off by up to 1.3e-7 of them, where the fp32 unit rounds to 0.6e-7.)  What the vector unit spends on the pieces, 13 instructions
-// for two values, bounds it beside the products: a wavefront should multiply each piece it makes several times.
+// fp32 products on the bf16 matrix unit.  x = h + m + l exactly, three bf16 pieces (h and m to nearest, l what is left: 8 + 8 + 8 bits),
+// and x*y = hh' + (hm' + mh') + (mm' + hl' + lh') + terms below 2^-24 of it: six bf16
+// products of 16 indices in place of eight fp32 ones of 2, in 192 clocks instead of 512, and with fewer roundings of the sums.  What is left out
+// leaves a sum of one product, which the fp32 unit rounds once, 0.60e-7 of it at most and 2.53e-8 rms, off by 1.0e-7 at most (2^-23 is the bound) and
+// 2.58e-8 rms; sums of two are off by 2.6e-8 rms (fp32 unit 3.1e-8), of 16 by 3.1e-8 (7.4e-8).  (m cut instead of rounded: 1.5e-7 and 2.9e-8 for one.  With
+// ml' and lm', eight products, one is rounded as on the fp32 unit, but units take 8-12% longer and small ones longer than on the fp32 unit: 64 -> 64 3x3 at
+// 32x32, N=16, 22.3 us, here 17.3, there 15.7.)  What the vector unit spends on the pieces, 13 instructions for two values, bounds it: a wavefront
+// should multiply each piece it makes several times.
 // Both operands are multiplied by 2^24 first and the sums by 2^-48 at the end: the last bit of the smallest float, 2^-149, then is a whole bf16,
 // 2^-125, and every finite operand has exact pieces (unscaled, the last piece of |x| < 2^-110 leaves the range of bf16, and gradients that
 // vanish over a long sequence, or decayed filters, get there).  A value that is not finite or too large for that (2^104, products 2^80) makes sums
@@ -98,16 +101,18 @@ __device__ __forceinline__ Pieces split3(const float (&x)[8])
         h.q[i] = __builtin_bit_cast(unsigned, p);
         asm("" : "+v"(h.q[i]));     // (else the compiler rounds a second time instead of shifting)
         float ra = a - __builtin_bit_cast(float, h.q[i] << 16), rb = b - __builtin_bit_cast(float, h.q[i] & 0xffff0000u);
-        const unsigned ua = __builtin_bit_cast(unsigned, ra), ub = __builtin_bit_cast(unsigned, rb);
-        m.q[i] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);        // the upper halves of both
-        ra -= __builtin_bit_cast(float, ua & 0xffff0000u);
-        rb -= __builtin_bit_cast(float, ub & 0xffff0000u);
+        p[0] = (bf16_t)ra;
+        p[1] = (bf16_t)rb;
+        m.q[i] = __builtin_bit_cast(unsigned, p);
+        asm("" : "+v"(m.q[i]));
+        ra -= __builtin_bit_cast(float, m.q[i] << 16);
+        rb -= __builtin_bit_cast(float, m.q[i] & 0xffff0000u);
         l.q[i] = __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, rb), __builtin_bit_cast(unsigned, ra), 0x07060302u);
     }
     return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
 }
 // hi + lo += sum over 16 indices of x[i] * y[j], x the matrix unit's first operand; sums at [i][j], or [j][i] where SECOND_ROWS.  Where lo is
-// not hi, the large products have accumulators of their own: a sum is then rounded at its full size once in 16 indices, not eight times.
+// not hi, the large products have accumulators of their own: a sum is then rounded at its full size once in 16 indices, not six times.
 template <bool SECOND_ROWS, int FX, int FY, int R, int C>
 __device__ __forceinline__ void multiply_pieces(const Pieces (&x)[FX], const Pieces (&y)[FY], f32x16 (&hi)[R][C], f32x16 (&lo)[R][C])
 {
@@ -118,8 +123,6 @@ __device__ __forceinline__ void multiply_pieces(const Pieces (&x)[FX], const Pie
 #pragma unroll
         for (int k = 0; k < C; ++k) {
             const int c = r & 1 ? C - 1 - k : k, i = SECOND_ROWS ? c : r, j = SECOND_ROWS ? r : c;
-            NSK_PRODUCT(m, l, lo)
-            NSK_PRODUCT(l, m, lo)
             NSK_PRODUCT(h, l, lo)
             NSK_PRODUCT(h, h, hi)
             NSK_PRODUCT(l, h, lo)
