@@ -67,8 +67,8 @@ def parse():
                     help="plain entry points only: no statistics hand-over from convolution to batch-norm, no ReLU mask")
     ap.add_argument("--fused-act", action="store_true",
                     help="a conv + batch-norm + ReLU that feeds one convolution does not store its normalised activation: that "
-                         "convolution applies it on load (measured: no gain on configuration 2, whose kernels have the fused "
-                         "load, 3-5%% slower where the activation is applied into the workspace instead; off by default)")
+                         "convolution applies it on load (measured: 3%% slower on configuration 2, whose kernels do that on the "
+                         "fp32 unit, 3-5%% where the activation is applied into the workspace instead; off by default)")
     ap.add_argument("--overlap", action="store_true",
                     help="issue the backward-weight calls on a second stream (measured: no gain on MI355X, the "
                          "convolution kernels already hold every CU)")

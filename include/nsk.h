@@ -272,8 +272,10 @@ int nsk_bn_relu_add_bwd_mask(const nsk_bn_desc_t *desc, const void *x, const uns
  *   over y.  Workspace: nsk_bn_workspace_bytes(desc, NSK_BN_FWD).
  * nsk_conv2d_fwd_act / nsk_conv2d_wgrad_act: nsk_conv2d_fwd[_stats] / nsk_conv2d_wgrad with x replaced by
  *   relu(coeffs[c]*x + coeffs[C + c]) rounded to desc->dtype, the value the apply pass would have stored (zero padding
- *   stays zero); coeffs belong to the C input channels of desc.  stats may be NULL.  The activation is applied into the
- *   workspace first.  Workspace: nsk_conv2d_act_workspace_bytes(desc, NSK_PASS_FWD | NSK_PASS_WGRAD) (host only);
+ *   stays zero); coeffs belong to the C input channels of desc.  stats may be NULL.  Kernels that apply it on
+ *   load (the fp32 3x3 64 -> 64 layers on 32-pixel-wide images) read x once and store nothing extra; every other layer is
+ *   served by applying the activation into the workspace first (same results, no saving).  Workspace:
+ *   nsk_conv2d_act_workspace_bytes(desc, NSK_PASS_FWD | NSK_PASS_WGRAD) (host only; may be 0 where the load applies it);
  *   nsk_conv2d_act_supported(desc) says whether the two calls take the layer at all.
  * nsk_bn_relu_bwd_act: nsk_bn_relu_add_bwd for that batch-norm without `out` and without a residual: the ReLU mask is
  *   [coeffs[c]*x + coeffs[C + c] > 0], the expression the consumers used.  Workspace: nsk_bn_workspace_bytes(desc,

@@ -75,7 +75,25 @@ void wgrad_geometry(const ConvGeo &g, WgradArgs *a)
 bool use_wgrad_halo(const ConvGeo &g, const WgradArgs &a)
 {
     if (!wgrad_halo64_applicable(g.dtype, a) || hooks().no_halo) return false;
-    return hooks().halo64_always || a.L >= (hooks().wh_min_rows >= 0 ? hooks().wh_min_rows : 150000);
+    return a.L >= (hooks().wh_min_rows >= 0 ? hooks().wh_min_rows : 150000);
+}
+
+// The fp32 64 -> 64 kernel that applies the activation on load gives every CU whole tiles of 8 image rows, 41 us each; ragged rounds of
+// them are slower than a pass for the activation and the pipelined kernel behind it (us with statistics, 32x32, pass and pipelined / on load: N=16
+// 22 / 42, 48 42.0 / 42.8, 64 49.3 / 46.5, 96 71 / 85, 128 88 / 87, 192 122 / 127, 256 157 / 167), and from three rounds on all are.  lean: for a call
+// without room for the activation, whole rounds of any number.
+bool takes_halo64_f32_act(const ConvGeo &g, const IgemmArgs &a, bool lean)
+{
+    if (hooks().igemm_tile != 0 || !halo64_f32_act_applicable(g.dtype, a)) return false;
+    const long tiles = (long)a.Nimg * (a.Hs / 8);
+    return hooks().halo64_always || ((lean || tiles <= 512) && (tiles + 255) / 256 * 256 * 100 <= tiles * 105);
+}
+
+// Its backward-weight sibling writes 147 KB of partial sums a block, up to 256 (us, as above: N=2 11 / 17, 16 24 / 31, 32 40 / 37, 64 57 / 54,
+// 128 96 / 90, 256 178 / 163).  lean: also below.
+bool takes_rows32_f32_act(const ConvGeo &g, const WgradArgs &a, bool lean)
+{
+    return !hooks().no_halo && rows32_f32_act_applicable(g.dtype, a) && (lean || a.L >= 32768 || hooks().halo64_always);
 }
 
 bool whole_vectors(const ConvGeo &g, int channels) { return channels % (g.dtype == NSK_BF16 ? 8 : 4) == 0; }
@@ -122,15 +140,17 @@ struct ConvPlan {
     bool grouped8 = false;   // wgrad: the kernel for groups of eight channels
     bool narrow = false;     // wgrad: the 3x3 kernel for 16 channels
     bool stem = false;   // the space-to-depth path plans its own workspace
-    size_t act_tmp = 0;  // calls that take a raw input: the applied activation
+    size_t act_tmp = 0;  // calls that take a raw input, on a kernel without a load that applies the activation: the applied activation
+    bool act_fused = false;
 };
 
 // groups > 1: grouped convolution (the filter holds C/groups input channels per output channel and only the generic
 // kernels run it).
 void fwd_geometry(const ConvGeo &g, IgemmArgs *a);
 
-// act: the call applies a batch-norm + ReLU to x (NHWC, one group), into the workspace.
-ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = false, bool pad = true)
+// act: the call applies a batch-norm + ReLU to x (NHWC, one group): on load where a kernel for the layer does that, else into the workspace.
+// lean: with as little workspace as the kernels for such a call can do with.
+ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = false, bool pad = true, bool lean = false)
 {
     ConvPlan p;
     const ConvGeo g = pad ? padded_geometry(desc, pass, groups) : desc;
@@ -144,7 +164,19 @@ ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = fal
         off += align_up(bytes);
         return at;
     };
-    if (act) p.act_tmp = take(desc.x_elems * g.es);
+    if (act) {
+        // (the pointers only matter for alignment tests: every tensor of these calls is 16-byte aligned)
+        if (pass == NSK_PASS_FWD && !p.stem) {
+            IgemmArgs a{};
+            fwd_geometry(g, &a);
+            p.act_fused = takes_halo64_f32_act(g, a, lean);
+        } else if (pass == NSK_PASS_WGRAD && !p.stem) {
+            WgradArgs wa{};
+            wgrad_geometry(g, &wa);
+            p.act_fused = takes_rows32_f32_act(g, wa, lean);
+        }
+        if (!p.act_fused) p.act_tmp = take(desc.x_elems * g.es);
+    }
     if (p.stem) {
         p.total = off + stem_workspace_bytes(g, pass);
         return p;
@@ -166,8 +198,10 @@ ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = fal
         if (nchw || pad_k) p.act_in2 = take(g.y_elems * g.es);
         WgradArgs wa{};
         wgrad_geometry(g, &wa);
-        p.halo = groups == 1 && use_wgrad_halo(g, wa);
-        if (p.halo)
+        p.halo = groups == 1 && !p.act_fused && use_wgrad_halo(g, wa);
+        if (p.act_fused)
+            p.splits = rows32_f32_act_partials(wa, nullptr);
+        else if (p.halo)
             p.splits = wgrad_halo64_partials(wa, nullptr);
         else {
             WgradArgs one = wa;   // one group's problem (aligned pointers and a split count stand for every launch)
@@ -209,12 +243,13 @@ ConvPlan plan_conv(const ConvGeo &desc, int pass, int groups = 1, bool act = fal
 }
 
 // The plan of a call: where the workspace is too small for the copies with whole channel vectors (an NHWC forward pass on the
-// operands as they lie needs none at all), the element-wise kernels take the layer.
+// operands as they lie needs none at all), the element-wise kernels take the layer; where it is too small for an applied activation, the kernel that
+// applies it on load, if there is one.
 ConvPlan plan_within(const ConvGeo &desc, int pass, int groups, bool act, const void *ws, size_t have)
 {
     const ConvPlan p = plan_conv(desc, pass, groups, act);
-    if ((ws ? have : 0) >= p.total || (p.geo.C == desc.C && p.geo.K == desc.K)) return p;
-    const ConvPlan q = plan_conv(desc, pass, groups, act, false);
+    if ((ws ? have : 0) >= p.total || ((!act || p.act_fused) && p.geo.C == desc.C && p.geo.K == desc.K)) return p;
+    const ConvPlan q = plan_conv(desc, pass, groups, act, false, true);
     return q.total <= (ws ? have : 0) ? q : p;
 }
 
@@ -345,7 +380,7 @@ int conv_fwd_impl(const nsk_conv_desc_t *desc, int groups, const void *x, const 
     NSK_TRY(check_ws(workspace, workspace_bytes, p.total));
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
-    if (act) {   // apply the activation first
+    if (act && !p.act_fused) {   // the kernel for this layer does not apply the activation on load
         NSK_TRY(launch_bn_act(input_as_bn(g), x, act, ws + p.act_tmp, st));
         x = ws + p.act_tmp;
         if (p.stem) ws += align_up(g.x_elems * g.es);
@@ -387,6 +422,10 @@ int conv_fwd_impl(const nsk_conv_desc_t *desc, int groups, const void *x, const 
         a.Ktot = a.ntaps * cg;
         a.Ngemm = kg;
         a.wpk_bytes = (unsigned)(g.w_elems / (size_t)groups * g.es);
+    }
+    if (p.act_fused) {
+        NSK_TRY(launch_halo64_f32_act(a, act, fused ? stats : nullptr, rows, st));
+        return stats && !fused ? launch_bn_stats(output_as_bn(g), dst, stats, rows, st) : NSK_OK;
     }
     if (fused) {
         a.stats = stats;
@@ -714,7 +753,7 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
     if (!partial) NSK_TRY(check_ws(workspace, workspace_bytes, p.total));
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
-    if (act) {   // apply the activation first
+    if (act && !p.act_fused) {   // the kernel for this layer does not apply the activation on load
         NSK_TRY(launch_bn_act(input_as_bn(g), x, act, ws + p.act_tmp, st));
         x = ws + p.act_tmp;
         if (p.stem) ws += align_up(g.x_elems * g.es);
@@ -754,7 +793,9 @@ static int conv_wgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
         a.part = dw;
         return launch_wgrad_pipe(g.dtype, a, st);
     }
-    if (p.halo)
+    if (p.act_fused)
+        NSK_TRY(launch_rows32_f32_act(a, act, st));
+    else if (p.halo)
         NSK_TRY(launch_wgrad_halo64(a, st));
     else if (p.pipe)
         NSK_TRY(launch_wgrad_pipe(g.dtype, a, st));

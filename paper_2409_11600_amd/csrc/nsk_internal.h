@@ -341,6 +341,11 @@ int launch_fs64_fwd_s2(const IgemmArgs &a, hipStream_t stream);
 bool halo_wide_multi_applicable(int dtype, const IgemmArgs *a, int count);
 int launch_halo_wide_multi(const IgemmArgs *a, int count, hipStream_t stream);
 
+// fp32 3x3 64 -> 64 layers on images 32 pixels wide, act [2][64]: of relu(act[c]*x + act[64 + c]), applied on load.  Forward (stats: the rows that the
+// kernel of the stored activation would leave) and backward-weight (partial sums as wgrad_halo64)
+bool halo64_f32_act_applicable(int dtype, const IgemmArgs &a);
+int launch_halo64_f32_act(const IgemmArgs &a, const float *act, float *stats, int stats_rows, hipStream_t stream);
+
 // layers with at most four channels on one side (the 3-channel stride-1 image stem): direct kernels, no MFMA
 bool tiny_src_applicable(int dtype, const IgemmArgs &a);    // few source channels (forward)
 int launch_tiny_src(int dtype, const IgemmArgs &a, hipStream_t stream);
@@ -386,6 +391,9 @@ int launch_wgrad_pipe(int dtype, const WgradArgs &a, hipStream_t stream);   // g
 bool wgrad_halo64_applicable(int dtype, const WgradArgs &a);
 int wgrad_halo64_partials(const WgradArgs &a, int *chunks_per_block);
 int launch_wgrad_halo64(const WgradArgs &a, hipStream_t stream);
+bool rows32_f32_act_applicable(int dtype, const WgradArgs &a);
+int rows32_f32_act_partials(const WgradArgs &a, int *chunks_per_block);
+int launch_rows32_f32_act(const WgradArgs &a, const float *act, hipStream_t stream);
 // at most four input channels: partial sums in the layout of the generic kernel
 bool tiny_wgrad_applicable(int dtype, const WgradArgs &a);
 int launch_tiny_wgrad(int dtype, const WgradArgs &a, hipStream_t stream);

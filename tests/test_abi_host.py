@@ -71,6 +71,19 @@ def test_workspace_queries_are_consistent():
     assert L.nsk_bn_workspace_bytes(ctypes.byref(bd), 5) == 0
 
 
+def test_activation_on_load_asks_for_no_room_for_it():
+    """fp32 3x3 64 -> 64 on 32-pixel-wide images: nothing forward, at most 256 partial sums for the weights; elsewhere the activation."""
+    L = B.lib()
+    size = lambda d, ps: L.nsk_conv2d_act_workspace_bytes(ctypes.byref(d), ps)
+    d = B.conv_desc((128, 64, 32, 32), (64, 3, 3), 1, 1, 1, B.NSK_F32, B.NSK_NHWC)
+    assert size(d, B.NSK_PASS_FWD) == 0
+    assert 0 < size(d, B.NSK_PASS_WGRAD) <= 256 * 64 * 9 * 64 * 4
+    for other in (B.conv_desc((128, 64, 32, 33), (64, 3, 3), 1, 1, 1, B.NSK_F32, B.NSK_NHWC),
+                  B.conv_desc((128, 64, 32, 32), (64, 3, 3), 1, 1, 1, B.NSK_BF16, B.NSK_NHWC)):
+        x = 128 * 64 * 32 * other.W * (4 if other.dtype == B.NSK_F32 else 2)
+        assert size(other, B.NSK_PASS_FWD) >= x and size(other, B.NSK_PASS_WGRAD) >= x
+
+
 def test_compute_calls_reject_bad_arguments_without_a_gpu():
     L = B.lib()
     d = B.conv_desc((2, 8, 8, 8), (8, 3, 3), 1, 1, 1, B.NSK_F32, B.NSK_NCHW)

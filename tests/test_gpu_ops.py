@@ -1,5 +1,7 @@
 """GPU parity of every libnsk entry point against the CPU oracle, element by element, on shapes
 that span several tiles and ragged tails (through the C ABI via the ctypes binding)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -704,6 +706,42 @@ def test_fused_activation_calls(i, nsk_env):
     assert max_rel_err(to_host(dy, B.NSK_NHWC), dy_want) <= tol
     assert max_rel_err(dg.cpu().numpy(), dg_want) <= 1e-4
     assert max_rel_err(db.cpu().numpy(), db_want) <= 1e-4
+
+
+# The kernels that apply it on load, without room for the activation: no workspace forward, the partial sums backward (256 at most).  Sizes: a
+# single chunk of two rows, ragged numbers of chunks and tiles a block; the hook takes the kernels below their size, without it the small ones are taken
+# because the workspace holds no activation.  Rows of statistics behind the kernel's own are zeros.
+@pytest.mark.parametrize("N,H,forward", [(1, 8, True), (3, 24, True), (87, 32, True), (128, 32, True), (192, 32, True), (1, 2, False), (5, 10, False)])
+@pytest.mark.parametrize("hook", [True, False])
+def test_activation_on_load_without_room_for_it(N, H, forward, hook, nsk_env):
+    if hook:
+        nsk_env("NSK_HALO64_ALWAYS", "1")
+    print(f"activation on load {N} {H} hook {hook}", flush=True)
+    L, lay, shape = B.lib(), B.NSK_NHWC, (N, 64, H, 32)
+    x, w, dz = gen.normal(1790, 0, shape), gen.he_normal(1790, 1, (64, 64, 3, 3)), gen.normal(1790, 2, shape)
+    coeffs = np.stack([1 + 0.3 * gen.normal(1790, 3, (64,)), 0.4 * gen.normal(1790, 4, (64,))]).astype(np.float32)
+    a = np.maximum(x * coeffs[0][:, None, None] + coeffs[1][:, None, None], 0).astype(np.float32)
+    gx, gw, gdz, gc = to_gpu(x, "f32", lay), to_gpu(w, "f32", lay), to_gpu(dz, "f32", lay), torch.from_numpy(coeffs).cuda()
+    st, p = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream), lambda t: ctypes.c_void_p(t.data_ptr())
+    d = B.conv_desc(shape, (64, 3, 3), 1, 1, 1, B.NSK_F32, lay)
+    if forward and (hook or N >= 128):       # (whole rounds of eight rows a CU)
+        rows = int(L.nsk_conv2d_stats_rows(ctypes.byref(d)))
+        y, check = guarded((N, H, 32, 64), torch.float32)
+        stats, check_stats = guarded((2, rows, 64), torch.float32)
+        assert L.nsk_conv2d_fwd_act(ctypes.byref(d), p(gx), p(gc), p(gw), p(y), p(stats), None, 0, st) == B.NSK_OK
+        torch.cuda.synchronize()
+        check(), check_stats()
+        got = to_host(y, lay)
+        assert max_rel_err(got, oracle.conv2d_fwd(a, w, 1, 1, 1)) <= TOL["f32"]
+        sums = stats.double().sum(1).cpu().numpy()
+        assert np.max(np.abs(sums[0] - got.sum((0, 2, 3))) / np.sqrt((got * got).sum((0, 2, 3)) * got[:, 0].size)) <= 1e-6
+        assert np.max(np.abs(sums[1] / (got * got).sum((0, 2, 3)) - 1)) <= 1e-5
+    room = torch.empty(min(N * H // 2, 256) * 64 * 9 * 64, device="cuda")
+    dw, check = guarded((64, 3, 3, 64), torch.float32)
+    assert L.nsk_conv2d_wgrad_act(ctypes.byref(d), p(gx), p(gc), p(gdz), p(dw), 0, p(room), room.numel() * 4, st) == B.NSK_OK
+    torch.cuda.synchronize()
+    check()
+    assert max_rel_err(to_host(dw, lay), oracle.conv2d_wgrad(a, dz, w.shape, 1, 1, 1)) <= TOL["f32"]
 
 
 BN_SHAPES = [(4, 64, 9, 11), (3, 16, 16, 16), (2, 256, 7, 7), (2, 1024, 5, 5), (5, 24, 6, 7), (2, 3, 10, 10),
