@@ -4,6 +4,7 @@
 #include <limits.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -700,9 +701,11 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
         }
         return NSK_OK;
     }
-    // Small fp32 layers whose launch is that of the pipelined kernel: it fetches the filter itself, and no packing goes before it.
+    // Small fp32 layers whose launch is that of the pipelined kernel: it fetches the filter itself, and no packing goes before it.  (The classes
+    // without a tap count for the tile as they do in the launch on a packed filter: the same sums in the same order.)
     const bool one_launch = n_pending + n_zeros <= 4 && n_pending > 0 && !nchw && groups == 1 && !packed;
-    if (one_launch && igemm_pipe_multi_applicable(g.dtype, pending, n_pending) && igemm_pipe_gathers(g.dtype, pending, n_pending)) {
+    if (one_launch) std::copy(zeros, zeros + n_zeros, pending + n_pending);
+    if (one_launch && igemm_pipe_multi_applicable(g.dtype, pending, n_pending) && igemm_pipe_gathers(g.dtype, pending, n_pending + n_zeros)) {
         for (int i = 0; i < n_pending; ++i) {
             pending[i].gather = 1;
             pending[i].wpk = w;
@@ -710,10 +713,7 @@ static int conv_dgrad_impl(const nsk_conv_desc_t *desc, int groups, const void *
             pending[i].w_sc = (int)w_sc;
             for (int t = 0; t < pk_nt[i]; ++t) pending[i].w_tap[t] = (unsigned char)(pk_taps[i][t] / cg);
         }
-        for (int i = 0; i < n_zeros; ++i) {
-            zeros[i].gather = 1;
-            pending[n_pending + i] = zeros[i];
-        }
+        for (int i = 0; i < n_zeros; ++i) pending[n_pending + i].gather = 1;
         return launch_igemm_pipe_multi(g.dtype, pending, n_pending + n_zeros, st);
     }
     // one packing launch for all classes, then their multiplies
