@@ -772,28 +772,13 @@ int launch_fs64_fwd_s2(const IgemmArgs &g, hipStream_t stream)
     a.magic_pw = ((1ULL << 40) + a.PW - 1) / a.PW;
     a.src_bytes = g.src_bytes;
     a.out_bytes = (unsigned)((size_t)g.Nimg * g.Ho * g.Wo * 64 * 2);
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return NSK_ERR_HIP;
-        cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    }
+    int cus = 0, rc = compute_units(&cus);
+    if (rc != NSK_OK) return rc;
     const int grid = f2_grid(g, g.stats ? F2_STATS_GRID : cus);
     if (g.stats && g.stats_rows != grid * 4) return NSK_ERR_BAD_DESC;   // the planner and the launch disagree
     const int smem = f2_lds_bytes(a.PW);
-    static bool attr_set = false;
-    if (!attr_set) {
-        const int smem_max = f2_lds_bytes(F2_MAX_PW);
-        hipError_t e = hipFuncSetAttribute((const void *)conv_fs64_fwd_s2_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_max);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)conv_fs64_fwd_s2_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_max);
-        if (e != hipSuccess) {
-            set_last_hip_error(e);
-            return NSK_ERR_HIP;
-        }
-        attr_set = true;
-    }
+    rc = g.stats ? allow_lds<conv_fs64_fwd_s2_kernel<true>>(f2_lds_bytes(F2_MAX_PW)) : allow_lds<conv_fs64_fwd_s2_kernel<false>>(f2_lds_bytes(F2_MAX_PW));
+    if (rc != NSK_OK) return rc;
     if (g.stats)
         hipLaunchKernelGGL(conv_fs64_fwd_s2_kernel<true>, dim3(grid), dim3(256), smem, stream, a);
     else
@@ -819,24 +804,12 @@ int launch_fs64_dgrad_s2(const IgemmArgs *g, int count, hipStream_t stream)
     a.magic_pw = ((1ULL << 40) + a.PW - 1) / a.PW;
     a.src_bytes = g[0].src_bytes;
     a.out_bytes = (unsigned)((size_t)g[0].Nimg * g[0].Ho * g[0].Wo * 64 * 2);
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return NSK_ERR_HIP;
-        cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    }
+    int cus = 0, rc = compute_units(&cus);
+    if (rc != NSK_OK) return rc;
     const int grid = a.tiles < cus ? a.tiles : cus;
     const int smem = S2_RING_MAX * S2_SLOT + 4 * 2 * S2_WPOS * S2_SLOT;
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)conv_fs64_dgrad_s2_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (e != hipSuccess) {
-            set_last_hip_error(e);
-            return NSK_ERR_HIP;
-        }
-        attr_set = true;
-    }
+    rc = allow_lds<conv_fs64_dgrad_s2_kernel>(smem);
+    if (rc != NSK_OK) return rc;
     hipLaunchKernelGGL(conv_fs64_dgrad_s2_kernel, dim3(grid), dim3(256), smem, stream, a);
     return check_launch();
 }

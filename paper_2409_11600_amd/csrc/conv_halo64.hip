@@ -971,67 +971,30 @@ int launch_halo64(const IgemmArgs &g, hipStream_t stream)
     a.stats = g.stats;
     a.stats_rows = g.stats_rows;
     for (int t = 0; t < 9; ++t) a.tapoff[t] = (g.add_h + g.off_h[t]) * a.PW + (g.add_w + g.off_w[t]);
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return NSK_ERR_HIP;
-        cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    }
+    int cus = 0, rc = compute_units(&cus);
+    if (rc != NSK_OK) return rc;
     const int want = g.stats ? kStatsGrid : cus;
     const int mi = fs_choice(g);
     if (mi) a.tiles = ceil_div(a.total_pos, 128 * mi);
     const int grid = a.tiles < want ? a.tiles : want;
     if (g.stats && g.stats_rows != grid * (mi ? 4 : 8)) return NSK_ERR_BAD_DESC;   // the planner and the launch disagree
-    static bool attr_set = false;
     const int smem = H_MAX_IN * H_IN_STRIDE + 64 * H_W_STRIDE + 256 * 4 + H_MAX_IN * 4 + 4 * 32 * H_IN_STRIDE;
     const int smem_pp = P_RING_MAX * P_SLOT + 64 * H_W_STRIDE;
     const int smem_fs = F_RING_MAX * F_SLOT + 4 * 64 * F_SLOT;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)conv_halo64_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)conv_halo64_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)conv_halo64_pp_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_pp);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)conv_halo64_pp_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_pp);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)conv_fs64_kernel<1, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_fs);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)conv_fs64_kernel<1, true>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_fs);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)conv_fs64_kernel<2, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_fs);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)conv_fs64_kernel<2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_fs);
-        if (e != hipSuccess) {
-            set_last_hip_error(e);
-            return NSK_ERR_HIP;
-        }
-        attr_set = true;
-    }
-    if (mi) {
-        if (mi == 1 && g.stats)
-            hipLaunchKernelGGL((conv_fs64_kernel<1, true>), dim3(grid), dim3(256), smem_fs, stream, a);
-        else if (mi == 1)
-            hipLaunchKernelGGL((conv_fs64_kernel<1, false>), dim3(grid), dim3(256), smem_fs, stream, a);
-        else if (g.stats)
-            hipLaunchKernelGGL((conv_fs64_kernel<2, true>), dim3(grid), dim3(256), smem_fs, stream, a);
-        else
-            hipLaunchKernelGGL((conv_fs64_kernel<2, false>), dim3(grid), dim3(256), smem_fs, stream, a);
+    auto go = [&](auto kernel, int threads, int bytes) {
+        rc = allow_lds<decltype(kernel)::value>(bytes);
+        if (rc != NSK_OK) return rc;
+        hipLaunchKernelGGL(decltype(kernel)::value, dim3(grid), dim3(threads), bytes, stream, a);
         return check_launch();
-    }
+    };
+    if (mi == 1 && g.stats) return go(Kernel<conv_fs64_kernel<1, true>>{}, 256, smem_fs);
+    if (mi == 1) return go(Kernel<conv_fs64_kernel<1, false>>{}, 256, smem_fs);
+    if (mi && g.stats) return go(Kernel<conv_fs64_kernel<2, true>>{}, 256, smem_fs);
+    if (mi) return go(Kernel<conv_fs64_kernel<2, false>>{}, 256, smem_fs);
     // the two-group kernel needs its ring (512 + 2*halo slots) to fit; wider images take the single-group kernel
-    const bool pp = two_group(g);
-    if (pp) {
-        if (a.accumulate)
-            hipLaunchKernelGGL(conv_halo64_pp_kernel<true>, dim3(grid), dim3(512), smem_pp, stream, a);
-        else
-            hipLaunchKernelGGL(conv_halo64_pp_kernel<false>, dim3(grid), dim3(512), smem_pp, stream, a);
-    } else if (a.accumulate)
-        hipLaunchKernelGGL(conv_halo64_kernel<true>, dim3(grid), dim3(256), smem, stream, a);
-    else
-        hipLaunchKernelGGL(conv_halo64_kernel<false>, dim3(grid), dim3(256), smem, stream, a);
-    return check_launch();
+    if (two_group(g))
+        return a.accumulate ? go(Kernel<conv_halo64_pp_kernel<true>>{}, 512, smem_pp) : go(Kernel<conv_halo64_pp_kernel<false>>{}, 512, smem_pp);
+    return a.accumulate ? go(Kernel<conv_halo64_kernel<true>>{}, 256, smem) : go(Kernel<conv_halo64_kernel<false>>{}, 256, smem);
 }
 
 }  // namespace nsk

@@ -698,30 +698,17 @@ int launch_classes(const IgemmArgs *g, int count, hipStream_t stream)
     a.out_bytes = (unsigned)((long long)f.Nimg * f.Ho * f.Wo * f.Co * 2);
     a.stats = count == 1 ? f.stats : nullptr;
     a.stats_rows = f.stats_rows;
-    static bool attr_set = false;
-    if (!attr_set) {
-        const void *k[12] = {
-            (const void *)conv_halo_wide_kernel<kNT, 4, 0, false>, (const void *)conv_halo_wide_kernel<kNT, 4, 1, false>,
-            (const void *)conv_halo_wide_kernel<kNT, 4, 2, false>, (const void *)conv_halo_wide_kernel<kNT, 2, 0, false>,
-            (const void *)conv_halo_wide_kernel<kNT, 2, 1, false>, (const void *)conv_halo_wide_kernel<kNT, 2, 2, false>,
-            (const void *)conv_halo_wide_kernel<kNT, 4, 0, true>,  (const void *)conv_halo_wide_kernel<kNT, 4, 1, true>,
-            (const void *)conv_halo_wide_kernel<kNT, 4, 2, true>,  (const void *)conv_halo_wide_kernel<kNT, 2, 0, true>,
-            (const void *)conv_halo_wide_kernel<kNT, 2, 1, true>,  (const void *)conv_halo_wide_kernel<kNT, 2, 2, true>};
-        for (int i = 0; i < 12; ++i) {
-            const hipError_t e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, W_LDS_MAX);
-            if (e != hipSuccess) {
-                set_last_hip_error(e);
-                return NSK_ERR_HIP;
-            }
-        }
-        attr_set = true;
-    }
     const int bn = block_channels(f);
     const int mode = f.accumulate ? 1 : a.stats ? 2 : 0;
     const bool nine = count == 1 && f.ntaps == 9;
     const dim3 grid((unsigned)(a.tiles * (a.K / bn)));
-#define NSK_WIDE_LAUNCH(MW, MODE, NINE) \
-    hipLaunchKernelGGL((conv_halo_wide_kernel<kNT, MW, MODE, NINE>), grid, dim3((MW + 1) * 64), p.smem, stream, a)
+    int rc = NSK_OK;
+#define NSK_WIDE_LAUNCH(MW, MODE, NINE)                                             \
+    do {                                                                            \
+        rc = allow_lds<conv_halo_wide_kernel<kNT, MW, MODE, NINE>>(W_LDS_MAX);      \
+        if (rc == NSK_OK)                                                           \
+            hipLaunchKernelGGL((conv_halo_wide_kernel<kNT, MW, MODE, NINE>), grid, dim3((MW + 1) * 64), p.smem, stream, a); \
+    } while (0)
 #define NSK_WIDE_MODES(MW, NINE)                    \
     do {                                            \
         if (mode == 1) NSK_WIDE_LAUNCH(MW, 1, NINE); \
@@ -737,7 +724,7 @@ int launch_classes(const IgemmArgs *g, int count, hipStream_t stream)
     }
 #undef NSK_WIDE_MODES
 #undef NSK_WIDE_LAUNCH
-    return check_launch();
+    return rc == NSK_OK ? check_launch() : rc;
 }
 
 }  // namespace
@@ -858,34 +845,16 @@ int launch_halo_wide_fwd_s2(const IgemmArgs &g, hipStream_t stream)
     a.stats = g.stats;
     a.stats_rows = g.stats_rows;
     if (g.stats && g.stats_rows != a.tiles) return NSK_ERR_BAD_DESC;   // the planner and the launch disagree
-    static bool attr_set = false;
-    if (!attr_set) {
-        const void *k[4] = {
-            (const void *)conv_halo_wide_kernel<kNT, 4, 0, false, true>, (const void *)conv_halo_wide_kernel<kNT, 4, 2, false, true>,
-            (const void *)conv_halo_wide_kernel<kNT, 2, 0, false, true>, (const void *)conv_halo_wide_kernel<kNT, 2, 2, false, true>};
-        for (int i = 0; i < 4; ++i) {
-            const hipError_t e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, W_LDS_MAX);
-            if (e != hipSuccess) {
-                set_last_hip_error(e);
-                return NSK_ERR_HIP;
-            }
-        }
-        attr_set = true;
-    }
     const int bn = block_channels(g);
-    const dim3 grid((unsigned)(a.tiles * (a.K / bn)));
-    if (bn == 128) {
-        if (a.stats)
-            hipLaunchKernelGGL((conv_halo_wide_kernel<kNT, 4, 2, false, true>), grid, dim3(6 * 64), p.smem, stream, a);
-        else
-            hipLaunchKernelGGL((conv_halo_wide_kernel<kNT, 4, 0, false, true>), grid, dim3(6 * 64), p.smem, stream, a);
-    } else {
-        if (a.stats)
-            hipLaunchKernelGGL((conv_halo_wide_kernel<kNT, 2, 2, false, true>), grid, dim3(4 * 64), p.smem, stream, a);
-        else
-            hipLaunchKernelGGL((conv_halo_wide_kernel<kNT, 2, 0, false, true>), grid, dim3(4 * 64), p.smem, stream, a);
-    }
-    return check_launch();
+    auto go = [&](auto kernel, int threads) {
+        const int rc = allow_lds<decltype(kernel)::value>(W_LDS_MAX);
+        if (rc != NSK_OK) return rc;
+        hipLaunchKernelGGL(decltype(kernel)::value, dim3((unsigned)(a.tiles * (a.K / bn))), dim3(threads), p.smem, stream, a);
+        return check_launch();
+    };
+    if (bn == 128)
+        return a.stats ? go(Kernel<conv_halo_wide_kernel<kNT, 4, 2, false, true>>{}, 6 * 64) : go(Kernel<conv_halo_wide_kernel<kNT, 4, 0, false, true>>{}, 6 * 64);
+    return a.stats ? go(Kernel<conv_halo_wide_kernel<kNT, 2, 2, false, true>>{}, 4 * 64) : go(Kernel<conv_halo_wide_kernel<kNT, 2, 0, false, true>>{}, 4 * 64);
 }
 
 }  // namespace nsk

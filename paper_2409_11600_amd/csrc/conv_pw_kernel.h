@@ -383,16 +383,8 @@ template <int KS, int FM, int TAPS, bool ACC, int NW> int launch_pw_acc(PwArgs p
     // at least half of a CU's LDS, so that 256 blocks land on 256 different CUs
     size_t smem = pw_smem(pa.g, 32 * FM);
     if (pw_grid(pa.g) == kPwGrid && smem < 84 * 1024) smem = 84 * 1024;
-    static bool configured = false;   // the attribute is a property of the function, set once per process
-    if (!configured) {
-        const hipError_t e = hipFuncSetAttribute((const void *)conv_pw_kernel<KS, FM, TAPS, ACC, NW>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) {
-            set_last_hip_error(e);
-            return NSK_ERR_HIP;
-        }
-        configured = true;
-    }
+    const int rc = allow_lds<conv_pw_kernel<KS, FM, TAPS, ACC, NW>>(160 * 1024);
+    if (rc != NSK_OK) return rc;
     hipLaunchKernelGGL((conv_pw_kernel<KS, FM, TAPS, ACC, NW>), dim3(pw_grid(pa.g)), dim3(256), smem, stream, pa);
     return check_launch();
 }

@@ -377,24 +377,10 @@ int launch_stem_halo(int backward, const void *src, const void *wpk, void *out, 
         const int u = t / 4 - 2, v = t % 4 - 2;
         a.tapoff[t] = backward ? -(u * a.PW + v) : u * a.PW + v;
     }
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return NSK_ERR_HIP;
-        cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    }
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)stem_halo_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kStemFwdSmem);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)stem_halo_dgrad_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kStemDgradSmem);
-        if (e != hipSuccess) {
-            set_last_hip_error(e);
-            return NSK_ERR_HIP;
-        }
-        attr_set = true;
-    }
+    int cus = 0, rc = compute_units(&cus);
+    if (rc != NSK_OK) return rc;
+    rc = backward ? allow_lds<stem_halo_dgrad_kernel>(kStemDgradSmem) : allow_lds<stem_halo_kernel>(kStemFwdSmem);
+    if (rc != NSK_OK) return rc;
     // two blocks per CU in the forward pass (65 KB of LDS each): one block's epilogue overlaps the other's MFMAs
     const int want = backward ? cus : (stats ? kStemStatsGrid : 2 * cus);
     const int grid = a.tiles < want ? a.tiles : want;

@@ -246,6 +246,32 @@ inline int allow_lds(const void *kernel, size_t bytes, std::atomic<unsigned long
     done.fetch_or(bit, std::memory_order_relaxed);
     return NSK_OK;
 }
+template <auto KERNEL> struct Kernel {
+    static constexpr auto value = KERNEL;
+};
+template <auto KERNEL> inline int allow_lds(size_t bytes)
+{
+    static std::atomic<unsigned long long> done{0};
+    return allow_lds((const void *)KERNEL, bytes, done);
+}
+
+// Compute units of the current device.
+inline int compute_units(int *n)
+{
+    static std::atomic<int> known[64];       // of each device, once asked for
+    int dev = 0, c = 0;
+    hipError_t e = hipGetDevice(&dev);
+    const bool kept = e == hipSuccess && dev >= 0 && dev < 64;
+    if (kept) c = known[dev].load(std::memory_order_relaxed);
+    if (e == hipSuccess && c == 0) e = hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) {
+        set_last_hip_error(e);
+        return NSK_ERR_HIP;
+    }
+    if (kept) known[dev].store(c, std::memory_order_relaxed);
+    *n = c > 0 ? c : 256;
+    return NSK_OK;
+}
 
 // Validated geometry of one convolution descriptor.
 struct ConvGeo {

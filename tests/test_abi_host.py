@@ -235,6 +235,21 @@ def test_the_tests_set_only_switches_that_the_library_reads():
             assert set(re.findall(r'(?:nsk_env\(|[{ ])"(NSK_[A-Z0-9_]+)"', text)) <= nsk_switches(), name
 
 
+def test_no_launcher_keeps_the_state_of_one_device():
+    """Room for dynamic LDS and the number of compute units belong to a device: granted and asked for through allow_lds and compute_units, which
+    know one device from another, and not behind a flag that the first call of the process sets."""
+    from paper_2409_11600_amd import build
+    seen = []
+    for name in sorted(os.listdir(build.CSRC)):
+        with open(os.path.join(build.CSRC, name)) as f:
+            text = f.read()
+        calls = len(re.findall(r"hipFuncSetAttribute\s*\(", text))
+        assert calls == (1 if name == "nsk_internal.h" else 0), name
+        assert not re.search(r"hipGetDeviceProperties|\bstatic (?:bool|int|unsigned|size_t) \w+\s*(?:=|;)", text), name
+        seen.append(name)
+    assert "nsk_internal.h" in seen and len(seen) > 20
+
+
 def test_kept_queries_follow_the_test_switches(nsk_env):
     """The binding keeps what the library answered for the sizes seen last: the same answer as asking again, an invalid size is
     refused every time, and a change of the switches (which may change the answer) is seen."""
