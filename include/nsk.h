@@ -107,8 +107,9 @@ int nsk_last_hip_error(void);
  *   NSK_POOL_GENERAL, NSK_REDUCE4, NSK_WH_NO_SPLIT   (set = that special kernel or variant is not chosen);
  *   NSK_HALO_WIDE_ALWAYS, NSK_HALO64_ALWAYS (set = chosen also where it does not pay);
  *   NSK_PW_MIN_ROWS, NSK_WH_MIN_ROWS = n   (size threshold of a special kernel);
- *   NSK_IGEMM_TILE = 1..6                           (tile shape of the generic kernel, which then takes every plain layer);
+ *   NSK_IGEMM_TILE = 1..7                           (tile shape of the generic kernel, which then takes every plain layer);
  *   NSK_GRU_SPLIT = 1, 2, 4                         (most blocks that share a sample of nsk_gru_seq_*);
+ *   NSK_GRU_FAR                                     (set = such blocks run on XCDs of their own);
  *   NSK_GRU_POLLS = n                               (failed polls after which such a block gives up; 0: at its first wait). */
 void nsk_test_hooks_reload(void);
 

@@ -129,7 +129,9 @@ __device__ inline float sum8(float v)
 }
 
 // values that blocks exchange: loaded at agent scope, which passes the CU's own cache by, and stored at that scope, which goes to memory, or,
-// where the group's blocks share an XCD (near), into the L2 that they share
+// where the group's blocks share an XCD (near), into the L2 that they share.  The language promises the latter to nobody outside the block
+// that stores: near is for gfx950, whose CUs write their stores through to the L2 of their XCD, where an agent-scope load from the same XCD finds them.  A
+// chip on which it did not would cost time, not results: the reader gives up after kPolls polls.
 template <typename U> __device__ inline void publish_bits(U *p, U b, bool near)
 {
     if (near)
@@ -168,6 +170,7 @@ struct GruSeqArgs {
     void *h, *saved, *dgi, *dgh;
     int T, N, H;
     int G, HU;       // blocks per sample and units per block (1 and H where a block has the sample to itself)
+    int apart;       // blocks of a sample lie so many apart: 8, on one XCD (1, test hook: on XCDs of their own)
     int polls;       // failed polls of a wavefront before it gives up
     bool unfinished; // G = 1: only the samples whose last row still holds the mark
 };
@@ -187,9 +190,9 @@ __global__ __launch_bounds__(8 * SLOTS + (SPLIT ? 64 * (BWD ? 3 : 1) : 0)) void 
     V *const lw = (V *)(smem + 2 * NV * HP * sizeof(T));        // [LS][M][MT]
     int *const near_lds = (int *)(lw + LS * M * MT);            // SPLIT: the group's blocks share an XCD
     const int tid = threadIdx.x, q = tid & 7, slot = tid >> 3, H = a.H, N = a.N;
-    // SPLIT: groups of G blocks that lie eight apart
-    const int n = SPLIT ? blockIdx.x / (8 * a.G) * 8 + blockIdx.x % 8 : blockIdx.x;
-    const int u0 = SPLIT ? blockIdx.x % (8 * a.G) / 8 * a.HU : 0, u1 = SPLIT ? min(u0 + a.HU, H) : H;
+    // SPLIT: groups of G blocks
+    const int block = (int)blockIdx.x, n = SPLIT ? block / (a.apart * a.G) * a.apart + block % a.apart : block;
+    const int u0 = SPLIT ? block % (a.apart * a.G) / a.apart * a.HU : 0, u1 = SPLIT ? min(u0 + a.HU, H) : H;
     if (SPLIT && n >= N) return;
     const long NH = (long)N * H;
     if constexpr (!SPLIT) {
@@ -601,6 +604,7 @@ int nsk_gru_seq_fwd(int dtype, int T, int N, int H, const void *gi, const void *
         GruSeqArgs a{};
         a.G = split_of(dtype, T, N, H, (hipStream_t)stream);
         a.polls = hooks().gru_polls >= 0 ? hooks().gru_polls : kPolls;
+        a.apart = hooks().gru_far ? 1 : 8;
         a.gi = gi; a.w = w_hh; a.b_ih = b_ih; a.b_hh = b_hh; a.h = h; a.saved = saved;
         a.T = T; a.N = N; a.H = H;
         return dispatch<false>(dtype, a, (hipStream_t)stream);
@@ -628,6 +632,7 @@ int nsk_gru_seq_bwd(int dtype, int T, int N, int H, const void *saved, const voi
         GruSeqArgs a{};
         a.G = split_of(dtype, T, N, H, (hipStream_t)stream);
         a.polls = hooks().gru_polls >= 0 ? hooks().gru_polls : kPolls;
+        a.apart = hooks().gru_far ? 1 : 8;
         a.saved_in = saved; a.h = (void *)h; a.dh_top = dh_top; a.w = w_hh_t; a.dgi = dgi; a.dgh = dgh;
         a.T = T; a.N = N; a.H = H;
         return dispatch<true>(dtype, a, (hipStream_t)stream);

@@ -455,6 +455,7 @@ void read_hooks()
     TestHooks h{};
     h.no_pw = on("NSK_NO_PW");
     h.no_halo = on("NSK_NO_HALO");
+    h.gru_far = on("NSK_GRU_FAR");
     h.no_fs = on("NSK_NO_FS");
     h.no_halo_wide = on("NSK_NO_HALO_WIDE");
     h.halo_wide_always = on("NSK_HALO_WIDE_ALWAYS");

@@ -212,7 +212,7 @@ template <int CPP> __device__ __forceinline__ void store_folded(const float (&su
 struct TestHooks {
     bool no_pw, no_halo, no_fs, no_halo_wide, halo_wide_always, halo64_always, halo_single, no_stem, no_stem_halo,
         no_tiny, no_depthwise, no_grouped8, no_pad, depthwise_no_rows, depthwise_no_cols, pool_general, reduce4,
-        wh_no_split;
+        wh_no_split, gru_far;
     long long pw_min_rows, wh_min_rows;   // -1: not set
     int igemm_tile, gru_split;                              // 0: not set
     int gru_polls;                                          // -1: not set

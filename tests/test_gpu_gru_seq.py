@@ -212,8 +212,11 @@ def test_gates_at_the_ends_of_their_range(H):
 # Blocks that share a sample: sequences too short to tell each other their XCD, the shortest that do, and longer ones, against one block a
 # sample.  (Forward the same products in the same order; the sums of the backward pass too.)
 @pytest.mark.parametrize("dtype,N,H", [("f32", 9, 256), ("f32", 70, 224), ("bf16", 5, 200)])
+# The blocks of a sample on one XCD, whose L2 they exchange through, and on several, through memory.
+@pytest.mark.parametrize("far", [None, "1"])
 @pytest.mark.parametrize("T", [2, 3, 4, 5, 17])
-def test_exchange_between_blocks(T, N, H, dtype, nsk_env):
+def test_exchange_between_blocks(T, far, N, H, dtype, nsk_env):
+    nsk_env("NSK_GRU_FAR", far) if far else None
     dt = torch_dtype(dtype)
     g = torch.Generator(device="cuda").manual_seed(T)
     r = lambda *shape: torch.randn(shape, generator=g, device="cuda")
