@@ -33,7 +33,7 @@ CONV_SHAPES = [
     (1, 4, 20, 16, 24, 5, 5, 2, 2, 1),         # 5x5 stride-2, 4 channels (space-to-depth, 3x3 coarse taps)
     (2, 1, 12, 18, 16, 3, 3, 2, 1, 1),         # 3x3 stride-2, single channel (space-to-depth, 2x2 coarse taps)
     (1, 64, 6, 66, 64, 3, 3, 1, 1, 1),         # 64->64 on a 66-wide image: too wide for the input ring, single-group halo kernel
-    (2, 64, 16, 32, 64, 3, 3, 1, 1, 1),        # 64->64 on 32-wide images with H % 8 == 0: the row-aligned fp32 kernels
+    (2, 64, 16, 32, 64, 3, 3, 1, 1, 1),        # 64->64 on 32-wide images
     (3, 3, 17, 19, 32, 3, 3, 1, 1, 1),         # 3 -> 32 stride-1 stem, odd extents (direct kernels for few channels)
     (2, 16, 11, 13, 3, 3, 3, 1, 1, 1),         # 16 -> 3: few OUTPUT channels (the same kernels with the roles swapped)
     (2, 2, 9, 9, 8, 3, 3, 2, 1, 1),            # 2 -> 8, stride 2 on odd extents (backward-data classes on the direct kernel)
@@ -409,7 +409,7 @@ def test_conv_gradients_accumulate(i, dtype, layout):
     assert max_rel_err(to_host(gdw, layout), want_dw) <= TOL[dtype]
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dtype", ["bf16"])       # (fp32 layers have no such kernel)
 def test_halo_backward_weight_many_chunks_per_block(dtype, nsk_env):
     """3x3 64->64 backward-weight on enough positions that every block of the halo kernel walks several chunks (the
     double-buffered hand-over between its moving and its multiplying wavefronts), against the oracle; the variant
@@ -560,7 +560,7 @@ def test_conv_is_bitwise_reproducible(dtype):
 # plus shapes that take the separate reduction pass.
 STATS_SHAPES = [
     ("bf16", (3, 64, 20, 24, 64, 3, 3, 1, 1, 1)),      # bf16 3x3 64->64 (two-group halo kernel), several tiles per block
-    ("f32", (2, 64, 16, 32, 64, 3, 3, 1, 1, 1)),       # fp32 row-aligned halo kernel
+    ("f32", (2, 64, 16, 32, 64, 3, 3, 1, 1, 1)),       # fp32 3x3 64->64, pipelined kernel
     ("bf16", (2, 128, 9, 9, 256, 1, 1, 1, 0, 1)),      # 1x1, pipelined kernel
     ("bf16", (2, 32, 16, 16, 64, 3, 3, 2, 1, 1)),      # stride 2, pipelined kernel
     ("f32", (2, 16, 15, 15, 32, 1, 1, 2, 0, 1)),       # fp32, ragged
@@ -579,7 +579,6 @@ def test_conv_statistics_feed_the_batch_norm(i, largest_tile, layout, nsk_env):
     sums of the stored y, and the batch-norm results must agree with the plain call (which reads y once more) and
     with the oracle."""
     dtype, (N, C, H, W, K, R, S, st, pd, dl) = STATS_SHAPES[i]
-    nsk_env("NSK_HALO64_ALWAYS", "1")
     if largest_tile:
         nsk_env("NSK_IGEMM_TILE", "1")
     print(f"stats case {STATS_SHAPES[i]} largest_tile={largest_tile} layout={layout}", flush=True)

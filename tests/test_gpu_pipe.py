@@ -24,12 +24,12 @@ SHAPES = [
 ]
 
 
-@pytest.mark.parametrize("tile", range(1, 7))
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+TILES = [("f32", t) for t in range(1, 7)] + [("bf16", t) for t in range(1, 8)]
+
+
+@pytest.mark.parametrize("dtype,tile", TILES)
 @pytest.mark.parametrize("i", range(len(SHAPES)))
 def test_every_tile(i, dtype, tile, nsk_env):
-    if dtype == "f32" and tile > 4:
-        pytest.skip("four tile shapes in f32")
     nsk_env("NSK_IGEMM_TILE", str(tile))
     N, C, H, W, K, R, S, st, pd, dl = SHAPES[i]
     print(f"pipelined kernel, shape {SHAPES[i]} {dtype} tile {tile}", flush=True)
@@ -64,11 +64,8 @@ def test_every_tile(i, dtype, tile, nsk_env):
         assert max_rel_err(to_host(dx, lay), want + old if accumulate else want) <= tol
 
 
-@pytest.mark.parametrize("tile", range(1, 7))
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dtype,tile", TILES)
 def test_every_tile_grouped(dtype, tile, nsk_env):
-    if dtype == "f32" and tile > 4:
-        pytest.skip("four tile shapes in f32")
     nsk_env("NSK_IGEMM_TILE", str(tile))
     N, cg, kg, G, H, W = 2, 16, 24, 3, 9, 13
     x = on_grid(gen.normal(950, 0, (N, G * cg, H, W)), dtype)
@@ -124,8 +121,7 @@ CLASSES = [
 ]
 
 
-@pytest.mark.parametrize("tile", [0, 1, 4, 6])
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dtype,tile", [("f32", 0), ("bf16", 0)] + TILES)
 @pytest.mark.parametrize("i", range(len(CLASSES)))
 def test_strided_backward_data_in_one_launch(i, dtype, tile, nsk_env):
     nsk_env("NSK_IGEMM_TILE", str(tile))
@@ -152,8 +148,7 @@ def test_strided_backward_data_in_one_launch(i, dtype, tile, nsk_env):
 
 
 @pytest.mark.parametrize("accumulate", [False, True])
-def test_f32_64_to_64_kernel_below_its_size(accumulate, nsk_env):
-    nsk_env("NSK_HALO64_ALWAYS", "1")
+def test_small_f32_64_to_64_layer(accumulate):
     x, dy = (on_grid(gen.normal(975, t, (3, 64, 16, 32)), "f32") for t in (0, 2))
     w = on_grid(gen.he_normal(975, 1, (64, 64, 3, 3)), "f32")
     gx, gw, gdy = (to_gpu(a, "f32", B.NSK_NHWC) for a in (x, w, dy))
@@ -230,7 +225,7 @@ def test_image_stem_copies(dtype, C, R):
 
 # A row of sums a wavefront row, or the sum of four and what rounding it cut off: 32 pixels of 2^19 in the first wavefront row and a 1 in a later one
 # add up to 2^24 + 1 (squares 2^43 + 1), which no single float holds.
-@pytest.mark.parametrize("dtype,tile", [("bf16", t) for t in range(1, 8)] + [("f32", t) for t in range(1, 7)])
+@pytest.mark.parametrize("dtype,tile", TILES)
 def test_statistics_round_no_block(dtype, tile, nsk_env):
     nsk_env("NSK_IGEMM_TILE", str(tile))
     x, w = torch.zeros(1, 16, 16, 8, device="cuda"), torch.zeros(8, 1, 1, 8, device="cuda")

@@ -1,6 +1,6 @@
 """The pipelined backward-weight kernel, every tile shape of it, where a tile can go wrong: fewer k-tiles than stages and every
 remainder of them, one and several splits, ragged rows and columns, stride, dilation, images of one pixel, groups; and the
-64 -> 64 kernels on problems that are below the size from which they are chosen."""
+bf16 64 -> 64 kernel on problems that are below the size from which it is chosen."""
 import numpy as np
 import pytest
 import torch
@@ -28,8 +28,6 @@ SHAPES = [
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("i", range(len(SHAPES)))
 def test_every_tile(i, dtype, tile, nsk_env):
-    if dtype == "f32" and tile > 1:
-        pytest.skip("one tile shape in f32")
     nsk_env("NSK_IGEMM_TILE", str(tile))
     nsk_env("NSK_NO_HALO", "1")
     N, C, H, W, K, R, S, st, pd, dl = SHAPES[i]
@@ -55,8 +53,6 @@ def test_every_tile(i, dtype, tile, nsk_env):
 @pytest.mark.parametrize("tile", [1, 2, 3])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_every_tile_grouped(dtype, tile, nsk_env):
-    if dtype == "f32" and tile > 1:
-        pytest.skip("one tile shape in f32")
     nsk_env("NSK_IGEMM_TILE", str(tile))
     N, cg, kg, G, H, W = 2, 16, 24, 3, 19, 13
     x = on_grid(gen.normal(980, 0, (N, G * cg, H, W)), dtype)
@@ -88,9 +84,10 @@ def test_error_does_not_grow_with_the_split(dtype, bar, N, C, H, K, R, stride):
             assert float((dw[:, r, s] - want).norm() / want.norm()) <= bar, (r, s)
 
 
+# (fp32 layers of these channels run on the pipelined kernel)
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(1, 7, 9), (3, 20, 20), (2, 16, 32), (5, 6, 66)])
-def test_64_to_64_kernels_below_their_size(shape, dtype, nsk_env):
+def test_64_to_64_layers_below_the_size_of_their_kernel(shape, dtype, nsk_env):
     nsk_env("NSK_WH_MIN_ROWS", "1")
     N, H, W = shape
     x, dy = (on_grid(gen.normal(990, t, (N, 64, H, W)), dtype) for t in (0, 2))
