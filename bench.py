@@ -313,6 +313,32 @@ def call_cost(net, f, args):
     return name, 0.0, 0.0
 
 
+def conv_totals(names, costs, ms):
+    """(flops, ms) of a step's convolutions: every nsk_conv2d call, the packing of all filters and the addition of all partial sums, which have
+    no flops, among them."""
+    own = [i for i, n in enumerate(names) if n.startswith("nsk_conv2d")]
+    return sum(costs[i][1] for i in own), sum(ms[i] for i in own)
+
+
+def roofline(dtype, kind, flops, byts, ms, names):
+    """What one launch of a group of equal calls reaches against what bounds it.  Large fp32 layers run on the bf16 matrix unit, six products
+    of pieces for one: its peak over six is theirs, and frac_of_f32_unit compares with the fp32 unit."""
+    pieces = dtype == "f32" and kind.startswith("conv2d") and flops >= 1e9
+    peak = PEAK["mfma_bf16"] / 6 if pieces else PEAK["mfma_bf16" if dtype == "bf16" else "mfma_f32"]
+    if flops > 0 and flops / byts > peak / PEAK["hbm"]:
+        roof = dict(bound="mfma", achieved=flops / (ms * 1e-3) / 1e12, peak=peak / 1e12, unit="TFLOP/s")
+        if pieces:
+            roof["frac_of_f32_unit"] = roof["achieved"] * 1e12 / PEAK["mfma_f32"]
+    else:
+        roof = dict(bound="hbm", achieved=byts / (ms * 1e-3) / 1e9, peak=PEAK["hbm"] / 1e9, unit="GB/s")
+    roof["frac"] = roof["achieved"] / roof["peak"]
+    elsewhere = [what for call, what in (("nsk_conv2d_dgrad_packed", "packing of the filters (nsk_conv2d_pack_filters)"),
+                                         ("nsk_conv2d_wgrad_partial", "addition of the partial sums (nsk_conv2d_wgrad_reduce)")) if call in names]
+    if elsewhere:
+        roof["not_in_launch"] = elsewhere
+    return roof
+
+
 def stored_traffic(workload, kind):
     """HBM bytes per launch of the dominant kernel from the committed rocprofv3 counter summary
     (profiles/traffic.txt: `<workload> <kernel kind> <bytes>`), or None if no line covers it."""
@@ -476,12 +502,8 @@ def main():
     value = batch * a.steps / (t1 - t0)
 
     kind, flops, byts = dominant
-    if flops > 0 and flops / byts > (PEAK["mfma_bf16" if wl["dtype"] == "bf16" else "mfma_f32"] / PEAK["hbm"]):
-        peak = PEAK["mfma_bf16" if wl["dtype"] == "bf16" else "mfma_f32"]
-        roof = dict(bound="mfma", achieved=flops / (dom_ms * 1e-3) / 1e12, peak=peak / 1e12, unit="TFLOP/s")
-    else:
-        roof = dict(bound="hbm", achieved=byts / (dom_ms * 1e-3) / 1e9, peak=PEAK["hbm"] / 1e9, unit="GB/s")
-    roof["frac"] = roof["achieved"] / roof["peak"]
+    names = [f.__name__ for f, _ in calls]
+    roof = roofline(wl["dtype"], kind, flops, byts, dom_ms, {names[i] for i in dom_idx})
     roof["traffic"] = stored_traffic(wl["name"], kind)
     roof["kernel"] = kind
     roof["launch_ms"] = dom_ms      # median over all launches of the group inside the timed steps: what `achieved` uses
@@ -490,8 +512,7 @@ def main():
     roof["launches_per_step"] = len(dom_idx)
     roof["algorithmic_per_launch"] = flops if roof["bound"] == "mfma" else byts
 
-    conv_flops = sum(c[1] for c in costs)
-    conv_ms = sum(per_call_ms[i] for i, c in enumerate(costs) if c[1] > 0)
+    conv_flops, conv_ms = conv_totals(names, costs, per_call_ms)
     if a.breakdown:
         print(f"{'call':<22}{'ms':>9}{'TFLOP/s':>10}{'GB/s':>9}", file=sys.stderr)
         for i, c in enumerate(costs):
