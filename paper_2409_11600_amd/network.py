@@ -35,6 +35,11 @@ def _to_device(a: np.ndarray, dtype, layout, device, is_filter=False):
     return t.contiguous().to(device=device, dtype=dtype)
 
 
+# Most bytes of partial sums that the layers of a network keep side by side until the end of the backward pass; layers beyond it use one workspace
+# after the other, as without the launch that adds them all up.
+SHARED_SUMS = 64 << 20
+
+
 class _Shared:
     """A place in the buffer that the layers of a backward pass share."""
     def __init__(self, offset):
@@ -173,7 +178,7 @@ class GpuNetwork:
                                                          ptr(self.beta[name]), ptr(self.act[u["dst"]]), ptr(self.mean[name]),
                                                          ptr(self.invstd[name]), None, None), "ws"))
 
-        filters, sums, shared_bytes = [], [], 0    # small layers: packed filters, partial sums of weight gradients
+        filters, sums, shared_bytes, sum_bytes = [], [], 0, 0    # small layers: packed filters, partial sums of weight gradients
 
         def at(nbytes):
             nonlocal shared_bytes
@@ -229,7 +234,8 @@ class GpuNetwork:
                                                           ptr(dy), ptr(self.dw[name]), 0), "side"))
             else:
                 pb = L.nsk_conv2d_wgrad_partial_bytes(ctypes.byref(cd))
-                if pb:
+                if pb and sum_bytes + pb <= SHARED_SUMS:
+                    sum_bytes += pb
                     part = at(pb)
                     bwd_plan.append((L.nsk_conv2d_wgrad_partial, (ctypes.byref(cd), ptr(self.act[u["src"]]), ptr(dy), part),
                                      "side, no workspace"))

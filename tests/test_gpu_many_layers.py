@@ -2,10 +2,11 @@
 kind of layer that they take, more layers than one launch holds, and the layers that they refuse."""
 import ctypes
 
+import numpy as np
 import pytest
 import torch
 
-from paper_2409_11600_amd import binding as B
+from paper_2409_11600_amd import binding as B, network
 from parity import torch_dtype
 
 pytestmark = pytest.mark.gpu
@@ -84,3 +85,27 @@ def test_layers_that_keep_their_own_calls():
         assert L.nsk_conv2d_dgrad_packed(ctypes.byref(d), ptr(t), ptr(t), ptr(t), 0, st) == B.NSK_ERR_UNSUPPORTED
     assert L.nsk_conv2d_pack_filters(0, None, st) == B.NSK_OK and L.nsk_conv2d_wgrad_reduce(0, None, 0, st) == B.NSK_OK
     assert L.nsk_conv2d_pack_filters(1, None, st) == B.NSK_ERR_NULL and L.nsk_conv2d_wgrad_reduce(-1, None, 0, st) == B.NSK_ERR_BAD_DESC
+
+
+def test_a_network_bounds_what_its_layers_keep(monkeypatch):
+    """Partial sums side by side up to a bound; the layers beyond it give the same gradients through the workspace."""
+    units = [dict(kind="conv_bn", name=f"u{i}", src="x" if i == 0 else f"a{i - 1}", dst=f"a{i}", C=32, K=32, R=3, S=3, stride=1, pad=1, relu=True, res=None) for i in range(6)]
+    wl = dict(name="six", dtype="bf16", input=(16, 32, 16, 16), units=units, output="a5")
+    g = np.random.default_rng(5)
+    normal = lambda *s: g.standard_normal(s, dtype=np.float32)
+    params = {u["name"]: dict(w=0.08 * normal(32, 32, 3, 3), gamma=1 + 0.1 * normal(32), beta=0.1 * normal(32)) for u in units}
+    tensors = dict(x=normal(*wl["input"]), params=params, dout=normal(16, 32, 16, 16))
+    d = B.conv_desc(wl["input"], (32, 3, 3), 1, 1, 1, B.NSK_BF16, B.NSK_NHWC)
+    one = B.lib().nsk_conv2d_wgrad_partial_bytes(ctypes.byref(d))
+    filters = 6 * ((B.lib().nsk_conv2d_packed_filter_bytes(ctypes.byref(d)) + 255) // 256 * 256)
+    assert one > 0 and one % 256 == 0 and network.SHARED_SUMS == 64 << 20
+    got = []
+    for most in (network.SHARED_SUMS, 3 * one, 0):
+        monkeypatch.setattr(network, "SHARED_SUMS", most)
+        net = network.GpuNetwork(wl, tensors)
+        assert net.shared.numel() == max(filters + min(6, most // one) * one, 16)
+        net.step()
+        torch.cuda.synchronize()
+        got.append({k: v.clone() for k, v in net.dw.items()})
+    for other in got[1:]:
+        assert all(torch.equal(other[k], got[0][k]) for k in got[0])
