@@ -26,7 +26,9 @@
  * Layouts and types.  Activations are NSK_NCHW (filters KCRS) or NSK_NHWC (filters KRSC),
  * dense and C-contiguous; NHWC is the fast path, NCHW is converted inside the call through
  * the workspace.  Element type NSK_F32 or NSK_BF16 (bfloat16, fp32 accumulation, round to
- * nearest even on store).  Filter gradients, batch-norm parameters, statistics and their
+ * nearest even on store).  Products of large NSK_F32 layers are made of three bf16 pieces of each operand, which hold all of its
+ * bits, without the products of two low pieces: a sum of one product is off by at most 2^-23 of it (an fp32 multiplication: 2^-24;
+ * 2.6e-8 rms in both), longer sums by less than on the fp32 unit; infinities, NaN and numbers of any size come out as there.  Filter gradients, batch-norm parameters, statistics and their
  * gradients are always float.  There is no convolution bias (batch-norm follows each one).
  *
  * Errors.  Every entry point returns an nsk_status_t and never throws or aborts.  Argument
