@@ -230,14 +230,12 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
 
 // The same sums in the same order for outputs that lie in dw as they lie in a partial sum (NHWC, one group): a lane takes
 // V consecutive outputs with one 8- or 16-byte load per split, so a wavefront's load is 512 or 1024 contiguous bytes.
-template <int V>
-__global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float *__restrict__ part, float *__restrict__ dw,
-                                                                int splits, long total, int accumulate)
+template <int V> __device__ inline void reduce_flat(const float *__restrict__ part, float *__restrict__ dw, int splits, long total, int block, int accumulate, float *lds)
 {
     typedef float fv __attribute__((ext_vector_type(V)));
-    __shared__ fv red[4][64];
+    fv(*red)[64] = (fv(*)[64])lds;
     const int g = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const long i = ((long)blockIdx.x * 64 + l) * V;      // total % V == 0: a vector is inside or outside as a whole
+    const long i = ((long)block * 64 + l) * V;           // total % V == 0: a vector is inside or outside as a whole
     fv s;
 #pragma unroll
     for (int e = 0; e < V; ++e) s[e] = 0.f;
@@ -251,6 +249,30 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float *__re
     fv *o = (fv *)(dw + i);
     *o = accumulate ? *o + s : s;
 }
+template <int V>
+__global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float *__restrict__ part, float *__restrict__ dw,
+                                                                int splits, long total, int accumulate)
+{
+    __shared__ __attribute__((aligned(16))) float lds[4 * 64 * V];
+    reduce_flat<V>(part, dw, splits, total, (int)blockIdx.x, accumulate, lds);
+}
+
+// sum of an output's splits in sixteen interleaved groups, those of one block's sixteen outputs together; valid in the first sixteen threads
+__device__ inline float sum_in_sixteen(const float *__restrict__ part, int splits, long step, long i, bool inside, float *lds)
+{
+    float(*red)[16] = (float(*)[16])lds;
+    const int g = threadIdx.x >> 4, j = threadIdx.x & 15;
+    float s = 0.f;
+    if (inside)
+#pragma unroll 4
+        for (int sp = g; sp < splits; sp += 16) s += part[(long)sp * step + i];
+    red[g][j] = s;
+    __syncthreads();
+    float r = 0.f;
+#pragma unroll
+    for (int q = 0; q < 16; q += 4) r += (red[q][j] + red[q + 1][j]) + (red[q + 2][j] + red[q + 3][j]);
+    return r;
+}
 
 // The same for small outputs with many splits (the 16- and 32-channel layers and the 3-channel stem of the CIFAR-sized
 // network: a few thousand outputs, hundreds of splits): 16 interleaved groups of splits instead of four, so that a lane's
@@ -259,20 +281,11 @@ __global__ __launch_bounds__(256) void wgrad_reduce16_kernel(const float *__rest
                                                               int splits, long step, int K, int ntaps, int C, int Cp, long sk, long st,
                                                               long sc, int accumulate)
 {
-    __shared__ float red[16][16];
+    __shared__ float lds[16 * 16];
     const long total = (long)K * ntaps * Cp;
-    const int g = threadIdx.x >> 4, j = threadIdx.x & 15;
-    const long i = (long)blockIdx.x * 16 + j;
-    float s = 0.f;
-    if (i < total)
-#pragma unroll 4
-        for (int sp = g; sp < splits; sp += 16) s += part[(long)sp * step + i];
-    red[g][j] = s;
-    __syncthreads();
-    if (g != 0 || i >= total) return;
-    float r = 0.f;
-#pragma unroll
-    for (int q = 0; q < 16; q += 4) r += (red[q][j] + red[q + 1][j]) + (red[q + 2][j] + red[q + 3][j]);
+    const long i = (long)blockIdx.x * 16 + (threadIdx.x & 15);
+    const float r = sum_in_sixteen(part, splits, step, i, i < total, lds);
+    if (threadIdx.x >= 16 || i >= total) return;
     const int c = (int)(i % Cp);
     const long rr = i / Cp;
     const int t = (int)(rr % ntaps);
@@ -290,25 +303,6 @@ struct ReduceMany {
     int count, accumulate;
 };
 static_assert(sizeof(ReduceMany) <= 4096, "kernel arguments");
-template <int V> __device__ inline void reduce_flat(const ReduceItem &a, int block, int accumulate, float *lds)
-{
-    typedef float fv __attribute__((ext_vector_type(V)));
-    fv(*red)[64] = (fv(*)[64])lds;
-    const int g = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const long i = ((long)block * 64 + l) * V;
-    fv s;
-#pragma unroll
-    for (int e = 0; e < V; ++e) s[e] = 0.f;
-    if (i < a.total)
-#pragma unroll 8
-        for (int sp = g; sp < a.splits; sp += 4) s += *(const fv *)(a.part + (long)sp * a.total + i);
-    red[g][l] = s;
-    __syncthreads();
-    if (g != 0 || i >= a.total) return;
-    s = (red[0][l] + red[1][l]) + (red[2][l] + red[3][l]);
-    fv *o = (fv *)(a.dw + i);
-    *o = accumulate ? *o + s : s;
-}
 __global__ __launch_bounds__(256) void wgrad_reduce_many_kernel(const ReduceMany m)
 {
     __shared__ __attribute__((aligned(16))) float lds[4 * 64 * 4];
@@ -316,21 +310,12 @@ __global__ __launch_bounds__(256) void wgrad_reduce_many_kernel(const ReduceMany
     while (k + 1 < m.count && (int)blockIdx.x >= m.e[k + 1].first_block) ++k;
     const ReduceItem &a = m.e[k];
     const int block = (int)blockIdx.x - a.first_block;
-    if (a.kind == 4) return reduce_flat<4>(a, block, m.accumulate, lds);
-    if (a.kind == 2) return reduce_flat<2>(a, block, m.accumulate, lds);
-    if (a.kind == 1) return reduce_flat<1>(a, block, m.accumulate, lds);
-    float(*red)[16] = (float(*)[16])lds;
-    const int g = threadIdx.x >> 4, j = threadIdx.x & 15, i = block * 16 + j;
-    float s = 0.f;
-    if (i < a.total)
-#pragma unroll 4
-        for (int sp = g; sp < a.splits; sp += 16) s += a.part[(long)sp * a.total + i];
-    red[g][j] = s;
-    __syncthreads();
-    if (g != 0 || i >= a.total) return;
-    float r = 0.f;
-#pragma unroll
-    for (int q = 0; q < 16; q += 4) r += (red[q][j] + red[q + 1][j]) + (red[q + 2][j] + red[q + 3][j]);
+    if (a.kind == 4) return reduce_flat<4>(a.part, a.dw, a.splits, a.total, block, m.accumulate, lds);
+    if (a.kind == 2) return reduce_flat<2>(a.part, a.dw, a.splits, a.total, block, m.accumulate, lds);
+    if (a.kind == 1) return reduce_flat<1>(a.part, a.dw, a.splits, a.total, block, m.accumulate, lds);
+    const int i = block * 16 + (int)(threadIdx.x & 15);
+    const float r = sum_in_sixteen(a.part, a.splits, a.total, i, i < a.total, lds);
+    if (threadIdx.x >= 16 || i >= a.total) return;
     a.dw[i] = m.accumulate ? a.dw[i] + r : r;
 }
 
