@@ -123,7 +123,7 @@ def _same(got, want, tol):
 
 
 @pytest.mark.parametrize("tile", [1, 2, 3, 4])
-@pytest.mark.parametrize("what", ["inf", "nan", "opposite", "largest", "smallest"])
+@pytest.mark.parametrize("what", ["inf", "nan", "opposite", "largest", "large sums", "smallest"])
 def test_operands_beyond_the_pieces(what, tile, nsk_env):
     nsk_env("NSK_IGEMM_TILE", str(tile))
     N, C, H, W, K = 2, 40, 12, 11, 72
@@ -139,6 +139,8 @@ def test_operands_beyond_the_pieces(what, tile, nsk_env):
     elif what == "largest":            # above the largest bf16; products of 1/4 stay in range
         x[0, 1, 1, 1], w[:, 1] = np.float32(3.4e38), 0.25
         dy[0, :, 1, 1] = 0.25
+    elif what == "large sums":         # 2^90, finite, but not times 2^48
+        x, w, dy = x * np.float32(2.0 ** 60), w * np.float32(2.0 ** 30), dy * np.float32(2.0 ** 30)
     else:                              # the last pieces would lie below the smallest bf16
         x, dy = x * np.float32(2.0 ** -112), dy * np.float32(2.0 ** -112)
     x64, w64, dy64 = x.astype(np.float64), w[:, :, 0, 0].astype(np.float64), dy.astype(np.float64)
@@ -151,8 +153,8 @@ def test_operands_beyond_the_pieces(what, tile, nsk_env):
         one = np.ones_like(dy64) if what == "smallest" else dy64      # (the product of both would not be a float)
         gone = to_gpu(one.astype(np.float32), "f32", LAY)
         dw_want = clip(np.einsum("nkhw,nchw->kc", one, x64))
-        _same(to_host(B.conv2d_wgrad(gx, gone, w.shape, 1, 0), LAY)[:, :, 0, 0], dw_want, 1e-5)
-        if what == "smallest":
+        _same(to_host(B.conv2d_wgrad(gx, gone, w.shape, 1, 0), LAY)[:, :, 0, 0], dw_want, 2e-6 if what == "smallest" else 1e-5)
+        if what in ("smallest", "large sums"):
             _same(to_host(B.conv2d_dgrad(gdy, gw, x.shape, 1, 0), LAY), np.einsum("nkhw,kc->nchw", dy64, w64), 2e-6)
 
 
